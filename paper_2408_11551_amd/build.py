@@ -39,6 +39,9 @@ UNITS = {
     "probes": ("probes.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
     "ablation": ("ablation.hip", []),
 }
+# the product call on torch tensors, a CPython extension beside the library it links (built by g++: host code only)
+CALL_SRC = os.path.join(CSRC, "torch_call.cpp")
+CALL_OUT = os.path.join(HERE, "_torch_call.so")
 HEADERS = ["kernels.h", "preprocess.h", "pack_layout.h", "spmm_rows.h", os.path.join("..", "..", "include", "smat.h"),
            os.path.join("..", "..", "include", "smat_bench.h"), "mfma_types.h"]
 
@@ -52,10 +55,10 @@ FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(OUT):
+    if not os.path.exists(OUT) or not os.path.exists(CALL_OUT):
         return True
-    built = os.path.getmtime(OUT)
-    deps = [os.path.join(CSRC, f) for f in sorted({src for src, _ in UNITS.values()}) + HEADERS] + [os.path.abspath(__file__)]
+    built = min(os.path.getmtime(OUT), os.path.getmtime(CALL_OUT))
+    deps = [CALL_SRC] + [os.path.join(CSRC, f) for f in sorted({src for src, _ in UNITS.values()}) + HEADERS] + [os.path.abspath(__file__)]
     return any(os.path.getmtime(d) > built for d in deps)
 
 
@@ -94,6 +97,21 @@ def _compile(item):
     return obj, usage
 
 
+def _build_call(verbose: bool) -> None:
+    """torch_call.cpp against the installed torch and the library just built."""
+    import importlib.util
+    import sysconfig
+    # the package's folder, without importing it
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(torch, "include"),
+           "-isystem", os.path.join(ROCM, "include"), CALL_SRC, "-o", CALL_OUT, "-L" + HERE, "-lsmat",
+           "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not is_stale():
         return OUT
@@ -115,6 +133,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    _build_call(verbose)
     if os.path.exists(EXAMPLE_SRC):
         cmd = [os.environ.get("CC", "gcc"), "-std=c11", "-O2", "-Wall", "-D__HIP_PLATFORM_AMD__", EXAMPLE_SRC,
                "-I" + os.path.join(HERE, "..", "include"), "-I" + os.path.join(ROCM, "include"),

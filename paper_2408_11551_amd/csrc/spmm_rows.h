@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <type_traits>
 
@@ -806,6 +807,10 @@ template <int DT>
 static const char* variant_name(int nt, int kw, int sw, int nch, int lmax)
 {
     static thread_local char buf[48];
+    static thread_local int known[5] = {0, 0, 0, 0, 0};        // the variant buf names: formatted only when it changes
+    const int asked[5] = {nt, kw, sw, nch, lmax};
+    if (std::equal(asked, asked + 5, known)) return buf;
+    std::copy(asked, asked + 5, known);
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
     snprintf(buf, sizeof(buf), "spmm_%s_n%dk%ds%dc%d_l%d", type, nt, kw, sw, nch, lmax);
     return buf;

@@ -60,7 +60,7 @@ def _load():
     # round, the process holds two runtimes, and the library's may not even find the device.)
     import torch  # noqa: F401
     path = lib_path()
-    if not os.path.exists(path):
+    if not os.path.exists(path) or not os.path.exists(_build.CALL_OUT):
         _build.build()                      # raises if hipcc is missing or the build fails
     lib = ctypes.CDLL(path)
     i64, vp, sz = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
@@ -120,6 +120,8 @@ def _load():
 
 
 _lib = _load()
+# smat_spmm on tensors without the marshalling (csrc/torch_call.cpp); it links the library loaded above
+from . import _torch_call  # noqa: E402
 
 
 def _check(status: int):
@@ -289,6 +291,12 @@ def smat_spmm(h, B, C, N=None, stream=None):
     types; the library does not know the tensor's type, the caller must match the handle);
     C: device tensor [M, >=N] of 4-byte elements (float32, int32 for "i8"); rows contiguous.
     Shapes, devices and element sizes are checked against the handle before the call (ValueError)."""
+    if stream is None:
+        done = _torch_call.spmm(h, B, C, N) if C is not None else NotImplemented
+        if done is C and C is not None:
+            return
+        if done is not NotImplemented:
+            _check(done)
     N, ldb, ldc = _check_device_operands(h, B, C, N)
     _check(_lib.smat_spmm(h, ctypes.c_void_p(B.data_ptr()), ldb, ctypes.c_void_p(C.data_ptr()), ldc, N,
                           _stream_ptr(stream)))
@@ -393,6 +401,11 @@ class SmatMatrix:
         return self
 
     def spmm(self, B, C=None, N=None):
+        done = _torch_call.spmm(self.handle, B, C, N)
+        if done is not NotImplemented:
+            if type(done) is int:
+                _check(done)
+            return done
         import torch
         if N is None:
             N = B.shape[1]
