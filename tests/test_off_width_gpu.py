@@ -1,0 +1,54 @@
+"""Rows of B, bases and widths that are off the load width of the per-row kernel: the last lane's columns end with
+column N - 1, nothing outside the N columns is read for or written to C.  Small integers: every result is exact."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2408_11551_amd as S                                        # noqa: E402
+from oracle import smat_ref as R                                        # noqa: E402
+from workloads import OCCUPANCY_SPEC, occupancy_csr, random_csr, recast  # noqa: E402
+
+
+def _exact(w, oracle_c, ldb, ldc, shift):
+    """One product with NaN around B and C; returns the variant's name."""
+    es = w.b_bits.dtype.itemsize
+    hole = 0x7E00 if w.dtype == "f16" else 0x7FC0 if w.dtype == "bf16" else 0x7F
+    # the K rows of B end with the buffer: a read past the last element would leave the tensor
+    flat = np.full(shift + (w.K - 1) * ldb + w.N, hole, dtype=w.b_bits.dtype)
+    for r in range(w.K):
+        flat[shift + r * ldb:shift + r * ldb + w.N] = w.b_bits[r]
+    flat = torch.from_numpy(flat.view(np.int16 if es == 2 else np.int8)).cuda()
+    b = torch.as_strided(flat, (w.K, w.N), (ldb, 1), shift)
+    integer = w.dtype == "i8"
+    c = torch.full((w.M, ldc), -77 if integer else float("nan"), dtype=torch.int32 if integer else torch.float32, device="cuda")
+    m = S.SmatMatrix(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, w.dtype, reorder=0, dense_tiles=-1)
+    S.smat_spmm(m.handle, b, c, w.N)
+    torch.cuda.synchronize()
+    name = S.smat_last_kernel()
+    m.close()
+    got = c.cpu().numpy()
+    pad = got[:, w.N:]
+    assert (pad == -77).all() if integer else np.isnan(pad).all()
+    ref, _ = oracle_c.spmm_ref_c(w.M, w.K, w.N, w.row_ptr, w.col_idx, R.decode_bits(w.a_bits, w.dtype), R.decode_bits(w.b_bits, w.dtype))
+    assert np.array_equal(got[:, :w.N].astype(np.float64), ref), (name, ldb, ldc, shift)
+    return name
+
+
+@pytest.mark.parametrize("N", [17, 33, 65, 129, 255, 257, 519])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "i8"])
+def test_widths_off_the_load_width(dtype, N, oracle_c):
+    # short rows (one wave each), the three row classes of one launch, and rows long enough to be split over waves
+    spec = random_csr(150, 170, N, 0.08, seed=N, values="smallint", b_dist="smallint")
+    mixed = occupancy_csr(OCCUPANCY_SPEC, K=16 * 64 + 5, N=N, seed=N)
+    sparse = occupancy_csr([OCCUPANCY_SPEC[5], [], OCCUPANCY_SPEC[7]], K=16 * 64 + 5, N=N, seed=N)
+    long = random_csr(48, 3000, N, 0.1, seed=N, values="smallint", b_dist="smallint")
+    names = set()
+    for w in (spec, mixed, sparse, long):
+        w = w if dtype == "f16" else recast(w, dtype)
+        for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1), (N + 3, N + 1, 2)):
+            names.add(_exact(w, oracle_c, ldb, ldc, shift))
+    assert any("_w" in n for n in names), names            # wider loads than the alignment allows did run
+    assert any("k1s" in n for n in names) and any("k1s" not in n for n in names), names
