@@ -751,36 +751,65 @@ char* scratch_area_of(const smat_handle* h, const void* stream)
     return h->scratch_base + (h->scratch_owner.size() - 1) * kTileScratchBytes;
 }
 
+// Fewest columns for which a B off 16-byte pieces is copied for the tile kernel: below, its tiles of 128
+// columns are mostly empty.
+constexpr int64_t kStageColumns = 32;
+
 // smat_spmm with the area for partial tiles given by the caller of this function.
 // hard_limit = 0: the launch is planned so that its partial tiles fit scratch_bytes.  Otherwise it
 // is planned as if the area were unlimited and refused when its partial tiles exceed hard_limit.
 smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t ldb, void* dC, int64_t ldc,
                                 int64_t N, void* stream, void* scratch, size_t scratch_bytes, size_t hard_limit = 0)
 {
-    // The dense path fetches B in 16-byte pieces (8 columns, or 16 for the 8-bit types) that must lie
-    // wholly inside or outside the N columns; otherwise every block row goes through the per-row kernel.  It also has to pay: a tile walks its steps at about
+    // The tile kernel fetches B in aligned 16-byte pieces (8 columns, or 16 for the 8-bit types) that lie wholly inside or
+    // outside the N columns.  A B that is not like that is copied to padded rows first, into the area of
+    // partial tiles; without one, or for few columns (a tile is 128 wide), it goes through the per-row kernel.
+    const int piece = 16 / h->elem_bytes;           // columns of B in 16 bytes
+    const bool in_pieces = N % piece == 0 && ldb % piece == 0 && reinterpret_cast<uintptr_t>(dB) % 16 == 0;
+    bool use_tiles = h->tiles.n > 0 && h->dense_mode >= 0 && (in_pieces || (scratch && N >= kStageColumns));
+    smat::DenseTiles tiles = h->tiles;
+    tiles.scratch = scratch;
+    tiles.scratch_bytes = scratch ? (hard_limit && in_pieces ? ~size_t{0} >> 1 : scratch_bytes) : 0;
+    // Columns staged at a time: all of them, or as many whole tiles as the area holds.
+    int64_t chunk = N, stage_ld = ldb;
+    if (use_tiles && !in_pieces) {
+        const int64_t line = 128 / h->elem_bytes;    // rows of the copy are whole cache lines
+        const int64_t fit = h->csr.K > 0 ? static_cast<int64_t>(scratch_bytes) / (h->csr.K * 128) * line : N;
+        if (fit >= N) {
+            stage_ld = (N + line - 1) / line * line;
+        } else {
+            const int64_t n_chunks = fit >= 128 ? (N + fit / 128 * 128 - 1) / (fit / 128 * 128) : 0;
+            if (n_chunks == 0) use_tiles = false;
+            else chunk = stage_ld = ((N + n_chunks - 1) / n_chunks + 127) / 128 * 128;
+        }
+        if (use_tiles) {
+            const size_t staged = align_up(static_cast<size_t>(h->csr.K) * static_cast<size_t>(stage_ld * h->elem_bytes));
+            tiles.scratch = static_cast<char*>(scratch) + staged;
+            tiles.scratch_bytes = scratch_bytes > staged ? scratch_bytes - staged : 0;
+        }
+    }
+    // It also has to pay: a tile walks its steps at about
     // 0.7 us each with little to overlap them, so few tiles leave most of the chip idle, while
     // the per-row kernel fetches every occupied column's row of B again for every block row but
     // spreads that over all compute units (about 10 TB/s of L1 fills).  Both estimates are
     // measured rates; the faster path is taken.
-    const int piece = 16 / h->elem_bytes;           // columns of B in 16 bytes
-    bool use_tiles = h->tiles.n > 0 && N % piece == 0 && ldb % piece == 0 && reinterpret_cast<uintptr_t>(dB) % 16 == 0;
-    if (h->dense_mode < 0) use_tiles = false;
-    smat::DenseTiles tiles = h->tiles;
-    tiles.scratch = scratch;
-    tiles.scratch_bytes = scratch ? (hard_limit ? ~size_t{0} >> 1 : scratch_bytes) : 0;
     if (use_tiles && h->dense_mode == 0) {
-        const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((N + 127) / 128);
-        const int ks = smat::dense_split(tiles, N);
-        const double step_us = h->elem_bytes == 1 ? 1.0 : 0.7;     // an 8-bit step covers twice the block columns
-        double t_tiles = std::ceil(n_tiles * ks / 256.0) * (tiles.mean_steps / ks * step_us + 4.0);
-        if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 4.0e6;     // partial tiles out and in again
+        double t_tiles = 0;
+        for (int64_t c0 = 0; c0 < N; c0 += chunk) {
+            const int64_t n = std::min(chunk, N - c0);
+            const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
+            const int ks = smat::dense_split(tiles, n);
+            const double step_us = h->elem_bytes == 1 ? 1.0 : 0.7;     // an 8-bit step covers twice the block columns
+            t_tiles += std::ceil(n_tiles * ks / 256.0) * (tiles.mean_steps / ks * step_us + 4.0);
+            if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 4.0e6;     // partial tiles out and in again
+            if (!in_pieces) t_tiles += 3.0 + 2.0 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes) / 4.0e6;  // the copy of B
+        }
         // (two bytes per value also for the 8-bit types: on block-dense rows the per-row kernel did not
         // get faster with them -- 35.6 us against 35 on the band workload -- while the tile kernel did)
         const double t_rows = static_cast<double>(h->dense_columns) * static_cast<double>((N + 15) / 16 * 16) * 2.0 / 10.0e6 + 4.0;
         use_tiles = t_tiles <= t_rows;
     }
-    if (use_tiles && hard_limit) {
+    if (use_tiles && hard_limit && in_pieces) {
         const size_t need = static_cast<size_t>(tiles.n) * static_cast<size_t>((N + 127) / 128) * 256 * 128 * 4 *
                             static_cast<size_t>(smat::dense_split(tiles, N));
         if (smat::dense_split(tiles, N) > 1 && need > hard_limit)
@@ -794,8 +823,16 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         if (h->dev_rest.n_order > 0)
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
         const char* dense_variant = "";
-        if (!e) e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &dense_variant);
-        name = std::string(dense_variant) + (h->dev_rest.n_order > 0 ? std::string("+") + variant : std::string());
+        for (int64_t c0 = 0; c0 < N && !e; c0 += chunk) {
+            const int64_t n = std::min(chunk, N - c0);
+            const char* b = static_cast<const char*>(dB) + c0 * h->elem_bytes;
+            if (!in_pieces) {
+                e = smat::launch_stage_b(b, ldb, h->csr.K, n, h->elem_bytes, scratch, stage_ld, stream);
+                b = static_cast<const char*>(scratch);
+            }
+            if (!e) e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
+        }
+        name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (h->dev_rest.n_order > 0 ? std::string("+") + variant : std::string());
         g_kernel = name.c_str();
     } else {
         e = smat::launch_spmm(h->dev, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);

@@ -99,8 +99,12 @@ int dense_split(const DenseTiles& t, int64_t N);
 // the address up.  Returns a hipError_t as int.
 int static_tile_scratch(void** area, size_t* bytes);
 
-// C rows of the dense super rows.  dtype is a smat_dtype_t.  Needs N and ldb multiples of the
-// elements in 16 bytes (8, or 16 for the 8-bit types) and B aligned to 16 bytes.
+// Copies `cols` columns of B (K rows) to rows of out_ld elements, a multiple of the elements in 16 bytes; what the last
+// piece of a row has beyond the columns is zero.  out: aligned to 16 bytes.
+int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem_bytes, void* out, int64_t out_ld, void* stream);
+
+// C rows of the dense super rows.  dtype is a smat_dtype_t.  Needs ldb a multiple of the elements in 16 bytes (8, or 16
+// for the 8-bit types), B aligned to 16 bytes, and N such a multiple too or B's rows padded with zeros to one.
 int launch_spmm_dense(const DeviceBcsr& d, const DenseTiles& t, int dtype, const void* B, int64_t ldb,
                       void* C, int64_t ldc, int64_t N, void* stream, const char** variant);
 

@@ -172,10 +172,11 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
     const int32_t* __restrict__ step_ptr = static_cast<const int32_t*>(steps_arg);
     const int full_steps = static_cast<int>(reinterpret_cast<uintptr_t>(steps_arg));
     constexpr uint32_t kElemBytes = Elem<DT>::ES;
-    // (the rows' padding after the last row is not B's.  Said to be wave-uniform in so many words: the compiler has
+    // (the rows' padding after the last row is not B's, but for a 16-byte piece that N ends in, which only a staged B
+    // has.  Said to be wave-uniform in so many words: the compiler has
     // computed it on the vector unit and then wrapped every load through the descriptor into a loop over lanes.)
     const uint32_t b_bytes = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
-        static_cast<int>(K > 0u ? (K - 1u) * ldb_bytes + static_cast<uint32_t>(N) * kElemBytes : 0u)));
+        static_cast<int>(K > 0u ? (K - 1u) * ldb_bytes + ((static_cast<uint32_t>(N) * kElemBytes + 15u) & ~15u) : 0u)));
     using Acc = typename Elem<DT>::Acc;
     using Out = typename Elem<DT>::Out;
     constexpr int ES = Elem<DT>::ES;               // bytes per element of A and B
@@ -227,7 +228,8 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
     // load e brings rows 4 wave .. 4 wave + 3 of block column e, lane l the piece l & 15 of row l >> 4.
     // 8-bit types: panel rows of 128 bytes, rows 16 c .. 16 c + 15 the step's c-th block column (c < 4);
     // the wave brings block column `wave`, load e its rows 8 e .. 8 e + 7, lane l the piece l & 7 of row l >> 3.
-    // (N is a multiple of the columns of a piece on this path, so a piece is all inside or all outside.)
+    // (A piece is all inside B or all outside: N is a multiple of the columns of a piece, or B is the staged copy, whose
+    // rows are padded with zeros to whole pieces.)
     const int st_row = ES == 2 ? 4 * wave + (lane >> 4) : lane >> 3;
     // The piece that lands at position p of row r of the panel is piece p ^ 2 (r & 3) ^ 8 (r / 8 & 1) of that
     // row of B (8-bit: p ^ (r / 2 & 7)).  LDS has 64 banks of four bytes and serves 32 lanes of an 8-byte read
@@ -638,12 +640,14 @@ void dense_reduce_kernel(DeviceBcsr d, DenseTiles t, int ks, Out* __restrict__ C
         const int e = static_cast<int>(blockIdx.z) * 1024 + j * 256 + static_cast<int>(threadIdx.x);
         const int row = e >> 5, c = (e & 31) * 4;
         const int64_t out_row = d.perm[static_cast<int64_t>(super) * 256 + row];
-        if (out_row < 0 || n0 + c >= N) continue;             // N is a multiple of 8 on this path
+        if (out_row < 0 || n0 + c >= N) continue;
         Out* dst = C + out_row * ldc + n0 + c;
-        if (vec_store) {
+        if (vec_store) {                                      // N is a multiple of 4
             *reinterpret_cast<V*>(dst) = v[j];
         } else {
-            dst[0] = v[j][0]; dst[1] = v[j][1]; dst[2] = v[j][2]; dst[3] = v[j][3];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (n0 + c + x < N) dst[x] = v[j][x];
         }
     }
 }
@@ -676,6 +680,49 @@ int static_tile_scratch(void** area, size_t* bytes)
     *area = addr[dev];
     *bytes = kStaticScratchBytes;
     return 0;
+}
+
+// The tile kernel brings B into LDS in 16-byte pieces, which have to be aligned and wholly inside or outside B.  For a B
+// that is not like that (N, ldb or the base off 16 bytes) `cols` columns of it are copied to rows of whole pieces first, the
+// last piece padded with zeros.  Bound by memory and small next to the product: each element is read once here and by
+// every super row there (4096 x 777 bytes: 4 us in front of a tile launch of 60 us; the per-row kernel, which needs no
+// copy, takes 128 us).  One thread per piece; the loads start anywhere (only a row's last piece goes element by element).
+template <int ES>
+__global__ __launch_bounds__(256)
+void stage_b_kernel(const uint8_t* __restrict__ B, uint32_t b_bytes, uint32_t ldb_bytes, uint32_t row_bytes, uint32_t pieces_per_row,
+                    uint32_t n_pieces, u32x4* __restrict__ out)
+{
+    const uint32_t p = blockIdx.x * 256u + threadIdx.x;
+    if (p >= n_pieces) return;
+    const uint32_t row = p / pieces_per_row, q = p - row * pieces_per_row;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(B), 0, static_cast<int>(b_bytes), kRsrcFlags);
+    const uint32_t at = row * ldb_bytes + 16u * q;
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    if (16u * q + 16u <= row_bytes) {
+        v = buf_load16(rsrc, at, 0u);
+    } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 16u / ES; ++e)
+            if (16u * q + ES * e < row_bytes) {
+                const uint32_t x = ES == 2 ? static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(rsrc, at + 2u * e, 0, 0))
+                                           : static_cast<uint8_t>(__builtin_amdgcn_raw_buffer_load_b8(rsrc, at + e, 0, 0));
+                v[ES * e / 4] |= x << (8u * (ES * e % 4u));
+            }
+    }
+    out[p] = v;
+}
+
+int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem_bytes, void* out, int64_t out_ld, void* stream)
+{
+    const uint32_t row_bytes = static_cast<uint32_t>(cols * elem_bytes), per_row = static_cast<uint32_t>(out_ld * elem_bytes / 16);
+    const uint32_t n = static_cast<uint32_t>(K) * per_row;
+    if (n == 0) return 0;
+    const uint32_t b_bytes = static_cast<uint32_t>(((K - 1) * ldb + cols) * elem_bytes), ldb_bytes = static_cast<uint32_t>(ldb * elem_bytes);
+    auto* kernel = elem_bytes == 2 ? stage_b_kernel<2> : stage_b_kernel<1>;
+    hipLaunchKernelGGL(kernel, dim3((n + 255u) / 256u), dim3(256), 0, static_cast<hipStream_t>(stream),
+                       static_cast<const uint8_t*>(B), b_bytes, ldb_bytes, row_bytes, per_row, n, static_cast<u32x4*>(out));
+    return static_cast<int>(hipGetLastError());
 }
 
 // How many workgroups share the steps of a 128-column tile: as many as fit the 256 compute
