@@ -116,7 +116,7 @@ Layout make_layout(const smat_handle& h)
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
     const size_t nbr = static_cast<size_t>(h.bcsr.nbr), n_e = static_cast<size_t>(h.bcsr.n_blocks);
     const size_t nnz = h.csr.col_idx.size();
-    l.perm = take(nbr * 16 * sizeof(int32_t));
+    l.perm = take((nbr + 15) / 16 * 256 * sizeof(int32_t));          // whole super rows: the tile kernel reads a last one that is not complete
     l.work = take(nbr * 16);
     l.work_rest = take(nbr * 16);
     l.slots = take(static_cast<size_t>(h.slots_units) * 32);
@@ -142,11 +142,14 @@ Layout make_layout(const smat_handle& h)
     return l;
 }
 
-// Decides which complete super rows (sixteen block rows) may go to the dense path and lays out
+// Decides which super rows (sixteen block rows; the last one may have fewer) may go to the dense path and lays out
 // their steps.  A super row qualifies when walking the union of its block columns wastes
 // little: at least 8 union columns, at least 35 % of the (block row, union column) grid
 // stored, and blocks whose columns are mostly occupied (>= 8 of 16 on average; blocks with a
-// few occupied columns are cheaper on the per-row path, which fetches only those rows of B).
+// few occupied columns are cheaper on the per-row path, which fetches only those rows of B).  A last super row
+// with less than sixteen block rows meets the same bounds, i.e. has at least six, and stores zeros for the rest: on the
+// per-row path a few long block rows leave most of the chip idle (seven of 128 packs, N = 777: 47 us
+// in front of a tile launch of 44).
 // With the option dense_tiles = -1 nothing qualifies.
 void plan_dense_tiles(smat_handle& h)
 {
@@ -162,8 +165,9 @@ void plan_dense_tiles(smat_handle& h)
     // take four per step (two MFMA 16x16x32 per output tile between barriers), so that a step moves
     // the same bytes and a tile has half as many of them
     const int64_t cps = h.elem_bytes == 1 ? 4 : 2;
-    for (int64_t s = 0; (s + 1) * 16 <= nbr; ++s) {
-        const int32_t lo = b.row_ptr[s * 16], hi = b.row_ptr[s * 16 + 16];
+    for (int64_t s = 0; s * 16 < nbr; ++s) {
+        const int n_rows = static_cast<int>(std::min<int64_t>(16, nbr - s * 16));
+        const int32_t lo = b.row_ptr[s * 16], hi = b.row_ptr[s * 16 + n_rows];
         if (hi - lo < 64) continue;
         uni.assign(b.col_idx.begin() + lo, b.col_idx.begin() + hi);
         std::sort(uni.begin(), uni.end());
@@ -176,12 +180,12 @@ void plan_dense_tiles(smat_handle& h)
         if (steps * 16 >= (int64_t{1} << 21) || h.dense_slots + static_cast<uint64_t>(steps) * 16 >= (uint64_t{1} << 31)) continue;
         h.dense_super.push_back(static_cast<int32_t>(s));
         h.dense_columns += occupied;
-        for (int j = 0; j < 16; ++j) h.row_dense[static_cast<size_t>(s * 16 + j)] = 1;
+        for (int j = 0; j < n_rows; ++j) h.row_dense[static_cast<size_t>(s * 16 + j)] = 1;
         for (int64_t q = 0; q < steps; ++q) {
             int32_t cols[4];
             for (int64_t e = 0; e < cps; ++e) cols[e] = cps * q + e < n_uni ? uni[cps * q + e] : 0x7FFFFFFF;
-            uint32_t rows = 0;
-            for (int j = 0; j < 16; ++j) {
+            uint32_t rows = 0xFFFFu & ~((1u << n_rows) - 1u);       // block rows past the end: present, all zeros
+            for (int j = 0; j < n_rows; ++j) {
                 const int32_t* first = b.col_idx.data() + b.row_ptr[s * 16 + j];
                 const int32_t* last = b.col_idx.data() + b.row_ptr[s * 16 + j + 1];
                 for (int64_t e = 0; e < cps; ++e)
@@ -511,7 +515,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         const size_t nbr = static_cast<size_t>(b.nbr), n_e = b.col_idx.size();
         const size_t M = static_cast<size_t>(h->csr.M), nnz = h->csr.col_idx.size();
 
-        std::vector<int32_t> perm_padded(nbr * 16, -1);
+        std::vector<int32_t> perm_padded((nbr + 15) / 16 * 256, -1);
         std::memcpy(perm_padded.data(), b.perm.data(), sizeof(int32_t) * M);
         // slot tables (pack_layout.h): the B row of every occupied column of every pack
         std::vector<uint32_t> slots(static_cast<size_t>(h->slots_units) * 8, static_cast<uint32_t>(h->csr.K));

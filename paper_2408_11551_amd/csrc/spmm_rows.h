@@ -899,7 +899,8 @@ static int launch_shape(const DeviceBcsr& d, const void* B, int64_t ldb, void* C
     // next (712 MB: 683 against 744 us).
     const bool whole_lines = 16 * NT * ES >= 256 && (ldb * ES) % 128 == 0 && reinterpret_cast<uintptr_t>(B) % 128 == 0;
     const bool one_slab = whole_lines && static_cast<double>(d.stream_bytes) <= 128.0e6;
-    const int sw = (wave_slabs >= 2 && !one_slab) ? 2 : 1;
+    // (and where one workgroup per slab does not even give every compute unit one: 7 rows, N = 777: 29 -> 16 us)
+    const int sw = (wave_slabs >= 2 && !one_slab && d.n_order * wave_slabs > 256) ? 2 : 1;
     const int64_t groups = d.n_order * ((wave_slabs + sw - 1) / sw);
     const double stream_us = (static_cast<double>(d.stream_bytes) + static_cast<double>(d.M) * N * 4.0 +
                               static_cast<double>(d.K) * N * ES) / 5.0e6;
@@ -984,13 +985,22 @@ static int launch_dtype(const DeviceBcsr& d, const void* B, int64_t ldb, void* C
     const double cost_off_dwords[17] = {0, 1.0, 2.1, 0, 2.1, 0, 0, 0, 2.4, 0, 0, 0, 0, 0, 0, 0, 2.6};
     constexpr int kWidest = 16 / ES;
     auto passes = [&](int nt) { return static_cast<double>((N + 16 * nt - 1) / (16 * nt)); };
+    // A few long block rows do not fill the chip: there the launch takes as long as one pass of a
+    // workgroup until about half of the compute units have one, so narrow passes, which make more workgroups, come
+    // first (7 rows of 128 packs, N = 777, e4m3: 46 us with loads of 16 bytes, 11.5 with 1 ... 4; bf16, 31 rows, N = 33:
+    // 13.2 -> 6.7, and at N = 777 8 elements stay the best).  Rows of up to 40 packs are short work for eight waves.
+    const bool few = d.mean_row_packs >= 40.0;
+    auto rounds = [&](int nt) {
+        const double groups = static_cast<double>(d.n_order) * passes(nt);
+        return few && groups < 128.0 ? 128.0 / static_cast<double>(d.n_order) : passes(nt);
+    };
     int aligned = 1, best = 1;         // the best width the alignment allows, and the best of all
-    double aligned_cost = passes(1), best_cost = passes(1);
+    double aligned_cost = rounds(1), best_cost = rounds(1);
     for (int nt = 2; nt <= kWidest && nt <= N; nt *= 2) {
         const bool fits = N % nt == 0 && ldb % nt == 0 && addr % (ES * nt) == 0;
         // (where N is no multiple of nt the last lane's load begins nt columns before the end of the row)
         const bool on_dwords = (ldb * ES) % 4 == 0 && addr % 4 == 0 && (N % nt == 0 || (N * ES) % 4 == 0);
-        const double cost = passes(nt) * (fits || on_dwords ? cost_on_dwords[ES * nt] : cost_off_dwords[ES * nt]);
+        const double cost = rounds(nt) * (fits || on_dwords ? cost_on_dwords[ES * nt] : cost_off_dwords[ES * nt]);
         if (fits && cost <= aligned_cost) { aligned = nt; aligned_cost = cost; }
         if (cost <= best_cost) { best = nt; best_cost = cost; }
     }
