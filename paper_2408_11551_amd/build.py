@@ -26,6 +26,7 @@ PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 UNITS = {
     "api": ("api.cpp", []),
     "preprocess": ("preprocess.cpp", []),
+    "workers": ("workers.cpp", []),
     "kernels": ("kernels.hip", PRELOAD),
     "kernels_narrow": ("kernels_narrow.hip", PRELOAD),
     # the per-row kernel for the 8-bit operand types: one object per type, built side by side
@@ -42,7 +43,7 @@ UNITS = {
 # the product call on torch tensors, a CPython extension beside the library it links (built by g++: host code only)
 CALL_SRC = os.path.join(CSRC, "torch_call.cpp")
 CALL_OUT = os.path.join(HERE, "_torch_call.so")
-HEADERS = ["kernels.h", "preprocess.h", "pack_layout.h", "spmm_rows.h", os.path.join("..", "..", "include", "smat.h"),
+HEADERS = ["kernels.h", "workers.h", "preprocess.h", "pack_layout.h", "spmm_rows.h", os.path.join("..", "..", "include", "smat.h"),
            os.path.join("..", "..", "include", "smat_bench.h"), "mfma_types.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

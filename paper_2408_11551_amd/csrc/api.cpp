@@ -35,8 +35,8 @@ struct smat_handle {
     // instruction multiplies.
     std::vector<int32_t> pack_ptr;       // [nbr+1] pack offsets per block row
     std::vector<int32_t> pack_first;     // [n_packs+1] first stored block of every pack
-    std::vector<int32_t> blk_pack;       // [n_blocks] pack of the block, counted inside its block row
-    std::vector<uint32_t> blk_meta;      // [n_blocks] column mask | occupied columns of the pack before the block << 16
+    smat::Buf<int32_t> blk_pack;         // [n_blocks] pack of the block, counted inside its block row
+    smat::Buf<uint32_t> blk_meta;        // [n_blocks] column mask | occupied columns of the pack before the block << 16
     std::vector<int32_t> order;          // [nbr] block rows in launch order
     // Row class: how many B-row loads per lane a pack of the block row needs at most (occupied
     // columns are dealt to four lane groups): 2, 4 or 8 -> class 0, 1, 2; class 3 is an entry row
@@ -151,7 +151,7 @@ Layout make_layout(const smat_handle& h)
 // per-row path a few long block rows leave most of the chip idle (seven of 128 packs, N = 777: 47 us
 // in front of a tile launch of 44).
 // With the option dense_tiles = -1 nothing qualifies.
-void plan_dense_tiles(smat_handle& h)
+void plan_dense_tiles(smat_handle& h, smat::Workers& workers)
 {
     const smat::Bcsr& b = h.bcsr;
     const int64_t nbr = b.nbr;
@@ -160,40 +160,57 @@ void plan_dense_tiles(smat_handle& h)
     h.dense_all_full = false;
     if (h.dense_mode < 0) return;
     h.dense_all_full = true;             // until a step says otherwise
-    std::vector<int32_t> uni;
     // block columns per step: the 32 k slots of a 16-bit MFMA are two block columns; the 8-bit types
     // take four per step (two MFMA 16x16x32 per output tile between barriers), so that a step moves
     // the same bytes and a tile has half as many of them
     const int64_t cps = h.elem_bytes == 1 ? 4 : 2;
-    for (int64_t s = 0; s * 16 < nbr; ++s) {
-        const int n_rows = static_cast<int>(std::min<int64_t>(16, nbr - s * 16));
-        const int32_t lo = b.row_ptr[s * 16], hi = b.row_ptr[s * 16 + n_rows];
-        if (hi - lo < 64) continue;
-        uni.assign(b.col_idx.begin() + lo, b.col_idx.begin() + hi);
-        std::sort(uni.begin(), uni.end());
-        uni.erase(std::unique(uni.begin(), uni.end()), uni.end());
-        int64_t occupied = 0;
-        for (int32_t k = lo; k < hi; ++k) occupied += __builtin_popcount(b.col_mask[k]);
-        const int64_t n_uni = static_cast<int64_t>(uni.size()), n_blk = hi - lo;
-        if (n_uni < 8 || n_blk * 20 < 7 * 16 * n_uni || occupied < 8 * n_blk) continue;
-        const int64_t steps = (n_uni + cps - 1) / cps;
+    // the super rows one by one: union of the block columns (empty: does not qualify), and per step the block rows present
+    struct Super { std::vector<int32_t> uni; std::vector<uint32_t> rows; int64_t occupied = 0; };
+    const int64_t n_super = (nbr + 15) / 16;
+    std::vector<Super> supers(static_cast<size_t>(n_super));
+    workers.ranges(n_super, 4, [&](int64_t s0, int64_t s1, int) {
+        for (int64_t s = s0; s < s1; ++s) {
+            const int n_rows = static_cast<int>(std::min<int64_t>(16, nbr - s * 16));
+            const int32_t lo = b.row_ptr[s * 16], hi = b.row_ptr[s * 16 + n_rows];
+            if (hi - lo < 64) continue;
+            const int64_t n_blk = hi - lo;
+            int64_t occupied = 0;
+            for (int32_t k = lo; k < hi; ++k) occupied += __builtin_popcount(b.col_mask[k]);
+            if (occupied < 8 * n_blk) continue;
+            std::vector<int32_t> uni(b.col_idx.begin() + lo, b.col_idx.begin() + hi);
+            std::sort(uni.begin(), uni.end());
+            uni.erase(std::unique(uni.begin(), uni.end()), uni.end());
+            const int64_t n_uni = static_cast<int64_t>(uni.size());
+            if (n_uni < 8 || n_blk * 20 < 7 * 16 * n_uni) continue;
+            Super& out = supers[static_cast<size_t>(s)];
+            // block rows past the end of the matrix: present, all zeros
+            out.rows.assign(static_cast<size_t>((n_uni + cps - 1) / cps), 0xFFFFu & ~((1u << n_rows) - 1u));
+            for (int j = 0; j < n_rows; ++j) {
+                size_t at = 0;
+                for (int32_t k = b.row_ptr[s * 16 + j]; k < b.row_ptr[s * 16 + j + 1]; ++k) {
+                    while (uni[at] < b.col_idx[k]) ++at;       // both ascend, and every block column is in the union
+                    out.rows[at / static_cast<size_t>(cps)] |= 1u << j;
+                }
+            }
+            out.occupied = occupied;
+            out.uni.swap(uni);
+        }
+    });
+    for (int64_t s = 0; s < n_super; ++s) {
+        const Super& sup = supers[static_cast<size_t>(s)];
+        const int64_t n_uni = static_cast<int64_t>(sup.uni.size()), steps = static_cast<int64_t>(sup.rows.size());
+        if (n_uni == 0) continue;
         if (steps * 16 >= (int64_t{1} << 21) || h.dense_slots + static_cast<uint64_t>(steps) * 16 >= (uint64_t{1} << 31)) continue;
         h.dense_super.push_back(static_cast<int32_t>(s));
-        h.dense_columns += occupied;
-        for (int j = 0; j < n_rows; ++j) h.row_dense[static_cast<size_t>(s * 16 + j)] = 1;
+        h.dense_columns += sup.occupied;
+        for (int64_t j = s * 16; j < std::min<int64_t>(nbr, s * 16 + 16); ++j) h.row_dense[static_cast<size_t>(j)] = 1;
         for (int64_t q = 0; q < steps; ++q) {
-            int32_t cols[4];
-            for (int64_t e = 0; e < cps; ++e) cols[e] = cps * q + e < n_uni ? uni[cps * q + e] : 0x7FFFFFFF;
-            uint32_t rows = 0xFFFFu & ~((1u << n_rows) - 1u);       // block rows past the end: present, all zeros
-            for (int j = 0; j < n_rows; ++j) {
-                const int32_t* first = b.col_idx.data() + b.row_ptr[s * 16 + j];
-                const int32_t* last = b.col_idx.data() + b.row_ptr[s * 16 + j + 1];
-                for (int64_t e = 0; e < cps; ++e)
-                    if (std::binary_search(first, last, cols[e])) rows |= 1u << j;
+            for (int64_t e = 0; e < cps; ++e) {
+                const int32_t col = cps * q + e < n_uni ? sup.uni[static_cast<size_t>(cps * q + e)] : 0x7FFFFFFF;
+                h.step_cols.push_back(col);
+                if (col != cps * q + e) h.dense_all_full = false;
             }
-            for (int64_t e = 0; e < cps; ++e) h.step_cols.push_back(cols[e]);
-            for (int64_t e = 0; e < cps; ++e)
-                if (cols[e] != cps * q + e) h.dense_all_full = false;
+            const uint32_t rows = sup.rows[static_cast<size_t>(q)];
             if (rows != 0xFFFFu) h.dense_all_full = false;
             h.step_rows.push_back(rows);
             h.step_base.push_back(static_cast<uint32_t>(h.dense_slots));
@@ -229,14 +246,13 @@ void entry_order(const smat_handle& h, size_t br, std::vector<uint64_t>& items)
 }
 
 // Cuts every block row into packs and derives the row classes (pack_layout.h).
-void plan_packs(smat_handle& h)
+void plan_packs(smat_handle& h, smat::Workers& workers)
 {
     const smat::Bcsr& b = h.bcsr;
     const size_t nbr = static_cast<size_t>(b.nbr), n_e = b.col_idx.size();
     h.pack_ptr.assign(nbr + 1, 0);
-    h.pack_first.clear();
-    h.blk_pack.assign(n_e, 0);
-    h.blk_meta.assign(n_e, 0);
+    h.blk_pack.resize(n_e);
+    h.blk_meta.resize(n_e);
     h.row_class.assign(nbr, 0);
     h.slots_off.assign(nbr + 1, 0);
     h.vals_off.assign(nbr + 1, 0);
@@ -244,29 +260,28 @@ void plan_packs(smat_handle& h)
     h.value_bytes = 0;
     h.b_rows = 0;
     h.row_b_rows.assign(nbr, 0);
-    // Cuts block row br into packs of occupied columns; with `record` the per-block records of
-    // the bind-time scatter are written.  Returns the number of packs.
-    struct Cut { int64_t packs, occupied; int worst; };
-    auto cut_row = [&](size_t br, bool record) {
-        int in_pack = 0, worst = 0;
-        int64_t pack = -1, occupied = 0;
-        for (int32_t s = b.row_ptr[br]; s < b.row_ptr[br + 1]; ++s) {
-            const int cols = __builtin_popcount(b.col_mask[s]);
-            if (pack < 0 || in_pack + cols > smat::kPackColumns) {
-                ++pack;
-                in_pack = 0;
-                if (record) h.pack_first.push_back(s);
-            }
-            if (record) {
+    // Cuts every block row into packs of occupied columns and writes the per-block records of the bind-time scatter.
+    struct Cut { int64_t packs, occupied, nnz; int worst; };
+    std::vector<Cut> cuts(nbr);
+    workers.ranges(b.nbr, 64, [&](int64_t b0, int64_t b1, int) {
+        for (int64_t br = b0; br < b1; ++br) {
+            int in_pack = 0, worst = 0;
+            int64_t pack = -1, occupied = 0;
+            for (int32_t s = b.row_ptr[br]; s < b.row_ptr[br + 1]; ++s) {
+                const int cols = __builtin_popcount(b.col_mask[s]);
+                if (pack < 0 || in_pack + cols > smat::kPackColumns) {
+                    ++pack;
+                    in_pack = 0;
+                }
                 h.blk_pack[static_cast<size_t>(s)] = static_cast<int32_t>(pack);
                 h.blk_meta[static_cast<size_t>(s)] = static_cast<uint32_t>(b.col_mask[s]) | static_cast<uint32_t>(in_pack) << 16;
+                in_pack += cols;
+                occupied += cols;
+                worst = std::max(worst, in_pack);
             }
-            in_pack += cols;
-            occupied += cols;
-            worst = std::max(worst, in_pack);
+            cuts[static_cast<size_t>(br)] = Cut{pack + 1, occupied, block_row_nnz(h, static_cast<size_t>(br)), worst};
         }
-        return Cut{pack + 1, occupied, worst};
-    };
+    });
     // How many stored entries per occupied column a block row of the densest class may have
     // and still be kept by entry (pack_layout.h).  A row kept by entry gathers one row of B per
     // entry instead of one per column but streams 2 bytes per entry instead of 32 per column.
@@ -275,34 +290,28 @@ void plan_packs(smat_handle& h)
     // 1.15 entries per column (1.08: by entry up to 6 % faster, 1.33: 10-20 % slower); once they
     // do not (290 MB), by entry is 11-22 % faster even at 1.33.
     int64_t by_column_bytes = 0;
-    for (size_t br = 0; br < nbr; ++br) {
-        const Cut c = cut_row(br, false);
+    for (const Cut& c : cuts) {
         const int cls = c.worst <= 8 ? 0 : (c.worst <= 16 ? 1 : 2);
         by_column_bytes += (c.packs * 64 * h.elem_bytes) << (cls + 1);
     }
     const int64_t entry_limit_16ths = by_column_bytes > 192000000 ? 24 : 18;      // 3/2 or 9/8
     uint64_t units = 0, vunits = 0;
+    int64_t packs = 0;
     for (size_t br = 0; br < nbr; ++br) {
-        const int32_t s1 = b.row_ptr[br + 1];
-        const Cut c = cut_row(br, true);
-        const int64_t occupied = c.occupied;
+        const Cut& c = cuts[br];
         int cls = c.worst <= 8 ? 0 : (c.worst <= 16 ? 1 : 2);
         int64_t n_packs = c.packs;
-        const int64_t nnz = block_row_nnz(h, br);
-        if (cls == 2 && nnz * 16 <= occupied * entry_limit_16ths) {
+        if (cls == 2 && c.nnz * 16 <= c.occupied * entry_limit_16ths) {
             // entry row: packs of 32 stored entries; the per-block records above are not used for it
             cls = smat::kEntryClass;
-            const int64_t by_entry = (nnz + 31) / 32;
-            for (int64_t x = n_packs; x < by_entry; ++x) h.pack_first.push_back(s1);
-            for (int64_t x = by_entry; x < n_packs; ++x) h.pack_first.pop_back();
-            n_packs = by_entry;
+            n_packs = (c.nnz + 31) / 32;
             h.value_bytes += n_packs * 32 * h.elem_bytes;
-            h.b_rows += nnz;
-            h.row_b_rows[br] = static_cast<int32_t>(nnz);
+            h.b_rows += c.nnz;
+            h.row_b_rows[br] = static_cast<int32_t>(c.nnz);
         } else {
             h.value_bytes += (n_packs * 64 * h.elem_bytes) << (cls + 1);
-            h.b_rows += occupied;
-            h.row_b_rows[br] = static_cast<int32_t>(occupied);
+            h.b_rows += c.occupied;
+            h.row_b_rows[br] = static_cast<int32_t>(c.occupied);
         }
         h.row_class[br] = static_cast<int8_t>(cls);
         h.max_class = std::max(h.max_class, cls);
@@ -311,9 +320,24 @@ void plan_packs(smat_handle& h)
         units += static_cast<uint64_t>(n_packs) * static_cast<uint64_t>(smat::pack_units(cls));
         vunits += static_cast<uint64_t>(n_packs) * static_cast<uint64_t>(smat::pack_value_units(cls, h.elem_bytes));
         if (units >= (uint64_t{1} << 32) || vunits >= (uint64_t{1} << 32)) throw std::length_error("slot table too large");
-        h.pack_ptr[br + 1] = static_cast<int32_t>(h.pack_first.size());
+        packs += n_packs;
+        h.pack_ptr[br + 1] = static_cast<int32_t>(packs);
     }
-    h.pack_first.push_back(static_cast<int32_t>(n_e));
+    h.pack_first.assign(static_cast<size_t>(packs) + 1, static_cast<int32_t>(n_e));
+    workers.ranges(b.nbr, 64, [&](int64_t b0, int64_t b1, int) {
+        for (int64_t br = b0; br < b1; ++br) {
+            int32_t* first = h.pack_first.data() + h.pack_ptr[static_cast<size_t>(br)];
+            const int32_t n_packs = h.pack_ptr[static_cast<size_t>(br) + 1] - h.pack_ptr[static_cast<size_t>(br)];
+            // (an entry row's packs are not runs of blocks: only their number counts)
+            if (h.row_class[static_cast<size_t>(br)] == smat::kEntryClass) { std::fill(first, first + n_packs, b.row_ptr[br + 1]); continue; }
+            int32_t last = -1;
+            for (int32_t s = b.row_ptr[br]; s < b.row_ptr[br + 1]; ++s) {
+                const int32_t pack = h.blk_pack[static_cast<size_t>(s)];
+                if (pack != last) first[pack] = s;
+                last = pack;
+            }
+        }
+    });
     h.slots_off[nbr] = static_cast<uint32_t>(units);
     h.vals_off[nbr] = static_cast<uint32_t>(vunits);
     h.slots_units = units;
@@ -391,7 +415,8 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
             if (row_ptr[r + 1] < row_ptr[r]) return fail(SMAT_ERR_BAD_CSR, "row_ptr decreases at row " + std::to_string(r));
         const int64_t nnz = row_ptr[M];
         if (nnz > 0 && (!col_idx || !vals)) return fail(SMAT_ERR_INVALID_ARG, "col_idx or vals is NULL");
-        const std::string bad = smat::validate_csr(M, K, row_ptr, col_idx);
+        smat::Workers workers;
+        const std::string bad = smat::validate_csr(M, K, row_ptr, col_idx, workers);
         if (!bad.empty()) return fail(SMAT_ERR_BAD_CSR, bad);
 
         std::unique_ptr<smat_handle> h(new smat_handle());      // freed if anything below throws
@@ -402,22 +427,26 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
         h->csr.M = M;
         h->csr.K = K;
         h->csr.row_ptr.assign(row_ptr, row_ptr + M + 1);
-        h->csr.col_idx.assign(col_idx, col_idx + nnz);
-        if (narrow)      // kept as 16-bit words, value in the low byte
-            h->csr.vals.assign(static_cast<const uint8_t*>(vals), static_cast<const uint8_t*>(vals) + nnz);
-        else
-            h->csr.vals.assign(static_cast<const uint16_t*>(vals), static_cast<const uint16_t*>(vals) + nnz);
-        smat::build_bcsr(h->csr, o.reorder != 0, o.tau_permille, h->bcsr);
+        h->csr.col_idx.resize(static_cast<size_t>(nnz));
+        h->csr.vals.resize(static_cast<size_t>(nnz));
+        workers.ranges(nnz, 1 << 18, [&](int64_t p0, int64_t p1, int) {
+            std::copy(col_idx + p0, col_idx + p1, h->csr.col_idx.begin() + p0);
+            if (narrow)      // kept as 16-bit words, value in the low byte
+                std::copy(static_cast<const uint8_t*>(vals) + p0, static_cast<const uint8_t*>(vals) + p1, h->csr.vals.begin() + p0);
+            else
+                std::copy(static_cast<const uint16_t*>(vals) + p0, static_cast<const uint16_t*>(vals) + p1, h->csr.vals.begin() + p0);
+        });
+        smat::build_bcsr(h->csr, o.reorder != 0, o.tau_permille, h->bcsr, workers);
         if (o.reorder == 2) {
-            h->cols_permuted = smat::reorder_columns(h->csr, o.tau_permille, h->bcsr);
+            h->cols_permuted = smat::reorder_columns(h->csr, o.tau_permille, h->bcsr, workers);
             if (h->cols_permuted) h->dense_mode = -1;
         }
         try {
-            plan_packs(*h);
+            plan_packs(*h, workers);
         } catch (const std::length_error& e) {
             return fail(SMAT_ERR_UNSUPPORTED, e.what());
         }
-        plan_dense_tiles(*h);
+        plan_dense_tiles(*h, workers);
         *out = h.release();
         return SMAT_OK;
     } catch (const std::bad_alloc&) {

@@ -13,6 +13,11 @@
 // intersection and could not have merged.  The result is the same permutation
 // the row-by-row scan gives.  (The index and the counters are kept per distinct
 // row pattern, not per row: rows with the same pattern have the same counter.)
+//
+// Most seeds of a graph or a uniformly random matrix end up alone, and finding that out by counting is nearly all the
+// time there is.  Whether a pattern can merge with any other at all is a question about pairs, not about the
+// state of the scan, so once the scan has shown that the clusters stay small it is answered for all remaining
+// patterns at once, on several threads (partners_of); seeds without a partner are then placed without counting.
 #include "preprocess.h"
 
 #include <algorithm>
@@ -20,35 +25,63 @@
 
 namespace smat {
 
-std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx)
+std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx, Workers& workers)
 {
-    if (row_ptr[0] != 0) return "row_ptr[0] must be 0";
-    for (int64_t r = 0; r < M; ++r) {
-        if (row_ptr[r + 1] < row_ptr[r]) return "row_ptr decreases at row " + std::to_string(r);
+    std::atomic<int64_t> first_bad{M};
+    auto fault = [&](int64_t r) -> const char* {
         int64_t prev = -1;
         for (int64_t p = row_ptr[r]; p < row_ptr[r + 1]; ++p) {
             const int64_t c = col_idx[p];
-            if (c < 0 || c >= K) return "column out of range in row " + std::to_string(r);
-            if (c <= prev) return "columns not strictly ascending in row " + std::to_string(r);
+            if (c < 0 || c >= K) return "column out of range in row ";
+            if (c <= prev) return "columns not strictly ascending in row ";
             prev = c;
         }
-    }
-    return std::string();
+        return nullptr;
+    };
+    workers.ranges(M, 4096, [&](int64_t r0, int64_t r1, int) {
+        for (int64_t r = r0; r < r1; ++r)
+            if (fault(r)) {
+                int64_t seen = first_bad.load();
+                while (r < seen && !first_bad.compare_exchange_weak(seen, r)) {}
+                return;
+            }
+    });
+    const int64_t r = first_bad.load();
+    return r < M ? fault(r) + std::to_string(r) : std::string();
 }
 
-void block_patterns(const Csr& a, std::vector<int64_t>& pat_ptr, std::vector<int32_t>& pat_idx)
+// Prefix sums in place: ptr[0] = 0, ptr[i + 1] holds the count of item i on entry.
+template <typename P>
+static void prefix_sums(P& ptr)
 {
-    pat_ptr.assign(a.M + 1, 0);
-    pat_idx.clear();
-    pat_idx.reserve(a.col_idx.size() / 2 + 16);
-    for (int64_t r = 0; r < a.M; ++r) {
+    for (size_t i = 1; i < ptr.size(); ++i) ptr[i] += ptr[i - 1];
+}
+
+void block_patterns(const Csr& a, Patterns& pat, Workers& workers)
+{
+    pat.ptr.resize(static_cast<size_t>(a.M) + 1);
+    pat.ptr[0] = 0;
+    auto walk = [&](int64_t r, int32_t* out) {
         int32_t last = -1;
+        int64_t n = 0;
         for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p) {
             const int32_t bc = a.col_idx[p] / kBlock;     // columns ascend, so block columns do too
-            if (bc != last) { pat_idx.push_back(bc); last = bc; }
+            if (bc != last) {
+                if (out) out[n] = bc;
+                ++n;
+                last = bc;
+            }
         }
-        pat_ptr[r + 1] = static_cast<int64_t>(pat_idx.size());
-    }
+        return n;
+    };
+    workers.ranges(a.M, 2048, [&](int64_t r0, int64_t r1, int) {
+        for (int64_t r = r0; r < r1; ++r) pat.ptr[r + 1] = walk(r, nullptr);
+    });
+    prefix_sums(pat.ptr);
+    pat.idx.resize(static_cast<size_t>(pat.ptr[a.M]));
+    workers.ranges(a.M, 2048, [&](int64_t r0, int64_t r1, int) {
+        for (int64_t r = r0; r < r1; ++r) walk(r, pat.idx.data() + pat.ptr[r]);
+    });
 }
 
 namespace {
@@ -111,110 +144,223 @@ private:
 // one mesh node) have the same intersection with any union, so the counting is done once per
 // distinct pattern ("class"), not once per row: the inverted index lists classes, and a class
 // whose count makes it a candidate puts all its unclustered rows ahead of the scan into the
-// candidate set.
+// candidate set.  Classes are numbered by the length of their pattern, then by their first row.
 struct PatternClasses {
-    std::vector<int32_t> class_of;     // [M]
-    std::vector<int32_t> first_row;    // [n] a row that carries the class's pattern
-    std::vector<int64_t> member_ptr;   // [n+1]
-    std::vector<int32_t> members;      // rows of every class, ascending
+    Buf<int32_t> class_of;             // [M]
+    Buf<int32_t> first_row;            // [n] the first row that carries the class's pattern
+    Buf<int32_t> len;                  // [n] length of the pattern
+    Buf<int64_t> member_ptr;           // [n+1]
+    Buf<int32_t> members;              // rows of every class, ascending
+    int64_t size() const { return static_cast<int64_t>(first_row.size()); }
 };
 
-PatternClasses group_equal_patterns(int64_t M, const std::vector<int64_t>& pat_ptr, const std::vector<int32_t>& pat_idx)
+static PatternClasses group_equal_patterns(int64_t M, const Patterns& pat, Workers& workers)
 {
-    std::vector<uint64_t> hash(M);
-    for (int64_t r = 0; r < M; ++r) {
-        uint64_t x = 0x9E3779B97F4A7C15ull ^ static_cast<uint64_t>(pat_ptr[r + 1] - pat_ptr[r]);
-        for (int64_t q = pat_ptr[r]; q < pat_ptr[r + 1]; ++q) {
-            x ^= static_cast<uint64_t>(static_cast<uint32_t>(pat_idx[q])) + 0x9E3779B97F4A7C15ull + (x << 6) + (x >> 2);
-            x *= 0xFF51AFD7ED558CCDull;
+    auto len_of = [&](int64_t r) { return static_cast<int32_t>(pat.ptr[r + 1] - pat.ptr[r]); };
+    Buf<uint64_t> hash(static_cast<size_t>(M));
+    workers.ranges(M, 4096, [&](int64_t r0, int64_t r1, int) {
+        for (int64_t r = r0; r < r1; ++r) {
+            uint64_t x = 0x9E3779B97F4A7C15ull ^ static_cast<uint64_t>(pat.ptr[r + 1] - pat.ptr[r]);
+            for (int64_t q = pat.ptr[r]; q < pat.ptr[r + 1]; ++q) {
+                x ^= static_cast<uint64_t>(static_cast<uint32_t>(pat.idx[q])) + 0x9E3779B97F4A7C15ull + (x << 6) + (x >> 2);
+                x *= 0xFF51AFD7ED558CCDull;
+            }
+            hash[r] = x;
         }
-        hash[r] = x;
-    }
+    });
     auto same = [&](int32_t a, int32_t b) {
-        const int64_t la = pat_ptr[a + 1] - pat_ptr[a];
-        return la == pat_ptr[b + 1] - pat_ptr[b] &&
-               std::equal(pat_idx.begin() + pat_ptr[a], pat_idx.begin() + pat_ptr[a + 1], pat_idx.begin() + pat_ptr[b]);
+        return hash[a] == hash[b] && len_of(a) == len_of(b) &&
+               std::equal(pat.idx.begin() + pat.ptr[a], pat.idx.begin() + pat.ptr[a + 1], pat.idx.begin() + pat.ptr[b]);
     };
-    auto less = [&](int32_t a, int32_t b) {            // a total order in which equal patterns are neighbours
-        if (hash[a] != hash[b]) return hash[a] < hash[b];
-        const auto a0 = pat_idx.begin() + pat_ptr[a], a1 = pat_idx.begin() + pat_ptr[a + 1];
-        const auto b0 = pat_idx.begin() + pat_ptr[b], b1 = pat_idx.begin() + pat_ptr[b + 1];
-        if (std::lexicographical_compare(a0, a1, b0, b1)) return true;
-        if (std::lexicographical_compare(b0, b1, a0, a1)) return false;
-        return a < b;                                   // same pattern: by row, so that members ascend
-    };
-    std::vector<int32_t> by_pattern(M);
-    std::iota(by_pattern.begin(), by_pattern.end(), 0);
-    std::sort(by_pattern.begin(), by_pattern.end(), less);
-    PatternClasses pc;
-    pc.class_of.assign(M, 0);
-    pc.member_ptr.push_back(0);
-    for (int64_t k = 0; k < M; ++k) {
-        const int32_t r = by_pattern[k];
-        if (k == 0 || !same(by_pattern[k - 1], r)) {
-            if (k > 0) pc.member_ptr.push_back(static_cast<int64_t>(pc.members.size()));
-            pc.first_row.push_back(r);
+    // first row with the same pattern, by open addressing; each piece has the rows of some of the top hash bits
+    Buf<int32_t> rep(static_cast<size_t>(M));
+    const int64_t shards = M < 8192 ? 1 : 64;
+    workers.ranges(shards, 1, [&](int64_t s0, int64_t s1, int) {
+        for (int64_t shard = s0; shard < s1; ++shard) {
+            auto mine = [&](int64_t r) { return shards == 1 || static_cast<int64_t>(hash[r] >> 58) == shard; };
+            int64_t n = 0;
+            for (int64_t r = 0; r < M; ++r) n += mine(r) ? 1 : 0;
+            size_t mask = 15;
+            while (mask < static_cast<size_t>(2 * n)) mask = 2 * mask + 1;
+            std::vector<int32_t> table(mask + 1, -1);
+            for (int64_t r = 0; r < M; ++r) {
+                if (!mine(r)) continue;
+                size_t at = static_cast<size_t>(hash[r]) & mask;
+                while (table[at] >= 0 && !same(table[at], static_cast<int32_t>(r))) at = (at + 1) & mask;
+                if (table[at] < 0) table[at] = static_cast<int32_t>(r);
+                rep[r] = table[at];
+            }
         }
-        pc.class_of[r] = static_cast<int32_t>(pc.first_row.size()) - 1;
-        pc.members.push_back(r);                        // ascending inside a class: ties are ordered by row
+    });
+    PatternClasses pc;
+    std::vector<int64_t> of_len(1, 0);           // by length: how many, then where the next one goes
+    int64_t n = 0;
+    for (int64_t r = 0; r < M; ++r) {
+        if (rep[r] != r) continue;
+        const size_t len = static_cast<size_t>(len_of(r));
+        if (len + 2 > of_len.size()) of_len.resize(len + 2, 0);
+        ++of_len[len + 1];
+        ++n;
     }
-    pc.member_ptr.push_back(static_cast<int64_t>(pc.members.size()));
-    if (M == 0) pc.member_ptr.assign(1, 0);
+    prefix_sums(of_len);
+    pc.first_row.resize(static_cast<size_t>(n));
+    for (int64_t r = 0; r < M; ++r)
+        if (rep[r] == r) pc.first_row[of_len[len_of(r)]++] = static_cast<int32_t>(r);
+    pc.class_of.resize(static_cast<size_t>(M));
+    pc.len.resize(static_cast<size_t>(n));
+    pc.member_ptr.assign(static_cast<size_t>(n) + 1, 0);
+    pc.members.resize(static_cast<size_t>(M));
+    for (int64_t k = 0; k < n; ++k) {
+        pc.len[k] = len_of(pc.first_row[k]);
+        pc.class_of[pc.first_row[k]] = static_cast<int32_t>(k);
+    }
+    for (int64_t r = 0; r < M; ++r) ++pc.member_ptr[(pc.class_of[r] = pc.class_of[rep[r]]) + 1];
+    prefix_sums(pc.member_ptr);
+    std::vector<int64_t> fill(pc.member_ptr.begin(), pc.member_ptr.end() - 1);
+    for (int64_t r = 0; r < M; ++r) pc.members[fill[pc.class_of[r]]++] = static_cast<int32_t>(r);
     return pc;
 }
 
-// kLazy chooses how rows become candidates of the open cluster (the result is the same):
-// false: every row ahead of the scan that shares a column with the union is visited; right
-// where a row shares many columns with the union (the visits are few next to the counting);
-// true: a row is visited only once its count could pass the merge test; right where most
-// rows share a single column (one visit per count otherwise).
-template <bool kLazy>
-static int64_t cluster_rows(int64_t M, int64_t nbc, const std::vector<int64_t>& pat_ptr,
-                            const std::vector<int32_t>& pat_idx, int tau_permille,
-                            std::vector<int32_t>& order)
+// Inverted index: for every block column the classes whose pattern has it, ascending.
+struct ColumnIndex {
+    Buf<int64_t> ptr;       // [nbc+1]
+    Buf<int64_t> len;       // [nbc] classes still listed (the clustering drops those that are used up)
+    Buf<int32_t> classes;
+};
+
+static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const PatternClasses& pc, Workers& workers)
+{
+    ColumnIndex inv;
+    const int64_t n = pc.size();
+    // counts by part of the classes and column, then the place of every part's first entry in every list
+    const int64_t parts = nbc * workers.most() <= (int64_t{1} << 23) && n > 1024 ? workers.most() : 1;
+    Buf<int64_t> place(static_cast<size_t>(parts * nbc));
+    auto entries = [&](int64_t part, auto&& take) {
+        for (int64_t k = n * part / parts; k < n * (part + 1) / parts; ++k)
+            for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) take(pat.idx[q], k);
+    };
+    workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
+        for (int64_t part = p0; part < p1; ++part) {
+            int64_t* count = place.data() + part * nbc;
+            std::fill(count, count + nbc, int64_t{0});
+            entries(part, [&](int32_t c, int64_t) { ++count[c]; });
+        }
+    });
+    inv.ptr.resize(static_cast<size_t>(nbc) + 1);
+    inv.len.resize(static_cast<size_t>(nbc));
+    int64_t total = 0;
+    for (int64_t c = 0; c < nbc; ++c) {
+        inv.ptr[c] = total;
+        for (int64_t part = 0; part < parts; ++part) {
+            const int64_t count = place[part * nbc + c];
+            place[part * nbc + c] = total;
+            total += count;
+        }
+        inv.len[c] = total - inv.ptr[c];
+    }
+    inv.ptr[nbc] = total;
+    inv.classes.resize(static_cast<size_t>(total));
+    workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
+        for (int64_t part = p0; part < p1; ++part)
+            entries(part, [&](int32_t c, int64_t k) { inv.classes[place[part * nbc + c]++] = static_cast<int32_t>(k); });
+    });
+    return inv;
+}
+
+// With which other classes could a cluster opened by a row of class k start to grow?  The first row of another class to
+// join has to pass the merge test against the seed's own pattern: 1000 |a n b| > keep |a u b|.  Lists such classes, class by
+// class (some more than once).  Each pair is counted once, from the shorter pattern: |b| < 1000 |a| / keep bounds
+// the longer one, and an increment is looked at only once the count could pass for the shortest b.
+struct Partners {
+    Buf<int64_t> ptr;       // [n+1]
+    Buf<int32_t> of;
+};
+
+template <typename Count>
+static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const ColumnIndex& inv, const std::vector<int32_t>& alive,
+                            int64_t keep, Workers& workers)
+{
+    // (alive[k] == 0: every row of the class is in a cluster)
+    const int64_t n = pc.size();
+    struct Local { std::vector<Count> count; std::vector<std::pair<int32_t, int32_t>> pairs; };
+    std::vector<Local> locals(static_cast<size_t>(workers.most()));
+    workers.ranges(n, 16, [&](int64_t j0, int64_t j1, int thread) {
+        Local& local = locals[static_cast<size_t>(thread)];
+        if (local.count.empty()) local.count.assign(static_cast<size_t>(n), 0);
+        Count* const count = local.count.data();
+        for (int64_t j = j0; j < j1; ++j) {
+            const int64_t k = n - 1 - j, len = pc.len[k];                       // long patterns, which take longest, first
+            if (len == 0 || alive[k] == 0) continue;
+            // the first class whose pattern is too long
+            const int64_t end = keep == 0 ? n
+                : std::partition_point(pc.len.begin() + k, pc.len.end(), [&](int32_t x) { return keep * x < 1000 * len; }) - pc.len.begin();
+            const int64_t least = 2 * keep * len / (1000 + keep) + 1;
+            auto lists = [&](auto&& each) {
+                for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) {
+                    const int32_t* p = inv.classes.data() + inv.ptr[pat.idx[q]];
+                    const int32_t* stop = p + inv.len[pat.idx[q]];
+                    for (p = std::upper_bound(p, stop, static_cast<int32_t>(k)); p < stop && *p < end; ++p) each(*p);
+                }
+            };
+            int64_t counted = 0;
+            lists([&](int32_t other) {
+                const int64_t shared = ++count[other];
+                ++counted;
+                if (shared < least || 1000 * shared <= keep * (len + pc.len[other] - shared)) return;
+                local.pairs.emplace_back(static_cast<int32_t>(k), other);
+            });
+            if (counted > (end - k) / 32) std::fill(count + k, count + end, Count{0});
+            else lists([&](int32_t other) { count[other] = 0; });
+        }
+    });
+    Partners partners;
+    partners.ptr.assign(static_cast<size_t>(n) + 1, 0);
+    for (const Local& local : locals)
+        for (const auto& p : local.pairs) { ++partners.ptr[p.first + 1]; ++partners.ptr[p.second + 1]; }
+    prefix_sums(partners.ptr);
+    partners.of.resize(static_cast<size_t>(partners.ptr[n]));
+    std::vector<int64_t> fill(partners.ptr.begin(), partners.ptr.end() - 1);
+    for (const Local& local : locals)
+        for (const auto& p : local.pairs) {
+            partners.of[fill[p.first]++] = p.second;
+            partners.of[fill[p.second]++] = p.first;
+        }
+    return partners;
+}
+
+int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers)
 {
     order.clear();
-    order.reserve(M);
-    const PatternClasses pc = group_equal_patterns(M, pat_ptr, pat_idx);
-    const int64_t n_classes = static_cast<int64_t>(pc.first_row.size());
-    auto class_begin = [&](int64_t k) { return pat_ptr[pc.first_row[k]]; };
-    auto class_end = [&](int64_t k) { return pat_ptr[pc.first_row[k] + 1]; };
+    order.reserve(static_cast<size_t>(M));
+    const PatternClasses pc = group_equal_patterns(M, pat, workers);
+    const int64_t n_classes = pc.size();
     // inverted index: classes of every block column
-    std::vector<int64_t> inv_ptr(nbc + 1, 0);
-    for (int64_t k = 0; k < n_classes; ++k)
-        for (int64_t q = class_begin(k); q < class_end(k); ++q) ++inv_ptr[pat_idx[q] + 1];
-    for (int64_t c = 0; c < nbc; ++c) inv_ptr[c + 1] += inv_ptr[c];
-    std::vector<int32_t> inv_classes(static_cast<size_t>(inv_ptr[nbc]));
-    {
-        std::vector<int64_t> fill(inv_ptr.begin(), inv_ptr.end() - 1);
-        for (int64_t k = 0; k < n_classes; ++k)
-            for (int64_t q = class_begin(k); q < class_end(k); ++q)
-                inv_classes[fill[pat_idx[q]]++] = static_cast<int32_t>(k);
-    }
-    std::vector<int64_t> inv_len(nbc);
-    for (int64_t c = 0; c < nbc; ++c) inv_len[c] = inv_ptr[c + 1] - inv_ptr[c];
+    ColumnIndex inv = index_columns(nbc, pat, pc, workers);
 
     std::vector<uint8_t> clustered(M, 0);
-    std::vector<int32_t> alive(n_classes);    // unclustered rows of the class
-    for (int64_t k = 0; k < n_classes; ++k) alive[k] = static_cast<int32_t>(pc.member_ptr[k + 1] - pc.member_ptr[k]);
-    // per class: 2 * |pattern n union of the open cluster| + (1 if its rows are in the candidate set)
-    std::vector<int32_t> shared(n_classes, 0);
+    // What the counting looks at per class, side by side.
+    struct ClassState {
+        int32_t alive;         // unclustered rows
+        int32_t shared;        // 2 * |pattern n union of the open cluster| + (1 if its rows are in the candidate set)
+        int32_t len, pad;
+    };
+    std::vector<ClassState> state(static_cast<size_t>(n_classes));
+    for (int64_t k = 0; k < n_classes; ++k)
+        state[k] = ClassState{static_cast<int32_t>(pc.member_ptr[k + 1] - pc.member_ptr[k]), 0, pc.len[k], 0};
     std::vector<int32_t> touched;             // classes with shared != 0, cleared when the cluster closes
     std::vector<int64_t> in_union(nbc, -1);   // id of the cluster whose union holds the column
-    std::vector<int32_t> class_len(n_classes);
     int64_t shortest = 0;                     // shortest non-empty pattern
-    for (int64_t k = 0; k < n_classes; ++k) {
-        class_len[k] = static_cast<int32_t>(class_end(k) - class_begin(k));
-        if (class_len[k] > 0 && (shortest == 0 || class_len[k] < shortest)) shortest = class_len[k];
-    }
+    for (int64_t k = 0; k < n_classes && shortest == 0; ++k) shortest = pc.len[k];
     AscendingSet candidates(M);
     int64_t n_clusters = 0;
     const int64_t keep = 1000 - tau_permille;
+    Partners partners;                        // once they have been asked for
+    int64_t spent = 0, ask_at = 300000;       // counting done so far; when to look whether it is worth asking
 
     // A column enters the union while the scan stands at row `pos`: every class that has the
     // column shares one more column with the union, and so does each of its rows.  Only rows
     // ahead of the scan can still be visited; their count when the scan reaches them is the
-    // class's.  kLazy: a row is only worth a visit once it could pass the merge test at all.  The
+    // class's.  A row is only worth a visit once it could pass the merge test at all.  The
     // test at the visit, with the union U' >= U of that later moment and the count n' of then, is
     // 1000 n' > keep (|w| + U' - n'), which implies (1000 + keep) n' > keep (|w| + U); n' is
     // reached at the last increment, where the same inequality with the U of that moment (smaller
@@ -227,45 +373,73 @@ static int64_t cluster_rows(int64_t M, int64_t nbc, const std::vector<int64_t>& 
         in_union[c] = cluster;
         ++union_size;
         const int64_t least = keep * (shortest + union_size) / (1000 + keep);   // a count must exceed this to matter for any row
-        int32_t* classes = inv_classes.data() + inv_ptr[c];
+        int32_t* classes = inv.classes.data() + inv.ptr[c];
         int64_t kept = 0;
-        for (int64_t x = 0; x < inv_len[c]; ++x) {
+        spent += inv.len[c];
+        for (int64_t x = 0; x < inv.len[c]; ++x) {
             const int32_t k = classes[x];
-            if (alive[k] == 0) continue;                 // drop classes that are gone for good
+            ClassState& at = state[k];
+            if (at.alive == 0) continue;                 // drop classes that are gone for good
             classes[kept++] = k;
-            const int32_t word = (shared[k] += 2);
+            const int32_t word = (at.shared += 2);
             if (word == 2) touched.push_back(k);
             if (word & 1) continue;                      // its rows are candidates already
             const int64_t n = word >> 1;
-            if (kLazy && !(n > least && (1000 + keep) * n > keep * (class_len[k] + union_size))) continue;
-            shared[k] = word | 1;
+            if (!(n > least && (1000 + keep) * n > keep * (at.len + union_size))) continue;
+            at.shared = word | 1;
             for (int64_t y = pc.member_ptr[k]; y < pc.member_ptr[k + 1]; ++y) {
                 const int32_t r = pc.members[y];
                 if (r > pos && !clustered[r]) candidates.insert(r);
             }
         }
-        inv_len[c] = kept;
+        inv.len[c] = kept;
+    };
+    // The counting still to come if the rest of the rows goes like the rows so far, against that of partners_of
+    // (at most half the pairs of every list), shared by the threads.
+    auto ask_partners = [&]() {
+        const double done = static_cast<double>(order.size()) / static_cast<double>(M);
+        const double ahead = static_cast<double>(spent) * (1.0 - done) / done;
+        double pairs = 0;
+        for (int64_t c = 0; c < nbc; ++c) pairs += 0.5 * static_cast<double>(inv.len[c]) * static_cast<double>(inv.len[c]);
+        if (ahead < 1.5 * pairs / workers.most() + 1e6) {
+            ask_at = 4 * spent;
+            return;
+        }
+        std::vector<int32_t> alive(static_cast<size_t>(n_classes));
+        for (int64_t k = 0; k < n_classes; ++k) alive[k] = state[k].alive;
+        const bool bytes = n_classes == 0 || pc.len[n_classes - 1] < 256;
+        partners = bytes ? partners_of<uint8_t>(pat, pc, inv, alive, keep, workers) : partners_of<int32_t>(pat, pc, inv, alive, keep, workers);
+    };
+    // Every row before the scan's position is in a cluster, so a class with a row left has it ahead.
+    auto has_partner = [&](int32_t k) {
+        if (partners.ptr.empty()) return true;            // not asked: it may
+        for (int64_t x = partners.ptr[k]; x < partners.ptr[k + 1]; ++x)
+            if (state[partners.of[x]].alive > 0) return true;
+        return false;
     };
 
     for (int64_t v = 0; v < M; ++v) {
         if (clustered[v]) continue;
         const int64_t cluster = n_clusters++;
+        const int32_t seed_class = pc.class_of[v];
         clustered[v] = 1;
-        --alive[pc.class_of[v]];
+        --state[seed_class].alive;
         order.push_back(static_cast<int32_t>(v));
-        if (pat_ptr[v] == pat_ptr[v + 1]) {
-            // empty seed: distance 0 to other empty rows, 1 to everything else
+        if (pc.len[seed_class] == 0 || !has_partner(seed_class)) {
+            // empty seed: distance 0 to other empty rows, 1 to everything else; no partner: the rows that join are
+            // those with the seed's own pattern, which leave the union as it is
             if (tau_permille > 0)
-                for (int64_t w = v + 1; w < M; ++w)
-                    if (!clustered[w] && pat_ptr[w] == pat_ptr[w + 1]) {
-                        clustered[w] = 1;
-                        --alive[pc.class_of[w]];
-                        order.push_back(static_cast<int32_t>(w));
-                    }
+                for (int64_t y = pc.member_ptr[seed_class]; state[seed_class].alive > 0 && y < pc.member_ptr[seed_class + 1]; ++y) {
+                    const int32_t w = pc.members[y];
+                    if (clustered[w]) continue;
+                    clustered[w] = 1;
+                    --state[seed_class].alive;
+                    order.push_back(w);
+                }
             continue;
         }
         int64_t union_size = 0;
-        for (int64_t q = pat_ptr[v]; q < pat_ptr[v + 1]; ++q) add_column(pat_idx[q], v, cluster, union_size);
+        for (int64_t q = pat.ptr[v]; q < pat.ptr[v + 1]; ++q) add_column(pat.idx[q], v, cluster, union_size);
         int64_t pos = v;
         for (;;) {
             const int64_t w = candidates.next(pos + 1);
@@ -273,120 +447,146 @@ static int64_t cluster_rows(int64_t M, int64_t nbc, const std::vector<int64_t>& 
             candidates.erase(w);
             pos = w;
             const int32_t k = pc.class_of[w];
-            const int64_t inter = shared[k] >> 1;
-            const int64_t uni = class_len[k] + union_size - inter;
+            const int64_t inter = state[k].shared >> 1;
+            const int64_t uni = pc.len[k] + union_size - inter;
             if (1000 * inter > keep * uni) {             // 1 - inter/uni < tau/1000
                 clustered[w] = 1;
-                --alive[k];
+                --state[k].alive;
                 order.push_back(static_cast<int32_t>(w));
-                if (inter < class_len[k])                // otherwise every column of the row is in the union already
-                    for (int64_t q = pat_ptr[w]; q < pat_ptr[w + 1]; ++q) add_column(pat_idx[q], w, cluster, union_size);
+                if (inter < pc.len[k])                   // otherwise every column of the row is in the union already
+                    for (int64_t q = pat.ptr[w]; q < pat.ptr[w + 1]; ++q) add_column(pat.idx[q], w, cluster, union_size);
             }
         }
-        for (int32_t k : touched) shared[k] = 0;
+        for (int32_t k : touched) state[k].shared = 0;
         touched.clear();
+        if (partners.ptr.empty() && spent > ask_at) ask_partners();
     }
     return n_clusters;
 }
 
-int64_t jaccard_cluster(int64_t M, int64_t nbc, const std::vector<int64_t>& pat_ptr,
-                        const std::vector<int32_t>& pat_idx, int tau_permille,
-                        std::vector<int32_t>& order)
-{
-    // A row of mean length l meets a union of about l columns in l * l / nbc of them on average:
-    // below a few, most rows ahead of the scan share one column and would be visited for it.
-    const double mean_len = M > 0 ? static_cast<double>(pat_idx.size()) / static_cast<double>(M) : 0.0;
-    const bool lazy = nbc > 0 && mean_len * mean_len < 4.0 * static_cast<double>(nbc);
-    return lazy ? cluster_rows<true>(M, nbc, pat_ptr, pat_idx, tau_permille, order)
-                : cluster_rows<false>(M, nbc, pat_ptr, pat_idx, tau_permille, order);
-}
-
-int64_t count_blocks(int64_t M, int64_t nbc, const std::vector<int64_t>& pat_ptr,
-                     const std::vector<int32_t>& pat_idx, const int32_t* perm)
-{
-    std::vector<int64_t> seen_in(nbc, -1);
-    int64_t n = 0;
-    for (int64_t i = 0; i < M; ++i) {
-        const int64_t br = i / kBlock, r = perm[i];
-        for (int64_t q = pat_ptr[r]; q < pat_ptr[r + 1]; ++q)
-            if (seen_in[pat_idx[q]] != br) { seen_in[pat_idx[q]] = br; ++n; }
+// Per thread, for the passes over block rows: an array over the block columns, made by the first piece a thread takes.
+template <typename T>
+class PerThread {
+public:
+    PerThread(const Workers& workers, int64_t n, T fill) : all_(static_cast<size_t>(workers.most())), n_(n), fill_(fill) {}
+    T* get(int thread)
+    {
+        std::vector<T>& v = all_[static_cast<size_t>(thread)];
+        if (v.empty()) v.assign(static_cast<size_t>(n_) + 1, fill_);
+        return v.data();
     }
-    return n;
+private:
+    std::vector<std::vector<T>> all_;
+    int64_t n_;
+    T fill_;
+};
+constexpr int64_t kBlockRowGrain = 32;
+
+int64_t count_blocks(int64_t M, int64_t nbc, const Patterns& pat, const int32_t* perm, Buf<int32_t>& per_row, Workers& workers)
+{
+    const int64_t nbr = (M + kBlock - 1) / kBlock;
+    per_row.resize(static_cast<size_t>(nbr));
+    PerThread<int32_t> seen_in(workers, nbc, -1);
+    workers.ranges(nbr, kBlockRowGrain, [&](int64_t b0, int64_t b1, int thread) {
+        int32_t* seen = seen_in.get(thread);
+        for (int64_t br = b0; br < b1; ++br) {
+            int32_t n = 0;
+            for (int64_t i = br * kBlock; i < std::min<int64_t>(M, (br + 1) * kBlock); ++i)
+                for (int64_t q = pat.ptr[perm[i]]; q < pat.ptr[perm[i] + 1]; ++q)
+                    if (seen[pat.idx[q]] != br) { seen[pat.idx[q]] = static_cast<int32_t>(br); ++n; }
+            per_row[br] = n;
+        }
+    });
+    return std::accumulate(per_row.begin(), per_row.end(), int64_t{0});
 }
 
-static void build_structure(const Csr& a, const std::vector<int64_t>& pat_ptr, const std::vector<int32_t>& pat_idx, Bcsr& out);
+static void build_structure(const Csr& a, const Patterns& pat, const Buf<int32_t>& per_row, Bcsr& out, Workers& workers);
 
-void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out)
+void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers)
 {
     const int64_t M = a.M;
     out.nbr = (M + kBlock - 1) / kBlock;
     out.nbc = (a.K + kBlock - 1) / kBlock;
-    std::vector<int64_t> pat_ptr;
-    std::vector<int32_t> pat_idx;
-    block_patterns(a, pat_ptr, pat_idx);
+    Patterns pat;
+    block_patterns(a, pat, workers);
 
-    std::vector<int32_t> ident(M);
-    std::iota(ident.begin(), ident.end(), 0);
-    out.n_blocks_identity = count_blocks(M, out.nbc, pat_ptr, pat_idx, ident.data());
-    out.perm = ident;
+    out.perm.resize(static_cast<size_t>(M));
+    std::iota(out.perm.begin(), out.perm.end(), 0);
+    Buf<int32_t> per_row, per_row_cand;
+    out.n_blocks_identity = count_blocks(M, out.nbc, pat, out.perm.data(), per_row, workers);
     out.n_blocks = out.n_blocks_identity;
     out.used_identity = true;
     out.n_clusters = 0;
     if (reorder) {
-        std::vector<int32_t> cand;
-        out.n_clusters = jaccard_cluster(M, out.nbc, pat_ptr, pat_idx, tau_permille, cand);
-        const int64_t n_cand = count_blocks(M, out.nbc, pat_ptr, pat_idx, cand.data());
+        Buf<int32_t> cand;
+        out.n_clusters = jaccard_cluster(M, out.nbc, pat, tau_permille, cand, workers);
+        const int64_t n_cand = count_blocks(M, out.nbc, pat, cand.data(), per_row_cand, workers);
         if (n_cand < out.n_blocks_identity) {            // strictly fewer, else keep P = I
             out.perm.swap(cand);
+            per_row.swap(per_row_cand);
             out.n_blocks = n_cand;
             out.used_identity = false;
         }
     }
 
-    build_structure(a, pat_ptr, pat_idx, out);
+    build_structure(a, pat, per_row, out, workers);
 }
 
 // Row pointer, block columns and column masks of the BCSR of A' = P A for the permutation
-// already in out.perm.
-static void build_structure(const Csr& a, const std::vector<int64_t>& pat_ptr, const std::vector<int32_t>& pat_idx, Bcsr& out)
+// already in out.perm; per_row holds the number of blocks of every block row.
+static void build_structure(const Csr& a, const Patterns& pat, const Buf<int32_t>& per_row, Bcsr& out, Workers& workers)
 {
     const int64_t M = a.M;
-    // structure: per block row the ascending union of its rows' patterns
-    out.row_ptr.assign(out.nbr + 1, 0);
-    out.col_idx.clear();
-    out.col_idx.reserve(out.n_blocks);
-    std::vector<int32_t> tmp;
-    for (int64_t br = 0; br < out.nbr; ++br) {
-        tmp.clear();
-        const int64_t i_end = std::min<int64_t>(M, (br + 1) * kBlock);
-        for (int64_t i = br * kBlock; i < i_end; ++i) {
-            const int64_t r = out.perm[i];
-            tmp.insert(tmp.end(), pat_idx.begin() + pat_ptr[r], pat_idx.begin() + pat_ptr[r + 1]);
-        }
-        std::sort(tmp.begin(), tmp.end());
-        tmp.erase(std::unique(tmp.begin(), tmp.end()), tmp.end());
-        out.col_idx.insert(out.col_idx.end(), tmp.begin(), tmp.end());
-        out.row_ptr[br + 1] = static_cast<int32_t>(out.col_idx.size());
-    }
-
-    // per block: which of its 16 columns hold a stored entry
-    out.col_mask.assign(out.col_idx.size(), 0);
-    std::vector<int32_t> slot_of(out.nbc, -1);
-    for (int64_t br = 0; br < out.nbr; ++br) {
-        for (int32_t s = out.row_ptr[br]; s < out.row_ptr[br + 1]; ++s) slot_of[out.col_idx[s]] = s;
-        const int64_t i_end = std::min<int64_t>(M, (br + 1) * kBlock);
-        for (int64_t i = br * kBlock; i < i_end; ++i) {
-            const int64_t r = out.perm[i];
-            for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p) {
-                const int32_t c = a.col_idx[p];
-                out.col_mask[slot_of[c / kBlock]] |= static_cast<uint16_t>(1u << (c % kBlock));
+    out.row_ptr.resize(static_cast<size_t>(out.nbr) + 1);
+    out.row_ptr[0] = 0;
+    std::copy(per_row.begin(), per_row.end(), out.row_ptr.begin() + 1);
+    prefix_sums(out.row_ptr);
+    out.col_idx.resize(static_cast<size_t>(out.n_blocks));
+    out.col_mask.resize(static_cast<size_t>(out.n_blocks));
+    PerThread<uint64_t> bits_of(workers, (out.nbc + 63) / 64, 0);      // block columns of the block row at hand
+    PerThread<int32_t> slot_of(workers, out.nbc, -1);                  // their places in col_idx
+    workers.ranges(out.nbr, kBlockRowGrain, [&](int64_t b0, int64_t b1, int thread) {
+        uint64_t* bits = bits_of.get(thread);
+        int32_t* slot = slot_of.get(thread);
+        for (int64_t br = b0; br < b1; ++br) {
+            const int64_t i_end = std::min<int64_t>(M, (br + 1) * kBlock);
+            int32_t* cols = out.col_idx.data() + out.row_ptr[br];
+            const int32_t n = out.row_ptr[br + 1] - out.row_ptr[br];
+            int32_t at = 0;
+            // ascending union of the rows' patterns: collected through the bit set, which then either is read off in
+            // order or, where the row has few blocks for its length, only keeps the list free of repetitions
+            for (int64_t i = br * kBlock; i < i_end; ++i)
+                for (int64_t q = pat.ptr[out.perm[i]]; q < pat.ptr[out.perm[i] + 1]; ++q) {
+                    const int32_t c = pat.idx[q];
+                    if (bits[c >> 6] >> (c & 63) & 1u) continue;
+                    bits[c >> 6] |= uint64_t{1} << (c & 63);
+                    cols[at++] = c;
+                }
+            if (out.nbc / 64 <= 4 * static_cast<int64_t>(n)) {
+                at = 0;
+                for (int64_t w = 0; w < (out.nbc + 63) / 64; ++w)
+                    for (uint64_t x = bits[w]; x; x &= x - 1) cols[at++] = static_cast<int32_t>(64 * w) + __builtin_ctzll(x);
+            } else {
+                std::sort(cols, cols + n);
+            }
+            for (int32_t s = 0; s < n; ++s) {
+                bits[cols[s] >> 6] = 0;
+                slot[cols[s]] = out.row_ptr[br] + s;
+                out.col_mask[out.row_ptr[br] + s] = 0;
+            }
+            // per block: which of its 16 columns hold a stored entry
+            for (int64_t i = br * kBlock; i < i_end; ++i) {
+                const int64_t r = out.perm[i];
+                for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p) {
+                    const int32_t c = a.col_idx[p];
+                    out.col_mask[slot[c / kBlock]] |= static_cast<uint16_t>(1u << (c % kBlock));
+                }
             }
         }
-    }
-
+    });
 }
 
-bool reorder_columns(Csr& a, int tau_permille, Bcsr& b)
+bool reorder_columns(Csr& a, int tau_permille, Bcsr& b, Workers& workers)
 {
     const int64_t M = a.M, K = a.K;
     b.col_perm.resize(static_cast<size_t>(K));
@@ -394,49 +594,51 @@ bool reorder_columns(Csr& a, int tau_permille, Bcsr& b)
     b.n_blocks_rows_only = b.n_blocks;
     if (K == 0 || M == 0) return false;
     // column patterns: ascending block rows of A' = P A per column (rows are walked in their new order)
-    std::vector<int64_t> cpat_ptr(K + 1, 0);
+    Patterns cpat;
+    cpat.ptr.assign(static_cast<size_t>(K) + 1, 0);
     std::vector<int32_t> last(K, -1);
     for (int64_t i = 0; i < M; ++i) {
         const int64_t r = b.perm[i];
         const int32_t br = static_cast<int32_t>(i / kBlock);
         for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p)
-            if (last[a.col_idx[p]] != br) { last[a.col_idx[p]] = br; ++cpat_ptr[a.col_idx[p] + 1]; }
+            if (last[a.col_idx[p]] != br) { last[a.col_idx[p]] = br; ++cpat.ptr[a.col_idx[p] + 1]; }
     }
-    for (int64_t c = 0; c < K; ++c) cpat_ptr[c + 1] += cpat_ptr[c];
-    std::vector<int32_t> cpat_idx(static_cast<size_t>(cpat_ptr[K]));
+    prefix_sums(cpat.ptr);
+    cpat.idx.resize(static_cast<size_t>(cpat.ptr[K]));
     {
-        std::vector<int64_t> fill(cpat_ptr.begin(), cpat_ptr.end() - 1);
+        std::vector<int64_t> fill(cpat.ptr.begin(), cpat.ptr.end() - 1);
         std::fill(last.begin(), last.end(), -1);
         for (int64_t i = 0; i < M; ++i) {
             const int64_t r = b.perm[i];
             const int32_t br = static_cast<int32_t>(i / kBlock);
             for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p)
-                if (last[a.col_idx[p]] != br) { last[a.col_idx[p]] = br; cpat_idx[fill[a.col_idx[p]]++] = br; }
+                if (last[a.col_idx[p]] != br) { last[a.col_idx[p]] = br; cpat.idx[fill[a.col_idx[p]]++] = br; }
         }
     }
-    std::vector<int32_t> cand;
-    jaccard_cluster(K, b.nbr, cpat_ptr, cpat_idx, tau_permille, cand);
-    const int64_t n_cand = count_blocks(K, b.nbr, cpat_ptr, cpat_idx, cand.data());     // blocks of the transpose = blocks of P A Q
+    Buf<int32_t> cand, per_row;
+    jaccard_cluster(K, b.nbr, cpat, tau_permille, cand, workers);
+    const int64_t n_cand = count_blocks(K, b.nbr, cpat, cand.data(), per_row, workers);     // blocks of the transpose = blocks of P A Q
     if (n_cand >= b.n_blocks) return false;              // strictly fewer, else keep Q = I
     b.col_perm.swap(cand);
     // A <- A Q: entry (r, c) moves to the new index of column c; columns ascend again inside every row
     std::vector<int32_t> new_of_old(static_cast<size_t>(K));
     for (int64_t c = 0; c < K; ++c) new_of_old[b.col_perm[c]] = static_cast<int32_t>(c);
-    std::vector<std::pair<int32_t, uint16_t>> row;
-    for (int64_t r = 0; r < M; ++r) {
-        row.clear();
-        for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p) row.emplace_back(new_of_old[a.col_idx[p]], a.vals[p]);
-        std::sort(row.begin(), row.end());
-        for (size_t x = 0; x < row.size(); ++x) {
-            a.col_idx[a.row_ptr[r] + static_cast<int64_t>(x)] = row[x].first;
-            a.vals[a.row_ptr[r] + static_cast<int64_t>(x)] = row[x].second;
+    workers.ranges(M, 2048, [&](int64_t r0, int64_t r1, int) {
+        std::vector<std::pair<int32_t, uint16_t>> row;
+        for (int64_t r = r0; r < r1; ++r) {
+            row.clear();
+            for (int64_t p = a.row_ptr[r]; p < a.row_ptr[r + 1]; ++p) row.emplace_back(new_of_old[a.col_idx[p]], a.vals[p]);
+            std::sort(row.begin(), row.end());
+            for (size_t x = 0; x < row.size(); ++x) {
+                a.col_idx[a.row_ptr[r] + static_cast<int64_t>(x)] = row[x].first;
+                a.vals[a.row_ptr[r] + static_cast<int64_t>(x)] = row[x].second;
+            }
         }
-    }
-    std::vector<int64_t> pat_ptr;
-    std::vector<int32_t> pat_idx;
-    block_patterns(a, pat_ptr, pat_idx);
-    b.n_blocks = n_cand;
-    build_structure(a, pat_ptr, pat_idx, b);
+    });
+    Patterns pat;
+    block_patterns(a, pat, workers);
+    b.n_blocks = count_blocks(M, b.nbc, pat, b.perm.data(), per_row, workers);      // = n_cand, now by block row
+    build_structure(a, pat, per_row, b, workers);
     return true;
 }
 

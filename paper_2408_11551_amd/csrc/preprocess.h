@@ -7,48 +7,53 @@
 #include <string>
 #include <vector>
 
+#include "workers.h"
+
 namespace smat {
 
 constexpr int kBlock = 16;   // h = w = 16
 
 struct Csr {
     int64_t M = 0, K = 0;
-    std::vector<int64_t> row_ptr;   // [M+1]
-    std::vector<int32_t> col_idx;   // [nnz]
-    std::vector<uint16_t> vals;     // [nnz] bit patterns (an 8-bit type sits in the low byte)
+    Buf<int64_t> row_ptr;           // [M+1]
+    Buf<int32_t> col_idx;           // [nnz]
+    Buf<uint16_t> vals;             // [nnz] bit patterns (an 8-bit type sits in the low byte)
 };
 
 struct Bcsr {
     int64_t nbr = 0, nbc = 0;
-    std::vector<int32_t> perm;       // [M] new -> old
-    std::vector<int32_t> row_ptr;    // [nbr+1]
-    std::vector<int32_t> col_idx;    // [n_e]
-    std::vector<uint16_t> col_mask;  // [n_e] bit c set iff column c of the block holds a stored entry
+    Buf<int32_t> perm;               // [M] new -> old
+    Buf<int32_t> row_ptr;            // [nbr+1]
+    Buf<int32_t> col_idx;            // [n_e]
+    Buf<uint16_t> col_mask;          // [n_e] bit c set iff column c of the block holds a stored entry
     int64_t n_blocks = 0, n_blocks_identity = 0;
     bool used_identity = true;
     // row + column reordering only (reorder_columns): new column -> old column, identity if unused
-    std::vector<int32_t> col_perm;
+    Buf<int32_t> col_perm;
     int64_t n_blocks_rows_only = 0;
     int64_t n_clusters = 0;
 };
 
-// Returns an empty string when the CSR is well formed, else what is wrong.
-std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx);
+// Returns an empty string when the columns are well formed, else what is wrong with the first row that is not.
+// row_ptr has been found to start at 0 and not to decrease.
+std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx, Workers& workers);
 
 // Row patterns: ascending block columns floor(c/16) per row, as a CSR-like pair.
-void block_patterns(const Csr& a, std::vector<int64_t>& pat_ptr, std::vector<int32_t>& pat_idx);
+struct Patterns {
+    Buf<int64_t> ptr;       // [M+1]
+    Buf<int32_t> idx;
+};
+void block_patterns(const Csr& a, Patterns& pat, Workers& workers);
 
 // Greedy Jaccard clustering; returns the cluster order (new -> old) and the number of clusters.
-int64_t jaccard_cluster(int64_t M, int64_t nbc, const std::vector<int64_t>& pat_ptr,
-                        const std::vector<int32_t>& pat_idx, int tau_permille,
-                        std::vector<int32_t>& order);
+int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers);
 
-// Number of nonzero blocks when rows are read in the order perm on the 16-row grid.
-int64_t count_blocks(int64_t M, int64_t nbc, const std::vector<int64_t>& pat_ptr,
-                     const std::vector<int32_t>& pat_idx, const int32_t* perm);
+// Number of nonzero blocks when rows are read in the order perm on the 16-row grid; per_row receives
+// the number of every block row.
+int64_t count_blocks(int64_t M, int64_t nbc, const Patterns& pat, const int32_t* perm, Buf<int32_t>& per_row, Workers& workers);
 
 // Full pipeline: patterns -> (optional) clustering -> guard -> BCSR structure and column masks.
-void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out);
+void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers);
 
 // Row + column variant (the one the paper tried next to the row-only reordering, Preprocessing
 // section): after build_bcsr, clusters the columns of A' = P A with the same greedy procedure, a
@@ -56,7 +61,7 @@ void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out);
 // has strictly fewer blocks.  If it does, `a` becomes A Q (columns renumbered, ascending inside
 // every row), b.col_perm holds Q (new -> old) and the structure of b is rebuilt; returns whether
 // it did.
-bool reorder_columns(Csr& a, int tau_permille, Bcsr& b);
+bool reorder_columns(Csr& a, int tau_permille, Bcsr& b, Workers& workers);
 
 // Launch order of the block rows, given their cost as a row_ptr-like prefix array
 // (cost of row br = cost_ptr[br+1] - cost_ptr[br]).
