@@ -328,8 +328,9 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
         for (int64_t br = b0; br < b1; ++br) {
             int32_t* first = h.pack_first.data() + h.pack_ptr[static_cast<size_t>(br)];
             const int32_t n_packs = h.pack_ptr[static_cast<size_t>(br) + 1] - h.pack_ptr[static_cast<size_t>(br)];
-            // (an entry row's packs are not runs of blocks: only their number counts)
-            if (h.row_class[static_cast<size_t>(br)] == smat::kEntryClass) { std::fill(first, first + n_packs, b.row_ptr[br + 1]); continue; }
+            // (an entry row's packs are not runs of blocks; its first one still says where the last pack of the block row
+            // before ends)
+            if (h.row_class[static_cast<size_t>(br)] == smat::kEntryClass) { std::fill(first, first + n_packs, b.row_ptr[br]); continue; }
             int32_t last = -1;
             for (int32_t s = b.row_ptr[br]; s < b.row_ptr[br + 1]; ++s) {
                 const int32_t pack = h.blk_pack[static_cast<size_t>(s)];
