@@ -51,6 +51,7 @@ struct smat_handle {
     int64_t value_bytes = 0;             // bytes of block values a launch over every block row reads
     int64_t b_rows = 0;                  // slots that name a row of B, over all packs
     std::vector<int32_t> row_b_rows;     // [nbr] the same per block row
+    bool even_rows = false;              // no block row has more than twice the packs of the average one, which has sixteen or more
     // Dense path (kernels.h, DenseTiles): complete super rows of sixteen block rows whose block
     // columns overlap enough.  row_dense marks the block rows it covers.
     std::vector<int32_t> dense_super, step_ptr, step_cols;
@@ -100,6 +101,30 @@ constexpr size_t kAlign = 256;
 // splits only while tiles x workgroups per tile stays within the 256 compute units, so at most
 // 256 partial tiles of 256 x 128 words are in use per launch.  One such area per stream.
 constexpr size_t kTileScratchBytes = size_t{256} * 256 * 128 * 4;
+
+// The per-row kernel on several slabs of columns gathers whole cache lines of B fastest: one slab per workgroup and two waves
+// per SIMD then (launch_shape in spmm_rows.h).  With rows of B off the lines (N = 1000) every piece of a row touches one
+// line more than it fills, and neither pays.  Where every row of B is used often enough such a B is copied to padded rows
+// first, as many columns at a time as the area of the stream holds.  Measured on block rows of similar length:
+// 2.7 GB gathered in 350 us as they lie and in 193 from whole lines, i.e. 0.055 us saved per MB, against 0.45 us per MB
+// of B and a launch for the copy: even at about eight uses of a row.  Rows of unequal length, which take neither of
+// the two, save half as much.
+constexpr int64_t kUsesForStaging = 12;
+
+// Does the workspace have an area for such copies (rows of similar length, used often enough)?
+bool rows_may_stage(const smat_handle& h)
+{
+    return h.csr.K > 0 && h.even_rows && h.b_rows >= kUsesForStaging * h.csr.K;
+}
+
+// Does the copy pay for N columns?  (A single slab has no gain from it.)
+bool rows_stage(const smat_handle& h, int64_t N)
+{
+    const double row_mb = static_cast<double>(N * h.elem_bytes) * 1e-6;
+    return rows_may_stage(h) && N * h.elem_bytes > 256 &&
+           0.055 * row_mb * static_cast<double>(h.b_rows) > 0.45 * row_mb * static_cast<double>(h.csr.K) + 5.0;
+}
+
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Workspace layout, every section aligned to 256 bytes.
@@ -137,7 +162,7 @@ Layout make_layout(const smat_handle& h)
     l.t_rows = take(h.step_rows.size() * sizeof(uint32_t));
     l.t_base = take(h.step_base.size() * sizeof(uint32_t));
     l.t_vals = take(static_cast<size_t>(h.dense_slots) * 1024);
-    l.t_scratch = take(h.dense_super.empty() ? 0 : kTileScratchBytes * static_cast<size_t>(h.n_scratch_areas));
+    l.t_scratch = take(h.dense_super.empty() && !rows_may_stage(h) ? 0 : kTileScratchBytes * static_cast<size_t>(h.n_scratch_areas));
     l.total = off ? off : kAlign;
     return l;
 }
@@ -343,6 +368,9 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
     h.vals_off[nbr] = static_cast<uint32_t>(vunits);
     h.slots_units = units;
     h.vals_units = vunits;
+    int64_t longest = 0;
+    for (size_t br = 0; br < nbr; ++br) longest = std::max<int64_t>(longest, h.pack_ptr[br + 1] - h.pack_ptr[br]);
+    h.even_rows = packs >= 16 * b.nbr && longest * b.nbr <= 2 * packs;
     smat::work_order(h.pack_ptr, h.order);
 }
 
@@ -677,7 +705,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         h->tiles = tiles;
         {
             std::lock_guard<std::mutex> lock(h->scratch_mutex);
-            h->scratch_base = h->dense_super.empty() ? nullptr : base + l.t_scratch;
+            h->scratch_base = l.total > l.t_scratch ? base + l.t_scratch : nullptr;
             h->scratch_owner.clear();
         }
         h->bound = true;
@@ -804,22 +832,29 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     smat::DenseTiles tiles = h->tiles;
     tiles.scratch = scratch;
     tiles.scratch_bytes = scratch ? (hard_limit && in_pieces ? ~size_t{0} >> 1 : scratch_bytes) : 0;
-    // Columns staged at a time: all of them, or as many whole tiles as the area holds.
-    int64_t chunk = N, stage_ld = ldb;
-    if (use_tiles && !in_pieces) {
+    // Columns staged at a time: all of them, or as many whole tiles as the area holds (0: not even one).
+    struct Staging { int64_t chunk, ld; size_t bytes; };
+    auto plan_staging = [&]() {
         const int64_t line = 128 / h->elem_bytes;    // rows of the copy are whole cache lines
         const int64_t fit = h->csr.K > 0 ? static_cast<int64_t>(scratch_bytes) / (h->csr.K * 128) * line : N;
-        if (fit >= N) {
-            stage_ld = (N + line - 1) / line * line;
-        } else {
+        Staging st{N, (N + line - 1) / line * line, 0};
+        if (fit < N) {
             const int64_t n_chunks = fit >= 128 ? (N + fit / 128 * 128 - 1) / (fit / 128 * 128) : 0;
-            if (n_chunks == 0) use_tiles = false;
-            else chunk = stage_ld = ((N + n_chunks - 1) / n_chunks + 127) / 128 * 128;
+            if (n_chunks == 0) return Staging{0, 0, 0};
+            st.chunk = st.ld = ((N + n_chunks - 1) / n_chunks + 127) / 128 * 128;
         }
-        if (use_tiles) {
-            const size_t staged = align_up(static_cast<size_t>(h->csr.K) * static_cast<size_t>(stage_ld * h->elem_bytes));
-            tiles.scratch = static_cast<char*>(scratch) + staged;
-            tiles.scratch_bytes = scratch_bytes > staged ? scratch_bytes - staged : 0;
+        st.bytes = align_up(static_cast<size_t>(h->csr.K) * static_cast<size_t>(st.ld * h->elem_bytes));
+        return st;
+    };
+    int64_t chunk = N, stage_ld = ldb;
+    if (use_tiles && !in_pieces) {
+        const Staging st = plan_staging();
+        if (st.chunk == 0) use_tiles = false;
+        else {
+            chunk = st.chunk;
+            stage_ld = st.ld;
+            tiles.scratch = static_cast<char*>(scratch) + st.bytes;
+            tiles.scratch_bytes = scratch_bytes > st.bytes ? scratch_bytes - st.bytes : 0;
         }
     }
     // It also has to pay: a tile walks its steps at about
@@ -869,7 +904,17 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (h->dev_rest.n_order > 0 ? std::string("+") + variant : std::string());
         g_kernel = name.c_str();
     } else {
-        e = smat::launch_spmm(h->dev, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        const bool lines = (ldb * h->elem_bytes) % 128 == 0 && reinterpret_cast<uintptr_t>(dB) % 128 == 0;
+        const Staging st = !lines && scratch && rows_stage(*h, N) ? plan_staging() : Staging{0, 0, 0};
+        if (st.chunk > 0) {
+            for (int64_t c0 = 0; c0 < N && !e; c0 += st.chunk) {
+                const int64_t n = std::min(st.chunk, N - c0);
+                e = smat::launch_stage_b(static_cast<const char*>(dB) + c0 * h->elem_bytes, ldb, h->csr.K, n, h->elem_bytes, scratch, st.ld, stream);
+                if (!e) e = smat::launch_spmm(h->dev, h->dtype, scratch, st.ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &variant);
+            }
+        } else {
+            e = smat::launch_spmm(h->dev, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        }
         g_kernel = variant;
     }
     if (e) return hip_fail("launch spmm", e);

@@ -65,3 +65,14 @@ def test_tile_kernel_on_a_copy_of_b(shape, oracle_c):
     for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
         name = _exact(w, oracle_c, ldb, ldc, shift, dense_tiles=1)
         assert name.startswith("spmm_dense") and "_staged" in name, name
+
+
+@pytest.mark.parametrize("N,dtype", [(519, "bf16"), (1001, "e4m3"), (1400, "f16")])
+def test_per_row_kernel_on_a_copy_of_b(N, dtype, oracle_c):
+    """Block rows of similar length that use every row of B many times, rows of B off the cache lines: the per-row kernel
+    runs on a padded copy (the last shape in column ranges: the area holds less than the whole of it)."""
+    M = K = 2048 if N < 1400 else 16384
+    w = random_csr(M, K, N, 0.1 if N < 1400 else 0.008, seed=N, values="smallint", b_dist="smallint")
+    w = w if dtype == "f16" else recast(w, dtype)
+    for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
+        _exact(w, oracle_c, ldb, ldc, shift)
