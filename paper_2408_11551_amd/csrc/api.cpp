@@ -117,12 +117,13 @@ bool rows_may_stage(const smat_handle& h)
     return h.csr.K > 0 && h.even_rows && h.b_rows >= kUsesForStaging * h.csr.K;
 }
 
-// Does the copy pay for N columns?  (A single slab has no gain from it.)
+// Does the copy pay for N columns?  Not for less than one and a half slabs (N = 140: 46.7 -> 48.9 us), nor for a B that
+// nearly fits the L2s (6.5 MB, N = 200: 32.5 -> 35.7 us; 13 MB: 65.3 -> 55.6).
 bool rows_stage(const smat_handle& h, int64_t N)
 {
-    const double row_mb = static_cast<double>(N * h.elem_bytes) * 1e-6;
-    return rows_may_stage(h) && N * h.elem_bytes > 256 &&
-           0.055 * row_mb * static_cast<double>(h.b_rows) > 0.45 * row_mb * static_cast<double>(h.csr.K) + 5.0;
+    const double row_mb = static_cast<double>(N * h.elem_bytes) * 1e-6, b_mb = row_mb * static_cast<double>(h.csr.K);
+    return rows_may_stage(h) && N * h.elem_bytes >= 384 && b_mb >= 8.0 &&
+           0.055 * row_mb * static_cast<double>(h.b_rows) > 0.45 * b_mb + 5.0;
 }
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }

@@ -22,21 +22,9 @@
 
 #include "kernels.h"
 #include "mfma_types.h"
+#include "tile_common.h"
 
 namespace smat {
-
-namespace {
-
-constexpr uint32_t kOutOfRange = 0x80000000u;
-constexpr int kRsrcFlags = 0x00020000;
-
-__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    const i32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
-    return u32x4{static_cast<uint32_t>(v[0]), static_cast<uint32_t>(v[1]), static_cast<uint32_t>(v[2]), static_cast<uint32_t>(v[3])};
-}
-
-}  // namespace
 
 // ---------------------------------------------------------------------------------------------
 // The tile kernel: C rows of the dense super rows, 128 columns per workgroup; 4 waves per group,
@@ -89,16 +77,6 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t v
 // for the lines of later steps through the scalar cache (88 us against 79 us at the time);
 // transposing reads two groups ahead (65 against 63 us); a ring of four steps with the transposing reads (no
 // change, hot or on flushed caches).
-// The tiles are numbered so that the workgroups an XCD runs (every eighth in dispatch order) form
-// compact rectangles of super rows x column slabs: the tile values of a super row and the panel rows
-// of a slab then miss that XCD's L2 once and hit it for the other workgroups that walk them at the
-// same time.
-constexpr int kTileGroup = 4;          // super rows of a rectangle
-
-// What the host and the kernel agree on: tile number -> (index of the super row, column slab).
-struct TileOrder {
-    int n_super, n_slab, per_xcd;      // per_xcd = ceil(tiles / 8)
-};
 // What the tile kernel needs later than its first loads (DenseTiles and DeviceBcsr have the rest).
 struct TileTables {
     const int32_t* step_cols;
@@ -107,56 +85,6 @@ struct TileTables {
     const int32_t* perm;
     void* scratch;
 };
-
-__device__ __forceinline__ uint32_t lds_offset_of(const void* p)
-{
-    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)p));
-}
-
-// One load straight into LDS: every lane fetches the 16 bytes at voff + soff of the buffer (zeros
-// when out of range), and the wave's 64 pieces land back to back from lds_addr on (wave-uniform).
-// The compiler counts it among the outstanding memory loads like any other.
-typedef __attribute__((address_space(3))) void lds_void;
-__device__ __forceinline__ void load_to_lds16(lds_void* lds_addr, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_addr, 16, voff, soff, 0, 0);
-}
-
-// Reads of what such loads delivered.  They are written as assembly so that the compiler does not
-// see an LDS read at all: it would hold every such read back until the most recent load into LDS
-// has completed (it cannot tell the ring's panels apart), which is the look-ahead this kernel is
-// for.  The panel's arrival is awaited by hand and made visible by a barrier.  (None of the
-// assembly statements of this kernel claims to touch memory: the compiler would then no longer
-// fetch the per-step tables with scalar loads, and its vector loads would wait for everything.)
-//
-// Transposing read (gfx950): every lane names eight bytes (four 16-bit elements of one row); inside
-// each group of sixteen lanes, lane i receives element i % 4 of the pieces named by lanes i / 4,
-// i / 4 + 4, i / 4 + 8 and i / 4 + 12, in that order -- four k-consecutive elements of one column
-// when those four lanes name four consecutive rows.
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-template <int OFFSET>
-__device__ __forceinline__ u32x2_t lds_read_tr(uint32_t addr)
-{
-    u32x2_t v;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET));
-    return v;
-}
-// The same for bytes: a lane names eight bytes of a row, and lane i receives byte i % 8 of the pieces
-// named by lanes i / 8, i / 8 + 2, ..., i / 8 + 14 -- eight k-consecutive bytes of one column when
-// those eight lanes name eight consecutive rows.
-template <int OFFSET>
-__device__ __forceinline__ u32x2_t lds_read_tr8(uint32_t addr)
-{
-    u32x2_t v;
-    asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET));
-    return v;
-}
-// the two reads into lo and hi have returned once at most YOUNGER later LDS reads are outstanding
-template <int YOUNGER>
-__device__ __forceinline__ void lds_pair_done(u32x2_t& lo, u32x2_t& hi)
-{
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(YOUNGER));
-}
 
 template <int DT, int KG, bool FULL = false>
 __global__ __launch_bounds__(256 * KG)
@@ -178,7 +106,6 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
     const uint32_t b_bytes = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
         static_cast<int>(K > 0u ? (K - 1u) * ldb_bytes + ((static_cast<uint32_t>(N) * kElemBytes + 15u) & ~15u) : 0u)));
     using Acc = typename Elem<DT>::Acc;
-    using Out = typename Elem<DT>::Out;
     constexpr int ES = Elem<DT>::ES;               // bytes per element of A and B
     constexpr int KS = ES == 1 ? 2 : 1;            // sub-steps of 32 k slots (two block columns) per step
     constexpr int NT = 8;                          // groups of 16 columns: 128 columns per tile
@@ -189,13 +116,8 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
     constexpr int kLdsWords = KG == 2 ? (KG * RD * 32 * 16 > 8192 ? KG * RD * 32 * 16 : 8192) : KG * RD * 32 * 16;
     __shared__ u32x4 lds_words[kLdsWords];
 
-    // tile of this workgroup: the XCD's share of the tile numbers is contiguous
-    const int tile = static_cast<int>(blockIdx.x % 8u) * per_xcd + static_cast<int>(blockIdx.x / 8u);
-    if (tile >= n_super * n_slab) return;
-    const int band = tile / (kTileGroup * n_slab), in_band = tile % (kTileGroup * n_slab);
-    const int band_rows = min(kTileGroup, n_super - kTileGroup * band);
-    const int sidx = kTileGroup * band + in_band % band_rows;
-    const int slab = in_band / band_rows;
+    int sidx, slab;
+    if (!tile_of_workgroup(n_super, n_slab, per_xcd, sidx, slab)) return;
 
     const int tid = threadIdx.x & 255;             // thread inside its wave group
     const int lane = tid & 63;
@@ -456,110 +378,24 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
         if constexpr (ES == 1) asm volatile("s_nop 15\n\ts_nop 15");
     }
 
-    // Where the lane's rows of C' go.  One group per workgroup: already asked for before the loop (the registers are
-    // there, and the stores then begin without one more trip to memory -- which a short tile on cold caches feels).
-    // Two groups: asked for when the loop ends, ahead of the hand-over, which hides the trip; a lane then stores two
-    // of its four block rows (group 0 the first two, group 1 the others).  (The empty statement makes the super
-    // row's number a value the compiler knows only from here on, so that it cannot move these loads above the loop:
-    // there the 8-bit instantiations once spilled registers inside it and ran 79 instead of 53 us.)
-    if constexpr (KG == 2) {
-        int super_now = super;
-        asm volatile("" : "+s"(super_now));
-        if (ks == 1) {
-#pragma unroll
-            for (int r = 0; r < RM; ++r)
-                if ((r >> 1) == kg) {
-#pragma unroll
-                    for (int y = 0; y < 4; ++y)
-                        out_rows[r][y] = tab.perm[(static_cast<int64_t>(super_now) * 16 + RM * wave + r) * 16 + 4 * g + y];
-                }
-        }
-    }
-    // acc[r][x][y] = C'[16 * (16 super + 4 wave + r) + 4g + y][n0 + 16x + i]
-    auto store_block_row = [&](int r) {
-        if (ks > 1) {
-            // partial tile, row-major 256 x 128 words, at [(tile * ks + z)]
-            const size_t tile_at = static_cast<size_t>(sidx) * n_slab + slab;
-            Out* part = static_cast<Out*>(tab.scratch) + (tile_at * ks + blockIdx.z) * (256 * 128);
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                Out* dst = part + (64 * wave + 16 * r + 4 * g + y) * 128 + i;
-#pragma unroll
-                for (int x = 0; x < NT; ++x) dst[16 * x] = acc[r][x][y];
-            }
-            return;
-        }
-        // sixteen lanes store 64 consecutive bytes of a row of C; the eight groups of columns of a lane
-        // lie 64 bytes apart.  (Turning the tile over through LDS first, to store 16 bytes per lane and whole
-        // rows of 512 bytes, was slower: 63.0 against 62.0 us hot, 71.5 against 68.7 us on flushed caches.)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const int64_t out_row = out_rows[r][y];
-            if (out_row < 0) continue;
-            Out* dst = C + out_row * ldc + n0 + i;
-#pragma unroll
-            for (int x = 0; x < NT; ++x)
-                if (n0 + 16 * x + i < N) dst[16 * x] = acc[r][x][y];
-        }
-    };
-    if constexpr (KG == 2) {
-        // The two groups hold partial sums of the same tile (even and odd steps).  Each hands two of its four block
-        // rows per wave to the other through LDS -- group 1 its first two, group 0 its last two, 64 KiB each way --
-        // and adds and stores the two it keeps: one barrier, and all eight waves store.
-        __syncthreads();
-        Out* handover = reinterpret_cast<Out*>(lds_words) + (kg == 0 ? 16384 : 0);      // where this group writes
-        const Out* incoming = reinterpret_cast<const Out*>(lds_words) + (kg == 0 ? 0 : 16384);
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr)
-#pragma unroll
-            for (int x = 0; x < NT; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    const Out v = kg == 0 ? acc[2 + rr][x][y] : acc[rr][x][y];
-                    handover[(((wave * 2 + rr) * NT + x) * 4 + y) * 64 + lane] = v;
-                }
-        __syncthreads();
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr)
-#pragma unroll
-            for (int x = 0; x < NT; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    const Out v = incoming[(((wave * 2 + rr) * NT + x) * 4 + y) * 64 + lane];
-                    if (kg == 0) acc[rr][x][y] += v;
-                    else acc[2 + rr][x][y] += v;
-                }
-        if (kg == 0) {
-            store_block_row(0);
-            store_block_row(1);
-        } else {
-            store_block_row(2);
-            store_block_row(3);
-        }
-        return;
-    }
-#pragma unroll
-    for (int r = 0; r < RM; ++r) store_block_row(r);
+    finish_tile<DT, KG>(acc, out_rows, lds_words, kg, wave, lane, super, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
 }
 
 template <int DT, int KG>
 static void launch_tile(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb,
                           void* C, int64_t ldc, int64_t N, hipStream_t s)
 {
-    TileOrder order;
-    order.n_super = t.n;
-    order.n_slab = static_cast<int>((N + 127) / 128);
-    order.per_xcd = (order.n_super * order.n_slab + 7) / 8;
-    dim3 grid(static_cast<unsigned>(8 * order.per_xcd), 1, static_cast<unsigned>(ks));
+    const int n_super = t.n, n_slab = static_cast<int>((N + 127) / 128), per_xcd = (n_super * n_slab + 7) / 8;
+    dim3 grid(static_cast<unsigned>(8 * per_xcd), 1, static_cast<unsigned>(ks));
     const TileTables tab{t.step_cols, t.step_rows, t.step_base, d.perm, t.scratch};
     const uint32_t ldb_bytes = static_cast<uint32_t>(ldb * Elem<DT>::ES);
     auto* out = static_cast<typename Elem<DT>::Out*>(C);
     if (t.all_full)
-        hipLaunchKernelGGL((spmm_tile_kernel<DT, KG, true>), grid, dim3(256 * KG), 0, s, order.n_super, order.n_slab, order.per_xcd,
+        hipLaunchKernelGGL((spmm_tile_kernel<DT, KG, true>), grid, dim3(256 * KG), 0, s, n_super, n_slab, per_xcd,
                            static_cast<int>(N), t.super_rows, reinterpret_cast<const void*>(static_cast<uintptr_t>(t.full_steps)), B,
                            t.vals, ldb_bytes, static_cast<uint32_t>(d.K), tab, out, ldc);
     else
-        hipLaunchKernelGGL((spmm_tile_kernel<DT, KG, false>), grid, dim3(256 * KG), 0, s, order.n_super, order.n_slab, order.per_xcd,
+        hipLaunchKernelGGL((spmm_tile_kernel<DT, KG, false>), grid, dim3(256 * KG), 0, s, n_super, n_slab, per_xcd,
                            static_cast<int>(N), t.super_rows, static_cast<const void*>(t.step_ptr), B,
                            t.vals, ldb_bytes, static_cast<uint32_t>(d.K), tab, out, ldc);
 }

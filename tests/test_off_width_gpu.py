@@ -67,12 +67,13 @@ def test_tile_kernel_on_a_copy_of_b(shape, oracle_c):
         assert name.startswith("spmm_dense") and "_staged" in name, name
 
 
-@pytest.mark.parametrize("N,dtype", [(519, "bf16"), (1001, "e4m3"), (1400, "f16")])
-def test_per_row_kernel_on_a_copy_of_b(N, dtype, oracle_c):
+@pytest.mark.parametrize("shape", [(2048, 8200, 519, 0.02, "bf16"), (2048, 8200, 1001, 0.02, "e4m3"), (4096, 16384, 1400, 0.008, "f16")],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_per_row_kernel_on_a_copy_of_b(shape, oracle_c):
     """Block rows of similar length that use every row of B many times, rows of B off the cache lines: the per-row kernel
     runs on a padded copy (the last shape in column ranges: the area holds less than the whole of it)."""
-    M = K = 2048 if N < 1400 else 16384
-    w = random_csr(M, K, N, 0.1 if N < 1400 else 0.008, seed=N, values="smallint", b_dist="smallint")
+    M, K, N, density, dtype = shape
+    w = random_csr(M, K, N, density, seed=N, values="smallint", b_dist="smallint")
     w = w if dtype == "f16" else recast(w, dtype)
     for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
         _exact(w, oracle_c, ldb, ldc, shift)
