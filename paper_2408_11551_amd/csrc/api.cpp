@@ -21,6 +21,7 @@
 #include "kernels.h"
 #include "pack_layout.h"
 #include "preprocess.h"
+#include "quad_layout.h"
 
 struct smat_handle {
     smat::Csr csr;
@@ -60,6 +61,10 @@ struct smat_handle {
     uint64_t dense_slots = 0;
     bool dense_all_full = false;         // every step of every dense super row: all sixteen block rows, block columns 2q and 2q+1,
                                          // and every dense super row has the same number of steps
+    // The two-of-four form of the dense super rows (quad_layout.h), in place of the tables above; empty if it does not pay.
+    std::vector<int32_t> quad_ptr, quad_rows;
+    int max_quad_steps = 0;
+    int64_t quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr.back(); }
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
     smat::DeviceBcsr dev;                // launch over every block row
     smat::DeviceBcsr dev_rest;           // launch over the block rows the dense path does not cover
@@ -132,7 +137,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t perm, work, work_rest, slots, vals, pack_ptr, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
     size_t csr_row_ptr, csr_col_idx, csr_vals;
-    size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_scratch, total;
+    size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, total;
 };
 
 Layout make_layout(const smat_handle& h)
@@ -158,11 +163,14 @@ Layout make_layout(const smat_handle& h)
     l.csr_col_idx = take(nnz * sizeof(int32_t));
     l.csr_vals = take(nnz * sizeof(uint16_t));
     l.t_super = take(h.dense_super.size() * sizeof(int32_t));
+    const size_t quads = static_cast<size_t>(h.quad_steps());
     l.t_ptr = take(h.step_ptr.size() * sizeof(int32_t));
-    l.t_cols = take(h.step_cols.size() * sizeof(int32_t));
-    l.t_rows = take(h.step_rows.size() * sizeof(uint32_t));
-    l.t_base = take(h.step_base.size() * sizeof(uint32_t));
-    l.t_vals = take(static_cast<size_t>(h.dense_slots) * 1024);
+    l.t_cols = take(quads ? 0 : h.step_cols.size() * sizeof(int32_t));
+    l.t_rows = take(quads ? 0 : h.step_rows.size() * sizeof(uint32_t));
+    l.t_base = take(quads ? 0 : h.step_base.size() * sizeof(uint32_t));
+    l.t_vals = take(quads ? quads * 16384 : static_cast<size_t>(h.dense_slots) * 1024);
+    l.t_quad_rows = take(h.quad_rows.size() * sizeof(int32_t));
+    l.t_quad_index = take(quads * (h.elem_bytes == 1 ? 4096 : 2048));
     l.t_scratch = take(h.dense_super.empty() && !rows_may_stage(h) ? 0 : kTileScratchBytes * static_cast<size_t>(h.n_scratch_areas));
     l.total = off ? off : kAlign;
     return l;
@@ -256,6 +264,97 @@ int64_t block_row_nnz(const smat_handle& h, size_t br)
         nnz += h.csr.row_ptr[r + 1] - h.csr.row_ptr[r];
     }
     return nnz;
+}
+
+// The two-of-four form of the dense super rows: deals the columns of every super row into quads of which no row stores more than
+// two.  First fit: a quad opens with the first column left, takes of the next eight the one that shares the fewest rows
+// with it, then the first two that meet no row that has two already, among the next 256.  Columns of 10 % fill
+// give full quads within a few candidates, 20 % 3.5 columns per quad, 25 % 3.0 (256 rows; 0.2 ... 1.4 ms of a
+// thread per super row of 4096 columns).  Taken where it brings the steps down far enough: one covers the columns of two of the other
+// form's and moves 34 KiB where those move 48.
+void plan_quads(smat_handle& h, smat::Workers& workers)
+{
+    const int es = h.elem_bytes;
+    const int64_t cols = smat::quad_columns(es), K = h.csr.K;
+    const int64_t n = static_cast<int64_t>(h.dense_super.size()), steps = static_cast<int64_t>(h.step_rows.size());
+    if (n == 0 || static_cast<double>(steps) < smat::kDeepSteps * static_cast<double>(n)) return;
+    if (h.dense_slots < static_cast<uint64_t>(12 * steps)) return;                       // block rows that are not there cost nothing in the other form
+    if (smat::quad_fill_lds(K, 1, es) > smat::kQuadFillLds) return;
+    int64_t nnz = 0;
+    for (int32_t s : h.dense_super)
+        for (int64_t br = 16 * static_cast<int64_t>(s); br < std::min<int64_t>(h.bcsr.nbr, 16 * static_cast<int64_t>(s) + 16); ++br)
+            nnz += block_row_nnz(h, static_cast<size_t>(br));
+    if (static_cast<double>(nnz) > 0.27 * 256.0 * static_cast<double>(steps * (cols / 2))) return;
+    std::vector<std::vector<int32_t>> placed(static_cast<size_t>(n));
+    workers.ranges(n, 1, [&](int64_t n0, int64_t n1, int) {
+        struct Rows { uint64_t w[4]; };
+        std::vector<Rows> mask(static_cast<size_t>(K));
+        std::vector<int32_t> next(static_cast<size_t>(K) + 1);                           // columns left: next[0] the first, next[c + 1] the one after c; 0: none
+        for (int64_t x = n0; x < n1; ++x) {
+            std::fill(mask.begin(), mask.end(), Rows{{0, 0, 0, 0}});
+            const int64_t first = static_cast<int64_t>(h.dense_super[static_cast<size_t>(x)]) * 256;
+            for (int64_t i = first; i < std::min<int64_t>(h.csr.M, first + 256); ++i) {
+                const size_t r = static_cast<size_t>(h.bcsr.perm[static_cast<size_t>(i)]);
+                for (int64_t p = h.csr.row_ptr[r]; p < h.csr.row_ptr[r + 1]; ++p)
+                    mask[static_cast<size_t>(h.csr.col_idx[static_cast<size_t>(p)])].w[(i - first) >> 6] |= uint64_t{1} << ((i - first) & 63);
+            }
+            int32_t tail = 0;
+            for (int32_t c = 0; c < K; ++c) {
+                const Rows& m = mask[static_cast<size_t>(c)];
+                if (m.w[0] | m.w[1] | m.w[2] | m.w[3]) { next[static_cast<size_t>(tail)] = c + 1; tail = c + 1; }
+            }
+            next[static_cast<size_t>(tail)] = 0;
+            std::vector<int32_t>& out = placed[static_cast<size_t>(x)];
+            auto rows_of = [&](int32_t node) -> const Rows& { return mask[static_cast<size_t>(node) - 1]; };
+            while (next[0]) {
+                Rows one{{0, 0, 0, 0}}, two{{0, 0, 0, 0}};                               // rows with one entry in the quad, with two
+                int members = 0;
+                auto take = [&](int32_t before) {
+                    const int32_t node = next[static_cast<size_t>(before)];
+                    const Rows& m = rows_of(node);
+                    for (int k = 0; k < 4; ++k) { two.w[k] |= one.w[k] & m.w[k]; one.w[k] |= m.w[k]; }
+                    next[static_cast<size_t>(before)] = next[static_cast<size_t>(node)];
+                    out.push_back(node - 1);
+                    ++members;
+                };
+                take(0);
+                int32_t best = -1, before = 0;
+                int fewest = 257;
+                for (int c = 0; c < 8 && next[static_cast<size_t>(before)]; ++c) {
+                    const Rows& m = rows_of(next[static_cast<size_t>(before)]);
+                    int both = 0;
+                    for (int k = 0; k < 4; ++k) both += __builtin_popcountll(one.w[k] & m.w[k]);
+                    if (both < fewest) { fewest = both; best = before; }
+                    before = next[static_cast<size_t>(before)];
+                }
+                if (best >= 0) take(best);
+                before = 0;
+                for (int c = 0; c < 256 && members < 4 && next[static_cast<size_t>(before)]; ++c) {
+                    const Rows& m = rows_of(next[static_cast<size_t>(before)]);
+                    if ((two.w[0] & m.w[0]) | (two.w[1] & m.w[1]) | (two.w[2] & m.w[2]) | (two.w[3] & m.w[3])) before = next[static_cast<size_t>(before)];
+                    else take(before);
+                }
+                while (members < 4) { out.push_back(static_cast<int32_t>(K)); ++members; }
+            }
+        }
+    });
+    int64_t total = 0, most = 0;
+    for (const auto& out : placed) {
+        const int64_t q = (static_cast<int64_t>(out.size()) + cols - 1) / cols;
+        total += q;
+        most = std::max(most, q);
+    }
+    if (3 * total > 2 * steps || smat::quad_fill_lds(K, most, es) > smat::kQuadFillLds || most * cols > 65535) return;
+    if ((total + 1) * cols * 4 >= (int64_t{1} << 31)) return;
+    h.quad_ptr.assign(1, 0);
+    h.quad_rows.assign(static_cast<size_t>((total + 1) * cols), static_cast<int32_t>(K));
+    for (const auto& out : placed) {
+        int32_t* rows = h.quad_rows.data() + h.quad_ptr.back() * cols;
+        for (size_t e = 0; e < out.size(); ++e)
+            rows[static_cast<int64_t>(e) / cols * cols + smat::quad_table_word(es, static_cast<int>(static_cast<int64_t>(e) % cols))] = out[e];
+        h.quad_ptr.push_back(h.quad_ptr.back() + static_cast<int32_t>((static_cast<int64_t>(out.size()) + cols - 1) / cols));
+    }
+    h.max_quad_steps = static_cast<int>(most);
 }
 
 // Stored entries of block row br in the order of an entry row's slots (pack_layout.h): by
@@ -477,6 +576,7 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
             return fail(SMAT_ERR_UNSUPPORTED, e.what());
         }
         plan_dense_tiles(*h, workers);
+        plan_quads(*h, workers);
         *out = h.release();
         return SMAT_OK;
     } catch (const std::bad_alloc&) {
@@ -632,10 +732,15 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         if ((e = up(l.work, work.data(), work.size() * 4))) return hip_fail("copy launch table", e);
         if ((e = up(l.work_rest, work_rest.data(), work_rest.size() * 4))) return hip_fail("copy launch table", e);
         if ((e = up(l.t_super, h->dense_super.data(), h->dense_super.size() * 4))) return hip_fail("copy tiles", e);
-        if ((e = up(l.t_ptr, h->step_ptr.data(), h->step_ptr.size() * 4))) return hip_fail("copy tiles", e);
-        if ((e = up(l.t_cols, h->step_cols.data(), h->step_cols.size() * 4))) return hip_fail("copy tiles", e);
-        if ((e = up(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4))) return hip_fail("copy tiles", e);
-        if ((e = up(l.t_base, h->step_base.data(), h->step_base.size() * 4))) return hip_fail("copy tiles", e);
+        const bool quads = h->quad_steps() > 0;
+        if ((e = up(l.t_ptr, quads ? h->quad_ptr.data() : h->step_ptr.data(), h->step_ptr.size() * 4))) return hip_fail("copy tiles", e);
+        if (quads) {
+            if ((e = up(l.t_quad_rows, h->quad_rows.data(), h->quad_rows.size() * 4))) return hip_fail("copy tiles", e);
+        } else {
+            if ((e = up(l.t_cols, h->step_cols.data(), h->step_cols.size() * 4))) return hip_fail("copy tiles", e);
+            if ((e = up(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4))) return hip_fail("copy tiles", e);
+            if ((e = up(l.t_base, h->step_base.data(), h->step_base.size() * 4))) return hip_fail("copy tiles", e);
+        }
         if ((e = up(l.slots, slots.data(), slots.size() * 4))) return hip_fail("copy slot tables", e);
         if ((e = up(l.pack_ptr, h->pack_ptr.data(), h->pack_ptr.size() * 4))) return hip_fail("copy pack offsets", e);
         if ((e = up(l.vals_off, h->vals_off.data(), h->vals_off.size() * 4))) return hip_fail("copy value offsets", e);
@@ -675,6 +780,9 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.step_rows = reinterpret_cast<const uint32_t*>(base + l.t_rows);
         tiles.step_base = reinterpret_cast<const uint32_t*>(base + l.t_base);
         tiles.vals = base + l.t_vals;
+        tiles.quad_rows = reinterpret_cast<const int32_t*>(base + l.t_quad_rows);
+        tiles.quad_index = reinterpret_cast<const uint8_t*>(base + l.t_quad_index);
+        tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
         tiles.scratch = nullptr;           // a call takes the area of its stream
         tiles.scratch_bytes = 0;
         tiles.n = static_cast<int32_t>(h->dense_super.size());
@@ -690,10 +798,11 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
             return hip_fail("zero block values", e);
         if ((e = smat::launch_bcsr_fill(d, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.vals, h->elem_bytes, s)))
             return hip_fail("fill block values", e);
-        if ((e = smat::launch_fill_zero(base + l.t_vals, static_cast<size_t>(h->dense_slots) * 64, s)))
-            return hip_fail("zero tile values", e);
-        if ((e = smat::launch_dense_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s)))
-            return hip_fail("fill tile values", e);
+        if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_rows - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
+        e = quads ? smat::launch_quad_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
+                                           h->elem_bytes, h->max_quad_steps, s)
+                  : smat::launch_dense_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);
+        if (e) return hip_fail("fill tile values", e);
         if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("bind synchronize", e);
         {
             // set-up is the place to find this device's copy of the static area (smat_spmm_static)
@@ -869,8 +978,9 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const int64_t n = std::min(chunk, N - c0);
             const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
             const int ks = smat::dense_split(tiles, n);
-            const double step_us = h->elem_bytes == 1 ? 1.0 : 0.7;     // an 8-bit step covers twice the block columns
-            t_tiles += std::ceil(n_tiles * ks / 256.0) * (tiles.mean_steps / ks * step_us + 4.0);
+            // an 8-bit step covers twice the block columns
+            const double walk_us = tiles.n_quad_steps ? 0.45 * tiles.n_quad_steps / tiles.n : tiles.mean_steps * (h->elem_bytes == 1 ? 1.0 : 0.7);
+            t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + 4.0);
             if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 4.0e6;     // partial tiles out and in again
             if (!in_pieces) t_tiles += 3.0 + 2.0 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes) / 4.0e6;  // the copy of B
         }

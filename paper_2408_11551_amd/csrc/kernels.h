@@ -59,7 +59,14 @@ struct DenseTiles {
                                            // steps: step q of super row i is step i full_steps + q and its values start at slot
                                            // 16 (i full_steps + q), so the kernel needs none of the step tables
     int32_t full_steps = 0;
+    // The two-of-four form (quad_layout.h, kernels_quads.hip), n_quad_steps > 0: step_ptr counts its steps, vals holds 16 KiB per step, the
+    // step_* tables are not there, and mean_steps is still what the other form would have.
+    const int32_t* quad_rows = nullptr;    // [quad_columns * (n_quad_steps + 1)] rows of B of a step's panel; the last step names none
+    const uint8_t* quad_index = nullptr;   // [2 or 4 KiB * n_quad_steps] positions of the values
+    int32_t n_quad_steps = 0;
 };
+
+constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave groups share a tile
 
 // Sets n16 16-byte words at dst to zero.
 int launch_fill_zero(void* dst, size_t n16, void* stream);
@@ -90,6 +97,13 @@ int launch_spmm_i8(const DeviceBcsr& d, const void* B, int64_t ldb, void* C, int
 // Scatters the CSR values of the dense super rows into the tile layout (vals zeroed before).
 int launch_dense_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* csr_row_ptr,
                       const int32_t* csr_col_idx, const uint16_t* csr_vals, void* vals_out, int elem_bytes, void* stream);
+
+// The same for the two-of-four form: values and positions.  max_steps: of any super row.
+int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
+                     const uint16_t* csr_vals, void* vals_out, void* index_out, int elem_bytes, int max_steps, void* stream);
+// Its part of launch_spmm_dense, the partial tiles of ks > 1 workgroups per tile left to the caller.
+void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
+                       int64_t N, void* stream);
 
 // Workgroups per 128-column tile the dense launch would use for this N (1: no split).
 int dense_split(const DenseTiles& t, int64_t N);

@@ -582,14 +582,15 @@ static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const vo
     using Acc = typename Elem<DT>::Acc;
     const int vec_store = (ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 && N % 4 == 0) ? 1 : 0;
     // long super rows: two wave groups per workgroup; short ones: one group, two workgroups per CU
-    const bool deep = t.mean_steps >= 32.0;
+    const bool deep = t.mean_steps >= kDeepSteps;
     const int ks = dense_split(t, N);
     static thread_local char name[40];
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
     if (ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d", type, deep ? 2 : 1, ks);
     else snprintf(name, sizeof(name), "spmm_dense_%s_g%d", type, deep ? 2 : 1);
     *variant = name;
-    if (deep) launch_tile<DT, 2>(d, t, ks, B, ldb, C, ldc, N, s);
+    if (t.n_quad_steps > 0) launch_quad_tiles(d, t, DT, ks, B, ldb, C, ldc, N, s);
+    else if (deep) launch_tile<DT, 2>(d, t, ks, B, ldb, C, ldc, N, s);
     else launch_tile<DT, 1>(d, t, ks, B, ldb, C, ldc, N, s);
     if (ks > 1)
         hipLaunchKernelGGL((dense_reduce_kernel<Acc, Out>), dim3(static_cast<unsigned>(t.n), static_cast<unsigned>((N + 127) / 128), 8),

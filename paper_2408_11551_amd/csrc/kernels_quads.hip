@@ -1,0 +1,376 @@
+// HIP kernel for gfx950: the tile kernel of kernels_dense.hip on the matrix units' two-of-four form.
+//
+// A pruned weight matrix fills a tenth of its blocks' entries or so, and the tile kernel multiplies the zeros as well.
+// The matrix units have a form (v_smfmac) that takes, of every four consecutive k of a row of the left operand, two values and
+// their positions, and covers twice the k extent in the time of the ordinary instruction (four times for the 8-bit
+// floats).  Which column of A sits in which k slot is free here -- the panel of B is brought into LDS row by
+// row -- so the columns of a super row are dealt into groups of four ("quads") in which no row has more than two stored entries
+// (plan_quads in api.cpp).  At random that succeeds for practically all columns up to 15 % fill (256 rows); at 20 %
+// a quad gets 3.5 columns on average, at 25 % 3.0.  Products and sums are those of the ordinary instruction.
+//
+// One step covers 64 k slots (8-bit types: 128), four bytes of which are a quad's: 16 KiB of B in LDS, 16 KiB of values (two of
+// four: 1 KiB per block row as in the other kernel) and 2 KiB (4 KiB) of positions.  The work split is the other kernel's with two
+// groups: a workgroup takes 256 rows x 128 columns, group 0 the even steps and group 1 the odd ones, a wave four
+// block rows x 128 columns.  Per step a wave issues as many matrix instructions as there, for twice (four times) the
+// matrix, and reads the panel with the same transposing reads; the loads of two steps are in flight, spread
+// between the matrix instructions.
+//
+// What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.
+#include <algorithm>
+#include <type_traits>
+
+#include <hip/hip_runtime.h>
+
+#include "kernels.h"
+#include "mfma_types.h"
+#include "quad_layout.h"
+#include "tile_common.h"
+
+namespace smat {
+
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+// 16 x 64 (8-bit types: 16 x 128) of A', two of every four k, times the same extent of B.  index: two bits per value; of a
+// 16-bit type's eight values in half HALF of the word.
+template <int DT, int HALF>
+__device__ __forceinline__ typename Elem<DT>::Acc smfmac(u32x4 a, u32x8 b, typename Elem<DT>::Acc c, uint32_t index)
+{
+    const int ix = static_cast<int>(index);
+    if constexpr (DT == kBF16)
+        return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x16, b), c, ix, 0, HALF);
+    else if constexpr (DT == kF16)
+        return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, ix, 0, HALF);
+    else if constexpr (DT == kE4M3)
+        return __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
+    else if constexpr (DT == kE5M2)
+        return __builtin_amdgcn_smfmac_f32_16x16x128_bf8_bf8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
+    else
+        return __builtin_amdgcn_smfmac_i32_16x16x128_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
+}
+
+// the four reads have returned once at most YOUNGER later LDS reads are outstanding
+template <int YOUNGER>
+__device__ __forceinline__ void lds_four_done(u32x2_t (&v)[4])
+{
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]) : "n"(YOUNGER));
+}
+
+// What the kernel needs later than its first loads.
+struct QuadTables {
+    const uint8_t* index;
+    const int32_t* perm;
+    void* scratch;
+    int no_step;                       // number of the step that names no row of B
+};
+
+template <int DT>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(2, 2)))
+void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t* __restrict__ super_rows,
+                           const int32_t* __restrict__ step_ptr, const void* __restrict__ B, const int32_t* __restrict__ quad_rows,
+                           uint32_t ldb_bytes, uint32_t K, const void* __restrict__ tile_vals, QuadTables tab,
+                           typename Elem<DT>::Out* __restrict__ C, int64_t ldc)
+{
+    using Acc = typename Elem<DT>::Acc;
+    constexpr int ES = Elem<DT>::ES;
+    constexpr int NT = 8;                          // groups of 16 columns: 128 columns per tile
+    constexpr int RM = 4;                          // block rows per wave
+    constexpr int RD = 3;                          // ring depth: panels in LDS, values and tables in registers
+    constexpr int KG = 2;                          // groups of four waves
+    constexpr uint32_t kPanel = 16384;             // 64 rows of 256 bytes, or 128 rows of 128
+    constexpr uint32_t kTable = quad_columns(ES) * 4u;
+    constexpr int IB = ES == 2 ? 8 : 16;           // bytes of positions per lane and step (four block rows)
+    constexpr int ID = IB / 4;
+    // two rings of panels (96 KiB); the hand-over at the end needs 128 KiB
+    __shared__ u32x4 lds_words[8192];
+
+    int sidx, slab;
+    if (!tile_of_workgroup(n_super, n_slab, per_xcd, sidx, slab)) return;
+    const int tid = threadIdx.x & 255;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 8);
+    const int i = lane & 15, g = lane >> 4;
+    const int super = super_rows[sidx];
+    const int n0 = slab * 128;
+    const int ks = static_cast<int>(gridDim.z);
+    const int q_first = step_ptr[sidx], q_last = step_ptr[sidx + 1];
+    const int per = (q_last - q_first + ks - 1) / ks;
+    const int q0 = min(q_first + static_cast<int>(blockIdx.z) * per, q_last);
+    const int nq = min(q0 + per, q_last) - q0;
+
+    const uint32_t b_bytes = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
+        static_cast<int>(K > 0u ? (K - 1u) * ldb_bytes + ((static_cast<uint32_t>(N) * ES + 15u) & ~15u) : 0u)));
+    const __amdgpu_buffer_rsrc_t b_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(B), 0, static_cast<int>(b_bytes), kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rows_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int32_t*>(quad_rows), 0, static_cast<int>((static_cast<uint32_t>(tab.no_step) + 1u) * kTable), kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<uint8_t*>(const_cast<void*>(tile_vals)) + static_cast<size_t>(q0) * 16384, 0, max(nq, 0) * 16384, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t ix_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(tab.index) + static_cast<size_t>(q0) * (256 * IB), 0, max(nq, 0) * (256 * IB), kRsrcFlags);
+
+    // The panel lies in LDS as in the other kernel (see there for the placement of the pieces), with twice the rows.  Load e of a wave
+    // (e < 4) brings panel rows 16 e + 4 wave + lane / 16 (8-bit types: 32 wave + 8 e + lane / 8), lane l the piece l % 16 (l % 8).
+    uint32_t st_off[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int piece = ES == 2 ? (lane & 15) ^ (2 * ((lane >> 4) & 3)) ^ (8 * ((wave >> 1) & 1)) : (lane & 7) ^ (4 * e + (lane >> 4));
+        const int col = n0 + (16 / ES) * piece;
+        st_off[e] = col < N ? static_cast<uint32_t>(col) * ES : kOutOfRange;
+    }
+    const uint32_t panels = lds_offset_of(lds_words) + static_cast<uint32_t>(kg) * (RD * kPanel);
+    auto lds_of_load = [&](int buf, int e) {
+        return panels + static_cast<uint32_t>(buf) * kPanel + (ES == 2 ? 4096u * e + 1024u * wave : 4096u * wave + 1024u * e);
+    };
+    // reads: 16-bit types two per 32 rows (+ 1024 bytes), twice (+ 8192); 8-bit types one per 32 rows (+ 4096)
+    uint32_t tr_addr[NT];
+#pragma unroll
+    for (int x = 0; x < NT; ++x) {
+        if constexpr (ES == 2) {
+            const int e = i >> 2, qq = i & 3;
+            tr_addr[x] = panels + (8 * g + e) * 256u + 32u * (x ^ e ^ (4 * (g & 1))) + 16u * (qq >> 1) + 8u * (qq & 1);
+        } else {
+            const int e = i >> 1, qq = i & 1;
+            tr_addr[x] = panels + (8 * g + e) * 128u + 16u * (x ^ (4 * (g & 1) + (e >> 1))) + 8u * qq;
+        }
+    }
+
+    // Loads of step gs of this wave group = step kg + 2 gs of the tile.  A step past the end reads values out of range (zeros) and
+    // the rows of no_step, whose panel is zeros.
+    auto is_live = [&](int gs) { return kg + KG * gs < nq; };
+    auto step_of = [&](int gs) { return static_cast<uint32_t>(is_live(gs) ? kg + KG * gs : 0); };
+    const uint32_t table_lane = ES == 2 ? (4u * wave + (lane >> 4)) * 16u : (8u * wave + (lane >> 3)) * 16u;
+    // which rows of B the lane fetches for step gs, one per load
+    auto load_table = [&](int gs) {
+        const uint32_t q = static_cast<uint32_t>(is_live(gs) ? q0 + kg + KG * gs : tab.no_step);
+        return buf_load16(rows_rsrc, table_lane, q * kTable);
+    };
+    auto load_panel = [&](const u32x4& rows, int buf, int e) {
+        load_to_lds16((lds_void*)(uintptr_t)lds_of_load(buf, e), b_rsrc, __umul24(rows[e], ldb_bytes) + st_off[ES == 2 ? 0 : e & 1], 0u);
+    };
+    auto load_a = [&](int gs, int r) {
+        const uint32_t voff = static_cast<uint32_t>(lane) * 16u | (is_live(gs) ? 0u : kOutOfRange);
+        return buf_load16(a_rsrc, voff, step_of(gs) * 16384u + static_cast<uint32_t>(RM * wave + r) * 1024u);
+    };
+    auto load_index = [&](int gs, uint32_t (&ix)[ID]) {
+        const uint32_t voff = static_cast<uint32_t>(lane) * IB | (is_live(gs) ? 0u : kOutOfRange);
+        const uint32_t soff = step_of(gs) * (256u * IB) + static_cast<uint32_t>(wave) * (64u * IB);
+        if constexpr (ES == 2) {
+            const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(ix_rsrc, voff, soff, 0);
+            ix[0] = static_cast<uint32_t>(v[0]);
+            ix[1] = static_cast<uint32_t>(v[1]);
+        } else {
+            const u32x4 v = buf_load16(ix_rsrc, voff, soff);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) ix[x] = v[x];
+        }
+    };
+
+    Acc acc[RM][NT];
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+#pragma unroll
+        for (int x = 0; x < NT; ++x) acc[r][x] = Acc{0, 0, 0, 0};
+
+    if (nq > 0) {
+        u32x4 a[RD][RM], table[RD];
+        uint32_t ix[RD][ID];
+        table[0] = load_table(0);
+        table[1] = load_table(1);
+        __builtin_amdgcn_sched_barrier(0);
+        // what steps -2 and -1 of the loop would have issued, in the loop's order
+#pragma unroll
+        for (int h = 0; h < RD - 1; ++h) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) load_panel(table[h], h, e);
+#pragma unroll
+            for (int r = 0; r < RM; ++r) a[h][r] = load_a(h, r);
+            load_index(h, ix[h]);
+            table[(h + 2) % RD] = load_table(h + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int gsteps = (nq + KG - 1) / KG;
+        const int iters = gsteps / RD, rem = gsteps % RD;
+        // step s of the group, s = u (mod RD).  table[(u + 2) % RD] names the rows of step s + 2; the table of step s + 4 takes the
+        // place of step s + 1's, which was used a step ago.
+        auto step = [&](auto u_, int s) {
+            constexpr int u = decltype(u_)::value;
+            constexpr int next = (u + 2) % RD;
+            // all but the youngest ten loads (those of the step before) have arrived: panel, values and positions of this step, and the table
+            // its loads below are made from
+            asm volatile("s_waitcnt vmcnt(10)");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            u32x2_t b[2][4];
+            auto read_four = [&](int x, u32x2_t (&v)[4]) {
+                if constexpr (ES == 2) {
+                    v[0] = lds_read_tr<kPanel * u>(tr_addr[x]);
+                    v[1] = lds_read_tr<kPanel * u + 1024>(tr_addr[x]);
+                    v[2] = lds_read_tr<kPanel * u + 8192>(tr_addr[x]);
+                    v[3] = lds_read_tr<kPanel * u + 8192 + 1024>(tr_addr[x]);
+                } else {
+                    v[0] = lds_read_tr8<kPanel * u>(tr_addr[x]);
+                    v[1] = lds_read_tr8<kPanel * u + 4096>(tr_addr[x]);
+                    v[2] = lds_read_tr8<kPanel * u + 8192>(tr_addr[x]);
+                    v[3] = lds_read_tr8<kPanel * u + 8192 + 4096>(tr_addr[x]);
+                }
+            };
+            read_four(0, b[0]);
+#pragma unroll
+            for (int x = 0; x < NT; ++x) {
+                if (x + 1 < NT) {
+                    read_four((x + 1) & 7, b[(x + 1) & 1]);
+                    lds_four_done<4>(b[x & 1]);
+                } else {
+                    lds_four_done<0>(b[x & 1]);
+                }
+                const u32x2_t(&v)[4] = b[x & 1];
+                const u32x8 operand = u32x8{v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], v[3][0], v[3][1]};
+                if constexpr (ES == 2) {
+                    acc[0][x] = smfmac<DT, 0>(a[u][0], operand, acc[0][x], ix[u][0]);
+                    acc[1][x] = smfmac<DT, 1>(a[u][1], operand, acc[1][x], ix[u][0]);
+                    acc[2][x] = smfmac<DT, 0>(a[u][2], operand, acc[2][x], ix[u][1]);
+                    acc[3][x] = smfmac<DT, 1>(a[u][3], operand, acc[3][x], ix[u][1]);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<DT, 0>(a[u][r], operand, acc[r][x], ix[u][r]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (x < 4) {
+                    load_panel(table[next], next, x);
+                } else if (x == 4) {
+                    a[next][0] = load_a(s + 2, 0);
+                } else if (x == 5) {
+                    a[next][1] = load_a(s + 2, 1);
+                    a[next][2] = load_a(s + 2, 2);
+                } else if (x == 6) {
+                    a[next][3] = load_a(s + 2, 3);
+                    load_index(s + 2, ix[next]);
+                } else {
+                    table[(u + 1) % RD] = load_table(s + 4);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        static_assert(RD == 3, "the loop body names its three steps");
+        for (int it = 0; it < iters; ++it) {
+            step(std::integral_constant<int, 0>{}, RD * it);
+            step(std::integral_constant<int, 1>{}, RD * it + 1);
+            step(std::integral_constant<int, 2>{}, RD * it + 2);
+        }
+        if (rem >= 1) step(std::integral_constant<int, 0>{}, RD * iters);
+        if (rem >= 2) step(std::integral_constant<int, 1>{}, RD * iters + 1);
+        // nothing may still be on its way into LDS when the buffers get another use or the workgroup ends
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)");
+    }
+    int32_t out_rows[RM][4] = {};
+    finish_tile<DT, KG>(acc, out_rows, lds_words, kg, wave, lane, super, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
+}
+
+template <int DT>
+static void launch_quad_dtype(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
+                              int64_t N, hipStream_t s)
+{
+    const int n_super = t.n, n_slab = static_cast<int>((N + 127) / 128), per_xcd = (n_super * n_slab + 7) / 8;
+    const dim3 grid(static_cast<unsigned>(8 * per_xcd), 1, static_cast<unsigned>(ks));
+    const QuadTables tab{t.quad_index, d.perm, t.scratch, t.n_quad_steps};
+    hipLaunchKernelGGL((spmm_quad_tile_kernel<DT>), grid, dim3(512), 0, s, n_super, n_slab, per_xcd, static_cast<int>(N), t.super_rows,
+                       t.step_ptr, B, t.quad_rows, static_cast<uint32_t>(ldb * Elem<DT>::ES), static_cast<uint32_t>(d.K), t.vals, tab,
+                       static_cast<typename Elem<DT>::Out*>(C), ldc);
+}
+
+void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
+                       int64_t N, void* stream)
+{
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (dtype) {
+    case kF16: return launch_quad_dtype<kF16>(d, t, ks, B, ldb, C, ldc, N, s);
+    case kBF16: return launch_quad_dtype<kBF16>(d, t, ks, B, ldb, C, ldc, N, s);
+    case kE4M3: return launch_quad_dtype<kE4M3>(d, t, ks, B, ldb, C, ldc, N, s);
+    case kE5M2: return launch_quad_dtype<kE5M2>(d, t, ks, B, ldb, C, ldc, N, s);
+    default: return launch_quad_dtype<kI8>(d, t, ks, B, ldb, C, ldc, N, s);
+    }
+}
+
+// Bind-time scatter: one workgroup per block row of a quad super row, sixteen threads per row.  Shared memory: the place (step,
+// panel row) of every column that the super row stores, and per row a bit for every place that it fills.
+template <typename T>
+__global__ __launch_bounds__(256)
+void quad_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __restrict__ csr_row_ptr, const int32_t* __restrict__ csr_col_idx,
+                      const uint16_t* __restrict__ csr_vals, T* __restrict__ vals_out, uint8_t* __restrict__ index_out, int place_bytes, int words)
+{
+    constexpr int ES = sizeof(T), COLS = quad_columns(ES), EL = 16 / ES;
+    extern __shared__ uint32_t shared[];
+    uint16_t* place = reinterpret_cast<uint16_t*>(shared);
+    uint32_t* bits = shared + place_bytes / 4;                      // [16][words]
+    const int sidx = static_cast<int>(blockIdx.x >> 4), j = static_cast<int>(blockIdx.x & 15);
+    const int q0 = t.step_ptr[sidx], nq = t.step_ptr[sidx + 1] - q0;
+    for (int x = threadIdx.x; x < 16 * words; x += 256) bits[x] = 0;
+    for (int x = threadIdx.x; x < nq * COLS; x += 256) {
+        const int32_t row = t.quad_rows[static_cast<size_t>(q0) * COLS + x];
+        if (row < d.K) place[row] = static_cast<uint16_t>(x / COLS * COLS + quad_panel_row(ES, x % COLS));
+    }
+    __syncthreads();
+    const int rr = static_cast<int>(threadIdx.x >> 4), part = static_cast<int>(threadIdx.x & 15);
+    const int64_t at = (static_cast<int64_t>(t.super_rows[sidx]) * 16 + j) * 16 + rr;
+    int64_t p0 = 0, p1 = 0;
+    if (at < d.M) {
+        const int64_t r = d.perm[at];
+        p0 = csr_row_ptr[r];
+        p1 = csr_row_ptr[r + 1];
+    }
+    uint32_t* mine = bits + rr * words;
+    for (int64_t p = p0 + part; p < p1; p += 16) {
+        const uint32_t pos = place[csr_col_idx[p]];
+        atomicOr(&mine[pos >> 5], 1u << (pos & 31));
+    }
+    __syncthreads();
+    for (int64_t p = p0 + part; p < p1; p += 16) {
+        const uint32_t pos = place[csr_col_idx[p]];
+        const uint32_t quad = mine[pos >> 5] >> (pos & 28) & 15u, q = pos / COLS;
+        const QuadSlot slot = quad_slot(ES, static_cast<int>(pos % COLS));
+        const int second = quad == 8u ? 1 : __popc(quad & ((1u << (pos & 3)) - 1u));
+        const size_t unit = (static_cast<size_t>(q0) + q) * 16 + static_cast<size_t>(j);
+        vals_out[(unit * 64 + static_cast<size_t>(16 * slot.lane_group + rr)) * EL + static_cast<size_t>(2 * slot.pair + second)] =
+            static_cast<T>(csr_vals[p]);
+    }
+    // positions, a lane's share (EL / 2 quads) at a time
+    for (int x = part; x < nq * 4; x += 16) {
+        const int q = x >> 2, group = x & 3;
+        uint32_t word = 0;
+        for (int pair = 0; pair < EL / 2; ++pair) {
+            const uint32_t pos = static_cast<uint32_t>(q * COLS + quad_first_row(ES, group, pair));
+            const uint32_t quad = mine[pos >> 5] >> (pos & 28) & 15u;
+            // ascending, whatever the quad holds: a single entry takes the first value and leaves position 3 to the second, unless it is in position 3 itself
+            const uint32_t lo = quad == 0u || quad == 8u ? 0u : static_cast<uint32_t>(__ffs(quad)) - 1u;
+            const uint32_t rest = quad & (quad - 1u);
+            const uint32_t hi = rest ? static_cast<uint32_t>(__ffs(rest)) - 1u : 3u;
+            word |= (lo | hi << 2) << (4 * pair);
+        }
+        const size_t lane_at = ((static_cast<size_t>(q0) + q) * 4 + static_cast<size_t>(j >> 2)) * 64 + static_cast<size_t>(16 * group + rr);
+        if constexpr (ES == 2) reinterpret_cast<uint16_t*>(index_out)[lane_at * 4 + (j & 3)] = static_cast<uint16_t>(word);
+        else reinterpret_cast<uint32_t*>(index_out)[lane_at * 4 + (j & 3)] = word;
+    }
+}
+
+int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
+                     const uint16_t* csr_vals, void* vals_out, void* index_out, int elem_bytes, int max_steps, void* stream)
+{
+    if (t.n == 0) return 0;
+    const int place_bytes = static_cast<int>(quad_place_bytes(d.K)), words = max_steps * quad_columns(elem_bytes) / 32;
+    const size_t lds = quad_fill_lds(d.K, max_steps, elem_bytes);
+    const dim3 grid(static_cast<unsigned>(t.n) * 16);
+    if (elem_bytes == 1)
+        hipLaunchKernelGGL(quad_fill_kernel<uint8_t>, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx,
+                           csr_vals, static_cast<uint8_t*>(vals_out), static_cast<uint8_t*>(index_out), place_bytes, words);
+    else
+        hipLaunchKernelGGL(quad_fill_kernel<uint16_t>, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx,
+                           csr_vals, static_cast<uint16_t*>(vals_out), static_cast<uint8_t*>(index_out), place_bytes, words);
+    return static_cast<int>(hipGetLastError());
+}
+
+}  // namespace smat
