@@ -270,8 +270,7 @@ int64_t block_row_nnz(const smat_handle& h, size_t br)
 // two.  First fit: a quad opens with the first column left, takes of the next eight the one that shares the fewest rows
 // with it, then the first two that meet no row that has two already, among the next 256.  Columns of 10 % fill
 // give full quads within a few candidates, 20 % 3.5 columns per quad, 25 % 3.0 (256 rows; 0.2 ... 1.4 ms of a
-// thread per super row of 4096 columns).  Taken where it brings the steps down far enough: one covers the columns of two of the other
-// form's and moves 34 KiB where those move 48.
+// thread per super row of 4096 columns).  Taken where it brings the steps down far enough.
 void plan_quads(smat_handle& h, smat::Workers& workers)
 {
     const int es = h.elem_bytes;
@@ -284,7 +283,11 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
     for (int32_t s : h.dense_super)
         for (int64_t br = 16 * static_cast<int64_t>(s); br < std::min<int64_t>(h.bcsr.nbr, 16 * static_cast<int64_t>(s) + 16); ++br)
             nnz += block_row_nnz(h, static_cast<size_t>(br));
-    if (static_cast<double>(nnz) > 0.27 * 256.0 * static_cast<double>(steps * (cols / 2))) return;
+    // What a step costs against one of the other form, measured: fp16 / bf16 0.43 us and 0.365, int8 0.37 and 0.27, the 8-bit floats,
+    // which take twice the matrix instructions there, 0.37 and 0.55.
+    const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : 1.0) * static_cast<double>(steps);
+    // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
+    if (static_cast<double>(nnz) > (es == 2 ? 0.3 : h.dtype == SMAT_I8 ? 0.27 : 0.4) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
     std::vector<std::vector<int32_t>> placed(static_cast<size_t>(n));
     workers.ranges(n, 1, [&](int64_t n0, int64_t n1, int) {
         struct Rows { uint64_t w[4]; };
@@ -344,7 +347,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
         total += q;
         most = std::max(most, q);
     }
-    if (3 * total > 2 * steps || smat::quad_fill_lds(K, most, es) > smat::kQuadFillLds || most * cols > 65535) return;
+    if (static_cast<double>(total) > most_steps || smat::quad_fill_lds(K, most, es) > smat::kQuadFillLds || most * cols > 65535) return;
     if ((total + 1) * cols * 4 >= (int64_t{1} << 31)) return;
     h.quad_ptr.assign(1, 0);
     h.quad_rows.assign(static_cast<size_t>((total + 1) * cols), static_cast<int32_t>(K));
@@ -967,26 +970,29 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             tiles.scratch_bytes = scratch_bytes > st.bytes ? scratch_bytes - st.bytes : 0;
         }
     }
-    // It also has to pay: a tile walks its steps at about
-    // 0.7 us each with little to overlap them, so few tiles leave most of the chip idle, while
-    // the per-row kernel fetches every occupied column's row of B again for every block row but
-    // spreads that over all compute units (about 10 TB/s of L1 fills).  Both estimates are
-    // measured rates; the faster path is taken.
+    // It also has to pay: few tiles leave most of the chip idle, while the per-row kernel fetches every occupied column's row
+    // of B again for every block row but spreads that over all compute units.  The estimates are measured rates, fitted on
+    // bands and random matrices of 1000 ... 65536 rows and 5-100 % fill at N = 8 ... 2048, 16-bit and 8-bit; the faster path is taken.
     if (use_tiles && h->dense_mode == 0) {
         double t_tiles = 0;
         for (int64_t c0 = 0; c0 < N; c0 += chunk) {
             const int64_t n = std::min(chunk, N - c0);
             const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
             const int ks = smat::dense_split(tiles, n);
-            // an 8-bit step covers twice the block columns
-            const double walk_us = tiles.n_quad_steps ? 0.45 * tiles.n_quad_steps / tiles.n : tiles.mean_steps * (h->elem_bytes == 1 ? 1.0 : 0.7);
-            t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + 4.0);
-            if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 4.0e6;     // partial tiles out and in again
+            // us per step of a tile, alone on its compute unit (an 8-bit step covers twice the block columns)
+            const double walk_us = tiles.n_quad_steps ? (h->elem_bytes == 1 ? 0.37 : 0.43) * tiles.n_quad_steps / tiles.n
+                                                      : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
+            t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (tiles.n_quad_steps ? 6.0 : 4.0)) + 1.5;
+            if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 8.0e6;     // partial tiles out and in again
             if (!in_pieces) t_tiles += 3.0 + 2.0 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes) / 4.0e6;  // the copy of B
         }
-        // (two bytes per value also for the 8-bit types: on block-dense rows the per-row kernel did not
-        // get faster with them -- 35.6 us against 35 on the band workload -- while the tile kernel did)
-        const double t_rows = static_cast<double>(h->dense_columns) * static_cast<double>((N + 15) / 16 * 16) * 2.0 / 10.0e6 + 4.0;
+        // rows of B at 22 TB/s over all compute units (in the shorter rows of the 8-bit types 19 and 13; a third less where
+        // they lie off the cache lines), values and C at 7
+        const double pieces = static_cast<double>(h->dense_columns) * static_cast<double>((N + 15) / 16 * 16 * h->elem_bytes);
+        const double groups = static_cast<double>(h->bcsr.nbr) * static_cast<double>((N * h->elem_bytes + 255) / 256);
+        const double rate = (h->elem_bytes == 2 ? 22.0e6 : N > 128 ? 19.0e6 : 13.0e6) * ((ldb * h->elem_bytes) % 128 == 0 ? 1.0 : 0.75);
+        const double t_rows = 4.0 + pieces / rate * std::max(1.0, 256.0 / groups) +
+                              (static_cast<double>(h->dense_columns) * 16.0 * h->elem_bytes + static_cast<double>(h->csr.M) * N * 4.0) / 7.0e6;
         use_tiles = t_tiles <= t_rows;
     }
     if (use_tiles && hard_limit && in_pieces) {

@@ -182,51 +182,55 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
         table[0] = load_table(0);
         table[1] = load_table(1);
         __builtin_amdgcn_sched_barrier(0);
-        // what steps -2 and -1 of the loop would have issued, in the loop's order
+        // what the loop would have issued before step 0, in its order
 #pragma unroll
         for (int h = 0; h < RD - 1; ++h) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) load_panel(table[h], h, e);
+            // (what does not depend on the table first)
 #pragma unroll
             for (int r = 0; r < RM; ++r) a[h][r] = load_a(h, r);
             load_index(h, ix[h]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) load_panel(table[h], h, e);
             table[(h + 2) % RD] = load_table(h + 2);
             __builtin_amdgcn_sched_barrier(0);
         }
         const int gsteps = (nq + KG - 1) / KG;
         const int iters = gsteps / RD, rem = gsteps % RD;
-        // step s of the group, s = u (mod RD).  table[(u + 2) % RD] names the rows of step s + 2; the table of step s + 4 takes the
-        // place of step s + 1's, which was used a step ago.
+        // Step s of the group, s = u (mod RD).  Its panel is known to be there, and the operand of its first group of columns has been asked
+        // for, when it begins: what the step waits for lies before the matrix instructions of its last group, so that
+        // these, and not an idle matrix unit, cover the first reads of the panel of step s + 1.
+        // table[(u + 2) % RD] names the rows of step s + 2; the table of step s + 4 takes the place of step s + 1's.
+        u32x2_t b[2][4];
+        auto read_four = [&](auto u_, int x, u32x2_t (&v)[4]) {
+            constexpr int u = decltype(u_)::value;
+            if constexpr (ES == 2) {
+                v[0] = lds_read_tr<kPanel * u>(tr_addr[x]);
+                v[1] = lds_read_tr<kPanel * u + 1024>(tr_addr[x]);
+                v[2] = lds_read_tr<kPanel * u + 8192>(tr_addr[x]);
+                v[3] = lds_read_tr<kPanel * u + 8192 + 1024>(tr_addr[x]);
+            } else {
+                v[0] = lds_read_tr8<kPanel * u>(tr_addr[x]);
+                v[1] = lds_read_tr8<kPanel * u + 4096>(tr_addr[x]);
+                v[2] = lds_read_tr8<kPanel * u + 8192>(tr_addr[x]);
+                v[3] = lds_read_tr8<kPanel * u + 8192 + 4096>(tr_addr[x]);
+            }
+        };
         auto step = [&](auto u_, int s) {
             constexpr int u = decltype(u_)::value;
             constexpr int next = (u + 2) % RD;
-            // all but the youngest ten loads (those of the step before) have arrived: panel, values and positions of this step, and the table
-            // its loads below are made from
-            asm volatile("s_waitcnt vmcnt(10)");
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            u32x2_t b[2][4];
-            auto read_four = [&](int x, u32x2_t (&v)[4]) {
-                if constexpr (ES == 2) {
-                    v[0] = lds_read_tr<kPanel * u>(tr_addr[x]);
-                    v[1] = lds_read_tr<kPanel * u + 1024>(tr_addr[x]);
-                    v[2] = lds_read_tr<kPanel * u + 8192>(tr_addr[x]);
-                    v[3] = lds_read_tr<kPanel * u + 8192 + 1024>(tr_addr[x]);
-                } else {
-                    v[0] = lds_read_tr8<kPanel * u>(tr_addr[x]);
-                    v[1] = lds_read_tr8<kPanel * u + 4096>(tr_addr[x]);
-                    v[2] = lds_read_tr8<kPanel * u + 8192>(tr_addr[x]);
-                    v[3] = lds_read_tr8<kPanel * u + 8192 + 4096>(tr_addr[x]);
-                }
-            };
-            read_four(0, b[0]);
 #pragma unroll
             for (int x = 0; x < NT; ++x) {
                 if (x + 1 < NT) {
-                    read_four((x + 1) & 7, b[(x + 1) & 1]);
+                    read_four(u_, x + 1, b[(x + 1) & 1]);
                     lds_four_done<4>(b[x & 1]);
                 } else {
+                    // This wave's reads of the panel have returned, and all of its loads but the youngest ten: the panel, values and
+                    // positions of step s + 1 are there, and the table that the loads after the barrier are made from.
                     lds_four_done<0>(b[x & 1]);
+                    asm volatile("s_waitcnt vmcnt(10)");
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_four(std::integral_constant<int, (u + 1) % RD>{}, 0, b[(x + 1) & 1]);
                 }
                 const u32x2_t(&v)[4] = b[x & 1];
                 const u32x8 operand = u32x8{v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], v[3][0], v[3][1]};
@@ -240,14 +244,17 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
                     for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<DT, 0>(a[u][r], operand, acc[r][x], ix[u][r]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (x < 4) {
-                    load_panel(table[next], next, x);
-                } else if (x == 4) {
+                // one set of ten loads per barrier: x = 7 opens the set of step s + 3, whose panel takes this step's place
+                if (x == 7) {
+                    load_panel(table[u], u, 0);
+                } else if (x < 3) {
+                    load_panel(table[next], next, x + 1);
+                } else if (x == 3) {
                     a[next][0] = load_a(s + 2, 0);
-                } else if (x == 5) {
+                } else if (x == 4) {
                     a[next][1] = load_a(s + 2, 1);
                     a[next][2] = load_a(s + 2, 2);
-                } else if (x == 6) {
+                } else if (x == 5) {
                     a[next][3] = load_a(s + 2, 3);
                     load_index(s + 2, ix[next]);
                 } else {
@@ -257,6 +264,12 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
             }
         };
         static_assert(RD == 3, "the loop body names its three steps");
+        asm volatile("s_waitcnt vmcnt(10)");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        read_four(std::integral_constant<int, 0>{}, 0, b[0]);
+        load_panel(table[2], 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
         for (int it = 0; it < iters; ++it) {
             step(std::integral_constant<int, 0>{}, RD * it);
             step(std::integral_constant<int, 1>{}, RD * it + 1);
