@@ -49,6 +49,7 @@ struct smat_handle {
     std::vector<uint32_t> vals_off;      // [nbr+1]
     uint64_t slots_units = 0, vals_units = 0;
     int max_class = 0;
+    bool by_column = false;              // there is a block row that is not an entry row
     int64_t value_bytes = 0;             // bytes of block values a launch over every block row reads
     int64_t b_rows = 0;                  // slots that name a row of B, over all packs
     std::vector<int32_t> row_b_rows;     // [nbr] the same per block row
@@ -135,8 +136,8 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Workspace layout, every section aligned to 256 bytes.
 struct Layout {
-    size_t perm, work, work_rest, slots, vals, pack_ptr, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
-    size_t csr_row_ptr, csr_col_idx, csr_vals;
+    size_t perm, work, work_rest, slots, vals, pack_ptr, slots_off, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
+    size_t csr_row_ptr, csr_col_idx, csr_vals, col_perm;
     size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, total;
 };
 
@@ -153,15 +154,17 @@ Layout make_layout(const smat_handle& h)
     l.slots = take(static_cast<size_t>(h.slots_units) * 32);
     l.vals = take(static_cast<size_t>(h.vals_units) * 64);
     l.pack_ptr = take((nbr + 1) * sizeof(int32_t));
+    l.slots_off = take((nbr + 1) * sizeof(uint32_t));
     l.vals_off = take((nbr + 1) * sizeof(uint32_t));
     l.row_class = take(nbr);
     l.blk_ptr = take((nbr + 1) * sizeof(int32_t));
     l.blk_col = take(n_e * sizeof(int32_t));
-    l.blk_pack = take(n_e * sizeof(int32_t));
-    l.blk_meta = take(n_e * sizeof(uint32_t));
+    l.blk_pack = take(h.by_column ? n_e * sizeof(int32_t) : 0);
+    l.blk_meta = take(h.by_column ? n_e * sizeof(uint32_t) : 0);
     l.csr_row_ptr = take((static_cast<size_t>(h.csr.M) + 1) * sizeof(int64_t));
     l.csr_col_idx = take(nnz * sizeof(int32_t));
     l.csr_vals = take(nnz * sizeof(uint16_t));
+    l.col_perm = take(h.cols_permuted ? static_cast<size_t>(h.csr.K) * sizeof(int32_t) : 0);
     l.t_super = take(h.dense_super.size() * sizeof(int32_t));
     const size_t quads = static_cast<size_t>(h.quad_steps());
     l.t_ptr = take(h.step_ptr.size() * sizeof(int32_t));
@@ -443,6 +446,7 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
         }
         h.row_class[br] = static_cast<int8_t>(cls);
         h.max_class = std::max(h.max_class, cls);
+        h.by_column |= cls != smat::kEntryClass && n_packs > 0;
         h.slots_off[br] = static_cast<uint32_t>(units);
         h.vals_off[br] = static_cast<uint32_t>(vunits);
         units += static_cast<uint64_t>(n_packs) * static_cast<uint64_t>(smat::pack_units(cls));
@@ -679,40 +683,6 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
 
         std::vector<int32_t> perm_padded((nbr + 15) / 16 * 256, -1);
         std::memcpy(perm_padded.data(), b.perm.data(), sizeof(int32_t) * M);
-        // slot tables (pack_layout.h): the B row of every occupied column of every pack
-        std::vector<uint32_t> slots(static_cast<size_t>(h->slots_units) * 8, static_cast<uint32_t>(h->csr.K));
-        std::vector<uint64_t> items;
-        for (size_t br = 0; br < nbr; ++br) {
-            uint32_t* table = slots.data() + static_cast<size_t>(h->slots_off[br]) * 8;
-            if (h->row_class[br] == smat::kEntryClass) {
-                // entry row: one slot per stored entry; the entries' row numbers go into the top
-                // bytes of the group's first four slots
-                entry_order(*h, br, items);
-                for (size_t e = 0; e < items.size(); ++e) {
-                    const size_t col = static_cast<size_t>(items[e] >> 4);
-                    const uint32_t rr = static_cast<uint32_t>(items[e] & 15u);
-                    const int rank = static_cast<int>(e & 31), g = smat::slot_group(rank), kk = smat::slot_pos(rank);
-                    uint32_t* group = table + (e >> 5) * 32 + g * 8;
-                    group[kk] = (group[kk] & 0xFF000000u) |
-                                (h->cols_permuted ? static_cast<uint32_t>(b.col_perm[col]) : static_cast<uint32_t>(col));
-                    group[kk >> 1] |= rr << (24 + 4 * (kk & 1));
-                }
-                continue;
-            }
-            const int L = 2 << h->row_class[br];
-            for (int32_t pk = h->pack_ptr[br]; pk < h->pack_ptr[br + 1]; ++pk, table += 4 * L) {
-                int rank = 0;
-                for (int32_t s = h->pack_first[static_cast<size_t>(pk)]; s < h->pack_first[static_cast<size_t>(pk) + 1]; ++s)
-                    for (int c = 0; c < 16; ++c) {
-                        if (!(b.col_mask[s] >> c & 1u)) continue;
-                        // the row of B is the ORIGINAL column: through Q when the columns were permuted
-                        const size_t col = static_cast<size_t>(b.col_idx[s]) * 16u + static_cast<size_t>(c);
-                        table[smat::slot_group(rank) * L + smat::slot_pos(rank)] =
-                            h->cols_permuted ? static_cast<uint32_t>(b.col_perm[col]) : static_cast<uint32_t>(col);
-                        ++rank;
-                    }
-            }
-        }
         // launch tables: all block rows, and those the dense path does not cover
         std::vector<int32_t> work(nbr * 4), work_rest;
         work_rest.reserve(nbr * 4);
@@ -744,14 +714,17 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
             if ((e = up(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4))) return hip_fail("copy tiles", e);
             if ((e = up(l.t_base, h->step_base.data(), h->step_base.size() * 4))) return hip_fail("copy tiles", e);
         }
-        if ((e = up(l.slots, slots.data(), slots.size() * 4))) return hip_fail("copy slot tables", e);
         if ((e = up(l.pack_ptr, h->pack_ptr.data(), h->pack_ptr.size() * 4))) return hip_fail("copy pack offsets", e);
+        if ((e = up(l.slots_off, h->slots_off.data(), h->slots_off.size() * 4))) return hip_fail("copy slot offsets", e);
         if ((e = up(l.vals_off, h->vals_off.data(), h->vals_off.size() * 4))) return hip_fail("copy value offsets", e);
         if ((e = up(l.row_class, h->row_class.data(), h->row_class.size()))) return hip_fail("copy row classes", e);
         if ((e = up(l.blk_ptr, b.row_ptr.data(), b.row_ptr.size() * 4))) return hip_fail("copy block offsets", e);
-        if ((e = up(l.blk_col, b.col_idx.data(), n_e * 4))) return hip_fail("copy block columns", e);
-        if ((e = up(l.blk_pack, h->blk_pack.data(), n_e * 4))) return hip_fail("copy block packs", e);
-        if ((e = up(l.blk_meta, h->blk_meta.data(), n_e * 4))) return hip_fail("copy block masks", e);
+        if (h->by_column) {
+            if ((e = up(l.blk_col, b.col_idx.data(), n_e * 4))) return hip_fail("copy block columns", e);
+            if ((e = up(l.blk_pack, h->blk_pack.data(), n_e * 4))) return hip_fail("copy block packs", e);
+            if ((e = up(l.blk_meta, h->blk_meta.data(), n_e * 4))) return hip_fail("copy block masks", e);
+        }
+        if (h->cols_permuted && (e = up(l.col_perm, b.col_perm.data(), b.col_perm.size() * 4))) return hip_fail("copy column order", e);
         if ((e = up(l.csr_row_ptr, h->csr.row_ptr.data(), (M + 1) * 8))) return hip_fail("copy csr row_ptr", e);
         if ((e = up(l.csr_col_idx, h->csr.col_idx.data(), nnz * 4))) return hip_fail("copy csr col_idx", e);
         if ((e = up(l.csr_vals, h->csr.vals.data(), nnz * 2))) return hip_fail("copy csr vals", e);
@@ -763,6 +736,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         d.slots = reinterpret_cast<const uint32_t*>(base + l.slots);
         d.vals = base + l.vals;
         d.pack_ptr = reinterpret_cast<const int32_t*>(base + l.pack_ptr);
+        d.slots_off = reinterpret_cast<const uint32_t*>(base + l.slots_off);
         d.vals_off = reinterpret_cast<const uint32_t*>(base + l.vals_off);
         d.row_class = reinterpret_cast<const int8_t*>(base + l.row_class);
         d.blk_ptr = reinterpret_cast<const int32_t*>(base + l.blk_ptr);
@@ -799,7 +773,9 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
 
         if ((e = smat::launch_fill_zero(base + l.vals, static_cast<size_t>(h->vals_units) * 4, s)))
             return hip_fail("zero block values", e);
-        if ((e = smat::launch_bcsr_fill(d, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.vals, h->elem_bytes, s)))
+        if ((e = smat::launch_bcsr_fill(d, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals,
+                                        h->cols_permuted ? reinterpret_cast<const int32_t*>(base + l.col_perm) : nullptr, base + l.vals,
+                                        reinterpret_cast<uint32_t*>(base + l.slots), static_cast<size_t>(h->slots_units) * 8, h->elem_bytes, s)))
             return hip_fail("fill block values", e);
         if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_rows - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
         e = quads ? smat::launch_quad_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
@@ -1127,6 +1103,10 @@ smat_status_t smat_ablation_bind(smat_handle_t* h, void* dev_area, size_t bytes,
             return hip_fail("copy canonical block values", e);
         if (!map.empty() && (e = static_cast<int>(hipMemcpyAsync(base + ablation_vals_bytes(h), map.data(), map.size() * 4, hipMemcpyHostToDevice, s))))
             return hip_fail("copy block map", e);
+        // (not copied at bind time where no block row is kept by column)
+        if (!h->by_column && !b.col_idx.empty() &&
+            (e = static_cast<int>(hipMemcpyAsync(const_cast<int32_t*>(h->dev.blk_col), b.col_idx.data(), b.col_idx.size() * 4, hipMemcpyHostToDevice, s))))
+            return hip_fail("copy block columns", e);
         if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("ablation bind synchronize", e);
         smat::CanonicalBcsr& m = h->ablation;
         m.row_ptr = h->dev.blk_ptr;

@@ -21,8 +21,10 @@ struct DeviceBcsr {
                                          // entry rows: the pack's 32 entry values in one 64-byte unit
     // bind-time value scatter only
     const int32_t* pack_ptr = nullptr;   // [nbr+1] pack offsets per block row
+    const uint32_t* slots_off = nullptr; // [nbr+1] start of the row's slot table, 32-byte units
     const uint32_t* vals_off = nullptr;  // [nbr+1] start of the row's values, 64-byte units
     const int8_t* row_class = nullptr;   // [nbr] 0..2: packs of occupied columns with L = 2, 4, 8; 3: entry row
+    // (not for entry rows: where there are no others, blk_pack and blk_meta are not there)
     const int32_t* blk_ptr = nullptr;    // [nbr+1] stored-block offsets per block row
     const int32_t* blk_col = nullptr;    // [n_blocks] block column, ascending inside a block row
     const int32_t* blk_pack = nullptr;   // [n_blocks] pack of the block, counted inside its block row
@@ -71,11 +73,11 @@ constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave gro
 // Sets n16 16-byte words at dst to zero.
 int launch_fill_zero(void* dst, size_t n16, void* stream);
 
-// Scatters the CSR values into the device block layout.  csr_* are device copies of the
-// caller's CSR (values as 16-bit words, 8-bit types in the low byte); vals_out holds elements
-// of elem_bytes (1 or 2) and must have been zeroed.
-int launch_bcsr_fill(const DeviceBcsr& d, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
-                     const uint16_t* csr_vals, void* vals_out, int elem_bytes, void* stream);
+// Scatters the CSR values into the device block layout and makes the slot tables (slot_words words).  csr_* are device copies of
+// the caller's CSR (values as 16-bit words, 8-bit types in the low byte); col_perm: the row of B of every column, or null for
+// the column's own number; vals_out holds elements of elem_bytes (1 or 2) and must have been zeroed.
+int launch_bcsr_fill(const DeviceBcsr& d, const int64_t* csr_row_ptr, const int32_t* csr_col_idx, const uint16_t* csr_vals,
+                     const int32_t* col_perm, void* vals_out, uint32_t* slots_out, size_t slot_words, int elem_bytes, void* stream);
 
 // C = A * B.  dtype is a smat_dtype_t; C holds fp32, or int32 for the integer type.  Returns
 // a hipError_t as int; *variant receives a static string naming the kernel.

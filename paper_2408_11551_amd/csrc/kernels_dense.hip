@@ -405,18 +405,18 @@ __global__ void dense_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __r
                                   const int32_t* __restrict__ csr_col_idx, const uint16_t* __restrict__ csr_vals,
                                   T* __restrict__ vals_out)
 {
-    const int sidx = blockIdx.x;                       // which dense super row
-    const int rr = threadIdx.x;                        // row inside the super row, 0..255
-    const int64_t i = static_cast<int64_t>(t.super_rows[sidx]) * 256 + rr;
+    // one workgroup per block row, sixteen threads per row
+    const int sidx = static_cast<int>(blockIdx.x >> 4);                      // which dense super row
+    const int j = static_cast<int>(blockIdx.x & 15), ii = static_cast<int>(threadIdx.x >> 4);
+    const int64_t i = static_cast<int64_t>(t.super_rows[sidx]) * 256 + 16 * j + ii;
     if (i >= d.M) return;
     const int64_t r = d.perm[i];
-    const int j = rr >> 4, ii = rr & 15;
     const int q0 = t.step_ptr[sidx], q1 = t.step_ptr[sidx + 1];
     const int cps = t.cols_per_step, ksub = cps / 2;
     const int32_t* cols = t.step_cols + static_cast<size_t>(cps) * static_cast<size_t>(q0);   // ascending; a missing last column is INT_MAX
     const int ncols = cps * (q1 - q0);
     int hint = 0;
-    for (int64_t p = csr_row_ptr[r]; p < csr_row_ptr[r + 1]; ++p) {
+    for (int64_t p = csr_row_ptr[r] + (threadIdx.x & 15); p < csr_row_ptr[r + 1]; p += 16) {
         const int c = csr_col_idx[p];
         const int bc = c >> 4;
         int lo = hint, hi = ncols;
@@ -439,10 +439,10 @@ int launch_dense_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* c
 {
     if (t.n == 0) return 0;
     if (elem_bytes == 1)
-        hipLaunchKernelGGL(dense_fill_kernel<uint8_t>, dim3(static_cast<unsigned>(t.n)), dim3(256), 0,
+        hipLaunchKernelGGL(dense_fill_kernel<uint8_t>, dim3(static_cast<unsigned>(t.n) * 16), dim3(256), 0,
                            static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx, csr_vals, static_cast<uint8_t*>(vals_out));
     else
-        hipLaunchKernelGGL(dense_fill_kernel<uint16_t>, dim3(static_cast<unsigned>(t.n)), dim3(256), 0,
+        hipLaunchKernelGGL(dense_fill_kernel<uint16_t>, dim3(static_cast<unsigned>(t.n) * 16), dim3(256), 0,
                            static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx, csr_vals, static_cast<uint16_t*>(vals_out));
     return static_cast<int>(hipGetLastError());
 }
