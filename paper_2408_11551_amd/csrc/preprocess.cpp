@@ -21,6 +21,7 @@
 #include "preprocess.h"
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 namespace smat {
@@ -226,6 +227,8 @@ struct ColumnIndex {
     Buf<int64_t> ptr;       // [nbc+1]
     Buf<int64_t> len;       // [nbc] classes still listed (the clustering drops those that are used up)
     Buf<int32_t> classes;
+    Buf<int32_t> at;        // [patterns] where a class stands in the list of a column of its pattern, as long as nothing has been dropped
+    bool dropped = false;
 };
 
 static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const PatternClasses& pc, Workers& workers)
@@ -237,13 +240,13 @@ static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const Pattern
     Buf<int64_t> place(static_cast<size_t>(parts * nbc));
     auto entries = [&](int64_t part, auto&& take) {
         for (int64_t k = n * part / parts; k < n * (part + 1) / parts; ++k)
-            for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) take(pat.idx[q], k);
+            for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) take(pat.idx[q], k, q);
     };
     workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
         for (int64_t part = p0; part < p1; ++part) {
             int64_t* count = place.data() + part * nbc;
             std::fill(count, count + nbc, int64_t{0});
-            entries(part, [&](int32_t c, int64_t) { ++count[c]; });
+            entries(part, [&](int32_t c, int64_t, int64_t) { ++count[c]; });
         }
     });
     inv.ptr.resize(static_cast<size_t>(nbc) + 1);
@@ -260,9 +263,14 @@ static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const Pattern
     }
     inv.ptr[nbc] = total;
     inv.classes.resize(static_cast<size_t>(total));
+    inv.at.resize(pat.idx.size());
     workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
         for (int64_t part = p0; part < p1; ++part)
-            entries(part, [&](int32_t c, int64_t k) { inv.classes[place[part * nbc + c]++] = static_cast<int32_t>(k); });
+            entries(part, [&](int32_t c, int64_t k, int64_t q) {
+                const int64_t to = place[part * nbc + c]++;
+                inv.classes[to] = static_cast<int32_t>(k);
+                inv.at[q] = static_cast<int32_t>(to - inv.ptr[c]);
+            });
     });
     return inv;
 }
@@ -270,7 +278,10 @@ static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const Pattern
 // With which other classes could a cluster opened by a row of class k start to grow?  The first row of another class to
 // join has to pass the merge test against the seed's own pattern: 1000 |a n b| > keep |a u b|.  Lists such classes, class by
 // class (some more than once).  Each pair is counted once, from the shorter pattern: |b| < 1000 |a| / keep bounds
-// the longer one, and an increment is looked at only once the count could pass for the shortest b.
+// the longer one.
+// Where a class has many increments to make, they are made without looking, and the counters are looked through (and cleared) once, in
+// order; and only some of its columns are counted: b has to share `least` of a's columns, so all but least - m of them (the
+// longest lists are left out) already hold m shared ones; whoever reaches m, about nobody by chance, is counted exactly.
 struct Partners {
     Buf<int64_t> ptr;       // [n+1]
     Buf<int32_t> of;
@@ -282,11 +293,16 @@ static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const
 {
     // (alive[k] == 0: every row of the class is in a cluster)
     const int64_t n = pc.size();
-    struct Local { std::vector<Count> count; std::vector<std::pair<int32_t, int32_t>> pairs; };
+    struct Local {
+        std::vector<Count> count;
+        std::vector<std::pair<int32_t, int32_t>> pairs;
+        std::vector<std::pair<const int32_t*, const int32_t*>> lists;      // what the columns of a list beyond class k
+    };
     std::vector<Local> locals(static_cast<size_t>(workers.most()));
     workers.ranges(n, 16, [&](int64_t j0, int64_t j1, int thread) {
         Local& local = locals[static_cast<size_t>(thread)];
-        if (local.count.empty()) local.count.assign(static_cast<size_t>(n), 0);
+        constexpr int64_t kStride = 64;
+        if (local.count.empty()) local.count.assign(static_cast<size_t>(n + kStride), 0);
         Count* const count = local.count.data();
         for (int64_t j = j0; j < j1; ++j) {
             const int64_t k = n - 1 - j, len = pc.len[k];                       // long patterns, which take longest, first
@@ -295,22 +311,59 @@ static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const
             const int64_t end = keep == 0 ? n
                 : std::partition_point(pc.len.begin() + k, pc.len.end(), [&](int32_t x) { return keep * x < 1000 * len; }) - pc.len.begin();
             const int64_t least = 2 * keep * len / (1000 + keep) + 1;
-            auto lists = [&](auto&& each) {
-                for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) {
-                    const int32_t* p = inv.classes.data() + inv.ptr[pat.idx[q]];
-                    const int32_t* stop = p + inv.len[pat.idx[q]];
-                    for (p = std::upper_bound(p, stop, static_cast<int32_t>(k)); p < stop && *p < end; ++p) each(*p);
+            local.lists.clear();
+            int64_t ahead = 0;
+            for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) {
+                const int32_t* p = inv.classes.data() + inv.ptr[pat.idx[q]];
+                const int32_t* stop = p + inv.len[pat.idx[q]];
+                p = inv.dropped ? std::upper_bound(p, stop, static_cast<int32_t>(k)) : p + inv.at[q] + 1;
+                if (p < stop && stop[-1] >= end) stop = std::lower_bound(p, stop, static_cast<int32_t>(end));
+                local.lists.emplace_back(p, stop);
+                ahead += stop - p;
+            }
+            const auto passes = [&](int64_t shared, int64_t other) { return 1000 * shared > keep * (len + pc.len[other] - shared); };
+            if (ahead > (end - k) / 16) {
+                // m: what chance gives a pattern of the average number of columns, and four deviations more
+                const double hit = static_cast<double>(ahead) / static_cast<double>((end - k) * len);
+                int64_t m = 2;
+                for (int round = 0; round < 3; ++round) {
+                    const double mean = hit * static_cast<double>(len - least + m);
+                    m = std::min(least, static_cast<int64_t>(mean + 4.0 * std::sqrt(mean)) + 3);
                 }
-            };
-            int64_t counted = 0;
-            lists([&](int32_t other) {
-                const int64_t shared = ++count[other];
-                ++counted;
-                if (shared < least || 1000 * shared <= keep * (len + pc.len[other] - shared)) return;
-                local.pairs.emplace_back(static_cast<int32_t>(k), other);
-            });
-            if (counted > (end - k) / 32) std::fill(count + k, count + end, Count{0});
-            else lists([&](int32_t other) { count[other] = 0; });
+                const int64_t counted = len - least + m;
+                if (counted < len)
+                    std::nth_element(local.lists.begin(), local.lists.begin() + counted, local.lists.end(),
+                                     [](const auto& x, const auto& y) { return x.second - x.first < y.second - y.first; });
+                for (int64_t x = 0; x < std::min(counted, len); ++x)
+                    for (const int32_t* p = local.lists[static_cast<size_t>(x)].first; p < local.lists[static_cast<size_t>(x)].second; ++p) ++count[*p];
+                const int32_t* mine = pat.idx.data() + pat.ptr[pc.first_row[k]];
+                for (int64_t x = k + 1; x < end; x += kStride) {
+                    Count most = 0;
+                    for (int64_t y = 0; y < kStride; ++y) most = std::max(most, count[x + y]);
+                    if (most >= m)
+                        for (int64_t other = x; other < std::min(end, x + kStride); ++other) {
+                            if (count[other] < m) continue;
+                            const int32_t* theirs = pat.idx.data() + pat.ptr[pc.first_row[other]];
+                            int64_t shared = 0;
+                            for (int64_t u = 0, v = 0; u < len && v < pc.len[other];) {
+                                shared += mine[u] == theirs[v];
+                                const bool up = mine[u] <= theirs[v], vp = theirs[v] <= mine[u];
+                                u += up;
+                                v += vp;
+                            }
+                            if (passes(shared, other)) local.pairs.emplace_back(static_cast<int32_t>(k), static_cast<int32_t>(other));
+                        }
+                    std::fill(count + x, count + x + kStride, Count{0});
+                }
+            } else {
+                for (const auto& list : local.lists)
+                    for (const int32_t* p = list.first; p < list.second; ++p) {
+                        const int64_t shared = ++count[*p];
+                        if (shared >= least && passes(shared, *p)) local.pairs.emplace_back(static_cast<int32_t>(k), *p);
+                    }
+                for (const auto& list : local.lists)
+                    for (const int32_t* p = list.first; p < list.second; ++p) count[*p] = 0;
+            }
         }
     });
     Partners partners;
@@ -349,16 +402,26 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         state[k] = ClassState{static_cast<int32_t>(pc.member_ptr[k + 1] - pc.member_ptr[k]), 0, pc.len[k], 0};
     std::vector<int32_t> touched;             // classes with shared != 0, cleared when the cluster closes
     std::vector<int64_t> in_union(nbc, -1);   // id of the cluster whose union holds the column
+    struct Column { int32_t c; int64_t at; }; // a column of the union: classes of its list counted so far
+    std::vector<Column> columns;
+    std::vector<int32_t> walked_over(nbc, 0); // by column: classes without rows met in its list since they were last dropped
     int64_t shortest = 0;                     // shortest non-empty pattern
     for (int64_t k = 0; k < n_classes && shortest == 0; ++k) shortest = pc.len[k];
+    const int64_t longest = n_classes ? pc.len[n_classes - 1] : 0;
+    std::vector<int64_t> first_of_len(static_cast<size_t>(longest) + 2);      // first class with a pattern of that length or more
+    for (int64_t k = n_classes - 1, len = longest + 1; len >= 0; --len) {
+        while (k >= 0 && pc.len[k] >= len) --k;
+        first_of_len[len] = k + 1;
+    }
     AscendingSet candidates(M);
     int64_t n_clusters = 0;
     const int64_t keep = 1000 - tau_permille;
     Partners partners;                        // once they have been asked for
-    int64_t spent = 0, ask_at = 300000;       // counting done so far; when to look whether it is worth asking
+    constexpr int64_t kFirstAsk = 300000;
+    int64_t spent = 0, ask_at = kFirstAsk;    // counting done so far; when to look whether it is worth asking
 
-    // A column enters the union while the scan stands at row `pos`: every class that has the
-    // column shares one more column with the union, and so does each of its rows.  Only rows
+    // Row `v` (a seed, or one that joins) brings its columns into the union, while the scan stands at it: every class that has
+    // one of them shares one more column with the union, and so does each of its rows.  Only rows
     // ahead of the scan can still be visited; their count when the scan reaches them is the
     // class's.  A row is only worth a visit once it could pass the merge test at all.  The
     // test at the visit, with the union U' >= U of that later moment and the count n' of then, is
@@ -368,31 +431,61 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     // increment that satisfies it, and no row that would be merged is left out; the exact test is
     // still taken at the visit.  The same bound with the shortest pattern of the matrix in place
     // of |w| comes first, so that most increments read nothing but the counter.
-    auto add_column = [&](int32_t c, int64_t pos, int64_t cluster, int64_t& union_size) {
-        if (in_union[c] == cluster) return;
-        in_union[c] = cluster;
-        ++union_size;
-        const int64_t least = keep * (shortest + union_size) / (1000 + keep);   // a count must exceed this to matter for any row
-        int32_t* classes = inv.classes.data() + inv.ptr[c];
-        int64_t kept = 0;
-        spent += inv.len[c];
-        for (int64_t x = 0; x < inv.len[c]; ++x) {
-            const int32_t k = classes[x];
-            ClassState& at = state[k];
-            if (at.alive == 0) continue;                 // drop classes that are gone for good
-            classes[kept++] = k;
-            const int32_t word = (at.shared += 2);
-            if (word == 2) touched.push_back(k);
-            if (word & 1) continue;                      // its rows are candidates already
-            const int64_t n = word >> 1;
-            if (!(n > least && (1000 + keep) * n > keep * (at.len + union_size))) continue;
-            at.shared = word | 1;
-            for (int64_t y = pc.member_ptr[k]; y < pc.member_ptr[k + 1]; ++y) {
-                const int32_t r = pc.members[y];
-                if (r > pos && !clustered[r]) candidates.insert(r);
+    // A row passes only if keep |w| < 1000 U' and keep U' < 1000 |w| (its count is at most the smaller of the two), and the lists are
+    // ordered by |w|: a new column's list is counted from the first class that is long enough now, as the union only grows, and every
+    // list of the union as far as the union's size allows now -- the rest when it has grown.  (A graph of 65536 rows: 28 -> 7 ms.)
+    auto add_row = [&](int64_t v, int64_t cluster, int64_t& union_size) {
+        const size_t known = columns.size();
+        for (int64_t q = pat.ptr[v]; q < pat.ptr[v + 1]; ++q)
+            if (in_union[pat.idx[q]] != cluster) {
+                in_union[pat.idx[q]] = cluster;
+                columns.push_back(Column{pat.idx[q], 0});
             }
+        if (columns.size() == known) return;
+        union_size = static_cast<int64_t>(columns.size());
+        const int64_t too_long = keep == 0 ? longest + 1 : std::min(longest + 1, (1000 * union_size + keep - 1) / keep);
+        const int32_t begin = static_cast<int32_t>(first_of_len[std::min(longest + 1, keep * union_size / 1000 + 1)]);
+        const int32_t end = static_cast<int32_t>(first_of_len[too_long]);
+        const int64_t least = keep * (shortest + union_size) / (1000 + keep);   // a count must exceed this to matter for any row
+        for (size_t u = 0; u < columns.size(); ++u) {
+            Column& column = columns[u];
+            int32_t* classes = inv.classes.data() + inv.ptr[column.c];
+            const int64_t len = inv.len[column.c];
+            if (u >= known) column.at = std::lower_bound(classes, classes + len, begin) - classes;
+            const int64_t from = column.at;
+            int64_t x = from, gone = 0;
+            for (; x < len && classes[x] < end; ++x) {
+                const int32_t k = classes[x];
+                ClassState& at = state[k];
+                if (at.alive == 0) { ++gone; continue; }
+                const int32_t word = (at.shared += 2);
+                if (word == 2) touched.push_back(k);
+                if (word & 1) continue;                      // its rows are candidates already
+                const int64_t n = word >> 1;
+                if (!(n > least && (1000 + keep) * n > keep * (at.len + union_size))) continue;
+                at.shared = word | 1;
+                for (int64_t y = pc.member_ptr[k]; y < pc.member_ptr[k + 1]; ++y) {
+                    const int32_t r = pc.members[y];
+                    if (r > v && !clustered[r]) candidates.insert(r);
+                }
+            }
+            spent += x - from;
+            // Drop classes that are gone for good once walking over them has cost as much as dropping them does (but not before
+            // it is known whether partners_of wants the lists as they were made).
+            walked_over[column.c] += static_cast<int32_t>(gone);
+            if (walked_over[column.c] > len && ask_at != kFirstAsk) {
+                walked_over[column.c] = 0;
+                int64_t kept = 0, before = 0;
+                for (int64_t y = 0; y < len; ++y) {
+                    if (y == x) before = kept;
+                    if (state[classes[y]].alive > 0) classes[kept++] = classes[y];
+                }
+                inv.len[column.c] = kept;
+                inv.dropped = true;
+                x = x == len ? kept : before;
+            }
+            column.at = x;
         }
-        inv.len[c] = kept;
     };
     // The counting still to come if the rest of the rows goes like the rows so far, against that of partners_of
     // (at most half the pairs of every list), shared by the threads.
@@ -407,6 +500,7 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         }
         std::vector<int32_t> alive(static_cast<size_t>(n_classes));
         for (int64_t k = 0; k < n_classes; ++k) alive[k] = state[k].alive;
+        ask_at = 0;
         const bool bytes = n_classes == 0 || pc.len[n_classes - 1] < 256;
         partners = bytes ? partners_of<uint8_t>(pat, pc, inv, alive, keep, workers) : partners_of<int32_t>(pat, pc, inv, alive, keep, workers);
     };
@@ -439,7 +533,8 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
             continue;
         }
         int64_t union_size = 0;
-        for (int64_t q = pat.ptr[v]; q < pat.ptr[v + 1]; ++q) add_column(pat.idx[q], v, cluster, union_size);
+        columns.clear();
+        add_row(v, cluster, union_size);
         int64_t pos = v;
         for (;;) {
             const int64_t w = candidates.next(pos + 1);
@@ -453,8 +548,7 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
                 clustered[w] = 1;
                 --state[k].alive;
                 order.push_back(static_cast<int32_t>(w));
-                if (inter < pc.len[k])                   // otherwise every column of the row is in the union already
-                    for (int64_t q = pat.ptr[w]; q < pat.ptr[w + 1]; ++q) add_column(pat.idx[q], w, cluster, union_size);
+                if (inter < pc.len[k]) add_row(w, cluster, union_size);      // otherwise every column of the row is in the union already
             }
         }
         for (int32_t k : touched) state[k].shared = 0;
