@@ -760,6 +760,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.quad_rows = reinterpret_cast<const int32_t*>(base + l.t_quad_rows);
         tiles.quad_index = reinterpret_cast<const uint8_t*>(base + l.t_quad_index);
         tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
+        tiles.max_quad_steps = h->max_quad_steps;
         tiles.scratch = nullptr;           // a call takes the area of its stream
         tiles.scratch_bytes = 0;
         tiles.n = static_cast<int32_t>(h->dense_super.size());
@@ -906,6 +907,20 @@ char* scratch_area_of(const smat_handle* h, const void* stream)
 // columns are mostly empty.
 constexpr int64_t kStageColumns = 32;
 
+// Does the kernel for few columns on the two-of-four form take N columns?  It pays where the values kept by column, which the per-row
+// kernel streams, are many: from about 18 MB on in the 16-bit types (22 MB where B takes 32 bytes per row: 4096 x 3000 at 10 %, N = 8: 5.9
+// against 5.5 us, N = 16: 5.9 against 6.3), 8 MB in the 8-bit ones.  More than sixteen columns take two passes over A,
+// which pays while A stays in the L2s (21 MB, N = 32: 11.3 against 9.1 us; 42 MB: 13.3 against 21.7).
+bool quad_rows_take(const smat_handle& h, int64_t N)
+{
+    if (h.tiles.n_quad_steps == 0 || N > 32) return false;
+    if (N > 16 && static_cast<int64_t>(h.tiles.n_quad_steps) * (h.elem_bytes == 1 ? 20480 : 18432) > 24000000) return false;
+    const int row_bytes = smat::quad_row_bytes(h.elem_bytes, N);
+    const int64_t by_column = h.dense_columns * 16 * h.elem_bytes;
+    return by_column >= (h.elem_bytes == 1 ? 8000000 : row_bytes == 32 ? 22000000 : 18000000) &&
+           smat::quad_rows_lds(h.max_quad_steps, h.elem_bytes, row_bytes) <= smat::kQuadRowsLds;
+}
+
 // smat_spmm with the area for partial tiles given by the caller of this function.
 // hard_limit = 0: the launch is planned so that its partial tiles fit scratch_bytes.  Otherwise it
 // is planned as if the area were unlimited and refused when its partial tiles exceed hard_limit.
@@ -981,7 +996,11 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     const char* variant = "";
     thread_local std::string name;
     int e = 0;
-    if (use_tiles) {
+    if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N)) {
+        if (h->dev_rest.n_order > 0) e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        if (!e) e = smat::launch_quad_rows(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        g_kernel = variant;
+    } else if (use_tiles) {
         if (h->dev_rest.n_order > 0)
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
         const char* dense_variant = "";

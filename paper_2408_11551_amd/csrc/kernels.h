@@ -65,7 +65,7 @@ struct DenseTiles {
     // step_* tables are not there, and mean_steps is still what the other form would have.
     const int32_t* quad_rows = nullptr;    // [quad_columns * (n_quad_steps + 1)] rows of B of a step's panel; the last step names none
     const uint8_t* quad_index = nullptr;   // [2 or 4 KiB * n_quad_steps] positions of the values
-    int32_t n_quad_steps = 0;
+    int32_t n_quad_steps = 0, max_quad_steps = 0;      // all, and those of the longest super row
 };
 
 constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave groups share a tile
@@ -106,6 +106,11 @@ int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* cs
 // Its part of launch_spmm_dense, the partial tiles of ks > 1 workgroups per tile left to the caller.
 void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
                        int64_t N, void* stream);
+
+// C rows of the quad super rows for few columns (N <= 16 per pass over A; any ldb and alignment).  Needs quad_rows_lds() of the row's bytes to be
+// at most kQuadRowsLds.
+int launch_quad_rows(const DeviceBcsr& d, const DenseTiles& t, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N,
+                     void* stream, const char** variant);
 
 // Workgroups per 128-column tile the dense launch would use for this N (1: no split).
 int dense_split(const DenseTiles& t, int64_t N);

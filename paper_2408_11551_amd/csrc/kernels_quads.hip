@@ -16,7 +16,7 @@
 // between the matrix instructions.
 //
 // What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.
-#include <algorithm>
+#include <cstdio>
 #include <type_traits>
 
 #include <hip/hip_runtime.h>
@@ -306,6 +306,271 @@ void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int 
     case kE4M3: return launch_quad_dtype<kE4M3>(d, t, ks, B, ldb, C, ldc, N, s);
     case kE5M2: return launch_quad_dtype<kE5M2>(d, t, ks, B, ldb, C, ldc, N, s);
     default: return launch_quad_dtype<kI8>(d, t, ks, B, ldb, C, ldc, N, s);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same values for few columns (a decode step, a few right-hand sides): block rows instead of tiles
+// ---------------------------------------------------------------------------------------------
+// With N <= 16 the product is the stream of A and nothing else, but the per-row kernel asks for a row of B per occupied
+// column and block row, eight requests of a few bytes per pack, and its rate of requests bounds it (8192 x 4096 in int8, N = 4:
+// 10.5 us for 34 MB).  Here a workgroup of sixteen waves takes RM block rows and all of their steps, wave w the steps w, w + 16, ...:
+// the first of a wave's values are asked for, all of B (K rows of RB bytes, rounded up from N) is brought into LDS in the order of the
+// super row's table, and what is left are transposing reads and one matrix instruction per step and block row.  The sixteen
+// partial tiles are added through LDS in a fixed order.
+// RB: bytes per row of B in LDS, 8, 16 or 32: 4, 8 or 16 columns of a 16-bit type, 8 or 16 of an 8-bit one.  The sixteen rows (8-bit types:
+// 32) that a transposing read takes lie one after the other, so it meets no bank twice; columns past RB are
+// read again from its beginning, and columns past N hold whatever follows in B: neither is stored.
+constexpr int kRowWaves = 16;
+constexpr int kRowPrefetch(int rm) { return rm == 1 ? 8 : 4; }
+
+template <int DT, int RM, int RB>
+__global__ __launch_bounds__(64 * kRowWaves)
+void spmm_quad_rows_kernel(int n_units, int per_xcd, int N, uint32_t b_bytes, const int32_t* __restrict__ super_rows,
+                           const int32_t* __restrict__ step_ptr, const void* __restrict__ B, const int32_t* __restrict__ quad_rows,
+                           uint32_t ldb_bytes, uint32_t K, const void* __restrict__ tile_vals, const uint8_t* __restrict__ index,
+                           const int32_t* __restrict__ perm, typename Elem<DT>::Out* __restrict__ C, int64_t ldc)
+{
+    using Acc = typename Elem<DT>::Acc;
+    using Out = typename Elem<DT>::Out;
+    constexpr int ES = Elem<DT>::ES, COLS = quad_columns(ES), PF = kRowPrefetch(RM);
+    constexpr int UNITS = 16 / RM;                 // workgroups per super row
+    constexpr uint32_t IB = ES == 2 ? 8 : 16;      // bytes of positions per lane and step: four block rows
+    extern __shared__ u32x4 lds_dyn[];
+    uint8_t* const panel = reinterpret_cast<uint8_t*>(lds_dyn);
+
+    const int unit = static_cast<int>(blockIdx.x % 8u) * per_xcd + static_cast<int>(blockIdx.x / 8u);      // an XCD has whole super rows
+    if (unit >= n_units) return;
+    const int sidx = unit / UNITS, j0 = unit % UNITS * RM;
+    const int col0 = static_cast<int>(blockIdx.y) * 16;
+    const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, i = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q_first = step_ptr[sidx], nq = step_ptr[sidx + 1] - q_first;
+    const int super = super_rows[sidx];
+
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<uint8_t*>(const_cast<void*>(tile_vals)) + static_cast<size_t>(q_first) * 16384, 0, nq * 16384, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t ix_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(index) + static_cast<size_t>(q_first) * (256 * IB), 0, nq * static_cast<int>(256 * IB), kRsrcFlags);
+    u32x4 a[PF][RM];
+    uint32_t ix[PF][RM];
+    // values and positions of step q for the block rows j0 ..; a step past the end is out of range (zeros)
+    auto load_step = [&](int q, u32x4 (&av)[RM], uint32_t (&iv)[RM]) {
+        const uint32_t past = q < nq ? 0u : kOutOfRange;
+        const uint32_t qs = static_cast<uint32_t>(q < nq ? q : 0);
+#pragma unroll
+        for (int r = 0; r < RM; ++r) av[r] = buf_load16(a_rsrc, static_cast<uint32_t>(lane) * 16u | past, qs * 16384u + static_cast<uint32_t>(j0 + r) * 1024u);
+        const uint32_t voff = (static_cast<uint32_t>(lane) * IB + static_cast<uint32_t>(j0 & 3) * (IB / 4)) | past;
+        const uint32_t soff = qs * (256u * IB) + static_cast<uint32_t>(j0 >> 2) * (64u * IB);
+        if constexpr (ES == 2 && RM == 1) {
+            iv[0] = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(ix_rsrc, voff, soff, 0));
+        } else if constexpr (ES == 2) {
+            const uint32_t both = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(ix_rsrc, voff, soff, 0));
+#pragma unroll
+            for (int r = 0; r < RM; ++r) iv[r] = both;                        // halves 0 and 1
+        } else if constexpr (RM == 1) {
+            iv[0] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(ix_rsrc, voff, soff, 0));
+        } else {
+            const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(ix_rsrc, voff, soff, 0);
+            iv[0] = static_cast<uint32_t>(v[0]);
+            iv[RM - 1] = static_cast<uint32_t>(v[1]);
+        }
+    };
+#pragma unroll
+    for (int h = 0; h < PF; ++h) load_step(wave + kRowWaves * h, a[h], ix[h]);
+
+    // B into LDS, four rows per thread at a time
+    // (from a base on a dword; where rows of B lie off the dwords, loads at their own addresses took twice the whole kernel: the
+    // dwords around a row are fetched instead and shifted into place)
+    const uint32_t shift_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(B) & 3u);
+    const bool off_dwords = ((ldb_bytes | shift_base) & 3u) != 0;
+    b_bytes += shift_base;
+    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<uint8_t*>(const_cast<void*>(B)) - shift_base, 0, static_cast<int>(b_bytes), kRsrcFlags);
+    const int n_rows = nq * COLS;
+    const int32_t* table = quad_rows + static_cast<size_t>(q_first) * COLS;
+    constexpr int RW = RB / 4;
+    for (int x0 = tid; x0 < n_rows; x0 += 4 * 64 * kRowWaves) {
+        uint32_t row[4], v[4][RW];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x = x0 + u * 64 * kRowWaves;
+            row[u] = x < n_rows ? static_cast<uint32_t>(table[x]) : K;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int w = 0; w < RW; ++w) v[u][w] = 0u;
+            if (row[u] >= K) continue;
+            const uint32_t off = row[u] * ldb_bytes + static_cast<uint32_t>(col0) * ES + shift_base;
+            if (off_dwords && (off & ~3u) + RB + 4 <= b_bytes) {
+                uint32_t p[RW + 1];
+#pragma unroll
+                for (int w = 0; w < RW; w += RB == 8 ? 2 : 4) {
+                    if constexpr (RB == 8) {
+                        const i32x2 q = __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, off & ~3u, 0, 0);
+                        p[0] = static_cast<uint32_t>(q[0]);
+                        p[1] = static_cast<uint32_t>(q[1]);
+                    } else {
+                        const u32x4 q = buf_load16(b_rsrc, (off & ~3u) + 4u * w, 0u);
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) p[w + y] = q[y];
+                    }
+                }
+                p[RW] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(b_rsrc, (off & ~3u) + RB, 0, 0));
+#pragma unroll
+                for (int w = 0; w < RW; ++w) v[u][w] = __builtin_amdgcn_alignbyte(p[w + 1], p[w], off & 3u);
+            } else if (!off_dwords && off + RB <= b_bytes) {
+                if constexpr (RB == 8) {
+                    const i32x2 p = __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, off, 0, 0);
+                    v[u][0] = static_cast<uint32_t>(p[0]);
+                    v[u][1] = static_cast<uint32_t>(p[1]);
+                } else {
+#pragma unroll
+                    for (int w = 0; w < RW; w += 4) {
+                        const u32x4 p = buf_load16(b_rsrc, off + 4u * w, 0u);
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) v[u][w + y] = p[y];
+                    }
+                }
+            } else {
+                // the end of B: element by element
+#pragma unroll
+                for (int e = 0; e < RB / ES; ++e) {
+                    if (col0 + e >= N) continue;
+                    const uint32_t x = ES == 2 ? static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(b_rsrc, off + 2u * e, 0, 0))
+                                               : static_cast<uint8_t>(__builtin_amdgcn_raw_buffer_load_b8(b_rsrc, off + e, 0, 0));
+                    v[u][ES * e / 4] |= x << (8 * (ES * e % 4));
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x = x0 + u * 64 * kRowWaves;
+            if (x >= n_rows) continue;
+            const int p = quad_panel_row(ES, x % COLS);
+            // 16-bit types: by read (32-row half, four rows of eight), lane group, row
+            const int at = ES == 2 ? 32 * (p >> 5) + 16 * ((p >> 2) & 1) + 4 * ((p >> 3) & 3) + (p & 3) : p;
+            uint32_t* dst = reinterpret_cast<uint32_t*>(panel + (static_cast<size_t>(x / COLS) * COLS + at) * RB);
+            if constexpr (RB == 8) {
+                *reinterpret_cast<u32x2*>(dst) = u32x2{v[u][0], v[u][1]};
+            } else {
+#pragma unroll
+                for (int w = 0; w < RW; w += 4) *reinterpret_cast<u32x4*>(dst + w) = u32x4{v[u][w], v[u][w + 1], v[u][w + 2], v[u][w + 3]};
+            }
+        }
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+
+    Acc acc[RM];
+#pragma unroll
+    for (int r = 0; r < RM; ++r) acc[r] = Acc{0, 0, 0, 0};
+    constexpr uint32_t kReadBytes = (ES == 2 ? 16 : 32) * RB;      // what one transposing read takes
+    const uint32_t read_at = lds_offset_of(panel) +
+        (ES == 2 ? static_cast<uint32_t>(4 * g + (i >> 2)) * RB + 8u * ((i & 3) & (RB / 8 - 1))
+                 : static_cast<uint32_t>(8 * g + (i >> 1)) * RB + 8u * ((i & 1) & (RB / 8 - 1)));
+    auto multiply = [&](int q, const u32x4 (&av)[RM], const uint32_t (&iv)[RM]) {
+        const uint32_t at = read_at + static_cast<uint32_t>(q) * (4u * kReadBytes);
+        u32x2_t b[4];
+        if constexpr (ES == 2) {
+            b[0] = lds_read_tr<0>(at);
+            b[1] = lds_read_tr<kReadBytes>(at);
+            b[2] = lds_read_tr<2 * kReadBytes>(at);
+            b[3] = lds_read_tr<3 * kReadBytes>(at);
+        } else {
+            b[0] = lds_read_tr8<0>(at);
+            b[1] = lds_read_tr8<kReadBytes>(at);
+            b[2] = lds_read_tr8<2 * kReadBytes>(at);
+            b[3] = lds_read_tr8<3 * kReadBytes>(at);
+        }
+        lds_four_done<0>(b);
+        const u32x8 operand = u32x8{b[0][0], b[0][1], b[1][0], b[1][1], b[2][0], b[2][1], b[3][0], b[3][1]};
+        acc[0] = smfmac<DT, 0>(av[0], operand, acc[0], iv[0]);
+        if constexpr (RM == 2) acc[1] = smfmac<DT, 1>(av[1], operand, acc[1], iv[1]);
+    };
+#pragma unroll
+    for (int h = 0; h < PF; ++h)
+        if (wave + kRowWaves * h < nq) multiply(wave + kRowWaves * h, a[h], ix[h]);
+    for (int base = kRowWaves * PF; base < nq; base += kRowWaves * PF) {
+#pragma unroll
+        for (int h = 0; h < PF; ++h) load_step(base + wave + kRowWaves * h, a[h], ix[h]);
+#pragma unroll
+        for (int h = 0; h < PF; ++h)
+            if (base + wave + kRowWaves * h < nq) multiply(base + wave + kRowWaves * h, a[h], ix[h]);
+    }
+
+    // acc[r][y] = partial C'[16 (16 super + j0 + r) + 4 g + y][col0 + i] of this wave's steps
+    __syncthreads();
+    Out* red = reinterpret_cast<Out*>(lds_dyn);
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) red[(wave * RM + r) * 256 + (4 * g + y) * 16 + i] = acc[r][y];
+    __syncthreads();
+    if (tid < RM * 256) {
+        const int r = tid >> 8, row = (tid >> 4) & 15, col = col0 + (tid & 15);
+        Out v = red[r * 256 + (tid & 255)];
+#pragma unroll
+        for (int w = 1; w < kRowWaves; ++w) v += red[(w * RM + r) * 256 + (tid & 255)];
+        const int64_t out_row = perm[(static_cast<int64_t>(super) * 16 + j0 + r) * 16 + row];
+        if (out_row >= 0 && col < N) C[out_row * ldc + col] = v;
+    }
+}
+
+template <int DT, int RM, int RB>
+static int launch_quad_rows_shape(const DeviceBcsr& d, const DenseTiles& t, size_t lds, const void* B, int64_t ldb, void* C, int64_t ldc,
+                                  int64_t N, hipStream_t s)
+{
+    static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_quad_rows_kernel<DT, RM, RB>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kQuadRowsLds));
+    if (ready != hipSuccess) return static_cast<int>(ready);
+    const int n_units = t.n * (16 / RM), per_xcd = (n_units + 7) / 8;
+    const dim3 grid(static_cast<unsigned>(8 * per_xcd), static_cast<unsigned>((N + 15) / 16));
+    constexpr int ES = Elem<DT>::ES;
+    hipLaunchKernelGGL((spmm_quad_rows_kernel<DT, RM, RB>), grid, dim3(64 * kRowWaves), lds, s, n_units, per_xcd, static_cast<int>(N),
+                       static_cast<uint32_t>(((d.K - 1) * ldb + N) * ES), t.super_rows, t.step_ptr, B, t.quad_rows,
+                       static_cast<uint32_t>(ldb * ES), static_cast<uint32_t>(d.K), t.vals, t.quad_index, d.perm,
+                       static_cast<typename Elem<DT>::Out*>(C), ldc);
+    return static_cast<int>(hipGetLastError());
+}
+
+template <int DT, int RM>
+static int launch_quad_rows_rm(const DeviceBcsr& d, const DenseTiles& t, int rb, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N,
+                               hipStream_t s)
+{
+    const size_t lds = quad_rows_lds(t.max_quad_steps, Elem<DT>::ES, rb);
+    if (rb == 8) return launch_quad_rows_shape<DT, RM, 8>(d, t, lds, B, ldb, C, ldc, N, s);
+    if (rb == 16) return launch_quad_rows_shape<DT, RM, 16>(d, t, lds, B, ldb, C, ldc, N, s);
+    if constexpr (Elem<DT>::ES == 2) return launch_quad_rows_shape<DT, RM, 32>(d, t, lds, B, ldb, C, ldc, N, s);
+    return static_cast<int>(hipErrorInvalidValue);
+}
+
+template <int DT>
+static int launch_quad_rows_dtype(const DeviceBcsr& d, const DenseTiles& t, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N,
+                                  hipStream_t s, const char** variant)
+{
+    const int rb = quad_row_bytes(Elem<DT>::ES, N);
+    static thread_local char name[40];
+    const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
+    // one block row per workgroup until every compute unit has one, two beyond that: B is brought in half as often
+    const int rm = t.n * 16 * ((N + 15) / 16) > 256 ? 2 : 1;
+    snprintf(name, sizeof(name), "spmm_%s_q%dr%d_l8", type, rb, rm);
+    *variant = name;
+    return rm == 2 ? launch_quad_rows_rm<DT, 2>(d, t, rb, B, ldb, C, ldc, N, s) : launch_quad_rows_rm<DT, 1>(d, t, rb, B, ldb, C, ldc, N, s);
+}
+
+int launch_quad_rows(const DeviceBcsr& d, const DenseTiles& t, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N,
+                     void* stream, const char** variant)
+{
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (dtype) {
+    case kF16: return launch_quad_rows_dtype<kF16>(d, t, B, ldb, C, ldc, N, s, variant);
+    case kBF16: return launch_quad_rows_dtype<kBF16>(d, t, B, ldb, C, ldc, N, s, variant);
+    case kE4M3: return launch_quad_rows_dtype<kE4M3>(d, t, B, ldb, C, ldc, N, s, variant);
+    case kE5M2: return launch_quad_rows_dtype<kE5M2>(d, t, B, ldb, C, ldc, N, s, variant);
+    default: return launch_quad_rows_dtype<kI8>(d, t, B, ldb, C, ldc, N, s, variant);
     }
 }
 

@@ -63,4 +63,13 @@ inline size_t quad_fill_lds(int64_t K, int64_t max_steps, int es)
 }
 constexpr size_t kQuadFillLds = 64 * 1024;
 
+// The kernel for few columns keeps all of B in LDS: bytes of a row there, and of the whole (the sum of the waves' partial tiles takes 32 KiB)
+inline int quad_row_bytes(int es, int64_t N) { return N * es <= 8 ? 8 : N * es <= 16 || es == 1 ? 16 : 32; }
+inline size_t quad_rows_lds(int64_t max_steps, int es, int row_bytes)
+{
+    const size_t panel = static_cast<size_t>(max_steps) * static_cast<size_t>(quad_columns(es)) * static_cast<size_t>(row_bytes);
+    return panel < 32768 ? 32768 : panel;
+}
+constexpr size_t kQuadRowsLds = 144 * 1024;
+
 }  // namespace smat

@@ -77,3 +77,31 @@ def test_per_row_kernel_on_a_copy_of_b(shape, oracle_c):
     w = w if dtype == "f16" else recast(w, dtype)
     for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
         _exact(w, oracle_c, ldb, ldc, shift)
+
+
+# columns dealt into quads (kernels_quads.hip): fills that give full quads, quads with gaps (20, 25 %), an incomplete last super row, a
+# ragged last step, steps split over workgroups
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
+@pytest.mark.parametrize("shape", [(512, 2100, 136, 0.02), (360, 3000, 129, 0.1), (256, 4100, 272, 0.2), (272, 2050, 8 * 128 + 16, 0.25)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_tile_kernel_on_quads(shape, dtype, oracle_c):
+    M, K, N, density = shape
+    density = max(density, 0.06)                    # (block-dense: eight of sixteen columns of a block)
+    w = random_csr(M, K, N, density, seed=M + N, values="smallint", b_dist="smallint")
+    w = w if dtype == "f16" else recast(w, dtype)
+    piece = 8 if dtype in ("f16", "bf16") else 16
+    ldb = (N + piece - 1) // piece * piece
+    name = _exact(w, oracle_c, ldb, N + 3, 0, dense_tiles=1)
+    assert name.startswith(f"spmm_dense_{dtype}_g2"), name
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
+@pytest.mark.parametrize("N", [1, 4, 7, 8, 9, 16, 17, 32])
+def test_few_columns_on_quads(N, dtype, oracle_c):
+    wide = dtype in ("f16", "bf16")
+    for M, K, density in ((4100, 4096 if N > 8 else 4110, 0.11), (6000, 2500, 0.2)) if wide else ((2600, 4110, 0.11), (4200, 2050, 0.25)):
+        w = random_csr(M, K, N, density, seed=K + N, values="smallint", b_dist="smallint")
+        w = w if dtype == "f16" else recast(w, dtype)
+        for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
+            name = _exact(w, oracle_c, ldb, ldc, shift, dense_tiles=0)
+            assert "_q" in name, (name, M, K)
