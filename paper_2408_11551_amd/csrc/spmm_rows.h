@@ -982,7 +982,9 @@ static int launch_dtype(const DeviceBcsr& d, const void* B, int64_t ldb, void* C
     // 95 us, N = 257 442 against 127; e4m3, 10 M entries, N = 500 173 against 76.)
     const uintptr_t addr = reinterpret_cast<uintptr_t>(B);
     const double cost_on_dwords[17] = {0, 1.0, 1.0, 0, 1.05, 0, 0, 0, 1.4, 0, 0, 0, 0, 0, 0, 0, 1.65};
-    const double cost_off_dwords[17] = {0, 1.0, 2.1, 0, 2.1, 0, 0, 0, 2.4, 0, 0, 0, 0, 0, 0, 0, 2.6};
+    // (16-bit, two elements per load: 1.8 in launches large enough that two passes of one element also read twice as much of A --
+    // 2 M entries, N = 31: 30.2 -> 23.5 us; 0.6 M columns, N = 17: 9.2 against 10.5)
+    const double cost_off_dwords[17] = {0, 1.0, 2.1, 0, ES == 2 && d.b_rows > 1000000 ? 1.8 : 2.1, 0, 0, 0, 2.4, 0, 0, 0, 0, 0, 0, 0, 2.6};
     constexpr int kWidest = 16 / ES;
     auto passes = [&](int nt) { return static_cast<double>((N + 16 * nt - 1) / (16 * nt)); };
     // A few long block rows do not fill the chip: there the launch takes as long as one pass of a
