@@ -484,7 +484,7 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
 // Launch statistics over a subset of block rows.
 void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
 {
-    int64_t longest = 0, packs = 0, rows = 0, bytes = 0, b_rows = 0;
+    int64_t longest = 0, packs = 0, rows = 0, bytes = 0, b_rows = 0, reach = 0;
     int cls = 0;
     for (int64_t br = 0; br < h.bcsr.nbr; ++br) {
         if (skip_dense && h.row_dense[static_cast<size_t>(br)]) continue;
@@ -495,6 +495,8 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
         bytes += len * (rc == smat::kEntryClass ? 32 * h.elem_bytes + 128 : smat::pack_units(rc) * (128 * h.elem_bytes + 32));
         cls = std::max<int>(cls, rc);
         b_rows += h.row_b_rows[static_cast<size_t>(br)];
+        if (h.bcsr.row_ptr[br + 1] > h.bcsr.row_ptr[br])
+            reach += h.bcsr.col_idx[h.bcsr.row_ptr[br + 1] - 1] - h.bcsr.col_idx[h.bcsr.row_ptr[br]];
         ++rows;
     }
     d.n_order = rows;
@@ -503,6 +505,7 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
     d.b_rows = b_rows;
     d.max_row_packs = longest;
     d.mean_row_packs = rows ? static_cast<double>(packs) / static_cast<double>(rows) : 0.0;
+    d.spread = 2 * reach > rows * h.bcsr.nbc;
     d.max_class = cls;
 }
 

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -129,6 +130,7 @@ __device__ __forceinline__ int last_fitting_column(int first, int N)
 constexpr int kStreamA = 1;        // block values and slot tables are read with the non-temporal hint
 constexpr int kStreamC = 2;        // C is stored with it
 constexpr int kUnalignedB = 4;     // N, the rows of B or its base are off the load width
+constexpr int kSlabsByXcd = 8;     // a workgroup's slabs go by its XCD (below)
 
 // Everything a wave needs to walk its share of a block row.
 struct RowWalk {
@@ -581,7 +583,7 @@ template <int NT, int KW, int SW, int NCH, int LMAX, int DT, int NARROW = 0>
 __global__ __launch_bounds__(KW * SW * 64)
 void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ slots, const void* __restrict__ vals,
                  const int32_t* __restrict__ perm, const void* __restrict__ B, uint32_t b_bytes, uint32_t ldb_bytes,
-                 uint32_t K, typename Elem<DT>::Out* __restrict__ C, int64_t ldc, int N, int hints)
+                 uint32_t K, typename Elem<DT>::Out* __restrict__ C, int64_t ldc, int N, int hints, int n_order)
 {
     // The arguments are plain words, the ones needed first in front: the compiler is asked
     // (build flag) to have the dispatcher place the leading ones in scalar registers, so that the
@@ -597,10 +599,22 @@ void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ 
     const int ks = wave % KW;                      // which share of the block row
     const int sl = wave / KW;                      // which column slab of the group
     const int i = lane & 15, g = lane >> 4;
-    const i32x4 rec = reinterpret_cast<const i32x4*>(work)[blockIdx.x];     // one record of the launch table
+    // Several groups of slabs (gridDim.y): group by group over all block rows, so that at any time one group's columns of B are gathered
+    // from -- but then every XCD brings all of B into its L2, S groups one after the other.  With kSlabsByXcd the (group, block row)
+    // pairs, group by group, are dealt to the eight XCDs (workgroup w runs on XCD w mod 8) in eight contiguous
+    // shares: an XCD has S / 8 groups' worth of B.  A share is S of the 8 S pieces "an eighth of the launch table
+    // for one group", an eighth being every eighth record, as without it.
+    uint32_t record = blockIdx.x, group = blockIdx.y;
+    if (hints & kSlabsByXcd) {
+        const uint32_t piece = (blockIdx.x & 7u) * gridDim.y + blockIdx.y;
+        record = (blockIdx.x & ~7u) | (piece & 7u);
+        group = piece >> 3;
+        if (record >= static_cast<uint32_t>(n_order)) return;
+    }
+    const i32x4 rec = reinterpret_cast<const i32x4*>(work)[record];     // one record of the launch table
     const int br = rec[0] & 0x0FFFFFFF;
     const int cls = rec[0] >> 28;                  // 0: L = 2, 1: L = 4, 2: L = 8, 3: entry row
-    const int n0 = (blockIdx.y * SW + sl) * WC;
+    const int n0 = (static_cast<int>(group) * SW + sl) * WC;
 
     RowWalk w;
     w.slots = slots + static_cast<size_t>(static_cast<uint32_t>(rec[2])) * 8;        // 32 bytes of slot table per unit
@@ -747,7 +761,7 @@ void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ 
                 }
             }
         __syncthreads();
-        const int nbase = blockIdx.y * SW * WC;
+        const int nbase = static_cast<int>(group) * SW * WC;
         if constexpr (NT >= 4) {
             // each thread sums and stores four consecutive columns
 #pragma unroll
@@ -846,12 +860,28 @@ static int launch_variant(const DeviceBcsr& d, const void* B, int64_t ldb, void*
     // not push it out: then C is stored past the cache (measured: -7 % where B is 4 MiB, no gain
     // or a loss where B is 16 MiB and more).
     if (static_cast<double>(d.K) * static_cast<double>(N) * ES <= 8.0e6) hints |= kStreamC;
+    // Slabs by XCD (see the kernel): what the L2s take in is B once per XCD and A once per group of slabs (once in all where an
+    // XCD's eighth of A stays in its L2); dealt by XCD, B only as often as XCDs share a group.  A counts three times: a
+    // matrix of 6 MB, B of 4 and 8 MB, lost 5 %.  It pays where rows reach all over B, a group's part of B about fits an L2 and
+    // the groups are full: 16384 rows of 16 entries, N = 256 15.1 -> 13.1 us, N = 512 26.0 -> 22.8; a graph of 22425 rows, N = 576
+    // 48.2 -> 43.5.  Not with rows in step (even_rows), which an XCD then no longer holds all at once: N = 512 93 -> 104 us.
+    const double per_group_b = static_cast<double>(d.K) * static_cast<double>(per_group) * ES;
+    if (grid.y > 1 && grid.x < (1u << 30) && !even_rows && d.spread && per_group_b <= 8.0e6 &&
+        static_cast<double>(N) >= 0.85 * static_cast<double>(per_group) * grid.y) {
+        const double b_once = static_cast<double>(d.K) * static_cast<double>(N) * ES, a_once = static_cast<double>(d.stream_bytes), groups = grid.y;
+        const double in_turn = 8.0 * b_once + (a_once < 16.0e6 ? 1.0 : groups) * a_once;
+        const double by_xcd = std::min(8.0, std::ceil(8.0 / groups) + (8 % grid.y ? 1.0 : 0.0)) * b_once + 3.0 * groups * a_once;
+        if (by_xcd < 0.8 * in_turn && in_turn - by_xcd > 20.0e6) {
+            hints |= kSlabsByXcd;
+            grid.x = (grid.x + 7u) / 8u * 8u;
+        }
+    }
     // asked once per kernel and process (the devices of a process are taken to be alike)
     static const Residency info = query_residency(reinterpret_cast<const void*>(&spmm_kernel<NT, KW, SW, NCH, LMAX, DT, NARROW>), KW * SW);
     const size_t lds = lds_to_limit_residency(info, KW * SW, static_cast<int64_t>(grid.x) * grid.y, even_rows);
     hipLaunchKernelGGL((spmm_kernel<NT, KW, SW, NCH, LMAX, DT, NARROW>), grid, dim3(KW * SW * 64), lds, stream,
                        d.work, d.slots, d.vals, d.perm, B, b_bytes, static_cast<uint32_t>(ldb * ES), static_cast<uint32_t>(d.K),
-                       static_cast<typename Elem<DT>::Out*>(C), ldc, static_cast<int>(N), hints);
+                       static_cast<typename Elem<DT>::Out*>(C), ldc, static_cast<int>(N), hints, static_cast<int>(d.n_order));
     return static_cast<int>(hipGetLastError());
 }
 
