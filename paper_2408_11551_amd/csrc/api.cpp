@@ -65,6 +65,7 @@ struct smat_handle {
     // The two-of-four form of the dense super rows (quad_layout.h), in place of the tables above; empty if it does not pay.
     std::vector<int32_t> quad_ptr, quad_rows;
     int max_quad_steps = 0;
+    int quad_tail = 0;                   // 1: a last super row too short for a tile follows the others, for the kernel for few columns
     int64_t quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr.back(); }
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
     smat::DeviceBcsr dev;                // launch over every block row
@@ -165,9 +166,9 @@ Layout make_layout(const smat_handle& h)
     l.csr_col_idx = take(nnz * sizeof(int32_t));
     l.csr_vals = take(nnz * sizeof(uint16_t));
     l.col_perm = take(h.cols_permuted ? static_cast<size_t>(h.csr.K) * sizeof(int32_t) : 0);
-    l.t_super = take(h.dense_super.size() * sizeof(int32_t));
+    l.t_super = take((h.dense_super.size() + static_cast<size_t>(h.quad_tail)) * sizeof(int32_t));
     const size_t quads = static_cast<size_t>(h.quad_steps());
-    l.t_ptr = take(h.step_ptr.size() * sizeof(int32_t));
+    l.t_ptr = take((quads ? h.quad_ptr.size() : h.step_ptr.size()) * sizeof(int32_t));
     l.t_cols = take(quads ? 0 : h.step_cols.size() * sizeof(int32_t));
     l.t_rows = take(quads ? 0 : h.step_rows.size() * sizeof(uint32_t));
     l.t_base = take(quads ? 0 : h.step_base.size() * sizeof(uint32_t));
@@ -291,14 +292,20 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
     const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : 1.0) * static_cast<double>(steps);
     // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
     if (static_cast<double>(nnz) > (es == 2 ? 0.3 : h.dtype == SMAT_I8 ? 0.27 : 0.4) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
-    std::vector<std::vector<int32_t>> placed(static_cast<size_t>(n));
-    workers.ranges(n, 1, [&](int64_t n0, int64_t n1, int) {
+    // A last super row of a few block rows is left to the per-row kernel by the tile kernels, whose tile would be mostly empty; in
+    // the kernel for few columns it saves a launch (1300 x 6000 in int8, N = 3: 12.6 us with it, of 82 block rows two).
+    std::vector<int32_t> supers(h.dense_super);
+    const int64_t last = (h.bcsr.nbr - 1) / 16;
+    if (n == last && h.dense_super.back() == last - 1) supers.push_back(static_cast<int32_t>(last));
+    const int64_t n_all = static_cast<int64_t>(supers.size());
+    std::vector<std::vector<int32_t>> placed(static_cast<size_t>(n_all));
+    workers.ranges(n_all, 1, [&](int64_t n0, int64_t n1, int) {
         struct Rows { uint64_t w[4]; };
         std::vector<Rows> mask(static_cast<size_t>(K));
         std::vector<int32_t> next(static_cast<size_t>(K) + 1);                           // columns left: next[0] the first, next[c + 1] the one after c; 0: none
         for (int64_t x = n0; x < n1; ++x) {
             std::fill(mask.begin(), mask.end(), Rows{{0, 0, 0, 0}});
-            const int64_t first = static_cast<int64_t>(h.dense_super[static_cast<size_t>(x)]) * 256;
+            const int64_t first = static_cast<int64_t>(supers[static_cast<size_t>(x)]) * 256;
             for (int64_t i = first; i < std::min<int64_t>(h.csr.M, first + 256); ++i) {
                 const size_t r = static_cast<size_t>(h.bcsr.perm[static_cast<size_t>(i)]);
                 for (int64_t p = h.csr.row_ptr[r]; p < h.csr.row_ptr[r + 1]; ++p)
@@ -344,13 +351,14 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
             }
         }
     });
-    int64_t total = 0, most = 0;
-    for (const auto& out : placed) {
-        const int64_t q = (static_cast<int64_t>(out.size()) + cols - 1) / cols;
+    int64_t total = 0, tiled = 0, most = 0;
+    for (int64_t x = 0; x < n_all; ++x) {
+        const int64_t q = (static_cast<int64_t>(placed[static_cast<size_t>(x)].size()) + cols - 1) / cols;
         total += q;
+        if (x < n) tiled += q;
         most = std::max(most, q);
     }
-    if (static_cast<double>(total) > most_steps || smat::quad_fill_lds(K, most, es) > smat::kQuadFillLds || most * cols > 65535) return;
+    if (static_cast<double>(tiled) > most_steps || smat::quad_fill_lds(K, most, es) > smat::kQuadFillLds || most * cols > 65535) return;
     if ((total + 1) * cols * 4 >= (int64_t{1} << 31)) return;
     h.quad_ptr.assign(1, 0);
     h.quad_rows.assign(static_cast<size_t>((total + 1) * cols), static_cast<int32_t>(K));
@@ -361,6 +369,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
         h.quad_ptr.push_back(h.quad_ptr.back() + static_cast<int32_t>((static_cast<int64_t>(out.size()) + cols - 1) / cols));
     }
     h.max_quad_steps = static_cast<int>(most);
+    h.quad_tail = static_cast<int>(n_all - n);
 }
 
 // Stored entries of block row br in the order of an entry row's slots (pack_layout.h): by
@@ -707,9 +716,12 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         if ((e = up(l.perm, perm_padded.data(), perm_padded.size() * 4))) return hip_fail("copy perm", e);
         if ((e = up(l.work, work.data(), work.size() * 4))) return hip_fail("copy launch table", e);
         if ((e = up(l.work_rest, work_rest.data(), work_rest.size() * 4))) return hip_fail("copy launch table", e);
-        if ((e = up(l.t_super, h->dense_super.data(), h->dense_super.size() * 4))) return hip_fail("copy tiles", e);
+        std::vector<int32_t> supers(h->dense_super);
+        if (h->quad_tail) supers.push_back(static_cast<int32_t>((b.nbr - 1) / 16));
+        if ((e = up(l.t_super, supers.data(), supers.size() * 4))) return hip_fail("copy tiles", e);
         const bool quads = h->quad_steps() > 0;
-        if ((e = up(l.t_ptr, quads ? h->quad_ptr.data() : h->step_ptr.data(), h->step_ptr.size() * 4))) return hip_fail("copy tiles", e);
+        if ((e = quads ? up(l.t_ptr, h->quad_ptr.data(), h->quad_ptr.size() * 4) : up(l.t_ptr, h->step_ptr.data(), h->step_ptr.size() * 4)))
+            return hip_fail("copy tiles", e);
         if (quads) {
             if ((e = up(l.t_quad_rows, h->quad_rows.data(), h->quad_rows.size() * 4))) return hip_fail("copy tiles", e);
         } else {
@@ -764,6 +776,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.quad_index = reinterpret_cast<const uint8_t*>(base + l.t_quad_index);
         tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
         tiles.max_quad_steps = h->max_quad_steps;
+        tiles.quad_tail = h->quad_tail;
         tiles.scratch = nullptr;           // a call takes the area of its stream
         tiles.scratch_bytes = 0;
         tiles.n = static_cast<int32_t>(h->dense_super.size());
@@ -910,18 +923,24 @@ char* scratch_area_of(const smat_handle* h, const void* stream)
 // columns are mostly empty.
 constexpr int64_t kStageColumns = 32;
 
-// Does the kernel for few columns on the two-of-four form take N columns?  It pays where the values kept by column, which the per-row
-// kernel streams, are many: from about 18 MB on in the 16-bit types (22 MB where B takes 32 bytes per row: 4096 x 3000 at 10 %, N = 8: 5.9
-// against 5.5 us, N = 16: 5.9 against 6.3), 8 MB in the 8-bit ones.  More than sixteen columns take two passes over A,
-// which pays while A stays in the L2s (21 MB, N = 32: 11.3 against 9.1 us; 42 MB: 13.3 against 21.7).
-bool quad_rows_take(const smat_handle& h, int64_t N)
+// Does the kernel for few columns on the two-of-four form take N columns?  Both estimates, in us, were fitted on random matrices of
+// 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
+// once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
+// out of the L2s or from further away.
+bool quad_rows_take(const smat_handle& h, int64_t N, bool off_dwords)
 {
     if (h.tiles.n_quad_steps == 0 || N > 32) return false;
-    if (N > 16 && static_cast<int64_t>(h.tiles.n_quad_steps) * (h.elem_bytes == 1 ? 20480 : 18432) > 24000000) return false;
-    const int row_bytes = smat::quad_row_bytes(h.elem_bytes, N);
-    const int64_t by_column = h.dense_columns * 16 * h.elem_bytes;
-    return by_column >= (h.elem_bytes == 1 ? 8000000 : row_bytes == 32 ? 22000000 : 18000000) &&
-           smat::quad_rows_lds(h.max_quad_steps, h.elem_bytes, row_bytes) <= smat::kQuadRowsLds;
+    const int es = h.elem_bytes, row_bytes = smat::quad_row_bytes(es, N, h.max_quad_steps);
+    if (row_bytes == 0) return false;
+    const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
+    const double columns = static_cast<double>(h.dense_columns), block_rows = 16.0 * h.tiles.n;
+    const double per_column = es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
+    const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
+    const double a_mb = static_cast<double>(h.tiles.n_quad_steps) * (es == 1 ? 20480e-6 : 18432e-6);
+    const double quads_us = 4.2 + 0.008 * h.max_quad_steps * passes + 1.0e-5 * static_cast<double>(smat::quad_rows_lds(h.max_quad_steps, es, row_bytes)) +
+                            a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (off_dwords ? 0.7 : 0.0) +
+                            (h.dev_rest.n_order > 0 && !h.quad_tail ? 5.0 : 0.0);      // a launch for the other block rows
+    return quads_us + 0.3 < rows_us;
 }
 
 // smat_spmm with the area for partial tiles given by the caller of this function.
@@ -999,8 +1018,9 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     const char* variant = "";
     thread_local std::string name;
     int e = 0;
-    if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N)) {
-        if (h->dev_rest.n_order > 0) e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+    if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N, ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0)) {
+        // (with the last few block rows among the quads, all are: quad_tail)
+        if (h->dev_rest.n_order > 0 && !h->quad_tail) e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
         if (!e) e = smat::launch_quad_rows(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
         g_kernel = variant;
     } else if (use_tiles) {

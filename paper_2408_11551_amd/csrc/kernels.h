@@ -67,6 +67,7 @@ struct DenseTiles {
     const int32_t* quad_rows = nullptr;    // [quad_columns * (n_quad_steps + 1)] rows of B of a step's panel; the last step names none
     const uint8_t* quad_index = nullptr;   // [2 or 4 KiB * n_quad_steps] positions of the values
     int32_t n_quad_steps = 0, max_quad_steps = 0;      // all, and those of the longest super row
+    int32_t quad_tail = 0;                 // 1: super row number n is there too (not as a tile, for launch_quad_rows), and then all block rows are
 };
 
 constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave groups share a tile

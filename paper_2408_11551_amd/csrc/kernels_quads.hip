@@ -318,7 +318,8 @@ void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int 
 // the first of a wave's values are asked for, all of B (K rows of RB bytes, rounded up from N) is brought into LDS in the order of the
 // super row's table, and what is left are transposing reads and one matrix instruction per step and block row.  The sixteen
 // partial tiles are added through LDS in a fixed order.
-// RB: bytes per row of B in LDS, 8, 16 or 32: 4, 8 or 16 columns of a 16-bit type, 8 or 16 of an 8-bit one.  The sixteen rows (8-bit types:
+// RB: bytes per row of B in LDS, 8, 16 or 32: 4, 8 or 16 columns of a 16-bit type, 8 or 16 of an 8-bit one; more columns, or a
+// B of which LDS holds no more at a time, take several passes over A (blockIdx.y).  The sixteen rows (8-bit types:
 // 32) that a transposing read takes lie one after the other, so it meets no bank twice; columns past RB are
 // read again from its beginning, and columns past N hold whatever follows in B: neither is stored.
 constexpr int kRowWaves = 16;
@@ -342,7 +343,8 @@ void spmm_quad_rows_kernel(int n_units, int per_xcd, int N, uint32_t b_bytes, co
     const int unit = static_cast<int>(blockIdx.x % 8u) * per_xcd + static_cast<int>(blockIdx.x / 8u);      // an XCD has whole super rows
     if (unit >= n_units) return;
     const int sidx = unit / UNITS, j0 = unit % UNITS * RM;
-    const int col0 = static_cast<int>(blockIdx.y) * 16;
+    constexpr int CP = RB / ES < 16 ? RB / ES : 16;        // columns per pass
+    const int col0 = static_cast<int>(blockIdx.y) * CP;
     const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, i = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q_first = step_ptr[sidx], nq = step_ptr[sidx + 1] - q_first;
@@ -515,7 +517,7 @@ void spmm_quad_rows_kernel(int n_units, int per_xcd, int N, uint32_t b_bytes, co
 #pragma unroll
         for (int w = 1; w < kRowWaves; ++w) v += red[(w * RM + r) * 256 + (tid & 255)];
         const int64_t out_row = perm[(static_cast<int64_t>(super) * 16 + j0 + r) * 16 + row];
-        if (out_row >= 0 && col < N) C[out_row * ldc + col] = v;
+        if (out_row >= 0 && (tid & 15) < CP && col < N) C[out_row * ldc + col] = v;
     }
 }
 
@@ -526,9 +528,9 @@ static int launch_quad_rows_shape(const DeviceBcsr& d, const DenseTiles& t, size
     static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_quad_rows_kernel<DT, RM, RB>),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kQuadRowsLds));
     if (ready != hipSuccess) return static_cast<int>(ready);
-    const int n_units = t.n * (16 / RM), per_xcd = (n_units + 7) / 8;
-    const dim3 grid(static_cast<unsigned>(8 * per_xcd), static_cast<unsigned>((N + 15) / 16));
+    const int n_units = (t.n + t.quad_tail) * (16 / RM), per_xcd = (n_units + 7) / 8;
     constexpr int ES = Elem<DT>::ES;
+    const dim3 grid(static_cast<unsigned>(8 * per_xcd), static_cast<unsigned>(quad_row_passes(ES, N, RB)));
     hipLaunchKernelGGL((spmm_quad_rows_kernel<DT, RM, RB>), grid, dim3(64 * kRowWaves), lds, s, n_units, per_xcd, static_cast<int>(N),
                        static_cast<uint32_t>(((d.K - 1) * ldb + N) * ES), t.super_rows, t.step_ptr, B, t.quad_rows,
                        static_cast<uint32_t>(ldb * ES), static_cast<uint32_t>(d.K), t.vals, t.quad_index, d.perm,
@@ -551,11 +553,11 @@ template <int DT>
 static int launch_quad_rows_dtype(const DeviceBcsr& d, const DenseTiles& t, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N,
                                   hipStream_t s, const char** variant)
 {
-    const int rb = quad_row_bytes(Elem<DT>::ES, N);
+    const int rb = quad_row_bytes(Elem<DT>::ES, N, t.max_quad_steps);
     static thread_local char name[40];
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
     // one block row per workgroup until every compute unit has one, two beyond that: B is brought in half as often
-    const int rm = t.n * 16 * ((N + 15) / 16) > 256 ? 2 : 1;
+    const int rm = (t.n + t.quad_tail) * 16 * quad_row_passes(Elem<DT>::ES, N, rb) > 256 ? 2 : 1;
     snprintf(name, sizeof(name), "spmm_%s_q%dr%d_l8", type, rb, rm);
     *variant = name;
     return rm == 2 ? launch_quad_rows_rm<DT, 2>(d, t, rb, B, ldb, C, ldc, N, s) : launch_quad_rows_rm<DT, 1>(d, t, rb, B, ldb, C, ldc, N, s);
@@ -641,7 +643,7 @@ int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* cs
     if (t.n == 0) return 0;
     const int place_bytes = static_cast<int>(quad_place_bytes(d.K)), words = max_steps * quad_columns(elem_bytes) / 32;
     const size_t lds = quad_fill_lds(d.K, max_steps, elem_bytes);
-    const dim3 grid(static_cast<unsigned>(t.n) * 16);
+    const dim3 grid(static_cast<unsigned>(t.n + t.quad_tail) * 16);
     if (elem_bytes == 1)
         hipLaunchKernelGGL(quad_fill_kernel<uint8_t>, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx,
                            csr_vals, static_cast<uint8_t*>(vals_out), static_cast<uint8_t*>(index_out), place_bytes, words);

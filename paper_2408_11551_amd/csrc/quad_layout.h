@@ -63,13 +63,24 @@ inline size_t quad_fill_lds(int64_t K, int64_t max_steps, int es)
 }
 constexpr size_t kQuadFillLds = 64 * 1024;
 
-// The kernel for few columns keeps all of B in LDS: bytes of a row there, and of the whole (the sum of the waves' partial tiles takes 32 KiB)
-inline int quad_row_bytes(int es, int64_t N) { return N * es <= 8 ? 8 : N * es <= 16 || es == 1 ? 16 : 32; }
+// The kernel for few columns keeps all rows of B in LDS, as many bytes of each as there are columns or as LDS holds: the whole
+// (the sum of the waves' partial tiles takes 32 KiB), bytes of a row -- 0 if not even eight fit -- and passes over the columns.
 inline size_t quad_rows_lds(int64_t max_steps, int es, int row_bytes)
 {
     const size_t panel = static_cast<size_t>(max_steps) * static_cast<size_t>(quad_columns(es)) * static_cast<size_t>(row_bytes);
     return panel < 32768 ? 32768 : panel;
 }
 constexpr size_t kQuadRowsLds = 144 * 1024;
+inline int quad_row_bytes(int es, int64_t N, int64_t max_steps)
+{
+    int bytes = N * es <= 8 ? 8 : N * es <= 16 || es == 1 ? 16 : 32;
+    while (bytes >= 8 && quad_rows_lds(max_steps, es, bytes) > kQuadRowsLds) bytes /= 2;
+    return bytes >= 8 ? bytes : 0;
+}
+inline int64_t quad_row_passes(int es, int64_t N, int row_bytes)
+{
+    const int64_t columns = row_bytes / es < 16 ? row_bytes / es : 16;
+    return (N + columns - 1) / columns;
+}
 
 }  // namespace smat
