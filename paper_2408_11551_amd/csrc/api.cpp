@@ -139,7 +139,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t perm, work, work_rest, slots, vals, pack_ptr, slots_off, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
     size_t csr_row_ptr, csr_col_idx, csr_vals, col_perm;
-    size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, total;
+    size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, tables_end, total;
 };
 
 Layout make_layout(const smat_handle& h)
@@ -149,22 +149,16 @@ Layout make_layout(const smat_handle& h)
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
     const size_t nbr = static_cast<size_t>(h.bcsr.nbr), n_e = static_cast<size_t>(h.bcsr.n_blocks);
     const size_t nnz = h.csr.col_idx.size();
+    // the tables, which are sent in one piece
     l.perm = take((nbr + 15) / 16 * 256 * sizeof(int32_t));          // whole super rows: the tile kernel reads a last one that is not complete
     l.work = take(nbr * 16);
     l.work_rest = take(nbr * 16);
-    l.slots = take(static_cast<size_t>(h.slots_units) * 32);
-    l.vals = take(static_cast<size_t>(h.vals_units) * 64);
     l.pack_ptr = take((nbr + 1) * sizeof(int32_t));
     l.slots_off = take((nbr + 1) * sizeof(uint32_t));
     l.vals_off = take((nbr + 1) * sizeof(uint32_t));
     l.row_class = take(nbr);
     l.blk_ptr = take((nbr + 1) * sizeof(int32_t));
-    l.blk_col = take(n_e * sizeof(int32_t));
-    l.blk_pack = take(h.by_column ? n_e * sizeof(int32_t) : 0);
-    l.blk_meta = take(h.by_column ? n_e * sizeof(uint32_t) : 0);
     l.csr_row_ptr = take((static_cast<size_t>(h.csr.M) + 1) * sizeof(int64_t));
-    l.csr_col_idx = take(nnz * sizeof(int32_t));
-    l.csr_vals = take(nnz * sizeof(uint16_t));
     l.col_perm = take(h.cols_permuted ? static_cast<size_t>(h.csr.K) * sizeof(int32_t) : 0);
     l.t_super = take((h.dense_super.size() + static_cast<size_t>(h.quad_tail)) * sizeof(int32_t));
     const size_t quads = static_cast<size_t>(h.quad_steps());
@@ -172,8 +166,18 @@ Layout make_layout(const smat_handle& h)
     l.t_cols = take(quads ? 0 : h.step_cols.size() * sizeof(int32_t));
     l.t_rows = take(quads ? 0 : h.step_rows.size() * sizeof(uint32_t));
     l.t_base = take(quads ? 0 : h.step_base.size() * sizeof(uint32_t));
-    l.t_vals = take(quads ? quads * 16384 : static_cast<size_t>(h.dense_slots) * 1024);
     l.t_quad_rows = take(h.quad_rows.size() * sizeof(int32_t));
+    l.tables_end = off;
+    // one element per stored entry or block, sent each by itself
+    l.blk_col = take(n_e * sizeof(int32_t));
+    l.blk_pack = take(h.by_column ? n_e * sizeof(int32_t) : 0);
+    l.blk_meta = take(h.by_column ? n_e * sizeof(uint32_t) : 0);
+    l.csr_col_idx = take(nnz * sizeof(int32_t));
+    l.csr_vals = take(nnz * sizeof(uint16_t));
+    // made on the device
+    l.slots = take(static_cast<size_t>(h.slots_units) * 32);
+    l.vals = take(static_cast<size_t>(h.vals_units) * 64);
+    l.t_vals = take(quads ? quads * 16384 : static_cast<size_t>(h.dense_slots) * 1024);
     l.t_quad_index = take(quads * (h.elem_bytes == 1 ? 4096 : 2048));
     l.t_scratch = take(h.dense_super.empty() && !rows_may_stage(h) ? 0 : kTileScratchBytes * static_cast<size_t>(h.n_scratch_areas));
     l.total = off ? off : kAlign;
@@ -563,7 +567,7 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
             if (row_ptr[r + 1] < row_ptr[r]) return fail(SMAT_ERR_BAD_CSR, "row_ptr decreases at row " + std::to_string(r));
         const int64_t nnz = row_ptr[M];
         if (nnz > 0 && (!col_idx || !vals)) return fail(SMAT_ERR_INVALID_ARG, "col_idx or vals is NULL");
-        smat::Workers workers;
+        smat::Workers workers(nnz);
         const std::string bad = smat::validate_csr(M, K, row_ptr, col_idx, workers);
         if (!bad.empty()) return fail(SMAT_ERR_BAD_CSR, bad);
 
@@ -693,54 +697,57 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         const size_t nbr = static_cast<size_t>(b.nbr), n_e = b.col_idx.size();
         const size_t M = static_cast<size_t>(h->csr.M), nnz = h->csr.col_idx.size();
 
-        std::vector<int32_t> perm_padded((nbr + 15) / 16 * 256, -1);
-        std::memcpy(perm_padded.data(), b.perm.data(), sizeof(int32_t) * M);
+        // The tables are put together here as they lie in the workspace and sent with one copy: a copy costs the host about 10 us
+        // however short it is (a band of 7339 rows: 0.3 of a set-up's 1.0 ms).
+        smat::Buf<char> tables(l.tables_end);
+        auto put = [&](size_t off, const void* src, size_t n) { if (n) std::memcpy(tables.data() + off, src, n); };
+        int32_t* perm = reinterpret_cast<int32_t*>(tables.data() + l.perm);
+        std::fill(perm, perm + (nbr + 15) / 16 * 256, -1);
+        put(l.perm, b.perm.data(), sizeof(int32_t) * M);
         // launch tables: all block rows, and those the dense path does not cover
-        std::vector<int32_t> work(nbr * 4), work_rest;
-        work_rest.reserve(nbr * 4);
+        int32_t* work = reinterpret_cast<int32_t*>(tables.data() + l.work);
+        int32_t* work_rest = reinterpret_cast<int32_t*>(tables.data() + l.work_rest);
         for (size_t x = 0; x < nbr; ++x) {
             const size_t br = static_cast<size_t>(h->order[x]);
-            int32_t* rec = work.data() + 4 * x;
+            int32_t* rec = work + 4 * x;
             rec[0] = static_cast<int32_t>(br) | (static_cast<int32_t>(h->row_class[br]) << 28);
             rec[1] = h->pack_ptr[br + 1] - h->pack_ptr[br];
             rec[2] = static_cast<int32_t>(h->slots_off[br]);
             rec[3] = static_cast<int32_t>(h->vals_off[br]);
-            if (!h->row_dense[br]) work_rest.insert(work_rest.end(), rec, rec + 4);
+            if (!h->row_dense[br]) work_rest = std::copy(rec, rec + 4, work_rest);
         }
+        std::vector<int32_t> supers(h->dense_super);
+        if (h->quad_tail) supers.push_back(static_cast<int32_t>((b.nbr - 1) / 16));
+        put(l.t_super, supers.data(), supers.size() * 4);
+        const bool quads = h->quad_steps() > 0;
+        if (quads) {
+            put(l.t_ptr, h->quad_ptr.data(), h->quad_ptr.size() * 4);
+            put(l.t_quad_rows, h->quad_rows.data(), h->quad_rows.size() * 4);
+        } else {
+            put(l.t_ptr, h->step_ptr.data(), h->step_ptr.size() * 4);
+            put(l.t_cols, h->step_cols.data(), h->step_cols.size() * 4);
+            put(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4);
+            put(l.t_base, h->step_base.data(), h->step_base.size() * 4);
+        }
+        put(l.pack_ptr, h->pack_ptr.data(), h->pack_ptr.size() * 4);
+        put(l.slots_off, h->slots_off.data(), h->slots_off.size() * 4);
+        put(l.vals_off, h->vals_off.data(), h->vals_off.size() * 4);
+        put(l.row_class, h->row_class.data(), h->row_class.size());
+        put(l.blk_ptr, b.row_ptr.data(), b.row_ptr.size() * 4);
+        if (h->cols_permuted) put(l.col_perm, b.col_perm.data(), b.col_perm.size() * 4);
+        put(l.csr_row_ptr, h->csr.row_ptr.data(), (M + 1) * 8);
 
         auto up = [&](size_t off, const void* src, size_t n) -> int {
             if (n == 0) return 0;
             return static_cast<int>(hipMemcpyAsync(base + off, src, n, hipMemcpyHostToDevice, s));
         };
         int e;
-        if ((e = up(l.perm, perm_padded.data(), perm_padded.size() * 4))) return hip_fail("copy perm", e);
-        if ((e = up(l.work, work.data(), work.size() * 4))) return hip_fail("copy launch table", e);
-        if ((e = up(l.work_rest, work_rest.data(), work_rest.size() * 4))) return hip_fail("copy launch table", e);
-        std::vector<int32_t> supers(h->dense_super);
-        if (h->quad_tail) supers.push_back(static_cast<int32_t>((b.nbr - 1) / 16));
-        if ((e = up(l.t_super, supers.data(), supers.size() * 4))) return hip_fail("copy tiles", e);
-        const bool quads = h->quad_steps() > 0;
-        if ((e = quads ? up(l.t_ptr, h->quad_ptr.data(), h->quad_ptr.size() * 4) : up(l.t_ptr, h->step_ptr.data(), h->step_ptr.size() * 4)))
-            return hip_fail("copy tiles", e);
-        if (quads) {
-            if ((e = up(l.t_quad_rows, h->quad_rows.data(), h->quad_rows.size() * 4))) return hip_fail("copy tiles", e);
-        } else {
-            if ((e = up(l.t_cols, h->step_cols.data(), h->step_cols.size() * 4))) return hip_fail("copy tiles", e);
-            if ((e = up(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4))) return hip_fail("copy tiles", e);
-            if ((e = up(l.t_base, h->step_base.data(), h->step_base.size() * 4))) return hip_fail("copy tiles", e);
-        }
-        if ((e = up(l.pack_ptr, h->pack_ptr.data(), h->pack_ptr.size() * 4))) return hip_fail("copy pack offsets", e);
-        if ((e = up(l.slots_off, h->slots_off.data(), h->slots_off.size() * 4))) return hip_fail("copy slot offsets", e);
-        if ((e = up(l.vals_off, h->vals_off.data(), h->vals_off.size() * 4))) return hip_fail("copy value offsets", e);
-        if ((e = up(l.row_class, h->row_class.data(), h->row_class.size()))) return hip_fail("copy row classes", e);
-        if ((e = up(l.blk_ptr, b.row_ptr.data(), b.row_ptr.size() * 4))) return hip_fail("copy block offsets", e);
+        if ((e = up(0, tables.data(), l.tables_end))) return hip_fail("copy tables", e);
         if (h->by_column) {
             if ((e = up(l.blk_col, b.col_idx.data(), n_e * 4))) return hip_fail("copy block columns", e);
             if ((e = up(l.blk_pack, h->blk_pack.data(), n_e * 4))) return hip_fail("copy block packs", e);
             if ((e = up(l.blk_meta, h->blk_meta.data(), n_e * 4))) return hip_fail("copy block masks", e);
         }
-        if (h->cols_permuted && (e = up(l.col_perm, b.col_perm.data(), b.col_perm.size() * 4))) return hip_fail("copy column order", e);
-        if ((e = up(l.csr_row_ptr, h->csr.row_ptr.data(), (M + 1) * 8))) return hip_fail("copy csr row_ptr", e);
         if ((e = up(l.csr_col_idx, h->csr.col_idx.data(), nnz * 4))) return hip_fail("copy csr col_idx", e);
         if ((e = up(l.csr_vals, h->csr.vals.data(), nnz * 2))) return hip_fail("copy csr vals", e);
         // the host vectors above must outlive the asynchronous copies: synchronised below, before they go
@@ -794,7 +801,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
                                         h->cols_permuted ? reinterpret_cast<const int32_t*>(base + l.col_perm) : nullptr, base + l.vals,
                                         reinterpret_cast<uint32_t*>(base + l.slots), static_cast<size_t>(h->slots_units) * 8, h->elem_bytes, s)))
             return hip_fail("fill block values", e);
-        if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_rows - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
+        if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_index - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
         e = quads ? smat::launch_quad_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
                                            h->elem_bytes, h->max_quad_steps, s)
                   : smat::launch_dense_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);

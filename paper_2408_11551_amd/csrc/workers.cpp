@@ -8,12 +8,12 @@
 
 namespace smat {
 
-Workers::Workers()
+Workers::Workers(int64_t entries)
 {
     cpu_set_t set;
     CPU_ZERO(&set);
     const int cpus = sched_getaffinity(0, sizeof(set), &set) == 0 ? CPU_COUNT(&set) : 1;
-    most_ = std::clamp(cpus, 1, 16);
+    most_ = static_cast<int>(std::clamp<int64_t>(std::min<int64_t>(cpus, entries / kPerThread + 1), 1, 16));
     if (const char* omp = std::getenv("OMP_NUM_THREADS")) {
         const int n = std::atoi(omp);
         if (n > 0) most_ = std::min(most_, n);

@@ -24,11 +24,13 @@ struct Uninitialized : std::allocator<T> {
 };
 template <typename T> using Buf = std::vector<T, Uninitialized<T>>;
 
-// Up to sixteen threads (no more than the process may run on, nor than OMP_NUM_THREADS), started by the first loop that is
+// Up to sixteen threads (no more than the process may run on, nor than OMP_NUM_THREADS, nor one per kPerThread stored
+// entries: starting one takes as long as some ten thousand entries), started by the first loop that is
 // worth it and joined by the destructor: an object lives as long as the call that made it.
 class Workers {
 public:
-    Workers();
+    static constexpr int64_t kPerThread = 16384;
+    explicit Workers(int64_t entries);
     ~Workers();
     Workers(const Workers&) = delete;
     Workers& operator=(const Workers&) = delete;
