@@ -79,8 +79,9 @@ typedef struct {
                            and keeps their partial tiles in the workspace; each of the first
                            concurrent_streams distinct streams the handle sees owns an area of
                            32 MiB for them (part of smat_device_bytes when the matrix has
-                           block-dense parts).  Calls on further streams are still correct:
-                           they run such launches unsplit                                    */
+                           block-dense parts, or uses the rows of B often enough for a copy of
+                           a B off the cache lines to pay).  Calls on further streams are still
+                           correct: they run such launches unsplit, and without the copy       */
 } smat_options_t;
 
 /* Default options: 16 x 16 blocks, reordering on, tau = 0.7, dense_tiles = 0, concurrent_streams = 2. */
@@ -194,9 +195,10 @@ smat_status_t smat_export_device_vals(const smat_handle_t *h, void *vals, void *
  *
  * Stream-ordered and re-entrant: calls on different handles, and calls on the SAME handle on
  * different streams with different C, may be in flight at the same time (from one host thread
- * or several).  The only state a call uses besides its arguments is an area of partial tiles
- * for launches with few block-dense tiles; every stream has its own (option concurrent_streams),
- * and a call on a stream without one runs such a launch unsplit -- the same product, summed in
+ * or several).  The only state a call uses besides its arguments is an area for the partial
+ * tiles of launches with few block-dense tiles and for a copy of a B whose rows lie off the pieces or
+ * lines the kernels want; every stream has its own (option concurrent_streams),
+ * and a call on a stream without one does without -- the same product, summed in
  * another order.  For a given handle, stream and arguments the result is bitwise reproducible.
  * Limits: the bytes of B that are addressed, ((K-1)*ldb + N) * bytes per value, must stay below 2 GiB;
  * ldb < 2^23; N <= 1048560.
