@@ -293,10 +293,11 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
         for (int64_t br = 16 * static_cast<int64_t>(s); br < std::min<int64_t>(h.bcsr.nbr, 16 * static_cast<int64_t>(s) + 16); ++br)
             nnz += block_row_nnz(h, static_cast<size_t>(br));
     // What a step costs against one of the other form, measured: fp16 / bf16 0.43 us and 0.365, int8 0.37 and 0.27, the 8-bit floats,
-    // which take twice the matrix instructions there, 0.37 and 0.55.
-    const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : 1.0) * static_cast<double>(steps);
+    // whose instructions go over the extent twice, 0.67 and 0.47 (4096 columns, N = 2048: at 10 % fill 34.4 us against 43.4, at 25 %
+    // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9).
+    const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : 0.7) * static_cast<double>(steps);
     // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
-    if (static_cast<double>(nnz) > (es == 2 ? 0.3 : h.dtype == SMAT_I8 ? 0.27 : 0.4) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
+    if (static_cast<double>(nnz) > (es == 2 ? 0.3 : 0.27) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
     // A last super row of a few block rows is left to the per-row kernel by the tile kernels, whose tile would be mostly empty; in
     // the kernel for few columns it saves a launch (1300 x 6000 in int8, N = 3: 12.6 us with it, of 82 block rows two).
     std::vector<int32_t> supers(h.dense_super);
@@ -1001,7 +1002,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
             const int ks = smat::dense_split(tiles, n);
             // us per step of a tile, alone on its compute unit (an 8-bit step covers twice the block columns)
-            const double walk_us = tiles.n_quad_steps ? (h->elem_bytes == 1 ? 0.37 : 0.43) * tiles.n_quad_steps / tiles.n
+            const double quad_us = h->elem_bytes == 2 ? 0.43 : h->dtype == SMAT_I8 ? 0.37 : 0.6;
+            const double walk_us = tiles.n_quad_steps ? quad_us * tiles.n_quad_steps / tiles.n
                                                       : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
             t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (tiles.n_quad_steps ? 6.0 : 4.0)) + 1.5;
             if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 8.0e6;     // partial tiles out and in again

@@ -6,16 +6,19 @@
 // floats).  Which column of A sits in which k slot is free here -- the panel of B is brought into LDS row by
 // row -- so the columns of a super row are dealt into groups of four ("quads") in which no row has more than two stored entries
 // (plan_quads in api.cpp).  At random that succeeds for practically all columns up to 15 % fill (256 rows); at 20 %
-// a quad gets 3.5 columns on average, at 25 % 3.0.  Products and sums are those of the ordinary instruction.
+// a quad gets 3.5 columns on average, at 25 % 3.0.  In the 16-bit types and int8 the sums are as exact as the ordinary instruction's; the
+// 8-bit floats go over a step twice to be so (every_second_pair).
 //
 // One step covers 64 k slots (8-bit types: 128), four bytes of which are a quad's: 16 KiB of B in LDS, 16 KiB of values (two of
 // four: 1 KiB per block row as in the other kernel) and 2 KiB (4 KiB) of positions.  The work split is the other kernel's with two
 // groups: a workgroup takes 256 rows x 128 columns, group 0 the even steps and group 1 the odd ones, a wave four
-// block rows x 128 columns.  Per step a wave issues as many matrix instructions as there, for twice (four times) the
+// block rows x 128 columns.  Per step a wave issues as many matrix instructions as there, for twice (int8: four times) the
 // matrix, and reads the panel with the same transposing reads; the loads of two steps are in flight, spread
 // between the matrix instructions.
 //
-// What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.
+// What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  The 8-bit
+// floats: the matrix units, which take 64 instructions of 16 clocks per step and wave (10 % fill: 6000 x 4096, N = 784
+// 29 us, against 25 with half as many; 8192 x 4096, N = 2048 65 us, against 82 in the other form).
 #include <cstdio>
 #include <type_traits>
 
@@ -49,6 +52,18 @@ __device__ __forceinline__ typename Elem<DT>::Acc smfmac(u32x4 a, u32x8 b, typen
         return __builtin_amdgcn_smfmac_f32_16x16x128_bf8_bf8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
     else
         return __builtin_amdgcn_smfmac_i32_16x16x128_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
+}
+
+// The matrix units add the products of an 8-bit float instruction below fp32, the less exactly the more of them are not zero: relative
+// error of a product against 64 bits at 5 / 10 / 20 % fill in e4m3, ordinary form 3.3e-6 / 3.7e-6 / 5.2e-6, this one 3.7e-6 / 5.0e-6 /
+// 6.5e-6 (16x16x64 instead of 16x16x128: the same bits).  So the kernels go over a step twice, with every second quad's values as
+// zeros: as many products at a time as the ordinary instruction meets, 2.8e-6 / 3.7e-6 / 4.9e-6.
+template <int DT> constexpr bool kInHalves = DT == kE4M3 || DT == kE5M2;
+// half HALF (0, 1) of a lane's values
+__device__ __forceinline__ u32x4 every_second_pair(u32x4 a, int half)
+{
+    const uint32_t keep = half ? 0xFFFF0000u : 0x0000FFFFu;
+    return u32x4{a[0] & keep, a[1] & keep, a[2] & keep, a[3] & keep};
 }
 
 // the four reads have returned once at most YOUNGER later LDS reads are outstanding
@@ -218,6 +233,14 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
         auto step = [&](auto u_, int s) {
             constexpr int u = decltype(u_)::value;
             constexpr int next = (u + 2) % RD;
+            u32x4 first[RM];                       // of an 8-bit float's values half 0; a[u] keeps half 1
+            if constexpr (kInHalves<DT>) {
+#pragma unroll
+                for (int r = 0; r < RM; ++r) {
+                    first[r] = every_second_pair(a[u][r], 0);
+                    a[u][r] = every_second_pair(a[u][r], 1);
+                }
+            }
 #pragma unroll
             for (int x = 0; x < NT; ++x) {
                 if (x + 1 < NT) {
@@ -240,6 +263,10 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
                     acc[2][x] = smfmac<DT, 0>(a[u][2], operand, acc[2][x], ix[u][1]);
                     acc[3][x] = smfmac<DT, 1>(a[u][3], operand, acc[3][x], ix[u][1]);
                 } else {
+                    if constexpr (kInHalves<DT>) {
+#pragma unroll
+                        for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<DT, 0>(first[r], operand, acc[r][x], ix[u][r]);
+                    }
 #pragma unroll
                     for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<DT, 0>(a[u][r], operand, acc[r][x], ix[u][r]);
                 }
@@ -489,8 +516,15 @@ void spmm_quad_rows_kernel(int n_units, int per_xcd, int N, uint32_t b_bytes, co
         }
         lds_four_done<0>(b);
         const u32x8 operand = u32x8{b[0][0], b[0][1], b[1][0], b[1][1], b[2][0], b[2][1], b[3][0], b[3][1]};
-        acc[0] = smfmac<DT, 0>(av[0], operand, acc[0], iv[0]);
-        if constexpr (RM == 2) acc[1] = smfmac<DT, 1>(av[1], operand, acc[1], iv[1]);
+        if constexpr (kInHalves<DT>) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+#pragma unroll
+                for (int r = 0; r < RM; ++r) acc[r] = smfmac<DT, 0>(every_second_pair(av[r], half), operand, acc[r], iv[r]);
+        } else {
+            acc[0] = smfmac<DT, 0>(av[0], operand, acc[0], iv[0]);
+            if constexpr (RM == 2) acc[1] = smfmac<DT, 1>(av[1], operand, acc[1], iv[1]);
+        }
     };
 #pragma unroll
     for (int h = 0; h < PF; ++h)

@@ -7,7 +7,7 @@
 // Which value multiplies which panel row: the kernel reads panel rows 32 r + 8 g .. 32 r + 8 g + 7 as the r-th eight k of lane group g of the
 // right operand (16-bit types r = 0, 1; 8-bit types r = 0 .. 3).  The instruction takes the k of its left operand in order, lane
 // group G the G-th quarter of them, and its right operand in halves, of which every lane group has a quarter.  (Checked on the
-// device, value by value and position by position, for the 16-bit types, fp8 and int8.)
+// device, value by value and position by position, for the 16-bit types, e4m3 and int8; e5m2 by products that come out exact.)
 //
 // Values: per step and block row 1 KiB, lane l = 16 G + i the 16 bytes at 16 l: row i, the pairs of values of its quads, in order.
 // Positions: two bits per value, ascending inside a pair; per step and wave (four block rows) and lane the block rows' words one after the
