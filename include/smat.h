@@ -80,8 +80,12 @@ typedef struct {
                            concurrent_streams distinct streams the handle sees owns an area of
                            32 MiB for them (part of smat_device_bytes when the matrix has
                            block-dense parts, or uses the rows of B often enough for a copy of
-                           a B off the cache lines to pay).  Calls on further streams are still
-                           correct: they run such launches unsplit, and without the copy       */
+                           a B off the cache lines to pay).  A graph capture counts as a stream of
+                           its own for every stream that records calls in it: its area is used
+                           when the graph runs, wherever that is.  Calls on further streams and in
+                           further captures are still correct: they run such launches unsplit, and
+                           without the copy; so does every call on hipStreamPerThread, which is
+                           one value for many streams                                          */
 } smat_options_t;
 
 /* Default options: 16 x 16 blocks, reordering on, tau = 0.7, dense_tiles = 0, concurrent_streams = 2. */
@@ -195,11 +199,14 @@ smat_status_t smat_export_device_vals(const smat_handle_t *h, void *vals, void *
  *
  * Stream-ordered and re-entrant: calls on different handles, and calls on the SAME handle on
  * different streams with different C, may be in flight at the same time (from one host thread
- * or several).  The only state a call uses besides its arguments is an area for the partial
+ * or several), and several host threads may call on one stream.  The only state a call uses besides its
+ * arguments is an area for the partial
  * tiles of launches with few block-dense tiles and for a copy of a B whose rows lie off the pieces or
  * lines the kernels want; every stream has its own (option concurrent_streams),
  * and a call on a stream without one does without -- the same product, summed in
- * another order.  For a given handle, stream and arguments the result is bitwise reproducible.
+ * another order.  (A stream is told by its handle: let its calls finish before it is destroyed.)  Under
+ * graph capture an area belongs to the capture; one graph's launches must not overlap each other.
+ * For a given handle, stream and arguments the result is bitwise reproducible.
  * Limits: the bytes of B that are addressed, ((K-1)*ldb + N) * bytes per value, must stay below 2 GiB;
  * ldb < 2^23; N <= 1048560.
  */
@@ -210,14 +217,16 @@ smat_status_t smat_spmm(const smat_handle_t *h, const void *dB, int64_t ldb,
  * smat_spmm for callers that cannot allocate device memory and cannot give the handle's workspace
  * the areas for partial tiles either: code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation.  Same arguments, same product, same kernels.  The partial
- * tiles of a launch that splits its block-dense tiles live in an array of 16 MiB that is part of
+ * tiles of a launch that splits its block-dense tiles, and the copy of a B off the pieces or lines, live in an
+ * array of 16 MiB that is part of
  * the library's device code (one copy per GPU, held from the first use of the library on that
  * GPU until the process ends); the call allocates and frees nothing, on the device or through
  * any library.  smat_bind_device looks the array's address up for its device.
  *   - a launch whose partial tiles would exceed the 16 MiB is refused with SMAT_ERR_UNSUPPORTED
  *     before anything is enqueued (smat_spmm takes it);
  *   - every call on a GPU uses that GPU's one array, whatever the handle or stream: calls that
- *     overlap in time on one GPU race -- order them on one stream, or with events.  The array
+ *     overlap in time on one GPU race -- order them on one stream (from any number of host threads),
+ *     or with events.  The array
  *     keeps what the last call left; nothing in it has to start at zero, every partial tile is
  *     written in full before it is read.
  */

@@ -23,6 +23,8 @@
 #include "preprocess.h"
 #include "quad_layout.h"
 
+constexpr int kMaxAreas = 16;            // option concurrent_streams at most
+
 struct smat_handle {
     smat::Csr csr;
     smat::Bcsr bcsr;
@@ -78,13 +80,15 @@ struct smat_handle {
     // canonical BCSR on the device, for the ablation kernels (smat_ablation_bind)
     smat::CanonicalBcsr ablation;
     bool ablation_bound = false;
-    // Areas of partial tiles (split dense launches), one per stream: entry i names the stream
-    // that owns area i of the workspace.  A stream keeps its area for the life of the handle;
-    // calls on one stream are ordered, so an area is never used by two launches at once.
+    // Areas of partial tiles and copies of B: entry i names who owns area i of the workspace, for the life of the handle
+    // -- a stream, or what one capture records on a stream.  The launches of an owner are ordered on the device, and an area is
+    // locked while a call enqueues those that share it: launches that may overlap never use one area.
     int n_scratch_areas = 2;             // option concurrent_streams
     char* scratch_base = nullptr;        // first area (device), set by smat_bind_device
-    mutable std::mutex scratch_mutex;
-    mutable std::vector<const void*> scratch_owner;
+    struct AreaOwner { const void* stream; unsigned long long capture; };
+    mutable std::mutex scratch_mutex;    // scratch_owner
+    mutable std::vector<AreaOwner> scratch_owner;
+    mutable std::mutex area_mutex[kMaxAreas];
 };
 
 namespace {
@@ -559,7 +563,7 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
         if (o.tau_permille < 0 || o.tau_permille > 1000) return fail(SMAT_ERR_INVALID_ARG, "tau_permille must be in 0..1000");
         if (o.dense_tiles < -1 || o.dense_tiles > 1) return fail(SMAT_ERR_INVALID_ARG, "dense_tiles must be -1, 0 or 1");
         if (o.concurrent_streams == 0) o.concurrent_streams = 2;      // a zeroed options struct: the default
-        if (o.concurrent_streams < 1 || o.concurrent_streams > 16) return fail(SMAT_ERR_INVALID_ARG, "concurrent_streams must be in 1..16");
+        if (o.concurrent_streams < 1 || o.concurrent_streams > kMaxAreas) return fail(SMAT_ERR_INVALID_ARG, "concurrent_streams must be in 1..16");
         if (M >= (int64_t{1} << 31) - 16 || K >= (int64_t{1} << 31) - 16)
             return fail(SMAT_ERR_UNSUPPORTED, "M and K must be below 2^31 - 16");
         if ((M + 15) / 16 >= (int64_t{1} << 28)) return fail(SMAT_ERR_UNSUPPORTED, "more than 2^28 block rows");
@@ -822,6 +826,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
             std::lock_guard<std::mutex> lock(h->scratch_mutex);
             h->scratch_base = l.total > l.t_scratch ? base + l.t_scratch : nullptr;
             h->scratch_owner.clear();
+            h->scratch_owner.reserve(static_cast<size_t>(h->n_scratch_areas));
         }
         h->bound = true;
         return SMAT_OK;
@@ -915,17 +920,42 @@ smat_status_t smat_export_device_vals(const smat_handle_t* h, void* vals, void* 
 
 namespace {
 
-// The area of partial tiles that belongs to `stream`: the one it already owns, else the first
-// free one, else none.
-char* scratch_area_of(const smat_handle* h, const void* stream)
+// The area of partial tiles and copies of B for one call on `stream`, locked until the call has enqueued its launches: the one
+// the stream already owns, else the first free one, else none.
+//   * hipStreamPerThread is one value for as many streams as there are threads: none.
+//   * What is captured runs when and where its graph is launched, so a stream under capture does not use what it owns
+//     outside: each capture is an owner of its own.  (The null stream cannot be captured.)
+struct ScratchArea {
+    char* at = nullptr;
+    std::unique_lock<std::mutex> hold;
+};
+
+ScratchArea scratch_area_of(const smat_handle* h, void* stream)
 {
-    if (!h->scratch_base) return nullptr;
-    std::lock_guard<std::mutex> lock(h->scratch_mutex);
-    for (size_t i = 0; i < h->scratch_owner.size(); ++i)
-        if (h->scratch_owner[i] == stream) return h->scratch_base + i * kTileScratchBytes;
-    if (static_cast<int>(h->scratch_owner.size()) >= h->n_scratch_areas) return nullptr;
-    h->scratch_owner.push_back(stream);
-    return h->scratch_base + (h->scratch_owner.size() - 1) * kTileScratchBytes;
+    ScratchArea area;
+    if (!h->scratch_base || stream == hipStreamPerThread) return area;
+    unsigned long long capture = 0;
+    if (stream != nullptr && stream != hipStreamLegacy) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        unsigned long long id = 0;
+        if (hipStreamGetCaptureInfo(static_cast<hipStream_t>(stream), &status, &id) != hipSuccess) {
+            (void)hipGetLastError();
+            return area;
+        }
+        if (status != hipStreamCaptureStatusNone) capture = id + 1;
+    }
+    size_t i = 0;
+    {
+        std::lock_guard<std::mutex> lock(h->scratch_mutex);
+        while (i < h->scratch_owner.size() && !(h->scratch_owner[i].stream == stream && h->scratch_owner[i].capture == capture)) ++i;
+        if (i == h->scratch_owner.size()) {
+            if (static_cast<int>(i) >= h->n_scratch_areas) return area;
+            h->scratch_owner.push_back({stream, capture});
+        }
+    }
+    area.at = h->scratch_base + i * kTileScratchBytes;
+    area.hold = std::unique_lock<std::mutex>(h->area_mutex[i]);
+    return area;
 }
 
 // Fewest columns for which a B off 16-byte pieces is copied for the tile kernel: below, its tiles of 128
@@ -1092,23 +1122,34 @@ extern "C" {
 smat_status_t smat_spmm(const smat_handle_t* h, const void* dB, int64_t ldb, void* dC, int64_t ldc,
                         int64_t N, void* stream)
 {
-    bool nothing = false;
-    const smat_status_t st = check_spmm_args(h, dB, ldb, dC, ldc, N, &nothing);
-    if (st != SMAT_OK || nothing) return st;
-    return spmm_with_scratch(h, dB, ldb, dC, ldc, N, stream, scratch_area_of(h, stream), kTileScratchBytes);
+    try {
+        bool nothing = false;
+        const smat_status_t st = check_spmm_args(h, dB, ldb, dC, ldc, N, &nothing);
+        if (st != SMAT_OK || nothing) return st;
+        const ScratchArea area = scratch_area_of(h, stream);
+        return spmm_with_scratch(h, dB, ldb, dC, ldc, N, stream, area.at, kTileScratchBytes);
+    } catch (const std::exception& e) {          // a lock or a name that could not be made
+        return fail(SMAT_ERR_ALLOC, e.what());
+    }
 }
 
 smat_status_t smat_spmm_static(const smat_handle_t* h, const void* dB, int64_t ldb, void* dC, int64_t ldc,
                                int64_t N, void* stream)
 {
-    bool nothing = false;
-    const smat_status_t st = check_spmm_args(h, dB, ldb, dC, ldc, N, &nothing);
-    if (st != SMAT_OK || nothing) return st;
-    void* area = nullptr;
-    size_t bytes = 0;
-    const int e = smat::static_tile_scratch(&area, &bytes);      // looked up at bind time; here from the cache
-    if (e) return hip_fail("address of the static area for partial tiles", e);
-    return spmm_with_scratch(h, dB, ldb, dC, ldc, N, stream, area, bytes, bytes);
+    try {
+        bool nothing = false;
+        const smat_status_t st = check_spmm_args(h, dB, ldb, dC, ldc, N, &nothing);
+        if (st != SMAT_OK || nothing) return st;
+        void* area = nullptr;
+        size_t bytes = 0;
+        const int e = smat::static_tile_scratch(&area, &bytes);      // looked up at bind time; here from the cache
+        if (e) return hip_fail("address of the static area for partial tiles", e);
+        static std::mutex enqueueing;            // the launches of one call stay together on their stream
+        const std::lock_guard<std::mutex> lock(enqueueing);
+        return spmm_with_scratch(h, dB, ldb, dC, ldc, N, stream, area, bytes, bytes);
+    } catch (const std::exception& e) {
+        return fail(SMAT_ERR_ALLOC, e.what());
+    }
 }
 
 // Largest block grid for which the ablation keeps a dense block map (level 0).

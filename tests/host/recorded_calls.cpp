@@ -1,0 +1,197 @@
+// The host side of smat_spmm without a GPU: the HIP calls and launchers that api.cpp makes are replaced by ones that write down what
+// was enqueued, in order.  A launch of the copy of B dawdles, so that another thread gets its chance to enqueue between a
+// copy and the product that reads it.  Prints what is wrong; exit code 0 if nothing is.
+#include <hip/hip_runtime_api.h>
+
+#include <chrono>
+#include <cstdio>
+#include <mutex>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "../../include/smat.h"
+#include "../../paper_2408_11551_amd/csrc/kernels.h"
+
+namespace {
+
+struct Event { bool copy; const void* from; const void* to; const void* stream; };     // a copy of B: B, area; a product: its B, C
+std::mutex g_mutex;
+std::vector<Event> g_events;
+hipStream_t g_capturing = nullptr;
+unsigned long long g_capture_id = 0;
+int g_wrong = 0;
+
+void record(bool copy, const void* from, const void* to, const void* stream)
+{
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        g_events.push_back(Event{copy, from, to, stream});
+    }
+    if (copy) std::this_thread::sleep_for(std::chrono::microseconds(300));
+}
+
+void expect(bool ok, const char* what)
+{
+    if (ok) return;
+    std::printf("wrong: %s\n", what);
+    ++g_wrong;
+}
+
+char g_static_area[256];
+
+}  // namespace
+
+extern "C" {
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipStreamGetCaptureInfo(hipStream_t stream, hipStreamCaptureStatus* status, unsigned long long* id)
+{
+    *status = g_capturing && stream == g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    if (id) *id = g_capture_id;
+    return hipSuccess;
+}
+}
+
+namespace smat {
+int launch_fill_zero(void*, size_t, void*) { return 0; }
+int launch_bcsr_fill(const DeviceBcsr&, const int64_t*, const int32_t*, const uint16_t*, const int32_t*, void*, uint32_t*, size_t, int, void*) { return 0; }
+int launch_dense_fill(const DeviceBcsr&, const DenseTiles&, const int64_t*, const int32_t*, const uint16_t*, void*, int, void*) { return 0; }
+int launch_quad_fill(const DeviceBcsr&, const DenseTiles&, const int64_t*, const int32_t*, const uint16_t*, void*, void*, int, int, void*) { return 0; }
+int launch_quad_rows(const DeviceBcsr&, const DenseTiles&, int, const void*, int64_t, void*, int64_t, int64_t, void*, const char** variant)
+{
+    *variant = "quad_rows";
+    return 0;
+}
+int launch_ablation(const CanonicalBcsr&, int, bool, const void*, int64_t, float*, int64_t, int64_t, void*) { return 0; }
+int dense_split(const DenseTiles&, int64_t) { return 1; }
+int static_tile_scratch(void** area, size_t* bytes)
+{
+    *area = g_static_area;
+    *bytes = size_t{16} << 20;
+    return 0;
+}
+int launch_stage_b(const void* B, int64_t, int64_t, int64_t, int, void* out, int64_t, void* stream)
+{
+    record(true, B, out, stream);
+    return 0;
+}
+int launch_spmm(const DeviceBcsr&, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
+{
+    record(false, B, C, stream);
+    *variant = "rows";
+    return 0;
+}
+int launch_spmm_dense(const DeviceBcsr&, const DenseTiles&, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
+{
+    record(false, B, C, stream);
+    *variant = "tiles";
+    return 0;
+}
+}  // namespace smat
+
+namespace {
+
+constexpr int64_t M = 1024, K = 4096, N = 1001;          // rows of B off the cache lines, and used often: the per-row kernel copies B
+
+smat_handle_t* make(int streams, int dense_tiles, std::vector<char>& workspace)
+{
+    std::vector<int64_t> ptr(M + 1, 0);
+    std::vector<int32_t> col;
+    for (int64_t r = 0; r < M; ++r) {
+        for (int64_t c = r % 7; c < K; c += 7) col.push_back(static_cast<int32_t>(c));
+        ptr[r + 1] = static_cast<int64_t>(col.size());
+    }
+    std::vector<uint16_t> vals(col.size(), 0x3C00);
+    smat_options_t opt;
+    smat_default_options(&opt);
+    opt.reorder = 0;
+    opt.dense_tiles = dense_tiles;
+    opt.concurrent_streams = streams;
+    smat_handle_t* h = nullptr;
+    size_t bytes = 0;
+    if (smat_preprocess(M, K, ptr.data(), col.data(), vals.data(), SMAT_F16, &opt, &h) != SMAT_OK || smat_device_bytes(h, &bytes) != SMAT_OK) return nullptr;
+    workspace.assign(bytes + 256, 0);
+    char* base = workspace.data() + (256 - reinterpret_cast<uintptr_t>(workspace.data()) % 256) % 256;
+    return smat_bind_device(h, base, bytes, nullptr) == SMAT_OK ? h : nullptr;
+}
+
+// operands are only named, never touched
+const void* operand_b(int which) { return reinterpret_cast<const void*>(uintptr_t{0x10000002} + (static_cast<uintptr_t>(which) << 28)); }
+void* operand_c(int which) { return reinterpret_cast<void*>(uintptr_t{0x18000000} + (static_cast<uintptr_t>(which) << 28)); }
+
+using Call = smat_status_t (*)(const smat_handle_t*, const void*, int64_t, void*, int64_t, int64_t, void*);
+
+// what one call enqueues; *area receives where it copied B to (null: it did not)
+void call(Call f, const smat_handle_t* h, int which, void* stream, const void** area)
+{
+    g_events.clear();
+    expect(f(h, operand_b(which), N, operand_c(which), N, N, stream) == SMAT_OK, "status of a call");
+    *area = nullptr;
+    for (const Event& e : g_events)
+        if (e.copy) *area = e.to;
+    if (!*area) expect(g_events.size() == 1 && g_events[0].from == operand_b(which), "without an area the product reads B in place");
+}
+
+// two threads, one stream, each its own B and C: every product must find its own B in the area it reads
+void threads_on_one_stream(Call f, const smat_handle_t* h, const char* what)
+{
+    g_events.clear();
+    auto work = [&](int which) {
+        for (int x = 0; x < 20; ++x)
+            if (f(h, operand_b(which), N, operand_c(which), N, N, nullptr) != SMAT_OK) std::printf("status\n");
+    };
+    std::thread one(work, 1), two(work, 2);
+    one.join();
+    two.join();
+    const void* copied = nullptr;              // (one area, so one last copy; a column range of B is told by its operand)
+    int mixed = 0, products = 0;
+    auto owner = [](const void* p) { return static_cast<int>((reinterpret_cast<uintptr_t>(p) - 0x10000000) >> 28); };
+    for (const Event& e : g_events) {
+        if (e.copy) { copied = e.from; continue; }
+        ++products;
+        mixed += copied == nullptr || owner(copied) != owner(e.to);
+    }
+    expect(products >= 40, "every call enqueues a product");
+    if (mixed) std::printf("%s: %d of %d products read the other thread's B\n", what, mixed, products);
+    expect(mixed == 0, what);
+}
+
+}  // namespace
+
+int main()
+{
+    for (int dense_tiles : {-1, 1}) {
+        std::vector<char> workspace;
+        smat_handle_t* h = make(2, dense_tiles, workspace);
+        if (!h) { std::printf("%s\n", smat_last_error()); return 2; }
+        const void *a, *b, *c;
+        call(smat_spmm, h, 1, nullptr, &a);
+        expect(a != nullptr, "the first stream has an area (or the matrix no longer asks for a copy of B)");
+        threads_on_one_stream(smat_spmm, h, "smat_spmm from two threads on one stream");
+        threads_on_one_stream(smat_spmm_static, h, "smat_spmm_static from two threads on one stream");
+        // one value for as many streams as there are threads: no area
+        call(smat_spmm, h, 1, hipStreamPerThread, &b);
+        expect(b == nullptr, "hipStreamPerThread has no area");
+        // a call under capture runs when and where the graph is launched: an area of that capture's own, or none
+        void* stream = reinterpret_cast<void*>(0x5000);
+        g_capturing = static_cast<hipStream_t>(stream);
+        g_capture_id = 7;
+        call(smat_spmm, h, 1, stream, &b);
+        call(smat_spmm, h, 2, stream, &c);
+        expect(b != nullptr && b != a && c == b, "calls of one capture share an area that nothing else has");
+        g_capture_id = 8;
+        call(smat_spmm, h, 1, stream, &c);
+        expect(c == nullptr, "a second capture finds both areas taken");
+        g_capturing = nullptr;
+        call(smat_spmm, h, 1, stream, &c);
+        expect(c == nullptr, "nor do calls outside the capture use the capture's area");
+        call(smat_spmm, h, 1, nullptr, &c);
+        expect(c == a, "the first stream keeps its area");
+        smat_destroy(h);
+    }
+    if (!g_wrong) std::printf("OK\n");
+    return g_wrong ? 1 : 0;
+}
