@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <memory>
 #include <numeric>
 
 namespace smat {
@@ -276,108 +277,208 @@ static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const Pattern
 }
 
 // With which other classes could a cluster opened by a row of class k start to grow?  The first row of another class to
-// join has to pass the merge test against the seed's own pattern: 1000 |a n b| > keep |a u b|.  Lists such classes, class by
-// class (some more than once).  Each pair is counted once, from the shorter pattern: |b| < 1000 |a| / keep bounds
-// the longer one.
-// Where a class has many increments to make, they are made without looking, and the counters are looked through (and cleared) once, in
-// order; and only some of its columns are counted: b has to share `least` of a's columns, so all but least - m of them (the
-// longest lists are left out) already hold m shared ones; whoever reaches m, about nobody by chance, is counted exactly.
+// join has to pass the merge test against the seed's own pattern: 1000 |a n b| > keep |a u b|.  All that is asked of a class is whether
+// one of these has rows left, so it is given at most kMostPartners of them; a class with more of them ("many") is taken to have one
+// left whatever happens, and its search ends.  (All pairs of 100 000 rows of two entries that share one column would be 5 G:
+// 30 GB and 346 s, against 25 s now.  A graph of 65536 rows of 16 has a few classes with more than 16 and none with more than 32.)
+constexpr size_t kMostPartners = 32;
 struct Partners {
-    Buf<int64_t> ptr;       // [n+1]
-    Buf<int32_t> of;
+    Buf<int64_t> ptr;              // [n+1]
+    Buf<int32_t> of;               // the partners of every class that has not many
+    std::vector<uint8_t> many;     // [n]
 };
 
+// One thread's search for partners.
+// Where a class has many increments to make, they are made without looking, and the counters are looked through (and cleared) once, in
+// order; and only some of its columns are counted: b has to share `least` of a's columns, so all but least - m of them (the
+// longest lists are left out) already hold m shared ones; whoever reaches m, about nobody by chance, is counted exactly.  Where the
+// average class has half of `least`, a few classes are gone through first: a class with many partners has enough of them there.
+template <typename Count>
+class PartnerSearch {
+public:
+    PartnerSearch(const Patterns& pat, const PatternClasses& pc, int64_t keep)
+        : pat_(pat), pc_(pc), keep_(keep), count_(static_cast<size_t>(pc.size() + kStride), 0) {}
+
+    std::vector<int32_t> found;
+    std::vector<std::pair<const int32_t*, const int32_t*>> lists;      // what the columns of class k list in [begin, end), set by the caller
+
+    // Puts the partners of class k among the classes [begin, end) into found; false: more than kMostPartners, and not all of them.
+    bool run(int64_t k, int64_t begin, int64_t end)
+    {
+        found.clear();
+        if (begin >= end) return true;
+        const int64_t len = pc_.len[k];
+        const int64_t least = keep_ * (len + pc_.len[begin]) / (1000 + keep_) + 1;
+        int64_t ahead = 0;
+        for (const auto& list : lists) ahead += list.second - list.first;
+        Count* const count = count_.data();
+        const auto passes = [&](int64_t shared, int64_t other) { return 1000 * shared > keep_ * (len + pc_.len[other] - shared); };
+        if (ahead <= (end - begin) / 16) {
+            size_t x = 0;
+            const int32_t* p = nullptr;
+            for (; x < lists.size() && found.size() <= kMostPartners; ++x) {
+                const int32_t* const stop = lists[x].second;
+                for (p = lists[x].first; p < stop; ++p) {
+                    const int64_t shared = ++count[*p];
+                    if (shared < least || !passes(shared, *p) || passes(shared - 1, *p)) continue;
+                    found.push_back(*p);
+                    if (found.size() > kMostPartners) { ++p; break; }
+                }
+            }
+            for (size_t y = 0; y < x; ++y)
+                for (const int32_t *q = lists[y].first, *stop = y + 1 < x ? lists[y].second : p; q < stop; ++q) count[*q] = 0;
+            return found.size() <= kMostPartners;
+        }
+        // m: what chance gives a pattern of the average number of columns, and four deviations more
+        const double hit = static_cast<double>(ahead) / static_cast<double>((end - begin) * len);
+        int64_t m = 2;
+        for (int round = 0; round < 3; ++round) {
+            const double mean = hit * static_cast<double>(len - least + m);
+            m = std::min(least, static_cast<int64_t>(mean + 4.0 * std::sqrt(mean)) + 3);
+        }
+        const int64_t counted = std::min(len, len - least + m);
+        if (counted < len)
+            std::nth_element(lists.begin(), lists.begin() + counted, lists.end(),
+                             [](const auto& x, const auto& y) { return x.second - x.first < y.second - y.first; });
+        const int32_t* mine = pat_.idx.data() + pat_.ptr[pc_.first_row[k]];
+        int64_t to = begin;
+        for (int64_t window = 2 * ahead >= least * (end - begin) ? 8 * kStride : end - begin; to < end && found.size() <= kMostPartners; window *= 64) {
+            const int64_t from = to;
+            to = std::min(end, from + window);
+            for (int64_t x = 0; x < counted; ++x) {
+                // (in locals: a counter of one byte may lie anywhere, for all the compiler knows)
+                const int32_t *p = lists[static_cast<size_t>(x)].first, *const stop = lists[static_cast<size_t>(x)].second;
+                if (to == end)
+                    for (; p < stop; ++p) ++count[*p];
+                else
+                    for (; p < stop && *p < to; ++p) ++count[*p];
+                lists[static_cast<size_t>(x)].first = p;
+            }
+            for (int64_t x = from; x < to; x += kStride) {
+                Count most = 0;
+                for (int64_t y = 0; y < kStride; ++y) most = std::max(most, count[x + y]);
+                if (most >= m)
+                    for (int64_t other = x; other < std::min(to, x + kStride) && found.size() <= kMostPartners; ++other) {
+                        if (count[other] < m) continue;
+                        const int32_t* theirs = pat_.idx.data() + pat_.ptr[pc_.first_row[other]];
+                        int64_t shared = 0;
+                        for (int64_t u = 0, v = 0; u < len && v < pc_.len[other];) {
+                            shared += mine[u] == theirs[v];
+                            const bool up = mine[u] <= theirs[v], vp = theirs[v] <= mine[u];
+                            u += up;
+                            v += vp;
+                        }
+                        if (passes(shared, other)) found.push_back(static_cast<int32_t>(other));
+                    }
+                std::fill(count + x, count + x + kStride, Count{0});
+            }
+        }
+        return found.size() <= kMostPartners;
+    }
+
+private:
+    static constexpr int64_t kStride = 64;
+    const Patterns& pat_;
+    const PatternClasses& pc_;
+    const int64_t keep_;
+    std::vector<Count> count_;
+};
+
+// Each pair is looked for from the shorter pattern: |b| < 1000 |a| / keep bounds the longer one.  What a class with many partners
+// did not list, the longer pattern looks for among those classes alone.
 template <typename Count>
 static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const ColumnIndex& inv, const std::vector<int32_t>& alive,
                             int64_t keep, Workers& workers)
 {
     // (alive[k] == 0: every row of the class is in a cluster)
-    const int64_t n = pc.size();
+    const int64_t n = pc.size(), nbc = static_cast<int64_t>(inv.len.size());
     struct Local {
-        std::vector<Count> count;
-        std::vector<std::pair<int32_t, int32_t>> pairs;
-        std::vector<std::pair<const int32_t*, const int32_t*>> lists;      // what the columns of a list beyond class k
+        std::unique_ptr<PartnerSearch<Count>> search;
+        std::vector<std::pair<int32_t, int32_t>> pairs;        // of partners
+        std::vector<std::pair<int32_t, int32_t>> longer;       // (a class, a partner of it that has many)
     };
     std::vector<Local> locals(static_cast<size_t>(workers.most()));
-    workers.ranges(n, 16, [&](int64_t j0, int64_t j1, int thread) {
+    auto local_of = [&](int thread) -> Local& {
         Local& local = locals[static_cast<size_t>(thread)];
-        constexpr int64_t kStride = 64;
-        if (local.count.empty()) local.count.assign(static_cast<size_t>(n + kStride), 0);
-        Count* const count = local.count.data();
+        if (!local.search) local.search = std::make_unique<PartnerSearch<Count>>(pat, pc, keep);
+        return local;
+    };
+    Partners partners;
+    partners.many.assign(static_cast<size_t>(n), 0);
+    workers.ranges(n, 16, [&](int64_t j0, int64_t j1, int thread) {
+        Local& local = local_of(thread);
+        PartnerSearch<Count>& search = *local.search;
         for (int64_t j = j0; j < j1; ++j) {
             const int64_t k = n - 1 - j, len = pc.len[k];                       // long patterns, which take longest, first
             if (len == 0 || alive[k] == 0) continue;
             // the first class whose pattern is too long
             const int64_t end = keep == 0 ? n
                 : std::partition_point(pc.len.begin() + k, pc.len.end(), [&](int32_t x) { return keep * x < 1000 * len; }) - pc.len.begin();
-            const int64_t least = 2 * keep * len / (1000 + keep) + 1;
-            local.lists.clear();
-            int64_t ahead = 0;
+            search.lists.clear();
             for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) {
                 const int32_t* p = inv.classes.data() + inv.ptr[pat.idx[q]];
                 const int32_t* stop = p + inv.len[pat.idx[q]];
                 p = inv.dropped ? std::upper_bound(p, stop, static_cast<int32_t>(k)) : p + inv.at[q] + 1;
                 if (p < stop && stop[-1] >= end) stop = std::lower_bound(p, stop, static_cast<int32_t>(end));
-                local.lists.emplace_back(p, stop);
-                ahead += stop - p;
+                search.lists.emplace_back(p, stop);
             }
-            const auto passes = [&](int64_t shared, int64_t other) { return 1000 * shared > keep * (len + pc.len[other] - shared); };
-            if (ahead > (end - k) / 16) {
-                // m: what chance gives a pattern of the average number of columns, and four deviations more
-                const double hit = static_cast<double>(ahead) / static_cast<double>((end - k) * len);
-                int64_t m = 2;
-                for (int round = 0; round < 3; ++round) {
-                    const double mean = hit * static_cast<double>(len - least + m);
-                    m = std::min(least, static_cast<int64_t>(mean + 4.0 * std::sqrt(mean)) + 3);
-                }
-                const int64_t counted = len - least + m;
-                if (counted < len)
-                    std::nth_element(local.lists.begin(), local.lists.begin() + counted, local.lists.end(),
-                                     [](const auto& x, const auto& y) { return x.second - x.first < y.second - y.first; });
-                for (int64_t x = 0; x < std::min(counted, len); ++x)
-                    for (const int32_t* p = local.lists[static_cast<size_t>(x)].first; p < local.lists[static_cast<size_t>(x)].second; ++p) ++count[*p];
-                const int32_t* mine = pat.idx.data() + pat.ptr[pc.first_row[k]];
-                for (int64_t x = k + 1; x < end; x += kStride) {
-                    Count most = 0;
-                    for (int64_t y = 0; y < kStride; ++y) most = std::max(most, count[x + y]);
-                    if (most >= m)
-                        for (int64_t other = x; other < std::min(end, x + kStride); ++other) {
-                            if (count[other] < m) continue;
-                            const int32_t* theirs = pat.idx.data() + pat.ptr[pc.first_row[other]];
-                            int64_t shared = 0;
-                            for (int64_t u = 0, v = 0; u < len && v < pc.len[other];) {
-                                shared += mine[u] == theirs[v];
-                                const bool up = mine[u] <= theirs[v], vp = theirs[v] <= mine[u];
-                                u += up;
-                                v += vp;
-                            }
-                            if (passes(shared, other)) local.pairs.emplace_back(static_cast<int32_t>(k), static_cast<int32_t>(other));
-                        }
-                    std::fill(count + x, count + x + kStride, Count{0});
-                }
-            } else {
-                for (const auto& list : local.lists)
-                    for (const int32_t* p = list.first; p < list.second; ++p) {
-                        const int64_t shared = ++count[*p];
-                        if (shared >= least && passes(shared, *p)) local.pairs.emplace_back(static_cast<int32_t>(k), *p);
-                    }
-                for (const auto& list : local.lists)
-                    for (const int32_t* p = list.first; p < list.second; ++p) count[*p] = 0;
-            }
+            if (!search.run(k, k + 1, end)) partners.many[k] = 1;
+            else for (int32_t other : search.found) local.pairs.emplace_back(static_cast<int32_t>(k), other);
         }
     });
-    Partners partners;
+    std::vector<int32_t> with_many;
+    for (int64_t k = 0; k < n; ++k)
+        if (partners.many[k]) with_many.push_back(static_cast<int32_t>(k));
+    if (!with_many.empty()) {
+        // these by column
+        std::vector<int64_t> ptr(static_cast<size_t>(nbc) + 1, 0);
+        auto entries = [&](auto&& take) {
+            for (int32_t k : with_many)
+                for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) take(pat.idx[q], k);
+        };
+        entries([&](int32_t c, int32_t) { ++ptr[c + 1]; });
+        prefix_sums(ptr);
+        Buf<int32_t> classes(static_cast<size_t>(ptr[nbc]));
+        std::vector<int64_t> fill(ptr.begin(), ptr.end() - 1);
+        entries([&](int32_t c, int32_t k) { classes[fill[c]++] = k; });
+        std::vector<uint8_t> many_too(static_cast<size_t>(n), 0);
+        workers.ranges(n, 256, [&](int64_t j0, int64_t j1, int thread) {
+            Local& local = local_of(thread);
+            PartnerSearch<Count>& search = *local.search;
+            for (int64_t j = j0; j < j1; ++j) {
+                const int64_t k = n - 1 - j, len = pc.len[k];
+                if (len == 0 || alive[k] == 0 || partners.many[k]) continue;
+                // (a partner has more than keep len / 1000 columns, and this many of the shared ones list it)
+                const int64_t least = keep * (len + keep * len / 1000 + 1) / (1000 + keep) + 1;
+                int64_t listing = 0;
+                for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) listing += ptr[pat.idx[q] + 1] > ptr[pat.idx[q]];
+                if (listing < least) continue;
+                const int64_t begin = std::partition_point(pc.len.begin(), pc.len.begin() + k, [&](int32_t x) { return keep * len >= 1000 * static_cast<int64_t>(x); }) - pc.len.begin();
+                search.lists.clear();
+                for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) {
+                    const int32_t* p = classes.data() + ptr[pat.idx[q]];
+                    const int32_t* stop = classes.data() + ptr[pat.idx[q] + 1];
+                    stop = std::lower_bound(p, stop, static_cast<int32_t>(k));
+                    search.lists.emplace_back(std::lower_bound(p, stop, static_cast<int32_t>(begin)), stop);
+                }
+                if (!search.run(k, begin, k)) many_too[k] = 1;
+                else for (int32_t other : search.found) local.longer.emplace_back(static_cast<int32_t>(k), other);
+            }
+        });
+        for (int64_t k = 0; k < n; ++k) partners.many[k] |= many_too[k];
+    }
+    auto listed = [&](auto&& take) {
+        for (const Local& local : locals) {
+            for (const auto& p : local.pairs) { take(p.first, p.second); take(p.second, p.first); }
+            for (const auto& p : local.longer) take(p.first, p.second);
+        }
+    };
     partners.ptr.assign(static_cast<size_t>(n) + 1, 0);
-    for (const Local& local : locals)
-        for (const auto& p : local.pairs) { ++partners.ptr[p.first + 1]; ++partners.ptr[p.second + 1]; }
+    listed([&](int32_t k, int32_t) { partners.ptr[k + 1] += partners.many[k] ? 0 : 1; });
     prefix_sums(partners.ptr);
     partners.of.resize(static_cast<size_t>(partners.ptr[n]));
     std::vector<int64_t> fill(partners.ptr.begin(), partners.ptr.end() - 1);
-    for (const Local& local : locals)
-        for (const auto& p : local.pairs) {
-            partners.of[fill[p.first]++] = p.second;
-            partners.of[fill[p.second]++] = p.first;
-        }
+    listed([&](int32_t k, int32_t other) { if (!partners.many[k]) partners.of[fill[k]++] = other; });
     return partners;
 }
 
@@ -506,7 +607,7 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     };
     // Every row before the scan's position is in a cluster, so a class with a row left has it ahead.
     auto has_partner = [&](int32_t k) {
-        if (partners.ptr.empty()) return true;            // not asked: it may
+        if (partners.ptr.empty() || partners.many[k]) return true;      // not asked, or too many to list: it may
         for (int64_t x = partners.ptr[k]; x < partners.ptr[k + 1]; ++x)
             if (state[partners.of[x]].alive > 0) return true;
         return false;
