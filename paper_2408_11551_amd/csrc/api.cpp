@@ -69,6 +69,7 @@ struct smat_handle {
     int max_quad_steps = 0;
     int quad_tail = 0;                   // 1: a last super row too short for a tile follows the others, for the kernel for few columns
     int64_t quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr.back(); }
+    int64_t tiled_quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr[dense_super.size()]; }      // without those of quad_tail
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
     smat::DeviceBcsr dev;                // launch over every block row
     smat::DeviceBcsr dev_rest;           // launch over the block rows the dense path does not cover
@@ -95,6 +96,9 @@ namespace {
 
 thread_local std::string g_error;
 thread_local const char* g_kernel = "";
+// what the last product enqueued, in order (smat_last_launches puts the names together)
+thread_local std::vector<const char*> g_launches;
+thread_local double g_flop = 0;
 
 smat_status_t fail(smat_status_t st, const std::string& msg)
 {
@@ -1058,14 +1062,30 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     const char* variant = "";
     thread_local std::string name;
     int e = 0;
+    auto enqueued = [](const char* kernel, double flop) { g_launches.push_back(kernel); g_flop += flop; };
+    // a pack is one matrix instruction of 16 x 16 x 32 per sixteen columns
+    auto rows_flop = [](const smat::DeviceBcsr& d, int64_t n) { return 2.0 * 16 * 16 * 32 * static_cast<double>(d.n_packs) * static_cast<double>((n + 15) / 16); };
+    // a step of either tile kernel: per block row and sixteen columns, 32 k slots of a 16-bit type's values or 64 of an 8-bit type's;
+    // the 8-bit floats go over the two-of-four form twice
+    const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
+    const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 || h->dtype == SMAT_E5M2 ? 2.0 : 1.0);
     if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N, ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0)) {
         // (with the last few block rows among the quads, all are: quad_tail)
-        if (h->dev_rest.n_order > 0 && !h->quad_tail) e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
-        if (!e) e = smat::launch_quad_rows(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        if (h->dev_rest.n_order > 0 && !h->quad_tail) {
+            e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+            enqueued("rows", rows_flop(h->dev_rest, N));
+        }
+        if (!e) {
+            e = smat::launch_quad_rows(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+            const int64_t passes = smat::quad_row_passes(h->elem_bytes, N, smat::quad_row_bytes(h->elem_bytes, N, h->max_quad_steps));
+            enqueued("quad_rows", quad_step_flop * static_cast<double>(tiles.n_quad_steps) * static_cast<double>(passes));
+        }
         g_kernel = variant;
     } else if (use_tiles) {
-        if (h->dev_rest.n_order > 0)
+        if (h->dev_rest.n_order > 0) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+            enqueued("rows", rows_flop(h->dev_rest, N));
+        }
         const char* dense_variant = "";
         for (int64_t c0 = 0; c0 < N && !e; c0 += chunk) {
             const int64_t n = std::min(chunk, N - c0);
@@ -1073,8 +1093,14 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             if (!in_pieces) {
                 e = smat::launch_stage_b(b, ldb, h->csr.K, n, h->elem_bytes, scratch, stage_ld, stream);
                 b = static_cast<const char*>(scratch);
+                enqueued("copy_b", 0);
             }
-            if (!e) e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
+            if (e) break;
+            e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
+            const double groups = static_cast<double>((n + 127) / 128 * 8);
+            if (tiles.n_quad_steps > 0) enqueued("quad_tiles", quad_step_flop * groups * static_cast<double>(h->tiled_quad_steps()));
+            else enqueued("tiles", step_flop * groups * static_cast<double>(h->step_rows.size()));
+            if (smat::dense_split(tiles, n) > 1) enqueued("sum_tiles", 0);
         }
         name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (h->dev_rest.n_order > 0 ? std::string("+") + variant : std::string());
         g_kernel = name.c_str();
@@ -1085,10 +1111,13 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             for (int64_t c0 = 0; c0 < N && !e; c0 += st.chunk) {
                 const int64_t n = std::min(st.chunk, N - c0);
                 e = smat::launch_stage_b(static_cast<const char*>(dB) + c0 * h->elem_bytes, ldb, h->csr.K, n, h->elem_bytes, scratch, st.ld, stream);
+                enqueued("copy_b", 0);
                 if (!e) e = smat::launch_spmm(h->dev, h->dtype, scratch, st.ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &variant);
+                enqueued("rows", rows_flop(h->dev, n));
             }
         } else {
             e = smat::launch_spmm(h->dev, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+            enqueued("rows", rows_flop(h->dev, N));
         }
         g_kernel = variant;
     }
@@ -1101,6 +1130,8 @@ smat_status_t check_spmm_args(const smat_handle_t* h, const void* dB, int64_t ld
                               int64_t N, bool* nothing_to_do)
 {
     *nothing_to_do = false;
+    g_launches.clear();
+    g_flop = 0;
     if (!h) return fail(SMAT_ERR_INVALID_ARG, "handle is NULL");
     if (!h->bound) return fail(SMAT_ERR_NOT_BOUND, "smat_spmm called before smat_bind_device");
     if (N < 0) return fail(SMAT_ERR_INVALID_ARG, "N is negative");
@@ -1240,5 +1271,18 @@ void smat_destroy(smat_handle_t* h) { delete h; }
 const char* smat_last_error(void) { return g_error.c_str(); }
 
 const char* smat_last_kernel(void) { return g_kernel; }
+
+const char* smat_last_launches(double* flop)
+{
+    thread_local std::string text;
+    try {
+        text.clear();
+        for (const char* kernel : g_launches) text.append(text.empty() ? "" : "+").append(kernel);
+    } catch (const std::bad_alloc&) {
+        return "";
+    }
+    if (flop) *flop = g_flop;
+    return text.c_str();
+}
 
 }  // extern "C"

@@ -116,6 +116,8 @@ def _load():
     lib.smat_last_error.argtypes = []
     lib.smat_last_kernel.restype = ctypes.c_char_p
     lib.smat_last_kernel.argtypes = []
+    lib.smat_last_launches.restype = ctypes.c_char_p
+    lib.smat_last_launches.argtypes = [ctypes.POINTER(ctypes.c_double)]
     return lib
 
 
@@ -149,6 +151,13 @@ def smat_last_error() -> str:
 
 def smat_last_kernel() -> str:
     return _lib.smat_last_kernel().decode()
+
+
+def smat_last_launches():
+    """(kernels of the last smat_spmm on this thread, in order and joined by "+", operations of their matrix instructions)"""
+    flop = ctypes.c_double()
+    names = _lib.smat_last_launches(ctypes.byref(flop)).decode()
+    return names, flop.value
 
 
 def smat_default_options() -> dict:

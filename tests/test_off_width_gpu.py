@@ -77,6 +77,7 @@ def test_per_row_kernel_on_a_copy_of_b(shape, oracle_c):
     w = w if dtype == "f16" else recast(w, dtype)
     for ldb, ldc, shift in ((N, N, 0), (N + 1, N + 2, 1)):
         _exact(w, oracle_c, ldb, ldc, shift)
+        assert S.smat_last_launches()[0] == "+".join(["copy_b+rows"] * (2 if N == 1400 else 1))
 
 
 # columns dealt into quads (kernels_quads.hip): fills that give full quads, quads with gaps (20, 25 %), an incomplete last super row, a
@@ -93,6 +94,7 @@ def test_tile_kernel_on_quads(shape, dtype, oracle_c):
     ldb = (N + piece - 1) // piece * piece
     name = _exact(w, oracle_c, ldb, N + 3, 0, dense_tiles=1)
     assert name.startswith(f"spmm_dense_{dtype}_g2"), name
+    assert "quad_tiles" in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])

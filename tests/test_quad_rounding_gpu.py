@@ -13,7 +13,7 @@ TORCH = {"f16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3
 
 
 def _errors(dtype, M, K, N, fill):
-    """(relative error on quads, on the per-row kernel), and the names of the two."""
+    """(relative error on quads, on the per-row kernel), and what the two enqueued."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M + N)
     mask = torch.rand((M, K), device="cuda", generator=gen) < fill
@@ -29,7 +29,7 @@ def _errors(dtype, M, K, N, fill):
     for dense_tiles in (1 if N >= 128 else 0, -1):
         m = S.SmatMatrix(M, K, row_ptr, cols.to(torch.int32).cpu().numpy(), vals, dtype, reorder=0, dense_tiles=dense_tiles)
         c = m.spmm(b.view(bits))
-        names.append(S.smat_last_kernel())
+        names.append(S.smat_last_launches()[0].split("+"))
         errors.append(((c.double() - ref).norm() / ref.norm()).item())
         m.close()
     return errors, names
@@ -42,8 +42,7 @@ def _errors(dtype, M, K, N, fill):
 @pytest.mark.parametrize("dtype", ["e4m3", "e5m2"])
 def test_8bit_floats_on_quads_are_as_exact_as_the_ordinary_instruction(dtype, shape, fill):
     (quads, rows), names = _errors(dtype, *shape, fill)
-    assert names[0].startswith("spmm_dense") if shape[2] >= 128 else "_q" in names[0], names
-    assert not names[1].startswith("spmm_dense") and "_q" not in names[1], names
+    assert ("quad_tiles" if shape[2] >= 128 else "quad_rows") in names[0] and names[1] == ["rows"], names
     assert quads <= 1.05 * rows, (quads, rows, names)
 
 
@@ -55,5 +54,5 @@ def test_8bit_floats_on_quads_are_as_exact_as_the_ordinary_instruction(dtype, sh
 def test_few_columns_on_quads_are_as_exact_as_the_per_row_kernel(dtype, N, shape):
     M, K, fill = shape
     (quads, rows), names = _errors(dtype, M, K, N, fill)
-    assert "_q" in names[0] and "_q" not in names[1], names
+    assert "quad_rows" in names[0] and names[1] == ["rows"], names
     assert quads <= rows, (quads, rows, names)
