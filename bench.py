@@ -153,6 +153,10 @@ class Bound:
     def step(self, stream):
         self.S.smat_spmm(self.h, self.B, self.C, self.w.N, stream)
 
+    def note_launches(self):
+        """What a product enqueues, and the operations its matrix instructions take: those of the step just made."""
+        self.launches, self.launched_flop = self.S.smat_last_launches()
+
     def close(self):
         self.S.smat_destroy(self.h)
         self.h = None
@@ -164,8 +168,10 @@ class Bound:
         mfma_peak = MFMA_PEAK_TFLOPS if self.es == 2 else MFMA_PEAK_TFLOPS_8BIT
         d = {
             "useful_flop": 2.0 * w.nnz * w.N,
+            # what the matrix units are given: of a two-of-four instruction the values it takes, not the extent it covers
+            "issued_flop": self.launched_flop,
             # one MFMA 16x16x32 per pack and 16 columns: on a block-dense matrix these are the flops of the stored blocks
-            "issued_flop": 2.0 * lay["n_packs"] * 16 * 32 * (-(-w.N // 16) * 16),
+            "stored_block_flop": 2.0 * lay["n_packs"] * 16 * 32 * (-(-w.N // 16) * 16),
             "bytes_alg": algorithmic_bytes(lay, w.K, w.N, w.M, self.es),
             "bytes_bcsr": bcsr_format_bytes(info["n_blocks"], info["n_block_rows"], w.M, w.K, w.N, self.es),
             "b_gather_bytes": lay["n_columns"] * w.N * self.es,
@@ -189,6 +195,7 @@ def timed_hot(torch, stream, bound, steps, warmup):
     ev1.record(stream)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
+    bound.note_launches()
     return wall * 1e3 / steps, ev0.elapsed_time(ev1) / steps
 
 
@@ -247,7 +254,7 @@ def roofline_of(bound, kernel_ms, cold_ms, kernel_name, probes, idle_ms=None):
         # stored, so every 256 x 128 tile walks K / 32 steps of 16 KiB of block values and an 8 KiB panel of B;
         # 16-bit types): against the rate at which the L2s fed the L1s in the probe
         full_grid = bound.info["n_blocks"] == -(-w.M // 16) * -(-w.K // 16) and w.M % 256 == 0 and w.K % 32 == 0
-        if kernel_name.startswith("spmm_dense") and "+" not in kernel_name and full_grid and bound.es == 2:
+        if bound.launches in ("tiles", "tiles+sum_tiles") and full_grid and bound.es == 2:
             fills = (w.M // 256) * -(-w.N // 128) * (w.K // 32) * 24576
             out["l1_fill_bytes"] = fills
             out["l1_fill_gbs"] = fills / (kernel_ms * 1e-3) / 1e9
@@ -352,7 +359,7 @@ def main():
     def summary(bound, ms_wall, k_ms, c_ms, name, i_ms=None):
         dd = bound.derived()
         roof = roofline_of(bound, k_ms, c_ms, name, probes, i_ms)
-        s = {"workload": WORKLOAD_TEXT[bound.name], "dtype": bound.w.dtype, "kernel": name,
+        s = {"workload": WORKLOAD_TEXT[bound.name], "dtype": bound.w.dtype, "kernel": name, "launches": bound.launches,
              "ms": k_ms, "cold_ms": c_ms, "first_launches_after_idle_ms": i_ms, "useful_tflops": dd["useful_flop"] / (k_ms * 1e-3) / 1e12,
              "bytes_algorithmic": dd["bytes_alg"], "flops_issued": dd["issued_flop"], "b_gather_bytes": dd["b_gather_bytes"],
              "n_packs": bound.layout["n_packs"], "n_blocks": bound.info["n_blocks"], "nnz": bound.w.nnz,
@@ -364,7 +371,7 @@ def main():
                 s["roofline"][k] = roof[k]
         if dd["mfma_bound"]:
             # block-dense: every block is stored, so these are the flops of the stored blocks
-            s["stored_block_tflops"] = dd["issued_flop"] / (k_ms * 1e-3) / 1e12
+            s["stored_block_tflops"] = dd["stored_block_flop"] / (k_ms * 1e-3) / 1e12
         return s
 
     all_configs = None
