@@ -292,7 +292,7 @@ struct Partners {
 // Where a class has many increments to make, they are made without looking, and the counters are looked through (and cleared) once, in
 // order; and only some of its columns are counted: b has to share `least` of a's columns, so all but least - m of them (the
 // longest lists are left out) already hold m shared ones; whoever reaches m, about nobody by chance, is counted exactly.  Where the
-// average class has half of `least`, a few classes are gone through first: a class with many partners has enough of them there.
+// average class has `least` of them, a few classes are gone through first: a class with many partners has enough of them there.
 template <typename Count>
 class PartnerSearch {
 public:
@@ -342,7 +342,7 @@ public:
                              [](const auto& x, const auto& y) { return x.second - x.first < y.second - y.first; });
         const int32_t* mine = pat_.idx.data() + pat_.ptr[pc_.first_row[k]];
         int64_t to = begin;
-        for (int64_t window = 2 * ahead >= least * (end - begin) ? 8 * kStride : end - begin; to < end && found.size() <= kMostPartners; window *= 64) {
+        for (int64_t window = ahead >= least * (end - begin) ? 8 * kStride : end - begin; to < end && found.size() <= kMostPartners; window *= 64) {
             const int64_t from = to;
             to = std::min(end, from + window);
             for (int64_t x = 0; x < counted; ++x) {
