@@ -45,6 +45,7 @@ HEADLINE = "hidden_blocks"
 # (HBM-side traffic) and matrix-unit counters.  The traffic figure of the line is read from there
 # by hand, never typed into this file: the line carries null and names the file.
 PROFILE_OF = {name: f"profiles/spmm_{name}.md" for name in WORKLOAD_TEXT if name != "tiny"}
+PROFILE_OF["pruned_weight"] = "profiles/spmm_quads.md"
 
 
 def algorithmic_bytes(layout, K, N, M, es=2):
