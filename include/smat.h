@@ -209,7 +209,8 @@ smat_status_t smat_export_device_vals(const smat_handle_t *h, void *vals, void *
  * For a given handle, stream and arguments the result is bitwise reproducible.
  * Infinities and NaN in B: the rows of A' that a kernel works on together are all multiplied by the rows of B that any
  * of them needs, most by stored zeros, and zero times infinity is NaN.  A non-finite element in row k and column n
- * of B therefore reaches column n of C in the rows that store column k, and as a NaN it may also reach the other
+ * of B therefore reaches column n of C in the rows that store column k (an infinity as what arithmetic gives, or as
+ * NaN where a block row is kept by entry), and as a NaN it may also reach the other
  * rows of their group: with dense_tiles = -1 the sixteen rows of a block row, otherwise the 256 rows perm[256 s] ... perm[256 s + 255]
  * of a group s of which any row stores an entry in block column k / 16.  Rows of other groups and the other columns of C are
  * not affected.

@@ -301,9 +301,9 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
         for (int64_t br = 16 * static_cast<int64_t>(s); br < std::min<int64_t>(h.bcsr.nbr, 16 * static_cast<int64_t>(s) + 16); ++br)
             nnz += block_row_nnz(h, static_cast<size_t>(br));
     // What a step costs against one of the other form, measured: fp16 / bf16 0.43 us and 0.365, int8 0.37 and 0.27, the 8-bit floats,
-    // whose instructions go over the extent twice, 0.67 and 0.47 (4096 columns, N = 2048: at 10 % fill 34.4 us against 43.4, at 25 %
-    // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9).
-    const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : 0.7) * static_cast<double>(steps);
+    // which take twice the instructions, e4m3 0.67 and 0.47 (4096 columns, N = 2048: at 10 % fill 34.4 us against 43.4, at 25 %
+    // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9), e5m2 0.79 and 0.47 (at 10 % fill 37.7 against 43.2).
+    const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : h.dtype == SMAT_E4M3 ? 0.7 : 0.6) * static_cast<double>(steps);
     // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
     if (static_cast<double>(nnz) > (es == 2 ? 0.3 : 0.27) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
     // A last super row of a few block rows is left to the per-row kernel by the tile kernels, whose tile would be mostly empty; in
@@ -812,8 +812,8 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
                                         reinterpret_cast<uint32_t*>(base + l.slots), static_cast<size_t>(h->slots_units) * 8, h->elem_bytes, s)))
             return hip_fail("fill block values", e);
         if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_index - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
-        e = quads ? smat::launch_quad_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
-                                           h->elem_bytes, h->max_quad_steps, s)
+        e = quads ? smat::launch_quad_fill(d, tiles, h->dtype, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
+                                           h->max_quad_steps, s)
                   : smat::launch_dense_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);
         if (e) return hip_fail("fill tile values", e);
         if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("bind synchronize", e);
@@ -1036,7 +1036,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
             const int ks = smat::dense_split(tiles, n);
             // us per step of a tile, alone on its compute unit (an 8-bit step covers twice the block columns)
-            const double quad_us = h->elem_bytes == 2 ? 0.43 : h->dtype == SMAT_I8 ? 0.37 : 0.6;
+            const double quad_us = h->elem_bytes == 2 ? 0.43 : h->dtype == SMAT_I8 ? 0.37 : h->dtype == SMAT_E4M3 ? 0.6 : 0.7;
             const double walk_us = tiles.n_quad_steps ? quad_us * tiles.n_quad_steps / tiles.n
                                                       : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
             t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (tiles.n_quad_steps ? 6.0 : 4.0)) + 1.5;
@@ -1066,9 +1066,9 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // a pack is one matrix instruction of 16 x 16 x 32 per sixteen columns
     auto rows_flop = [](const smat::DeviceBcsr& d, int64_t n) { return 2.0 * 16 * 16 * 32 * static_cast<double>(d.n_packs) * static_cast<double>((n + 15) / 16); };
     // a step of either tile kernel: per block row and sixteen columns, 32 k slots of a 16-bit type's values or 64 of an 8-bit type's;
-    // the 8-bit floats go over the two-of-four form twice
+    // e4m3 goes over the two-of-four form twice
     const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
-    const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 || h->dtype == SMAT_E5M2 ? 2.0 : 1.0);
+    const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 ? 2.0 : 1.0);
     if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N, ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0)) {
         // (with the last few block rows among the quads, all are: quad_tail)
         if (h->dev_rest.n_order > 0 && !h->quad_tail) {

@@ -103,8 +103,8 @@ int launch_dense_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* c
                       const int32_t* csr_col_idx, const uint16_t* csr_vals, void* vals_out, int elem_bytes, void* stream);
 
 // The same for the two-of-four form: values and positions.  max_steps: of any super row.
-int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
-                     const uint16_t* csr_vals, void* vals_out, void* index_out, int elem_bytes, int max_steps, void* stream);
+int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, int dtype, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
+                     const uint16_t* csr_vals, void* vals_out, void* index_out, int max_steps, void* stream);
 // Its part of launch_spmm_dense, the partial tiles of ks > 1 workgroups per tile left to the caller.
 void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
                        int64_t N, void* stream);

@@ -7,7 +7,7 @@
 // row -- so the columns of a super row are dealt into groups of four ("quads") in which no row has more than two stored entries
 // (plan_quads in api.cpp).  At random that succeeds for practically all columns up to 15 % fill (256 rows); at 20 %
 // a quad gets 3.5 columns on average, at 25 % 3.0.  In the 16-bit types and int8 the sums are as exact as the ordinary instruction's; the
-// 8-bit floats go over a step twice to be so (every_second_pair).
+// 8-bit floats take twice the instructions to be so (every_second_pair, kAsF16).
 //
 // One step covers 64 k slots (8-bit types: 128), four bytes of which are a quad's: 16 KiB of B in LDS, 16 KiB of values (two of
 // four: 1 KiB per block row as in the other kernel) and 2 KiB (4 KiB) of positions.  The work split is the other kernel's with two
@@ -18,7 +18,7 @@
 //
 // What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  The 8-bit
 // floats: the matrix units, which take 64 instructions of 16 clocks per step and wave (10 % fill: 6000 x 4096, N = 784
-// 29 us, against 25 with half as many; 8192 x 4096, N = 2048 65 us, against 82 in the other form).
+// e4m3 29 us and e5m2 36, against 25 with half as many; 8192 x 8192, N = 2048 111 and 126, against 149 in the other form).
 #include <cstdio>
 #include <type_traits>
 
@@ -36,7 +36,7 @@ typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-// 16 x 64 (8-bit types: 16 x 128) of A', two of every four k, times the same extent of B.  index: two bits per value; of a
+// 16 x 64 (e4m3 and int8: 16 x 128) of A', two of every four k, times the same extent of B.  index: two bits per value; of a
 // 16-bit type's eight values in half HALF of the word.
 template <int DT, int HALF>
 __device__ __forceinline__ typename Elem<DT>::Acc smfmac(u32x4 a, u32x8 b, typename Elem<DT>::Acc c, uint32_t index)
@@ -48,8 +48,6 @@ __device__ __forceinline__ typename Elem<DT>::Acc smfmac(u32x4 a, u32x8 b, typen
         return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x16, b), c, ix, 0, HALF);
     else if constexpr (DT == kE4M3)
         return __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
-    else if constexpr (DT == kE5M2)
-        return __builtin_amdgcn_smfmac_f32_16x16x128_bf8_bf8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
     else
         return __builtin_amdgcn_smfmac_i32_16x16x128_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x8, b), c, ix, 0, 0);
 }
@@ -58,12 +56,29 @@ __device__ __forceinline__ typename Elem<DT>::Acc smfmac(u32x4 a, u32x8 b, typen
 // error of a product against 64 bits at 5 / 10 / 20 % fill in e4m3, ordinary form 3.3e-6 / 3.7e-6 / 5.2e-6, this one 3.7e-6 / 5.0e-6 /
 // 6.5e-6 (16x16x64 instead of 16x16x128: the same bits).  So the kernels go over a step twice, with every second quad's values as
 // zeros: as many products at a time as the ordinary instruction meets, 2.8e-6 / 3.7e-6 / 4.9e-6.
-template <int DT> constexpr bool kInHalves = DT == kE4M3 || DT == kE5M2;
+template <int DT> constexpr bool kInHalves = DT == kE4M3;
 // half HALF (0, 1) of a lane's values
 __device__ __forceinline__ u32x4 every_second_pair(u32x4 a, int half)
 {
     const uint32_t keep = half ? 0xFFFF0000u : 0x0000FFFFu;
     return u32x4{a[0] & keep, a[1] & keep, a[2] & keep, a[3] & keep};
+}
+
+// e5m2 has infinities, and a value taken as zero times the infinity that it is stored for is NaN.  But it is the upper byte of f16: its
+// bytes are widened in registers (16 permutes per group of columns, 32 for a step's values) and go through two of the f16 type's
+// instructions, which round like fp32 (7e-8 at 10 % fill).  4096 x 4096, N = 2048: 37.7 us, 33.6 in two halves of 8-bit instructions.
+template <int DT> constexpr bool kAsF16 = DT == kE5M2;
+// eight bytes (two words) as halves
+__device__ __forceinline__ u32x4 widened(uint32_t lo, uint32_t hi)
+{
+    return u32x4{__builtin_amdgcn_perm(0u, lo, 0x010C000Cu), __builtin_amdgcn_perm(0u, lo, 0x030C020Cu),
+                 __builtin_amdgcn_perm(0u, hi, 0x010C000Cu), __builtin_amdgcn_perm(0u, hi, 0x030C020Cu)};
+}
+// k slots 64 h .. 64 h + 63 of a step: two of the four transposing reads
+__device__ __forceinline__ u32x8 widened_operand(const u32x2_t& p, const u32x2_t& q)
+{
+    const u32x4 lo = widened(p[0], p[1]), hi = widened(q[0], q[1]);
+    return u32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
 // the four reads have returned once at most YOUNGER later LDS reads are outstanding
@@ -233,7 +248,14 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
         auto step = [&](auto u_, int s) {
             constexpr int u = decltype(u_)::value;
             constexpr int next = (u + 2) % RD;
-            u32x4 first[RM];                       // of an 8-bit float's values half 0; a[u] keeps half 1
+            u32x4 wide[2][RM];                     // e5m2: the values as f16, those of the step's first 64 k slots and of the others
+            if constexpr (kAsF16<DT>) {
+#pragma unroll
+                for (int r = 0; r < RM; ++r)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) wide[h][r] = widened(a[u][r][2 * h], a[u][r][2 * h + 1]);
+            }
+            u32x4 first[RM];                       // e4m3: half 0 of the values; a[u] keeps half 1
             if constexpr (kInHalves<DT>) {
 #pragma unroll
                 for (int r = 0; r < RM; ++r) {
@@ -262,6 +284,13 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
                     acc[1][x] = smfmac<DT, 1>(a[u][1], operand, acc[1][x], ix[u][0]);
                     acc[2][x] = smfmac<DT, 0>(a[u][2], operand, acc[2][x], ix[u][1]);
                     acc[3][x] = smfmac<DT, 1>(a[u][3], operand, acc[3][x], ix[u][1]);
+                } else if constexpr (kAsF16<DT>) {
+                    const u32x8 lower = widened_operand(v[0], v[1]);
+#pragma unroll
+                    for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<kF16, 0>(wide[0][r], lower, acc[r][x], ix[u][r]);
+                    const u32x8 upper = widened_operand(v[2], v[3]);
+#pragma unroll
+                    for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<kF16, 1>(wide[1][r], upper, acc[r][x], ix[u][r]);
                 } else {
                     if constexpr (kInHalves<DT>) {
 #pragma unroll
@@ -516,7 +545,13 @@ void spmm_quad_rows_kernel(int n_units, int per_xcd, int N, uint32_t b_bytes, co
         }
         lds_four_done<0>(b);
         const u32x8 operand = u32x8{b[0][0], b[0][1], b[1][0], b[1][1], b[2][0], b[2][1], b[3][0], b[3][1]};
-        if constexpr (kInHalves<DT>) {
+        if constexpr (kAsF16<DT>) {
+            const u32x8 lower = widened_operand(b[0], b[1]), upper = widened_operand(b[2], b[3]);
+#pragma unroll
+            for (int r = 0; r < RM; ++r) acc[r] = smfmac<kF16, 0>(widened(av[r][0], av[r][1]), lower, acc[r], iv[r]);
+#pragma unroll
+            for (int r = 0; r < RM; ++r) acc[r] = smfmac<kF16, 1>(widened(av[r][2], av[r][3]), upper, acc[r], iv[r]);
+        } else if constexpr (kInHalves<DT>) {
 #pragma unroll
             for (int half = 0; half < 2; ++half)
 #pragma unroll
@@ -618,7 +653,8 @@ int launch_quad_rows(const DeviceBcsr& d, const DenseTiles& t, int dtype, const 
 
 // Bind-time scatter: one workgroup per block row of a quad super row, sixteen threads per row.  Shared memory: the place (step,
 // panel row) of every column that the super row stores, and per row a bit for every place that it fills.
-template <typename T>
+// (HALVES: the k slots of a step go to two instructions, kAsF16; quad_layout.h)
+template <typename T, bool HALVES>
 __global__ __launch_bounds__(256)
 void quad_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __restrict__ csr_row_ptr, const int32_t* __restrict__ csr_col_idx,
                       const uint16_t* __restrict__ csr_vals, T* __restrict__ vals_out, uint8_t* __restrict__ index_out, int place_bytes, int words)
@@ -652,7 +688,7 @@ void quad_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __restrict__ cs
     for (int64_t p = p0 + part; p < p1; p += 16) {
         const uint32_t pos = place[csr_col_idx[p]];
         const uint32_t quad = mine[pos >> 5] >> (pos & 28) & 15u, q = pos / COLS;
-        const QuadSlot slot = quad_slot(ES, static_cast<int>(pos % COLS));
+        const QuadSlot slot = quad_slot(ES, HALVES, static_cast<int>(pos % COLS));
         const int second = quad == 8u ? 1 : __popc(quad & ((1u << (pos & 3)) - 1u));
         const size_t unit = (static_cast<size_t>(q0) + q) * 16 + static_cast<size_t>(j);
         vals_out[(unit * 64 + static_cast<size_t>(16 * slot.lane_group + rr)) * EL + static_cast<size_t>(2 * slot.pair + second)] =
@@ -663,7 +699,7 @@ void quad_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __restrict__ cs
         const int q = x >> 2, group = x & 3;
         uint32_t word = 0;
         for (int pair = 0; pair < EL / 2; ++pair) {
-            const uint32_t pos = static_cast<uint32_t>(q * COLS + quad_first_row(ES, group, pair));
+            const uint32_t pos = static_cast<uint32_t>(q * COLS + quad_first_row(ES, HALVES, group, pair));
             const uint32_t quad = mine[pos >> 5] >> (pos & 28) & 15u;
             // ascending, whatever the quad holds: a single entry takes the first value and leaves position 3 to the second, unless it is in position 3 itself
             const uint32_t lo = quad == 0u || quad == 8u ? 0u : static_cast<uint32_t>(__ffs(quad)) - 1u;
@@ -677,19 +713,21 @@ void quad_fill_kernel(DeviceBcsr d, DenseTiles t, const int64_t* __restrict__ cs
     }
 }
 
-int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
-                     const uint16_t* csr_vals, void* vals_out, void* index_out, int elem_bytes, int max_steps, void* stream)
+int launch_quad_fill(const DeviceBcsr& d, const DenseTiles& t, int dtype, const int64_t* csr_row_ptr, const int32_t* csr_col_idx,
+                     const uint16_t* csr_vals, void* vals_out, void* index_out, int max_steps, void* stream)
 {
     if (t.n == 0) return 0;
-    const int place_bytes = static_cast<int>(quad_place_bytes(d.K)), words = max_steps * quad_columns(elem_bytes) / 32;
-    const size_t lds = quad_fill_lds(d.K, max_steps, elem_bytes);
+    const int es = dtype == kF16 || dtype == kBF16 ? 2 : 1;
+    const int place_bytes = static_cast<int>(quad_place_bytes(d.K)), words = max_steps * quad_columns(es) / 32;
+    const size_t lds = quad_fill_lds(d.K, max_steps, es);
     const dim3 grid(static_cast<unsigned>(t.n + t.quad_tail) * 16);
-    if (elem_bytes == 1)
-        hipLaunchKernelGGL(quad_fill_kernel<uint8_t>, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx,
-                           csr_vals, static_cast<uint8_t*>(vals_out), static_cast<uint8_t*>(index_out), place_bytes, words);
-    else
-        hipLaunchKernelGGL(quad_fill_kernel<uint16_t>, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx,
-                           csr_vals, static_cast<uint16_t*>(vals_out), static_cast<uint8_t*>(index_out), place_bytes, words);
+    auto fill = [&](auto kernel, auto* vals) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, static_cast<hipStream_t>(stream), d, t, csr_row_ptr, csr_col_idx, csr_vals, vals,
+                           static_cast<uint8_t*>(index_out), place_bytes, words);
+    };
+    if (es == 2) fill(quad_fill_kernel<uint16_t, false>, static_cast<uint16_t*>(vals_out));
+    else if (dtype == kE5M2) fill(quad_fill_kernel<uint8_t, true>, static_cast<uint8_t*>(vals_out));
+    else fill(quad_fill_kernel<uint8_t, false>, static_cast<uint8_t*>(vals_out));
     return static_cast<int>(hipGetLastError());
 }
 

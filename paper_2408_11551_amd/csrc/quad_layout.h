@@ -7,7 +7,8 @@
 // Which value multiplies which panel row: the kernel reads panel rows 32 r + 8 g .. 32 r + 8 g + 7 as the r-th eight k of lane group g of the
 // right operand (16-bit types r = 0, 1; 8-bit types r = 0 .. 3).  The instruction takes the k of its left operand in order, lane
 // group G the G-th quarter of them, and its right operand in halves, of which every lane group has a quarter.  (Checked on the
-// device, value by value and position by position, for the 16-bit types, e4m3 and int8; e5m2 by products that come out exact.)
+// device, value by value and position by position, for the 16-bit types, e4m3 and int8.)  `halves`: an 8-bit type whose 128 k slots go to
+// two instructions of a 16-bit type, 64 each; the first has a lane's first eight bytes of values and lower half of positions.
 //
 // Values: per step and block row 1 KiB, lane l = 16 G + i the 16 bytes at 16 l: row i, the pairs of values of its quads, in order.
 // Positions: two bits per value, ascending inside a pair; per step and wave (four block rows) and lane the block rows' words one after the
@@ -42,15 +43,17 @@ SMAT_QUAD_HD inline int quad_table_word(int es, int row)
 
 struct QuadSlot { int lane_group, pair; };
 // lane group of the left operand and pair of values (inside the lane's 16 bytes) of a panel row
-SMAT_QUAD_HD inline QuadSlot quad_slot(int es, int row)
+SMAT_QUAD_HD inline QuadSlot quad_slot(int es, bool halves, int row)
 {
     const int r = row >> 5, g = (row & 31) >> 3, h = (row >> 2) & 1;
+    if (halves) return QuadSlot{2 * (r & 1) + (g >> 1), 4 * (r >> 1) + 2 * (g & 1) + h};
     return es == 2 ? QuadSlot{2 * r + (g >> 1), 2 * (g & 1) + h}
                    : QuadSlot{2 * (r >> 1) + (g >> 1), 4 * (g & 1) + 2 * (r & 1) + h};
 }
 // first panel row of the quad of a pair
-SMAT_QUAD_HD inline int quad_first_row(int es, int lane_group, int pair)
+SMAT_QUAD_HD inline int quad_first_row(int es, bool halves, int lane_group, int pair)
 {
+    if (halves) return 64 * (pair >> 2) + 32 * (lane_group >> 1) + 8 * (2 * (lane_group & 1) + ((pair >> 1) & 1)) + 4 * (pair & 1);
     return es == 2 ? 32 * (lane_group >> 1) + 8 * (2 * (lane_group & 1) + (pair >> 1)) + 4 * (pair & 1)
                    : 32 * (2 * (lane_group >> 1) + ((pair >> 1) & 1)) + 8 * (2 * (lane_group & 1) + (pair >> 2)) + 4 * (pair & 1);
 }

@@ -1,5 +1,5 @@
-"""How far an infinity or a NaN in B reaches (include/smat.h, smat_spmm): the rows that store its column, as NaN perhaps the rest
-of their group, and nothing else.  Small integers: whatever it does not reach is exact."""
+"""How far an infinity or a NaN in B reaches (include/smat.h, smat_spmm): the rows that store its column, where on tiles
+and quads an infinity stays one, as NaN perhaps the rest of their group, and nothing else.  Small integers: whatever it does not reach is exact."""
 import numpy as np
 import pytest
 
@@ -38,8 +38,15 @@ def _check(dtype, bits, shape, dense_tiles, oracle_c):
         needs = w.col_idx == k if dense_tiles < 0 else w.col_idx // 16 == k // 16
         groups = np.unique(rows[needs] // group)
         may[:, n] |= np.isin(np.arange(M) // group, groups)
-        stored = rows[(w.col_idx == k) & (R.decode_bits(w.a_bits, dtype) != 0)]
-        assert stored.size and not np.isfinite(got[stored, n]).any(), name
+        a = R.decode_bits(w.a_bits, dtype)
+        stored = (w.col_idx == k) & (a != 0)
+        assert stored.any(), name
+        if bits in NAN.values():
+            assert np.isnan(got[rows[stored], n]).all(), name
+        elif name == "rows":                                                    # (a block row kept by entry multiplies a column once per entry)
+            assert not np.isfinite(got[rows[stored], n]).any(), name
+        else:                                                                   # infinity times what is stored, sign and all
+            assert np.array_equal(got[rows[stored], n], np.sign(a[stored]) * np.inf), name
     assert (~may).any(axis=1).any()
     assert np.array_equal(got[~may], ref[~may]), name                          # not reached: exact
     reached = may & (got != ref)                                               # reached without storing the column: NaN
