@@ -59,7 +59,7 @@ namespace smat {
 int launch_fill_zero(void*, size_t, void*) { return 0; }
 int launch_bcsr_fill(const DeviceBcsr&, const int64_t*, const int32_t*, const uint16_t*, const int32_t*, void*, uint32_t*, size_t, int, void*) { return 0; }
 int launch_dense_fill(const DeviceBcsr&, const DenseTiles&, const int64_t*, const int32_t*, const uint16_t*, void*, int, void*) { return 0; }
-int launch_quad_fill(const DeviceBcsr&, const DenseTiles&, const int64_t*, const int32_t*, const uint16_t*, void*, void*, int, int, void*) { return 0; }
+int launch_quad_fill(const DeviceBcsr&, const DenseTiles&, int, const int64_t*, const int32_t*, const uint16_t*, void*, void*, int, void*) { return 0; }
 int launch_quad_rows(const DeviceBcsr&, const DenseTiles&, int, const void*, int64_t, void*, int64_t, int64_t, void*, const char** variant)
 {
     *variant = "quad_rows";
