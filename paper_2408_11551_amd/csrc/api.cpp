@@ -302,7 +302,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
             nnz += block_row_nnz(h, static_cast<size_t>(br));
     // What a step costs against one of the other form, measured: fp16 / bf16 0.43 us and 0.365, int8 0.37 and 0.27, the 8-bit floats,
     // which take twice the instructions, e4m3 0.67 and 0.47 (4096 columns, N = 2048: at 10 % fill 34.4 us against 43.4, at 25 %
-    // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9), e5m2 0.79 and 0.47 (at 10 % fill 37.7 against 43.2).
+    // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9), e5m2 0.79 and 0.47 (at 10 % fill 38.8 against 42.8).
     const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : h.dtype == SMAT_E4M3 ? 0.7 : 0.6) * static_cast<double>(steps);
     // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
     if (static_cast<double>(nnz) > (es == 2 ? 0.3 : 0.27) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
