@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -794,6 +795,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
         tiles.max_quad_steps = h->max_quad_steps;
         tiles.quad_tail = h->quad_tail;
+        tiles.quad_tail_rows = h->quad_tail ? static_cast<int32_t>(b.nbr % 16) : 0;
         tiles.scratch = nullptr;           // a call takes the area of its stream
         tiles.scratch_bytes = 0;
         tiles.n = static_cast<int32_t>(h->dense_super.size());
@@ -970,11 +972,14 @@ constexpr int64_t kStageColumns = 32;
 // 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
 // once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
 // out of the L2s or from further away.
-bool quad_rows_take(const smat_handle& h, int64_t N, bool off_dwords)
+// (Both infinite where it does not take N columns at all.)
+struct FewColumns { double quads_us, rows_us; bool take() const { return quads_us + 0.3 < rows_us; } };
+FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
 {
-    if (h.tiles.n_quad_steps == 0 || N > 32) return false;
+    constexpr double kNever = std::numeric_limits<double>::infinity();
+    if (h.tiles.n_quad_steps == 0 || N > 32) return {kNever, kNever};
     const int es = h.elem_bytes, row_bytes = smat::quad_row_bytes(es, N, h.max_quad_steps);
-    if (row_bytes == 0) return false;
+    if (row_bytes == 0) return {kNever, kNever};
     const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
     const double columns = static_cast<double>(h.dense_columns), block_rows = 16.0 * h.tiles.n;
     const double per_column = es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
@@ -983,7 +988,44 @@ bool quad_rows_take(const smat_handle& h, int64_t N, bool off_dwords)
     const double quads_us = 4.2 + 0.008 * h.max_quad_steps * passes + 1.0e-5 * static_cast<double>(smat::quad_rows_lds(h.max_quad_steps, es, row_bytes)) +
                             a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (off_dwords ? 0.7 : 0.0) +
                             (h.dev_rest.n_order > 0 && !h.quad_tail ? 5.0 : 0.0);      // a launch for the other block rows
-    return quads_us + 0.3 < rows_us;
+    return {quads_us, rows_us};
+}
+
+// What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
+// other, a little per step of all (what the units share), the write of C; with split steps, the partial tiles.  Fitted on
+// 400 products of random matrices (1000 ... 8192 rows and columns, 5-20 % fill, N = 16 ... 4096, all types): within 3-8 % (rms).
+double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
+{
+    struct Cost { double start, step, shared; };
+    static constexpr Cost kCosts[4][smat::kQuadShapes] = {
+        {{3.4, 0.39, 0.06}, {5.0, 0.311, 0.088}, {4.1, 0.256, 0.093}, {3.4, 0.1825, 0.062}, {2.9, 0.142, 0.054}},     // fp16, bf16
+        {{3.4, 0.562, 0.079}, {5.2, 0.467, 0.05}, {4.3, 0.346, 0.064}, {3.15, 0.2125, 0.081}, {2.6, 0.171, 0.108}},   // e4m3
+        {{4.5, 0.81, 0.0}, {5.4, 0.627, 0.03}, {4.3, 0.514, 0.0}, {4.4, 0.33, 0.0}, {2.8, 0.239, 0.026}},             // e5m2
+        {{5.1, 0.431, 0.0}, {5.1, 0.312, 0.24}, {4.2, 0.254, 0.17}, {3.7, 0.174, 0.12}, {2.85, 0.151, 0.122}},        // int8
+    };
+    static constexpr double kWrite[smat::kQuadShapes] = {0.22, 0.22, 0.22, 0.12, 0.04};                            // us per MB of C
+    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : h.dtype == SMAT_E4M3 ? 1 : h.dtype == SMAT_E5M2 ? 2 : 3][t.quad_shape];
+    const int64_t columns = smat::quad_shape_columns(t.quad_shape);
+    const double n_tiles = static_cast<double>(smat::quad_row_tiles(t)) * static_cast<double>((N + columns - 1) / columns);
+    const double steps = static_cast<double>(h.tiled_quad_steps()) / t.n, c_mb = static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
+    const int ks = smat::dense_split(t, N);
+    if (ks > 1) return 10.5 + c.step * std::ceil(steps / ks) + std::min(9.0, 0.05 * n_tiles * ks);
+    return c.start + std::ceil(n_tiles / 256.0) * steps * c.step + n_tiles / 256.0 * steps * c.shared + kWrite[t.quad_shape] * c_mb;
+}
+
+// The same on the per-row kernel, fitted on the same products (within 10-20 %): rows of B by the byte and by the 256-byte slab, values, C; rows
+// of B on whole cache lines, on dwords, and off them.
+double rows_us(const smat_handle& h, int64_t N, int64_t ldb)
+{
+    struct Cost { double start, gather, slab, values, write; };
+    static constexpr Cost kCosts[2][3] = {{{2.7, 0.053, 0.39, 0.14, 0.29}, {3.0, 0.058, 0.31, 0.105, 0.33}, {4.0, 0.057, 0.0, 0.35, 0.75}},
+                                          {{2.8, 0.051, 0.0, 0.25, 0.52}, {3.15, 0.057, 1.82, 0.153, 0.48}, {2.9, 0.085, 0.0, 0.66, 0.82}}};
+    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256;
+    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][ldb * h.elem_bytes % 128 == 0 ? 0 : ldb * h.elem_bytes % 4 == 0 ? 1 : 2];
+    const double m_rows = static_cast<double>(h.b_rows) * 1e-6;
+    const double idle = std::max(1.0, 256.0 / (static_cast<double>(h.bcsr.nbr) * static_cast<double>(slabs)));
+    return c.start + m_rows * (c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs)) * idle +
+           c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
 }
 
 // smat_spmm with the area for partial tiles given by the caller of this function.
@@ -1029,7 +1071,37 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // It also has to pay: few tiles leave most of the chip idle, while the per-row kernel fetches every occupied column's row
     // of B again for every block row but spreads that over all compute units.  The estimates are measured rates, fitted on
     // bands and random matrices of 1000 ... 65536 rows and 5-100 % fill at N = 8 ... 2048, 16-bit and 8-bit; the faster path is taken.
-    if (use_tiles && h->dense_mode == 0) {
+    const bool off_dwords = ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0;
+    if (use_tiles && h->dense_mode == 0 && tiles.n_quad_steps > 0 && !hard_limit) {
+        // On quads the shape is chosen too: narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
+        // a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
+        // 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  A last
+        // super row with few block rows gets tiles like the others where that pays.
+        auto take = [&](int shape, bool tail) {
+            tiles.quad_shape = shape;
+            tiles.quad_tail_tiled = tail;
+        };
+        double best = std::numeric_limits<double>::infinity();
+        int best_shape = smat::kQuad256x128;
+        bool best_tail = false;
+        for (int choice = 0; choice < 2 * smat::kQuadShapes; ++choice) {
+            const int shape = choice / 2;
+            const bool tail = choice % 2 != 0;
+            if (tail && !tiles.quad_tail) continue;
+            take(shape, tail);
+            // (a launch of a few block rows: as long as the longest one's walk)
+            double us = h->dev_rest.n_order > 0 && !tail ? 3.0 + 0.09 * static_cast<double>(h->dev_rest.max_row_packs) : 0.0;
+            for (int64_t c0 = 0; c0 < N; c0 += chunk) {
+                const int64_t n = std::min(chunk, N - c0);
+                us += quad_tiles_us(*h, tiles, n);
+                if (!in_pieces) us += 3.7 + 0.3e-6 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes);      // the copy of B
+            }
+            if (us < best) { best = us; best_shape = shape; best_tail = tail; }
+        }
+        take(best_shape, best_tail);
+        const FewColumns few = few_columns(*h, N, off_dwords);
+        use_tiles = 1.08 * best + 0.5 <= rows_us(*h, N, ldb) && !(few.take() && few.quads_us < best);
+    } else if (use_tiles && h->dense_mode == 0) {
         double t_tiles = 0;
         for (int64_t c0 = 0; c0 < N; c0 += chunk) {
             const int64_t n = std::min(chunk, N - c0);
@@ -1069,7 +1141,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // e4m3 goes over the two-of-four form twice
     const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
     const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 ? 2.0 : 1.0);
-    if (!use_tiles && h->dense_mode == 0 && quad_rows_take(*h, N, ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0)) {
+    if (!use_tiles && h->dense_mode == 0 && few_columns(*h, N, off_dwords).take()) {
         // (with the last few block rows among the quads, all are: quad_tail)
         if (h->dev_rest.n_order > 0 && !h->quad_tail) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
@@ -1082,7 +1154,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         }
         g_kernel = variant;
     } else if (use_tiles) {
-        if (h->dev_rest.n_order > 0) {
+        const bool rest = h->dev_rest.n_order > 0 && !tiles.quad_tail_tiled;
+        if (rest) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
             enqueued("rows", rows_flop(h->dev_rest, N));
         }
@@ -1097,12 +1170,20 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             }
             if (e) break;
             e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
-            const double groups = static_cast<double>((n + 127) / 128 * 8);
-            if (tiles.n_quad_steps > 0) enqueued("quad_tiles", quad_step_flop * groups * static_cast<double>(h->tiled_quad_steps()));
-            else enqueued("tiles", step_flop * groups * static_cast<double>(h->step_rows.size()));
+            const int64_t columns = tiles.n_quad_steps > 0 ? smat::quad_shape_columns(tiles.quad_shape) : 128;
+            const double groups = static_cast<double>((n + columns - 1) / columns * (columns / 16));
+            if (tiles.n_quad_steps > 0) {
+                // (of a last super row with few block rows, the part that has tiles)
+                const int tile_rows = smat::quad_shape_rows(tiles.quad_shape) / 16;
+                const double tail = tiles.quad_tail_tiled ? (tiles.quad_tail_rows + tile_rows - 1) / tile_rows * tile_rows / 16.0 : 0.0;
+                enqueued("quad_tiles", quad_step_flop * groups * (static_cast<double>(h->tiled_quad_steps()) +
+                                                                  tail * static_cast<double>(h->quad_steps() - h->tiled_quad_steps())));
+            } else {
+                enqueued("tiles", step_flop * groups * static_cast<double>(h->step_rows.size()));
+            }
             if (smat::dense_split(tiles, n) > 1) enqueued("sum_tiles", 0);
         }
-        name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (h->dev_rest.n_order > 0 ? std::string("+") + variant : std::string());
+        name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (rest ? std::string("+") + variant : std::string());
         g_kernel = name.c_str();
     } else {
         const bool lines = (ldb * h->elem_bytes) % 128 == 0 && reinterpret_cast<uintptr_t>(dB) % 128 == 0;

@@ -68,7 +68,22 @@ struct DenseTiles {
     const uint8_t* quad_index = nullptr;   // [2 or 4 KiB * n_quad_steps] positions of the values
     int32_t n_quad_steps = 0, max_quad_steps = 0;      // all, and those of the longest super row
     int32_t quad_tail = 0;                 // 1: super row number n is there too (not as a tile, for launch_quad_rows), and then all block rows are
+    int32_t quad_tail_rows = 0;            // its block rows
+    // of a call
+    int quad_shape = 0;                    // QuadShape; only the first one's steps may be split over workgroups
+    bool quad_tail_tiled = false;          // the tiles cover super row number n too
 };
+
+// Rows and columns of a tile on quads.
+enum QuadShape { kQuad256x128 = 0, kQuad256x96, kQuad256x64, kQuad128x64, kQuad128x32, kQuadShapes };
+constexpr int quad_shape_rows(int shape) { return shape >= kQuad128x64 ? 128 : 256; }
+constexpr int quad_shape_columns(int shape) { return shape == kQuad256x128 ? 128 : shape == kQuad256x96 ? 96 : shape == kQuad128x32 ? 32 : 64; }
+// Tiles per slab of columns.  Of a last super row with few block rows those that have any.
+inline int64_t quad_row_tiles(const DenseTiles& t)
+{
+    const int rows = quad_shape_rows(t.quad_shape);
+    return static_cast<int64_t>(t.n) * (256 / rows) + (t.quad_tail_tiled ? (t.quad_tail_rows + rows / 16 - 1) / (rows / 16) : 0);
+}
 
 constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave groups share a tile
 

@@ -378,7 +378,7 @@ void spmm_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t
         if constexpr (ES == 1) asm volatile("s_nop 15\n\ts_nop 15");
     }
 
-    finish_tile<DT, KG>(acc, out_rows, lds_words, kg, wave, lane, super, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
+    finish_tile<DT, KG>(acc, out_rows, lds_words, kg, wave, lane, super, RM * wave, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
 }
 
 template <int DT, int KG>
@@ -580,10 +580,14 @@ int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem
 int dense_split(const DenseTiles& t, int64_t N)
 {
     const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
-    if (tiles <= 0 || tiles > 128 || t.scratch == nullptr) return 1;
+    if (tiles <= 0 || tiles > 128 || t.scratch == nullptr || t.quad_shape != kQuad256x128 || t.quad_tail_tiled) return 1;
     int64_t ks = std::min<int64_t>(8, 256 / tiles);
     ks = std::min<int64_t>(ks, static_cast<int64_t>(t.mean_steps / 8.0));
     ks = std::min<int64_t>(ks, static_cast<int64_t>(t.scratch_bytes / (static_cast<size_t>(tiles) * 256 * 128 * 4)));
+    // An XCD has an eighth of the tiles, rounded up, and 32 compute units: one workgroup more and the launch takes two rounds (81 tiles
+    // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps leave room for two workgroups.
+    if (t.mean_steps >= kDeepSteps)
+        while (ks > 1 && (tiles + 7) / 8 * ks > 32) --ks;
     return ks < 2 ? 1 : static_cast<int>(ks);
 }
 
@@ -596,10 +600,12 @@ static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const vo
     const int vec_store = (ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 && N % 4 == 0) ? 1 : 0;
     // long super rows: two wave groups per workgroup; short ones: one group, two workgroups per CU
     const bool deep = t.mean_steps >= kDeepSteps;
+    const int shape = t.n_quad_steps > 0 ? t.quad_shape : kQuad256x128;
     const int ks = dense_split(t, N);
     static thread_local char name[40];
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
-    if (ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d", type, deep ? 2 : 1, ks);
+    if (shape != kQuad256x128) snprintf(name, sizeof(name), "spmm_dense_%s_g2_%dx%d", type, quad_shape_rows(shape), quad_shape_columns(shape));
+    else if (ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d", type, deep ? 2 : 1, ks);
     else snprintf(name, sizeof(name), "spmm_dense_%s_g%d", type, deep ? 2 : 1);
     *variant = name;
     if (t.n_quad_steps > 0) launch_quad_tiles(d, t, DT, ks, B, ldb, C, ldc, N, s);

@@ -16,11 +16,21 @@
 // matrix, and reads the panel with the same transposing reads; the loads of two steps are in flight, spread
 // between the matrix instructions.
 //
-// What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  The 8-bit
+// Tiles of 256 x 96, 256 x 64, 128 x 64 and 128 x 32 (NT groups of sixteen columns, RM block rows per wave; api.cpp chooses) are for products
+// of which 256 x 128 gives the 256 compute units too few, or just more than they hold at a time.  They bring in more bytes per flop (34 KiB
+// a step for 256 x 128 in 16-bit types, 13 for an eighth of that) but use the whole chip; before, the steps of few tiles were split over up
+// to eight workgroups, whose partial tiles cost 7-14 us.  us, split and now: 3762 x 3966 at 10 % in fp16, N = 256 / 512 / 1024
+// 22.4 / 24.7 / 31.5 -> 16.9 / 20.2 / 26.2; 6000 x 4096 in e4m3, N = 128 / 256 / 512 22.1 / 23.6 / 27.0 -> 9.9 / 12.3 / 19.4; 7286 x 2652 at 20 %
+// in int8, N = 256 / 512 21.9 / 24.5 -> 10.4 / 15.9.  Also built: 112 and 80 columns, 128 x 128, 128 x 96 (within 1 % of the best of these on 400
+// products), and a deeper ring for the smallest, which is not bound by latency (10.9 -> 11.9 us).
+//
+// What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  (4096 x 4096
+// in bf16, N = 2048, with parts left out: all 42 us, no matrix instructions 35, loads alone 35, matrix instructions alone 27, neither 13.)  The 8-bit
 // floats: the matrix units, which take 64 instructions of 16 clocks per step and wave (10 % fill: 6000 x 4096, N = 784
 // e4m3 29 us and e5m2 36, against 25 with half as many; 8192 x 8192, N = 2048 111 and 126, against 149 in the other form).
 #include <cstdio>
 #include <type_traits>
+#include <utility>
 
 #include <hip/hip_runtime.h>
 
@@ -88,6 +98,9 @@ __device__ __forceinline__ void lds_four_done(u32x2_t (&v)[4])
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]) : "n"(YOUNGER));
 }
 
+template <int... U, typename F>
+__device__ __forceinline__ void with_constants(std::integer_sequence<int, U...>, F&& f) { f(std::integral_constant<int, U>{}...); }
+
 // What the kernel needs later than its first loads.
 struct QuadTables {
     const uint8_t* index;
@@ -96,36 +109,46 @@ struct QuadTables {
     int no_step;                       // number of the step that names no row of B
 };
 
-template <int DT>
+template <int DT, int NT, int RM>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(2, 2)))
-void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const int32_t* __restrict__ super_rows,
+__attribute__((amdgpu_waves_per_eu(RM == 2 && NT <= 4 ? 4 : 2, RM == 2 && NT <= 4 ? 4 : 2)))
+void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, const int32_t* __restrict__ super_rows,
                            const int32_t* __restrict__ step_ptr, const void* __restrict__ B, const int32_t* __restrict__ quad_rows,
                            uint32_t ldb_bytes, uint32_t K, const void* __restrict__ tile_vals, QuadTables tab,
                            typename Elem<DT>::Out* __restrict__ C, int64_t ldc)
 {
     using Acc = typename Elem<DT>::Acc;
     constexpr int ES = Elem<DT>::ES;
-    constexpr int NT = 8;                          // groups of 16 columns: 128 columns per tile
-    constexpr int RM = 4;                          // block rows per wave
+    // a tile: 16 NT columns of NP block rows, four waves of RM each
+    constexpr int NP = 4 * RM, PARTS = 16 / NP;    // tiles per super row and slab
+    static_assert(NT % 2 == 0, "operands of groups of columns take turns in two sets of registers, also across steps");
+    constexpr int PW = NT > 4 ? 8 : NT > 2 ? 4 : 2;        // groups of 16 columns that a panel has room for
+    constexpr int PL = PW / 2;                     // loads of a wave per panel
     constexpr int RD = 3;                          // ring depth: panels in LDS, values and tables in registers
+    constexpr int AHEAD = RD - 1;                  // steps that loads are ahead of the matrix instructions
     constexpr int KG = 2;                          // groups of four waves
-    constexpr uint32_t kPanel = 16384;             // 64 rows of 256 bytes, or 128 rows of 128
+    constexpr uint32_t kRow = 16u * PW * ES;       // bytes of a panel row
+    constexpr uint32_t kPanel = quad_columns(ES) * kRow;
     constexpr uint32_t kTable = quad_columns(ES) * 4u;
-    constexpr int IB = ES == 2 ? 8 : 16;           // bytes of positions per lane and step (four block rows)
-    constexpr int ID = IB / 4;
-    // two rings of panels (96 KiB); the hand-over at the end needs 128 KiB
-    __shared__ u32x4 lds_words[8192];
+    constexpr int IB = ES == 2 ? 8 : 16;           // bytes of positions per lane and step of four block rows
+    constexpr int ID = IB * RM / 16;               // dwords of them for this wave
+    constexpr int LOADS = PL + RM + 2;             // loads of a wave per step: panel, values, positions, table
+    // two rings of panels; the hand-over at the end
+    constexpr uint32_t kRings = 2 * RD * kPanel, kHandover = 4096u * RM * NT;
+    __shared__ u32x4 lds_words[(kRings > kHandover ? kRings : kHandover) / 16];
 
     int sidx, slab;
-    if (!tile_of_workgroup(n_super, n_slab, per_xcd, sidx, slab)) return;
+    if (!tile_of_workgroup(n_row_tiles, n_slab, per_xcd, sidx, slab)) return;
+    const int part = sidx % PARTS;
+    sidx /= PARTS;
     const int tid = threadIdx.x & 255;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 8);
     const int i = lane & 15, g = lane >> 4;
     const int super = super_rows[sidx];
-    const int n0 = slab * 128;
+    const int n0 = slab * (16 * NT);
+    const int j0 = NP * part + RM * wave;          // first block row of this wave in the super row
     const int ks = static_cast<int>(gridDim.z);
     const int q_first = step_ptr[sidx], q_last = step_ptr[sidx + 1];
     const int per = (q_last - q_first + ks - 1) / ks;
@@ -143,53 +166,85 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
     const __amdgpu_buffer_rsrc_t ix_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(tab.index) + static_cast<size_t>(q0) * (256 * IB), 0, max(nq, 0) * (256 * IB), kRsrcFlags);
 
-    // The panel lies in LDS as in the other kernel (see there for the placement of the pieces), with twice the rows.  Load e of a wave
-    // (e < 4) brings panel rows 16 e + 4 wave + lane / 16 (8-bit types: 32 wave + 8 e + lane / 8), lane l the piece l % 16 (l % 8).
-    uint32_t st_off[2];
+    // The panel.  A load brings kLoadRows rows, lane l the piece l % kPieces of 16 bytes of row l / kPieces among them, and lays them into LDS
+    // back to back.  Which rows those are: word x of the step's table is load x % 4 of unit x / 4 (quad_panel_row); a wave has kUnits of
+    // the units, o = lane / kPieces is the row among the load's, and load e of a wave
+    //   PW = 8: unit o % kUnits, word e;   PW = 4: word 2 (o / kUnits) + e;   PW = 2: word o / kUnits
+    // i.e. the row with unit U = kUnits w + v and word L lies in place ((PL w + e) kLoadRows + o) of the panel.
+    constexpr uint32_t kPieces = kRow / 16u;
+    constexpr int kLoadRows = 64 / static_cast<int>(kPieces);
+    constexpr int kUnits = quad_columns(ES) / 16;  // 4 or 8
+    const int row_in_load = lane / static_cast<int>(kPieces), unit = kUnits * wave + row_in_load % kUnits;
+    // Pieces of a row are placed so that the 32 lanes that LDS serves at a time (rows of two lane groups, 32 or 16 bytes of each) meet
+    // every bank once: piece p of a panel row lies at p ^ swizzle.
+    //   16-bit types, lane group g and row e = 0 .. 3 of it:  PW = 8: 2 (e ^ 4 (g % 2))   4: 2 (e / 2 + 2 (g % 2))   2: 2 (g % 2)
+    //   8-bit types, e = 0 .. 7:                              PW = 8: e / 2 + 4 (g % 2)   4: e / 4 + 2 (g % 2)       2: g % 2
+    auto swizzle = [](int g_, int e_) {
+        if constexpr (ES == 2) return PW == 8 ? 2 * (e_ ^ (4 * (g_ & 1))) : PW == 4 ? 2 * ((e_ >> 1) + 2 * (g_ & 1)) : 2 * (g_ & 1);
+        else return PW == 8 ? (e_ >> 1) + 4 * (g_ & 1) : PW == 4 ? (e_ >> 2) + 2 * (g_ & 1) : g_ & 1;
+    };
+    // byte offset inside a row of B of what this lane fetches with load e
+    uint32_t st_off[PL];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int piece = ES == 2 ? (lane & 15) ^ (2 * ((lane >> 4) & 3)) ^ (8 * ((wave >> 1) & 1)) : (lane & 7) ^ (4 * e + (lane >> 4));
+    for (int e = 0; e < PL; ++e) {
+        const int word = PW == 8 ? e : PW == 4 ? 2 * (row_in_load / kUnits) + e : row_in_load / kUnits;
+        const int row = quad_panel_row(ES, 4 * unit + word);
+        const int piece = (lane & static_cast<int>(kPieces - 1u)) ^ swizzle((row >> 3) & 3, ES == 2 ? row & 3 : row & 7);
         const int col = n0 + (16 / ES) * piece;
-        st_off[e] = col < N ? static_cast<uint32_t>(col) * ES : kOutOfRange;
+        st_off[e] = col < N && (16 / ES) * piece < 16 * NT ? static_cast<uint32_t>(col) * ES : kOutOfRange;
     }
     const uint32_t panels = lds_offset_of(lds_words) + static_cast<uint32_t>(kg) * (RD * kPanel);
-    auto lds_of_load = [&](int buf, int e) {
-        return panels + static_cast<uint32_t>(buf) * kPanel + (ES == 2 ? 4096u * e + 1024u * wave : 4096u * wave + 1024u * e);
-    };
-    // reads: 16-bit types two per 32 rows (+ 1024 bytes), twice (+ 8192); 8-bit types one per 32 rows (+ 4096)
+    auto lds_of_load = [&](int buf, int e) { return panels + static_cast<uint32_t>(buf) * kPanel + 1024u * (PW == 8 && ES == 2 ? 4 * e + wave : PL * wave + e); };
+    // Reads of group of columns x: 16-bit types rows 8 g + e + {0, 4, 32, 36}, 8-bit types rows 8 g + e + {0, 32, 64, 96}, from the
+    // first of them kRead1 and kRead2 (and both) bytes on, or one to three times kRead1.
+    constexpr uint32_t kRead1 = ES == 2 ? (PW == 8 ? 1024u : PW == 4 ? 2048u : 1024u) : 1024u * PL;
+    constexpr uint32_t kRead2 = ES == 2 ? (PW == 8 ? 8192u : 512u) : 2048u * PL;
     uint32_t tr_addr[NT];
+    {
+        const int e = ES == 2 ? i >> 2 : i >> 1;
+        const uint32_t place = ES == 2 ? (PW == 8 ? 8 * g + e : PW == 4 ? 32 * (g & 1) + 8 * (g >> 1) + e : 32 * (g & 1) + 4 * (g >> 1) + e)
+                                       : (PW == 8 ? 8 * g + e : PW == 4 ? 16 * (g & 1) + 8 * (g >> 1) + e : 8 * g + e);
 #pragma unroll
-    for (int x = 0; x < NT; ++x) {
-        if constexpr (ES == 2) {
-            const int e = i >> 2, qq = i & 3;
-            tr_addr[x] = panels + (8 * g + e) * 256u + 32u * (x ^ e ^ (4 * (g & 1))) + 16u * (qq >> 1) + 8u * (qq & 1);
-        } else {
-            const int e = i >> 1, qq = i & 1;
-            tr_addr[x] = panels + (8 * g + e) * 128u + 16u * (x ^ (4 * (g & 1) + (e >> 1))) + 8u * qq;
-        }
+        for (int x = 0; x < NT; ++x)
+            tr_addr[x] = panels + place * kRow + (ES == 2 ? 16u * ((2 * x) ^ swizzle(g, e)) + 8u * (i & 3) : 16u * (x ^ swizzle(g, e)) + 8u * (i & 1));
     }
 
     // Loads of step gs of this wave group = step kg + 2 gs of the tile.  A step past the end reads values out of range (zeros) and
     // the rows of no_step, whose panel is zeros.
     auto is_live = [&](int gs) { return kg + KG * gs < nq; };
     auto step_of = [&](int gs) { return static_cast<uint32_t>(is_live(gs) ? kg + KG * gs : 0); };
-    const uint32_t table_lane = ES == 2 ? (4u * wave + (lane >> 4)) * 16u : (8u * wave + (lane >> 3)) * 16u;
+    const uint32_t table_lane = static_cast<uint32_t>(unit) * 16u + (PW == 4 ? 8u : 4u) * (row_in_load / kUnits);
     // which rows of B the lane fetches for step gs, one per load
+    struct Rows { uint32_t of[PL]; };
     auto load_table = [&](int gs) {
         const uint32_t q = static_cast<uint32_t>(is_live(gs) ? q0 + kg + KG * gs : tab.no_step);
-        return buf_load16(rows_rsrc, table_lane, q * kTable);
+        Rows rows;
+        if constexpr (PL == 4) {
+            const u32x4 v = buf_load16(rows_rsrc, table_lane, q * kTable);
+#pragma unroll
+            for (int e = 0; e < PL; ++e) rows.of[e] = v[e];
+        } else if constexpr (PL == 2) {
+            const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rows_rsrc, table_lane, q * kTable, 0);
+#pragma unroll
+            for (int e = 0; e < PL; ++e) rows.of[e] = static_cast<uint32_t>(v[e]);
+        } else {
+            rows.of[0] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(rows_rsrc, table_lane, q * kTable, 0));
+        }
+        return rows;
     };
-    auto load_panel = [&](const u32x4& rows, int buf, int e) {
-        load_to_lds16((lds_void*)(uintptr_t)lds_of_load(buf, e), b_rsrc, __umul24(rows[e], ldb_bytes) + st_off[ES == 2 ? 0 : e & 1], 0u);
+    auto load_panel = [&](const Rows& rows, int buf, int e) {
+        load_to_lds16((lds_void*)(uintptr_t)lds_of_load(buf, e), b_rsrc, __umul24(rows.of[e], ldb_bytes) + st_off[e], 0u);
     };
     auto load_a = [&](int gs, int r) {
         const uint32_t voff = static_cast<uint32_t>(lane) * 16u | (is_live(gs) ? 0u : kOutOfRange);
-        return buf_load16(a_rsrc, voff, step_of(gs) * 16384u + static_cast<uint32_t>(RM * wave + r) * 1024u);
+        return buf_load16(a_rsrc, voff, step_of(gs) * 16384u + static_cast<uint32_t>(j0 + r) * 1024u);
     };
     auto load_index = [&](int gs, uint32_t (&ix)[ID]) {
-        const uint32_t voff = static_cast<uint32_t>(lane) * IB | (is_live(gs) ? 0u : kOutOfRange);
-        const uint32_t soff = step_of(gs) * (256u * IB) + static_cast<uint32_t>(wave) * (64u * IB);
-        if constexpr (ES == 2) {
+        const uint32_t voff = (static_cast<uint32_t>(lane) * IB + static_cast<uint32_t>(j0 & 3) * (IB / 4)) | (is_live(gs) ? 0u : kOutOfRange);
+        const uint32_t soff = step_of(gs) * (256u * IB) + static_cast<uint32_t>(j0 >> 2) * (64u * IB);
+        if constexpr (ID == 1) {
+            ix[0] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(ix_rsrc, voff, soff, 0));
+        } else if constexpr (ID == 2) {
             const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(ix_rsrc, voff, soff, 0);
             ix[0] = static_cast<uint32_t>(v[0]);
             ix[1] = static_cast<uint32_t>(v[1]);
@@ -207,21 +262,22 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
         for (int x = 0; x < NT; ++x) acc[r][x] = Acc{0, 0, 0, 0};
 
     if (nq > 0) {
-        u32x4 a[RD][RM], table[RD];
+        u32x4 a[RD][RM];
+        Rows table[RD];
         uint32_t ix[RD][ID];
-        table[0] = load_table(0);
-        table[1] = load_table(1);
+#pragma unroll
+        for (int h = 0; h < AHEAD; ++h) table[h] = load_table(h);
         __builtin_amdgcn_sched_barrier(0);
         // what the loop would have issued before step 0, in its order
 #pragma unroll
-        for (int h = 0; h < RD - 1; ++h) {
+        for (int h = 0; h < AHEAD; ++h) {
             // (what does not depend on the table first)
 #pragma unroll
             for (int r = 0; r < RM; ++r) a[h][r] = load_a(h, r);
             load_index(h, ix[h]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) load_panel(table[h], h, e);
-            table[(h + 2) % RD] = load_table(h + 2);
+            for (int e = 0; e < PL; ++e) load_panel(table[h], h, e);
+            table[(h + AHEAD) % RD] = load_table(h + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
         }
         const int gsteps = (nq + KG - 1) / KG;
@@ -229,25 +285,25 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
         // Step s of the group, s = u (mod RD).  Its panel is known to be there, and the operand of its first group of columns has been asked
         // for, when it begins: what the step waits for lies before the matrix instructions of its last group, so that
         // these, and not an idle matrix unit, cover the first reads of the panel of step s + 1.
-        // table[(u + 2) % RD] names the rows of step s + 2; the table of step s + 4 takes the place of step s + 1's.
-        u32x2_t b[2][4];
+        // Loads of step s + AHEAD: from table[(s + AHEAD) % RD]; the table of step s + 2 AHEAD takes the place of one that has been used.
+        u32x2_t b[2][4];                           // operands of the groups of columns, in turn
         auto read_four = [&](auto u_, int x, u32x2_t (&v)[4]) {
             constexpr int u = decltype(u_)::value;
             if constexpr (ES == 2) {
                 v[0] = lds_read_tr<kPanel * u>(tr_addr[x]);
-                v[1] = lds_read_tr<kPanel * u + 1024>(tr_addr[x]);
-                v[2] = lds_read_tr<kPanel * u + 8192>(tr_addr[x]);
-                v[3] = lds_read_tr<kPanel * u + 8192 + 1024>(tr_addr[x]);
+                v[1] = lds_read_tr<kPanel * u + kRead1>(tr_addr[x]);
+                v[2] = lds_read_tr<kPanel * u + kRead2>(tr_addr[x]);
+                v[3] = lds_read_tr<kPanel * u + kRead2 + kRead1>(tr_addr[x]);
             } else {
                 v[0] = lds_read_tr8<kPanel * u>(tr_addr[x]);
-                v[1] = lds_read_tr8<kPanel * u + 4096>(tr_addr[x]);
-                v[2] = lds_read_tr8<kPanel * u + 8192>(tr_addr[x]);
-                v[3] = lds_read_tr8<kPanel * u + 8192 + 4096>(tr_addr[x]);
+                v[1] = lds_read_tr8<kPanel * u + kRead1>(tr_addr[x]);
+                v[2] = lds_read_tr8<kPanel * u + kRead2>(tr_addr[x]);
+                v[3] = lds_read_tr8<kPanel * u + kRead2 + kRead1>(tr_addr[x]);
             }
         };
-        auto step = [&](auto u_, int s) {
+        auto step = [&](auto u_, int s) __attribute__((always_inline)) {
             constexpr int u = decltype(u_)::value;
-            constexpr int next = (u + 2) % RD;
+            constexpr int next = (u + AHEAD) % RD;
             u32x4 wide[2][RM];                     // e5m2: the values as f16, those of the step's first 64 k slots and of the others
             if constexpr (kAsF16<DT>) {
 #pragma unroll
@@ -269,21 +325,23 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
                     read_four(u_, x + 1, b[(x + 1) & 1]);
                     lds_four_done<4>(b[x & 1]);
                 } else {
-                    // This wave's reads of the panel have returned, and all of its loads but the youngest ten: the panel, values and
+                    // This wave's reads of the panel have returned, and all of its loads but the youngest
+                    // (AHEAD - 1) LOADS: the panel, values and
                     // positions of step s + 1 are there, and the table that the loads after the barrier are made from.
                     lds_four_done<0>(b[x & 1]);
-                    asm volatile("s_waitcnt vmcnt(10)");
+                    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((AHEAD - 1) * LOADS));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
-                    read_four(std::integral_constant<int, (u + 1) % RD>{}, 0, b[(x + 1) & 1]);
+                    read_four(std::integral_constant<int, (u + 1) % RD>{}, 0, b[0]);
                 }
                 const u32x2_t(&v)[4] = b[x & 1];
                 const u32x8 operand = u32x8{v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], v[3][0], v[3][1]};
                 if constexpr (ES == 2) {
-                    acc[0][x] = smfmac<DT, 0>(a[u][0], operand, acc[0][x], ix[u][0]);
-                    acc[1][x] = smfmac<DT, 1>(a[u][1], operand, acc[1][x], ix[u][0]);
-                    acc[2][x] = smfmac<DT, 0>(a[u][2], operand, acc[2][x], ix[u][1]);
-                    acc[3][x] = smfmac<DT, 1>(a[u][3], operand, acc[3][x], ix[u][1]);
+#pragma unroll
+                    for (int r = 0; r < RM; r += 2) {
+                        acc[r][x] = smfmac<DT, 0>(a[u][r], operand, acc[r][x], ix[u][r / 2]);
+                        acc[r + 1][x] = smfmac<DT, 1>(a[u][r + 1], operand, acc[r + 1][x], ix[u][r / 2]);
+                    }
                 } else if constexpr (kAsF16<DT>) {
                     const u32x8 lower = widened_operand(v[0], v[1]);
 #pragma unroll
@@ -300,56 +358,63 @@ void spmm_quad_tile_kernel(int n_super, int n_slab, int per_xcd, int N, const in
                     for (int r = 0; r < RM; ++r) acc[r][x] = smfmac<DT, 0>(a[u][r], operand, acc[r][x], ix[u][r]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                // one set of ten loads per barrier: x = 7 opens the set of step s + 3, whose panel takes this step's place
-                if (x == 7) {
+                // One set of LOADS loads per barrier: the last group of columns opens the set of step s + RD, whose panel takes this step's
+                // place, and the others share what is left of that of step s + AHEAD.
+                if (x == NT - 1) {
                     load_panel(table[u], u, 0);
-                } else if (x < 3) {
-                    load_panel(table[next], next, x + 1);
-                } else if (x == 3) {
-                    a[next][0] = load_a(s + 2, 0);
-                } else if (x == 4) {
-                    a[next][1] = load_a(s + 2, 1);
-                    a[next][2] = load_a(s + 2, 2);
-                } else if (x == 5) {
-                    a[next][3] = load_a(s + 2, 3);
-                    load_index(s + 2, ix[next]);
                 } else {
-                    table[(u + 1) % RD] = load_table(s + 4);
+#pragma unroll
+                    for (int load = 1 + x * (LOADS - 1) / (NT - 1); load < 1 + (x + 1) * (LOADS - 1) / (NT - 1); ++load) {
+                        if (load < PL) load_panel(table[next], next, load);
+                        else if (load < PL + RM) a[next][load - PL] = load_a(s + AHEAD, load - PL);
+                        else if (load == PL + RM) load_index(s + AHEAD, ix[next]);
+                        else table[(u + 2 * AHEAD) % RD] = load_table(s + 2 * AHEAD);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        static_assert(RD == 3, "the loop body names its three steps");
-        asm volatile("s_waitcnt vmcnt(10)");
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"((AHEAD - 1) * LOADS));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         read_four(std::integral_constant<int, 0>{}, 0, b[0]);
-        load_panel(table[2], 2, 0);
+        load_panel(table[AHEAD], AHEAD, 0);
         __builtin_amdgcn_sched_barrier(0);
-        for (int it = 0; it < iters; ++it) {
-            step(std::integral_constant<int, 0>{}, RD * it);
-            step(std::integral_constant<int, 1>{}, RD * it + 1);
-            step(std::integral_constant<int, 2>{}, RD * it + 2);
-        }
-        if (rem >= 1) step(std::integral_constant<int, 0>{}, RD * iters);
-        if (rem >= 2) step(std::integral_constant<int, 1>{}, RD * iters + 1);
+        // the first `count` of steps s, s + 1, ..., s = 0 (mod RD)
+        auto several = [&](int s, int count, auto... u) __attribute__((always_inline)) { (void)((decltype(u)::value < count && (step(u, s + decltype(u)::value), true)) && ...); };
+        for (int it = 0; it < iters; ++it) with_constants(std::make_integer_sequence<int, RD>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * it, RD, u...); });
+        with_constants(std::make_integer_sequence<int, RD - 1>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * iters, rem, u...); });
         // nothing may still be on its way into LDS when the buffers get another use or the workgroup ends
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)");
     }
     int32_t out_rows[RM][4] = {};
-    finish_tile<DT, KG>(acc, out_rows, lds_words, kg, wave, lane, super, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
+    finish_tile<DT, KG, RM, NT>(acc, out_rows, lds_words, kg, wave, lane, super, j0, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
+}
+
+template <int DT, int NT, int RM>
+static void launch_quad_shape(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
+                              int64_t N, hipStream_t s)
+{
+    const int n_row_tiles = static_cast<int>(quad_row_tiles(t)), n_slab = static_cast<int>((N + 16 * NT - 1) / (16 * NT));
+    const int per_xcd = (n_row_tiles * n_slab + 7) / 8;
+    const dim3 grid(static_cast<unsigned>(8 * per_xcd), 1, static_cast<unsigned>(ks));
+    const QuadTables tab{t.quad_index, d.perm, t.scratch, t.n_quad_steps};
+    hipLaunchKernelGGL((spmm_quad_tile_kernel<DT, NT, RM>), grid, dim3(512), 0, s, n_row_tiles, n_slab, per_xcd, static_cast<int>(N), t.super_rows,
+                       t.step_ptr, B, t.quad_rows, static_cast<uint32_t>(ldb * Elem<DT>::ES), static_cast<uint32_t>(d.K), t.vals, tab,
+                       static_cast<typename Elem<DT>::Out*>(C), ldc);
 }
 
 template <int DT>
 static void launch_quad_dtype(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
                               int64_t N, hipStream_t s)
 {
-    const int n_super = t.n, n_slab = static_cast<int>((N + 127) / 128), per_xcd = (n_super * n_slab + 7) / 8;
-    const dim3 grid(static_cast<unsigned>(8 * per_xcd), 1, static_cast<unsigned>(ks));
-    const QuadTables tab{t.quad_index, d.perm, t.scratch, t.n_quad_steps};
-    hipLaunchKernelGGL((spmm_quad_tile_kernel<DT>), grid, dim3(512), 0, s, n_super, n_slab, per_xcd, static_cast<int>(N), t.super_rows,
-                       t.step_ptr, B, t.quad_rows, static_cast<uint32_t>(ldb * Elem<DT>::ES), static_cast<uint32_t>(d.K), t.vals, tab,
-                       static_cast<typename Elem<DT>::Out*>(C), ldc);
+    switch (t.quad_shape) {
+    case kQuad256x96: return launch_quad_shape<DT, 6, 4>(d, t, 1, B, ldb, C, ldc, N, s);
+    case kQuad256x64: return launch_quad_shape<DT, 4, 4>(d, t, 1, B, ldb, C, ldc, N, s);
+    case kQuad128x64: return launch_quad_shape<DT, 4, 2>(d, t, 1, B, ldb, C, ldc, N, s);
+    case kQuad128x32: return launch_quad_shape<DT, 2, 2>(d, t, 1, B, ldb, C, ldc, N, s);
+    default: return launch_quad_shape<DT, 8, 4>(d, t, ks, B, ldb, C, ldc, N, s);
+    }
 }
 
 void launch_quad_tiles(const DeviceBcsr& d, const DenseTiles& t, int dtype, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,

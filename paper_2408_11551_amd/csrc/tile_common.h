@@ -90,18 +90,17 @@ __device__ __forceinline__ void lds_pair_done(u32x2_t& lo, u32x2_t& hi)
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(YOUNGER));
 }
 
-// The end of a tile: acc[r][x][y] = C'[16 * (16 super + 4 wave + r) + 4g + y][128 slab + 16x + i] of this wave (and, with two
-// groups, the same of the other group's steps).  With ks > 1 workgroups per tile the partial tile goes to the scratch area.
-// lds_words: 128 KiB with two groups, not used with one.  out_rows: read here with two groups, by the caller with one.
-template <int DT, int KG>
-__device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_in)[4][8], const int32_t (&out_rows_in)[4][4], u32x4* lds_words, int kg,
-                                            int wave, int lane, int super, int sidx, int slab, int n_slab, int ks,
+// The end of a tile of 16 NT columns: acc[r][x][y] = C'[16 * (16 super + first_row + r) + 4g + y][16 (NT slab + x) + i] of this wave (and, with two
+// groups, the same of the other group's steps).  With ks > 1 workgroups per tile (256 x 128) the partial tile goes to the scratch area.
+// lds_words: 4 RM NT KiB with two groups, not used with one.  out_rows: read here with two groups, by the caller with one.
+template <int DT, int KG, int RM = 4, int NT = 8>
+__device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_in)[RM][NT], const int32_t (&out_rows_in)[RM][4], u32x4* lds_words, int kg,
+                                            int wave, int lane, int super, int first_row, int sidx, int slab, int n_slab, int ks,
                                             const int32_t* __restrict__ perm, void* scratch, typename Elem<DT>::Out* __restrict__ C,
                                             int64_t ldc, int N)
 {
     using Out = typename Elem<DT>::Out;
-    constexpr int NT = 8, RM = 4;
-    const int i = lane & 15, g = lane >> 4, n0 = slab * 128;
+    const int i = lane & 15, g = lane >> 4, n0 = slab * (16 * NT);
     // (copies of the function's own: through the reference the compiler picks between two accumulators by their addresses,
     // and then keeps all of them in memory)
     typename Elem<DT>::Acc acc[RM][NT];
@@ -115,38 +114,38 @@ __device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_i
     }
     // Where the lane's rows of C' go.  One group per workgroup: already asked for before the loop (the registers are
     // there, and the stores then begin without one more trip to memory -- which a short tile on cold caches feels).
-    // Two groups: asked for when the loop ends, ahead of the hand-over, which hides the trip; a lane then stores two
-    // of its four block rows (group 0 the first two, group 1 the others).  (The empty statement makes the super
+    // Two groups: asked for when the loop ends, ahead of the hand-over, which hides the trip; a lane then stores half
+    // of its block rows (group 0 the first, group 1 the others).  (The empty statement makes the super
     // row's number a value the compiler knows only from here on, so that it cannot move these loads above the loop:
     // there the 8-bit instantiations once spilled registers inside it and ran 79 instead of 53 us.)
+    constexpr int HALF = RM / 2;
     if constexpr (KG == 2) {
         int super_now = super;
         asm volatile("" : "+s"(super_now));
         if (ks == 1) {
 #pragma unroll
             for (int r = 0; r < RM; ++r)
-                if ((r >> 1) == kg) {
+                if (r / HALF == kg) {
 #pragma unroll
                     for (int y = 0; y < 4; ++y)
-                        out_rows[r][y] = perm[(static_cast<int64_t>(super_now) * 16 + RM * wave + r) * 16 + 4 * g + y];
+                        out_rows[r][y] = perm[(static_cast<int64_t>(super_now) * 16 + first_row + r) * 16 + 4 * g + y];
                 }
         }
     }
-    // acc[r][x][y] = C'[16 * (16 super + 4 wave + r) + 4g + y][n0 + 16x + i]
     auto store_block_row = [&](int r) {
-        if (ks > 1) {
+        if (RM == 4 && NT == 8 && ks > 1) {
             // partial tile, row-major 256 x 128 words, at [(tile * ks + z)]
             const size_t tile_at = static_cast<size_t>(sidx) * n_slab + slab;
             Out* part = static_cast<Out*>(scratch) + (tile_at * ks + blockIdx.z) * (256 * 128);
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
-                Out* dst = part + (64 * wave + 16 * r + 4 * g + y) * 128 + i;
+                Out* dst = part + (16 * (first_row + r) + 4 * g + y) * 128 + i;
 #pragma unroll
                 for (int x = 0; x < NT; ++x) dst[16 * x] = acc[r][x][y];
             }
             return;
         }
-        // sixteen lanes store 64 consecutive bytes of a row of C; the eight groups of columns of a lane
+        // sixteen lanes store 64 consecutive bytes of a row of C; the groups of columns of a lane
         // lie 64 bytes apart.  (Turning the tile over through LDS first, to store 16 bytes per lane and whole
         // rows of 512 bytes, was slower: 63.0 against 62.0 us hot, 71.5 against 68.7 us on flushed caches.)
 #pragma unroll
@@ -160,38 +159,37 @@ __device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_i
         }
     };
     if constexpr (KG == 2) {
-        // The two groups hold partial sums of the same tile (even and odd steps).  Each hands two of its four block
-        // rows per wave to the other through LDS -- group 1 its first two, group 0 its last two, 64 KiB each way --
-        // and adds and stores the two it keeps: one barrier, and all eight waves store.
+        // The two groups hold partial sums of the same tile (even and odd steps).  Each hands half of its
+        // block rows per wave to the other through LDS -- group 1 its first ones, group 0 its last (RM = 4, NT = 8: 64 KiB each way) --
+        // and adds and stores those it keeps: one barrier, and all eight waves store.
+        constexpr int kWords = 4 * HALF * NT * 4 * 64;     // one way
         __syncthreads();
-        Out* handover = reinterpret_cast<Out*>(lds_words) + (kg == 0 ? 16384 : 0);      // where this group writes
-        const Out* incoming = reinterpret_cast<const Out*>(lds_words) + (kg == 0 ? 0 : 16384);
+        Out* handover = reinterpret_cast<Out*>(lds_words) + (kg == 0 ? kWords : 0);      // where this group writes
+        const Out* incoming = reinterpret_cast<const Out*>(lds_words) + (kg == 0 ? 0 : kWords);
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr)
+        for (int rr = 0; rr < HALF; ++rr)
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
                 for (int y = 0; y < 4; ++y) {
-                    const Out v = kg == 0 ? acc[2 + rr][x][y] : acc[rr][x][y];
-                    handover[(((wave * 2 + rr) * NT + x) * 4 + y) * 64 + lane] = v;
+                    const Out v = kg == 0 ? acc[HALF + rr][x][y] : acc[rr][x][y];
+                    handover[(((wave * HALF + rr) * NT + x) * 4 + y) * 64 + lane] = v;
                 }
         __syncthreads();
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr)
+        for (int rr = 0; rr < HALF; ++rr)
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
                 for (int y = 0; y < 4; ++y) {
-                    const Out v = incoming[(((wave * 2 + rr) * NT + x) * 4 + y) * 64 + lane];
+                    const Out v = incoming[(((wave * HALF + rr) * NT + x) * 4 + y) * 64 + lane];
                     if (kg == 0) acc[rr][x][y] += v;
-                    else acc[2 + rr][x][y] += v;
+                    else acc[HALF + rr][x][y] += v;
                 }
-        if (kg == 0) {
-            store_block_row(0);
-            store_block_row(1);
-        } else {
-            store_block_row(2);
-            store_block_row(3);
+#pragma unroll
+        for (int rr = 0; rr < HALF; ++rr) {
+            if (kg == 0) store_block_row(rr);
+            else store_block_row(HALF + rr);
         }
         return;
     }

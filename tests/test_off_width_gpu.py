@@ -98,6 +98,24 @@ def test_tile_kernel_on_quads(shape, dtype, oracle_c):
     assert ("tiles" if dtype == "e5m2" and density == 0.25 else "quad_tiles") in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
 
 
+# the smaller tiles on quads: last slabs of every width, B in place and copied, a last super row of two and of five block rows (one tile of 128
+# rows, or none below the first) and one of twelve, an odd number of steps, quads with gaps (20 %)
+@pytest.mark.parametrize("case", [(2330, 4110, 264, 0.1, "128x32"), (1100, 4100, 777, 0.1, "128x32"), (1100, 4100, 1040, 0.1, "128x64"), (1100, 4100, 1041, 0.2, ""),
+                                  (2330, 4110, 1040, 0.1, "256x64"), (3000, 2500, 777, 0.1, "256x64"), (2330, 4110, 2080, 0.1, "256x96"), (3000, 2500, 1601, 0.1, "256x96")],
+                         ids=lambda c: "x".join(map(str, c[:3])) + f"-{c[3]}")
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
+def test_smaller_tiles_on_quads(case, dtype, oracle_c):
+    M, K, N, density, shape = case
+    w = random_csr(M, K, N, density, seed=M + N, values="smallint", b_dist="smallint")
+    w = w if dtype == "f16" else recast(w, dtype)
+    name = _exact(w, oracle_c, N, N + 3, 0, dense_tiles=0)
+    # (these types take another kernel at that size)
+    others = {264: ("e4m3", "e5m2", "i8"), 2080: ("i8",), 1601: ("i8",)}
+    assert dtype in others.get(N, ()) or shape in name, name
+    # no launch of its own for the last block rows
+    assert dtype in others.get(N, ()) or "rows" not in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
 @pytest.mark.parametrize("N", [1, 4, 7, 8, 9, 16, 17, 32])
 def test_few_columns_on_quads(N, dtype, oracle_c):
