@@ -28,7 +28,8 @@ constexpr int kMaxAreas = 16;            // option concurrent_streams at most
 
 struct smat_handle {
     smat::Csr csr;
-    smat::Bcsr bcsr;
+    smat::Bcsr bcsr;                     // what the caller sees
+    const smat::Bcsr& layout() const { return bcsr.grouped ? *bcsr.grouped : bcsr; }      // what everything below is made from
     smat_dtype_t dtype = SMAT_F16;
     int elem_bytes = 2;                  // bytes per stored value of A and B: 2, or 1 for the 8-bit types
     int dense_mode = 0;                  // option dense_tiles
@@ -156,7 +157,7 @@ Layout make_layout(const smat_handle& h)
     Layout l{};
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
-    const size_t nbr = static_cast<size_t>(h.bcsr.nbr), n_e = static_cast<size_t>(h.bcsr.n_blocks);
+    const size_t nbr = static_cast<size_t>(h.bcsr.nbr), n_e = static_cast<size_t>(h.layout().n_blocks);
     const size_t nnz = h.csr.col_idx.size();
     // the tables, which are sent in one piece
     l.perm = take((nbr + 15) / 16 * 256 * sizeof(int32_t));          // whole super rows: the tile kernel reads a last one that is not complete
@@ -205,7 +206,7 @@ Layout make_layout(const smat_handle& h)
 // With the option dense_tiles = -1 nothing qualifies.
 void plan_dense_tiles(smat_handle& h, smat::Workers& workers)
 {
-    const smat::Bcsr& b = h.bcsr;
+    const smat::Bcsr& b = h.layout();
     const int64_t nbr = b.nbr;
     h.row_dense.assign(static_cast<size_t>(nbr), 0);
     h.step_ptr.assign(1, 0);
@@ -278,7 +279,7 @@ int64_t block_row_nnz(const smat_handle& h, size_t br)
 {
     int64_t nnz = 0;
     for (int64_t i = static_cast<int64_t>(br) * 16; i < static_cast<int64_t>(br) * 16 + 16 && i < h.csr.M; ++i) {
-        const size_t r = static_cast<size_t>(h.bcsr.perm[static_cast<size_t>(i)]);
+        const size_t r = static_cast<size_t>(h.layout().perm[static_cast<size_t>(i)]);
         nnz += h.csr.row_ptr[r + 1] - h.csr.row_ptr[r];
     }
     return nnz;
@@ -322,7 +323,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
             std::fill(mask.begin(), mask.end(), Rows{{0, 0, 0, 0}});
             const int64_t first = static_cast<int64_t>(supers[static_cast<size_t>(x)]) * 256;
             for (int64_t i = first; i < std::min<int64_t>(h.csr.M, first + 256); ++i) {
-                const size_t r = static_cast<size_t>(h.bcsr.perm[static_cast<size_t>(i)]);
+                const size_t r = static_cast<size_t>(h.layout().perm[static_cast<size_t>(i)]);
                 for (int64_t p = h.csr.row_ptr[r]; p < h.csr.row_ptr[r + 1]; ++p)
                     mask[static_cast<size_t>(h.csr.col_idx[static_cast<size_t>(p)])].w[(i - first) >> 6] |= uint64_t{1} << ((i - first) & 63);
             }
@@ -393,7 +394,7 @@ void entry_order(const smat_handle& h, size_t br, std::vector<uint64_t>& items)
 {
     items.clear();
     for (size_t rr = 0; rr < 16 && br * 16 + rr < static_cast<size_t>(h.csr.M); ++rr) {
-        const size_t r = static_cast<size_t>(h.bcsr.perm[br * 16 + rr]);
+        const size_t r = static_cast<size_t>(h.layout().perm[br * 16 + rr]);
         for (int64_t p = h.csr.row_ptr[r]; p < h.csr.row_ptr[r + 1]; ++p)
             items.push_back(static_cast<uint64_t>(h.csr.col_idx[static_cast<size_t>(p)]) << 4 | static_cast<uint64_t>(rr));
     }
@@ -403,7 +404,7 @@ void entry_order(const smat_handle& h, size_t br, std::vector<uint64_t>& items)
 // Cuts every block row into packs and derives the row classes (pack_layout.h).
 void plan_packs(smat_handle& h, smat::Workers& workers)
 {
-    const smat::Bcsr& b = h.bcsr;
+    const smat::Bcsr& b = h.layout();
     const size_t nbr = static_cast<size_t>(b.nbr), n_e = b.col_idx.size();
     h.pack_ptr.assign(nbr + 1, 0);
     h.blk_pack.resize(n_e);
@@ -508,9 +509,10 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
 // Launch statistics over a subset of block rows.
 void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
 {
+    const smat::Bcsr& b = h.layout();
     int64_t longest = 0, packs = 0, rows = 0, bytes = 0, b_rows = 0, reach = 0;
     int cls = 0;
-    for (int64_t br = 0; br < h.bcsr.nbr; ++br) {
+    for (int64_t br = 0; br < b.nbr; ++br) {
         if (skip_dense && h.row_dense[static_cast<size_t>(br)]) continue;
         const int64_t len = h.pack_ptr[static_cast<size_t>(br) + 1] - h.pack_ptr[static_cast<size_t>(br)];
         longest = std::max(longest, len);
@@ -519,8 +521,7 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
         bytes += len * (rc == smat::kEntryClass ? 32 * h.elem_bytes + 128 : smat::pack_units(rc) * (128 * h.elem_bytes + 32));
         cls = std::max<int>(cls, rc);
         b_rows += h.row_b_rows[static_cast<size_t>(br)];
-        if (h.bcsr.row_ptr[br + 1] > h.bcsr.row_ptr[br])
-            reach += h.bcsr.col_idx[h.bcsr.row_ptr[br + 1] - 1] - h.bcsr.col_idx[h.bcsr.row_ptr[br]];
+        if (b.row_ptr[br + 1] > b.row_ptr[br]) reach += b.col_idx[b.row_ptr[br + 1] - 1] - b.col_idx[b.row_ptr[br]];
         ++rows;
     }
     d.n_order = rows;
@@ -529,7 +530,7 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
     d.b_rows = b_rows;
     d.max_row_packs = longest;
     d.mean_row_packs = rows ? static_cast<double>(packs) / static_cast<double>(rows) : 0.0;
-    d.spread = 2 * reach > rows * h.bcsr.nbc;
+    d.spread = 2 * reach > rows * b.nbc;
     d.max_class = cls;
 }
 
@@ -704,7 +705,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
     try {
         hipStream_t s = static_cast<hipStream_t>(stream);
         char* base = static_cast<char*>(dev_workspace);
-        const smat::Bcsr& b = h->bcsr;
+        const smat::Bcsr& b = h->layout();
         const size_t nbr = static_cast<size_t>(b.nbr), n_e = b.col_idx.size();
         const size_t M = static_cast<size_t>(h->csr.M), nnz = h->csr.col_idx.size();
 
@@ -865,22 +866,34 @@ smat_status_t smat_export_device_vals(const smat_handle_t* h, void* vals, void* 
         };
         std::memset(vals, 0, n_e * 256 * es);
         std::vector<uint64_t> items;
-        for (size_t br = 0; br < static_cast<size_t>(h->bcsr.nbr); ++br) {
+        const smat::Bcsr& lay = h->layout();
+        std::vector<int32_t> new_of_old(static_cast<size_t>(h->csr.M));
+        for (size_t i = 0; i < new_of_old.size(); ++i) new_of_old[static_cast<size_t>(h->bcsr.perm[i])] = static_cast<int32_t>(i);
+        // A value of row rr of the layout's block row br and column col, to its place in the caller's blocks; false where there is none and it is not zero.
+        auto place = [&](size_t br, size_t rr, int32_t col, uint16_t v) {
+            if (br * 16 + rr >= static_cast<size_t>(h->csr.M)) return v == 0;
+            const size_t row = static_cast<size_t>(new_of_old[static_cast<size_t>(lay.perm[br * 16 + rr])]);
+            const int32_t* bc0 = h->bcsr.col_idx.data() + h->bcsr.row_ptr[row / 16];
+            const int32_t* bc1 = h->bcsr.col_idx.data() + h->bcsr.row_ptr[row / 16 + 1];
+            const int32_t* at = std::lower_bound(bc0, bc1, col >> 4);
+            if (at == bc1 || *at != col >> 4) return v == 0;
+            put(static_cast<size_t>(at - h->bcsr.col_idx.data()) * 256 + row % 16 * 16 + static_cast<size_t>(col & 15), v);
+            return true;
+        };
+        const auto stray = [] { return fail(SMAT_ERR_HIP, "device block values: a value outside the stored blocks"); };
+        for (size_t br = 0; br < static_cast<size_t>(lay.nbr); ++br) {
             if (h->row_class[br] == smat::kEntryClass) {
                 // entry row: the values of the stored entries in the order of the slot tables
                 const size_t src0 = static_cast<size_t>(h->vals_off[br]) * (64 / es), stride = 64 / es;   // in elements
-                const int32_t* bc0 = h->bcsr.col_idx.data() + h->bcsr.row_ptr[br];
-                const int32_t* bc1 = h->bcsr.col_idx.data() + h->bcsr.row_ptr[br + 1];
                 entry_order(*h, br, items);
                 const int64_t e = static_cast<int64_t>(items.size());
                 for (int64_t x = 0; x < e; ++x) {
                     const int32_t col = static_cast<int32_t>(items[static_cast<size_t>(x)] >> 4);
                     const size_t rr = static_cast<size_t>(items[static_cast<size_t>(x)] & 15u);
-                    const size_t sb = static_cast<size_t>(std::lower_bound(bc0, bc1, col >> 4) - h->bcsr.col_idx.data());
                     const int rank = static_cast<int>(x & 31);
                     const size_t at = src0 + static_cast<size_t>(x >> 5) * stride +
                                       static_cast<size_t>(smat::entry_elem_index(smat::slot_group(rank), smat::slot_pos(rank)));
-                    put(sb * 256 + rr * 16 + static_cast<size_t>(col & 15), get(at));
+                    if (!place(br, rr, col, get(at))) return stray();
                 }
                 // the rest of the last pack's 32 values must have stayed zero
                 for (int64_t x = e; x < (e + 31) / 32 * 32; ++x) {
@@ -900,12 +913,12 @@ smat_status_t smat_export_device_vals(const smat_handle_t* h, void* vals, void* 
                 int rank = 0;
                 for (int32_t sb = h->pack_first[static_cast<size_t>(pk)]; sb < h->pack_first[static_cast<size_t>(pk) + 1]; ++sb) {
                     for (int c = 0; c < 16; ++c) {
-                        if (!(h->bcsr.col_mask[sb] >> c & 1u)) continue;
+                        if (!(lay.col_mask[static_cast<size_t>(sb)] >> c & 1u)) continue;
                         const int g = smat::slot_group(rank), kk = smat::slot_pos(rank);
                         ++rank;
                         for (int r = 0; r < 16; ++r) {
                             const int at = smat::pack_elem_index(L, r, g, kk);
-                            put(static_cast<size_t>(sb) * 256 + static_cast<size_t>(r * 16 + c), get(src + static_cast<size_t>(at)));
+                            if (!place(br, static_cast<size_t>(r), 16 * lay.col_idx[static_cast<size_t>(sb)] + c, get(src + static_cast<size_t>(at)))) return stray();
                             used[at] = 1;
                         }
                     }
@@ -1269,14 +1282,21 @@ static constexpr int64_t kAblationMapEntries = int64_t{1} << 26;
 
 static size_t ablation_vals_bytes(const smat_handle* h) { return align_up(static_cast<size_t>(h->bcsr.n_blocks) * 512); }
 static bool ablation_has_map(const smat_handle* h) { return h->bcsr.nbr * h->bcsr.nbc <= kAblationMapEntries; }
+static size_t ablation_map_bytes(const smat_handle* h) { return ablation_has_map(h) ? align_up(static_cast<size_t>(h->bcsr.nbr * h->bcsr.nbc) * sizeof(int32_t)) : 0; }
+// Row pointer, block columns and permutation, where the workspace has those of another block structure.
+static size_t ablation_structure_bytes(const smat_handle* h)
+{
+    if (!h->bcsr.grouped) return 0;
+    const size_t nbr = static_cast<size_t>(h->bcsr.nbr);
+    return align_up((nbr + 1) * sizeof(int32_t)) + align_up(h->bcsr.col_idx.size() * sizeof(int32_t)) + align_up(nbr * 16 * sizeof(int32_t));
+}
 
 smat_status_t smat_ablation_bytes(const smat_handle_t* h, size_t* bytes)
 {
     if (!h || !bytes) return fail(SMAT_ERR_INVALID_ARG, "NULL argument");
     if (h->elem_bytes != 2) return fail(SMAT_ERR_UNSUPPORTED, "the ablation kernels handle fp16 and bf16 only");
     if (h->cols_permuted) return fail(SMAT_ERR_UNSUPPORTED, "the ablation kernels read B in whole block columns: not with a column permutation");
-    size_t n = ablation_vals_bytes(h);
-    if (ablation_has_map(h)) n += align_up(static_cast<size_t>(h->bcsr.nbr * h->bcsr.nbc) * sizeof(int32_t));
+    const size_t n = ablation_vals_bytes(h) + ablation_map_bytes(h) + ablation_structure_bytes(h);
     *bytes = n ? n : kAlign;
     return SMAT_OK;
 }
@@ -1309,14 +1329,31 @@ smat_status_t smat_ablation_bind(smat_handle_t* h, void* dev_area, size_t bytes,
         if (!map.empty() && (e = static_cast<int>(hipMemcpyAsync(base + ablation_vals_bytes(h), map.data(), map.size() * 4, hipMemcpyHostToDevice, s))))
             return hip_fail("copy block map", e);
         // (not copied at bind time where no block row is kept by column)
-        if (!h->by_column && !b.col_idx.empty() &&
+        if (!h->by_column && !b.col_idx.empty() && !b.grouped &&
             (e = static_cast<int>(hipMemcpyAsync(const_cast<int32_t*>(h->dev.blk_col), b.col_idx.data(), b.col_idx.size() * 4, hipMemcpyHostToDevice, s))))
             return hip_fail("copy block columns", e);
-        if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("ablation bind synchronize", e);
         smat::CanonicalBcsr& m = h->ablation;
         m.row_ptr = h->dev.blk_ptr;
         m.col_idx = h->dev.blk_col;
         m.perm = h->dev.perm;
+        std::vector<int32_t> perm;
+        if (b.grouped) {
+            perm.assign(static_cast<size_t>(b.nbr) * 16, -1);
+            std::copy(b.perm.begin(), b.perm.end(), perm.begin());
+            size_t off = ablation_vals_bytes(h) + ablation_map_bytes(h);
+            auto up = [&](const int32_t* src, size_t n) -> const int32_t* {
+                char* dst = base + off;
+                off += align_up(n * sizeof(int32_t));
+                if (n && !e) e = static_cast<int>(hipMemcpyAsync(dst, src, n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+                return reinterpret_cast<const int32_t*>(dst);
+            };
+            e = 0;
+            m.row_ptr = up(b.row_ptr.data(), static_cast<size_t>(b.nbr) + 1);
+            m.col_idx = up(b.col_idx.data(), b.col_idx.size());
+            m.perm = up(perm.data(), perm.size());
+            if (e) return hip_fail("copy canonical block structure", e);
+        }
+        if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("ablation bind synchronize", e);
         m.vals = reinterpret_cast<const uint16_t*>(base);
         m.block_map = map.empty() ? nullptr : reinterpret_cast<const int32_t*>(base + ablation_vals_bytes(h));
         m.M = h->csr.M;

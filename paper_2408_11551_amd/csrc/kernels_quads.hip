@@ -166,13 +166,12 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
     const __amdgpu_buffer_rsrc_t ix_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(tab.index) + static_cast<size_t>(q0) * (256 * IB), 0, max(nq, 0) * (256 * IB), kRsrcFlags);
 
-    // The panel.  A load brings kLoadRows rows, lane l the piece l % kPieces of 16 bytes of row l / kPieces among them, and lays them into LDS
+    // The panel.  A load brings 64 / kPieces rows, lane l the piece l % kPieces of 16 bytes of row l / kPieces among them, and lays them into LDS
     // back to back.  Which rows those are: word x of the step's table is load x % 4 of unit x / 4 (quad_panel_row); a wave has kUnits of
     // the units, o = lane / kPieces is the row among the load's, and load e of a wave
     //   PW = 8: unit o % kUnits, word e;   PW = 4: word 2 (o / kUnits) + e;   PW = 2: word o / kUnits
-    // i.e. the row with unit U = kUnits w + v and word L lies in place ((PL w + e) kLoadRows + o) of the panel.
+    // i.e. the row with unit U = kUnits w + v and word L lies in place (PL w + e) 64 / kPieces + o of the panel.
     constexpr uint32_t kPieces = kRow / 16u;
-    constexpr int kLoadRows = 64 / static_cast<int>(kPieces);
     constexpr int kUnits = quad_columns(ES) / 16;  // 4 or 8
     const int row_in_load = lane / static_cast<int>(kPieces), unit = kUnits * wave + row_in_load % kUnits;
     // Pieces of a row are placed so that the 32 lanes that LDS serves at a time (rows of two lane groups, 32 or 16 bytes of each) meet

@@ -482,7 +482,8 @@ static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const
     return partners;
 }
 
-int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers)
+int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers,
+                        Buf<int32_t>* by_pattern)
 {
     order.clear();
     order.reserve(static_cast<size_t>(M));
@@ -656,6 +657,20 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         touched.clear();
         if (partners.ptr.empty() && spent > ask_at) ask_partners();
     }
+    if (by_pattern) {
+        by_pattern->clear();
+        if (n_classes < M) {
+            by_pattern->reserve(static_cast<size_t>(M));
+            std::vector<uint8_t> taken(static_cast<size_t>(n_classes), 0);
+            for (int32_t r : order) {
+                const int32_t k = pc.class_of[r];
+                if (taken[k]) continue;
+                taken[k] = 1;
+                by_pattern->insert(by_pattern->end(), pc.members.begin() + pc.member_ptr[k], pc.members.begin() + pc.member_ptr[k + 1]);
+            }
+            if (*by_pattern == order) by_pattern->clear();
+        }
+    }
     return n_clusters;
 }
 
@@ -697,6 +712,45 @@ int64_t count_blocks(int64_t M, int64_t nbc, const Patterns& pat, const int32_t*
 
 static void build_structure(const Csr& a, const Patterns& pat, const Buf<int32_t>& per_row, Bcsr& out, Workers& workers);
 
+// Occupied columns over all block rows when rows are read in the order perm: the rows of B that a product asks for.
+static int64_t occupied_columns(const Csr& a, const int32_t* perm, Workers& workers)
+{
+    const int64_t nbr = (a.M + kBlock - 1) / kBlock;
+    Buf<int64_t> per_row(static_cast<size_t>(nbr));
+    PerThread<int32_t> seen_in(workers, a.K, -1);
+    workers.ranges(nbr, kBlockRowGrain, [&](int64_t b0, int64_t b1, int thread) {
+        int32_t* seen = seen_in.get(thread);
+        for (int64_t br = b0; br < b1; ++br) {
+            int64_t n = 0;
+            for (int64_t i = br * kBlock; i < std::min<int64_t>(a.M, (br + 1) * kBlock); ++i)
+                for (int64_t p = a.row_ptr[perm[i]]; p < a.row_ptr[perm[i] + 1]; ++p)
+                    if (seen[a.col_idx[p]] != br) { seen[a.col_idx[p]] = static_cast<int32_t>(br); ++n; }
+            per_row[br] = n;
+        }
+    });
+    return std::accumulate(per_row.begin(), per_row.end(), int64_t{0});
+}
+
+// The clustering merges a row into a cluster where it comes upon it, so the rows of several patterns lie mixed in one cluster, some of a
+// pattern's perhaps in another, and the sixteen rows of a block row then occupy the columns of most of these patterns: 2 % of
+// 627 x 627 hidden blocks 762 000 columns, where by pattern it is 124 000.  What the caller sees (permutation, blocks) is the clustering's; the
+// device layout, whose products cost a row of B per occupied column, takes the rows by pattern where that saves a tenth.  us in
+// fp16, before and now: that matrix at N = 160 29.4 and 8.6, N = 1000 185 and 33.
+static void grouped_layout(const Csr& a, const Patterns& pat, Buf<int32_t>& by_pattern, Bcsr& out, Workers& workers)
+{
+    if (by_pattern.empty()) return;
+    if (10 * occupied_columns(a, by_pattern.data(), workers) > 9 * occupied_columns(a, out.perm.data(), workers)) return;
+    out.grouped = std::make_unique<Bcsr>();
+    Bcsr& g = *out.grouped;
+    g.nbr = out.nbr;
+    g.nbc = out.nbc;
+    g.used_identity = false;
+    g.perm.swap(by_pattern);
+    Buf<int32_t> per_row;
+    g.n_blocks = count_blocks(a.M, g.nbc, pat, g.perm.data(), per_row, workers);
+    build_structure(a, pat, per_row, g, workers);
+}
+
 void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers)
 {
     const int64_t M = a.M;
@@ -707,14 +761,14 @@ void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers
 
     out.perm.resize(static_cast<size_t>(M));
     std::iota(out.perm.begin(), out.perm.end(), 0);
-    Buf<int32_t> per_row, per_row_cand;
+    Buf<int32_t> per_row, per_row_cand, by_pattern;
     out.n_blocks_identity = count_blocks(M, out.nbc, pat, out.perm.data(), per_row, workers);
     out.n_blocks = out.n_blocks_identity;
     out.used_identity = true;
     out.n_clusters = 0;
     if (reorder) {
         Buf<int32_t> cand;
-        out.n_clusters = jaccard_cluster(M, out.nbc, pat, tau_permille, cand, workers);
+        out.n_clusters = jaccard_cluster(M, out.nbc, pat, tau_permille, cand, workers, &by_pattern);
         const int64_t n_cand = count_blocks(M, out.nbc, pat, cand.data(), per_row_cand, workers);
         if (n_cand < out.n_blocks_identity) {            // strictly fewer, else keep P = I
             out.perm.swap(cand);
@@ -725,6 +779,7 @@ void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers
     }
 
     build_structure(a, pat, per_row, out, workers);
+    grouped_layout(a, pat, by_pattern, out, workers);
 }
 
 // Row pointer, block columns and column masks of the BCSR of A' = P A for the permutation
@@ -815,6 +870,7 @@ bool reorder_columns(Csr& a, int tau_permille, Bcsr& b, Workers& workers)
     const int64_t n_cand = count_blocks(K, b.nbr, cpat, cand.data(), per_row, workers);     // blocks of the transpose = blocks of P A Q
     if (n_cand >= b.n_blocks) return false;              // strictly fewer, else keep Q = I
     b.col_perm.swap(cand);
+    b.grouped.reset();                                   // (of A with its columns in the old order)
     // A <- A Q: entry (r, c) moves to the new index of column c; columns ascend again inside every row
     std::vector<int32_t> new_of_old(static_cast<size_t>(K));
     for (int64_t c = 0; c < K; ++c) new_of_old[b.col_perm[c]] = static_cast<int32_t>(c);

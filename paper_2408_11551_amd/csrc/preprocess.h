@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -32,6 +33,8 @@ struct Bcsr {
     Buf<int32_t> col_perm;
     int64_t n_blocks_rows_only = 0;
     int64_t n_clusters = 0;
+    // The block structure that the device layout is made from, where it is another one (grouped_layout): perm, row_ptr, col_idx, col_mask, n_blocks.
+    std::unique_ptr<Bcsr> grouped;
 };
 
 // Returns an empty string when the columns are well formed, else what is wrong with the first row that is not.
@@ -45,8 +48,10 @@ struct Patterns {
 };
 void block_patterns(const Csr& a, Patterns& pat, Workers& workers);
 
-// Greedy Jaccard clustering; returns the cluster order (new -> old) and the number of clusters.
-int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers);
+// Greedy Jaccard clustering; returns the cluster order (new -> old) and the number of clusters.  by_pattern: the rows of each
+// pattern together, in the place of the first of them; empty where that is the same order.
+int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers,
+                        Buf<int32_t>* by_pattern = nullptr);
 
 // Number of nonzero blocks when rows are read in the order perm on the 16-row grid; per_row receives
 // the number of every block row.

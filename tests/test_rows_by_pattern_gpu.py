@@ -1,0 +1,78 @@
+"""The device layout takes rows of the same pattern together where the clustering leaves them mixed; permutation, blocks and products are
+those of the clustering."""
+import numpy as np
+import pytest
+
+import paper_2408_11551_amd as S                # noqa: E402
+from oracle import cref                         # noqa: E402
+from oracle import smat_ref as R                # noqa: E402
+from workloads import random_csr, recast        # noqa: E402
+from workloads.configs import Workload          # noqa: E402
+
+
+def _hidden(grid, extra, N, seed, size=16):
+    """2 % or so of grid x grid blocks of size x 16 entries, rows and columns permuted; `extra` rows of a pattern of their own."""
+    rng = np.random.default_rng(seed)
+    M, K = size * grid + extra, 16 * grid
+    new_row, new_col = rng.permutation(M), rng.permutation(K)
+    dense = np.zeros((M, K), bool)
+    for i, j in zip(*np.nonzero(rng.random((grid, grid)) < 0.03)):
+        dense[np.ix_(new_row[size * i:size * i + size], new_col[16 * j:16 * j + 16])] = True
+    dense[new_row[size * grid:]] = rng.random((extra, K)) < 0.05
+    rows, cols = np.nonzero(dense)
+    row_ptr = np.zeros(M + 1, np.int64)
+    np.cumsum(np.bincount(rows, minlength=M), out=row_ptr[1:])
+    w = random_csr(8, K, N, 0.5, seed=seed, values="smallint", b_dist="smallint")
+    vals = rng.integers(1, 4, rows.size).astype(np.float16).view(np.uint16)
+    return Workload("hidden", "f16", M, K, N, row_ptr, cols.astype(np.int32), vals, w.b_bits, {})
+
+
+SHAPES = [(120, 0, 16), (150, 37, 16), (90, 5, 7)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_the_clustering_s_permutation_and_fewer_rows_of_b(shape):
+    grid, extra, size = shape
+    w = _hidden(grid, extra, 8, seed=grid, size=size)
+    h = S.smat_preprocess(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, w.dtype)
+    pp, pi = cref.block_pattern_csr(w.M, w.K, w.row_ptr, w.col_idx)
+    perm, n_e, _, _ = cref.choose_perm_c(w.M, pp, pi, (w.K + 15) // 16, 700)
+    assert np.array_equal(S.smat_export_perm(h, w.M), perm)
+    row_ptr, col_idx, _ = S.smat_export_bcsr(h)
+    assert S.smat_get_info(h)["n_blocks"] == n_e == row_ptr[-1]
+    # as the clustering leaves them
+    in_order = np.empty(w.M, np.int64)
+    in_order[perm] = np.arange(w.M) // 16
+    rows = np.repeat(np.arange(w.M), np.diff(w.row_ptr))
+    occupied = np.unique(in_order[rows] * w.K + w.col_idx).size
+    assert S.smat_get_layout_info(h)["n_columns"] < 0.9 * occupied
+    if extra == 0 and size == 16:                   # sixteen rows of every pattern: the hidden blocks are found whole
+        assert S.smat_get_layout_info(h)["n_columns"] == w.col_idx.size // 16
+    S.smat_destroy(h)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "i8"])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_products_and_exports(shape, dtype, oracle_c):
+    import torch
+    grid, extra, size = shape
+    N = 72
+    w = _hidden(grid, extra, N, seed=grid, size=size)
+    w = w if dtype == "f16" else recast(w, dtype)
+    es = w.b_bits.dtype.itemsize
+    b = torch.from_numpy(w.b_bits.view(np.int16 if es == 2 else np.int8).reshape(w.K, N)).cuda()
+    ref, _ = oracle_c.spmm_ref_c(w.M, w.K, N, w.row_ptr, w.col_idx, R.decode_bits(w.a_bits, dtype), R.decode_bits(w.b_bits, dtype))
+    for reorder in (0, 1, 2):
+        m = S.SmatMatrix(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, dtype, reorder=reorder)
+        assert np.array_equal(m.spmm(b).cpu().numpy().astype(np.float64), ref), reorder
+        assert np.array_equal(S.smat_export_device_vals(m.handle), S.smat_export_bcsr(m.handle)[2]), reorder
+        if es == 2 and reorder == 1:                # the ablation kernels walk the blocks of the clustering
+            area = torch.empty(S.smat_ablation_bytes(m.handle), dtype=torch.uint8, device="cuda")
+            S.smat_ablation_bind(m.handle, area)
+            for level in (0, 1, 2):
+                c = torch.full((w.M, N), -1.0, device="cuda")
+                S.smat_ablation_spmm(m.handle, level, b, c)
+                torch.cuda.synchronize()
+                assert np.array_equal(c.cpu().numpy().astype(np.float64), ref), level
+        m.close()
