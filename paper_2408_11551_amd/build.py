@@ -29,6 +29,7 @@ UNITS = {
     "workers": ("workers.cpp", []),
     "kernels": ("kernels.hip", PRELOAD),
     "kernels_narrow": ("kernels_narrow.hip", PRELOAD),
+    "kernels_lines": ("kernels_lines.hip", PRELOAD),
     # the per-row kernel for the 8-bit operand types: one object per type, built side by side
     "kernels_e4m3": ("kernels_8bit.hip", ["-DSMAT_8BIT_DT=2", *PRELOAD]),
     "kernels_e5m2": ("kernels_8bit.hip", ["-DSMAT_8BIT_DT=3", *PRELOAD]),
@@ -67,7 +68,7 @@ def is_stale() -> bool:
 # Kernels that place their own waits for outstanding loads (the tile kernel counts its six loads per step, the
 # walks of the per-row kernel theirs): a register spilled inside their loops adds loads the counts do not know
 # of and serialises the prefetch (seen once: 79 instead of 53 us).  The build fails if one of them spills.
-NO_SPILL = ("spmm_tile_kernel", "spmm_quad_tile_kernel", "spmm_quad_rows_kernel", "spmm_kernel")
+NO_SPILL = ("spmm_tile_kernel", "spmm_quad_tile_kernel", "spmm_quad_rows_kernel", "spmm_lines_kernel", "spmm_kernel")
 _REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill|SGPRs Spill|TotalSGPRs|LDS Size \[bytes/block\]): (\S+)")
 
 

@@ -98,9 +98,6 @@ __device__ __forceinline__ void lds_four_done(u32x2_t (&v)[4])
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]) : "n"(YOUNGER));
 }
 
-template <int... U, typename F>
-__device__ __forceinline__ void with_constants(std::integer_sequence<int, U...>, F&& f) { f(std::integral_constant<int, U>{}...); }
-
 // What the kernel needs later than its first loads.
 struct QuadTables {
     const uint8_t* index;

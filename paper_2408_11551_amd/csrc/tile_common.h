@@ -1,6 +1,9 @@
-// What the two tile kernels share (kernels_dense.hip, kernels_quads.hip): which tile a workgroup takes, loads straight
+// What the two tile kernels (kernels_dense.hip, kernels_quads.hip) share, partly also with kernels_lines.hip: which tile a workgroup takes, loads straight
 // into LDS and the transposing reads of what they delivered, and the end of a tile.
 #pragma once
+
+#include <type_traits>
+#include <utility>
 
 #include <hip/hip_runtime.h>
 
@@ -20,6 +23,10 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t v
 }
 
 }  // namespace
+
+// f(the numbers of the sequence as constants): the steps of a ring, whose places have to be known to the compiler
+template <int... U, typename F>
+__device__ __forceinline__ void with_constants(std::integer_sequence<int, U...>, F&& f) { f(std::integral_constant<int, U>{}...); }
 
 // The tiles are numbered so that the workgroups an XCD runs (every eighth in dispatch order) form
 // compact rectangles of super rows x column slabs: the tile values of a super row and the panel rows
