@@ -27,6 +27,12 @@
 
 namespace smat {
 
+// Rows per piece of a loop over rows that costs by the entry: as many as hold some ten thousand, and not too many.
+static int64_t row_grain(int64_t M, int64_t entries, int64_t most)
+{
+    return std::clamp<int64_t>(entries > 0 ? M * 16384 / entries : most, 1, most);
+}
+
 std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx, Workers& workers)
 {
     std::atomic<int64_t> first_bad{M};
@@ -40,7 +46,7 @@ std::string validate_csr(int64_t M, int64_t K, const int64_t* row_ptr, const int
         }
         return nullptr;
     };
-    workers.ranges(M, 4096, [&](int64_t r0, int64_t r1, int) {
+    workers.ranges(M, row_grain(M, row_ptr[M], 4096), [&](int64_t r0, int64_t r1, int) {
         for (int64_t r = r0; r < r1; ++r)
             if (fault(r)) {
                 int64_t seen = first_bad.load();
@@ -76,12 +82,13 @@ void block_patterns(const Csr& a, Patterns& pat, Workers& workers)
         }
         return n;
     };
-    workers.ranges(a.M, 2048, [&](int64_t r0, int64_t r1, int) {
+    const int64_t grain = row_grain(a.M, a.row_ptr[a.M], 2048);
+    workers.ranges(a.M, grain, [&](int64_t r0, int64_t r1, int) {
         for (int64_t r = r0; r < r1; ++r) pat.ptr[r + 1] = walk(r, nullptr);
     });
     prefix_sums(pat.ptr);
     pat.idx.resize(static_cast<size_t>(pat.ptr[a.M]));
-    workers.ranges(a.M, 2048, [&](int64_t r0, int64_t r1, int) {
+    workers.ranges(a.M, grain, [&](int64_t r0, int64_t r1, int) {
         for (int64_t r = r0; r < r1; ++r) walk(r, pat.idx.data() + pat.ptr[r]);
     });
 }
@@ -160,7 +167,7 @@ static PatternClasses group_equal_patterns(int64_t M, const Patterns& pat, Worke
 {
     auto len_of = [&](int64_t r) { return static_cast<int32_t>(pat.ptr[r + 1] - pat.ptr[r]); };
     Buf<uint64_t> hash(static_cast<size_t>(M));
-    workers.ranges(M, 4096, [&](int64_t r0, int64_t r1, int) {
+    workers.ranges(M, row_grain(M, pat.ptr[M], 4096), [&](int64_t r0, int64_t r1, int) {
         for (int64_t r = r0; r < r1; ++r) {
             uint64_t x = 0x9E3779B97F4A7C15ull ^ static_cast<uint64_t>(pat.ptr[r + 1] - pat.ptr[r]);
             for (int64_t q = pat.ptr[r]; q < pat.ptr[r + 1]; ++q) {
@@ -174,22 +181,39 @@ static PatternClasses group_equal_patterns(int64_t M, const Patterns& pat, Worke
         return hash[a] == hash[b] && len_of(a) == len_of(b) &&
                std::equal(pat.idx.begin() + pat.ptr[a], pat.idx.begin() + pat.ptr[a + 1], pat.idx.begin() + pat.ptr[b]);
     };
-    // first row with the same pattern, by open addressing; each piece has the rows of some of the top hash bits
-    Buf<int32_t> rep(static_cast<size_t>(M));
-    const int64_t shards = M < 8192 ? 1 : 64;
+    // First row with the same pattern, by open addressing; each piece has the rows of some of the top hash bits, which a counting sort
+    // has put together.
+    Buf<int32_t> rep(static_cast<size_t>(M)), by_shard(static_cast<size_t>(M));
+    const int64_t shards = M < 8192 ? 1 : 64, parts = shards == 1 ? 1 : workers.most();
+    auto shard_of = [&](int64_t r) { return shards == 1 ? int64_t{0} : static_cast<int64_t>(hash[r] >> 58); };
+    std::vector<int64_t> place(static_cast<size_t>(parts * shards), 0), shard_at(static_cast<size_t>(shards) + 1, 0);
+    workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
+        for (int64_t part = p0; part < p1; ++part)
+            for (int64_t r = M * part / parts; r < M * (part + 1) / parts; ++r) ++place[part * shards + shard_of(r)];
+    });
+    for (int64_t shard = 0, at = 0; shard < shards; ++shard) {
+        for (int64_t part = 0; part < parts; ++part) {
+            const int64_t n = place[part * shards + shard];
+            place[part * shards + shard] = at;
+            at += n;
+        }
+        shard_at[shard + 1] = at;
+    }
+    workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
+        for (int64_t part = p0; part < p1; ++part)
+            for (int64_t r = M * part / parts; r < M * (part + 1) / parts; ++r) by_shard[place[part * shards + shard_of(r)]++] = static_cast<int32_t>(r);
+    });
     workers.ranges(shards, 1, [&](int64_t s0, int64_t s1, int) {
+        std::vector<int32_t> table;
         for (int64_t shard = s0; shard < s1; ++shard) {
-            auto mine = [&](int64_t r) { return shards == 1 || static_cast<int64_t>(hash[r] >> 58) == shard; };
-            int64_t n = 0;
-            for (int64_t r = 0; r < M; ++r) n += mine(r) ? 1 : 0;
             size_t mask = 15;
-            while (mask < static_cast<size_t>(2 * n)) mask = 2 * mask + 1;
-            std::vector<int32_t> table(mask + 1, -1);
-            for (int64_t r = 0; r < M; ++r) {
-                if (!mine(r)) continue;
+            while (mask < static_cast<size_t>(2 * (shard_at[shard + 1] - shard_at[shard]))) mask = 2 * mask + 1;
+            table.assign(mask + 1, -1);
+            for (int64_t x = shard_at[shard]; x < shard_at[shard + 1]; ++x) {
+                const int32_t r = by_shard[x];
                 size_t at = static_cast<size_t>(hash[r]) & mask;
-                while (table[at] >= 0 && !same(table[at], static_cast<int32_t>(r))) at = (at + 1) & mask;
-                if (table[at] < 0) table[at] = static_cast<int32_t>(r);
+                while (table[at] >= 0 && !same(table[at], r)) at = (at + 1) & mask;
+                if (table[at] < 0) table[at] = r;
                 rep[r] = table[at];
             }
         }
@@ -506,6 +530,7 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     std::vector<int64_t> in_union(nbc, -1);   // id of the cluster whose union holds the column
     struct Column { int32_t c; int64_t at; }; // a column of the union: classes of its list counted so far
     std::vector<Column> columns;
+    int32_t counted_to = 0;                   // first class that the lists of the union's columns have not been counted up to
     std::vector<int32_t> walked_over(nbc, 0); // by column: classes without rows met in its list since they were last dropped
     int64_t shortest = 0;                     // shortest non-empty pattern
     for (int64_t k = 0; k < n_classes && shortest == 0; ++k) shortest = pc.len[k];
@@ -519,8 +544,9 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     int64_t n_clusters = 0;
     const int64_t keep = 1000 - tau_permille;
     Partners partners;                        // once they have been asked for
-    constexpr int64_t kFirstAsk = 300000;
+    constexpr int64_t kFirstAsk = 20000, kFirstClusters = 8;
     int64_t spent = 0, ask_at = kFirstAsk;    // counting done so far; when to look whether it is worth asking
+    int64_t spent_alone = 0;                  // of it, for clusters that no other pattern joined
 
     // Row `v` (a seed, or one that joins) brings its columns into the union, while the scan stands at it: every class that has
     // one of them shares one more column with the union, and so does each of its rows.  Only rows
@@ -549,7 +575,8 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         const int32_t begin = static_cast<int32_t>(first_of_len[std::min(longest + 1, keep * union_size / 1000 + 1)]);
         const int32_t end = static_cast<int32_t>(first_of_len[too_long]);
         const int64_t least = keep * (shortest + union_size) / (1000 + keep);   // a count must exceed this to matter for any row
-        for (size_t u = 0; u < columns.size(); ++u) {
+        // (where the bound has not moved, the lists of the columns that were there are as far as they go)
+        for (size_t u = known > 0 && end == counted_to ? known : 0; u < columns.size(); ++u) {
             Column& column = columns[u];
             int32_t* classes = inv.classes.data() + inv.ptr[column.c];
             const int64_t len = inv.len[column.c];
@@ -588,16 +615,19 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
             }
             column.at = x;
         }
+        counted_to = end;
     };
-    // The counting still to come if the rest of the rows goes like the rows so far, against that of partners_of
-    // (at most half the pairs of every list), shared by the threads.
+    // What it would save: the counting still to come for seeds that end up alone, if the rest of the rows goes like the rows so far, against
+    // that of partners_of (at most half the pairs of every list, a sixth of the time each), shared by the threads.  With the first look after
+    // 300 000 counted and weighed dearer, the whole of smat_preprocess took 1.8 ms for 1317 rows of five entries (now 1.4), 3.4 for 6872 of 19 (2.3),
+    // 14.9 for a graph of 65536 rows (13.7).
     auto ask_partners = [&]() {
         const double done = static_cast<double>(order.size()) / static_cast<double>(M);
-        const double ahead = static_cast<double>(spent) * (1.0 - done) / done;
+        const double ahead = static_cast<double>(spent_alone) * (1.0 - done) / done;
         double pairs = 0;
         for (int64_t c = 0; c < nbc; ++c) pairs += 0.5 * static_cast<double>(inv.len[c]) * static_cast<double>(inv.len[c]);
-        if (ahead < 1.5 * pairs / workers.most() + 1e6) {
-            ask_at = 4 * spent;
+        if (ahead < 0.25 * pairs / workers.most() + 5e4) {
+            ask_at = 2 * spent;
             return;
         }
         std::vector<int32_t> alive(static_cast<size_t>(n_classes));
@@ -636,6 +666,8 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         }
         int64_t union_size = 0;
         columns.clear();
+        const int64_t spent_before = spent;
+        bool alone = true;
         add_row(v, cluster, union_size);
         int64_t pos = v;
         for (;;) {
@@ -650,16 +682,21 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
                 clustered[w] = 1;
                 --state[k].alive;
                 order.push_back(static_cast<int32_t>(w));
+                alone &= k == seed_class;
                 if (inter < pc.len[k]) add_row(w, cluster, union_size);      // otherwise every column of the row is in the union already
             }
         }
         for (int32_t k : touched) state[k].shared = 0;
         touched.clear();
-        if (partners.ptr.empty() && spent > ask_at) ask_partners();
+        if (alone) spent_alone += spent - spent_before;
+        if (partners.ptr.empty() && spent > ask_at && n_clusters >= kFirstClusters) ask_partners();
     }
     if (by_pattern) {
+        // (the rows of B that putting a pattern's rows together can save are those of all its rows but one)
         by_pattern->clear();
-        if (n_classes < M) {
+        int64_t could_save = 0;
+        for (int64_t k = 0; k < n_classes; ++k) could_save += (pc.member_ptr[k + 1] - pc.member_ptr[k] - 1) * pc.len[k];
+        if (10 * could_save >= pat.ptr[M]) {
             by_pattern->reserve(static_cast<size_t>(M));
             std::vector<uint8_t> taken(static_cast<size_t>(n_classes), 0);
             for (int32_t r : order) {
@@ -712,20 +749,21 @@ int64_t count_blocks(int64_t M, int64_t nbc, const Patterns& pat, const int32_t*
 
 static void build_structure(const Csr& a, const Patterns& pat, const Buf<int32_t>& per_row, Bcsr& out, Workers& workers);
 
-// Occupied columns over all block rows when rows are read in the order perm: the rows of B that a product asks for.
-static int64_t occupied_columns(const Csr& a, const int32_t* perm, Workers& workers)
+// Occupied columns over every `stride`-th block row when rows are read in the order perm: the rows of B that a product asks for.
+static int64_t occupied_columns(const Csr& a, const int32_t* perm, int64_t stride, Workers& workers)
 {
-    const int64_t nbr = (a.M + kBlock - 1) / kBlock;
-    Buf<int64_t> per_row(static_cast<size_t>(nbr));
+    const int64_t nbr = (a.M + kBlock - 1) / kBlock, n_counted = (nbr + stride - 1) / stride;
+    Buf<int64_t> per_row(static_cast<size_t>(n_counted));
     PerThread<int32_t> seen_in(workers, a.K, -1);
-    workers.ranges(nbr, kBlockRowGrain, [&](int64_t b0, int64_t b1, int thread) {
+    workers.ranges(n_counted, kBlockRowGrain, [&](int64_t b0, int64_t b1, int thread) {
         int32_t* seen = seen_in.get(thread);
-        for (int64_t br = b0; br < b1; ++br) {
+        for (int64_t x = b0; x < b1; ++x) {
+            const int64_t br = x * stride;
             int64_t n = 0;
             for (int64_t i = br * kBlock; i < std::min<int64_t>(a.M, (br + 1) * kBlock); ++i)
                 for (int64_t p = a.row_ptr[perm[i]]; p < a.row_ptr[perm[i] + 1]; ++p)
                     if (seen[a.col_idx[p]] != br) { seen[a.col_idx[p]] = static_cast<int32_t>(br); ++n; }
-            per_row[br] = n;
+            per_row[x] = n;
         }
     });
     return std::accumulate(per_row.begin(), per_row.end(), int64_t{0});
@@ -739,7 +777,8 @@ static int64_t occupied_columns(const Csr& a, const int32_t* perm, Workers& work
 static void grouped_layout(const Csr& a, const Patterns& pat, Buf<int32_t>& by_pattern, Bcsr& out, Workers& workers)
 {
     if (by_pattern.empty()) return;
-    if (10 * occupied_columns(a, by_pattern.data(), workers) > 9 * occupied_columns(a, out.perm.data(), workers)) return;
+    const int64_t stride = out.nbr >= 256 ? 8 : 1;      // (a sample tells: counting all of a band of 7339 rows takes a tenth of its set-up)
+    if (10 * occupied_columns(a, by_pattern.data(), stride, workers) > 9 * occupied_columns(a, out.perm.data(), stride, workers)) return;
     out.grouped = std::make_unique<Bcsr>();
     Bcsr& g = *out.grouped;
     g.nbr = out.nbr;
