@@ -380,6 +380,10 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
         auto several = [&](int s, int count, auto... u) __attribute__((always_inline)) { (void)((decltype(u)::value < count && (step(u, s + decltype(u)::value), true)) && ...); };
         for (int it = 0; it < iters; ++it) with_constants(std::make_integer_sequence<int, RD>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * it, RD, u...); });
         with_constants(std::make_integer_sequence<int, RD - 1>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * iters, rem, u...); });
+        // The last step asked for the operand of one more.  Its registers are in use until that has arrived, which the compiler
+        // cannot know: it would give them to something else in the last step, and the data would land on top of that (e5m2 in tiles
+        // of 128 x 64: 1 % of the result).
+        lds_four_done<0>(b[0]);
         // nothing may still be on its way into LDS when the buffers get another use or the workgroup ends
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)");
     }

@@ -116,6 +116,17 @@ def test_smaller_tiles_on_quads(case, dtype, oracle_c):
     assert dtype in others.get(N, ()) or "rows" not in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "e4m3", "e5m2", "i8"])
+def test_every_end_of_a_walk_on_quads(dtype, oracle_c):
+    """The numbers of steps of either wave group modulo the ring: the last step's operands while the one that it has asked for in vain is under way."""
+    shapes = set()
+    for K in range(3200, 4200, 100):
+        w = random_csr(1100, K, 1040, 0.1, seed=K, values="smallint", b_dist="smallint")
+        w = w if dtype == "f16" else recast(w, dtype)
+        shapes.add(_exact(w, oracle_c, 1040, 1043, 0, dense_tiles=0))
+    assert any("128x64" in name for name in shapes), shapes
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
 @pytest.mark.parametrize("N", [1, 4, 7, 8, 9, 16, 17, 32])
 def test_few_columns_on_quads(N, dtype, oracle_c):
