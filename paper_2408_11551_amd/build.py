@@ -29,7 +29,8 @@ UNITS = {
     "workers": ("workers.cpp", []),
     "kernels": ("kernels.hip", PRELOAD),
     "kernels_narrow": ("kernels_narrow.hip", PRELOAD),
-    "kernels_lines": ("kernels_lines.hip", PRELOAD),
+    # (one object per type)
+    **{f"kernels_lines_{i}": ("kernels_lines.hip", [f"-DSMAT_LINES_DT={i}", *PRELOAD]) for i in range(5)},
     # the per-row kernel for the 8-bit operand types: one object per type, built side by side
     "kernels_e4m3": ("kernels_8bit.hip", ["-DSMAT_8BIT_DT=2", *PRELOAD]),
     "kernels_e5m2": ("kernels_8bit.hip", ["-DSMAT_8BIT_DT=3", *PRELOAD]),

@@ -105,9 +105,9 @@ int launch_spmm(const DeviceBcsr& d, int dtype, const void* B, int64_t ldb, void
 constexpr int kNotNarrow = -1;
 int launch_spmm_narrow(const DeviceBcsr& d, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc,
                        int64_t N, void* stream, const char** variant);
-// The variant for rows of B on whole cache lines (kernels_lines.hip).  Returns kNotLines where it does not apply.
-constexpr int kNotLines = -2;
-int launch_spmm_lines(const DeviceBcsr& d, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc,
+// The variant that gathers whole slabs of rows of B through LDS (kernels_lines.hip, compiled once per type).
+template <int DT>
+int launch_lines_type(const DeviceBcsr& d, const void* B, int64_t ldb, void* C, int64_t ldc,
                       int64_t N, void* stream, const char** variant);
 // the 8-bit types (kernels_8bit.hip, compiled once per type)
 int launch_spmm_e4m3(const DeviceBcsr& d, const void* B, int64_t ldb, void* C, int64_t ldc,

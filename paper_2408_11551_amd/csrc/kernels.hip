@@ -158,14 +158,57 @@ int launch_bcsr_fill(const DeviceBcsr& d, const int64_t* csr_row_ptr, const int3
     return static_cast<int>(hipGetLastError());
 }
 
+// Whether a product goes to kernels_lines.hip
+static bool takes_lines(const DeviceBcsr& d, int dtype, const void* B, int64_t ldb, int64_t N)
+{
+    const int es = dtype == kF16 || dtype == kBF16 ? 2 : 1;
+    const int64_t bytes = N * es, starts = (ldb * es) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(B));
+    // block rows with packs of 32 slots, and not a few of them (which are a launch and little else); 32 bytes of a row of B and less are for narrower loads
+    if (d.n_order < 64 || d.K == 0 || d.max_class < 2 || bytes <= 32 || bytes > 128 * 65535) return false;
+    const bool entries = d.max_class == kEntryClass, on_lines = starts % 128 == 0;
+    const int64_t span = bytes + (starts % 4 == 0 ? 0 : 4 - es);
+    // A single slab is faster there nearly throughout.  (us here and there.  On lines: 2048 block rows of 21 packs, N = 64 in fp16 19.1, 17.4, N = 128 in e4m3 20.5,
+    // 15.9; a graph of 65536 rows, N = 64 15.9, 14.2, N = 32 11.5, 8.5.  On dwords: 50021 rows of a band, N = 34 in bf16 7.4, 5.8; the graph, N = 24 11.4, 8.9;
+    // 1117 block rows of 38, N = 100 in e4m3 26.9, 24.2.  Off them: the band, N = 17 6.4, 4.7, N = 33 8.6, 6.7, N = 63 9.2, 7.2, N = 91 in int8 8.0, 8.0; the graph, N = 33 17.4,
+    // 14.0; 1117 of 38, N = 33 in fp16 31.9, 24.8, N = 65 in e4m3 34.8, 25.9.)  Not for short rows kept by entry across a whole line of
+    // bytes, with a slab of more than an L2 holds: 60000 rows of 10 entries, N = 128 in e5m2 13.3, 14.4.
+    if (span <= 128) return !(bytes > 112 && es == 1 && on_lines && entries && d.mean_row_packs < 6.0 && static_cast<double>(d.K) * 128.0 >= 6.0e6);
+    // Several slabs only on lines: off them a slab is two lines of most rows (1117 block rows of 12 packs, N = 100 12.0, 14.1).
+    if (!on_lines) return false;
+    // They read A once for each, where the other kernel's are twice as wide, and rows kept by entry are expanded once for each; what they save is what
+    // one slab less would have found in the L2s, and half-empty slabs.  (us here and there, inputs not in the caches:)
+    // 8-bit types, whose operands cost the other kernel more: faster throughout.  14000 rows of 16 entries, N = 256 15.3, 9.0, N = 1024 27.7, 22.2; 7000 of 30
+    // 16.8, 11.7 at N = 512; a band of 201, N = 256 7.3, 5.4; 2048 x 2048 hidden blocks, N = 256 30.6, 26.7.
+    // 16-bit types, rows by column: where rows of B come from all over.  627 block rows of 7 packs, N = 1024 33.3, 26.0; 1117 of 12, N = 512 39.5, 38.0; but
+    // 1700 of 17, N = 256 39.1, 43.2, and bands of 81 and 257 columns 24.1, 26.4 and 15.7, 17.3.
+    // By entry: short rows throughout (18000 of 12, N = 256 13.7, 11.8; 7000 of 6, N = 1024 13.7, 11.4; 2000 of 6 5.1, 5.5), longer ones in few slabs or where a
+    // wide slab does not fit an L2 (16384 of 16, N = 128 10.2, 8.9, N = 384 17.0, 15.7, N = 512 23.1, 23.3; 30000 of 16 49.7, 39.8), the longest
+    // also in three, of which the other kernel's last is half empty (12000 of 50, N = 192 24.5, 19.4, N = 512 41.1, 43.7; 40000 of 30, N = 256 53.5, 44.3; 24000
+    // of 30 25.3, 28.3).
+    const int64_t slabs = (bytes + 127) / 128;
+    const double wide_slab = static_cast<double>(d.K) * 256.0, packs = d.mean_row_packs;
+    if (es == 1) return packs < (entries ? 16.0 : 14.0) && (slabs <= 8 || !entries || wide_slab >= 5.0e6);
+    if (!d.spread) return false;
+    if (!entries) return packs < 14.0;
+    if (packs < 12.0) return slabs <= (packs < 7.0 ? 16 : 6) || wide_slab >= 5.0e6;
+    return slabs == 3 ? packs < 30.0 : packs < 16.0 && wide_slab >= (slabs == 2 ? 5.0e6 : 8.0e6);
+}
+
 int launch_spmm(const DeviceBcsr& d, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc,
                 int64_t N, void* stream, const char** variant)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int narrow = launch_spmm_narrow(d, dtype, B, ldb, C, ldc, N, stream, variant);
     if (narrow != kNotNarrow) return narrow;
-    const int lines = launch_spmm_lines(d, dtype, B, ldb, C, ldc, N, stream, variant);
-    if (lines != kNotLines) return lines;
+    if (takes_lines(d, dtype, B, ldb, N)) {
+        switch (dtype) {
+        case kF16: return launch_lines_type<kF16>(d, B, ldb, C, ldc, N, stream, variant);
+        case kBF16: return launch_lines_type<kBF16>(d, B, ldb, C, ldc, N, stream, variant);
+        case kE4M3: return launch_lines_type<kE4M3>(d, B, ldb, C, ldc, N, stream, variant);
+        case kE5M2: return launch_lines_type<kE5M2>(d, B, ldb, C, ldc, N, stream, variant);
+        default: return launch_lines_type<kI8>(d, B, ldb, C, ldc, N, stream, variant);
+        }
+    }
     switch (dtype) {
     case kF16: return launch_dtype<kF16>(d, B, ldb, C, ldc, N, s, variant);
     case kBF16: return launch_dtype<kBF16>(d, B, ldb, C, ldc, N, s, variant);
