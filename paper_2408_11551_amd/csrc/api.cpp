@@ -531,6 +531,7 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
     d.max_row_packs = longest;
     d.mean_row_packs = rows ? static_cast<double>(packs) / static_cast<double>(rows) : 0.0;
     d.spread = 2 * reach > rows * b.nbc;
+    d.full_packs = h.bcsr.grouped != nullptr;
     d.max_class = cls;
 }
 

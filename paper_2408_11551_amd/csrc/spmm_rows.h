@@ -131,6 +131,7 @@ constexpr int kStreamA = 1;        // block values and slot tables are read with
 constexpr int kStreamC = 2;        // C is stored with it
 constexpr int kUnalignedB = 4;     // N, the rows of B or its base are off the load width
 constexpr int kSlabsByXcd = 8;     // a workgroup's slabs go by its XCD (below)
+constexpr int kInQuarters = 16;    // DeviceBcsr::full_packs
 
 // Everything a wave needs to walk its share of a block row.
 struct RowWalk {
@@ -146,7 +147,7 @@ struct RowWalk {
 };
 
 // Per-class pieces shared by the two pipelines below.
-template <int NT, int L, int NCH, int DT, bool ENTRY = false>
+template <int NT, int L, int NCH, int DT, bool ENTRY = false, bool IN_QUARTERS = false>
 struct PackOps {
     using Acc = typename Elem<DT>::Acc;
     static constexpr int ES = Elem<DT>::ES;
@@ -308,7 +309,8 @@ struct PackOps {
                         }
                     }
                 }
-                acc[c * NT + t] = mfma_pack<DT>(a, b, acc[c * NT + t]);
+                if constexpr (IN_QUARTERS) acc[c * NT + t] = mfma_pack_in_quarters<DT>(a, b, acc[c * NT + t]);
+                else acc[c * NT + t] = mfma_pack<DT>(a, b, acc[c * NT + t]);
             }
         }
     }
@@ -320,10 +322,10 @@ struct PackOps {
 // handles two packs and has no exit in the middle (an odd tail multiplies zeros).  The
 // scheduling barriers keep every load ahead of the multiply that precedes its use, and the
 // prologue issues its loads in the order the loop body leaves them in flight.
-template <int NT, int KW, int L, int NCH, int DT, bool ENTRY = false>
+template <int NT, int KW, int L, int NCH, int DT, bool ENTRY = false, bool IN_QUARTERS = false>
 __device__ __forceinline__ void walk_row(const RowWalk& w, __amdgpu_buffer_rsrc_t rsrc, typename Elem<DT>::Acc (&acc)[NCH * NT])
 {
-    using Ops = PackOps<NT, L, NCH, DT, ENTRY>;
+    using Ops = PackOps<NT, L, NCH, DT, ENTRY, IN_QUARTERS>;
     if (w.ks >= w.npacks) return;
     const Ops ops(w, rsrc);
     const int count = (w.npacks - w.ks + KW - 1) / KW;     // packs of this wave
@@ -675,7 +677,14 @@ void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ 
     for (int t = 0; t < NCH * NT; ++t) acc[t] = Acc{0, 0, 0, 0};
 
     if constexpr (LMAX >= 8) {
-        if (cls == 2) walk_row<NT, KW, 8, NCH, DT>(w, rsrc, acc);
+        if (cls == 2) {
+            if constexpr (DT == kE4M3 || DT == kE5M2) {
+                if (hints & kInQuarters) walk_row<NT, KW, 8, NCH, DT, false, true>(w, rsrc, acc);
+                else walk_row<NT, KW, 8, NCH, DT>(w, rsrc, acc);
+            } else {
+                walk_row<NT, KW, 8, NCH, DT>(w, rsrc, acc);
+            }
+        }
         if (cls == kEntryClass) {
             if constexpr (NARROW != 0) {
                 static_assert(NT == 1 && SW == 1 && NCH == 1, "the narrow walk covers one slab of 16 columns");
@@ -856,6 +865,7 @@ static int launch_variant(const DeviceBcsr& d, const void* B, int64_t ldb, void*
     // then keeps the rows of B.
     int hints = (grid.y == 1 && SW == 1 && static_cast<double>(d.stream_bytes) > 200e6) ? kStreamA : 0;
     if (unaligned) hints |= kUnalignedB;
+    if (d.full_packs) hints |= kInQuarters;
     // A B of about the size of the L2s stays there between its uses only if the write of C does
     // not push it out: then C is stored past the cache (measured: -7 % where B is 4 MiB, no gain
     // or a loss where B is 16 MiB and more).
