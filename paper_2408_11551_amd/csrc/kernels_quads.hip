@@ -297,8 +297,9 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
                 v[3] = lds_read_tr8<kPanel * u + kRead2 + kRead1>(tr_addr[x]);
             }
         };
-        auto step = [&](auto u_, int s) __attribute__((always_inline)) {
+        auto step = [&](auto u_, int s, auto behind_) __attribute__((always_inline)) {
             constexpr int u = decltype(u_)::value;
+            constexpr bool behind = decltype(behind_)::value;      // a step behind the loop
             constexpr int next = (u + AHEAD) % RD;
             u32x4 wide[2][RM];                     // e5m2: the values as f16, those of the step's first 64 k slots and of the others
             if constexpr (kAsF16<DT>) {
@@ -324,8 +325,10 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
                     // This wave's reads of the panel have returned, and all of its loads but the youngest
                     // (AHEAD - 1) LOADS: the panel, values and
                     // positions of step s + 1 are there, and the table that the loads after the barrier are made from.
+                    // Behind the loop only the loads into LDS count: of the others the compiler leaves out those of steps that are not there
+                    // (all LOADS counted, 4 loads of step 1's panel could still be out where a workgroup has two steps per group).
                     lds_four_done<0>(b[x & 1]);
-                    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((AHEAD - 1) * LOADS));
+                    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((AHEAD - 1) * (behind ? PL : LOADS)));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                     read_four(std::integral_constant<int, (u + 1) % RD>{}, 0, b[0]);
@@ -377,9 +380,9 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
         load_panel(table[AHEAD], AHEAD, 0);
         __builtin_amdgcn_sched_barrier(0);
         // the first `count` of steps s, s + 1, ..., s = 0 (mod RD)
-        auto several = [&](int s, int count, auto... u) __attribute__((always_inline)) { (void)((decltype(u)::value < count && (step(u, s + decltype(u)::value), true)) && ...); };
-        for (int it = 0; it < iters; ++it) with_constants(std::make_integer_sequence<int, RD>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * it, RD, u...); });
-        with_constants(std::make_integer_sequence<int, RD - 1>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * iters, rem, u...); });
+        auto several = [&](int s, int count, auto behind, auto... u) __attribute__((always_inline)) { (void)((decltype(u)::value < count && (step(u, s + decltype(u)::value, behind), true)) && ...); };
+        for (int it = 0; it < iters; ++it) with_constants(std::make_integer_sequence<int, RD>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * it, RD, std::false_type{}, u...); });
+        with_constants(std::make_integer_sequence<int, RD - 1>{}, [&](auto... u) __attribute__((always_inline)) { several(RD * iters, rem, std::true_type{}, u...); });
         // The last step asked for the operand of one more.  Its registers are in use until that has arrived, which the compiler
         // cannot know: it would give them to something else in the last step, and the data would land on top of that (e5m2 in tiles
         // of 128 x 64: 1 % of the result).

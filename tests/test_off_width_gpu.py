@@ -127,6 +127,26 @@ def test_every_end_of_a_walk_on_quads(dtype, oracle_c):
     assert any("128x64" in name for name in shapes), shapes
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2", "i8"])
+@pytest.mark.parametrize("K", [1100, 1500, 2100, 2400, 3000, 4100])
+def test_short_walks_on_quads(K, dtype, oracle_c):
+    """The steps of a tile split over workgroups: walks that the loop of three steps does not enter or leaves after one pass, where the panel of the
+    second step is awaited behind the loads of the prologue, whose order is another one.  Other inputs in between, so that a panel that
+    is not there shows."""
+    w = random_csr(512, K, 144, 0.1, seed=K, dtype="bf16", values="smallint", b_dist="smallint")
+    w = recast(w, dtype)
+    m = S.SmatMatrix(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, w.dtype, reorder=0, dense_tiles=1)
+    b = torch.from_numpy(w.b_bits.view(np.int16 if dtype == "bf16" else np.int8).reshape(K, w.N)).cuda()
+    other = torch.zeros_like(b)
+    ref, _ = oracle_c.spmm_ref_c(w.M, w.K, w.N, w.row_ptr, w.col_idx, R.decode_bits(w.a_bits, w.dtype), R.decode_bits(w.b_bits, w.dtype))
+    for _ in range(20):
+        m.spmm(other)
+        assert np.array_equal(m.spmm(b).cpu().numpy().astype(np.float64), ref)
+    name = S.smat_last_kernel()
+    assert K < 2000 or name.startswith(f"spmm_dense_{dtype}_g2k") or dtype == "e5m2" and name.startswith("spmm_dense_e5m2_g"), name
+    m.close()
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
 @pytest.mark.parametrize("N", [1, 4, 7, 8, 9, 16, 17, 32])
 def test_few_columns_on_quads(N, dtype, oracle_c):
