@@ -281,6 +281,10 @@ __device__ __forceinline__ void walk_lines(const LineWalk& w, __amdgpu_buffer_rs
 
 }  // namespace
 
+// Columns of a slab, a multiple of four: with what a row is shifted by they have to be in it.
+template <int ES, int SLAB, bool SHIFTED>
+__host__ __device__ constexpr int columns_of_slab(int N) { return SHIFTED && N > (SLAB - 4) / ES + 1 ? (SLAB - 4) / ES / 4 * 4 : SLAB / ES; }
+
 // NX: groups of sixteen columns that there are in a slab, or three quarters of them where N has no more
 template <int DT, int KW, int SLAB, int NX, bool SHIFTED>
 __global__ __launch_bounds__(64 * KW)
@@ -303,14 +307,14 @@ void spmm_lines_kernel(const int32_t* __restrict__ work, const uint32_t* __restr
     if (record >= static_cast<uint32_t>(n_order)) return;
     const i32x4 rec = reinterpret_cast<const i32x4*>(work)[record];
     const int br = rec[0] & 0x0FFFFFFF, cls = rec[0] >> 28;
-    const int n0 = static_cast<int>(slab) * (SLAB / ES);
+    const int step = columns_of_slab<ES, SLAB, SHIFTED>(N), n0 = static_cast<int>(slab) * step;
     LineWalk w;
     w.slots = slots + static_cast<size_t>(static_cast<uint32_t>(rec[2])) * 8;
     w.vals = static_cast<const uint8_t*>(vals) + static_cast<size_t>(static_cast<uint32_t>(rec[3])) * 64;
     w.npacks = rec[1];
     w.ks = ks;
     w.lane = lane;
-    w.first_byte = slab * SLAB;
+    w.first_byte = static_cast<uint32_t>(n0) * ES;
     w.bytes = static_cast<uint32_t>(N - n0) * ES + (SHIFTED ? 4 - ES : 0);
     w.ldb_bytes = ldb_bytes;
     w.K = K;
@@ -347,7 +351,7 @@ void spmm_lines_kernel(const int32_t* __restrict__ work, const uint32_t* __restr
         const int e = static_cast<int>(threadIdx.x) + 64 * KW * k;
         const int row = e / Q, c = 4 * (e % Q);
         const int64_t out_row = out_rows[k];
-        if (out_row < 0 || n0 + c >= N) continue;
+        if (out_row < 0 || c >= step || n0 + c >= N) continue;
         const Out* src = reinterpret_cast<const Out*>(lds_dyn) + row * LD + c;
         Acc v = *reinterpret_cast<const Acc*>(src);
 #pragma unroll
@@ -369,7 +373,8 @@ template <int DT, int KW, int SLAB, int NX, bool SHIFTED>
 static int launch_lines(const DeviceBcsr& d, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N, hipStream_t s)
 {
     constexpr int ES = Elem<DT>::ES;
-    const dim3 grid(static_cast<unsigned>((d.n_order + 7) / 8 * 8), static_cast<unsigned>((N * ES + SLAB - 1) / SLAB));
+    const int step = columns_of_slab<ES, SLAB, SHIFTED>(static_cast<int>(N));
+    const dim3 grid(static_cast<unsigned>((d.n_order + 7) / 8 * 8), static_cast<unsigned>((N + step - 1) / step));
     // (from the dword in which B begins to that in which it ends)
     const uint32_t off_dword = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(B) & 3u);
     const uint32_t b_bytes = static_cast<uint32_t>((off_dword + ((d.K - 1) * ldb + N) * ES + 3) / 4 * 4);
@@ -410,12 +415,12 @@ int launch_lines_type(const DeviceBcsr& d, const void* B, int64_t ldb, void* C, 
     // Waves per block row: until there are two for every SIMD, as long as a wave has four packs to walk; five where some rows are much longer
     // than the average; and a little later for four waves that move what they read.  (us with 1 / 2 / 4 waves: 1117 block rows of 12 packs, N = 64 10.3 / 7.4
     // / 8.1; 2048 of 21 18.6 / 17.4 / 18.8; 4096 of a graph, 8 on average, 19.9 / 16.5 / 19.2; 166 of 22 9.4 / 6.1 / 4.8.  Moved: 1117 of 38, N = 65 in e4m3
-    // 44.4 / 28.0 / 26.1; 2500 of 6, N = 125 in e5m2 12.6 / 13.2 / 14.3; of a graph, N = 33 in fp16 15.6 / 14.0 / 17.0, but N = 125 in int8, 96 of whose
-    // registers hold a pack, 20.7 / 22.5 / 25.0.)
+    // 44.4 / 28.0 / 26.1; 2500 of 6, N = 125 in e5m2 12.6 / 13.2 / 14.3; of a graph, N = 33 in fp16 15.6 / 14.0 / 17.0, but N = 125 in int8, which moves
+    // four times as much, 20.7 / 22.5 / 25.0; the graph's half, 1875, 15.9 / 11.8 / 12.3.)
     const int64_t units = d.n_order * ((span + slab - 1) / slab);
-    const bool skewed = static_cast<double>(d.max_row_packs) > 2.0 * d.mean_row_packs && (ES == 2 || on_dwords || span <= 96);
+    const bool skewed = static_cast<double>(d.max_row_packs) > 2.0 * d.mean_row_packs, full = ES == 1 && !on_dwords && span > 96;
     int kw = 1;
-    while (kw < 8 && d.mean_row_packs >= 4.0 * kw && units * kw < (skewed ? 5000 : !on_dwords && kw > 1 ? 3000 : 2200)) kw *= 2;
+    while (kw < 8 && d.mean_row_packs >= 4.0 * kw && units * kw < (skewed ? (full ? 3000 : 5000) : !on_dwords && kw > 1 ? 3000 : 2200)) kw *= 2;
     *variant = kNames[slab == 128][!on_dwords][kw == 8 ? 3 : kw >> 1];
     if (slab == 128) {
         constexpr int NX = 8 / ES;

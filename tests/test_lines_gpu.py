@@ -59,13 +59,28 @@ def test_rows_that_begin_anywhere(dtype, slab, widest, oracle_c):
         N = (slab - (0 if on_dwords else 4 - es)) // es if widest else slab // 2 // es + 1
         ldb = (N * es + 3) // 4 * 4 // es + ldb_off
         for w in (random_csr(1030, 1700, N, 0.008, seed=1, values="smallint", b_dist="smallint"),
-                  random_csr(1024, 3000, N, 0.1, seed=4, values="smallint", b_dist="smallint"),
+                  random_csr(1610, 1500, N, 0.1, seed=4, values="smallint", b_dist="smallint"),
                   occupancy_csr(OCCUPANCY_SPEC * 9, K=16 * 64 + 5, N=N, seed=5)):
             w = w if dtype == "f16" else recast(w, dtype)
             name = _exact(w, oracle_c, ldb, N + 1, shift)
             assert name.endswith("_lds_l8" if on_dwords else "_ldso_l8"), (name, N, ldb, shift)
             names.add(name)
     assert len({name.split("_")[2][:2] for name in names}) == 1 and len(names) > 2, names
+
+
+@pytest.mark.parametrize("dtype", ["f16", "e4m3", "i8"])
+@pytest.mark.parametrize("more", [1, 30, 127])
+def test_several_slabs_that_begin_anywhere(dtype, more, oracle_c):
+    """Off the dwords a slab has as many columns fewer as a row may be shifted by."""
+    es = 2 if dtype == "f16" else 1
+    N = 120 // es + more
+    for ldb_off, shift in ((0, 0), (4 // es, 4 // es), (1, 0), (0, 1), (3, 2)):
+        ldb = (N * es + 3) // 4 * 4 // es + ldb_off
+        for w in (random_csr(1030, 1700, N, 0.008, seed=more, values="smallint", b_dist="smallint"),
+                  random_csr(1024, 400, N, 0.1, seed=more, values="smallint", b_dist="smallint")):
+            w = w if dtype == "f16" else recast(w, dtype)
+            name = _exact(w, oracle_c, ldb, N + 1, shift)
+            assert "_lds" in name, (name, N, ldb, shift)
 
 
 def test_columns_of_infinities_stay_in_their_columns(oracle_c):
