@@ -1027,19 +1027,25 @@ double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
     return c.start + std::ceil(n_tiles / 256.0) * steps * c.step + n_tiles / 256.0 * steps * c.shared + kWrite[t.quad_shape] * c_mb;
 }
 
-// The same on the per-row kernel, fitted on the same products (within 10-20 %): rows of B by the byte and by the 256-byte slab, values, C; rows
-// of B on whole cache lines, on dwords, and off them.
+// The same on the per-row kernels, fitted on these products and 1000 more (within 11-16 %; up to 128 bytes of a row of B 7-12 %): rows of B by the byte and by
+// the 256-byte slab, values, C; rows of B on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes
+// (kernels_lines.hip) on dwords and off them.
 double rows_us(const smat_handle& h, int64_t N, int64_t ldb)
 {
     struct Cost { double start, gather, slab, values, write; };
-    static constexpr Cost kCosts[2][3] = {{{2.7, 0.053, 0.39, 0.14, 0.29}, {3.0, 0.058, 0.31, 0.105, 0.33}, {4.0, 0.057, 0.0, 0.35, 0.75}},
-                                          {{2.8, 0.051, 0.0, 0.25, 0.52}, {3.15, 0.057, 1.82, 0.153, 0.48}, {2.9, 0.085, 0.0, 0.66, 0.82}}};
-    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256;
-    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][ldb * h.elem_bytes % 128 == 0 ? 0 : ldb * h.elem_bytes % 4 == 0 ? 1 : 2];
+    static constexpr Cost kCosts[2][6] = {{{3.35, 0.003, 12.3, 0.026, 0.24}, {3.7, 0.021, 9.5, 0.0, 0.06}, {3.55, 0.007, 12.65, 0.0, 0.21}, {7.7, 0.0, 13.6, 0.32, 0.6},
+                                           {2.9, 0.05, 0.94, 0.06, 0.0}, {2.8, 0.11, 1.5, 0.0, 0.55}},
+                                          {{3.7, 0.0, 14.4, 0.09, 0.37}, {4.6, 0.017, 11.2, 0.013, 0.28}, {4.15, 0.012, 12.3, 0.0, 0.36}, {6.0, 0.0, 17.2, 0.57, 0.5},
+                                           {3.35, 0.064, 0.0, 0.06, 0.0}, {4.35, 0.104, 1.05, 0.0, 0.0}}};
+    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256, row_bytes = ldb * h.elem_bytes;
+    const bool on_dwords = row_bytes % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - h.elem_bytes) <= 128;
+    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : row_bytes % 128 == 0 ? 0 : row_bytes % 16 == 0 ? 1 : on_dwords ? 2 : 3];
     const double m_rows = static_cast<double>(h.b_rows) * 1e-6;
-    const double idle = std::max(1.0, 256.0 / (static_cast<double>(h.bcsr.nbr) * static_cast<double>(slabs)));
-    return c.start + m_rows * (c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs)) * idle +
-           c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
+    // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
+    const double groups = static_cast<double>(h.bcsr.nbr) * static_cast<double>(slabs) / 256.0;
+    const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
+    const double row = std::min(c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs), 0.14 * static_cast<double>(bytes));
+    return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
 }
 
 // smat_spmm with the area for partial tiles given by the caller of this function.
