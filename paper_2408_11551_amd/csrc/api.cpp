@@ -69,7 +69,7 @@ struct smat_handle {
     // The two-of-four form of the dense super rows (quad_layout.h), in place of the tables above; empty if it does not pay.
     std::vector<int32_t> quad_ptr, quad_rows;
     int max_quad_steps = 0;
-    int quad_tail = 0;                   // 1: a last super row too short for a tile follows the others, for the kernel for few columns
+    int quad_tail = 0;                   // 1: a last super row too short or too sparse for the tile kernels follows the others
     int64_t quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr.back(); }
     int64_t tiled_quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr[dense_super.size()]; }      // without those of quad_tail
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
@@ -308,8 +308,8 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
     const double most_steps = (es == 2 ? 0.85 : h.dtype == SMAT_I8 ? 0.73 : h.dtype == SMAT_E4M3 ? 0.7 : 0.6) * static_cast<double>(steps);
     // (columns per quad come down to two at 40 % fill, where there are as many steps as in the other form)
     if (static_cast<double>(nnz) > (es == 2 ? 0.3 : 0.27) * 256.0 * static_cast<double>(steps * (cols / 2))) return;
-    // A last super row of a few block rows is left to the per-row kernel by the tile kernels, whose tile would be mostly empty; in
-    // the kernel for few columns it saves a launch (1300 x 6000 in int8, N = 3: 12.6 us with it, of 82 block rows two).
+    // A last super row of a few block rows, or of sixteen that are too sparse, did not qualify above.  On quads it saves a launch to take it along: in
+    // the kernel for few columns (1300 x 6000 in int8, N = 3: 12.6 us with it, of 82 block rows two), and in tiles where that pays.
     std::vector<int32_t> supers(h.dense_super);
     const int64_t last = (h.bcsr.nbr - 1) / 16;
     if (n == last && h.dense_super.back() == last - 1) supers.push_back(static_cast<int32_t>(last));
@@ -797,7 +797,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
         tiles.max_quad_steps = h->max_quad_steps;
         tiles.quad_tail = h->quad_tail;
-        tiles.quad_tail_rows = h->quad_tail ? static_cast<int32_t>(b.nbr % 16) : 0;
+        tiles.quad_tail_rows = h->quad_tail ? static_cast<int32_t>(b.nbr - 16 * ((b.nbr - 1) / 16)) : 0;      // 1 ... 16
         tiles.scratch = nullptr;           // a call takes the area of its stream
         tiles.scratch_bytes = 0;
         tiles.n = static_cast<int32_t>(h->dense_super.size());
@@ -1095,8 +1095,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     if (use_tiles && h->dense_mode == 0 && tiles.n_quad_steps > 0 && !hard_limit) {
         // On quads the shape is chosen too: narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
         // a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
-        // 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  A last
-        // super row with few block rows gets tiles like the others where that pays.
+        // 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
+        // last super row of quad_tail gets tiles like the others where that pays.
         auto take = [&](int shape, bool tail) {
             tiles.quad_shape = shape;
             tiles.quad_tail_tiled = tail;
@@ -1162,7 +1162,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
     const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 ? 2.0 : 1.0);
     if (!use_tiles && h->dense_mode == 0 && few_columns(*h, N, off_dwords).take()) {
-        // (with the last few block rows among the quads, all are: quad_tail)
+        // (with quad_tail all block rows are among the quads)
         if (h->dev_rest.n_order > 0 && !h->quad_tail) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
             enqueued("rows", rows_flop(h->dev_rest, N));
@@ -1193,7 +1193,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const int64_t columns = tiles.n_quad_steps > 0 ? smat::quad_shape_columns(tiles.quad_shape) : 128;
             const double groups = static_cast<double>((n + columns - 1) / columns * (columns / 16));
             if (tiles.n_quad_steps > 0) {
-                // (of a last super row with few block rows, the part that has tiles)
+                // (of the last super row of quad_tail, the part that has tiles)
                 const int tile_rows = smat::quad_shape_rows(tiles.quad_shape) / 16;
                 const double tail = tiles.quad_tail_tiled ? (tiles.quad_tail_rows + tile_rows - 1) / tile_rows * tile_rows / 16.0 : 0.0;
                 enqueued("quad_tiles", quad_step_flop * groups * (static_cast<double>(h->tiled_quad_steps()) +

@@ -69,8 +69,8 @@ struct DenseTiles {
     const int32_t* quad_rows = nullptr;    // [quad_columns * (n_quad_steps + 1)] rows of B of a step's panel; the last step names none
     const uint8_t* quad_index = nullptr;   // [2 or 4 KiB * n_quad_steps] positions of the values
     int32_t n_quad_steps = 0, max_quad_steps = 0;      // all, and those of the longest super row
-    int32_t quad_tail = 0;                 // 1: super row number n is there too (not as a tile, for launch_quad_rows), and then all block rows are
-    int32_t quad_tail_rows = 0;            // its block rows
+    int32_t quad_tail = 0;                 // 1: super row number n is there too (for launch_quad_rows, and for the tiles with quad_tail_tiled), and then all block rows are
+    int32_t quad_tail_rows = 0;            // its block rows: all sixteen, too, where it is only too sparse to be one of the n
     // of a call
     int quad_shape = 0;                    // QuadShape; only the first one's steps may be split over workgroups
     bool quad_tail_tiled = false;          // the tiles cover super row number n too

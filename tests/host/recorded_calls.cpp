@@ -3,6 +3,7 @@
 // copy and the product that reads it.  Prints what is wrong; exit code 0 if nothing is.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstdio>
 #include <mutex>
@@ -16,6 +17,8 @@
 namespace {
 
 struct Event { bool copy; const void* from; const void* to; const void* stream; };     // a copy of B: B, area; a product: its B, C
+int64_t g_block_rows = 0;                // that the launches cover, those of the tiles counted once per range of columns
+bool g_on_quads = false;
 std::mutex g_mutex;
 std::vector<Event> g_events;
 hipStream_t g_capturing = nullptr;
@@ -60,8 +63,9 @@ int launch_fill_zero(void*, size_t, void*) { return 0; }
 int launch_bcsr_fill(const DeviceBcsr&, const int64_t*, const int32_t*, const uint16_t*, const int32_t*, void*, uint32_t*, size_t, int, void*) { return 0; }
 int launch_dense_fill(const DeviceBcsr&, const DenseTiles&, const int64_t*, const int32_t*, const uint16_t*, void*, int, void*) { return 0; }
 int launch_quad_fill(const DeviceBcsr&, const DenseTiles&, int, const int64_t*, const int32_t*, const uint16_t*, void*, void*, int, void*) { return 0; }
-int launch_quad_rows(const DeviceBcsr&, const DenseTiles&, int, const void*, int64_t, void*, int64_t, int64_t, void*, const char** variant)
+int launch_quad_rows(const DeviceBcsr&, const DenseTiles& t, int, const void*, int64_t, void*, int64_t, int64_t, void*, const char** variant)
 {
+    g_block_rows += 16 * int64_t{t.n} + t.quad_tail_rows;
     *variant = "quad_rows";
     return 0;
 }
@@ -78,14 +82,19 @@ int launch_stage_b(const void* B, int64_t, int64_t, int64_t, int, void* out, int
     record(true, B, out, stream);
     return 0;
 }
-int launch_spmm(const DeviceBcsr&, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
+int launch_spmm(const DeviceBcsr& d, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
 {
+    g_block_rows += d.n_order;
     record(false, B, C, stream);
     *variant = "rows";
     return 0;
 }
-int launch_spmm_dense(const DeviceBcsr&, const DenseTiles&, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
+int launch_spmm_dense(const DeviceBcsr&, const DenseTiles& t, int, const void* B, int64_t, void* C, int64_t, int64_t, void* stream, const char** variant)
 {
+    // (tiles of a last super row that is not complete reach past its block rows)
+    const int64_t per_tile = quad_shape_rows(t.quad_shape) / 16, tail = quad_row_tiles(t) * per_tile - 16 * int64_t{t.n};
+    g_on_quads = t.n_quad_steps > 0;
+    g_block_rows += 16 * int64_t{t.n} + std::min<int64_t>(tail, t.quad_tail_rows);
     record(false, B, C, stream);
     *variant = "tiles";
     return 0;
@@ -96,12 +105,13 @@ namespace {
 
 constexpr int64_t M = 1024, K = 4096, N = 1001;          // rows of B off the cache lines, and used often: the per-row kernel copies B
 
-smat_handle_t* make(int streams, int dense_tiles, std::vector<char>& workspace)
+// `sparse` more rows with one entry in every `stride` columns (none at all: stride 0)
+smat_handle_t* make(int streams, int dense_tiles, std::vector<char>& workspace, int64_t sparse = 0, int64_t stride = 0)
 {
-    std::vector<int64_t> ptr(M + 1, 0);
+    std::vector<int64_t> ptr(M + sparse + 1, 0);
     std::vector<int32_t> col;
-    for (int64_t r = 0; r < M; ++r) {
-        for (int64_t c = r % 7; c < K; c += 7) col.push_back(static_cast<int32_t>(c));
+    for (int64_t r = 0; r < M + sparse; ++r) {
+        for (int64_t c = r % 7; c < K && (r < M || stride); c += r < M ? 7 : stride) col.push_back(static_cast<int32_t>(c));
         ptr[r + 1] = static_cast<int64_t>(col.size());
     }
     std::vector<uint16_t> vals(col.size(), 0x3C00);
@@ -112,7 +122,7 @@ smat_handle_t* make(int streams, int dense_tiles, std::vector<char>& workspace)
     opt.concurrent_streams = streams;
     smat_handle_t* h = nullptr;
     size_t bytes = 0;
-    if (smat_preprocess(M, K, ptr.data(), col.data(), vals.data(), SMAT_F16, &opt, &h) != SMAT_OK || smat_device_bytes(h, &bytes) != SMAT_OK) return nullptr;
+    if (smat_preprocess(M + sparse, K, ptr.data(), col.data(), vals.data(), SMAT_F16, &opt, &h) != SMAT_OK || smat_device_bytes(h, &bytes) != SMAT_OK) return nullptr;
     workspace.assign(bytes + 256, 0);
     char* base = workspace.data() + (256 - reinterpret_cast<uintptr_t>(workspace.data()) % 256) % 256;
     return smat_bind_device(h, base, bytes, nullptr) == SMAT_OK ? h : nullptr;
@@ -159,10 +169,34 @@ void threads_on_one_stream(Call f, const smat_handle_t* h, const char* what)
     expect(mixed == 0, what);
 }
 
+// Every block row is some launch's, whatever the last 256 rows are like: fewer than sixteen block rows, or all sixteen but too sparse for tiles.
+void every_block_row_is_covered()
+{
+    for (int64_t stride : {int64_t{0}, K / 8})
+        for (int64_t sparse = 16; sparse <= 256; sparse += 16)
+            for (int64_t more : {0, -7})
+                for (int64_t n : {8, 512, 1008, 1001}) {
+                    std::vector<char> workspace;
+                    smat_handle_t* h = make(2, 0, workspace, sparse + more, stride);
+                    g_block_rows = 0;
+                    g_events.clear();
+                    expect(smat_spmm(h, operand_b(1), n, operand_c(1), n, n, nullptr) == SMAT_OK, "status of a call");
+                    if (g_block_rows != (M + sparse) / 16) {
+                        std::printf("%d sparse rows of %d entries, N = %d: %d block rows of %d\n", static_cast<int>(sparse + more), stride ? 8 : 0,
+                                    static_cast<int>(n), static_cast<int>(g_block_rows), static_cast<int>((M + sparse) / 16));
+                        ++g_wrong;
+                    }
+                    expect(n == 8 || g_on_quads, "these products go to tiles on quads");
+                    g_on_quads = false;
+                    smat_destroy(h);
+                }
+}
+
 }  // namespace
 
 int main()
 {
+    every_block_row_is_covered();
     for (int dense_tiles : {-1, 1}) {
         std::vector<char> workspace;
         smat_handle_t* h = make(2, dense_tiles, workspace);

@@ -1,5 +1,7 @@
 """Rows of B, bases and widths that are off the load width of the per-row kernel: the last lane's columns end with
 column N - 1, nothing outside the N columns is read for or written to C.  Small integers: every result is exact."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -114,6 +116,23 @@ def test_smaller_tiles_on_quads(case, dtype, oracle_c):
     assert dtype in others.get(N, ()) or shape in name, name
     # no launch of its own for the last block rows
     assert dtype in others.get(N, ()) or "rows" not in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
+@pytest.mark.parametrize("left", [0.0, 0.02])
+@pytest.mark.parametrize("rows", [256, 249, 240, 80])
+def test_last_super_row_too_sparse_for_tiles(rows, left, dtype, oracle_c):
+    """Padded weights: up to sixteen block rows at the end, empty or nearly, behind super rows that go to tiles on quads.  Their rows of C
+    are written, too."""
+    M, K, N = 1024 + rows, 4110, 1040
+    w = random_csr(M, K, N, 0.1, seed=rows, values="smallint", b_dist="smallint")
+    at = np.repeat(np.arange(M), np.diff(w.row_ptr))
+    keep = (at < 1024) | (np.random.default_rng(rows).random(at.size) < left)
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(at[keep], minlength=M))])
+    w = replace(w, row_ptr=row_ptr, col_idx=w.col_idx[keep], a_bits=w.a_bits[keep])
+    w = w if dtype == "f16" else recast(w, dtype)
+    _exact(w, oracle_c, N, N + 3, 0, dense_tiles=0)
+    assert "quad_tiles" in S.smat_last_launches()[0].split("+"), S.smat_last_launches()
 
 
 @pytest.mark.parametrize("dtype", ["f16", "e4m3", "e5m2", "i8"])
