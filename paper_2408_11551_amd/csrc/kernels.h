@@ -36,7 +36,7 @@ struct DeviceBcsr {
     int64_t max_row_packs = 0;           // longest block row
     double mean_row_packs = 0;
     bool full_packs = false;             // rows of one pattern were put together, whose packs have a product in every slot, and not in one of six: the
-                                         // 8-bit floats' are then multiplied in quarters (mfma_types.h), to be added no less exactly than before
+                                         // 8-bit floats' are then multiplied in parts (mfma_types.h), to be added no less exactly than before
     bool spread = false;                 // a block row's block columns reach over more than half of all, on average
     int max_class = 0;                   // highest row class present (0: <=8, 1: <=16, 2: <=32 occupied columns per pack, 3: entry rows)
 };

@@ -97,7 +97,7 @@ __device__ __forceinline__ uint32_t from_further(uint32_t v, uint32_t next, uint
 // SHIFTED: rows of B begin anywhere.  A row is fetched from the dword on that it begins in, so that its columns lie up to 4 / ES - 1 places
 // further on in LDS.  What a transposing read brings a lane of a shifted row belongs to a lane before it, and is moved there: by DPP, for all rows of
 // the pack, and then taken for those that are shifted.
-template <int DT, int KW, int SLAB, int NX, bool SHIFTED, int L, bool ENTRY, bool IN_QUARTERS = false>
+template <int DT, int KW, int SLAB, int NX, bool SHIFTED, int L, bool ENTRY, bool IN_PARTS = false>
 __device__ __forceinline__ void walk_lines(const LineWalk& w, __amdgpu_buffer_rsrc_t b_rsrc, typename Elem<DT>::Acc (&acc)[NX])
 {
     constexpr int ES = Elem<DT>::ES;
@@ -268,7 +268,7 @@ __device__ __forceinline__ void walk_lines(const LineWalk& w, __amdgpu_buffer_rs
             // (positions past L hold another row's elements)
             if constexpr (L == 2) b = u32x4{ES == 2 ? b[0] : b[0] & 0xFFFFu, 0u, 0u, 0u};
             if constexpr (L == 4 && ES == 1) b[1] = 0u;
-            if constexpr (IN_QUARTERS) acc[x] = mfma_pack_in_quarters<DT>(av, b, acc[x]);
+            if constexpr (IN_PARTS) acc[x] = mfma_pack_in_parts<DT, L>(av, b, acc[x]);
             else acc[x] = mfma_pack<DT>(av, b, acc[x]);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -290,7 +290,7 @@ template <int DT, int KW, int SLAB, int NX, bool SHIFTED>
 __global__ __launch_bounds__(64 * KW)
 void spmm_lines_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ slots, const void* __restrict__ vals,
                        const int32_t* __restrict__ perm, const void* __restrict__ B, uint32_t b_bytes, uint32_t ldb_bytes,
-                       uint32_t K, typename Elem<DT>::Out* __restrict__ C, int64_t ldc, int N, int n_order, uint32_t off_dword, int in_quarters)
+                       uint32_t K, typename Elem<DT>::Out* __restrict__ C, int64_t ldc, int N, int n_order, uint32_t off_dword, int in_parts)
 {
     using Acc = typename Elem<DT>::Acc;
     using Out = typename Elem<DT>::Out;
@@ -329,7 +329,9 @@ void spmm_lines_kernel(const int32_t* __restrict__ work, const uint32_t* __restr
     Acc acc[NX];
 #pragma unroll
     for (int x = 0; x < NX; ++x) acc[x] = Acc{0, 0, 0, 0};
-    if ((DT == kE4M3 || DT == kE5M2) && cls == 2 && in_quarters) walk_lines<DT, KW, SLAB, NX, SHIFTED, 8, false, DT == kE4M3 || DT == kE5M2>(w, b_rsrc, acc);
+    constexpr bool PARTS = DT == kE4M3 || DT == kE5M2;
+    if (PARTS && cls == 2 && in_parts) walk_lines<DT, KW, SLAB, NX, SHIFTED, 8, false, PARTS>(w, b_rsrc, acc);
+    else if (PARTS && cls == 1 && in_parts) walk_lines<DT, KW, SLAB, NX, SHIFTED, 4, false, PARTS>(w, b_rsrc, acc);
     else if (cls == 2) walk_lines<DT, KW, SLAB, NX, SHIFTED, 8, false>(w, b_rsrc, acc);
     else if (cls == kEntryClass) walk_lines<DT, KW, SLAB, NX, SHIFTED, 8, true>(w, b_rsrc, acc);
     else if (cls == 1) walk_lines<DT, KW, SLAB, NX, SHIFTED, 4, false>(w, b_rsrc, acc);

@@ -47,13 +47,16 @@ __device__ __forceinline__ typename Elem<DT>::Acc mfma_pack(u32x4 a, u32x4 b, ty
 
 // The matrix units add the products of an 8-bit float instruction below fp32, the less exactly the more of them are not zero: relative error of
 // a product against 64 bits with 6 / 16 / 32 products at a time in e4m3 5.3e-6 / 7.5e-6 / 1.1e-5, in e5m2 - / 6.0e-6 / 8.7e-6.  Here eight at a time: 4.4e-6 and
-// 3.5e-6.  (b too where it may be infinite: infinity times a value taken as zero is NaN.)
-template <int DT>
-__device__ __forceinline__ typename Elem<DT>::Acc mfma_pack_in_quarters(u32x4 a, u32x4 b, typename Elem<DT>::Acc c)
+// 3.5e-6.  L: places of a lane group that a pack fills, 8 in four parts and 4 in two.
+// (b too where it may be infinite: infinity times a value taken as zero is NaN.)
+template <int DT, int L>
+__device__ __forceinline__ typename Elem<DT>::Acc mfma_pack_in_parts(u32x4 a, u32x4 b, typename Elem<DT>::Acc c)
 {
+    static_assert(L == 8 || L == 4, "fewer places are eight products at most");
+    constexpr int PARTS = L / 2, BITS = 32 / PARTS;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        const uint32_t keep = 0xFFu << (8 * h), keep_b = DT == kE5M2 ? keep : 0xFFFFFFFFu;
+    for (int h = 0; h < PARTS; ++h) {
+        const uint32_t keep = (0xFFFFFFFFu >> (32 - BITS)) << (BITS * h), keep_b = DT == kE5M2 ? keep : 0xFFFFFFFFu;
         c = mfma_pack<DT>(u32x4{a[0] & keep, a[1] & keep, 0u, 0u}, u32x4{b[0] & keep_b, b[1] & keep_b, 0u, 0u}, c);
     }
     return c;

@@ -131,7 +131,7 @@ constexpr int kStreamA = 1;        // block values and slot tables are read with
 constexpr int kStreamC = 2;        // C is stored with it
 constexpr int kUnalignedB = 4;     // N, the rows of B or its base are off the load width
 constexpr int kSlabsByXcd = 8;     // a workgroup's slabs go by its XCD (below)
-constexpr int kInQuarters = 16;    // DeviceBcsr::full_packs
+constexpr int kInParts = 16;       // DeviceBcsr::full_packs
 
 // Everything a wave needs to walk its share of a block row.
 struct RowWalk {
@@ -147,7 +147,7 @@ struct RowWalk {
 };
 
 // Per-class pieces shared by the two pipelines below.
-template <int NT, int L, int NCH, int DT, bool ENTRY = false, bool IN_QUARTERS = false>
+template <int NT, int L, int NCH, int DT, bool ENTRY = false, bool IN_PARTS = false>
 struct PackOps {
     using Acc = typename Elem<DT>::Acc;
     static constexpr int ES = Elem<DT>::ES;
@@ -309,7 +309,7 @@ struct PackOps {
                         }
                     }
                 }
-                if constexpr (IN_QUARTERS) acc[c * NT + t] = mfma_pack_in_quarters<DT>(a, b, acc[c * NT + t]);
+                if constexpr (IN_PARTS) acc[c * NT + t] = mfma_pack_in_parts<DT, L>(a, b, acc[c * NT + t]);
                 else acc[c * NT + t] = mfma_pack<DT>(a, b, acc[c * NT + t]);
             }
         }
@@ -322,10 +322,10 @@ struct PackOps {
 // handles two packs and has no exit in the middle (an odd tail multiplies zeros).  The
 // scheduling barriers keep every load ahead of the multiply that precedes its use, and the
 // prologue issues its loads in the order the loop body leaves them in flight.
-template <int NT, int KW, int L, int NCH, int DT, bool ENTRY = false, bool IN_QUARTERS = false>
+template <int NT, int KW, int L, int NCH, int DT, bool ENTRY = false, bool IN_PARTS = false>
 __device__ __forceinline__ void walk_row(const RowWalk& w, __amdgpu_buffer_rsrc_t rsrc, typename Elem<DT>::Acc (&acc)[NCH * NT])
 {
-    using Ops = PackOps<NT, L, NCH, DT, ENTRY, IN_QUARTERS>;
+    using Ops = PackOps<NT, L, NCH, DT, ENTRY, IN_PARTS>;
     if (w.ks >= w.npacks) return;
     const Ops ops(w, rsrc);
     const int count = (w.npacks - w.ks + KW - 1) / KW;     // packs of this wave
@@ -366,10 +366,10 @@ __device__ __forceinline__ void walk_row(const RowWalk& w, __amdgpu_buffer_rsrc_
 // h+1..h+3 and the slot tables of packs h+4..h+6 (pack x has its slot table requested at step
 // x-6, its B rows and values at step x-3) -- about three packs per wave in flight.  The loop
 // body is four steps without an exit; steps past the wave's last pack multiply zeros.
-template <int NT, int KW, int L, int NCH, int DT>
+template <int NT, int KW, int L, int NCH, int DT, bool IN_PARTS = false>
 __device__ __forceinline__ void walk_row_deep(const RowWalk& w, __amdgpu_buffer_rsrc_t rsrc, typename Elem<DT>::Acc (&acc)[NCH * NT])
 {
-    using Ops = PackOps<NT, L, NCH, DT>;
+    using Ops = PackOps<NT, L, NCH, DT, false, IN_PARTS>;
     static_assert(L <= 4, "the deep ring is meant for the sparse classes");
     if (w.ks >= w.npacks) return;
     const Ops ops(w, rsrc);
@@ -679,7 +679,7 @@ void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ 
     if constexpr (LMAX >= 8) {
         if (cls == 2) {
             if constexpr (DT == kE4M3 || DT == kE5M2) {
-                if (hints & kInQuarters) walk_row<NT, KW, 8, NCH, DT, false, true>(w, rsrc, acc);
+                if (hints & kInParts) walk_row<NT, KW, 8, NCH, DT, false, true>(w, rsrc, acc);
                 else walk_row<NT, KW, 8, NCH, DT>(w, rsrc, acc);
             } else {
                 walk_row<NT, KW, 8, NCH, DT>(w, rsrc, acc);
@@ -695,7 +695,14 @@ void spmm_kernel(const int32_t* __restrict__ work, const uint32_t* __restrict__ 
         }
     }
     if constexpr (LMAX >= 4) {
-        if (cls == 1) walk_row_deep<NT, KW, 4, NCH, DT>(w, rsrc, acc);
+        if (cls == 1) {
+            if constexpr (DT == kE4M3 || DT == kE5M2) {
+                if (hints & kInParts) walk_row_deep<NT, KW, 4, NCH, DT, true>(w, rsrc, acc);
+                else walk_row_deep<NT, KW, 4, NCH, DT>(w, rsrc, acc);
+            } else {
+                walk_row_deep<NT, KW, 4, NCH, DT>(w, rsrc, acc);
+            }
+        }
     }
     if (cls == 0) walk_row_deep<NT, KW, 2, NCH, DT>(w, rsrc, acc);
 
@@ -865,7 +872,7 @@ static int launch_variant(const DeviceBcsr& d, const void* B, int64_t ldb, void*
     // then keeps the rows of B.
     int hints = (grid.y == 1 && SW == 1 && static_cast<double>(d.stream_bytes) > 200e6) ? kStreamA : 0;
     if (unaligned) hints |= kUnalignedB;
-    if (d.full_packs) hints |= kInQuarters;
+    if (d.full_packs) hints |= kInParts;
     // A B of about the size of the L2s stays there between its uses only if the write of C does
     // not push it out: then C is stored past the cache (measured: -7 % where B is 4 MiB, no gain
     // or a loss where B is 16 MiB and more).

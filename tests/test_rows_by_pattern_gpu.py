@@ -83,9 +83,12 @@ def test_products_and_exports(shape, dtype, oracle_c):
 @pytest.mark.parametrize("N", [3, 33, 64, 91, 128, 300, 512])
 def test_full_packs_of_8_bit_floats_add_no_less_exactly(dtype, N):
     """A pack with a product in every slot: the instruction's error against 64 bits is 1.1e-5 / 8.7e-6 (e4m3 / e5m2) with 32 products at a time and
-    7.5e-6 / 6.0e-6 with sixteen; the packs of the clustering's order had 5e-6 - 9e-6.  At most eight stay below 5e-6 (4.6e-6 and 3.6e-6 measured)."""
+    7.5e-6 / 6.0e-6 with sixteen; the packs of the clustering's order had 5e-6 - 9e-6.  At most eight stay below 5e-6 (4.6e-6 and 3.6e-6 measured).
+    Rows of one hidden block, whose packs have sixteen places, rows of two and rows of more are looked at apart: with sixteen products 7.3e-6 - 8.6e-6
+    and 5.8e-6 - 7.1e-6, with eight 3.5e-6 - 5.1e-6 and 2.8e-6 - 5.1e-6 (of a few hundred rows, grids of 128 and 150, N = 64 - 512)."""
     import torch
     w = _hidden(150, 0, 8, seed=N)
+    blocks = torch.from_numpy(np.diff(w.row_ptr) // 16)
     gen = torch.Generator().manual_seed(N)
     kind = torch.float8_e4m3fn if dtype == "e4m3" else torch.float8_e5m2
     vals = (torch.randn(w.col_idx.size, generator=gen) * 0.25).to(kind)
@@ -96,6 +99,9 @@ def test_full_packs_of_8_bit_floats_add_no_less_exactly(dtype, N):
     ref = dense @ b.double()
     out = m.spmm(b.view(torch.uint8).cuda()).cpu().double()
     assert (out - ref).norm() < 5e-6 * ref.norm(), (S.smat_last_kernel(), (out - ref).norm() / ref.norm())
+    for some in (blocks == 1, blocks == 2, blocks > 2):
+        error = (out - ref)[some].norm() / ref[some].norm()
+        assert some.sum() >= 32 and error < 5.5e-6, (S.smat_last_kernel(), error)
     if dtype == "e5m2":                             # infinity times the values of its column, not times what stands for them in the other quarters
         b[5, N - 1] = float("inf")
         out = m.spmm(b.view(torch.uint8).cuda()).cpu()[:, N - 1]
