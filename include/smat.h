@@ -156,7 +156,8 @@ smat_status_t smat_device_bytes(const smat_handle_t *h, size_t *bytes);
  * is kept by entry instead: packs of 32 stored entries, one value and one
  * named row of B per entry, expanded into the instruction's operand in registers.
  * The rows are taken in the order of perm -- unless rows with the same block columns, which the clustering may leave
- * mixed with others, put together name a tenth fewer rows of B: then in that order, which the other exports do not show.
+ * mixed with others, put together name a tenth fewer rows of B: then in that order, which the other exports do not show
+ * (not for 8-bit floats where it would have block-dense regions).
  *   n_packs       packs of the whole matrix
  *   value_bytes   bytes of block values over all packs
  *   table_bytes   bytes of the per-pack tables naming the rows of B, plus the

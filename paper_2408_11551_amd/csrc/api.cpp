@@ -210,6 +210,12 @@ void plan_dense_tiles(smat_handle& h, smat::Workers& workers)
     const int64_t nbr = b.nbr;
     h.row_dense.assign(static_cast<size_t>(nbr), 0);
     h.step_ptr.assign(1, 0);
+    h.dense_super.clear();
+    h.step_cols.clear();
+    h.step_rows.clear();
+    h.step_base.clear();
+    h.dense_slots = 0;
+    h.dense_columns = 0;
     h.dense_all_full = false;
     if (h.dense_mode < 0) return;
     h.dense_all_full = true;             // until a step says otherwise
@@ -606,12 +612,18 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
             h->cols_permuted = smat::reorder_columns(h->csr, o.tau_permille, h->bcsr, workers);
             if (h->cols_permuted) h->dense_mode = -1;
         }
+        plan_dense_tiles(*h, workers);
+        // Rows by pattern bring a product into every place of the tile kernels' instructions, which then add 8-bit floats less exactly than in the
+        // clustering's order (the per-row kernels multiply such packs in parts): these types keep that order where there would be tiles.
+        if (h->bcsr.grouped && (dtype == SMAT_E4M3 || dtype == SMAT_E5M2) && !h->dense_super.empty()) {
+            h->bcsr.grouped.reset();
+            plan_dense_tiles(*h, workers);
+        }
         try {
             plan_packs(*h, workers);
         } catch (const std::length_error& e) {
             return fail(SMAT_ERR_UNSUPPORTED, e.what());
         }
-        plan_dense_tiles(*h, workers);
         plan_quads(*h, workers);
         *out = h.release();
         return SMAT_OK;
