@@ -13,6 +13,7 @@
 
 #include "../../include/smat.h"
 #include "../../paper_2408_11551_amd/csrc/kernels.h"
+#include "../../paper_2408_11551_amd/csrc/lines_rule.h"
 
 namespace {
 
@@ -192,11 +193,37 @@ void every_block_row_is_covered()
                 }
 }
 
+// The gather through LDS names rows that are not there by the offset 2^31: past the end of any B it may be given, from the dword on in which B begins.
+void no_gather_past_the_range()
+{
+    smat::DeviceBcsr d;
+    d.n_order = 1000;
+    d.mean_row_packs = 10.0;
+    d.max_row_packs = 10;
+    d.max_class = 2;
+    int met = 0;
+    for (int es : {1, 2})
+        for (uintptr_t off = 0; off < 4; off += static_cast<uintptr_t>(es))
+            for (d.K = 260; d.K < 400; ++d.K) {
+                const void* const B = reinterpret_cast<const void*>(uintptr_t{0x10000000} + off);
+                const int64_t most = ((int64_t{1} << 31) - 1) / es, ldb = (most - 33) / (d.K - 1);
+                for (int64_t elements = most - 3; elements <= most; ++elements) {
+                    const int64_t n = elements - (d.K - 1) * ldb;
+                    if (n * es > 124 || (static_cast<int64_t>(off) + elements * es + 3) / 4 * 4 <= int64_t{1} << 31) continue;
+                    expect(!smat::takes_lines(d, es, B, ldb, n), "a B that ends past 2^31 bytes from its first dword");
+                    ++met;
+                }
+                expect(smat::takes_lines(d, es, B, ldb / 2, 60 / es), "one well inside");
+            }
+    expect(met > 0, "the limit is met");
+}
+
 }  // namespace
 
 int main()
 {
     every_block_row_is_covered();
+    no_gather_past_the_range();
     for (int dense_tiles : {-1, 1}) {
         std::vector<char> workspace;
         smat_handle_t* h = make(2, dense_tiles, workspace);
