@@ -1,6 +1,7 @@
 // HIP kernels for gfx950 (CDNA4, wave64): device-side BCSR value fill and the 16-bit
 // instantiations (fp16, bf16) of the per-row SpMM kernel (spmm_rows.h); the 8-bit ones are
 // in kernels_8bit.hip.
+#include "lines_rule.h"
 #include "spmm_rows.h"
 
 namespace smat {
