@@ -1040,24 +1040,31 @@ double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
 }
 
 // The same on the per-row kernels, fitted on these products and 1000 more (within 11-16 %; up to 128 bytes of a row of B 7-12 %): rows of B by the byte and by
-// the 256-byte slab, values, C; rows of B on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes
-// (kernels_lines.hip) on dwords and off them.
-double rows_us(const smat_handle& h, int64_t N, int64_t ldb)
+// the 256-byte slab, values, C; rows of B that begin on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes, where
+// mostly kernels_lines.hip runs, on dwords and off them.
+// Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
+// four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, now 0.87-0.92, and on dwords, where a row
+// reaches into a line more, 0.83-0.92 either way.)
+double rows_us(const smat_handle& h, const void* dB, int64_t ldb, int64_t N)
 {
     struct Cost { double start, gather, slab, values, write; };
     static constexpr Cost kCosts[2][6] = {{{3.35, 0.003, 12.3, 0.026, 0.24}, {3.7, 0.021, 9.5, 0.0, 0.06}, {3.55, 0.007, 12.65, 0.0, 0.21}, {7.7, 0.0, 13.6, 0.32, 0.6},
                                            {2.9, 0.05, 0.94, 0.06, 0.0}, {2.8, 0.11, 1.5, 0.0, 0.55}},
                                           {{3.7, 0.0, 14.4, 0.09, 0.37}, {4.6, 0.017, 11.2, 0.013, 0.28}, {4.15, 0.012, 12.3, 0.0, 0.36}, {6.0, 0.0, 17.2, 0.57, 0.5},
                                            {3.35, 0.064, 0.0, 0.06, 0.0}, {4.35, 0.104, 1.05, 0.0, 0.0}}};
-    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256, row_bytes = ldb * h.elem_bytes;
-    const bool on_dwords = row_bytes % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - h.elem_bytes) <= 128;
-    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : row_bytes % 128 == 0 ? 0 : row_bytes % 16 == 0 ? 1 : on_dwords ? 2 : 3];
+    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256;
     const double m_rows = static_cast<double>(h.b_rows) * 1e-6;
     // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
     const double groups = static_cast<double>(h.bcsr.nbr) * static_cast<double>(slabs) / 256.0;
     const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
-    const double row = std::min(c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs), 0.14 * static_cast<double>(bytes));
-    return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
+    auto us_of = [&](int64_t starts) {
+        const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - h.elem_bytes) <= 128;
+        const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
+        const double row = std::min(c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs), 0.14 * static_cast<double>(bytes));
+        return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
+    };
+    const int64_t distance = ldb * h.elem_bytes;
+    return std::max(us_of(distance), us_of(distance | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))));
 }
 
 // smat_spmm with the area for partial tiles given by the caller of this function.
@@ -1103,7 +1110,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // It also has to pay: few tiles leave most of the chip idle, while the per-row kernel fetches every occupied column's row
     // of B again for every block row but spreads that over all compute units.  The estimates are measured rates, fitted on
     // bands and random matrices of 1000 ... 65536 rows and 5-100 % fill at N = 8 ... 2048, 16-bit and 8-bit; the faster path is taken.
-    const bool off_dwords = ((ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))) % 4 != 0;
+    const int64_t starts = (ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB));
+    const bool off_dwords = starts % 4 != 0;
     if (use_tiles && h->dense_mode == 0 && tiles.n_quad_steps > 0 && !hard_limit) {
         // On quads the shape is chosen too: narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
         // a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
@@ -1132,7 +1140,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         }
         take(best_shape, best_tail);
         const FewColumns few = few_columns(*h, N, off_dwords);
-        use_tiles = 1.08 * best + 0.5 <= rows_us(*h, N, ldb) && !(few.take() && few.quads_us < best);
+        use_tiles = 1.08 * best + 0.5 <= rows_us(*h, dB, ldb, N) && !(few.take() && few.quads_us < best);
     } else if (use_tiles && h->dense_mode == 0) {
         double t_tiles = 0;
         for (int64_t c0 = 0; c0 < N; c0 += chunk) {
@@ -1151,7 +1159,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         // they lie off the cache lines), values and C at 7
         const double pieces = static_cast<double>(h->dense_columns) * static_cast<double>((N + 15) / 16 * 16 * h->elem_bytes);
         const double groups = static_cast<double>(h->bcsr.nbr) * static_cast<double>((N * h->elem_bytes + 255) / 256);
-        const double rate = (h->elem_bytes == 2 ? 22.0e6 : N > 128 ? 19.0e6 : 13.0e6) * ((ldb * h->elem_bytes) % 128 == 0 ? 1.0 : 0.75);
+        const double rate = (h->elem_bytes == 2 ? 22.0e6 : N > 128 ? 19.0e6 : 13.0e6) * (starts % 128 == 0 ? 1.0 : 0.75);
         const double t_rows = 4.0 + pieces / rate * std::max(1.0, 256.0 / groups) +
                               (static_cast<double>(h->dense_columns) * 16.0 * h->elem_bytes + static_cast<double>(h->csr.M) * N * 4.0) / 7.0e6;
         use_tiles = t_tiles <= t_rows;
@@ -1218,7 +1226,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         name = std::string(dense_variant) + (in_pieces ? "" : "_staged") + (rest ? std::string("+") + variant : std::string());
         g_kernel = name.c_str();
     } else {
-        const bool lines = (ldb * h->elem_bytes) % 128 == 0 && reinterpret_cast<uintptr_t>(dB) % 128 == 0;
+        const bool lines = starts % 128 == 0;
         const Staging st = !lines && scratch && rows_stage(*h, N) ? plan_staging() : Staging{0, 0, 0};
         if (st.chunk > 0) {
             for (int64_t c0 = 0; c0 < N && !e; c0 += st.chunk) {

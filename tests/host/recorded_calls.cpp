@@ -19,7 +19,7 @@ namespace {
 
 struct Event { bool copy; const void* from; const void* to; const void* stream; };     // a copy of B: B, area; a product: its B, C
 int64_t g_block_rows = 0;                // that the launches cover, those of the tiles counted once per range of columns
-bool g_on_quads = false;
+bool g_on_quads = false, g_tiles = false;
 std::mutex g_mutex;
 std::vector<Event> g_events;
 hipStream_t g_capturing = nullptr;
@@ -95,6 +95,7 @@ int launch_spmm_dense(const DeviceBcsr&, const DenseTiles& t, int, const void* B
     // (tiles of a last super row that is not complete reach past its block rows)
     const int64_t per_tile = quad_shape_rows(t.quad_shape) / 16, tail = quad_row_tiles(t) * per_tile - 16 * int64_t{t.n};
     g_on_quads = t.n_quad_steps > 0;
+    g_tiles = true;
     g_block_rows += 16 * int64_t{t.n} + std::min<int64_t>(tail, t.quad_tail_rows);
     record(false, B, C, stream);
     *variant = "tiles";
@@ -193,6 +194,26 @@ void every_block_row_is_covered()
                 }
 }
 
+// Tiles or rows goes by where the rows of B begin, be it that their distance or that the first one is off the dwords.
+void choice_follows_alignment()
+{
+    std::vector<char> workspace;
+    smat_handle_t* h = make(2, 0, workspace);
+    auto tiles = [&](int64_t n, int64_t ldb, uintptr_t past) {
+        g_tiles = false;
+        g_events.clear();
+        expect(smat_spmm(h, reinterpret_cast<const void*>(uintptr_t{0x20000000} + past), ldb, operand_c(1), n, n, nullptr) == SMAT_OK, "status of a call");
+        return g_tiles;
+    };
+    int taken = 0;
+    for (int64_t n = 33; n < 1000; n += 6) {
+        taken += tiles(n, 1025, 0);
+        if (tiles(n, 1024, 2) != tiles(n, 1025, 0)) std::printf("N = %d off the dwords\n", static_cast<int>(n)), ++g_wrong;
+    }
+    expect(taken > 0 && taken < 162, "some of these go to tiles and some do not");
+    smat_destroy(h);
+}
+
 // The gather through LDS names rows that are not there by the offset 2^31: past the end of any B it may be given, from the dword on in which B begins.
 void no_gather_past_the_range()
 {
@@ -224,6 +245,7 @@ int main()
 {
     every_block_row_is_covered();
     no_gather_past_the_range();
+    choice_follows_alignment();
     for (int dense_tiles : {-1, 1}) {
         std::vector<char> workspace;
         smat_handle_t* h = make(2, dense_tiles, workspace);
