@@ -9,6 +9,12 @@
 namespace smat {
 
 // es: bytes of an element of B
+//
+// The lines below were drawn on 1381 products of random, graph, band, hidden-block and pruned matrices (1000 ... 262144 rows, 33 ... 2200 bytes of a row of
+// B, all types) and looked at on 1387 others and 652 of mostly wider B (to 8192 bytes): profiles/lines_rule.csv, which tests/test_lines_rule.py goes
+// over.  Of all of them, the geometric mean of the times over the faster kernel's is 1.019, over the registers' 0.894 (everything here: 0.914); 81
+// products are more than 5 % slower than on registers, 28 of them more than 10 %, at most 1.34.  (The rule before, whose lines were drawn between single
+// products: 1.047, 0.919; 164, 84, 1.39.)
 inline bool takes_lines(const DeviceBcsr& d, int es, const void* B, int64_t ldb, int64_t N)
 {
     const int64_t bytes = N * es, starts = (ldb * es) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(B));
@@ -17,49 +23,34 @@ inline bool takes_lines(const DeviceBcsr& d, int es, const void* B, int64_t ldb,
     // rows that are not there are named by the offset 2^31, which has to lie past the end of B (from the dword on in which it begins)
     const int64_t ends = static_cast<int64_t>(reinterpret_cast<uintptr_t>(B) & 3u) + ((d.K - 1) * ldb + N) * es;
     if ((ends + 3) / 4 * 4 > (int64_t{1} << 31)) return false;
-    const bool entries = d.max_class == kEntryClass, on_lines = starts % 128 == 0;
-    const int64_t span = bytes + (starts % 4 == 0 ? 0 : 4 - es);
-    // A single slab is faster there nearly throughout.  (us here and there.  On lines: 2048 block rows of 21 packs, N = 64 in fp16 19.1, 17.4, N = 128 in e4m3 20.5,
-    // 15.9; a graph of 65536 rows, N = 64 15.9, 14.2, N = 32 11.5, 8.5.  On dwords: 50021 rows of a band, N = 34 in bf16 7.4, 5.8; the graph, N = 24 11.4, 8.9;
-    // 1117 block rows of 38, N = 100 in e4m3 26.9, 24.2.  Off them: the band, N = 17 6.4, 4.7, N = 33 8.6, 6.7, N = 63 9.2, 7.2, N = 91 in int8 8.0, 8.0; the graph, N = 33 17.4,
-    // 14.0; 1117 of 38, N = 33 in fp16 31.9, 24.8, N = 65 in e4m3 34.8, 25.9.)  Not for short rows kept by entry across a whole line of
-    // bytes, with a slab of more than an L2 holds: 60000 rows of 10 entries, N = 128 in e5m2 13.3, 14.4.
-    // Nor off the dwords, where moving what a row is shifted by takes its time: for a few long rows (69 block rows of 51 packs, N = 33 in fp16 6.1, 6.9, N = 90 in
-    // e4m3 6.0, 8.0), for columns that just miss half a line (2048 block rows of 8, N = 63 in e4m3 7.0, 8.1), and for such short rows on pairs of bytes (60000 of
-    // 10, N = 110 in int8 18.1, 20.1).
-    if (span <= 128) {
-        const bool short_rows = es == 1 && entries && d.mean_row_packs < 6.0 && static_cast<double>(d.K) * 128.0 >= 6.0e6;
-        if (starts % 4 == 0) return !(short_rows && on_lines && bytes > 112);
-        return !(d.n_order < 100 && d.mean_row_packs >= 32.0) && !(es == 1 && span > 64 && bytes <= 64) && !(short_rows && starts % 2 == 0 && bytes > 96);
+
+    const bool on_dwords = starts % 4 == 0;
+    const int64_t slabs = (bytes + (on_dwords ? 0 : 4 - es) + 127) / 128, units = d.n_order * slabs;
+    const double rows = static_cast<double>(d.b_rows), uses = rows / static_cast<double>(d.K);              // uses: of a row of B
+    const double mb = 1.0e-6 * static_cast<double>(bytes), slab_mb = 128.0e-6 * static_cast<double>(d.K);    // of a row; of one slab of all rows
+    // A single slab on dwords is faster here nearly throughout: 0.87 of the time in the mean of 701 products, three more than 1.1 and at most 1.22.
+    if (slabs == 1 && on_dwords) return true;
+    // Off them what a row is shifted by is moved, which a launch of few packs does not hide, and in the 8-bit types neither do short rows (us on registers, here: 283
+    // block rows of 3 packs, N = 55 in fp16 4.6, 5.7; 273 of 4, N = 103 in int8 4.2, 5.8; 1179 of 2, N = 71 in e4m3 4.8, 5.7; but 395 of 9, N = 30 4.1, 3.4).
+    // Nor is it worth a whole line for columns that just miss half of one (N = 62 ... 64 in bytes: 0.88 ... 1.34 of the time).  Fewer than 128 block rows go either way
+    // (65 ... 101 of 2 ... 38 packs, N = 17 ... 125: 0.73 ... 1.28).
+    const bool few = !on_dwords && d.n_order < 128;
+    if (slabs == 1) return !(es == 1 && bytes > 61 && bytes <= 64) && (few || (d.n_packs > 2300 && (es == 2 || d.mean_row_packs > 4.0 || d.n_order > 1900)));
+    if (starts % 128 == 0) {
+        // Several slabs on whole lines.  8-bit types, whose operands cost the other kernel more: throughout, 0.81 of the time, but where many units gather little each (bands of
+        // 1087 block rows of 4 packs, N = 743 18.4, 24.1) unless C is large, which is stored past the caches here (3042 of 3, N = 640 45.2, 31.5), and
+        // not for a slab that no L2 holds any of (239562 rows of a graph, N = 193 154, 179).
+        if (es == 1) return slab_mb <= 16.0 && (uses > 6.0 || units <= 2800 || mb * static_cast<double>(d.K) > 16.0);
+        // 16-bit types read A twice as often here as the other kernel does: where rows of B come from all over, and not for rows as long as those of pruned weights (114 block rows of 230 packs, N = 232
+        // 25.3, 30.9; but 2701 of 23, N = 704 234, 167), or few packs in all.
+        return (d.spread && uses <= 60.0 && slab_mb <= 16.0) || d.n_packs * slabs <= 4000;
     }
-    // Several slabs off the lines are two lines of most rows each: only where one slab of all rows is well inside an L2 (us here and there, inputs not in the caches: 14000 rows of 20 entries, N = 160 in fp16 14.9, 11.7, N = 559 44.9, 38.1, in e4m3
-    // 29.5, 27.2, N = 144 15.2, 10.9; 24000 of 16, N = 332 in int8 25.6, 24.2, but 40000 42.9, 50.8, and in fp16 30000 of 16, N = 134 21.3, 29.4; 400 x 400 hidden blocks,
-    // N = 160 in fp16 7.0, 6.1, but 1000 x 1000, N = 134 16.3, 18.3).
-    const int64_t slabs = (bytes + 127) / 128;
-    const double packs = d.mean_row_packs;
-    if (!on_lines) {
-        const double narrow_slab = static_cast<double>(d.K) * 128.0;
-        // (how far the other kernel's wider slabs, of loads as wide as it can, are behind: 9029 rows of 20, N = 332 in e4m3 17.3, 11.7, N = 668 16.4, 19.3)
-        const int64_t most = es == 1 ? (starts % 16 == 0 ? 4 : starts % 4 == 0 ? 3 : 5) : (starts % 16 == 0 ? 4 : starts % 4 == 0 ? 5 : 10);
-        if (slabs > most || packs >= (entries ? (es == 1 ? 16.0 : 12.0) : 14.0)) return false;
-        return es == 1 ? narrow_slab <= 3.1e6 : d.spread && narrow_slab <= (entries ? 1.9e6 : 1.0e6);
-    }
-    // They read A once for each, where the other kernel's are twice as wide, and rows kept by entry are expanded once for each; what they save is what
-    // one slab less would have found in the L2s, and half-empty slabs.  (us here and there, inputs not in the caches:)
-    // 8-bit types, whose operands cost the other kernel more: faster throughout.  14000 rows of 16 entries, N = 256 15.3, 9.0, N = 1024 27.7, 22.2; 7000 of 30
-    // 16.8, 11.7 at N = 512; a band of 201, N = 256 7.3, 5.4; 2048 x 2048 hidden blocks, N = 256 30.6, 26.7.
-    // 16-bit types, rows by column: where rows of B come from all over.  627 block rows of 7 packs, N = 1024 33.3, 26.0; 1117 of 12, N = 512 39.5, 38.0; but
-    // 1700 of 17, N = 256 39.1, 43.2, and bands of 81 and 257 columns 24.1, 26.4 and 15.7, 17.3.
-    // By entry: short rows throughout (18000 of 12, N = 256 13.7, 11.8; 7000 of 6, N = 1024 13.7, 11.4; 2000 of 6 5.1, 5.5), longer ones in few slabs or where a
-    // wide slab does not fit an L2 (16384 of 16, N = 128 10.2, 8.9, N = 384 17.0, 15.7, N = 512 23.1, 23.3; 30000 of 16 49.7, 39.8), the longest
-    // also in three, of which the other kernel's last is half empty (12000 of 50, N = 192 24.5, 19.4, N = 512 41.1, 43.7; 40000 of 30, N = 256 53.5, 44.3; 24000
-    // of 30 25.3, 28.3).
-    const double wide_slab = static_cast<double>(d.K) * 256.0;
-    if (es == 1) return packs < (entries ? 16.0 : 14.0) && (slabs <= 8 || !entries || wide_slab >= 5.0e6);
-    if (!d.spread) return false;
-    if (!entries) return packs < 14.0;
-    if (packs < 12.0) return slabs <= (packs < 7.0 ? 16 : 6) || wide_slab >= 5.0e6;
-    return slabs == 3 ? packs < 30.0 : packs < 16.0 && wide_slab >= (slabs == 2 ? 5.0e6 : 8.0e6);
+    // Several slabs off the lines are two lines of most rows each: where a slab of all rows, or what is gathered, is well inside an L2 (24000 rows of 16, N = 332 in int8
+    // 25.6, 24.2, but 40000 42.9, 50.8; 30000 of 16, N = 134 in fp16 21.3, 29.4; 400 x 400 hidden blocks, N = 160 in fp16 7.0, 6.1, but 1000 x 1000, N = 134
+    // 16.3, 18.3; a graph of 21397 rows, N = 131 in e4m3 off the dwords 18.7, 23.2).
+    if (on_dwords) return uses <= 60.0 && (es == 1 ? slab_mb <= 3.0 && (d.spread || uses > 6.0) : d.spread && rows * mb <= 36.0);
+    if (es == 1) return slab_mb <= 0.43 || (slab_mb <= 2.0 && uses > 6.0 && bytes > 142 && rows * mb <= 170.0);
+    return (d.spread && slabs > 4 && slab_mb <= 1.3) || (slab_mb <= 0.6 && (few || rows * mb > 4.0));
 }
 
 }  // namespace smat
