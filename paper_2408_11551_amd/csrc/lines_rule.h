@@ -11,10 +11,10 @@ namespace smat {
 // es: bytes of an element of B
 //
 // The lines below were drawn on 1381 products of random, graph, band, hidden-block and pruned matrices (1000 ... 262144 rows, 33 ... 2200 bytes of a row of
-// B, all types) and looked at on 1387 others and 652 of mostly wider B (to 8192 bytes): profiles/lines_rule.csv, which tests/test_lines_rule.py goes
-// over.  Of all of them, the geometric mean of the times over the faster kernel's is 1.019, over the registers' 0.894 (everything here: 0.914); 81
-// products are more than 5 % slower than on registers, 28 of them more than 10 %, at most 1.34.  (The rule before, whose lines were drawn between single
-// products: 1.047, 0.919; 164, 84, 1.39.)
+// B, all types) and looked at on 1387 others, 652 of mostly wider B (to 8192 bytes) and 477 of the largest: profiles/lines_rule.csv, which
+// tests/test_lines_rule.py goes over.  Of all of them, the geometric mean of the times over the faster kernel's is 1.020, over the registers' 0.886
+// (everything here: 0.901); 78 products are more than 5 % slower than on registers, 29 of them more than 10 %, at most 1.34.  (The rule before, whose lines
+// were drawn between single products: 1.050, 0.912; 165, 85, 1.39.)
 inline bool takes_lines(const DeviceBcsr& d, int es, const void* B, int64_t ldb, int64_t N)
 {
     const int64_t bytes = N * es, starts = (ldb * es) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(B));
@@ -41,9 +41,11 @@ inline bool takes_lines(const DeviceBcsr& d, int es, const void* B, int64_t ldb,
         // 1087 block rows of 4 packs, N = 743 18.4, 24.1) unless C is large, which is stored past the caches here (3042 of 3, N = 640 45.2, 31.5), and
         // not for a slab that no L2 holds any of (239562 rows of a graph, N = 193 154, 179).
         if (es == 1) return slab_mb <= 16.0 && (uses > 6.0 || units <= 2800 || mb * static_cast<double>(d.K) > 16.0);
-        // 16-bit types read A twice as often here as the other kernel does: where rows of B come from all over, and not for rows as long as those of pruned weights (114 block rows of 230 packs, N = 232
-        // 25.3, 30.9; but 2701 of 23, N = 704 234, 167), or few packs in all.
-        return (d.spread && uses <= 60.0 && slab_mb <= 16.0) || d.n_packs * slabs <= 4000;
+        // 16-bit types read A twice as often here as the other kernel does: where rows of B come from all over, of rows kept by column only as long as a slab leaves an L2
+        // room (2048 x 2048 hidden blocks, N = 256 47, 63, but 956 x 956, N = 960 59, 47), and not for rows as long as those of pruned weights (114 block rows of
+        // 230 packs, N = 232 25.3, 30.9); or few packs in all.
+        const double most_mb = d.max_class == kEntryClass ? 16.0 : 3.0;
+        return (d.spread && uses <= 60.0 && slab_mb <= most_mb) || d.n_packs * slabs <= 4000;
     }
     // Several slabs off the lines are two lines of most rows each: where a slab of all rows, or what is gathered, is well inside an L2 (24000 rows of 16, N = 332 in int8
     // 25.6, 24.2, but 40000 42.9, 50.8; 30000 of 16, N = 134 in fp16 21.3, 29.4; 400 x 400 hidden blocks, N = 160 in fp16 7.0, 6.1, but 1000 x 1000, N = 134
