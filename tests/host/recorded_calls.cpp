@@ -219,6 +219,8 @@ void no_gather_past_the_range()
 {
     smat::DeviceBcsr d;
     d.n_order = 1000;
+    d.n_packs = 10000;
+    d.b_rows = 320000;
     d.mean_row_packs = 10.0;
     d.max_row_packs = 10;
     d.max_class = 2;
