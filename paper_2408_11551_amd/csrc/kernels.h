@@ -89,6 +89,18 @@ inline int64_t quad_row_tiles(const DenseTiles& t)
 
 constexpr double kDeepSteps = 32.0;        // mean_steps from which two wave groups share a tile
 
+// Into how many parts the steps of every tile (256 x 128) could be split for one workgroup per compute unit.
+inline int dense_parts(const DenseTiles& t, int64_t N)
+{
+    const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
+    if (tiles <= 0 || tiles > 128 || t.scratch == nullptr || t.quad_shape != kQuad256x128 || t.quad_tail_tiled) return 1;
+    int64_t ks = 256 / tiles < 8 ? 256 / tiles : 8;
+    const int64_t by_steps = static_cast<int64_t>(t.mean_steps / 8.0), by_room = static_cast<int64_t>(t.scratch_bytes / (static_cast<size_t>(tiles) * 256 * 128 * 4));
+    ks = ks < by_steps ? ks : by_steps;
+    ks = ks < by_room ? ks : by_room;
+    return ks < 2 ? 1 : static_cast<int>(ks);
+}
+
 // Sets n16 16-byte words at dst to zero.
 int launch_fill_zero(void* dst, size_t n16, void* stream);
 

@@ -580,15 +580,12 @@ int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem
 int dense_split(const DenseTiles& t, int64_t N)
 {
     const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
-    if (tiles <= 0 || tiles > 128 || t.scratch == nullptr || t.quad_shape != kQuad256x128 || t.quad_tail_tiled) return 1;
-    int64_t ks = std::min<int64_t>(8, 256 / tiles);
-    ks = std::min<int64_t>(ks, static_cast<int64_t>(t.mean_steps / 8.0));
-    ks = std::min<int64_t>(ks, static_cast<int64_t>(t.scratch_bytes / (static_cast<size_t>(tiles) * 256 * 128 * 4)));
+    int64_t ks = dense_parts(t, N);
     // An XCD has an eighth of the tiles, rounded up, and 32 compute units: one workgroup more and the launch takes two rounds (81 tiles
     // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps leave room for two workgroups.
     if (t.mean_steps >= kDeepSteps)
         while (ks > 1 && (tiles + 7) / 8 * ks > 32) --ks;
-    return ks < 2 ? 1 : static_cast<int>(ks);
+    return static_cast<int>(ks);
 }
 
 template <int DT>

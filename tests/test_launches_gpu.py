@@ -35,6 +35,19 @@ def test_tile_kernel_without_quads_every_tail_of_its_step_loop(dtype, steps, ora
     m.close()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "e4m3", "i8"])
+@pytest.mark.parametrize("case", [(2304, 6000, 1152), (1792, 6000, 896)], ids=str)
+def test_long_tiles_that_are_split_go_before_rows(case, dtype):
+    """81 and 49 tiles of 94 ... 188 steps at 50 % fill, in as many parts as an XCD's compute units take at a time: 31 ... 45 us, block rows 43 ... 70."""
+    M, K, N = case
+    w = random_csr(M, K, 8, 0.5, seed=M, values="ones")
+    w = w if dtype == "f16" else recast(w, dtype)
+    m = S.SmatMatrix(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, dtype, reorder=0)
+    m.spmm(torch.zeros((K, N), dtype=torch.int16 if dtype == "f16" else torch.uint8, device="cuda"))
+    assert S.smat_last_launches()[0] == "tiles+sum_tiles"
+    m.close()
+
+
 def test_launches_of_other_products():
     w = random_csr(300, 700, 33, 0.02, seed=1, dtype="bf16")
     m = S.SmatMatrix(w.M, w.K, w.row_ptr, w.col_idx, w.a_bits, w.dtype)
