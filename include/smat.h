@@ -157,7 +157,7 @@ smat_status_t smat_device_bytes(const smat_handle_t *h, size_t *bytes);
  * named row of B per entry, expanded into the instruction's operand in registers.
  * The rows are taken in the order of perm -- unless rows with the same block columns, which the clustering may leave
  * mixed with others, put together name a tenth fewer rows of B: then in that order, which the other exports do not show
- * (not for 8-bit floats where it would have block-dense regions).
+ * (block-dense tiles keep the order of perm).
  *   n_packs       packs of the whole matrix
  *   value_bytes   bytes of block values over all packs
  *   table_bytes   bytes of the per-pack tables naming the rows of B, plus the
@@ -214,9 +214,8 @@ smat_status_t smat_export_device_vals(const smat_handle_t *h, void *vals, void *
  * of them needs, most by stored zeros, and zero times infinity is NaN.  A non-finite element in row k and column n
  * of B therefore reaches column n of C in the rows that store column k (an infinity as what arithmetic gives, or as
  * NaN where a block row is kept by entry), and as a NaN it may also reach the other
- * rows of their group: with dense_tiles = -1 the sixteen rows of a block row, otherwise the 256 rows perm[256 s] ... perm[256 s + 255]
- * of a group s of which any row stores an entry in block column k / 16 (groups in the order of rows that
- * smat_get_layout_info describes).  Rows of other groups and the other columns of C are not affected.
+ * rows of their group: the sixteen rows of a block row in the order that smat_get_layout_info describes, and unless dense_tiles = -1
+ * the 256 rows perm[256 s] ... perm[256 s + 255] of a group s of which any row stores an entry in block column k / 16.  Rows of other groups and the other columns of C are not affected.
  * Limits: the bytes of B that are addressed, ((K-1)*ldb + N) * bytes per value, must stay below 2 GiB;
  * ldb < 2^23; N <= 1048560.
  */

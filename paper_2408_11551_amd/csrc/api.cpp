@@ -29,7 +29,7 @@ constexpr int kMaxAreas = 16;            // option concurrent_streams at most
 struct smat_handle {
     smat::Csr csr;
     smat::Bcsr bcsr;                     // what the caller sees
-    const smat::Bcsr& layout() const { return bcsr.grouped ? *bcsr.grouped : bcsr; }      // what everything below is made from
+    const smat::Bcsr& layout() const { return bcsr.grouped ? *bcsr.grouped : bcsr; }      // what the block rows are made from; tiles and quads are from bcsr
     smat_dtype_t dtype = SMAT_F16;
     int elem_bytes = 2;                  // bytes per stored value of A and B: 2, or 1 for the 8-bit types
     int dense_mode = 0;                  // option dense_tiles
@@ -75,6 +75,7 @@ struct smat_handle {
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
     smat::DeviceBcsr dev;                // launch over every block row
     smat::DeviceBcsr dev_rest;           // launch over the block rows the dense path does not cover
+    smat::DeviceBcsr dev_tiles;          // what the tile kernels take: dev, with the rows in the order of bcsr
     smat::DenseTiles tiles;
     // device copies of the CSR (kept: they live in the caller's workspace anyway)
     const int64_t* d_csr_row_ptr = nullptr;
@@ -149,7 +150,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t perm, work, work_rest, slots, vals, pack_ptr, slots_off, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
     size_t csr_row_ptr, csr_col_idx, csr_vals, col_perm;
-    size_t t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, tables_end, total;
+    size_t t_perm, t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, tables_end, total;
 };
 
 Layout make_layout(const smat_handle& h)
@@ -170,6 +171,7 @@ Layout make_layout(const smat_handle& h)
     l.blk_ptr = take((nbr + 1) * sizeof(int32_t));
     l.csr_row_ptr = take((static_cast<size_t>(h.csr.M) + 1) * sizeof(int64_t));
     l.col_perm = take(h.cols_permuted ? static_cast<size_t>(h.csr.K) * sizeof(int32_t) : 0);
+    l.t_perm = take(h.bcsr.grouped && !h.dense_super.empty() ? (nbr + 15) / 16 * 256 * sizeof(int32_t) : 0);
     l.t_super = take((h.dense_super.size() + static_cast<size_t>(h.quad_tail)) * sizeof(int32_t));
     const size_t quads = static_cast<size_t>(h.quad_steps());
     l.t_ptr = take((quads ? h.quad_ptr.size() : h.step_ptr.size()) * sizeof(int32_t));
@@ -204,18 +206,16 @@ Layout make_layout(const smat_handle& h)
 // per-row path a few long block rows leave most of the chip idle (seven of 128 packs, N = 777: 47 us
 // in front of a tile launch of 44).
 // With the option dense_tiles = -1 nothing qualifies.
+// Rows by pattern (grouped_layout) are for block rows only.  The clustering's order brings super rows together that tiles take, at a cost
+// that does not depend on how full they are, and leaves rows of several patterns in a block row, which adds 8-bit floats more exactly on the tile
+// kernels, whose instructions then have fewer products.  A launch of tiles and one for the remaining block rows have to be of one order: where
+// tiles take some super rows only, one of the two is given up.
 void plan_dense_tiles(smat_handle& h, smat::Workers& workers)
 {
-    const smat::Bcsr& b = h.layout();
+    const smat::Bcsr& b = h.bcsr;
     const int64_t nbr = b.nbr;
     h.row_dense.assign(static_cast<size_t>(nbr), 0);
     h.step_ptr.assign(1, 0);
-    h.dense_super.clear();
-    h.step_cols.clear();
-    h.step_rows.clear();
-    h.step_base.clear();
-    h.dense_slots = 0;
-    h.dense_columns = 0;
     h.dense_all_full = false;
     if (h.dense_mode < 0) return;
     h.dense_all_full = true;             // until a step says otherwise
@@ -278,14 +278,36 @@ void plan_dense_tiles(smat_handle& h, smat::Workers& workers)
         h.step_ptr.push_back(static_cast<int32_t>(h.step_rows.size()));
         if (steps != h.step_ptr[1]) h.dense_all_full = false;      // the first dense super row's count
     }
+    if (!h.bcsr.grouped || h.dense_super.empty()) return;
+    if (static_cast<int64_t>(h.dense_super.size()) == n_super) {
+        // (block rows of 8-bit floats by pattern take four times the matrix instructions: 128 x 128 hidden blocks of which 30 % are stored, 0.71 of the columns, N = 512 in e4m3
+        // 11.1 -> 13.4 us, 20 %, 0.26, 11.0 -> 11.5; 15 %, 0.16, 11.2 -> 7.6)
+        if ((h.dtype == SMAT_E4M3 || h.dtype == SMAT_E5M2) && h.bcsr.grouped_share > 0.25) h.bcsr.grouped.reset();
+        return;
+    }
+    // A fifth of the columns makes up for tiles (128 x 128 hidden blocks of which 5 % are stored, a tenth of the columns, seven of eight super rows: N = 64 / 2048 in e4m3 4.2 / 8.0 us,
+    // without rows by pattern 4.8 / 24.2).
+    if (h.dense_mode > 0 || h.bcsr.grouped_share > 0.2) {
+        h.bcsr.grouped.reset();
+        return;
+    }
+    h.row_dense.assign(static_cast<size_t>(nbr), 0);
+    h.dense_super.clear();
+    h.step_ptr.assign(1, 0);
+    h.step_cols.clear();
+    h.step_rows.clear();
+    h.step_base.clear();
+    h.dense_slots = 0;
+    h.dense_columns = 0;
+    h.dense_all_full = false;
 }
 
-// Stored entries of block row br of A' (rows perm[16 br] ...).
-int64_t block_row_nnz(const smat_handle& h, size_t br)
+// Stored entries of block row br of b (rows perm[16 br] ...).
+int64_t block_row_nnz(const smat_handle& h, const smat::Bcsr& b, size_t br)
 {
     int64_t nnz = 0;
     for (int64_t i = static_cast<int64_t>(br) * 16; i < static_cast<int64_t>(br) * 16 + 16 && i < h.csr.M; ++i) {
-        const size_t r = static_cast<size_t>(h.layout().perm[static_cast<size_t>(i)]);
+        const size_t r = static_cast<size_t>(b.perm[static_cast<size_t>(i)]);
         nnz += h.csr.row_ptr[r + 1] - h.csr.row_ptr[r];
     }
     return nnz;
@@ -307,7 +329,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
     int64_t nnz = 0;
     for (int32_t s : h.dense_super)
         for (int64_t br = 16 * static_cast<int64_t>(s); br < std::min<int64_t>(h.bcsr.nbr, 16 * static_cast<int64_t>(s) + 16); ++br)
-            nnz += block_row_nnz(h, static_cast<size_t>(br));
+            nnz += block_row_nnz(h, h.bcsr, static_cast<size_t>(br));
     // What a step costs against one of the other form, measured: fp16 / bf16 0.43 us and 0.365, int8 0.37 and 0.27, the 8-bit floats,
     // which take twice the instructions, e4m3 0.67 and 0.47 (4096 columns, N = 2048: at 10 % fill 34.4 us against 43.4, at 25 %
     // and 0.69 of the steps 41.8 against 43.5, at 30 % and 0.89 50.9), e5m2 0.79 and 0.47 (at 10 % fill 38.8 against 42.8).
@@ -329,7 +351,7 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
             std::fill(mask.begin(), mask.end(), Rows{{0, 0, 0, 0}});
             const int64_t first = static_cast<int64_t>(supers[static_cast<size_t>(x)]) * 256;
             for (int64_t i = first; i < std::min<int64_t>(h.csr.M, first + 256); ++i) {
-                const size_t r = static_cast<size_t>(h.layout().perm[static_cast<size_t>(i)]);
+                const size_t r = static_cast<size_t>(h.bcsr.perm[static_cast<size_t>(i)]);
                 for (int64_t p = h.csr.row_ptr[r]; p < h.csr.row_ptr[r + 1]; ++p)
                     mask[static_cast<size_t>(h.csr.col_idx[static_cast<size_t>(p)])].w[(i - first) >> 6] |= uint64_t{1} << ((i - first) & 63);
             }
@@ -441,7 +463,7 @@ void plan_packs(smat_handle& h, smat::Workers& workers)
                 occupied += cols;
                 worst = std::max(worst, in_pack);
             }
-            cuts[static_cast<size_t>(br)] = Cut{pack + 1, occupied, block_row_nnz(h, static_cast<size_t>(br)), worst};
+            cuts[static_cast<size_t>(br)] = Cut{pack + 1, occupied, block_row_nnz(h, b, static_cast<size_t>(br)), worst};
         }
     });
     // How many stored entries per occupied column a block row of the densest class may have
@@ -613,12 +635,6 @@ smat_status_t smat_preprocess(int64_t M, int64_t K, const int64_t* row_ptr, cons
             if (h->cols_permuted) h->dense_mode = -1;
         }
         plan_dense_tiles(*h, workers);
-        // Rows by pattern bring a product into every place of the tile kernels' instructions, which then add 8-bit floats less exactly than in the
-        // clustering's order (the per-row kernels multiply such packs in parts): these types keep that order where there would be tiles.
-        if (h->bcsr.grouped && (dtype == SMAT_E4M3 || dtype == SMAT_E5M2) && !h->dense_super.empty()) {
-            h->bcsr.grouped.reset();
-            plan_dense_tiles(*h, workers);
-        }
         try {
             plan_packs(*h, workers);
         } catch (const std::length_error& e) {
@@ -726,9 +742,14 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         // however short it is (a band of 7339 rows: 0.3 of a set-up's 1.0 ms).
         smat::Buf<char> tables(l.tables_end);
         auto put = [&](size_t off, const void* src, size_t n) { if (n) std::memcpy(tables.data() + off, src, n); };
-        int32_t* perm = reinterpret_cast<int32_t*>(tables.data() + l.perm);
-        std::fill(perm, perm + (nbr + 15) / 16 * 256, -1);
-        put(l.perm, b.perm.data(), sizeof(int32_t) * M);
+        const bool two_orders = h->bcsr.grouped && !h->dense_super.empty();
+        auto put_perm = [&](size_t off, const smat::Buf<int32_t>& rows) {
+            int32_t* perm = reinterpret_cast<int32_t*>(tables.data() + off);
+            std::fill(perm, perm + (nbr + 15) / 16 * 256, -1);
+            put(off, rows.data(), sizeof(int32_t) * M);
+        };
+        put_perm(l.perm, b.perm);
+        if (two_orders) put_perm(l.t_perm, h->bcsr.perm);
         // launch tables: all block rows, and those the dense path does not cover
         int32_t* work = reinterpret_cast<int32_t*>(tables.data() + l.work);
         int32_t* work_rest = reinterpret_cast<int32_t*>(tables.data() + l.work_rest);
@@ -797,6 +818,8 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         row_stats(*h, false, d);
         row_stats(*h, true, d_rest);
         d_rest.work = reinterpret_cast<const int32_t*>(base + l.work_rest);
+        smat::DeviceBcsr d_tiles = d;
+        if (two_orders) d_tiles.perm = reinterpret_cast<const int32_t*>(base + l.t_perm);
         smat::DenseTiles tiles;
         tiles.super_rows = reinterpret_cast<const int32_t*>(base + l.t_super);
         tiles.step_ptr = reinterpret_cast<const int32_t*>(base + l.t_ptr);
@@ -828,9 +851,9 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
                                         reinterpret_cast<uint32_t*>(base + l.slots), static_cast<size_t>(h->slots_units) * 8, h->elem_bytes, s)))
             return hip_fail("fill block values", e);
         if ((e = smat::launch_fill_zero(base + l.t_vals, (l.t_quad_index - l.t_vals) / 16, s))) return hip_fail("zero tile values", e);
-        e = quads ? smat::launch_quad_fill(d, tiles, h->dtype, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
+        e = quads ? smat::launch_quad_fill(d_tiles, tiles, h->dtype, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, base + l.t_quad_index,
                                            h->max_quad_steps, s)
-                  : smat::launch_dense_fill(d, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);
+                  : smat::launch_dense_fill(d_tiles, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);
         if (e) return hip_fail("fill tile values", e);
         if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("bind synchronize", e);
         {
@@ -841,6 +864,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         }
         h->dev = d;
         h->dev_rest = d_rest;
+        h->dev_tiles = d_tiles;
         h->tiles = tiles;
         {
             std::lock_guard<std::mutex> lock(h->scratch_mutex);
@@ -994,6 +1018,9 @@ ScratchArea scratch_area_of(const smat_handle* h, void* stream)
 // columns are mostly empty.
 constexpr int64_t kStageColumns = 32;
 
+// Columns that the block rows occupy which tiles would take in their place.
+int64_t columns_of_rows(const smat_handle& h) { return h.bcsr.grouped ? h.b_rows : h.dense_columns; }
+
 // Does the kernel for few columns on the two-of-four form take N columns?  Both estimates, in us, were fitted on random matrices of
 // 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
 // once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
@@ -1007,7 +1034,7 @@ FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
     const int es = h.elem_bytes, row_bytes = smat::quad_row_bytes(es, N, h.max_quad_steps);
     if (row_bytes == 0) return {kNever, kNever};
     const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
-    const double columns = static_cast<double>(h.dense_columns), block_rows = 16.0 * h.tiles.n;
+    const double columns = static_cast<double>(columns_of_rows(h)), block_rows = 16.0 * h.tiles.n;
     const double per_column = es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
     const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
     const double a_mb = static_cast<double>(h.tiles.n_quad_steps) * (es == 1 ? 20480e-6 : 18432e-6);
@@ -1159,11 +1186,11 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         }
         // rows of B at 22 TB/s over all compute units (in the shorter rows of the 8-bit types 19 and 13; a third less where
         // they lie off the cache lines), values and C at 7
-        const double pieces = static_cast<double>(h->dense_columns) * static_cast<double>((N + 15) / 16 * 16 * h->elem_bytes);
+        const double pieces = static_cast<double>(columns_of_rows(*h)) * static_cast<double>((N + 15) / 16 * 16 * h->elem_bytes);
         const double groups = static_cast<double>(h->bcsr.nbr) * static_cast<double>((N * h->elem_bytes + 255) / 256);
         const double rate = (h->elem_bytes == 2 ? 22.0e6 : N > 128 ? 19.0e6 : 13.0e6) * (starts % 128 == 0 ? 1.0 : 0.75);
         const double t_rows = 4.0 + pieces / rate * std::max(1.0, 256.0 / groups) +
-                              (static_cast<double>(h->dense_columns) * 16.0 * h->elem_bytes + static_cast<double>(h->csr.M) * N * 4.0) / 7.0e6;
+                              (static_cast<double>(columns_of_rows(*h)) * 16.0 * h->elem_bytes + static_cast<double>(h->csr.M) * N * 4.0) / 7.0e6;
         use_tiles = t_tiles <= t_rows;
     }
     if (use_tiles && hard_limit && in_pieces) {
@@ -1190,7 +1217,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             enqueued("rows", rows_flop(h->dev_rest, N));
         }
         if (!e) {
-            e = smat::launch_quad_rows(h->dev, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+            e = smat::launch_quad_rows(h->dev_tiles, tiles, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
             const int64_t passes = smat::quad_row_passes(h->elem_bytes, N, smat::quad_row_bytes(h->elem_bytes, N, h->max_quad_steps));
             enqueued("quad_rows", quad_step_flop * static_cast<double>(tiles.n_quad_steps) * static_cast<double>(passes));
         }
@@ -1211,7 +1238,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
                 enqueued("copy_b", 0);
             }
             if (e) break;
-            e = smat::launch_spmm_dense(h->dev, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
+            e = smat::launch_spmm_dense(h->dev_tiles, tiles, h->dtype, b, stage_ld, static_cast<char*>(dC) + 4 * c0, ldc, n, stream, &dense_variant);
             const int64_t columns = tiles.n_quad_steps > 0 ? smat::quad_shape_columns(tiles.quad_shape) : 128;
             const double groups = static_cast<double>((n + columns - 1) / columns * (columns / 16));
             if (tiles.n_quad_steps > 0) {

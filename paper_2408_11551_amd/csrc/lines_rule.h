@@ -42,10 +42,10 @@ inline bool takes_lines(const DeviceBcsr& d, int es, const void* B, int64_t ldb,
         // not for a slab that no L2 holds any of (239562 rows of a graph, N = 193 154, 179).
         if (es == 1) return slab_mb <= 16.0 && (uses > 6.0 || units <= 2800 || mb * static_cast<double>(d.K) > 16.0);
         // 16-bit types read A twice as often here as the other kernel does: where rows of B come from all over, of rows kept by column only as long as a slab leaves an L2
-        // room (2048 x 2048 hidden blocks, N = 256 47, 63, but 956 x 956, N = 960 59, 47), and not for rows as long as those of pruned weights (114 block rows of
-        // 230 packs, N = 232 25.3, 30.9); or few packs in all.
-        const double most_mb = d.max_class == kEntryClass ? 16.0 : 3.0;
-        return (d.spread && uses <= 60.0 && slab_mb <= most_mb) || d.n_packs * slabs <= 4000;
+        // room (2048 x 2048 hidden blocks, N = 256 47, 63, but 956 x 956, N = 960 59, 47) and there are more than a few long ones (256 of 25 packs, N = 512 16.4, 22.3),
+        // and not for rows as long as those of pruned weights (114 block rows of 230 packs, N = 232 25.3, 30.9); or few packs in all.
+        const bool by_column = d.max_class != kEntryClass, room = slab_mb <= 3.0 && (d.mean_row_packs < 14.0 || d.n_order > 400);
+        return (d.spread && uses <= 60.0 && (by_column ? room : slab_mb <= 16.0)) || d.n_packs * slabs <= 4000;
     }
     // Several slabs off the lines are two lines of most rows each: where a slab of all rows, or what is gathered, is well inside an L2 (24000 rows of 16, N = 332 in int8
     // 25.6, 24.2, but 40000 42.9, 50.8; 30000 of 16, N = 134 in fp16 21.3, 29.4; 400 x 400 hidden blocks, N = 160 in fp16 7.0, 6.1, but 1000 x 1000, N = 134

@@ -774,13 +774,15 @@ static int64_t occupied_columns(const Csr& a, const int32_t* perm, int64_t strid
 // The clustering merges a row into a cluster where it comes upon it, so the rows of several patterns lie mixed in one cluster, some of a
 // pattern's perhaps in another, and the sixteen rows of a block row then occupy the columns of most of these patterns: 2 % of
 // 627 x 627 hidden blocks 762 000 columns, where by pattern it is 124 000.  What the caller sees (permutation, blocks) is the clustering's; the
-// device layout, whose products cost a row of B per occupied column, takes the rows by pattern where that saves a tenth.  us in
+// device's block rows, whose products cost a row of B per occupied column, take the rows by pattern where that saves a tenth.  us in
 // fp16, before and now: that matrix at N = 160 29.4 and 8.6, N = 1000 185 and 33.
 static void grouped_layout(const Csr& a, const Patterns& pat, Buf<int32_t>& by_pattern, Bcsr& out, Workers& workers)
 {
     if (by_pattern.empty()) return;
     const int64_t stride = out.nbr >= 256 ? 8 : 1;      // (a sample tells: counting all of a band of 7339 rows takes a tenth of its set-up)
-    if (10 * occupied_columns(a, by_pattern.data(), stride, workers) > 9 * occupied_columns(a, out.perm.data(), stride, workers)) return;
+    const int64_t by = occupied_columns(a, by_pattern.data(), stride, workers), now = occupied_columns(a, out.perm.data(), stride, workers);
+    if (10 * by > 9 * now) return;
+    out.grouped_share = static_cast<double>(by) / static_cast<double>(now);
     out.grouped = std::make_unique<Bcsr>();
     Bcsr& g = *out.grouped;
     g.nbr = out.nbr;

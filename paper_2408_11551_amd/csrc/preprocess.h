@@ -33,8 +33,9 @@ struct Bcsr {
     Buf<int32_t> col_perm;
     int64_t n_blocks_rows_only = 0;
     int64_t n_clusters = 0;
-    // The block structure that the device layout is made from, where it is another one (grouped_layout): perm, row_ptr, col_idx, col_mask, n_blocks.
+    // The block structure that the block rows on the device are made from, where it is another one (grouped_layout): perm, row_ptr, col_idx, col_mask, n_blocks.
     std::unique_ptr<Bcsr> grouped;
+    double grouped_share = 1.0;          // columns that its block rows occupy, of this one's
 };
 
 // Returns an empty string when the columns are well formed, else what is wrong with the first row that is not.
