@@ -1047,6 +1047,7 @@ FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
 // What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
 // other, a little per step of all (what the units share), the write of C; with split steps, the partial tiles.  Fitted on
 // 400 products of random matrices (1000 ... 8192 rows and columns, 5-20 % fill, N = 16 ... 4096, all types): within 3-8 % (rms).
+// (Of 318 products drawn later, profiles/quad_shapes.csv, within 3-13 %; with rows_us below the choice was 1.3 % behind the best of rows and five shapes.)
 double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
 {
     struct Cost { double start, step, shared; };
