@@ -39,6 +39,7 @@ UNITS = {
     # MFMA results live in ordinary VGPRs instead of being shuffled between the two register files
     "kernels_dense": ("kernels_dense.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1", *PRELOAD]),
     "kernels_quads": ("kernels_quads.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1", *PRELOAD]),
+    "kernels_setup": ("kernels_setup.hip", []),
     # the tile-step probe is the tile kernel's loop: same flag
     "probes": ("probes.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
     "ablation": ("ablation.hip", []),

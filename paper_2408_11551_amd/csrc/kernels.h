@@ -164,6 +164,25 @@ int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem
 int launch_spmm_dense(const DeviceBcsr& d, const DenseTiles& t, int dtype, const void* B, int64_t ldb,
                       void* C, int64_t ldc, int64_t N, void* stream, const char** variant);
 
+// The search for patterns that could start a cluster together (kernels_setup.hip).  Pattern k has the block columns columns[ptr[k]] ..., the patterns are
+// numbered by their lengths, and lists[list_ptr[c]] ... are those that have column c.  All on the device.
+struct PartnerTables {
+    int64_t n = 0;                         // patterns, below 2^31
+    uint32_t keep = 0;                     // 1000 - tau_permille
+    uint32_t longest = 0;                  // columns of the longest pattern, below 2^16
+    const uint32_t* ptr = nullptr;         // [n+1]
+    const uint32_t* columns = nullptr;
+    const uint32_t* list_ptr = nullptr;    // [block columns + 1]
+    const uint32_t* lists = nullptr;
+    const uint32_t* first_of_len = nullptr;      // [longest + 2] first pattern of that length or more
+    uint32_t* pairs = nullptr;             // [2 most_pairs]
+    uint32_t most_pairs = 0;
+    uint32_t* found = nullptr;             // [2] pairs that there are, which may be more than most_pairs but stay below 2^32; not 0: a pattern has too many (both zero before)
+};
+// first_long: the first pattern of more than short_pattern() columns.
+uint32_t short_pattern();
+int launch_partners(const PartnerTables& t, uint32_t first_long, void* stream);
+
 // The canonical BCSR of the paper on the device (Data Structures section), for the ablation
 // kernels only (ablation.hip).
 struct CanonicalBcsr {

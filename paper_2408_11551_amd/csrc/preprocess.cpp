@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 #include <memory>
 #include <numeric>
 
@@ -508,8 +509,34 @@ static Partners partners_of(const Patterns& pat, const PatternClasses& pc, const
     return partners;
 }
 
+// The same from a search elsewhere, which finds all pairs: no class has many.  False: it did not.
+static bool partners_elsewhere(const Patterns& pat, const PatternClasses& pc, const ColumnIndex& inv, const std::vector<int64_t>& first_of_len, int64_t keep,
+                               PairSearch& elsewhere, Partners& partners, Workers& workers)
+{
+    const int64_t n = pc.size(), nbc = static_cast<int64_t>(inv.len.size()), longest = n ? pc.len[n - 1] : 0;
+    Buf<uint32_t> ptr(static_cast<size_t>(n) + 1), list_ptr(static_cast<size_t>(nbc) + 1);
+    ptr[0] = 0;
+    for (int64_t k = 0; k < n; ++k) ptr[k + 1] = ptr[k] + static_cast<uint32_t>(pc.len[k]);
+    for (int64_t c = 0; c <= nbc; ++c) list_ptr[c] = static_cast<uint32_t>(inv.ptr[c]);
+    Buf<uint32_t> columns(ptr[n]);
+    workers.ranges(n, row_grain(n, ptr[n], 4096, workers), [&](int64_t k0, int64_t k1, int) {
+        for (int64_t k = k0; k < k1; ++k) std::copy_n(pat.idx.begin() + pat.ptr[pc.first_row[k]], pc.len[k], columns.begin() + ptr[k]);
+    });
+    const std::vector<uint32_t> from(first_of_len.begin(), first_of_len.end());
+    Buf<int32_t> found;
+    if (!elsewhere.run(PairSearch::Tables{n, nbc, longest, keep, ptr, columns, list_ptr, inv.classes, from}, found)) return false;
+    partners.many.assign(static_cast<size_t>(n), 0);
+    partners.ptr.assign(static_cast<size_t>(n) + 1, 0);
+    for (int32_t k : found) ++partners.ptr[k + 1];
+    prefix_sums(partners.ptr);
+    partners.of.resize(found.size());
+    std::vector<int64_t> fill(partners.ptr.begin(), partners.ptr.end() - 1);
+    for (size_t x = 0; x < found.size(); ++x) partners.of[fill[found[x]]++] = found[x ^ 1];
+    return true;
+}
+
 int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers,
-                        Buf<int32_t>* by_pattern)
+                        Buf<int32_t>* by_pattern, PairSearch* elsewhere)
 {
     order.clear();
     order.reserve(static_cast<size_t>(M));
@@ -628,8 +655,15 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         const double ahead = static_cast<double>(spent_alone) * (1.0 - done) / done;
         double pairs = 0;
         for (int64_t c = 0; c < nbc; ++c) pairs += 0.5 * static_cast<double>(inv.len[c]) * static_cast<double>(inv.len[c]);
-        if (ahead < 0.25 * pairs / workers.most() + 5e4) {
+        const double here = 0.25 * pairs / workers.most();
+        // (a search elsewhere takes the lists as they were made)
+        const double there = elsewhere && !inv.dropped ? elsewhere->price(n_classes, nbc, inv.ptr[nbc], pairs, longest) : std::numeric_limits<double>::infinity();
+        if (ahead < std::min(here, there) + 5e4) {
             ask_at = 2 * spent;
+            return;
+        }
+        if (there < here && partners_elsewhere(pat, pc, inv, first_of_len, keep, *elsewhere, partners, workers)) {
+            ask_at = 0;
             return;
         }
         std::vector<int32_t> alive(static_cast<size_t>(n_classes));
@@ -794,7 +828,7 @@ static void grouped_layout(const Csr& a, const Patterns& pat, Buf<int32_t>& by_p
     build_structure(a, pat, per_row, g, workers);
 }
 
-void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers)
+void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers, PairSearch* elsewhere)
 {
     const int64_t M = a.M;
     out.nbr = (M + kBlock - 1) / kBlock;
@@ -811,7 +845,7 @@ void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers
     out.n_clusters = 0;
     if (reorder) {
         Buf<int32_t> cand;
-        out.n_clusters = jaccard_cluster(M, out.nbc, pat, tau_permille, cand, workers, &by_pattern);
+        out.n_clusters = jaccard_cluster(M, out.nbc, pat, tau_permille, cand, workers, &by_pattern, elsewhere);
         const int64_t n_cand = count_blocks(M, out.nbc, pat, cand.data(), per_row_cand, workers);
         if (n_cand < out.n_blocks_identity) {            // strictly fewer, else keep P = I
             out.perm.swap(cand);

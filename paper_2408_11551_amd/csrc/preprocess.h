@@ -49,17 +49,36 @@ struct Patterns {
 };
 void block_patterns(const Csr& a, Patterns& pat, Workers& workers);
 
+// A search for the pairs of patterns that pass the merge test against each other, somewhere else than on the host's threads.
+class PairSearch {
+public:
+    virtual ~PairSearch() = default;
+    // What run() takes for n patterns with `entries` block columns (of nbc) and `pairs` pairs of entries in a column, in the counting of a pattern in a list
+    // that one thread does meanwhile; infinity where it does not take them.
+    virtual double price(int64_t n, int64_t nbc, int64_t entries, double pairs, int64_t longest) const = 0;
+    // Pattern k (numbered by length, then as they come) has columns[ptr[k]] ..., column c the patterns lists[list_ptr[c]] ... in ascending order;
+    // first_of_len[x] is the first pattern of x columns or more, x = 0 ... longest + 1.
+    // Puts every pair into `found` once, as two numbers, the shorter pattern's first; false where it could not.
+    struct Tables {
+        int64_t n, nbc, longest, keep;
+        const Buf<uint32_t>&ptr, &columns, &list_ptr;
+        const Buf<int32_t>& lists;
+        const std::vector<uint32_t>& first_of_len;
+    };
+    virtual bool run(const Tables& tables, Buf<int32_t>& found) = 0;
+};
+
 // Greedy Jaccard clustering; returns the cluster order (new -> old) and the number of clusters.  by_pattern: the rows of each
 // pattern together, in the place of the first of them; empty where that is the same order.
 int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_permille, Buf<int32_t>& order, Workers& workers,
-                        Buf<int32_t>* by_pattern = nullptr);
+                        Buf<int32_t>* by_pattern = nullptr, PairSearch* elsewhere = nullptr);
 
 // Number of nonzero blocks when rows are read in the order perm on the 16-row grid; per_row receives
 // the number of every block row.
 int64_t count_blocks(int64_t M, int64_t nbc, const Patterns& pat, const int32_t* perm, Buf<int32_t>& per_row, Workers& workers);
 
 // Full pipeline: patterns -> (optional) clustering -> guard -> BCSR structure and column masks.
-void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers);
+void build_bcsr(const Csr& a, bool reorder, int tau_permille, Bcsr& out, Workers& workers, PairSearch* elsewhere = nullptr);
 
 // Row + column variant (the one the paper tried next to the row-only reordering, Preprocessing
 // section): after build_bcsr, clusters the columns of A' = P A with the same greedy procedure, a

@@ -69,6 +69,12 @@ def _load():
     lib.smat_preprocess.restype = ctypes.c_int
     lib.smat_preprocess.argtypes = [i64, i64, vp, vp, vp, ctypes.c_int, ctypes.POINTER(_Options),
                                     ctypes.POINTER(vp)]
+    lib.smat_preprocess_on_device.restype = ctypes.c_int
+    lib.smat_preprocess_on_device.argtypes = lib.smat_preprocess.argtypes[:-1] + [vp, sz, vp, ctypes.POINTER(vp)]
+    lib.smat_preprocess_scratch_bytes.restype = ctypes.c_int
+    lib.smat_preprocess_scratch_bytes.argtypes = [i64, i64, i64, ctypes.POINTER(_Options), ctypes.POINTER(sz)]
+    lib.smat_pattern_partners.restype = ctypes.c_int
+    lib.smat_pattern_partners.argtypes = [i64, i64, vp, vp, ctypes.c_int, vp, sz, vp, vp, i64, ctypes.POINTER(i64)]
     lib.smat_probe_read.restype = ctypes.c_int
     lib.smat_probe_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
     lib.smat_probe_read_window.restype = ctypes.c_int
@@ -171,6 +177,13 @@ def smat_preprocess(M, K, row_ptr, col_idx, vals_bits, dtype, *, reorder=1, tau_
                     block_h=16, block_w=16, dense_tiles=0, concurrent_streams=2) -> int:
     """row_ptr int64[M+1], col_idx int32[nnz], vals_bits uint16[nnz] (uint8 for the 8-bit types)
     (HOST) -> opaque handle."""
+    return smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, device=None, reorder=reorder, tau_permille=tau_permille,
+                                     block_h=block_h, block_w=block_w, dense_tiles=dense_tiles, concurrent_streams=concurrent_streams)
+
+
+def smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, *, device, reorder=1, tau_permille=700,
+                              block_h=16, block_w=16, dense_tiles=0, concurrent_streams=2) -> int:
+    """The same with the help of a device, in scratch memory that is given back before the call returns; None: none."""
     rp, rp_p = _host(row_ptr, np.int64)
     ci, ci_p = _host(col_idx, np.int32)
     vals_bits = np.asarray(vals_bits)
@@ -184,7 +197,21 @@ def smat_preprocess(M, K, row_ptr, col_idx, vals_bits, dtype, *, reorder=1, tau_
         raise ValueError("col_idx / vals shorter than row_ptr[M]")
     opt = _Options(block_h, block_w, reorder, tau_permille, dense_tiles, concurrent_streams)
     out = ctypes.c_void_p()
-    _check(_lib.smat_preprocess(M, K, rp_p, ci_p, vb_p, _dtype_code(dtype), ctypes.byref(opt), ctypes.byref(out)))
+    args = (M, K, rp_p, ci_p, vb_p, _dtype_code(dtype), ctypes.byref(opt))
+    need = ctypes.c_size_t()
+    if device is not None and min(M, K, nnz) >= 0:
+        _check(_lib.smat_preprocess_scratch_bytes(M, K, nnz, ctypes.byref(opt), ctypes.byref(need)))
+    if need.value == 0:
+        _check(_lib.smat_preprocess(*args, ctypes.byref(out)))
+        return out.value
+    import torch
+    with torch.cuda.device(device):
+        try:
+            scratch = torch.empty(need.value, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            _check(_lib.smat_preprocess(*args, ctypes.byref(out)))
+            return out.value
+        _check(_lib.smat_preprocess_on_device(*args, ctypes.c_void_p(scratch.data_ptr()), need.value, _stream_ptr(None), ctypes.byref(out)))
     return out.value
 
 
@@ -382,6 +409,18 @@ def smat_probe_mfma(workgroups, iters, sink, stream=None):
     _check(_lib.smat_probe_mfma(workgroups, iters, ctypes.c_void_p(sink.data_ptr()), _stream_ptr(stream)))
 
 
+def smat_pattern_partners(ptr, columns, nbc, keep, scratch, room, stream=None):
+    """ptr uint32[n+1], columns uint32[ptr[n]] (HOST); scratch: device bytes -> int32[found, 2]"""
+    p, p_p = _host(ptr, np.uint32)
+    c, c_p = _host(columns, np.uint32)
+    if c.size < int(p[-1]):
+        raise ValueError("columns shorter than ptr[n]")
+    pairs, count = np.empty((room, 2), np.int32), ctypes.c_int64()
+    _check(_lib.smat_pattern_partners(p.size - 1, nbc, p_p, c_p, keep, ctypes.c_void_p(scratch.data_ptr()), scratch.numel() * scratch.element_size(),
+                                    _stream_ptr(stream), pairs.ctypes.data_as(ctypes.c_void_p), room, ctypes.byref(count)))
+    return pairs[:count.value]
+
+
 def smat_destroy(h):
     if h:
         _lib.smat_destroy(h)
@@ -393,9 +432,9 @@ class SmatMatrix:
     def __init__(self, M, K, row_ptr, col_idx, vals_bits, dtype, *, reorder=1, tau_permille=700,
                  dense_tiles=0, concurrent_streams=2, device="cuda:0", bind=True):
         self.M, self.K, self.dtype = M, K, dtype
-        self.handle = smat_preprocess(M, K, row_ptr, col_idx, vals_bits, dtype,
-                                      reorder=reorder, tau_permille=tau_permille, dense_tiles=dense_tiles,
-                                      concurrent_streams=concurrent_streams)
+        self.handle = smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, device=device if bind else None,
+                                                reorder=reorder, tau_permille=tau_permille, dense_tiles=dense_tiles,
+                                                concurrent_streams=concurrent_streams)
         self.workspace = None
         self.info = smat_get_info(self.handle)
         if bind:

@@ -1,0 +1,103 @@
+"""The search for rows that could start a cluster together, on the device: its pairs against brute force on dense patterns, and the handle that it helps to
+make against the one that the host makes alone."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2408_11551_amd as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _patterns(n, nbc, lengths, seed, families):
+    """n distinct patterns in the order of their lengths; `families`: that many of the patterns are others with a few columns changed."""
+    rng = np.random.default_rng(seed)
+    lists = []
+    for i in range(n):
+        if lists and rng.random() < families:
+            src = lists[rng.integers(0, len(lists))]
+            cols = np.union1d(src[rng.random(src.size) < 0.8], rng.integers(0, nbc, 1 + src.size // 8))
+        else:
+            cols = np.unique(rng.integers(0, nbc, rng.choice(lengths)))
+        lists.append(cols)
+    lists = sorted({tuple(x) for x in lists if len(x)}, key=lambda x: (len(x), x))
+    ptr = np.zeros(len(lists) + 1, np.uint32)
+    np.cumsum([len(x) for x in lists], out=ptr[1:])
+    return ptr, np.concatenate([np.array(x, np.uint32) for x in lists])
+
+
+def _brute(ptr, columns, nbc, keep):
+    n, lens = ptr.size - 1, np.diff(ptr).astype(np.int64)
+    dense = torch.zeros((n, nbc), dtype=torch.float32)
+    dense[torch.from_numpy(np.repeat(np.arange(n), lens)), torch.from_numpy(columns.astype(np.int64))] = 1.0
+    want = []
+    for k0 in range(0, n, 512):
+        shared = (dense[k0:k0 + 512] @ dense.t()).numpy().astype(np.int64)         # (counts: exact in fp32)
+        union = lens[k0:k0 + 512, None] + lens[None, :] - shared
+        a, b = np.nonzero(1000 * shared > keep * union)
+        want.append(np.stack([a + k0, b], 1)[a + k0 < b])
+    return np.concatenate(want)
+
+
+# one and two columns; on both sides of the 32 columns up to which a wave takes a pattern, and of the 255 that a byte counts; a column with thousands of
+# patterns; more patterns than the counters of a workgroup (65536 bytes, 32768 halves)
+@pytest.mark.parametrize("n,nbc,lengths,families", [
+    (1, 5, [3], 0), (2, 5, [2], 0), (3000, 4000, [1, 2, 3], 0.2), (3000, 300, [30, 31, 32, 33, 34, 40], 0.3),
+    (2000, 4000, [200, 250, 255, 256, 300], 0.5), (1500, 9000, [1, 2, 31, 33, 600, 700], 0.4), (4000, 40, [4, 5], 0.0), (3000, 64, [2, 40], 0.0)])
+@pytest.mark.parametrize("keep", [300, 700, 1])
+def test_pairs_are_those_of_brute_force(n, nbc, lengths, families, keep):
+    ptr, columns = _patterns(n, nbc, lengths, n + nbc, families)
+    want = _brute(ptr, columns, nbc, keep)
+    scratch = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    most = np.bincount(want.reshape(-1), minlength=ptr.size - 1).max() if want.size else 0
+    try:
+        got = S.smat_pattern_partners(ptr, columns, nbc, keep, scratch, want.shape[0] + 1)
+    except S.SmatError as e:
+        assert e.status_name == "SMAT_ERR_UNSUPPORTED" and most > 128
+        return
+    assert got.shape == want.shape and np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], want)
+
+
+@pytest.mark.parametrize("per_row", [34, 300])
+def test_more_patterns_than_a_workgroup_counts_at_a_time(per_row):
+    """70 000 patterns beyond the short ones, in bytes and in halves; checked on the pairs that were planted, and that every pair found is one."""
+    n, nbc = 70000, 1000000
+    rng = np.random.default_rng(per_row)
+    base = np.sort(rng.integers(0, nbc, (n, per_row)), axis=1)
+    base[1::1000] = base[0::1000]                    # a partner for every thousandth ...
+    base[1::1000, 0] = rng.integers(0, 1000, n // 1000)      # ... with another first column
+    lists = sorted({tuple(np.unique(x)) for x in base}, key=lambda x: (len(x), x))
+    ptr = np.zeros(len(lists) + 1, np.uint32)
+    np.cumsum([len(x) for x in lists], out=ptr[1:])
+    columns = np.concatenate([np.array(x, np.uint32) for x in lists])
+    scratch = torch.empty(512 << 20, dtype=torch.uint8, device="cuda:0")
+    got = S.smat_pattern_partners(ptr, columns, nbc, 300, scratch, n)
+    for a, b in got:
+        shared = len(set(lists[a]) & set(lists[b]))
+        assert a < b and 1000 * shared > 300 * (len(lists[a]) + len(lists[b]) - shared)
+    where = {x: i for i, x in enumerate(lists)}
+    planted = {tuple(sorted((where[tuple(np.unique(base[i]))], where[tuple(np.unique(base[i + 1]))]))) for i in range(0, n, 1000)}
+    assert {p for p in planted if p[0] != p[1]} <= {tuple(p) for p in got}
+
+
+def _graph(M, K, per_row, seed):
+    rng = np.random.default_rng(seed)
+    deg = np.minimum(rng.zipf(1.6, M), 40 * per_row)
+    deg = np.maximum(1, (deg * (per_row / deg.mean())).astype(np.int64))
+    keys = np.unique(np.repeat(np.arange(M), deg) * K + rng.integers(0, K, deg.sum()))
+    row_ptr = np.zeros(M + 1, np.int64)
+    np.cumsum(np.bincount(keys // K, minlength=M), out=row_ptr[1:])
+    return row_ptr, (keys % K).astype(np.int32)
+
+
+@pytest.mark.parametrize("M,K,per_row,tau", [(40000, 40000, 12, 700), (30001, 9000, 20, 500), (20000, 300000, 30, 900), (16000, 16000, 60, 700)])
+def test_the_handle_is_the_hosts(M, K, per_row, tau):
+    row_ptr, col_idx = _graph(M, K, per_row, M + tau)
+    args = (M, K, row_ptr, col_idx, np.ones(col_idx.size, np.uint16), "f16")
+    alone = S.smat_preprocess(*args, tau_permille=tau)
+    helped = S.smat_preprocess_on_device(*args, device="cuda:0", tau_permille=tau)
+    assert np.array_equal(S.smat_export_perm(alone, M), S.smat_export_perm(helped, M))
+    for a, b in zip(S.smat_export_bcsr(alone, with_vals=False)[:2], S.smat_export_bcsr(helped, with_vals=False)[:2]):
+        assert np.array_equal(a, b)
+    S.smat_destroy(alone)
+    S.smat_destroy(helped)
