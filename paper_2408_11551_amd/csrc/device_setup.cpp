@@ -1,0 +1,176 @@
+// Set-up with the device's help: the search of preprocess.cpp for patterns that could start a cluster, on the kernels of kernels_setup.hip, and the entry points
+// for it (include/smat.h).
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+#include <cmath>
+#include <limits>
+#include <new>
+#include <vector>
+
+#include "api.h"
+#include "kernels.h"
+
+namespace smat {
+
+namespace {
+
+constexpr size_t kAlign = 256;
+size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+
+// The search for partners of preprocess.cpp on the device, in memory of the caller's.
+class DevicePairSearch : public PairSearch {
+public:
+    DevicePairSearch(void* scratch, size_t bytes, void* stream) : scratch_(static_cast<char*>(scratch)), bytes_(bytes), stream_(static_cast<hipStream_t>(stream)) {}
+
+    // 0.4 ms for the tables' way up (8.6 MB of a graph of 65536 rows of 16), the launches and the pairs' way down, and 134 million pairs of entries in
+    // 0.4 ms; a unit, one pattern counted, is 2.4 ns of a thread.  (That graph, smat_preprocess: 14.7 ms, with sixteen threads looking for partners, 11.2 with the
+    // device; 28740 rows 6.8 and 5.5.)  The counters have two bytes at most, entries and pairs numbers of 32 bits.
+    double price(int64_t n, int64_t nbc, int64_t entries, double pairs, int64_t longest) const override
+    {
+        constexpr double kNever = std::numeric_limits<double>::infinity();
+        if (n >= (int64_t{1} << 22) || longest >= 65536 || entries >= (int64_t{1} << 31) || pairs >= 4e9 || needed(n, nbc, entries, longest) > bytes_) return kNever;
+        return 1.7e5 + 0.0014 * pairs;
+    }
+
+    bool run(const Tables& t, Buf<int32_t>& found) override
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream_, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        const size_t entries = t.columns.size(), n = static_cast<size_t>(t.n);
+        size_t off = 0;
+        auto take = [&](size_t count) { char* at = scratch_ + off; off = align_up(off + count * 4); return reinterpret_cast<uint32_t*>(at); };
+        uint32_t* d_found = take(4);
+        uint32_t* d_ptr = take(n + 1);
+        uint32_t* d_columns = take(entries);
+        uint32_t* d_list_ptr = take(static_cast<size_t>(t.nbc) + 1);
+        uint32_t* d_lists = take(entries);
+        uint32_t* d_first = take(t.first_of_len.size());
+        const size_t most = std::min((bytes_ - off) / 8, size_t{1} << 24);
+        auto up = [&](uint32_t* dst, const void* src, size_t count) {
+            return count == 0 || hipMemcpyAsync(dst, src, count * 4, hipMemcpyHostToDevice, stream_) == hipSuccess;
+        };
+        bool ok = launch_fill_zero(d_found, 1, stream_) == 0 && up(d_ptr, t.ptr.data(), n + 1) && up(d_columns, t.columns.data(), entries) &&
+                  up(d_list_ptr, t.list_ptr.data(), t.list_ptr.size()) && up(d_lists, t.lists.data(), entries) &&
+                  up(d_first, t.first_of_len.data(), t.first_of_len.size());
+        PartnerTables d;
+        d.n = t.n;
+        d.keep = static_cast<uint32_t>(t.keep);
+        d.longest = static_cast<uint32_t>(t.longest);
+        d.ptr = d_ptr;
+        d.columns = d_columns;
+        d.list_ptr = d_list_ptr;
+        d.lists = d_lists;
+        d.first_of_len = d_first;
+        d.pairs = reinterpret_cast<uint32_t*>(scratch_ + off);
+        d.most_pairs = static_cast<uint32_t>(most);
+        d.found = d_found;
+        const uint32_t first_long = t.first_of_len[static_cast<size_t>(std::min<int64_t>(short_pattern(), t.longest)) + 1];
+        ok = ok && launch_partners(d, first_long, stream_) == 0;
+        uint32_t got[2] = {0, 0};
+        ok = ok && hipMemcpyAsync(got, d_found, 8, hipMemcpyDeviceToHost, stream_) == hipSuccess;
+        ok = hipStreamSynchronize(stream_) == hipSuccess && ok;       // also where something failed: the copies read the caller's tables
+        const uint32_t count = got[0];
+        if (!ok || got[1] != 0 || count > most) {
+            (void)hipGetLastError();
+            return false;
+        }
+        found.resize(2 * static_cast<size_t>(count));
+        if (count > 0 && (hipMemcpyAsync(found.data(), d.pairs, size_t{8} * count, hipMemcpyDeviceToHost, stream_) != hipSuccess ||
+                          hipStreamSynchronize(stream_) != hipSuccess)) {
+            (void)hipGetLastError();
+            return false;
+        }
+        return true;
+    }
+
+    // Bytes for n patterns with `entries` block columns in all, and for four pairs per pattern.
+    static size_t needed(int64_t n, int64_t nbc, int64_t entries, int64_t longest)
+    {
+        size_t bytes = 32 * static_cast<size_t>(n);
+        for (int64_t words : {int64_t{4}, n + 1, entries, nbc + 1, entries, longest + 2}) bytes += align_up(static_cast<size_t>(words) * 4);
+        return bytes;
+    }
+
+private:
+    char* scratch_;
+    size_t bytes_;
+    hipStream_t stream_;
+};
+
+}  // namespace
+
+}  // namespace smat
+
+using smat::DevicePairSearch;
+using smat::fail;
+using smat::kAlign;
+
+extern "C" {
+
+smat_status_t smat_preprocess_scratch_bytes(int64_t M, int64_t K, int64_t nnz, const smat_options_t* opt, size_t* bytes)
+{
+    if (!bytes) return fail(SMAT_ERR_INVALID_ARG, "bytes is NULL");
+    if (M < 0 || K < 0 || nnz < 0) return fail(SMAT_ERR_INVALID_ARG, "negative size");
+    // (below some hundred thousand entries the host's threads are done before the tables are up; 64 MiB: a graph of 300 000 rows of 16)
+    const bool worth = (!opt || opt->reorder != 0) && nnz >= 200000 && nnz < (int64_t{1} << 24) && M < (int64_t{1} << 22);
+    const size_t need = worth ? DevicePairSearch::needed(M, (K + 15) / 16, nnz, std::min<int64_t>(K, 65535)) : 0;
+    *bytes = need <= (size_t{64} << 20) ? need : 0;
+    return SMAT_OK;
+}
+
+smat_status_t smat_preprocess_on_device(int64_t M, int64_t K, const int64_t* row_ptr, const int32_t* col_idx, const void* vals, smat_dtype_t dtype,
+                                        const smat_options_t* opt, void* dev_scratch, size_t bytes, void* stream, smat_handle_t** out)
+{
+    if (reinterpret_cast<uintptr_t>(dev_scratch) % kAlign != 0) return fail(SMAT_ERR_INVALID_ARG, "dev_scratch must be 256-byte aligned");
+    DevicePairSearch search(dev_scratch, dev_scratch ? bytes : 0, stream);
+    return smat::preprocess(M, K, row_ptr, col_idx, vals, dtype, opt, &search, out);
+}
+
+smat_status_t smat_pattern_partners(int64_t n, int64_t nbc, const uint32_t* ptr, const uint32_t* columns, int keep, void* dev_scratch, size_t bytes, void* stream,
+                                  int32_t* pairs, int64_t room, int64_t* count)
+{
+    if (n < 1 || nbc < 1 || !ptr || !columns || !pairs || !count || keep < 0 || keep > 1000) return fail(SMAT_ERR_INVALID_ARG, "invalid argument");
+    if (!dev_scratch || reinterpret_cast<uintptr_t>(dev_scratch) % kAlign != 0) return fail(SMAT_ERR_INVALID_ARG, "dev_scratch must be 256-byte aligned");
+    try {
+        const smat::Buf<uint32_t> p(ptr, ptr + n + 1), cols(columns, columns + ptr[n]);
+        smat::Buf<uint32_t> list_ptr(static_cast<size_t>(nbc) + 1, 0u);
+        smat::Buf<int32_t> lists(cols.size());
+        int64_t longest = 0;
+        for (int64_t k = 0; k < n; ++k) {
+            const int64_t len = static_cast<int64_t>(p[k + 1]) - p[k];
+            if (len < longest) return fail(SMAT_ERR_INVALID_ARG, "patterns are not in the order of their lengths");
+            longest = len;
+        }
+        for (uint32_t c : cols) {
+            if (c >= nbc) return fail(SMAT_ERR_INVALID_ARG, "column out of range");
+            ++list_ptr[c + 1];
+        }
+        double of_lists = 0;
+        for (int64_t c = 0; c < nbc; ++c) {
+            of_lists += 0.5 * list_ptr[c + 1] * list_ptr[c + 1];
+            list_ptr[c + 1] += list_ptr[c];
+        }
+        std::vector<uint32_t> fill(list_ptr.begin(), list_ptr.end() - 1), first_of_len(static_cast<size_t>(longest) + 2, static_cast<uint32_t>(n));
+        for (int64_t k = n - 1; k >= 0; --k)
+            for (int64_t len = static_cast<int64_t>(p[k + 1]) - p[k]; len >= 0 && first_of_len[len] > k; --len) first_of_len[len] = static_cast<uint32_t>(k);
+        for (int64_t k = 0; k < n; ++k)
+            for (uint32_t x = p[k]; x < p[k + 1]; ++x) lists[fill[cols[x]]++] = static_cast<int32_t>(k);
+        DevicePairSearch search(dev_scratch, bytes, stream);
+        smat::Buf<int32_t> found;
+        if (!std::isfinite(search.price(n, nbc, p[n], of_lists, longest)) ||
+            !search.run(smat::PairSearch::Tables{n, nbc, longest, keep, p, cols, list_ptr, lists, first_of_len}, found))
+            return fail(SMAT_ERR_UNSUPPORTED, "the search does not take these patterns, or they have too many partners");
+        *count = static_cast<int64_t>(found.size() / 2);
+        if (*count > room) return fail(SMAT_ERR_INVALID_ARG, "more pairs than there is room for");
+        std::copy(found.begin(), found.end(), pairs);
+        return SMAT_OK;
+    } catch (const std::bad_alloc&) {
+        return fail(SMAT_ERR_ALLOC, "out of host memory in smat_pattern_partners");
+    }
+}
+
+}  // extern "C"
