@@ -1059,26 +1059,35 @@ FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
 }
 
 // What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
-// other, a little per step of all (what the units share), the write of C; with split steps, the partial tiles.  Fitted on
-// 400 products of random matrices (1000 ... 8192 rows and columns, 5-20 % fill, N = 16 ... 4096, all types): within 3-8 % (rms).
-// (Of 318 products drawn later, profiles/quad_shapes.csv, within 3-13 %; with rows_us below the choice was 1.3 % behind the best of rows and five shapes.)
+// other, a little per step of all (what the units share), steps once more for every round of as many workgroups as a unit holds, where it holds several, the
+// write of C; with split steps, the partial tiles.  Fitted on 1935 products of random matrices (1000 ... 8192 rows, 600 ... 8192 columns, 5-20 % fill, N = 16 ... 4096, all
+// types, each on all shapes): within 4-9 % (rms), and the shape it chooses is 0.5 % behind the best one on average.
 double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
 {
-    struct Cost { double start, step, shared; };
+    struct Cost { double start, step, shared, round, write; };        // write: us per MB of C
     static constexpr Cost kCosts[4][smat::kQuadShapes] = {
-        {{3.4, 0.39, 0.06}, {5.0, 0.311, 0.088}, {4.1, 0.256, 0.093}, {3.4, 0.1825, 0.062}, {2.9, 0.142, 0.054}},     // fp16, bf16
-        {{3.4, 0.562, 0.079}, {5.2, 0.467, 0.05}, {4.3, 0.346, 0.064}, {3.15, 0.2125, 0.081}, {2.6, 0.171, 0.108}},   // e4m3
-        {{4.5, 0.81, 0.0}, {5.4, 0.627, 0.03}, {4.3, 0.514, 0.0}, {4.4, 0.33, 0.0}, {2.8, 0.239, 0.026}},             // e5m2
-        {{5.1, 0.431, 0.0}, {5.1, 0.312, 0.24}, {4.2, 0.254, 0.17}, {3.7, 0.174, 0.12}, {2.85, 0.151, 0.122}},        // int8
+        // fp16, bf16
+        {{5.82, 0.317, 0.091, 0.0, 0.189}, {5.51, 0.305, 0.058, 0.0, 0.205}, {4.57, 0.260, 0.025, 0.0, 0.257}, {4.27, 0.178, 0.023, 0.0, 0.189},
+         {3.74, 0.147, 0.018, 0.0, 0.187}},
+        // e4m3
+        {{6.25, 0.529, 0.020, 0.0, 0.231}, {5.60, 0.451, 0.0, 0.0, 0.269}, {4.57, 0.358, 0.0, 0.0, 0.289}, {4.05, 0.224, 0.033, 0.0, 0.212},
+         {3.62, 0.197, 0.035, 0.0, 0.250}, {5.62, 0.405, 0.009, 0.260, 0.129}, {4.86, 0.303, 0.008, 0.263, 0.154}, {4.36, 0.251, 0.009, 0.185, 0.162}},
+        // e5m2
+        {{6.66, 0.701, 0.019, 0.0, 0.234}, {5.95, 0.592, 0.0, 0.0, 0.254}, {4.92, 0.469, 0.0, 0.0, 0.308}, {4.66, 0.296, 0.0, 0.0, 0.201},
+         {3.79, 0.208, 0.024, 0.0, 0.269}},
+        // int8
+        {{6.16, 0.336, 0.035, 0.0, 0.212}, {5.24, 0.365, 0.041, 0.0, 0.223}, {4.25, 0.320, 0.019, 0.0, 0.274}, {4.13, 0.210, 0.036, 0.0, 0.209},
+         {3.86, 0.173, 0.061, 0.0, 0.222}, {5.46, 0.301, 0.026, 0.088, 0.130}, {4.52, 0.319, 0.054, 0.061, 0.146}, {4.03, 0.221, 0.052, 0.107, 0.160}},
     };
-    static constexpr double kWrite[smat::kQuadShapes] = {0.22, 0.22, 0.22, 0.12, 0.04};                            // us per MB of C
     const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : h.dtype == SMAT_E4M3 ? 1 : h.dtype == SMAT_E5M2 ? 2 : 3][t.quad_shape];
     const int64_t columns = smat::quad_shape_columns(t.quad_shape);
     const double n_tiles = static_cast<double>(smat::quad_row_tiles(t)) * static_cast<double>((N + columns - 1) / columns);
     const double steps = static_cast<double>(h.tiled_quad_steps()) / t.n, c_mb = static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
     const int ks = smat::dense_split(t, N);
     if (ks > 1) return 10.5 + c.step * std::ceil(steps / ks) + std::min(9.0, 0.05 * n_tiles * ks);
-    return c.start + std::ceil(n_tiles / 256.0) * steps * c.step + n_tiles / 256.0 * steps * c.shared + kWrite[t.quad_shape] * c_mb;
+    const double in_a_unit = std::ceil(n_tiles / 256.0);
+    return c.start + in_a_unit * steps * c.step + n_tiles / 256.0 * steps * c.shared +
+           std::ceil(in_a_unit / smat::quad_shape_resident(t.quad_shape)) * steps * c.round + c.write * c_mb;
 }
 
 // The same on the per-row kernels, fitted on these products and 1000 more (within 11-16 %; up to 128 bytes of a row of B 7-12 %): rows of B by the byte and by
@@ -1166,7 +1175,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         double best = std::numeric_limits<double>::infinity();
         int best_shape = smat::kQuad256x128;
         bool best_tail = false;
-        for (int choice = 0; choice < 2 * smat::kQuadShapes; ++choice) {
+        for (int choice = 0; choice < 2 * smat::quad_shapes(h->dtype); ++choice) {
             const int shape = choice / 2;
             const bool tail = choice % 2 != 0;
             if (tail && !tiles.quad_tail) continue;
@@ -1176,7 +1185,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             for (int64_t c0 = 0; c0 < N; c0 += chunk) {
                 const int64_t n = std::min(chunk, N - c0);
                 us += quad_tiles_us(*h, tiles, n);
-                if (!in_pieces) us += 3.7 + 0.3e-6 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes);      // the copy of B
+                if (!in_pieces) us += 2.4 + 0.5e-6 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes);      // the copy of B
             }
             if (us < best) { best = us; best_shape = shape; best_tail = tail; }
         }

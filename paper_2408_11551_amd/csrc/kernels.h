@@ -76,10 +76,20 @@ struct DenseTiles {
     bool quad_tail_tiled = false;          // the tiles cover super row number n too
 };
 
-// Rows and columns of a tile on quads.
-enum QuadShape { kQuad256x128 = 0, kQuad256x96, kQuad256x64, kQuad128x64, kQuad128x32, kQuadShapes };
-constexpr int quad_shape_rows(int shape) { return shape >= kQuad128x64 ? 128 : 256; }
-constexpr int quad_shape_columns(int shape) { return shape == kQuad256x128 ? 128 : shape == kQuad256x96 ? 96 : shape == kQuad128x32 ? 32 : 64; }
+// Rows and columns of a tile on quads; the last three have one group of four waves per workgroup instead of two, and several workgroups share a compute unit.
+enum QuadShape { kQuad256x128 = 0, kQuad256x96, kQuad256x64, kQuad128x64, kQuad128x32, kQuad256x128Single, kQuad256x96Single, kQuad256x64Single, kQuadShapes };
+constexpr int quad_shape_rows(int shape) { return shape == kQuad128x64 || shape == kQuad128x32 ? 128 : 256; }
+constexpr int quad_shape_columns(int shape)
+{
+    return shape == kQuad256x128 || shape == kQuad256x128Single ? 128 : shape == kQuad256x96 || shape == kQuad256x96Single ? 96 : shape == kQuad128x32 ? 32 : 64;
+}
+constexpr int quad_shape_groups(int shape) { return shape >= kQuad256x128Single ? 1 : 2; }
+// Shapes that a type (smat_dtype_t) has: one group adds the products of all steps in one chain where two add two halves, and in fp32 that is less exact (relative
+// error against 64 bits, 4096 x 4096 at 10 % in bf16 9.4e-8 with two groups, 1.34e-7 with one; e5m2 6.9e-9 and 7.8e-9).  int8 is exact, and what e4m3 loses
+// it loses inside an instruction (3.63e-6 either way).
+constexpr int quad_shapes(int dtype) { return dtype == 2 || dtype == 4 ? kQuadShapes : kQuad256x128Single; }
+// workgroups that a compute unit holds
+constexpr int quad_shape_resident(int shape) { return quad_shape_groups(shape) == 2 ? 1 : shape == kQuad256x64Single ? 3 : 2; }
 // Tiles per slab of columns.  Of a last super row with few block rows those that have any.
 inline int64_t quad_row_tiles(const DenseTiles& t)
 {

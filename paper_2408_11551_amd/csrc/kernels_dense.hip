@@ -596,12 +596,12 @@ static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const vo
     using Acc = typename Elem<DT>::Acc;
     const int vec_store = (ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 && N % 4 == 0) ? 1 : 0;
     // long super rows: two wave groups per workgroup; short ones: one group, two workgroups per CU
-    const bool deep = t.mean_steps >= kDeepSteps;
+    const bool deep = t.mean_steps >= kDeepSteps || t.n_quad_steps > 0;
     const int shape = t.n_quad_steps > 0 ? t.quad_shape : kQuad256x128;
     const int ks = dense_split(t, N);
     static thread_local char name[40];
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
-    if (shape != kQuad256x128) snprintf(name, sizeof(name), "spmm_dense_%s_g2_%dx%d", type, quad_shape_rows(shape), quad_shape_columns(shape));
+    if (shape != kQuad256x128) snprintf(name, sizeof(name), "spmm_dense_%s_g%d_%dx%d", type, quad_shape_groups(shape), quad_shape_rows(shape), quad_shape_columns(shape));
     else if (ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d", type, deep ? 2 : 1, ks);
     else snprintf(name, sizeof(name), "spmm_dense_%s_g%d", type, deep ? 2 : 1);
     *variant = name;

@@ -24,6 +24,13 @@
 // in int8, N = 256 / 512 21.9 / 24.5 -> 10.4 / 15.9.  Also built: 112 and 80 columns, 128 x 128, 128 x 96 (within 1 % of the best of these on 400
 // products), and a deeper ring for the smallest, which is not bound by latency (10.9 -> 11.9 us).
 //
+// Two groups leave a compute unit to one workgroup (eight waves of up to 256 registers): all of it waits while a tile begins, hands over and stores.  With
+// more tiles than compute units that is worse than what the groups are for, so e4m3 and int8 have three of the shapes also with one group of four waves that takes all
+// steps (KG = 1): two workgroups share a compute unit (256 x 64: three), one's loop runs beside the other's start and stores, no partial sums change
+// hands, and a barrier joins four waves instead of eight.  us, the best shape of two groups and of one: 4696 x 3919 at 10 % in int8, N = 2368 40.8 -> 34.8;
+// 3247 x 2257 at 20 %, N = 2816 30.4 -> 25.0; 3484 x 3387 at 5 % in e4m3, N = 3560 54.9 -> 46.9.  (The other types would gain as much, f16 5541 x 1077, N = 1598 31.7 ->
+// 25.8, but add less exactly in one chain: kernels.h.  128 x 64 and 128 x 32 with one group: the best of 0.2 % of 1935 products, not built.)
+//
 // What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  (4096 x 4096
 // in bf16, N = 2048, with parts left out: all 42 us, no matrix instructions 35, loads alone 35, matrix instructions alone 27, neither 13.)  The 8-bit
 // floats: the matrix units, which take 64 instructions of 16 clocks per step and wave (10 % fill: 6000 x 4096, N = 784
@@ -106,8 +113,8 @@ struct QuadTables {
     int no_step;                       // number of the step that names no row of B
 };
 
-template <int DT, int NT, int RM>
-__global__ __launch_bounds__(512)
+template <int DT, int NT, int RM, int KG>
+__global__ __launch_bounds__(256 * KG)
 __attribute__((amdgpu_waves_per_eu(RM == 2 && NT <= 4 ? 4 : 2, RM == 2 && NT <= 4 ? 4 : 2)))
 void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, const int32_t* __restrict__ super_rows,
                            const int32_t* __restrict__ step_ptr, const void* __restrict__ B, const int32_t* __restrict__ quad_rows,
@@ -123,7 +130,6 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
     constexpr int PL = PW / 2;                     // loads of a wave per panel
     constexpr int RD = 3;                          // ring depth: panels in LDS, values and tables in registers
     constexpr int AHEAD = RD - 1;                  // steps that loads are ahead of the matrix instructions
-    constexpr int KG = 2;                          // groups of four waves
     constexpr uint32_t kRow = 16u * PW * ES;       // bytes of a panel row
     constexpr uint32_t kPanel = quad_columns(ES) * kRow;
     constexpr uint32_t kTable = quad_columns(ES) * 4u;
@@ -131,7 +137,7 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
     constexpr int ID = IB * RM / 16;               // dwords of them for this wave
     constexpr int LOADS = PL + RM + 2;             // loads of a wave per step: panel, values, positions, table
     // two rings of panels; the hand-over at the end
-    constexpr uint32_t kRings = 2 * RD * kPanel, kHandover = 4096u * RM * NT;
+    constexpr uint32_t kRings = KG * RD * kPanel, kHandover = KG == 2 ? 4096u * RM * NT : 0u;
     __shared__ u32x4 lds_words[(kRings > kHandover ? kRings : kHandover) / 16];
 
     int sidx, slab;
@@ -141,7 +147,7 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
     const int tid = threadIdx.x & 255;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 8);
+    const int kg = KG == 2 ? __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 8) : 0;
     const int i = lane & 15, g = lane >> 4;
     const int super = super_rows[sidx];
     const int n0 = slab * (16 * NT);
@@ -391,10 +397,16 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)");
     }
     int32_t out_rows[RM][4] = {};
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int r = 0; r < RM; ++r)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) out_rows[r][y] = tab.perm[(static_cast<int64_t>(super) * 16 + j0 + r) * 16 + 4 * g + y];
+    }
     finish_tile<DT, KG, RM, NT>(acc, out_rows, lds_words, kg, wave, lane, super, j0, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
 }
 
-template <int DT, int NT, int RM>
+template <int DT, int NT, int RM, int KG = 2>
 static void launch_quad_shape(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
                               int64_t N, hipStream_t s)
 {
@@ -402,7 +414,7 @@ static void launch_quad_shape(const DeviceBcsr& d, const DenseTiles& t, int ks, 
     const int per_xcd = (n_row_tiles * n_slab + 7) / 8;
     const dim3 grid(static_cast<unsigned>(8 * per_xcd), 1, static_cast<unsigned>(ks));
     const QuadTables tab{t.quad_index, d.perm, t.scratch, t.n_quad_steps};
-    hipLaunchKernelGGL((spmm_quad_tile_kernel<DT, NT, RM>), grid, dim3(512), 0, s, n_row_tiles, n_slab, per_xcd, static_cast<int>(N), t.super_rows,
+    hipLaunchKernelGGL((spmm_quad_tile_kernel<DT, NT, RM, KG>), grid, dim3(256 * KG), 0, s, n_row_tiles, n_slab, per_xcd, static_cast<int>(N), t.super_rows,
                        t.step_ptr, B, t.quad_rows, static_cast<uint32_t>(ldb * Elem<DT>::ES), static_cast<uint32_t>(d.K), t.vals, tab,
                        static_cast<typename Elem<DT>::Out*>(C), ldc);
 }
@@ -411,6 +423,13 @@ template <int DT>
 static void launch_quad_dtype(const DeviceBcsr& d, const DenseTiles& t, int ks, const void* B, int64_t ldb, void* C, int64_t ldc,
                               int64_t N, hipStream_t s)
 {
+    if constexpr (quad_shapes(DT) == kQuadShapes) {
+        switch (t.quad_shape) {
+        case kQuad256x128Single: return launch_quad_shape<DT, 8, 4, 1>(d, t, 1, B, ldb, C, ldc, N, s);
+        case kQuad256x96Single: return launch_quad_shape<DT, 6, 4, 1>(d, t, 1, B, ldb, C, ldc, N, s);
+        case kQuad256x64Single: return launch_quad_shape<DT, 4, 4, 1>(d, t, 1, B, ldb, C, ldc, N, s);
+        }
+    }
     switch (t.quad_shape) {
     case kQuad256x96: return launch_quad_shape<DT, 6, 4>(d, t, 1, B, ldb, C, ldc, N, s);
     case kQuad256x64: return launch_quad_shape<DT, 4, 4>(d, t, 1, B, ldb, C, ldc, N, s);
