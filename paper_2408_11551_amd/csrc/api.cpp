@@ -327,7 +327,11 @@ void plan_quads(smat_handle& h, smat::Workers& workers)
     const int es = h.elem_bytes;
     const int64_t cols = smat::quad_columns(es), K = h.csr.K;
     const int64_t n = static_cast<int64_t>(h.dense_super.size()), steps = static_cast<int64_t>(h.step_rows.size());
-    if (n == 0 || static_cast<double>(steps) < smat::kDeepSteps * static_cast<double>(n)) return;
+    // (Fewer than 32 steps of the other form, with tiles asked for: that form, two workgroups to a compute unit.  Chosen by estimate it was never the best of
+    // 4200 products of 600 ... 8192 columns: 4949 x 904 at 20 % in int8, N = 352 13.3 us, rows 18.7, smaller tiles on quads 7.6; 5352 x 1392 at 10 % in e4m3,
+    // N = 192 18.0, 16.7 and 7.4; 7658 x 608 at 10 % in bf16, N = 247 20.1, 19.8 and 10.5.)
+    const double fewest = h.dense_mode == 0 ? 4.0 : smat::kDeepSteps;
+    if (n == 0 || static_cast<double>(steps) < fewest * static_cast<double>(n)) return;
     if (h.dense_slots < static_cast<uint64_t>(12 * steps)) return;                       // block rows that are not there cost nothing in the other form
     if (smat::quad_fill_lds(K, 1, es) > smat::kQuadFillLds) return;
     int64_t nnz = 0;
@@ -1039,18 +1043,18 @@ int64_t columns_of_rows(const smat_handle& h) { return h.bcsr.grouped ? h.b_rows
 // 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
 // once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
 // out of the L2s or from further away.
-// (Both infinite where it does not take N columns at all.)
+// (This one infinite where it does not take N columns at all, and where a super row has few steps: rows are faster then, 7693 x 1617 at 20 % in e5m2, N = 32 6.9 and 8.7 us.)
 struct FewColumns { double quads_us, rows_us; bool take() const { return quads_us + 0.3 < rows_us; } };
 FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
 {
     constexpr double kNever = std::numeric_limits<double>::infinity();
     if (h.tiles.n_quad_steps == 0 || N > 32) return {kNever, kNever};
     const int es = h.elem_bytes, row_bytes = smat::quad_row_bytes(es, N, h.max_quad_steps);
-    if (row_bytes == 0) return {kNever, kNever};
-    const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
     const double columns = static_cast<double>(columns_of_rows(h)), block_rows = 16.0 * h.tiles.n;
     const double per_column = es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
     const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
+    if (row_bytes == 0 || h.tiles.mean_steps < smat::kDeepSteps) return {kNever, rows_us};
+    const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
     const double a_mb = static_cast<double>(h.tiles.n_quad_steps) * (es == 1 ? 20480e-6 : 18432e-6);
     const double quads_us = 4.2 + 0.008 * h.max_quad_steps * passes + 1.0e-5 * static_cast<double>(smat::quad_rows_lds(h.max_quad_steps, es, row_bytes)) +
                             a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (off_dwords ? 0.7 : 0.0) +
@@ -1090,19 +1094,20 @@ double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
            std::ceil(in_a_unit / smat::quad_shape_resident(t.quad_shape)) * steps * c.round + c.write * c_mb;
 }
 
-// The same on the per-row kernels, fitted on these products and 1000 more (within 11-16 %; up to 128 bytes of a row of B 7-12 %): rows of B by the byte and by
+// The same on the per-row kernels, fitted on 1241 of these products that took up to 45 us (N > 32; within 8-14 %; with it the faster of rows and tiles is missed by
+// 0.6 % on average): rows of B by the byte and by
 // the 256-byte slab, values, C; rows of B that begin on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes, where
 // mostly kernels_lines.hip runs, on dwords and off them.
 // Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
-// four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, now 0.87-0.92, and on dwords, where a row
+// four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, and on dwords, where a row
 // reaches into a line more, 0.83-0.92 either way.)
 double rows_us(const smat_handle& h, const void* dB, int64_t ldb, int64_t N)
 {
     struct Cost { double start, gather, slab, values, write; };
-    static constexpr Cost kCosts[2][6] = {{{3.35, 0.003, 12.3, 0.026, 0.24}, {3.7, 0.021, 9.5, 0.0, 0.06}, {3.55, 0.007, 12.65, 0.0, 0.21}, {7.7, 0.0, 13.6, 0.32, 0.6},
-                                           {2.9, 0.05, 0.94, 0.06, 0.0}, {2.8, 0.11, 1.5, 0.0, 0.55}},
-                                          {{3.7, 0.0, 14.4, 0.09, 0.37}, {4.6, 0.017, 11.2, 0.013, 0.28}, {4.15, 0.012, 12.3, 0.0, 0.36}, {6.0, 0.0, 17.2, 0.57, 0.5},
-                                           {3.35, 0.064, 0.0, 0.06, 0.0}, {4.35, 0.104, 1.05, 0.0, 0.0}}};
+    static constexpr Cost kCosts[2][6] = {{{3.67, 0.0215, 8.71, 0.0, 0.196}, {4.02, 0.0311, 8.06, 0.0, 0.041}, {3.83, 0.0375, 7.14, 0.0, 0.218}, {4.00, 0.0701, 0.0, 0.450, 0.248},
+                                           {3.73, 0.0159, 6.89, 0.0, 0.0}, {3.65, 0.0412, 5.62, 0.043, 0.0}},
+                                          {{4.52, 0.0352, 5.34, 0.0, 0.014}, {4.34, 0.0, 15.52, 0.018, 0.260}, {4.79, 0.0088, 13.49, 0.0, 0.324}, {3.86, 0.0576, 4.36, 0.663, 0.405},
+                                           {4.05, 0.0540, 0.0, 0.104, 0.0}, {4.05, 0.1053, 0.0, 0.130, 0.0}}};
     const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256;
     const double m_rows = static_cast<double>(h.b_rows) * 1e-6;
     // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
@@ -1111,7 +1116,7 @@ double rows_us(const smat_handle& h, const void* dB, int64_t ldb, int64_t N)
     auto us_of = [&](int64_t starts) {
         const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - h.elem_bytes) <= 128;
         const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
-        const double row = std::min(c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs), 0.14 * static_cast<double>(bytes));
+        const double row = c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs);
         return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
     };
     const int64_t distance = ldb * h.elem_bytes;
@@ -1180,6 +1185,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const bool tail = choice % 2 != 0;
             if (tail && !tiles.quad_tail) continue;
             take(shape, tail);
+            // (one group per workgroup is for units that share several)
+            if (smat::quad_shape_groups(shape) == 1 && smat::quad_row_tiles(tiles) * ((N + smat::quad_shape_columns(shape) - 1) / smat::quad_shape_columns(shape)) <= 256) continue;
             // (a launch of a few block rows: as long as the longest one's walk)
             double us = h->dev_rest.n_order > 0 && !tail ? 3.0 + 0.09 * static_cast<double>(h->dev_rest.max_row_packs) : 0.0;
             for (int64_t c0 = 0; c0 < N; c0 += chunk) {
@@ -1191,7 +1198,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         }
         take(best_shape, best_tail);
         const FewColumns few = few_columns(*h, N, off_dwords);
-        use_tiles = 1.08 * best + 0.5 <= rows_us(*h, dB, ldb, N) && !(few.take() && few.quads_us < best);
+        const double rows = N <= 32 ? few.rows_us : rows_us(*h, dB, ldb, N);        // (each fitted on its widths)
+        use_tiles = best + 0.5 <= rows && !(few.take() && few.quads_us < best);
     } else if (use_tiles && h->dense_mode == 0) {
         double t_tiles = 0;
         for (int64_t c0 = 0; c0 < N; c0 += chunk) {
@@ -1202,9 +1210,10 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const int ks = hard_limit ? smat::dense_split(tiles, n) : smat::dense_parts(tiles, n);
             // us per step of a tile, alone on its compute unit (an 8-bit step covers twice the block columns)
             const double quad_us = h->elem_bytes == 2 ? 0.43 : h->dtype == SMAT_I8 ? 0.37 : h->dtype == SMAT_E4M3 ? 0.6 : 0.7;
-            const double walk_us = tiles.n_quad_steps ? quad_us * tiles.n_quad_steps / tiles.n
-                                                      : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
-            t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (tiles.n_quad_steps ? 6.0 : 4.0)) + 1.5;
+            // (on quads where the static area is the limit: tiles of 256 x 128, and of few steps priced as the other form, which such calls are accepted or refused by)
+            const bool as_quads = tiles.n_quad_steps > 0 && tiles.mean_steps >= smat::kDeepSteps;
+            const double walk_us = as_quads ? quad_us * tiles.n_quad_steps / tiles.n : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
+            t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (as_quads ? 6.0 : 4.0)) + 1.5;
             if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 8.0e6;     // partial tiles out and in again
             if (!in_pieces) t_tiles += 3.0 + 2.0 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes) / 4.0e6;  // the copy of B
         }
