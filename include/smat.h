@@ -115,18 +115,19 @@ smat_status_t smat_preprocess(int64_t M, int64_t K,
                               smat_dtype_t dtype, const smat_options_t *opt,
                               smat_handle_t **out);
 
+/* Device memory on demand: `bytes` of it, 256-byte aligned, and in *stream the stream it may be used on, which is to be one of the calling
+ * thread's current device then; or NULL.  Called at most once, on the thread of the call that it is given to, which has no use for the memory any more when
+ * it returns. */
+typedef void *(*smat_scratch_fn)(size_t bytes, void *user, void **stream);
+
 /* The same handle, made with the device's help: of a large matrix in which most clusters stay single rows (a graph, random
- * entries) the pairs of rows that could start a cluster are looked for on the device, in dev_scratch (DEVICE, 256-byte aligned,
- * smat_preprocess_scratch_bytes() of the matrix, or NULL), which is the library's for the duration of the call only.  The call may enqueue copies
- * and kernels on `stream` and waits for them; where it does not pay, the scratch is too small, or the stream is being captured, it does what
- * smat_preprocess does. */
+ * entries) the pairs of rows that could start a cluster are looked for on the device, in memory (64 MiB at most) that `scratch` gives.  The call may
+ * enqueue copies and kernels on that stream and waits for them; where it does not pay it asks for nothing, and there, where it gets nothing, and
+ * where the stream is being captured, it does what smat_preprocess does. */
 smat_status_t smat_preprocess_on_device(int64_t M, int64_t K,
                                         const int64_t *row_ptr, const int32_t *col_idx, const void *vals,
                                         smat_dtype_t dtype, const smat_options_t *opt,
-                                        void *dev_scratch, size_t bytes, void *stream, smat_handle_t **out);
-
-/* Device memory for smat_preprocess_on_device on a matrix of this size: 64 MiB at most, 0 where it would not use any. */
-smat_status_t smat_preprocess_scratch_bytes(int64_t M, int64_t K, int64_t nnz, const smat_options_t *opt, size_t *bytes);
+                                        smat_scratch_fn scratch, void *user, smat_handle_t **out);
 
 /* The search of smat_preprocess_on_device by itself: all pairs of n row patterns of which 1000 |a n b| > keep |a u b| (keep = 1000 - tau_permille), as
  * two numbers each (the smaller first), in any order.  Pattern k has the block columns columns[ptr[k]] ... columns[ptr[k + 1] - 1] (HOST,

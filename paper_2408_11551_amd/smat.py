@@ -7,6 +7,7 @@ missing and cannot be built, importing this module fails.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -49,6 +50,9 @@ class _Options(ctypes.Structure):
                 ("concurrent_streams", ctypes.c_int)]
 
 
+_ScratchFn = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p))
+
+
 def lib_path() -> str:
     return _build.OUT
 
@@ -70,9 +74,7 @@ def _load():
     lib.smat_preprocess.argtypes = [i64, i64, vp, vp, vp, ctypes.c_int, ctypes.POINTER(_Options),
                                     ctypes.POINTER(vp)]
     lib.smat_preprocess_on_device.restype = ctypes.c_int
-    lib.smat_preprocess_on_device.argtypes = lib.smat_preprocess.argtypes[:-1] + [vp, sz, vp, ctypes.POINTER(vp)]
-    lib.smat_preprocess_scratch_bytes.restype = ctypes.c_int
-    lib.smat_preprocess_scratch_bytes.argtypes = [i64, i64, i64, ctypes.POINTER(_Options), ctypes.POINTER(sz)]
+    lib.smat_preprocess_on_device.argtypes = lib.smat_preprocess.argtypes[:-1] + [_ScratchFn, vp, ctypes.POINTER(vp)]
     lib.smat_pattern_partners.restype = ctypes.c_int
     lib.smat_pattern_partners.argtypes = [i64, i64, vp, vp, ctypes.c_int, vp, sz, vp, vp, i64, ctypes.POINTER(i64)]
     lib.smat_probe_read.restype = ctypes.c_int
@@ -183,7 +185,7 @@ def smat_preprocess(M, K, row_ptr, col_idx, vals_bits, dtype, *, reorder=1, tau_
 
 def smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, *, device, reorder=1, tau_permille=700,
                               block_h=16, block_w=16, dense_tiles=0, concurrent_streams=2) -> int:
-    """The same with the help of a device, in scratch memory that is given back before the call returns; None: none."""
+    """The same with the help of a device (None: none), in scratch memory that is asked for once it pays and given back before the call returns."""
     rp, rp_p = _host(row_ptr, np.int64)
     ci, ci_p = _host(col_idx, np.int32)
     vals_bits = np.asarray(vals_bits)
@@ -198,20 +200,23 @@ def smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, *, devic
     opt = _Options(block_h, block_w, reorder, tau_permille, dense_tiles, concurrent_streams)
     out = ctypes.c_void_p()
     args = (M, K, rp_p, ci_p, vb_p, _dtype_code(dtype), ctypes.byref(opt))
-    need = ctypes.c_size_t()
-    if device is not None and min(M, K, nnz) >= 0:
-        _check(_lib.smat_preprocess_scratch_bytes(M, K, nnz, ctypes.byref(opt), ctypes.byref(need)))
-    if need.value == 0:
+    if device is None:
         _check(_lib.smat_preprocess(*args, ctypes.byref(out)))
         return out.value
-    import torch
-    with torch.cuda.device(device):
-        try:
-            scratch = torch.empty(need.value, dtype=torch.uint8, device=device)
-        except torch.cuda.OutOfMemoryError:
-            _check(_lib.smat_preprocess(*args, ctypes.byref(out)))
-            return out.value
-        _check(_lib.smat_preprocess_on_device(*args, ctypes.c_void_p(scratch.data_ptr()), need.value, _stream_ptr(None), ctypes.byref(out)))
+    with contextlib.ExitStack() as until_done:
+        def scratch(nbytes, _user, stream):
+            import torch
+            until_done.enter_context(torch.cuda.device(device))
+            if torch.cuda.is_current_stream_capturing():
+                return None
+            try:
+                held = torch.empty(nbytes, dtype=torch.uint8, device=device)
+            except torch.cuda.OutOfMemoryError:
+                return None
+            until_done.callback(lambda _held: None, held)
+            stream[0] = _stream_ptr(None).value
+            return held.data_ptr()
+        _check(_lib.smat_preprocess_on_device(*args, _ScratchFn(scratch), None, ctypes.byref(out)))
     return out.value
 
 

@@ -101,3 +101,21 @@ def test_the_handle_is_the_hosts(M, K, per_row, tau):
         assert np.array_equal(a, b)
     S.smat_destroy(alone)
     S.smat_destroy(helped)
+
+
+def test_memory_is_asked_for_only_where_the_search_pays():
+    """A band's rows join their clusters, so nothing is looked for: its set-up takes no memory of the device."""
+    M, half = 20000, 16
+    rows = np.repeat(np.arange(M), 2 * half + 1)
+    cols = rows + np.tile(np.arange(-half, half + 1), M)
+    ok = (cols >= 0) & (cols < M)
+    row_ptr = np.zeros(M + 1, np.int64)
+    np.cumsum(np.bincount(rows[ok], minlength=M), out=row_ptr[1:])
+    before = torch.cuda.memory_stats().get("allocation.all.allocated", 0)
+    band = S.smat_preprocess_on_device(M, M, row_ptr, cols[ok].astype(np.int32), np.ones(ok.sum(), np.uint16), "f16", device="cuda:0")
+    assert torch.cuda.memory_stats().get("allocation.all.allocated", 0) == before
+    S.smat_destroy(band)
+    row_ptr, col_idx = _graph(40000, 40000, 12, 1)
+    graph = S.smat_preprocess_on_device(40000, 40000, row_ptr, col_idx, np.ones(col_idx.size, np.uint16), "f16", device="cuda:0")
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before + 1
+    S.smat_destroy(graph)
