@@ -255,19 +255,29 @@ struct ColumnIndex {
     Buf<int64_t> ptr;       // [nbc+1]
     Buf<int64_t> len;       // [nbc] classes still listed (the clustering drops those that are used up)
     Buf<int32_t> classes;
-    Buf<int32_t> at;        // [patterns] where a class stands in the list of a column of its pattern, as long as nothing has been dropped
+    Buf<int32_t> at;        // [patterns] where a class stands in the list of a column of its pattern, as long as nothing has been dropped; for partners_of,
+                            // and empty where a search elsewhere may take its place
     bool dropped = false;
 };
 
-static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const PatternClasses& pc, Workers& workers)
+// wants_at(index): asked once the lists' lengths are known.
+template <typename F>
+static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const PatternClasses& pc, F&& wants_at, Workers& workers)
 {
     ColumnIndex inv;
     const int64_t n = pc.size();
     // counts by part of the classes and column, then the place of every part's first entry in every list
     const int64_t parts = nbc * workers.most() <= (int64_t{1} << 23) && n > 1024 ? workers.most() : 1;
     Buf<int64_t> place(static_cast<size_t>(parts * nbc));
+    // (Parts of as many entries: of a graph's patterns, which are in the order of their lengths, the last sixteenth has a third of them.  65536 rows of 16,
+    // sixteen threads: 2.5-2.9 ms in parts of as many patterns and with the places that partners_of wants, 0.8 in these and without.)
+    int64_t all = 0;
+    for (int64_t k = 0; k < n; ++k) all += pc.len[k];
+    std::vector<int64_t> first(static_cast<size_t>(parts) + 1, n);
+    for (int64_t k = 0, part = 0, before = 0; k < n && part < parts; before += pc.len[k++])
+        while (part < parts && before >= all * part / parts) first[part++] = k;
     auto entries = [&](int64_t part, auto&& take) {
-        for (int64_t k = n * part / parts; k < n * (part + 1) / parts; ++k)
+        for (int64_t k = first[part]; k < first[part + 1]; ++k)
             for (int64_t q = pat.ptr[pc.first_row[k]]; q < pat.ptr[pc.first_row[k] + 1]; ++q) take(pat.idx[q], k, q);
     };
     workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
@@ -291,13 +301,14 @@ static ColumnIndex index_columns(int64_t nbc, const Patterns& pat, const Pattern
     }
     inv.ptr[nbc] = total;
     inv.classes.resize(static_cast<size_t>(total));
-    inv.at.resize(pat.idx.size());
+    const bool with_at = wants_at(inv);
+    if (with_at) inv.at.resize(pat.idx.size());
     workers.ranges(parts, 1, [&](int64_t p0, int64_t p1, int) {
         for (int64_t part = p0; part < p1; ++part)
             entries(part, [&](int32_t c, int64_t k, int64_t q) {
                 const int64_t to = place[part * nbc + c]++;
                 inv.classes[to] = static_cast<int32_t>(k);
-                inv.at[q] = static_cast<int32_t>(to - inv.ptr[c]);
+                if (with_at) inv.at[q] = static_cast<int32_t>(to - inv.ptr[c]);
             });
     });
     return inv;
@@ -542,8 +553,19 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     order.reserve(static_cast<size_t>(M));
     const PatternClasses pc = group_equal_patterns(M, pat, workers);
     const int64_t n_classes = pc.size();
+    const int64_t keep = 1000 - tau_permille;
+    // What partners_of takes, in the counting of a pattern in a list by one thread (at most half the pairs of every list, a sixth of the time each, shared by the
+    // threads), and what a search elsewhere does, which takes the lists as they were made.
+    struct Prices { double here, there; };
+    auto prices = [&](const ColumnIndex& index) {
+        double pairs = 0;
+        for (int64_t c = 0; c < nbc; ++c) pairs += 0.5 * static_cast<double>(index.len[c]) * static_cast<double>(index.len[c]);
+        return Prices{0.25 * pairs / workers.most(), elsewhere && !index.dropped ? elsewhere->price(n_classes, nbc, index.ptr[nbc], pairs, n_classes ? pc.len[n_classes - 1] : 0)
+                                                                                 : std::numeric_limits<double>::infinity()};
+    };
+    auto found_here = [&](const ColumnIndex& index) { const Prices p = prices(index); return !(p.there < p.here); };
     // inverted index: classes of every block column
-    ColumnIndex inv = index_columns(nbc, pat, pc, workers);
+    ColumnIndex inv = index_columns(nbc, pat, pc, found_here, workers);
 
     std::vector<uint8_t> clustered(M, 0);
     // What the counting looks at per class, side by side.
@@ -571,7 +593,6 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
     }
     AscendingSet candidates(M);
     int64_t n_clusters = 0;
-    const int64_t keep = 1000 - tau_permille;
     Partners partners;                        // once they have been asked for
     constexpr int64_t kFirstAsk = 20000, kFirstClusters = 8, kFewClusters = 300000;     // (fewer clusters tell enough once so much has been counted)
     int64_t spent = 0, ask_at = kFirstAsk;    // counting done so far; when to look whether it is worth asking
@@ -647,17 +668,13 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
         counted_to = end;
     };
     // What it would save: the counting still to come for seeds that end up alone, if the rest of the rows goes like the rows so far, against
-    // that of partners_of (at most half the pairs of every list, a sixth of the time each), shared by the threads.  With the first look after
+    // what the search takes.  With the first look after
     // 300 000 counted and weighed dearer, the whole of smat_preprocess took 1.8 ms for 1317 rows of five entries (now 1.4), 3.4 for 6872 of 19 (2.3),
     // 14.9 for a graph of 65536 rows (13.7).
     auto ask_partners = [&]() {
         const double done = static_cast<double>(order.size()) / static_cast<double>(M);
         const double ahead = static_cast<double>(spent_alone) * (1.0 - done) / done;
-        double pairs = 0;
-        for (int64_t c = 0; c < nbc; ++c) pairs += 0.5 * static_cast<double>(inv.len[c]) * static_cast<double>(inv.len[c]);
-        const double here = 0.25 * pairs / workers.most();
-        // (a search elsewhere takes the lists as they were made)
-        const double there = elsewhere && !inv.dropped ? elsewhere->price(n_classes, nbc, inv.ptr[nbc], pairs, longest) : std::numeric_limits<double>::infinity();
+        const auto [here, there] = prices(inv);
         if (ahead < std::min(here, there) + 5e4) {
             ask_at = 2 * spent;
             return;
@@ -666,6 +683,7 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
             ask_at = 0;
             return;
         }
+        if (inv.at.empty() && !inv.dropped) inv = index_columns(nbc, pat, pc, [](const ColumnIndex&) { return true; }, workers);
         std::vector<int32_t> alive(static_cast<size_t>(n_classes));
         for (int64_t k = 0; k < n_classes; ++k) alive[k] = state[k].alive;
         ask_at = 0;
