@@ -80,7 +80,9 @@ public:
         d.most_pairs = static_cast<uint32_t>(most);
         d.found = d_found;
         const uint32_t first_long = t.first_of_len[static_cast<size_t>(std::min<int64_t>(short_pattern(), t.longest)) + 1];
-        ok = ok && launch_partners(d, first_long, stream) == 0;
+        double pairs = 0;
+        for (int64_t c = 0; c < t.nbc; ++c) pairs += std::pow(static_cast<double>(t.list_ptr[c + 1] - t.list_ptr[c]), 2.0);
+        ok = ok && launch_partners(d, first_long, entries > 0 ? pairs / static_cast<double>(entries) : 0.0, stream) == 0;
         uint32_t got[2] = {0, 0};
         ok = ok && hipMemcpyAsync(got, d_found, 8, hipMemcpyDeviceToHost, stream) == hipSuccess;
         ok = hipStreamSynchronize(stream) == hipSuccess && ok;       // also where something failed: the copies read the caller's tables

@@ -189,9 +189,9 @@ struct PartnerTables {
     uint32_t most_pairs = 0;
     uint32_t* found = nullptr;             // [2] pairs that there are, which may be more than most_pairs but stay below 2^32; not 0: a pattern has too many (both zero before)
 };
-// first_long: the first pattern of more than short_pattern() columns.
+// first_long: the first pattern of more than short_pattern() columns; mean_list: patterns in a column's list, as a pattern's column has them on average.
 uint32_t short_pattern();
-int launch_partners(const PartnerTables& t, uint32_t first_long, void* stream);
+int launch_partners(const PartnerTables& t, uint32_t first_long, double mean_list, void* stream);
 
 // The canonical BCSR of the paper on the device (Data Structures section), for the ablation
 // kernels only (ablation.hip).

@@ -6,8 +6,9 @@
 //
 //   * Patterns of more than kShortPattern columns: a workgroup each, exact counters of one or two bytes for a window of the patterns at a
 //     time (64 KiB of LDS).  Who comes to a counter first in the second pass takes it, and leaves zero behind.
-//   * Shorter ones, which are most of them: a wave each, without a barrier, and 2048 counters for all patterns, several to a counter.
-//     The few pairs that reach `least` by accident are told by comparing their columns, as are those that do.
+//   * Shorter ones, which are most of them: a wave each, without a barrier, and 2048 or 8192 counters for all patterns, several to a counter.
+//     The few pairs that reach `least` by accident are told by comparing their columns, as are those that do.  (Few as long as the lists are
+//     short: launch_partners.)
 //
 // What bounds it: the lists, read twice each from the L2s, and for a workgroup's pattern two barriers and the trip to its lists between them.  A graph
 // of 65536 rows of 16 (52 000 patterns, 134 million pairs of entries): 220 us for the long ones and 150-200 for the short, 740 with a workgroup for every
@@ -24,7 +25,7 @@ constexpr uint32_t kShortPattern = 32;         // (at most 64: a lane per column
 constexpr int kLongThreads = 512, kLongWaves = kLongThreads / 64;
 constexpr uint32_t kLongLds = 64 * 1024;
 constexpr int kShortThreads = 256, kShortWaves = kShortThreads / 64;
-constexpr uint32_t kSketch = 2048;             // counters of two bytes per wave
+constexpr uint32_t kSketch = 2048, kWideSketch = 8192;      // counters of two bytes per wave
 
 struct Pattern { uint32_t first, len, end, least; };
 
@@ -156,10 +157,11 @@ void long_partners_kernel(PartnerTables t, uint32_t first, uint32_t window)
 }
 
 // Patterns below number `last`, of kShortPattern columns at most.  (A counter reaches at most 32 n / 2048: n is below 2^22.)
+template <uint32_t SKETCH>
 __global__ __launch_bounds__(kShortThreads)
 void short_partners_kernel(PartnerTables t, uint32_t last)
 {
-    __shared__ uint32_t sketches[kShortWaves][kSketch / 2];
+    __shared__ uint32_t sketches[kShortWaves][SKETCH / 2];
     __shared__ HeldPairs<128> helds[kShortWaves];
     const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(tid >> 6));
@@ -179,7 +181,7 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
         const uint32_t k = last - 1 - static_cast<uint32_t>(y);
         const Pattern p = pattern_of(t, k);
         if (p.len == 0) break;                         // the empty pattern is number 0
-        for (uint32_t x = static_cast<uint32_t>(lane); x < kSketch / 2; x += 64) counts[x] = 0;
+        for (uint32_t x = static_cast<uint32_t>(lane); x < SKETCH / 2; x += 64) counts[x] = 0;
         uint32_t column = 0, begin = 0, stop = 0;
         if (static_cast<uint32_t>(lane) < p.len) {
             column = t.columns[p.first + static_cast<uint32_t>(lane)];
@@ -189,7 +191,7 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
         wave_fence();
         for (uint32_t q = 0; q < p.len; ++q)
             listed(t, lane_value(begin, q), lane_value(stop, q), k + 1, p.end, lane,
-                   [&](uint32_t other) { atomicAdd(&counts[other % kSketch / 2], 1u << (16 * (other % 2))); });
+                   [&](uint32_t other) { atomicAdd(&counts[other % SKETCH / 2], 1u << (16 * (other % 2))); });
         wave_fence();
         for (uint32_t q = 0; q < p.len; ++q) {
             const uint32_t from = lane_value(begin, q), to = lane_value(stop, q);
@@ -202,7 +204,7 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
                 for (uint32_t u = 0; u < 4; ++u) {
                     const uint32_t other = named[u];
                     // columns shared, or more
-                    const uint32_t most = other > k && other < p.end ? min(counts[other % kSketch / 2] >> (16 * (other % 2)) & 0xFFFFu, p.len) : 0u;
+                    const uint32_t most = other > k && other < p.end ? min(counts[other % SKETCH / 2] >> (16 * (other % 2)) & 0xFFFFu, p.len) : 0u;
                     const bool may = most >= p.least && passes(t, most, p.len, t.ptr[other + 1] - t.ptr[other]);
                     for (uint64_t left = __ballot(may); left; left &= left - 1) {
                         const uint32_t who = lane_value(other, static_cast<uint32_t>(__builtin_ctzll(left)));
@@ -227,9 +229,15 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
     empty_hands();
 }
 
-int launch_partners(const PartnerTables& t, uint32_t first_long, void* stream)
+int launch_partners(const PartnerTables& t, uint32_t first_long, double mean_list, void* stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // A counter holds mean_list / counters per column of a pattern by accident and a partner at least 2 keep / (1000 + keep), whatever the pattern's length.  Above
+    // a third of that ever more pairs have to be told by their columns: 4200 rows of 50 (lists of 700) 1930 us with 2048 counters, 104 with 8192, which hold
+    // four times the lists; a graph of rows of 16 (lists of 256) 197 with 2048.
+    const double most_list = 0.35 * 2.0 * t.keep / (1000.0 + t.keep);
+    const uint32_t sketch = mean_list <= most_list * kSketch ? kSketch : kWideSketch;
+    if (mean_list > most_list * kWideSketch && t.n > kWideSketch) first_long = 0;
     if (t.n > first_long) {
         const bool bytes = t.longest < 256;
         const uint32_t counter = bytes ? 1 : 2, most = kLongLds / counter, left = static_cast<uint32_t>(t.n) - first_long;
@@ -240,7 +248,9 @@ int launch_partners(const PartnerTables& t, uint32_t first_long, void* stream)
     }
     if (first_long > 0) {
         const uint32_t groups = (first_long + kShortWaves - 1) / kShortWaves;
-        hipLaunchKernelGGL(short_partners_kernel, dim3(groups < 2048 ? groups : 2048), dim3(kShortThreads), 0, s, t, first_long);
+        const dim3 grid(groups < 2048 ? groups : 2048);
+        if (sketch == kSketch) hipLaunchKernelGGL(short_partners_kernel<kSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
+        else hipLaunchKernelGGL(short_partners_kernel<kWideSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
     }
     return static_cast<int>(hipGetLastError());
 }

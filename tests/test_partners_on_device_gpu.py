@@ -58,6 +58,15 @@ def test_pairs_are_those_of_brute_force(n, nbc, lengths, families, keep):
     assert got.shape == want.shape and np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], want)
 
 
+# Lists so long that many short patterns reach the bound by accident: more counters (keep = 700, and fewer patterns than these), or none but exact ones
+@pytest.mark.parametrize("n,nbc,lengths,keep", [(9000, 52, [9, 10, 11], 300), (9000, 52, [9, 10, 11], 700), (8150, 48, [9, 10, 11], 360), (3000, 80, [20, 31, 40], 400)])
+def test_pairs_where_columns_have_long_lists(n, nbc, lengths, keep):
+    ptr, columns = _patterns(n, nbc, lengths, n + keep, 0.05)
+    want = _brute(ptr, columns, nbc, keep)
+    got = S.smat_pattern_partners(ptr, columns, nbc, keep, torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0"), want.shape[0] + 1)
+    assert got.shape == want.shape and np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], want)
+
+
 @pytest.mark.parametrize("per_row", [34, 300])
 def test_more_patterns_than_a_workgroup_counts_at_a_time(per_row):
     """70 000 patterns beyond the short ones, in bytes and in halves; checked on the pairs that were planted, and that every pair found is one."""
