@@ -203,8 +203,9 @@ def smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, *, devic
     if device is None:
         _check(_lib.smat_preprocess(*args, ctypes.byref(out)))
         return out.value
+    raised = []
     with contextlib.ExitStack() as until_done:
-        def scratch(nbytes, _user, stream):
+        def give(nbytes, stream):
             import torch
             until_done.enter_context(torch.cuda.device(device))
             if torch.cuda.is_current_stream_capturing():
@@ -216,7 +217,19 @@ def smat_preprocess_on_device(M, K, row_ptr, col_idx, vals_bits, dtype, *, devic
             until_done.callback(lambda _held: None, held)
             stream[0] = _stream_ptr(None).value
             return held.data_ptr()
-        _check(_lib.smat_preprocess_on_device(*args, _ScratchFn(scratch), None, ctypes.byref(out)))
+
+        def scratch(nbytes, _user, stream):
+            # (an exception may not leave a callback: ctypes prints it, and the library would go on with whatever the result register held)
+            try:
+                return give(nbytes, stream)
+            except BaseException as e:
+                raised.append(e)
+                return None
+        status = _lib.smat_preprocess_on_device(*args, _ScratchFn(scratch), None, ctypes.byref(out))
+    if raised:
+        smat_destroy(out.value)
+        raise raised[0]
+    _check(status)
     return out.value
 
 
