@@ -130,8 +130,9 @@ smat_status_t smat_preprocess_on_device(int64_t M, int64_t K, const int64_t* row
                                         const smat_options_t* opt, smat_scratch_fn scratch, void* user, smat_handle_t** out)
 {
     // (below some hundred thousand entries the host's threads are done before the tables are up)
-    const int64_t nnz = row_ptr && M >= 0 ? row_ptr[M] : 0;
-    const bool worth = scratch && nnz >= 200000 && nnz < (int64_t{1} << 24) && M < (int64_t{1} << 22);
+    // (row_ptr[M] is only read of an M that smat_preprocess does not refuse before it looks at row_ptr)
+    const int64_t nnz = row_ptr && M >= 0 && M < (int64_t{1} << 22) ? row_ptr[M] : 0;
+    const bool worth = scratch && nnz >= 200000 && nnz < (int64_t{1} << 24);
     DevicePairSearch search(scratch, user, kMostScratch);
     return smat::preprocess(M, K, row_ptr, col_idx, vals, dtype, opt, worth ? &search : nullptr, out);
 }
