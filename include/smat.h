@@ -129,15 +129,6 @@ smat_status_t smat_preprocess_on_device(int64_t M, int64_t K,
                                         smat_dtype_t dtype, const smat_options_t *opt,
                                         smat_scratch_fn scratch, void *user, smat_handle_t **out);
 
-/* The search of smat_preprocess_on_device by itself: all pairs of n row patterns of which 1000 |a n b| > keep |a u b| (keep = 1000 - tau_permille), as
- * two numbers each (the smaller first), in any order.  Pattern k has the block columns columns[ptr[k]] ... columns[ptr[k + 1] - 1] (HOST,
- * ascending, below n_columns), and none has fewer than the one before it.  pairs: HOST int32[2 * room].  SMAT_ERR_UNSUPPORTED where
- * smat_preprocess_on_device would leave the search to the host: a pattern with more partners than the kernels hold at a time, or
- * not enough scratch. */
-smat_status_t smat_pattern_partners(int64_t n, int64_t n_columns, const uint32_t *ptr, const uint32_t *columns, int keep,
-                                    void *dev_scratch, size_t bytes, void *stream,
-                                    int32_t *pairs, int64_t room, int64_t *count);
-
 /* Sizes and counts of the preprocessed matrix: number of block rows ceil(M/16),
  * number of stored blocks n_e (Eq. 2 bounds it), n_e under the identity order,
  * and whether the identity order was kept.  Any out pointer may be NULL. */

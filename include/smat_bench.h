@@ -2,8 +2,8 @@
  * smat_bench.h -- measurement entry points of the MI355X (gfx950) blocked SpMM library.
  *
  * Not part of the method's interface (that is smat.h): the reduced kernels of the paper's
- * optimisation-step comparison, and six probe kernels that measure what the device delivers
- * for the access patterns the SpMM kernels are made of.  Conventions as in smat.h.
+ * optimisation-step comparison, six probe kernels that measure what the device delivers
+ * for the access patterns the SpMM kernels are made of, and a part of the set-up by itself.  Conventions as in smat.h.
  */
 #ifndef SMAT_BENCH_H
 #define SMAT_BENCH_H
@@ -81,6 +81,15 @@ smat_status_t smat_probe_pieces(const void *dev_table, uint32_t row_bytes, const
 smat_status_t smat_probe_tile_step(int workgroups, int steps, int parts, const void *dev_buf, size_t bytes,
                                    void *dev_sink, void *stream);
 smat_status_t smat_probe_mfma(int workgroups, int iters, void *dev_sink, void *stream);
+
+/* The search of smat_preprocess_on_device by itself, for its test: all pairs of n row patterns of which 1000 |a n b| > keep |a u b| (keep = 1000 - tau_permille), as
+ * two numbers each (the smaller first), in any order.  Pattern k has the block columns columns[ptr[k]] ... columns[ptr[k + 1] - 1] (HOST,
+ * ascending, each once, below n_columns; ptr[0] = 0), and none has fewer than the one before it: anything else is SMAT_ERR_INVALID_ARG.  pairs: HOST int32[2 * room].  SMAT_ERR_UNSUPPORTED where
+ * smat_preprocess_on_device would leave the search to the host: a pattern with more partners than the kernels hold at a time, or
+ * not enough scratch. */
+smat_status_t smat_pattern_partners(int64_t n, int64_t n_columns, const uint32_t *ptr, const uint32_t *columns, int keep,
+                                    void *dev_scratch, size_t bytes, void *stream,
+                                    int32_t *pairs, int64_t room, int64_t *count);
 
 #ifdef __cplusplus
 }

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "api.h"
+#include "../../include/smat_bench.h"
 #include "kernels.h"
 
 namespace smat {
@@ -143,19 +144,24 @@ smat_status_t smat_pattern_partners(int64_t n, int64_t nbc, const uint32_t* ptr,
     if (n < 1 || nbc < 1 || !ptr || !columns || !pairs || !count || keep < 0 || keep > 1000) return fail(SMAT_ERR_INVALID_ARG, "invalid argument");
     if (!dev_scratch || reinterpret_cast<uintptr_t>(dev_scratch) % kAlign != 0) return fail(SMAT_ERR_INVALID_ARG, "dev_scratch must be 256-byte aligned");
     try {
+        // (the kernels' counters and the searches by length rest on all of this: a column named twice would carry from one pattern's counter into the next one's)
+        if (ptr[0] != 0) return fail(SMAT_ERR_INVALID_ARG, "ptr[0] must be 0");
+        for (int64_t k = 0; k < n; ++k) {
+            if (ptr[k + 1] < ptr[k]) return fail(SMAT_ERR_INVALID_ARG, "ptr decreases");
+            for (uint32_t x = ptr[k]; x < ptr[k + 1]; ++x)
+                if (columns[x] >= nbc || (x > ptr[k] && columns[x] <= columns[x - 1]))
+                    return fail(SMAT_ERR_INVALID_ARG, "columns of a pattern must ascend and lie below n_columns");
+        }
         const smat::Buf<uint32_t> p(ptr, ptr + n + 1), cols(columns, columns + ptr[n]);
         smat::Buf<uint32_t> list_ptr(static_cast<size_t>(nbc) + 1, 0u);
         smat::Buf<int32_t> lists(cols.size());
         int64_t longest = 0;
         for (int64_t k = 0; k < n; ++k) {
-            const int64_t len = static_cast<int64_t>(p[k + 1]) - p[k];
+            const int64_t len = p[k + 1] - p[k];
             if (len < longest) return fail(SMAT_ERR_INVALID_ARG, "patterns are not in the order of their lengths");
             longest = len;
         }
-        for (uint32_t c : cols) {
-            if (c >= nbc) return fail(SMAT_ERR_INVALID_ARG, "column out of range");
-            ++list_ptr[c + 1];
-        }
+        for (uint32_t c : cols) ++list_ptr[c + 1];
         double of_lists = 0;
         for (int64_t c = 0; c < nbc; ++c) {
             of_lists += 0.5 * list_ptr[c + 1] * list_ptr[c + 1];
