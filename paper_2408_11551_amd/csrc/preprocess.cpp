@@ -679,9 +679,17 @@ int64_t jaccard_cluster(int64_t M, int64_t nbc, const Patterns& pat, int tau_per
             ask_at = 2 * spent;
             return;
         }
-        if (there < here && partners_elsewhere(pat, pc, inv, first_of_len, keep, *elsewhere, partners, workers)) {
-            ask_at = 0;
-            return;
+        if (there < here) {
+            if (partners_elsewhere(pat, pc, inv, first_of_len, keep, *elsewhere, partners, workers)) {
+                ask_at = 0;
+                return;
+            }
+            // It did not, and would not later; what is left for the threads has to pay at their price.
+            elsewhere = nullptr;
+            if (ahead < here + 5e4) {
+                ask_at = 2 * spent;
+                return;
+            }
         }
         if (inv.at.empty() && !inv.dropped) inv = index_columns(nbc, pat, pc, [](const ColumnIndex&) { return true; }, workers);
         std::vector<int32_t> alive(static_cast<size_t>(n_classes));
