@@ -187,7 +187,7 @@ struct PartnerTables {
     const uint32_t* first_of_len = nullptr;      // [longest + 2] first pattern of that length or more
     uint32_t* pairs = nullptr;             // [2 most_pairs]
     uint32_t most_pairs = 0;
-    uint32_t* found = nullptr;             // [2] pairs that there are, which may be more than most_pairs but stay below 2^32; not 0: a pattern has too many (both zero before)
+    uint32_t* found = nullptr;             // [2] pairs that there are, which may be more than most_pairs but stay below 2^32; not 0: a pattern has too many, and the rest was not looked at (both zero before)
 };
 // first_long: the first pattern of more than short_pattern() columns; mean_list: patterns in a column's list, as a pattern's column has them on average.
 uint32_t short_pattern();

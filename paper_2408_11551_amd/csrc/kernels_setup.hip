@@ -26,6 +26,8 @@ constexpr int kLongThreads = 512, kLongWaves = kLongThreads / 64;
 constexpr uint32_t kLongLds = 64 * 1024;
 constexpr int kShortThreads = 256, kShortWaves = kShortThreads / 64;
 constexpr uint32_t kSketch = 2048, kWideSketch = 8192;      // counters of two bytes per wave
+// Partners that a pattern may have as the shorter one; pairs held from which they are put down.
+constexpr uint32_t kMostOfLong = 512, kHeldOfLong = 256, kMostOfShort = 128, kHeldOfShort = 64;
 
 struct Pattern { uint32_t first, len, end, least; };
 
@@ -47,8 +49,10 @@ __device__ __forceinline__ bool passes(const PartnerTables& t, uint32_t shared, 
 }
 
 // Pairs found by a workgroup or a wave, put down some tens at a time between two patterns.  (One counter for all, in memory, is good for 40 pairs per
-// us: 740 us for the graph above, whatever else was done.)  A pattern with more partners than there is room for ends the search: the host's lists no
-// more than a few of each, and all of 20 000 rows that share a column would be 200 million.
+// us: 740 us for the graph above, whatever else was done.)  There is room for the most that a pattern may have beside those that are held when it begins.  One with
+// more gives the search up: the host's lists no more than a few of each, and all of 20 000 rows that share a column would be 200 million.  A workgroup looks for
+// that once per pattern, a wave after 64 comparisons (once per pattern, 50 000 loads of one word took as long as the rest), and ends.  50 000 rows of
+// 16 and a column in all of them: 18.0 -> 0.21 ms, most of it as the long ones no longer come first; 20 000 of 40 1.49 -> 0.46; 20 000 of three 1.55 -> 0.14.
 template <uint32_t ROOM> struct HeldPairs { uint32_t n, to, pairs[2 * ROOM]; };
 
 template <uint32_t ROOM>
@@ -64,21 +68,22 @@ __device__ __forceinline__ void put_pair(HeldPairs<ROOM>& held, uint32_t k, uint
 template <uint32_t ROOM>
 __device__ __forceinline__ void make_room(const PartnerTables& t, HeldPairs<ROOM>& held, uint32_t x)
 {
-    if (x != 0 || held.n == 0) return;
-    if (held.n > ROOM) atomicOr(t.found + 1, 1u);
-    held.to = atomicAdd(t.found, held.n);
+    if (x == 0 && held.n > 0) held.to = atomicAdd(t.found, held.n);
 }
 
 template <uint32_t ROOM>
 __device__ __forceinline__ void put_down(const PartnerTables& t, const HeldPairs<ROOM>& held, uint32_t x, uint32_t threads)
 {
-    for (uint32_t n = min(held.n, ROOM); x < n; x += threads) {
+    for (; x < held.n; x += threads) {
         const size_t to = static_cast<size_t>(held.to) + x;
         if (to >= t.most_pairs) return;
         t.pairs[2 * to] = held.pairs[2 * x];
         t.pairs[2 * to + 1] = held.pairs[2 * x + 1];
     }
 }
+
+__device__ __forceinline__ uint32_t given_up(const PartnerTables& t) { return __hip_atomic_load(t.found + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void give_up(const PartnerTables& t) { atomicOr(t.found + 1, 1u); }
 
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
@@ -109,16 +114,23 @@ __global__ __launch_bounds__(kLongThreads)
 void long_partners_kernel(PartnerTables t, uint32_t first, uint32_t window)
 {
     extern __shared__ uint32_t counts[];
-    __shared__ HeldPairs<512> held;
+    __shared__ HeldPairs<kMostOfLong + kHeldOfLong> held;
+    __shared__ uint32_t enough;
     constexpr uint32_t PER = 32 / BITS, MASK = (1u << BITS) - 1u;
     const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(tid >> 6));
-    if (tid == 0) held.n = 0;
+    if (tid == 0) {
+        held.n = 0;
+        enough = given_up(t);
+    }
     for (uint32_t x = static_cast<uint32_t>(tid); x < (window + PER - 1) / PER; x += kLongThreads) counts[x] = 0;
     __syncthreads();
+    if (enough) return;
     for (int64_t y = blockIdx.x; y < t.n - first; y += gridDim.x) {
-        const uint32_t k = static_cast<uint32_t>(t.n - 1 - y);       // long patterns, which take longest, first
+        // a short one to begin with, of which those have too many partners that share a column with thousands; then the long ones, which take longest
+        const uint32_t k = y < gridDim.x ? first + static_cast<uint32_t>(y) : static_cast<uint32_t>(t.n - 1 - (y - gridDim.x));
         const Pattern p = pattern_of(t, k);
+        const uint32_t held_before = held.n;                         // (pairs are put there behind the first barrier below)
         for (uint32_t w0 = k + 1; w0 < p.end; w0 += window) {
             const uint32_t w1 = min(p.end, w0 + window);
             auto each = [&](auto&& f) __attribute__((always_inline)) {
@@ -137,15 +149,21 @@ void long_partners_kernel(PartnerTables t, uint32_t first, uint32_t window)
             };
             each([&](uint32_t other) { atomicAdd(&counts[(other - w0) / PER], 1u << (BITS * ((other - w0) % PER))); });
             __syncthreads();
+            if (tid == 0) enough = given_up(t);
             each([&](uint32_t other) {
                 const uint32_t place = BITS * ((other - w0) % PER);
                 const uint32_t shared = atomicAnd(&counts[(other - w0) / PER], ~(MASK << place)) >> place & MASK;
                 if (shared >= p.least && passes(t, shared, p.len, t.ptr[other + 1] - t.ptr[other])) put_pair(held, k, other);
             });
             __syncthreads();
+            // (uniform: both are written between the barriers only)
+            if (enough || held.n - held_before > kMostOfLong) {
+                if (tid == 0) give_up(t);
+                return;
+            }
         }
         // (the last pattern's, or enough of them: uniform, as nobody counts here)
-        if (held.n >= 256 || y + gridDim.x >= t.n - first) {
+        if (held.n >= kHeldOfLong || y + gridDim.x >= t.n - first) {
             make_room(t, held, static_cast<uint32_t>(tid));
             __syncthreads();
             put_down(t, held, static_cast<uint32_t>(tid), kLongThreads);
@@ -162,11 +180,11 @@ __global__ __launch_bounds__(kShortThreads)
 void short_partners_kernel(PartnerTables t, uint32_t last)
 {
     __shared__ uint32_t sketches[kShortWaves][SKETCH / 2];
-    __shared__ HeldPairs<128> helds[kShortWaves];
+    __shared__ HeldPairs<kMostOfShort + kHeldOfShort> helds[kShortWaves];
     const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(tid >> 6));
     uint32_t* const counts = sketches[wave];
-    HeldPairs<128>& held = helds[wave];
+    auto& held = helds[wave];
     if (lane == 0) held.n = 0;
     wave_fence();
     auto empty_hands = [&]() {
@@ -181,6 +199,7 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
         const uint32_t k = last - 1 - static_cast<uint32_t>(y);
         const Pattern p = pattern_of(t, k);
         if (p.len == 0) break;                         // the empty pattern is number 0
+        const uint32_t held_before = held.n;
         for (uint32_t x = static_cast<uint32_t>(lane); x < SKETCH / 2; x += 64) counts[x] = 0;
         uint32_t column = 0, begin = 0, stop = 0;
         if (static_cast<uint32_t>(lane) < p.len) {
@@ -193,6 +212,13 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
             listed(t, lane_value(begin, q), lane_value(stop, q), k + 1, p.end, lane,
                    [&](uint32_t other) { atomicAdd(&counts[other % SKETCH / 2], 1u << (16 * (other % 2))); });
         wave_fence();
+        uint32_t compared = 0;
+        auto too_many = [&]() {
+            wave_fence();
+            const bool more = held.n - held_before > kMostOfShort;
+            if (more && lane == 0) give_up(t);
+            return more;
+        };
         for (uint32_t q = 0; q < p.len; ++q) {
             const uint32_t from = lane_value(begin, q), to = lane_value(stop, q);
             for (uint32_t x0 = from; x0 < to; x0 += 256) {
@@ -206,7 +232,7 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
                     // columns shared, or more
                     const uint32_t most = other > k && other < p.end ? min(counts[other % SKETCH / 2] >> (16 * (other % 2)) & 0xFFFFu, p.len) : 0u;
                     const bool may = most >= p.least && passes(t, most, p.len, t.ptr[other + 1] - t.ptr[other]);
-                    for (uint64_t left = __ballot(may); left; left &= left - 1) {
+                    for (uint64_t left = __ballot(may); left; left &= left - 1, ++compared) {
                         const uint32_t who = lane_value(other, static_cast<uint32_t>(__builtin_ctzll(left)));
                         const uint32_t at = t.ptr[who], their = t.ptr[who + 1] - at;
                         // the columns that both have, and the first of them: the pair is found once
@@ -221,10 +247,15 @@ void short_partners_kernel(PartnerTables t, uint32_t last)
                             put_pair(held, k, who);
                     }
                 }
+                // (here too: a pattern that shares a column with thousands is compared with them one by one)
+                if (compared >= 64) {
+                    compared = 0;
+                    if (too_many() || __builtin_amdgcn_readfirstlane(static_cast<int>(given_up(t)))) return;
+                }
             }
         }
-        wave_fence();
-        if (held.n >= 64) empty_hands();
+        if (too_many()) return;
+        if (held.n >= kHeldOfShort) empty_hands();
     }
     empty_hands();
 }
@@ -238,6 +269,13 @@ int launch_partners(const PartnerTables& t, uint32_t first_long, double mean_lis
     const double most_list = 0.35 * 2.0 * t.keep / (1000.0 + t.keep);
     const uint32_t sketch = mean_list <= most_list * kSketch ? kSketch : kWideSketch;
     if (mean_list > most_list * kWideSketch && t.n > kWideSketch) first_long = 0;
+    // (short patterns first: where a search is given up it is mostly theirs, and the other kernel ends at once)
+    if (first_long > 0) {
+        const uint32_t groups = (first_long + kShortWaves - 1) / kShortWaves;
+        const dim3 grid(groups < 2048 ? groups : 2048);
+        if (sketch == kSketch) hipLaunchKernelGGL(short_partners_kernel<kSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
+        else hipLaunchKernelGGL(short_partners_kernel<kWideSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
+    }
     if (t.n > first_long) {
         const bool bytes = t.longest < 256;
         const uint32_t counter = bytes ? 1 : 2, most = kLongLds / counter, left = static_cast<uint32_t>(t.n) - first_long;
@@ -245,12 +283,6 @@ int launch_partners(const PartnerTables& t, uint32_t first_long, double mean_lis
         const dim3 grid(left < 768 ? left : 768);
         if (bytes) hipLaunchKernelGGL(long_partners_kernel<8>, grid, dim3(kLongThreads), window * counter, s, t, first_long, window);
         else hipLaunchKernelGGL(long_partners_kernel<16>, grid, dim3(kLongThreads), window * counter, s, t, first_long, window);
-    }
-    if (first_long > 0) {
-        const uint32_t groups = (first_long + kShortWaves - 1) / kShortWaves;
-        const dim3 grid(groups < 2048 ? groups : 2048);
-        if (sketch == kSketch) hipLaunchKernelGGL(short_partners_kernel<kSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
-        else hipLaunchKernelGGL(short_partners_kernel<kWideSketch>, grid, dim3(kShortThreads), 0, s, t, first_long);
     }
     return static_cast<int>(hipGetLastError());
 }

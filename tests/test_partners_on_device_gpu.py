@@ -49,13 +49,38 @@ def test_pairs_are_those_of_brute_force(n, nbc, lengths, families, keep):
     ptr, columns = _patterns(n, nbc, lengths, n + nbc, families)
     want = _brute(ptr, columns, nbc, keep)
     scratch = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
-    most = np.bincount(want.reshape(-1), minlength=ptr.size - 1).max() if want.size else 0
+    # (what the kernels hold of a pattern that is the shorter one: 128 pairs up to 32 columns, where a wave takes it, else 512)
+    partners, lens = np.bincount(want[:, 0], minlength=ptr.size - 1), np.diff(ptr)
     try:
         got = S.smat_pattern_partners(ptr, columns, nbc, keep, scratch, want.shape[0] + 1)
     except S.SmatError as e:
-        assert e.status_name == "SMAT_ERR_UNSUPPORTED" and most > 128
+        assert e.status_name == "SMAT_ERR_UNSUPPORTED" and (partners[lens <= 32].max(initial=0) > 128 or partners[lens > 32].max(initial=0) > 512)
         return
+    assert partners.max(initial=0) <= 512
     assert got.shape == want.shape and np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], want)
+
+
+# A pattern with as many partners as the kernels hold of one, taken by a wave or a workgroup that holds as many of another already; and one more
+@pytest.mark.parametrize("length,together,held,most,keep", [(8, 8192, 63, 128, 850), (40, 768, 255, 512, 960)])
+@pytest.mark.parametrize("one_more", [0, 1])
+def test_most_partners_of_a_pattern(length, together, held, most, keep, one_more):
+    # `together` patterns on, the same wave or workgroup comes by; a partner has the pattern's columns and one more
+    partners = np.zeros(together + 8, np.int64)
+    partners[:8], partners[together:] = most, held
+    partners[3] += one_more
+    n_bases, n_more = partners.size, int(partners.sum())
+    base = np.arange(n_bases * length).reshape(n_bases, length)
+    more = np.concatenate([base[np.repeat(np.arange(n_bases), partners)], n_bases * length + np.arange(n_more)[:, None]], axis=1)
+    ptr = np.concatenate([np.arange(n_bases + 1) * length, n_bases * length + (length + 1) * np.arange(1, n_more + 1)]).astype(np.uint32)
+    columns = np.concatenate([base.reshape(-1), more.reshape(-1)]).astype(np.uint32)
+    want = np.stack([np.repeat(np.arange(n_bases), partners), n_bases + np.arange(n_more)], axis=1)
+    scratch = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    if one_more:
+        with pytest.raises(S.SmatError, match="UNSUPPORTED"):
+            S.smat_pattern_partners(ptr, columns, n_bases * length + n_more, keep, scratch, n_more)
+    else:
+        got = S.smat_pattern_partners(ptr, columns, n_bases * length + n_more, keep, scratch, n_more)
+        assert np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], want)
 
 
 # Lists so long that many short patterns reach the bound by accident: more counters (keep = 700, and fewer patterns than these), or none but exact ones
@@ -99,12 +124,32 @@ def _graph(M, K, per_row, seed):
     return row_ptr, (keys % K).astype(np.int32)
 
 
-@pytest.mark.parametrize("M,K,per_row,tau", [(40000, 40000, 12, 700), (30001, 9000, 20, 500), (20000, 300000, 30, 900), (16000, 16000, 60, 700)])
-def test_the_handle_is_the_hosts(M, K, per_row, tau):
+def _pattern_table(M, row_ptr, col_idx):
+    """What the clustering sends to the device: every row pattern once, by length."""
+    rows = np.repeat(np.arange(M), np.diff(row_ptr))
+    keys = np.unique(rows * (1 << 24) + col_idx // 16)
+    cols = (keys % (1 << 24)).astype(np.uint32)
+    ends = np.searchsorted(keys, np.arange(M + 1) * (1 << 24))
+    lists = sorted({cols[a:b].tobytes() for a, b in zip(ends[:-1], ends[1:])}, key=len)
+    ptr = np.zeros(len(lists) + 1, np.uint32)
+    np.cumsum([len(x) // 4 for x in lists], out=ptr[1:])
+    return ptr, np.frombuffer(b"".join(lists), np.uint32)
+
+
+# (searched: on the device with any number of threads; with sixteen the others may be the threads' own)
+@pytest.mark.parametrize("M,K,per_row,tau,searched", [(40000, 40000, 12, 700, True), (30001, 9000, 20, 500, True), (60000, 60000, 20, 900, True), (30000, 60000, 40, 700, True),
+                                                      (20000, 300000, 30, 900, False), (16000, 16000, 60, 700, False)])
+def test_the_handle_is_the_hosts(M, K, per_row, tau, searched):
     row_ptr, col_idx = _graph(M, K, per_row, M + tau)
     args = (M, K, row_ptr, col_idx, np.ones(col_idx.size, np.uint16), "f16")
     alone = S.smat_preprocess(*args, tau_permille=tau)
+    before = torch.cuda.memory_stats().get("allocation.all.allocated", 0)
     helped = S.smat_preprocess_on_device(*args, device="cuda:0", tau_permille=tau)
+    if searched:
+        # it asked for memory, and these patterns are none that the search declines
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before + 1
+        ptr, columns = _pattern_table(M, row_ptr, col_idx)
+        S.smat_pattern_partners(ptr, columns, (K + 15) // 16, 1000 - tau, torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0"), 4 << 20)
     assert np.array_equal(S.smat_export_perm(alone, M), S.smat_export_perm(helped, M))
     for a, b in zip(S.smat_export_bcsr(alone, with_vals=False)[:2], S.smat_export_bcsr(helped, with_vals=False)[:2]):
         assert np.array_equal(a, b)
