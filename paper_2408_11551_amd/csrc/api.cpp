@@ -24,6 +24,7 @@
 #include "pack_layout.h"
 #include "preprocess.h"
 #include "quad_layout.h"
+#include "tile_rule.h"
 
 constexpr int kMaxAreas = 16;            // option concurrent_streams at most
 
@@ -1039,88 +1040,20 @@ constexpr int64_t kStageColumns = 32;
 // Columns that the block rows occupy which tiles would take in their place.
 int64_t columns_of_rows(const smat_handle& h) { return h.bcsr.grouped ? h.b_rows : h.dense_columns; }
 
-// Does the kernel for few columns on the two-of-four form take N columns?  Both estimates, in us, were fitted on random matrices of
-// 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
-// once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
-// out of the L2s or from further away.
-// (This one infinite where it does not take N columns at all, and where a super row has few steps: rows are faster then, 7693 x 1617 at 20 % in e5m2, N = 32 6.9 and 8.7 us.)
-struct FewColumns { double quads_us, rows_us; bool take() const { return quads_us + 0.3 < rows_us; } };
-FewColumns few_columns(const smat_handle& h, int64_t N, bool off_dwords)
+// What the rule for tiles goes by (tile_rule.h).
+smat::RuleMatrix rule_matrix(const smat_handle& h)
 {
-    constexpr double kNever = std::numeric_limits<double>::infinity();
-    if (h.tiles.n_quad_steps == 0 || N > 32) return {kNever, kNever};
-    const int es = h.elem_bytes, row_bytes = smat::quad_row_bytes(es, N, h.max_quad_steps);
-    const double columns = static_cast<double>(columns_of_rows(h)), block_rows = 16.0 * h.tiles.n;
-    const double per_column = es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
-    const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
-    if (row_bytes == 0 || h.tiles.mean_steps < smat::kDeepSteps) return {kNever, rows_us};
-    const double passes = static_cast<double>(smat::quad_row_passes(es, N, row_bytes));
-    const double a_mb = static_cast<double>(h.tiles.n_quad_steps) * (es == 1 ? 20480e-6 : 18432e-6);
-    const double quads_us = 4.2 + 0.008 * h.max_quad_steps * passes + 1.0e-5 * static_cast<double>(smat::quad_rows_lds(h.max_quad_steps, es, row_bytes)) +
-                            a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (off_dwords ? 0.7 : 0.0) +
-                            (h.dev_rest.n_order > 0 && !h.quad_tail ? 5.0 : 0.0);      // a launch for the other block rows
-    return {quads_us, rows_us};
-}
-
-// What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
-// other, a little per step of all (what the units share), steps once more for every round of as many workgroups as a unit holds, where it holds several, the
-// write of C; with split steps, the partial tiles.  Fitted on 1935 products of random matrices (1000 ... 8192 rows, 600 ... 8192 columns, 5-20 % fill, N = 16 ... 4096, all
-// types, each on all shapes): within 4-9 % (rms), and the shape it chooses is 0.5 % behind the best one on average.
-double quad_tiles_us(const smat_handle& h, const smat::DenseTiles& t, int64_t N)
-{
-    struct Cost { double start, step, shared, round, write; };        // write: us per MB of C
-    static constexpr Cost kCosts[4][smat::kQuadShapes] = {
-        // fp16, bf16
-        {{5.82, 0.317, 0.091, 0.0, 0.189}, {5.51, 0.305, 0.058, 0.0, 0.205}, {4.57, 0.260, 0.025, 0.0, 0.257}, {4.27, 0.178, 0.023, 0.0, 0.189},
-         {3.74, 0.147, 0.018, 0.0, 0.187}},
-        // e4m3
-        {{6.25, 0.529, 0.020, 0.0, 0.231}, {5.60, 0.451, 0.0, 0.0, 0.269}, {4.57, 0.358, 0.0, 0.0, 0.289}, {4.05, 0.224, 0.033, 0.0, 0.212},
-         {3.62, 0.197, 0.035, 0.0, 0.250}, {5.62, 0.405, 0.009, 0.260, 0.129}, {4.86, 0.303, 0.008, 0.263, 0.154}, {4.36, 0.251, 0.009, 0.185, 0.162}},
-        // e5m2
-        {{6.66, 0.701, 0.019, 0.0, 0.234}, {5.95, 0.592, 0.0, 0.0, 0.254}, {4.92, 0.469, 0.0, 0.0, 0.308}, {4.66, 0.296, 0.0, 0.0, 0.201},
-         {3.79, 0.208, 0.024, 0.0, 0.269}},
-        // int8
-        {{6.16, 0.336, 0.035, 0.0, 0.212}, {5.24, 0.365, 0.041, 0.0, 0.223}, {4.25, 0.320, 0.019, 0.0, 0.274}, {4.13, 0.210, 0.036, 0.0, 0.209},
-         {3.86, 0.173, 0.061, 0.0, 0.222}, {5.46, 0.301, 0.026, 0.088, 0.130}, {4.52, 0.319, 0.054, 0.061, 0.146}, {4.03, 0.221, 0.052, 0.107, 0.160}},
-    };
-    const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : h.dtype == SMAT_E4M3 ? 1 : h.dtype == SMAT_E5M2 ? 2 : 3][t.quad_shape];
-    const int64_t columns = smat::quad_shape_columns(t.quad_shape);
-    const double n_tiles = static_cast<double>(smat::quad_row_tiles(t)) * static_cast<double>((N + columns - 1) / columns);
-    const double steps = static_cast<double>(h.tiled_quad_steps()) / t.n, c_mb = static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
-    const int ks = smat::dense_split(t, N);
-    if (ks > 1) return 10.5 + c.step * std::ceil(steps / ks) + std::min(9.0, 0.05 * n_tiles * ks);
-    const double in_a_unit = std::ceil(n_tiles / 256.0);
-    return c.start + in_a_unit * steps * c.step + n_tiles / 256.0 * steps * c.shared +
-           std::ceil(in_a_unit / smat::quad_shape_resident(t.quad_shape)) * steps * c.round + c.write * c_mb;
-}
-
-// The same on the per-row kernels, fitted on 1241 of these products that took up to 45 us (N > 32; within 8-14 %; with it the faster of rows and tiles is missed by
-// 0.6 % on average): rows of B by the byte and by
-// the 256-byte slab, values, C; rows of B that begin on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes, where
-// mostly kernels_lines.hip runs, on dwords and off them.
-// Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
-// four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, and on dwords, where a row
-// reaches into a line more, 0.83-0.92 either way.)
-double rows_us(const smat_handle& h, const void* dB, int64_t ldb, int64_t N)
-{
-    struct Cost { double start, gather, slab, values, write; };
-    static constexpr Cost kCosts[2][6] = {{{3.67, 0.0215, 8.71, 0.0, 0.196}, {4.02, 0.0311, 8.06, 0.0, 0.041}, {3.83, 0.0375, 7.14, 0.0, 0.218}, {4.00, 0.0701, 0.0, 0.450, 0.248},
-                                           {3.73, 0.0159, 6.89, 0.0, 0.0}, {3.65, 0.0412, 5.62, 0.043, 0.0}},
-                                          {{4.52, 0.0352, 5.34, 0.0, 0.014}, {4.34, 0.0, 15.52, 0.018, 0.260}, {4.79, 0.0088, 13.49, 0.0, 0.324}, {3.86, 0.0576, 4.36, 0.663, 0.405},
-                                           {4.05, 0.0540, 0.0, 0.104, 0.0}, {4.05, 0.1053, 0.0, 0.130, 0.0}}};
-    const int64_t bytes = N * h.elem_bytes, slabs = (bytes + 255) / 256;
-    const double m_rows = static_cast<double>(h.b_rows) * 1e-6;
-    // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
-    const double groups = static_cast<double>(h.bcsr.nbr) * static_cast<double>(slabs) / 256.0;
-    const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
-    auto us_of = [&](int64_t starts) {
-        const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - h.elem_bytes) <= 128;
-        const Cost& c = kCosts[h.elem_bytes == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
-        const double row = c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs);
-        return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * h.elem_bytes + c.write * static_cast<double>(h.csr.M) * static_cast<double>(N) * 4e-6;
-    };
-    const int64_t distance = ldb * h.elem_bytes;
-    return std::max(us_of(distance), us_of(distance | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB))));
+    smat::RuleMatrix m;
+    m.dtype = h.dtype;
+    m.es = h.elem_bytes;
+    m.M = h.csr.M;
+    m.K = h.csr.K;
+    m.nbr = h.bcsr.nbr;
+    m.b_rows = h.b_rows;
+    m.columns = columns_of_rows(h);
+    m.tiled_steps = h.tiled_quad_steps();
+    m.rest_packs = h.dev_rest.n_order > 0 ? h.dev_rest.max_row_packs : -1;
+    return m;
 }
 
 // smat_spmm with the area for partial tiles given by the caller of this function.
@@ -1166,40 +1099,19 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // It also has to pay: few tiles leave most of the chip idle, while the per-row kernel fetches every occupied column's row
     // of B again for every block row but spreads that over all compute units.  The estimates are measured rates, fitted on
     // bands and random matrices of 1000 ... 65536 rows and 5-100 % fill at N = 8 ... 2048, 16-bit and 8-bit; the faster path is taken.
-    const int64_t starts = (ldb * h->elem_bytes) | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB));
-    const bool off_dwords = starts % 4 != 0;
+    smat::RuleProduct product;
+    product.N = N;
+    product.distance = ldb * h->elem_bytes;
+    product.starts = product.distance | static_cast<int64_t>(reinterpret_cast<uintptr_t>(dB));
+    product.in_pieces = in_pieces;
+    product.chunk = chunk;
+    const int64_t starts = product.starts;
+    const smat::RuleMatrix rule = tiles.n_quad_steps > 0 ? rule_matrix(*h) : smat::RuleMatrix();
     if (use_tiles && h->dense_mode == 0 && tiles.n_quad_steps > 0 && !hard_limit) {
-        // On quads the shape is chosen too: narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
-        // a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
-        // 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
-        // last super row of quad_tail gets tiles like the others where that pays.
-        auto take = [&](int shape, bool tail) {
-            tiles.quad_shape = shape;
-            tiles.quad_tail_tiled = tail;
-        };
-        double best = std::numeric_limits<double>::infinity();
-        int best_shape = smat::kQuad256x128;
-        bool best_tail = false;
-        for (int choice = 0; choice < 2 * smat::quad_shapes(h->dtype); ++choice) {
-            const int shape = choice / 2;
-            const bool tail = choice % 2 != 0;
-            if (tail && !tiles.quad_tail) continue;
-            take(shape, tail);
-            // (one group per workgroup is for units that share several)
-            if (smat::quad_shape_groups(shape) == 1 && smat::quad_row_tiles(tiles) * ((N + smat::quad_shape_columns(shape) - 1) / smat::quad_shape_columns(shape)) <= 256) continue;
-            // (a launch of a few block rows: as long as the longest one's walk)
-            double us = h->dev_rest.n_order > 0 && !tail ? 3.0 + 0.09 * static_cast<double>(h->dev_rest.max_row_packs) : 0.0;
-            for (int64_t c0 = 0; c0 < N; c0 += chunk) {
-                const int64_t n = std::min(chunk, N - c0);
-                us += quad_tiles_us(*h, tiles, n);
-                if (!in_pieces) us += 2.4 + 0.5e-6 * static_cast<double>(h->csr.K) * static_cast<double>(n * h->elem_bytes);      // the copy of B
-            }
-            if (us < best) { best = us; best_shape = shape; best_tail = tail; }
-        }
-        take(best_shape, best_tail);
-        const FewColumns few = few_columns(*h, N, off_dwords);
-        const double rows = N <= 32 ? few.rows_us : rows_us(*h, dB, ldb, N);        // (each fitted on its widths)
-        use_tiles = best + 0.5 <= rows && !(few.take() && few.quads_us < best);
+        const smat::TileChoice best = smat::best_tiles(rule, tiles, product);
+        tiles.quad_shape = best.shape;
+        tiles.quad_tail_tiled = best.tail;
+        use_tiles = smat::tiles_pay(rule, tiles, product, best);
     } else if (use_tiles && h->dense_mode == 0) {
         double t_tiles = 0;
         for (int64_t c0 = 0; c0 < N; c0 += chunk) {
@@ -1243,7 +1155,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // e4m3 goes over the two-of-four form twice
     const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
     const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 ? 2.0 : 1.0);
-    if (!use_tiles && h->dense_mode == 0 && few_columns(*h, N, off_dwords).take()) {
+    if (!use_tiles && h->dense_mode == 0 && smat::few_columns(rule, tiles, product).take()) {
         // (with quad_tail all block rows are among the quads)
         if (h->dev_rest.n_order > 0 && !h->quad_tail) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);

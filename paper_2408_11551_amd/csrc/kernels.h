@@ -111,6 +111,18 @@ inline int dense_parts(const DenseTiles& t, int64_t N)
     return ks < 2 ? 1 : static_cast<int>(ks);
 }
 
+// The parts that are launched: as many as fit the 256 compute units in one round.
+inline int dense_even_parts(const DenseTiles& t, int64_t N)
+{
+    const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
+    int64_t ks = dense_parts(t, N);
+    // An XCD has an eighth of the tiles, rounded up, and 32 compute units: one workgroup more and the launch takes two rounds (81 tiles
+    // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps leave room for two workgroups.
+    if (t.mean_steps >= kDeepSteps)
+        while (ks > 1 && (tiles + 7) / 8 * ks > 32) --ks;
+    return static_cast<int>(ks);
+}
+
 // Sets n16 16-byte words at dst to zero.
 int launch_fill_zero(void* dst, size_t n16, void* stream);
 

@@ -577,16 +577,7 @@ int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem
 // How many workgroups share the steps of a 128-column tile: as many as fit the 256 compute
 // units in one round, as long as each keeps at least eight steps and the partial tiles fit the
 // scratch area.
-int dense_split(const DenseTiles& t, int64_t N)
-{
-    const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
-    int64_t ks = dense_parts(t, N);
-    // An XCD has an eighth of the tiles, rounded up, and 32 compute units: one workgroup more and the launch takes two rounds (81 tiles
-    // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps leave room for two workgroups.
-    if (t.mean_steps >= kDeepSteps)
-        while (ks > 1 && (tiles + 7) / 8 * ks > 32) --ks;
-    return static_cast<int>(ks);
-}
+int dense_split(const DenseTiles& t, int64_t N) { return dense_even_parts(t, N); }
 
 template <int DT>
 static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const void* B, int64_t ldb, void* C, int64_t ldc,

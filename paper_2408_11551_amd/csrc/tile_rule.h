@@ -1,0 +1,152 @@
+// Which products go to the tiles on quads, and in which shape, which to the kernel for few columns, which row by row: estimates in us, fitted on measurements.
+// Host only.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <limits>
+
+#include "kernels.h"
+#include "quad_layout.h"
+
+namespace smat {
+
+// What the estimates go by besides the tiles: of a matrix with super rows on quads, ...
+struct RuleMatrix {
+    int dtype = 0, es = 2;               // smat_dtype_t, bytes of an element
+    int64_t M = 0, K = 0, nbr = 0;       // rows, columns, block rows
+    int64_t b_rows = 0;                  // rows of B that the per-row kernels fetch per slab of columns
+    int64_t columns = 0;                 // of them what tiles would take in their place
+    int64_t tiled_steps = 0;             // quad steps of the super rows, without those of quad_tail
+    int64_t rest_packs = -1;             // packs of the longest block row outside the super rows; -1: there is none
+};
+// ... and of a product.
+struct RuleProduct {
+    int64_t N = 0;
+    int64_t distance = 0, starts = 0;    // bytes from one row of B to the next; the same with the bits of the address of the first
+    bool in_pieces = true;               // the tile kernels can read B where it is
+    int64_t chunk = 0;                   // columns that are copied at a time where they cannot
+    bool off_dwords() const { return starts % 4 != 0; }
+};
+
+// Does the kernel for few columns on the two-of-four form take N columns?  Both estimates, in us, were fitted on random matrices of
+// 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
+// once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
+// out of the L2s or from further away.
+// (This one infinite where it does not take N columns at all, and where a super row has few steps: rows are faster then, 7693 x 1617 at 20 % in e5m2, N = 32 6.9 and 8.7 us.)
+struct FewColumns { double quads_us, rows_us; bool take() const { return quads_us + 0.3 < rows_us; } };
+inline FewColumns few_columns(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
+{
+    constexpr double kNever = std::numeric_limits<double>::infinity();
+    if (t.n_quad_steps == 0 || p.N > 32) return {kNever, kNever};
+    const int row_bytes = quad_row_bytes(m.es, p.N, t.max_quad_steps);
+    const double columns = static_cast<double>(m.columns), block_rows = 16.0 * t.n;
+    const double per_column = m.es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
+    const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
+    if (row_bytes == 0 || t.mean_steps < kDeepSteps) return {kNever, rows_us};
+    const double passes = static_cast<double>(quad_row_passes(m.es, p.N, row_bytes));
+    const double a_mb = static_cast<double>(t.n_quad_steps) * (m.es == 1 ? 20480e-6 : 18432e-6);
+    const double quads_us = 4.2 + 0.008 * t.max_quad_steps * passes + 1.0e-5 * static_cast<double>(quad_rows_lds(t.max_quad_steps, m.es, row_bytes)) +
+                            a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (p.off_dwords() ? 0.7 : 0.0) +
+                            (m.rest_packs >= 0 && !t.quad_tail ? 5.0 : 0.0);      // a launch for the other block rows
+    return {quads_us, rows_us};
+}
+
+// What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
+// other, a little per step of all (what the units share), steps once more for every round of as many workgroups as a unit holds, where it holds several, the
+// write of C; with split steps, the partial tiles.  Fitted on 1935 products of random matrices (1000 ... 8192 rows, 600 ... 8192 columns, 5-20 % fill, N = 16 ... 4096, all
+// types, each on all shapes): within 4-9 % (rms), and the shape it chooses is 0.5 % behind the best one on average.
+inline double quad_tiles_us(const RuleMatrix& m, const DenseTiles& t, int64_t N)
+{
+    struct Cost { double start, step, shared, round, write; };        // write: us per MB of C
+    static constexpr Cost kCosts[4][kQuadShapes] = {
+        // fp16, bf16 (a smat_dtype_t of 0 and 1; then 2, 3 and 4)
+        {{5.82, 0.317, 0.091, 0.0, 0.189}, {5.51, 0.305, 0.058, 0.0, 0.205}, {4.57, 0.260, 0.025, 0.0, 0.257}, {4.27, 0.178, 0.023, 0.0, 0.189},
+         {3.74, 0.147, 0.018, 0.0, 0.187}},
+        // e4m3
+        {{6.25, 0.529, 0.020, 0.0, 0.231}, {5.60, 0.451, 0.0, 0.0, 0.269}, {4.57, 0.358, 0.0, 0.0, 0.289}, {4.05, 0.224, 0.033, 0.0, 0.212},
+         {3.62, 0.197, 0.035, 0.0, 0.250}, {5.62, 0.405, 0.009, 0.260, 0.129}, {4.86, 0.303, 0.008, 0.263, 0.154}, {4.36, 0.251, 0.009, 0.185, 0.162}},
+        // e5m2
+        {{6.66, 0.701, 0.019, 0.0, 0.234}, {5.95, 0.592, 0.0, 0.0, 0.254}, {4.92, 0.469, 0.0, 0.0, 0.308}, {4.66, 0.296, 0.0, 0.0, 0.201},
+         {3.79, 0.208, 0.024, 0.0, 0.269}},
+        // int8
+        {{6.16, 0.336, 0.035, 0.0, 0.212}, {5.24, 0.365, 0.041, 0.0, 0.223}, {4.25, 0.320, 0.019, 0.0, 0.274}, {4.13, 0.210, 0.036, 0.0, 0.209},
+         {3.86, 0.173, 0.061, 0.0, 0.222}, {5.46, 0.301, 0.026, 0.088, 0.130}, {4.52, 0.319, 0.054, 0.061, 0.146}, {4.03, 0.221, 0.052, 0.107, 0.160}},
+    };
+    const Cost& c = kCosts[m.es == 2 ? 0 : m.dtype - 1][t.quad_shape];
+    const int64_t columns = quad_shape_columns(t.quad_shape);
+    const double n_tiles = static_cast<double>(quad_row_tiles(t)) * static_cast<double>((N + columns - 1) / columns);
+    const double steps = static_cast<double>(m.tiled_steps) / t.n, c_mb = static_cast<double>(m.M) * static_cast<double>(N) * 4e-6;
+    const int ks = dense_even_parts(t, N);
+    if (ks > 1) return 10.5 + c.step * std::ceil(steps / ks) + std::min(9.0, 0.05 * n_tiles * ks);
+    const double in_a_unit = std::ceil(n_tiles / 256.0);
+    return c.start + in_a_unit * steps * c.step + n_tiles / 256.0 * steps * c.shared +
+           std::ceil(in_a_unit / quad_shape_resident(t.quad_shape)) * steps * c.round + c.write * c_mb;
+}
+
+// The same on the per-row kernels, fitted on 1241 of these products that took up to 45 us (N > 32; within 8-14 %; with it the faster of rows and tiles is missed by
+// 0.6 % on average): rows of B by the byte and by
+// the 256-byte slab, values, C; rows of B that begin on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes, where
+// mostly kernels_lines.hip runs, on dwords and off them.
+// Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
+// four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, and on dwords, where a row
+// reaches into a line more, 0.83-0.92 either way.)
+inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
+{
+    struct Cost { double start, gather, slab, values, write; };
+    static constexpr Cost kCosts[2][6] = {{{3.67, 0.0215, 8.71, 0.0, 0.196}, {4.02, 0.0311, 8.06, 0.0, 0.041}, {3.83, 0.0375, 7.14, 0.0, 0.218}, {4.00, 0.0701, 0.0, 0.450, 0.248},
+                                           {3.73, 0.0159, 6.89, 0.0, 0.0}, {3.65, 0.0412, 5.62, 0.043, 0.0}},
+                                          {{4.52, 0.0352, 5.34, 0.0, 0.014}, {4.34, 0.0, 15.52, 0.018, 0.260}, {4.79, 0.0088, 13.49, 0.0, 0.324}, {3.86, 0.0576, 4.36, 0.663, 0.405},
+                                           {4.05, 0.0540, 0.0, 0.104, 0.0}, {4.05, 0.1053, 0.0, 0.130, 0.0}}};
+    const int64_t bytes = p.N * m.es, slabs = (bytes + 255) / 256;
+    const double m_rows = static_cast<double>(m.b_rows) * 1e-6;
+    // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
+    const double groups = static_cast<double>(m.nbr) * static_cast<double>(slabs) / 256.0;
+    const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
+    auto us_of = [&](int64_t starts) {
+        const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - m.es) <= 128;
+        const Cost& c = kCosts[m.es == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
+        const double row = c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs);
+        return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * m.es + c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6;
+    };
+    return std::max(us_of(p.distance), us_of(p.starts));
+}
+
+struct TileChoice { int shape = kQuad256x128; bool tail = false; double us = std::numeric_limits<double>::infinity(); };
+
+// The shape to take.  Narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
+// a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
+// 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
+// last super row of quad_tail gets tiles like the others where that pays.
+inline TileChoice best_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduct& p)
+{
+    TileChoice best;
+    for (int choice = 0; choice < 2 * quad_shapes(m.dtype); ++choice) {
+        t.quad_shape = choice / 2;
+        t.quad_tail_tiled = choice % 2 != 0;
+        if (t.quad_tail_tiled && !t.quad_tail) continue;
+        const int64_t columns = quad_shape_columns(t.quad_shape);
+        // (one group per workgroup is for units that share several)
+        if (quad_shape_groups(t.quad_shape) == 1 && quad_row_tiles(t) * ((p.N + columns - 1) / columns) <= 256) continue;
+        // (a launch of a few block rows: as long as the longest one's walk)
+        double us = m.rest_packs >= 0 && !t.quad_tail_tiled ? 3.0 + 0.09 * static_cast<double>(m.rest_packs) : 0.0;
+        for (int64_t c0 = 0; c0 < p.N; c0 += p.in_pieces ? p.N : p.chunk) {
+            const int64_t n = std::min(p.in_pieces ? p.N : p.chunk, p.N - c0);
+            us += quad_tiles_us(m, t, n);
+            if (!p.in_pieces) us += 2.4 + 0.5e-6 * static_cast<double>(m.K) * static_cast<double>(n * m.es);      // the copy of B
+        }
+        if (us < best.us) best = TileChoice{t.quad_shape, t.quad_tail_tiled, us};
+    }
+    return best;
+}
+
+// Are these tiles faster than rows and the kernel for few columns?
+inline bool tiles_pay(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p, const TileChoice& tiles)
+{
+    const FewColumns few = few_columns(m, t, p);
+    const double rows = p.N <= 32 ? few.rows_us : rows_us(m, p);        // (each fitted on its widths)
+    return tiles.us + 0.5 <= rows && !(few.take() && few.quads_us < tiles.us);
+}
+
+}  // namespace smat
