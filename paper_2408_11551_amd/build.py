@@ -72,7 +72,7 @@ def is_stale() -> bool:
 # walks of the per-row kernel theirs): a register spilled inside their loops adds loads the counts do not know
 # of and serialises the prefetch (seen once: 79 instead of 53 us).  The build fails if one of them spills.
 NO_SPILL = ("spmm_tile_kernel", "spmm_quad_tile_kernel", "spmm_quad_rows_kernel", "spmm_lines_kernel", "spmm_kernel")
-_REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill|SGPRs Spill|TotalSGPRs|LDS Size \[bytes/block\]): (\S+)")
+_REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill|SGPRs Spill|TotalSGPRs|LDS Size \[bytes/block\]|Occupancy \[waves/SIMD\]): (\S+)")
 
 
 def _compile(item):

@@ -88,8 +88,8 @@ constexpr int quad_shape_groups(int shape) { return shape >= kQuad256x128Single 
 // error against 64 bits, 4096 x 4096 at 10 % in bf16 9.4e-8 with two groups, 1.34e-7 with one; e5m2 6.9e-9 and 7.8e-9).  int8 is exact, and what e4m3 loses
 // it loses inside an instruction (3.63e-6 either way).
 constexpr int quad_shapes(int dtype) { return dtype == 2 || dtype == 4 ? kQuadShapes : kQuad256x128Single; }
-// workgroups that a compute unit holds
-constexpr int quad_shape_resident(int shape) { return quad_shape_groups(shape) == 2 ? 1 : shape == kQuad256x64Single ? 3 : 2; }
+// Workgroups that a compute unit holds: a SIMD has two waves of 256 registers of these kernels (128 x 64 and 128 x 32, which have four, are priced with one).
+constexpr int quad_shape_resident(int shape) { return quad_shape_groups(shape) == 2 ? 1 : 2; }
 // Tiles per slab of columns.  Of a last super row with few block rows those that have any.
 inline int64_t quad_row_tiles(const DenseTiles& t)
 {

@@ -26,7 +26,7 @@
 //
 // Two groups leave a compute unit to one workgroup (eight waves of up to 256 registers): all of it waits while a tile begins, hands over and stores.  With
 // more tiles than compute units that is worse than what the groups are for, so e4m3 and int8 have three of the shapes also with one group of four waves that takes all
-// steps (KG = 1): two workgroups share a compute unit (256 x 64: three), one's loop runs beside the other's start and stores, no partial sums change
+// steps (KG = 1): two workgroups share a compute unit, one's loop runs beside the other's start and stores, no partial sums change
 // hands, and a barrier joins four waves instead of eight.  us, the best shape of two groups and of one: 4696 x 3919 at 10 % in int8, N = 2368 40.8 -> 34.8;
 // 3247 x 2257 at 20 %, N = 2816 30.4 -> 25.0; 3484 x 3387 at 5 % in e4m3, N = 3560 54.9 -> 46.9.  (The other types would gain as much, f16 5541 x 1077, N = 1598 31.7 ->
 // 25.8, but add less exactly in one chain: kernels.h.  128 x 64 and 128 x 32 with one group: the best of 0.2 % of 1935 products, not built.)

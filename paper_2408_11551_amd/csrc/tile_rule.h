@@ -55,24 +55,25 @@ inline FewColumns few_columns(const RuleMatrix& m, const DenseTiles& t, const Ru
 
 // What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
 // other, a little per step of all (what the units share), steps once more for every round of as many workgroups as a unit holds, where it holds several, the
-// write of C; with split steps, the partial tiles.  Fitted on 1935 products of random matrices (1000 ... 8192 rows, 600 ... 8192 columns, 5-20 % fill, N = 16 ... 4096, all
-// types, each on all shapes): within 4-9 % (rms), and the shape it chooses is 0.5 % behind the best one on average.
+// write of C; with split steps, the partial tiles.  Fitted on the products of random matrices of profiles/tile_rule.csv that say so (1000 ... 8192 rows, 600 ... 8192
+// columns, 5-20 % fill, N = 16 ... 4096, all types, each on all shapes, three matrices in turn), of a shape on those where it is at most 1.4 times behind the best one: within
+// 4-8 % (rms).
 inline double quad_tiles_us(const RuleMatrix& m, const DenseTiles& t, int64_t N)
 {
     struct Cost { double start, step, shared, round, write; };        // write: us per MB of C
     static constexpr Cost kCosts[4][kQuadShapes] = {
         // fp16, bf16 (a smat_dtype_t of 0 and 1; then 2, 3 and 4)
-        {{5.82, 0.317, 0.091, 0.0, 0.189}, {5.51, 0.305, 0.058, 0.0, 0.205}, {4.57, 0.260, 0.025, 0.0, 0.257}, {4.27, 0.178, 0.023, 0.0, 0.189},
-         {3.74, 0.147, 0.018, 0.0, 0.187}},
+        {{3.45, 0.401, 0.0127, 0.0, 0.287}, {4.43, 0.357, 0.01, 0.0, 0.26}, {4.05, 0.278, 0.0242, 0.0, 0.281}, {3.85, 0.192, 0.0359, 0.0, 0.184},
+         {3.17, 0.167, 0.0213, 0.0, 0.185}},
         // e4m3
-        {{6.25, 0.529, 0.020, 0.0, 0.231}, {5.60, 0.451, 0.0, 0.0, 0.269}, {4.57, 0.358, 0.0, 0.0, 0.289}, {4.05, 0.224, 0.033, 0.0, 0.212},
-         {3.62, 0.197, 0.035, 0.0, 0.250}, {5.62, 0.405, 0.009, 0.260, 0.129}, {4.86, 0.303, 0.008, 0.263, 0.154}, {4.36, 0.251, 0.009, 0.185, 0.162}},
+        {{4.31, 0.606, 0.0, 0.0, 0.28}, {5.03, 0.481, 0.0371, 0.0, 0.25}, {4.31, 0.372, 0.021, 0.0, 0.284}, {3.46, 0.255, 0.0174, 0.0, 0.245},
+         {2.68, 0.247, 0.0328, 0.0, 0.257}, {5.58, 0.336, 0.165, 0.328, 0.109}, {3.94, 0.34, 0.0614, 0.25, 0.151}, {3.55, 0.247, 0.0628, 0.167, 0.162}},
         // e5m2
-        {{6.66, 0.701, 0.019, 0.0, 0.234}, {5.95, 0.592, 0.0, 0.0, 0.254}, {4.92, 0.469, 0.0, 0.0, 0.308}, {4.66, 0.296, 0.0, 0.0, 0.201},
-         {3.79, 0.208, 0.024, 0.0, 0.269}},
+        {{5.53, 0.771, 0.0, 0.0, 0.258}, {5.48, 0.633, 0.0, 0.0, 0.257}, {4.38, 0.496, 0.0, 0.0, 0.308}, {4.26, 0.323, 0.0, 0.0, 0.205},
+         {3.05, 0.253, 0.0, 0.0, 0.313}},
         // int8
-        {{6.16, 0.336, 0.035, 0.0, 0.212}, {5.24, 0.365, 0.041, 0.0, 0.223}, {4.25, 0.320, 0.019, 0.0, 0.274}, {4.13, 0.210, 0.036, 0.0, 0.209},
-         {3.86, 0.173, 0.061, 0.0, 0.222}, {5.46, 0.301, 0.026, 0.088, 0.130}, {4.52, 0.319, 0.054, 0.061, 0.146}, {4.03, 0.221, 0.052, 0.107, 0.160}},
+        {{5.11, 0.405, 0.0049, 0.0, 0.246}, {5.32, 0.351, 0.122, 0.0, 0.212}, {3.89, 0.358, 0.0, 0.0, 0.27}, {3.25, 0.257, 0.0172, 0.0, 0.257},
+         {2.54, 0.248, 0.0277, 0.0, 0.284}, {3.69, 0.333, 0.0, 0.16, 0.155}, {5.53, 0.299, 0.194, 0.0, 0.0923}, {4.28, 0.278, 0.0, 0.116, 0.136}},
     };
     const Cost& c = kCosts[m.es == 2 ? 0 : m.dtype - 1][t.quad_shape];
     const int64_t columns = quad_shape_columns(t.quad_shape);
@@ -134,7 +135,7 @@ inline TileChoice best_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduc
         for (int64_t c0 = 0; c0 < p.N; c0 += p.in_pieces ? p.N : p.chunk) {
             const int64_t n = std::min(p.in_pieces ? p.N : p.chunk, p.N - c0);
             us += quad_tiles_us(m, t, n);
-            if (!p.in_pieces) us += 2.4 + 0.5e-6 * static_cast<double>(m.K) * static_cast<double>(n * m.es);      // the copy of B
+            if (!p.in_pieces) us += 2.9 + 0.21e-6 * static_cast<double>(m.K) * static_cast<double>(n * m.es);      // the copy of B
         }
         if (us < best.us) best = TileChoice{t.quad_shape, t.quad_tail_tiled, us};
     }
