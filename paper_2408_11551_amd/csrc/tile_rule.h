@@ -86,30 +86,45 @@ inline double quad_tiles_us(const RuleMatrix& m, const DenseTiles& t, int64_t N)
            std::ceil(in_a_unit / quad_shape_resident(t.quad_shape)) * steps * c.round + c.write * c_mb;
 }
 
-// The same on the per-row kernels, fitted on 1241 of these products that took up to 45 us (N > 32; within 8-14 %; with it the faster of rows and tiles is missed by
-// 0.6 % on average): rows of B by the byte and by
-// the 256-byte slab, values, C; rows of B that begin on whole cache lines, on 16-byte pieces, on dwords, and off them, and up to 128 bytes, where
-// mostly kernels_lines.hip runs, on dwords and off them.
+// The same on the per-row kernels (N > 32): rows of B by the byte and by the 256-byte slab; for every round of 256 workgroups the walk of one over its block row,
+// by the row of B and by the byte of it that the slab has; values, C and B by the MB.  Separately for rows of B that begin on whole cache lines, on 16-byte
+// pieces, on dwords, and off them, and up to 128 bytes, where mostly kernels_lines.hip runs, on dwords and off them.  Fitted on the products of
+// profiles/tile_rule.csv that say so, where rows take half to twice the time of the best tiles: within 6-14 % (rms; fitted for each 8-bit type by itself no closer).
 // Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
 // four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, and on dwords, where a row
 // reaches into a line more, 0.83-0.92 either way.)
 inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
 {
-    struct Cost { double start, gather, slab, values, write; };
-    static constexpr Cost kCosts[2][6] = {{{3.67, 0.0215, 8.71, 0.0, 0.196}, {4.02, 0.0311, 8.06, 0.0, 0.041}, {3.83, 0.0375, 7.14, 0.0, 0.218}, {4.00, 0.0701, 0.0, 0.450, 0.248},
-                                           {3.73, 0.0159, 6.89, 0.0, 0.0}, {3.65, 0.0412, 5.62, 0.043, 0.0}},
-                                          {{4.52, 0.0352, 5.34, 0.0, 0.014}, {4.34, 0.0, 15.52, 0.018, 0.260}, {4.79, 0.0088, 13.49, 0.0, 0.324}, {3.86, 0.0576, 4.36, 0.663, 0.405},
-                                           {4.05, 0.0540, 0.0, 0.104, 0.0}, {4.05, 0.1053, 0.0, 0.130, 0.0}}};
+    struct Cost { double start, gather, slab, walk, walk_bytes, values, write, b; };
+    static constexpr Cost kCosts[2][6] = {
+        // fp16, bf16
+        {
+            {2.625, 0.0009163, 0.6356, 2.508, 0.0, 0.09484, 0.4215, 0.7133},
+            {3.34, 0.0, 0.0, 0.994, 1.713, 0.08708, 0.288, 1.194},
+            {3.013, 0.0, 1.85, 0.6629, 1.888, 0.126, 0.4265, 1.069},
+            {3.898, 0.03859, 0.0, 0.0, 1.738, 0.3708, 0.04456, 1.353},
+            {2.49, 0.005195, 0.0, 1.688, 0.0, 0.02168, 0.6225, 1.522},
+            {3.038, 0.0, 0.0, 1.613, 0.772, 0.03413, 0.9655, 2.548},
+        },
+        // 8-bit types
+        {
+            {4.647, 0.04582, 0.0, 0.0, 0.6966, 0.06739, 0.0, 0.2049},
+            {4.21, 0.01093, 1.088, 0.8266, 1.543, 0.3384, 0.2404, 0.2081},
+            {3.647, 0.0, 2.324, 1.018, 1.334, 0.374, 0.4324, 0.7352},
+            {3.625, 0.0, 4.841, 0.0, 1.452, 1.04, 0.521, 1.571},
+            {2.736, 0.02149, 0.0, 0.5958, 1.325, 0.0, 0.2584, 3.776},
+            {2.694, 0.01871, 0.0, 0.8682, 2.81, 0.0, 0.3031, 8.393},
+        },
+    };
     const int64_t bytes = p.N * m.es, slabs = (bytes + 255) / 256;
     const double m_rows = static_cast<double>(m.b_rows) * 1e-6;
-    // (workgroups per compute unit, and what the fullest has of them: 297 workgroups take 1.5 times as long as their share of 256)
-    const double groups = static_cast<double>(m.nbr) * static_cast<double>(slabs) / 256.0;
-    const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
+    const double walk = 1e-3 * static_cast<double>(m.b_rows) / static_cast<double>(m.nbr) * std::ceil(static_cast<double>(m.nbr) * static_cast<double>(slabs) / 256.0);
     auto us_of = [&](int64_t starts) {
         const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - m.es) <= 128;
         const Cost& c = kCosts[m.es == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
-        const double row = c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs);
-        return c.start + m_rows * row * idle + c.values * m_rows * 16.0 * m.es + c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6;
+        return c.start + m_rows * (c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs) + c.values * 16.0 * m.es) +
+               walk * (c.walk + c.walk_bytes * static_cast<double>(std::min<int64_t>(bytes, 256)) / 256.0) +
+               c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6 + c.b * static_cast<double>(m.K) * static_cast<double>(bytes) * 1e-6;
     };
     return std::max(us_of(p.distance), us_of(p.starts));
 }

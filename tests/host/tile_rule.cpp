@@ -1,0 +1,47 @@
+// Goes over products with the rule for tiles (tile_rule.h).  In: one product a line, sixteen numbers.  Out: what it takes, a word a line: rows, quad_rows, or
+// the tiles' rows x columns, "s" for one group of waves, "t" with the last super row.
+#include <cstdio>
+
+#include "../../paper_2408_11551_amd/csrc/tile_rule.h"
+
+int main()
+{
+    constexpr size_t kArea = size_t{256} * 256 * 128 * 4;
+    static char area[1];
+    smat::RuleMatrix m;
+    smat::RuleProduct p;
+    smat::DenseTiles t;
+    long long M, K, N, ldb, base, b_rows, columns, tiled, rest;
+    while (std::scanf("%d %lld %lld %lld %lld %lld %lld %lld %lld %lld %d %d %d %lf %d %d", &m.dtype, &M, &K, &N, &ldb, &base, &b_rows, &columns, &tiled, &rest, &t.n,
+                      &t.n_quad_steps, &t.max_quad_steps, &t.mean_steps, &t.quad_tail, &t.quad_tail_rows) == 16) {
+        m.es = m.dtype < 2 ? 2 : 1;
+        m.M = M;
+        m.K = K;
+        m.nbr = (M + 15) / 16;
+        m.b_rows = b_rows;
+        m.columns = columns;
+        m.tiled_steps = tiled;
+        m.rest_packs = rest;
+        p.N = N;
+        p.distance = ldb * m.es;
+        p.starts = p.distance | base * m.es;
+        p.in_pieces = N % (16 / m.es) == 0 && p.starts % 16 == 0;
+        // as smat_spmm plans the copy of B
+        const int64_t line = 128 / m.es, fit = static_cast<int64_t>(kArea) / (K * 128) * line;
+        int64_t ld = (N + line - 1) / line * line, parts = 1;
+        p.chunk = N;
+        if (fit < N) {
+            parts = fit >= 128 ? (N + fit / 128 * 128 - 1) / (fit / 128 * 128) : 0;
+            if (parts > 0) p.chunk = ld = ((N + parts - 1) / parts + 127) / 128 * 128;
+        }
+        t.scratch = area;
+        const size_t copy = p.in_pieces ? 0 : static_cast<size_t>((K * ld * m.es + 255) / 256 * 256);
+        t.scratch_bytes = copy < kArea ? kArea - copy : 0;
+        const bool possible = p.in_pieces || (N >= 32 && parts > 0);
+        const smat::TileChoice best = possible ? smat::best_tiles(m, t, p) : smat::TileChoice();
+        if (possible && smat::tiles_pay(m, t, p, best))
+            std::printf("%dx%d%s%s\n", smat::quad_shape_rows(best.shape), smat::quad_shape_columns(best.shape), smat::quad_shape_groups(best.shape) == 1 ? "s" : "", best.tail ? "t" : "");
+        else
+            std::puts(smat::few_columns(m, t, p).take() ? "quad_rows" : "rows");
+    }
+}
