@@ -93,6 +93,11 @@ inline double quad_tiles_us(const RuleMatrix& m, const DenseTiles& t, int64_t N)
 // Where the base is off what the distance of the rows is on, the dearer of the two counts.  (The fit's products had their base on a line.  Of 360 at one or
 // four bytes past lines, with rows whole lines apart, the distance alone gave 0.53-0.61 of the time off the dwords, and on dwords, where a row
 // reaches into a line more, 0.83-0.92 either way.)
+inline int rows_class(int es, int64_t bytes, int64_t starts)
+{
+    const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - es) <= 128;
+    return one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3;
+}
 inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
 {
     struct Cost { double start, gather, slab, walk, walk_bytes, values, write, b; };
@@ -120,8 +125,7 @@ inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
     const double m_rows = static_cast<double>(m.b_rows) * 1e-6;
     const double walk = 1e-3 * static_cast<double>(m.b_rows) / static_cast<double>(m.nbr) * std::ceil(static_cast<double>(m.nbr) * static_cast<double>(slabs) / 256.0);
     auto us_of = [&](int64_t starts) {
-        const bool on_dwords = starts % 4 == 0, one_slab = bytes > 32 && bytes + (on_dwords ? 0 : 4 - m.es) <= 128;
-        const Cost& c = kCosts[m.es == 2 ? 0 : 1][one_slab ? (on_dwords ? 4 : 5) : starts % 128 == 0 ? 0 : starts % 16 == 0 ? 1 : on_dwords ? 2 : 3];
+        const Cost& c = kCosts[m.es == 2 ? 0 : 1][rows_class(m.es, bytes, starts)];
         return c.start + m_rows * (c.gather * static_cast<double>(bytes) + c.slab * static_cast<double>(slabs) + c.values * 16.0 * m.es) +
                walk * (c.walk + c.walk_bytes * static_cast<double>(std::min<int64_t>(bytes, 256)) / 256.0) +
                c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6 + c.b * static_cast<double>(m.K) * static_cast<double>(bytes) * 1e-6;
@@ -131,14 +135,12 @@ inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
 
 struct TileChoice { int shape = kQuad256x128; bool tail = false; double us = std::numeric_limits<double>::infinity(); };
 
-// The shape to take.  Narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
-// a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
-// 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
-// last super row of quad_tail gets tiles like the others where that pays.
-inline TileChoice best_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduct& p)
+// The cheapest of the first `shapes`, by what one launch of n columns takes and by the copy of B (a start and us per MB).
+template <typename F>
+inline TileChoice cheapest_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduct& p, int shapes, double copy, double copy_mb, F&& launch_us)
 {
     TileChoice best;
-    for (int choice = 0; choice < 2 * quad_shapes(m.dtype); ++choice) {
+    for (int choice = 0; choice < 2 * shapes; ++choice) {
         t.quad_shape = choice / 2;
         t.quad_tail_tiled = choice % 2 != 0;
         if (t.quad_tail_tiled && !t.quad_tail) continue;
@@ -149,12 +151,55 @@ inline TileChoice best_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduc
         double us = m.rest_packs >= 0 && !t.quad_tail_tiled ? 3.0 + 0.09 * static_cast<double>(m.rest_packs) : 0.0;
         for (int64_t c0 = 0; c0 < p.N; c0 += p.in_pieces ? p.N : p.chunk) {
             const int64_t n = std::min(p.in_pieces ? p.N : p.chunk, p.N - c0);
-            us += quad_tiles_us(m, t, n);
-            if (!p.in_pieces) us += 2.9 + 0.21e-6 * static_cast<double>(m.K) * static_cast<double>(n * m.es);      // the copy of B
+            us += launch_us(t, n);
+            if (!p.in_pieces) us += copy + copy_mb * 1e-6 * static_cast<double>(m.K) * static_cast<double>(n * m.es);
         }
         if (us < best.us) best = TileChoice{t.quad_shape, t.quad_tail_tiled, us};
     }
     return best;
+}
+
+// The shape to take.  Narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
+// a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
+// 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
+// last super row of quad_tail gets tiles like the others where that pays.
+inline TileChoice best_tiles(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
+{
+    return cheapest_tiles(m, t, p, quad_shapes(m.dtype), 2.9, 0.21, [&](const DenseTiles& tiles, int64_t n) { return quad_tiles_us(m, tiles, n); });
+}
+
+// 8-bit floats are added less exactly row by row than on quads (2-norm of the error over that of the result, 5 % fill: e5m2 2.75e-6 and 0.8e-6, e4m3 3.3e-6 and
+// 2.8e-6).  Where super rows are long a product of theirs is taken from the tiles only if a second pair of estimates says so, too: coarser ones, fitted on 400
+// products that are not among those above, which send more to tiles.  (Of 3158 such products with N > 32 it keeps 74 on tiles, at 0.9 ... 1.4 of the time of
+// rows, nine in ten of them.)
+inline bool coarse_estimates_take_tiles(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
+{
+    struct Tile { double start, step, shared, write; };
+    static constexpr Tile kTiles[2][kQuad256x128Single] = {
+        {{3.4, 0.562, 0.079, 0.22}, {5.2, 0.467, 0.05, 0.22}, {4.3, 0.346, 0.064, 0.22}, {3.15, 0.2125, 0.081, 0.12}, {2.6, 0.171, 0.108, 0.04}},     // e4m3
+        {{4.5, 0.81, 0.0, 0.22}, {5.4, 0.627, 0.03, 0.22}, {4.3, 0.514, 0.0, 0.22}, {4.4, 0.33, 0.0, 0.12}, {2.8, 0.239, 0.026, 0.04}},               // e5m2
+    };
+    const double steps = static_cast<double>(m.tiled_steps) / t.n;
+    const TileChoice tiles = cheapest_tiles(m, t, p, kQuad256x128Single, 3.7, 0.3, [&](const DenseTiles& of, int64_t n) {
+        const Tile& c = kTiles[m.dtype - 2][of.quad_shape];
+        const int64_t columns = quad_shape_columns(of.quad_shape);
+        const double n_tiles = static_cast<double>(quad_row_tiles(of)) * static_cast<double>((n + columns - 1) / columns);
+        const int ks = dense_even_parts(of, n);
+        if (ks > 1) return 10.5 + c.step * std::ceil(steps / ks) + std::min(9.0, 0.05 * n_tiles * ks);
+        return c.start + std::ceil(n_tiles / 256.0) * steps * c.step + n_tiles / 256.0 * steps * c.shared + c.write * static_cast<double>(m.M) * static_cast<double>(n) * 4e-6;
+    });
+    struct Rows { double start, gather, slab, values, write; };
+    static constexpr Rows kRows[6] = {{3.7, 0.0, 14.4, 0.09, 0.37}, {4.6, 0.017, 11.2, 0.013, 0.28}, {4.15, 0.012, 12.3, 0.0, 0.36}, {6.0, 0.0, 17.2, 0.57, 0.5},
+                                      {3.35, 0.064, 0.0, 0.06, 0.0}, {4.35, 0.104, 1.05, 0.0, 0.0}};
+    const double bytes = static_cast<double>(p.N), slabs = static_cast<double>((p.N + 255) / 256), m_rows = static_cast<double>(m.b_rows) * 1e-6;
+    const double groups = static_cast<double>(m.nbr) * slabs / 256.0;
+    const double idle = groups > 1.0 ? std::pow(std::ceil(groups) / groups, 0.75) : std::max(1.0, 0.75 / groups);
+    auto rows = [&](int64_t starts) {
+        const Rows& c = kRows[rows_class(1, p.N, starts)];
+        return c.start + m_rows * std::min(c.gather * bytes + c.slab * slabs, 0.14 * bytes) * idle + c.values * m_rows * 16.0 +
+               c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6;
+    };
+    return 1.08 * tiles.us + 0.5 <= std::max(rows(p.distance), rows(p.starts));
 }
 
 // Are these tiles faster than rows and the kernel for few columns?
@@ -162,7 +207,9 @@ inline bool tiles_pay(const RuleMatrix& m, const DenseTiles& t, const RuleProduc
 {
     const FewColumns few = few_columns(m, t, p);
     const double rows = p.N <= 32 ? few.rows_us : rows_us(m, p);        // (each fitted on its widths)
-    return tiles.us + 0.5 <= rows && !(few.take() && few.quads_us < tiles.us);
+    if (few.take() && few.quads_us < tiles.us) return false;
+    const bool inexact_rows = (m.dtype == 2 || m.dtype == 3) && t.mean_steps >= kDeepSteps;
+    return tiles.us + 0.5 <= rows || (inexact_rows && coarse_estimates_take_tiles(m, t, p));
 }
 
 }  // namespace smat

@@ -58,3 +58,9 @@ def test_workgroups_that_share_a_compute_unit():
     assert set(single) == {(t, n, "4") for t in "24" for n in "468"}
     for use in single.values():
         assert use["Occupancy"] == 2 and 2 * use["LDS Size"] <= 160 * 1024, single
+
+
+def test_products_of_8_bit_floats_stay_on_the_kernels_that_add_more_exactly(measured):
+    """Those of long super rows that ran on tiles when the coarse estimates alone decided (column coarse_tiles; empty: another type or short super rows) are not sent to rows."""
+    on_tiles = [r for r in measured if r["coarse_tiles"] == "1"]
+    assert len(on_tiles) > 500 and all(r["taken"] != "rows" for r in on_tiles)
