@@ -34,7 +34,8 @@ struct RuleProduct {
 // 1000 ... 8192 rows and columns, 5-20 % fill, N = 1 ... 32.  The per-row kernel: the longest workgroup's columns, or all of them, dearer
 // once values and tables no longer stay in the L2s.  This one: the steps of a workgroup, B into LDS, A -- again per pass --
 // out of the L2s or from further away.
-// (This one infinite where it does not take N columns at all, and where a super row has few steps: rows are faster then, 7693 x 1617 at 20 % in e5m2, N = 32 6.9 and 8.7 us.)
+// (This one infinite where it does not take N columns at all, and where super rows have few steps.  Of 1502 products of such matrices it takes 1.06 of the time of rows on average, 1.02 at N <= 4
+// and 1.17 at N = 17 ... 32, and is more than 3 % faster for one in five, up to 0.63: the estimates do not tell which.  7693 x 1617 at 20 % in e5m2, N = 32 8.7 us, rows 6.9.)
 struct FewColumns { double quads_us, rows_us; bool take() const { return quads_us + 0.3 < rows_us; } };
 inline FewColumns few_columns(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
 {
@@ -43,7 +44,8 @@ inline FewColumns few_columns(const RuleMatrix& m, const DenseTiles& t, const Ru
     const int row_bytes = quad_row_bytes(m.es, p.N, t.max_quad_steps);
     const double columns = static_cast<double>(m.columns), block_rows = 16.0 * t.n;
     const double per_column = m.es == 1 ? 4.2e-6 : columns * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
-    const double rows_us = 3.5 + std::max(1.0e-3 * columns / block_rows, per_column * columns);
+    // (off the dwords a row of B of more than sixteen bytes takes moves and often a piece more: 467 products are 5 % behind the faster kernel on average, 8 without this)
+    const double rows_us = 3.5 + (p.off_dwords() && p.N * m.es > 16 ? 1.3 : 1.0) * std::max(1.0e-3 * columns / block_rows, per_column * columns);
     if (row_bytes == 0 || t.mean_steps < kDeepSteps) return {kNever, rows_us};
     const double passes = static_cast<double>(quad_row_passes(m.es, p.N, row_bytes));
     const double a_mb = static_cast<double>(t.n_quad_steps) * (m.es == 1 ? 20480e-6 : 18432e-6);

@@ -64,3 +64,11 @@ def test_products_of_8_bit_floats_stay_on_the_kernels_that_add_more_exactly(meas
     """Those of long super rows that ran on tiles when the coarse estimates alone decided (column coarse_tiles; empty: another type or short super rows) are not sent to rows."""
     on_tiles = [r for r in measured if r["coarse_tiles"] == "1"]
     assert len(on_tiles) > 500 and all(r["taken"] != "rows" for r in on_tiles)
+
+
+def test_few_columns_off_the_dwords(measured):
+    """N <= 32, more than sixteen bytes, rows of B off the dwords: the per-row kernels take longer there.  (Priced as on them: 1.12 behind the faster kernel on average.)"""
+    size = {"f16": 2, "bf16": 2}
+    off = [r["behind"] for r in measured for es in [size.get(r["type"], 1)]
+           if int(r["N"]) <= 32 and int(r["N"]) * es > 16 and (int(r["ldb"]) | int(r["base"])) * es % 4 != 0]
+    assert len(off) > 50 and math.exp(sum(map(math.log, off)) / len(off)) < 1.06
