@@ -1107,6 +1107,9 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     product.chunk = chunk;
     const int64_t starts = product.starts;
     const smat::RuleMatrix rule = tiles.n_quad_steps > 0 ? rule_matrix(*h) : smat::RuleMatrix();
+    // With the static area: the parts that a call is priced, accepted or refused by.  On quads of few steps these are those of the other form, whatever is launched.
+    const bool few_steps = tiles.n_quad_steps > 0 && tiles.mean_steps < smat::kDeepSteps;
+    auto asked_parts = [&](int64_t n) { return few_steps ? smat::dense_parts(tiles, n) : smat::dense_split(tiles, n); };
     if (use_tiles && h->dense_mode == 0 && tiles.n_quad_steps > 0 && !hard_limit) {
         const smat::TileChoice best = smat::best_tiles(rule, tiles, product);
         tiles.quad_shape = best.shape;
@@ -1119,11 +1122,11 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
             const double n_tiles = static_cast<double>(tiles.n) * static_cast<double>((n + 127) / 128);
             // (The parts that the estimate was fitted with.  A launch whose tiles the XCDs do not share evenly takes fewer, and less time: 81 tiles of 94 steps in int8 41.6 us in three
             // parts, 30.7 in two, but priced as two they went to rows, 69.8.  With the static area still priced as two: on tiles some of these would be refused below.)
-            const int ks = hard_limit ? smat::dense_split(tiles, n) : smat::dense_parts(tiles, n);
+            const int ks = hard_limit ? asked_parts(n) : smat::dense_parts(tiles, n);
             // us per step of a tile, alone on its compute unit (an 8-bit step covers twice the block columns)
             const double quad_us = h->elem_bytes == 2 ? 0.43 : h->dtype == SMAT_I8 ? 0.37 : h->dtype == SMAT_E4M3 ? 0.6 : 0.7;
-            // (on quads where the static area is the limit: tiles of 256 x 128, and of few steps priced as the other form, which such calls are accepted or refused by)
-            const bool as_quads = tiles.n_quad_steps > 0 && tiles.mean_steps >= smat::kDeepSteps;
+            // (on quads where the static area is the limit; few steps as the other form)
+            const bool as_quads = tiles.n_quad_steps > 0 && !few_steps;
             const double walk_us = as_quads ? quad_us * tiles.n_quad_steps / tiles.n : (h->elem_bytes == 1 ? 1.0 : 0.7) * tiles.mean_steps;
             t_tiles += std::ceil(n_tiles * ks / 256.0) * (walk_us / ks + (as_quads ? 6.0 : 4.0)) + 1.5;
             if (ks > 1) t_tiles += 3.0 + n_tiles * (ks + 1) * 256.0 * 128.0 * 4.0 * 2.0 / 8.0e6;     // partial tiles out and in again
@@ -1139,11 +1142,17 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         use_tiles = t_tiles <= t_rows;
     }
     if (use_tiles && hard_limit && in_pieces) {
-        const size_t need = static_cast<size_t>(tiles.n) * static_cast<size_t>((N + 127) / 128) * 256 * 128 * 4 *
-                            static_cast<size_t>(smat::dense_split(tiles, N));
-        if (smat::dense_split(tiles, N) > 1 && need > hard_limit)
+        const int parts = asked_parts(N);
+        const size_t need = static_cast<size_t>(tiles.n) * static_cast<size_t>((N + 127) / 128) * 256 * 128 * 4 * static_cast<size_t>(parts);
+        if (parts > 1 && need > hard_limit)
             return fail(SMAT_ERR_UNSUPPORTED, "this launch keeps " + std::to_string(need) + " bytes of partial tiles, the static area holds " +
                                                   std::to_string(hard_limit) + ": use smat_spmm, whose area is part of the workspace");
+    }
+    if (use_tiles && hard_limit && few_steps) {
+        // (the shape of any other call: 256 x 128 on quads has a compute unit to itself, which short super rows leave idle)
+        const smat::TileChoice best = smat::best_tiles(rule, tiles, product);
+        tiles.quad_shape = best.shape;
+        tiles.quad_tail_tiled = best.tail;
     }
     const char* variant = "";
     thread_local std::string name;

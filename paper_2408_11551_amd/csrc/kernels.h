@@ -117,8 +117,8 @@ inline int dense_even_parts(const DenseTiles& t, int64_t N)
     const int64_t tiles = static_cast<int64_t>(t.n) * ((N + 127) / 128);
     int64_t ks = dense_parts(t, N);
     // An XCD has an eighth of the tiles, rounded up, and 32 compute units: one workgroup more and the launch takes two rounds (81 tiles
-    // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps leave room for two workgroups.
-    if (t.mean_steps >= kDeepSteps)
+    // of 61 steps on quads, e5m2: 56 us in three parts each, 38 in two).  Tiles of few steps that are not on quads leave room for two workgroups.
+    if (t.mean_steps >= kDeepSteps || t.n_quad_steps > 0)
         while (ks > 1 && (tiles + 7) / 8 * ks > 32) --ks;
     return static_cast<int>(ks);
 }

@@ -55,3 +55,14 @@ def test_tiles_that_are_asked_for_stay_without_quads(dtype):
     A, m = _matrix(1000, 700, dtype, 0.1, 1, dense_tiles=1)
     assert "tiles" in _check(A, m, 128, 128, 2).split("+")
     m.close()
+
+
+@pytest.mark.parametrize("dtype,M,K,fill,N", [("e5m2", 6298, 1353, 0.2, 794), ("e4m3", 4997, 528, 0.05, 1184), ("f16", 8083, 853, 0.2, 751), ("i8", 6486, 973, 0.2, 736)])
+def test_the_static_call_takes_the_shape_of_any_other(dtype, M, K, fill, N):
+    A, m = _matrix(M, K, dtype, fill, M)
+    _check(A, m, N, N, N)
+    with_static_area = S.smat_last_kernel()
+    m.spmm(torch.zeros((K, N), dtype=torch.int16 if TYPES[dtype].itemsize == 2 else torch.uint8, device="cuda:0"))
+    # (not 256 x 128 in two groups, whose name has no shape in it)
+    assert with_static_area == S.smat_last_kernel() and "x" in with_static_area, with_static_area
+    m.close()
