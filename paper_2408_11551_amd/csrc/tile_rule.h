@@ -135,17 +135,21 @@ inline double rows_us(const RuleMatrix& m, const RuleProduct& p)
     return std::max(us_of(p.distance), us_of(p.starts));
 }
 
+// 8-bit floats are added less exactly row by row than on quads (2-norm of the error over that of the result, 5 % fill: e4m3 3.3e-6 and 2.8e-6, e5m2 2.75e-6 and, where
+// everything is on quads, 3e-9): where the estimates are within their own error of each other these types take the quads, and their tiles have the last super row, too.
+inline bool inexact_rows(const RuleMatrix& m) { return m.dtype == 2 || m.dtype == 3; }
+
 struct TileChoice { int shape = kQuad256x128; bool tail = false; double us = std::numeric_limits<double>::infinity(); };
 
-// The cheapest of the first `shapes`, by what one launch of n columns takes and by the copy of B (a start and us per MB).
+// The cheapest of the first `shapes` (without_tail: the last super row of quad_tail may go row by row), by what one launch of n columns takes and by the copy of B (a start and us per MB).
 template <typename F>
-inline TileChoice cheapest_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduct& p, int shapes, double copy, double copy_mb, F&& launch_us)
+inline TileChoice cheapest_tiles(const RuleMatrix& m, DenseTiles t, const RuleProduct& p, int shapes, bool without_tail, double copy, double copy_mb, F&& launch_us)
 {
     TileChoice best;
     for (int choice = 0; choice < 2 * shapes; ++choice) {
         t.quad_shape = choice / 2;
         t.quad_tail_tiled = choice % 2 != 0;
-        if (t.quad_tail_tiled && !t.quad_tail) continue;
+        if (t.quad_tail_tiled ? !t.quad_tail : t.quad_tail && !without_tail) continue;
         const int64_t columns = quad_shape_columns(t.quad_shape);
         // (one group per workgroup is for units that share several)
         if (quad_shape_groups(t.quad_shape) == 1 && quad_row_tiles(t) * ((p.N + columns - 1) / columns) <= 256) continue;
@@ -167,13 +171,11 @@ inline TileChoice cheapest_tiles(const RuleMatrix& m, DenseTiles t, const RulePr
 // last super row of quad_tail gets tiles like the others where that pays.
 inline TileChoice best_tiles(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
 {
-    return cheapest_tiles(m, t, p, quad_shapes(m.dtype), 2.9, 0.21, [&](const DenseTiles& tiles, int64_t n) { return quad_tiles_us(m, tiles, n); });
+    return cheapest_tiles(m, t, p, quad_shapes(m.dtype), !inexact_rows(m), 2.9, 0.21, [&](const DenseTiles& tiles, int64_t n) { return quad_tiles_us(m, tiles, n); });
 }
 
-// 8-bit floats are added less exactly row by row than on quads (2-norm of the error over that of the result, 5 % fill: e5m2 2.75e-6 and 0.8e-6, e4m3 3.3e-6 and
-// 2.8e-6).  Where super rows are long a product of theirs is taken from the tiles only if a second pair of estimates says so, too: coarser ones, fitted on 400
-// products that are not among those above, which send more to tiles.  (Of 3158 such products with N > 32 it keeps 74 on tiles, at 0.9 ... 1.4 of the time of
-// rows, nine in ten of them.)
+// Where super rows are long a product of these types is taken from the tiles only if a second pair of estimates says so, too: coarser ones, fitted on 400
+// products that are not among those above, which send more to tiles.
 inline bool coarse_estimates_take_tiles(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
 {
     struct Tile { double start, step, shared, write; };
@@ -182,7 +184,7 @@ inline bool coarse_estimates_take_tiles(const RuleMatrix& m, const DenseTiles& t
         {{4.5, 0.81, 0.0, 0.22}, {5.4, 0.627, 0.03, 0.22}, {4.3, 0.514, 0.0, 0.22}, {4.4, 0.33, 0.0, 0.12}, {2.8, 0.239, 0.026, 0.04}},               // e5m2
     };
     const double steps = static_cast<double>(m.tiled_steps) / t.n;
-    const TileChoice tiles = cheapest_tiles(m, t, p, kQuad256x128Single, 3.7, 0.3, [&](const DenseTiles& of, int64_t n) {
+    const TileChoice tiles = cheapest_tiles(m, t, p, kQuad256x128Single, true, 3.7, 0.3, [&](const DenseTiles& of, int64_t n) {
         const Tile& c = kTiles[m.dtype - 2][of.quad_shape];
         const int64_t columns = quad_shape_columns(of.quad_shape);
         const double n_tiles = static_cast<double>(quad_row_tiles(of)) * static_cast<double>((n + columns - 1) / columns);
@@ -210,8 +212,9 @@ inline bool tiles_pay(const RuleMatrix& m, const DenseTiles& t, const RuleProduc
     const FewColumns few = few_columns(m, t, p);
     const double rows = p.N <= 32 ? few.rows_us : rows_us(m, p);        // (each fitted on its widths)
     if (few.take() && few.quads_us < tiles.us) return false;
-    const bool inexact_rows = (m.dtype == 2 || m.dtype == 3) && t.mean_steps >= kDeepSteps;
-    return tiles.us + 0.5 <= rows || (inexact_rows && coarse_estimates_take_tiles(m, t, p));
+    if (!inexact_rows(m)) return tiles.us + 0.5 <= rows;
+    // (1.1 and the coarse estimates: of 4983 such products with N > 32 that were measured they keep 287 on tiles, nine in ten of them at 0.84 ... 1.21 of the time of rows.)
+    return tiles.us + 0.5 <= 1.1 * rows || (t.mean_steps >= kDeepSteps && coarse_estimates_take_tiles(m, t, p));
 }
 
 }  // namespace smat

@@ -1,0 +1,56 @@
+"""What the choice of a kernel does to the error of random products, against float64: tiles of one group and super rows of few steps are no less exact than the tiles they
+stand in for, and products of 8-bit floats whose last super row is short stay on the kernels that add more exactly."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2408_11551_amd as S
+
+pytestmark = pytest.mark.gpu
+TYPES = {"f16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn, "e5m2": torch.float8_e5m2}
+
+
+def _errors(M, K, fill, N, dtype, seed, modes=(0, 1)):
+    """2-norm of the error over that of the result, and the kernel, per dense_tiles in `modes` (0: chosen, 1: tiles that are asked for)."""
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    mask = torch.rand((M, K), device="cuda:0", generator=gen) < fill
+    vals = (0.25 * torch.randn((M, K), device="cuda:0", generator=gen)).to(TYPES[dtype])
+    B = torch.randn((K, N), device="cuda:0", generator=gen).to(TYPES[dtype])
+    want = torch.where(mask, vals.double(), 0.0) @ B.double()
+    rows, cols = mask.nonzero(as_tuple=True)
+    row_ptr = np.zeros(M + 1, np.int64)
+    np.cumsum(mask.sum(1).cpu().numpy(), out=row_ptr[1:])
+    bits = torch.int16 if TYPES[dtype].itemsize == 2 else torch.uint8
+    stored = vals[rows, cols].view(bits).cpu().numpy().view(np.uint16 if bits == torch.int16 else np.uint8)
+    out = []
+    for mode in modes:
+        m = S.SmatMatrix(M, K, row_ptr, cols.to(torch.int32).cpu().numpy(), stored, dtype, dense_tiles=mode, device="cuda:0")
+        C = m.spmm(B.view(bits))
+        out.append((float((C.double() - want).norm() / want.norm()), S.smat_last_kernel()))
+        m.close()
+    return out
+
+
+@pytest.mark.parametrize("M,K,fill,N", [(4096, 4096, 0.05, 4000), (3500, 8192, 0.1, 3800), (4096, 4096, 0.2, 4000), (5000, 2100, 0.2, 3000)])
+def test_tiles_of_one_group(M, K, fill, N):
+    """e4m3 adds all steps in one chain there, two groups in two: what it loses it loses inside an instruction."""
+    (one, name), (two, name_two) = _errors(M, K, fill, N, "e4m3", M + N)
+    assert "_g1_" in name and "_g2" in name_two, (name, name_two)
+    assert one <= 1.01 * two, (one, two)
+
+
+@pytest.mark.parametrize("dtype", list(TYPES))
+@pytest.mark.parametrize("M,K,fill,N", [(4000, 900, 0.1, 1200), (5000, 750, 0.1, 1000)])
+def test_super_rows_of_few_steps(dtype, M, K, fill, N):
+    (quads, name), (tiles, name_tiles) = _errors(M, K, fill, N, dtype, K)
+    assert name != name_tiles and "dense" in name, (name, name_tiles)
+    # (a matrix's own scatter: half the steps in two chains, or one as long as before in e4m3)
+    assert quads <= 1.02 * tiles, (quads, tiles)
+
+
+@pytest.mark.parametrize("M,K,fill,N", [(1538, 7724, 0.1, 2435), (2576, 4096, 0.1, 800)])
+def test_a_last_super_row_of_few_rows_is_on_tiles_too(M, K, fill, N):
+    """e5m2 on quads is widened to f16 and added in fp32, where an addition is off by half of 2^-23 at most; by themselves the last two rows of 1538 would be off by 3e-6,
+    which is 1.1e-7 of the whole, and the last sixteen of 2576 2.3e-7."""
+    (error, name), = _errors(M, K, fill, N, "e5m2", N, modes=(0,))
+    assert "+" not in name and "dense" in name and error < 2.0 ** -24, (error, name)
