@@ -60,6 +60,19 @@ static int cmp_i32(const void* a, const void* b)
     return (x > y) - (x < y);
 }
 
+/* Scratch memory for the set-up of a large matrix, asked for only where searching on the device pays. */
+typedef struct { void* at; hipStream_t stream; } scratch_t;
+static void* scratch_of(size_t bytes, void* user, void** stream)
+{
+    scratch_t* s = (scratch_t*)user;
+    if (hipMalloc(&s->at, bytes) != hipSuccess) {        /* then the host searches */
+        (void)hipGetLastError();                         /* (the next launch would report it) */
+        return s->at = NULL;
+    }
+    *stream = s->stream;
+    return s->at;
+}
+
 int main(int argc, char** argv)
 {
     const int64_t M = argc > 1 ? atoll(argv[1]) : 1000;
@@ -98,17 +111,20 @@ int main(int argc, char** argv)
         b_bits[i] = half_of_small_int(b_int[i]);
     }
 
-    /* preprocess on the host, bind to device memory of our own, multiply */
+    /* preprocess (smat_preprocess does it on the host alone), bind to device memory of our own, multiply */
+    hipStream_t stream;
+    CHECK_HIP(hipStreamCreate(&stream));
+    scratch_t scratch = {NULL, stream};
     smat_handle_t* h = NULL;
-    CHECK_SMAT(smat_preprocess(M, K, row_ptr, col_idx, a_bits, SMAT_F16, NULL, &h));
+    CHECK_SMAT(smat_preprocess_on_device(M, K, row_ptr, col_idx, a_bits, SMAT_F16, NULL, scratch_of, &scratch, &h));
+    const int searched = scratch.at != NULL;
+    CHECK_HIP(hipFree(scratch.at));
     int64_t nbr = 0, n_blocks = 0, n_packs = 0;
     CHECK_SMAT(smat_get_info(h, &nbr, &n_blocks, NULL, NULL));
     CHECK_SMAT(smat_get_layout_info(h, &n_packs, NULL, NULL, NULL));
     size_t ws_bytes = 0;
     CHECK_SMAT(smat_device_bytes(h, &ws_bytes));
     void *ws = NULL, *dB = NULL, *dC = NULL;
-    hipStream_t stream;
-    CHECK_HIP(hipStreamCreate(&stream));
     CHECK_HIP(hipMalloc(&ws, ws_bytes));
     CHECK_HIP(hipMalloc(&dB, (size_t)K * N * 2));
     CHECK_HIP(hipMalloc(&dC, (size_t)M * N * 4));
@@ -128,8 +144,8 @@ int main(int argc, char** argv)
             for (int j = 0; j < per_row; ++j) sum += (long)a_int[r * per_row + j] * b_int[(int64_t)col_idx[r * per_row + j] * N + n];
             if (c[r * N + n] != (float)sum) ++wrong;
         }
-    printf("M=%lld K=%lld N=%lld nnz=%lld blocks=%lld packs=%lld kernel=%s wrong=%lld\n", (long long)M, (long long)K,
-           (long long)N, (long long)(M * per_row), (long long)n_blocks, (long long)n_packs, smat_last_kernel(), (long long)wrong);
+    printf("M=%lld K=%lld N=%lld nnz=%lld blocks=%lld packs=%lld searched=%d kernel=%s wrong=%lld\n", (long long)M, (long long)K,
+           (long long)N, (long long)(M * per_row), (long long)n_blocks, (long long)n_packs, searched, smat_last_kernel(), (long long)wrong);
     smat_destroy(h);
     CHECK_HIP(hipFree(ws));
     CHECK_HIP(hipFree(dB));
