@@ -27,9 +27,9 @@
 // Two groups leave a compute unit to one workgroup (eight waves of up to 256 registers): all of it waits while a tile begins, hands over and stores.  With
 // more tiles than compute units that is worse than what the groups are for, so e4m3 and int8 have three of the shapes also with one group of four waves that takes all
 // steps (KG = 1): two workgroups share a compute unit, one's loop runs beside the other's start and stores, no partial sums change
-// hands, and a barrier joins four waves instead of eight.  us, the best shape of two groups and of one: 4696 x 3919 at 10 % in int8, N = 2368 40.8 -> 34.8;
-// 3247 x 2257 at 20 %, N = 2816 30.4 -> 25.0; 3484 x 3387 at 5 % in e4m3, N = 3560 54.9 -> 46.9.  (The other types would gain as much, f16 5541 x 1077, N = 1598 31.7 ->
-// 25.8, but add less exactly in one chain: kernels.h.  128 x 64 and 128 x 32 with one group: the best of 0.2 % of 1935 products, not built.)
+// hands, and a barrier joins four waves instead of eight.  us of the kernel, the best shape of two groups and of one: 4696 x 3919 at 10 % in int8, N = 2368 43.4 (256 x 96) -> 37.8
+// (256 x 96); 3247 x 2257 at 20 %, N = 2816 32.0 -> 26.0 (256 x 128); 3484 x 3387 at 5 % in e4m3, N = 3560 54.3 -> 45.8.  (The other types would gain as much, f16 5541 x 1077,
+// N = 1598 31.7 -> 25.8, but add less exactly in one chain: kernels.h.  128 x 64 and 128 x 32 with one group: the best of 0.2 % of 1935 products, not built.)
 //
 // What bounds it: the fills.  A step moves 34 KiB (36) into the compute unit where two steps of the other kernel move 48.  (4096 x 4096
 // in bf16, N = 2048, with parts left out: all 42 us, no matrix instructions 35, loads alone 35, matrix instructions alone 27, neither 13.)  The 8-bit
@@ -398,6 +398,7 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
     }
     int32_t out_rows[RM][4] = {};
     if constexpr (KG == 1) {
+        // (Behind the loop, in which 256 x 128 in e4m3 uses 252 of 256 registers.  Nothing of this workgroup hides the trip, but another one shares the unit.)
 #pragma unroll
         for (int r = 0; r < RM; ++r)
 #pragma unroll

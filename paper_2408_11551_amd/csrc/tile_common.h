@@ -119,8 +119,8 @@ __device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_i
 #pragma unroll
         for (int y = 0; y < 4; ++y) out_rows[r][y] = KG == 1 ? out_rows_in[r][y] : 0;
     }
-    // Where the lane's rows of C' go.  One group per workgroup: already asked for before the loop (the registers are
-    // there, and the stores then begin without one more trip to memory -- which a short tile on cold caches feels).
+    // Where the lane's rows of C' go.  One group per workgroup: asked for by the caller, where its registers allow before the loop
+    // (the stores then begin without one more trip to memory -- which a short tile on cold caches feels).
     // Two groups: asked for when the loop ends, ahead of the hand-over, which hides the trip; a lane then stores half
     // of its block rows (group 0 the first, group 1 the others).  (The empty statement makes the super
     // row's number a value the compiler knows only from here on, so that it cannot move these loads above the loop:
