@@ -11,7 +11,7 @@
 //     short: launch_partners.)
 //
 // What bounds it: the lists, read twice each from the L2s, and for a workgroup's pattern two barriers and the trip to its lists between them.  A graph
-// of 65536 rows of 16 (52 000 patterns, 134 million pairs of entries): 220 us for the long ones and 150-200 for the short, 740 with a workgroup for every
+// of 65536 rows of 16 (52 000 patterns, 134 million pairs of entries): 223 us for the long ones and 216 for the short, 740 with a workgroup for every
 // pattern and a global counter of pairs; sixteen host threads 4700-5000.
 #include <hip/hip_runtime.h>
 
