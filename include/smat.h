@@ -122,8 +122,9 @@ typedef void *(*smat_scratch_fn)(size_t bytes, void *user, void **stream);
 
 /* The same handle, made with the device's help: of a large matrix in which most clusters stay single rows (a graph, random
  * entries) the pairs of rows that could start a cluster are looked for on the device, in memory (64 MiB at most) that `scratch` gives.  The call may
- * enqueue copies and kernels on that stream and waits for them; where it does not pay it asks for nothing, and there, where it gets nothing, and
- * where the stream is being captured, it does what smat_preprocess does. */
+ * enqueue copies and kernels on that stream and waits for them; where it does not pay it asks for nothing, and there, where it gets nothing,
+ * where the stream is being captured, and where a pattern of rows has more partners than the kernels hold of one (128, or 512 with more than 32 block columns), it
+ * does what smat_preprocess does. */
 smat_status_t smat_preprocess_on_device(int64_t M, int64_t K,
                                         const int64_t *row_ptr, const int32_t *col_idx, const void *vals,
                                         smat_dtype_t dtype, const smat_options_t *opt,
