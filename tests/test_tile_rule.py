@@ -49,7 +49,7 @@ def test_the_rule_takes_about_the_fastest(measured, fitted, mean, share):
 def test_workgroups_that_share_a_compute_unit():
     """Tiles of one group of four waves are priced with two workgroups to a compute unit: a wave of each on every SIMD, and their LDS together."""
     if not os.path.exists(build.RESOURCES) or os.path.getmtime(build.RESOURCES) + 60 < os.path.getmtime(lib_path()):
-        pytest.skip("no report of this build")
+        pytest.skip("the library was built elsewhere, or after the report")
     single = {}
     for name, use in json.load(open(build.RESOURCES)).items():
         m = re.search(r"spmm_quad_tile_kernelILi(\d)ELi(\d)ELi(\d)ELi1E", name)
