@@ -270,7 +270,7 @@ const char *smat_last_kernel(void);
 /* What the last smat_spmm on this thread enqueued (for profiles, logs and tests), in order and joined by "+":
  * "rows" the per-row kernel, "copy_b" the copy of a B off the pieces or lines (of a range of columns at a time), "tiles" and
  * "quad_tiles" the tile kernels without and with the two-of-four instructions, "quad_rows" the kernel for few columns on the latter,
- * "sum_tiles" the sum of partial tiles; "" if nothing.  *flop (may be NULL) receives the operations that the matrix
+ * "entries" the one on the list of stored entries, which has no matrix instructions, "sum_tiles" the sum of partial tiles; "" if nothing.  *flop (may be NULL) receives the operations that the matrix
  * instructions of these launches take, two per pair of values (zeros that are stored, padded or left out by the two-of-four
  * instructions: only those that fill a value's place); per-row kernel: with N rounded up to sixteen columns.  The
  * string is valid until the next call on the same thread. */

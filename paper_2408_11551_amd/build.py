@@ -40,6 +40,7 @@ UNITS = {
     # MFMA results live in ordinary VGPRs instead of being shuffled between the two register files
     "kernels_dense": ("kernels_dense.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1", *PRELOAD]),
     "kernels_quads": ("kernels_quads.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1", *PRELOAD]),
+    "kernels_entries": ("kernels_entries.hip", PRELOAD),
     "kernels_setup": ("kernels_setup.hip", []),
     # the tile-step probe is the tile kernel's loop: same flag
     "probes": ("probes.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
@@ -48,7 +49,7 @@ UNITS = {
 # the product call on torch tensors, a CPython extension beside the library it links (built by g++: host code only)
 CALL_SRC = os.path.join(CSRC, "torch_call.cpp")
 CALL_OUT = os.path.join(HERE, "_torch_call.so")
-HEADERS = ["api.h", "kernels.h", "lines_rule.h", "tile_rule.h", "tile_common.h", "quad_layout.h", "workers.h", "preprocess.h", "pack_layout.h", "spmm_rows.h", os.path.join("..", "..", "include", "smat.h"),
+HEADERS = ["api.h", "kernels.h", "lines_rule.h", "tile_rule.h", "tile_common.h", "quad_layout.h", "entry_layout.h", "workers.h", "preprocess.h", "pack_layout.h", "spmm_rows.h", os.path.join("..", "..", "include", "smat.h"),
            os.path.join("..", "..", "include", "smat_bench.h"), "mfma_types.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -71,7 +72,7 @@ def is_stale() -> bool:
 # Kernels that place their own waits for outstanding loads (the tile kernel counts its six loads per step, the
 # walks of the per-row kernel theirs): a register spilled inside their loops adds loads the counts do not know
 # of and serialises the prefetch (seen once: 79 instead of 53 us).  The build fails if one of them spills.
-NO_SPILL = ("spmm_tile_kernel", "spmm_quad_tile_kernel", "spmm_quad_rows_kernel", "spmm_lines_kernel", "spmm_kernel")
+NO_SPILL = ("spmm_tile_kernel", "spmm_quad_tile_kernel", "spmm_quad_rows_kernel", "spmm_lines_kernel", "spmm_entry_kernel", "spmm_kernel")
 _REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill|SGPRs Spill|TotalSGPRs|LDS Size \[bytes/block\]|Occupancy \[waves/SIMD\]): (\S+)")
 
 

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "api.h"
+#include "entry_layout.h"
 #include "kernels.h"
 #include "pack_layout.h"
 #include "preprocess.h"
@@ -75,10 +76,12 @@ struct smat_handle {
     int64_t quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr.back(); }
     int64_t tiled_quad_steps() const { return quad_ptr.empty() ? 0 : quad_ptr[dense_super.size()]; }      // without those of quad_tail
     int64_t dense_columns = 0;           // occupied columns over the blocks of the dense super rows
+    std::vector<uint32_t> entry_row_at;  // [M+1] first record of every row of the entry list (entry_layout.h); empty: there is none
     smat::DeviceBcsr dev;                // launch over every block row
     smat::DeviceBcsr dev_rest;           // launch over the block rows the dense path does not cover
     smat::DeviceBcsr dev_tiles;          // what the tile kernels take: dev, with the rows in the order of bcsr
     smat::DenseTiles tiles;
+    smat::EntryList entries;
     // device copies of the CSR (kept: they live in the caller's workspace anyway)
     const int64_t* d_csr_row_ptr = nullptr;
     const int32_t* d_csr_col_idx = nullptr;
@@ -155,7 +158,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t perm, work, work_rest, slots, vals, pack_ptr, slots_off, vals_off, row_class, blk_ptr, blk_col, blk_pack, blk_meta;
     size_t csr_row_ptr, csr_col_idx, csr_vals, col_perm;
-    size_t t_perm, t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, tables_end, total;
+    size_t t_perm, t_super, t_ptr, t_cols, t_rows, t_base, t_vals, t_quad_rows, t_quad_index, t_scratch, e_row_at, e_records, tables_end, total;
 };
 
 Layout make_layout(const smat_handle& h)
@@ -184,6 +187,7 @@ Layout make_layout(const smat_handle& h)
     l.t_rows = take(quads ? 0 : h.step_rows.size() * sizeof(uint32_t));
     l.t_base = take(quads ? 0 : h.step_base.size() * sizeof(uint32_t));
     l.t_quad_rows = take(h.quad_rows.size() * sizeof(int32_t));
+    l.e_row_at = take(h.entry_row_at.size() * sizeof(uint32_t));
     l.tables_end = off;
     // made on the device, and with the tables what a launch reads: next to them (behind what only a bind reads, 21.5 M
     // entries further on, hidden blocks took 52.0 us instead of 47.5)
@@ -191,6 +195,7 @@ Layout make_layout(const smat_handle& h)
     l.vals = take(static_cast<size_t>(h.vals_units) * 64);
     l.t_vals = take(quads ? quads * 16384 : static_cast<size_t>(h.dense_slots) * 1024);
     l.t_quad_index = take(quads * (h.elem_bytes == 1 ? 4096 : 2048));
+    l.e_records = take(h.entry_row_at.empty() ? 0 : static_cast<size_t>(h.entry_row_at.back()) * static_cast<size_t>(smat::entry_record_bytes(h.elem_bytes)));
     // one element per stored entry or block, sent each by itself
     l.blk_col = take(n_e * sizeof(int32_t));
     l.blk_pack = take(h.by_column ? n_e * sizeof(int32_t) : 0);
@@ -572,6 +577,74 @@ void row_stats(const smat_handle& h, bool skip_dense, smat::DeviceBcsr& d)
     d.max_class = cls;
 }
 
+// Columns that the block rows occupy which tiles would take in their place.
+int64_t columns_of_rows(const smat_handle& h) { return h.bcsr.grouped ? h.b_rows : h.dense_columns; }
+
+// What the rule for tiles goes by (tile_rule.h).
+smat::RuleMatrix rule_matrix(const smat_handle& h)
+{
+    smat::RuleMatrix m;
+    m.dtype = h.dtype;
+    m.es = h.elem_bytes;
+    m.M = h.csr.M;
+    m.K = h.csr.K;
+    m.nbr = h.bcsr.nbr;
+    m.b_rows = h.b_rows;
+    m.columns = columns_of_rows(h);
+    m.tiled_steps = h.tiled_quad_steps();
+    m.rest_packs = h.dev_rest.n_order > 0 ? h.dev_rest.max_row_packs : -1;
+    m.entry_records = h.entry_row_at.empty() ? 0 : h.entry_row_at.back();
+    return m;
+}
+
+// What the plan says of the tiles (bind adds where they are, a call its scratch area and shape).
+smat::DenseTiles planned_tiles(const smat_handle& h)
+{
+    smat::DenseTiles t;
+    t.n_quad_steps = static_cast<int32_t>(h.quad_steps());
+    t.max_quad_steps = h.max_quad_steps;
+    t.quad_tail = h.quad_tail;
+    t.quad_tail_rows = h.quad_tail ? static_cast<int32_t>(h.bcsr.nbr - 16 * ((h.bcsr.nbr - 1) / 16)) : 0;      // 1 ... 16
+    t.n = static_cast<int32_t>(h.dense_super.size());
+    t.mean_steps = t.n ? static_cast<double>(h.step_rows.size()) / t.n : 0.0;
+    t.cols_per_step = h.elem_bytes == 1 ? 4 : 2;
+    t.all_full = h.dense_all_full && t.n > 0;
+    t.full_steps = t.all_full ? h.step_ptr[1] : 0;
+    return t;
+}
+
+// The entry list (entry_layout.h): for matrices of which B has a column or more in LDS, whose rows are long enough to be shared by lanes, and whose block rows are
+// by and large not kept by entry (those have a walk of their own for few columns) -- and only where the list is the faster one for some number of columns.
+void plan_entries(smat_handle& h)
+{
+    const int64_t M = h.csr.M, K = h.csr.K, nnz = static_cast<int64_t>(h.csr.col_idx.size());
+    h.entry_row_at.clear();
+    if (!smat::launch_entries || h.dense_mode != 0 || h.cols_permuted || K >= 65536 || smat::entry_columns(K, h.elem_bytes, 1) == 0 || nnz < 48 * M || nnz < 500000 ||
+        nnz >= int64_t{1} << 32 || 16 * nnz <= 18 * h.b_rows)
+        return;
+    auto records = [&](int64_t r) { return static_cast<uint32_t>((h.csr.row_ptr[r + 1] - h.csr.row_ptr[r] + smat::kEntriesPerRecord - 1) / smat::kEntriesPerRecord); };
+    smat::RuleMatrix m = rule_matrix(h);
+    for (int64_t r = 0; r < M; ++r) m.entry_records += records(r);
+    for (size_t br = 0; br < h.row_dense.size(); ++br)
+        if (!h.row_dense[br]) m.rest_packs = std::max<int64_t>(m.rest_packs, h.pack_ptr[br + 1] - h.pack_ptr[br]);
+    const smat::DenseTiles tiles = planned_tiles(h);
+    bool pays = false;
+    for (int64_t n = 1; n <= smat::kEntryMostColumns && !pays; ++n) {
+        smat::RuleProduct p;
+        p.N = n;
+        p.distance = p.starts = n * h.elem_bytes;
+        pays = smat::entries_pay(m, tiles, p);
+    }
+    if (!pays) return;
+    h.entry_row_at.resize(static_cast<size_t>(M) + 1);
+    uint32_t at = 0;
+    for (int64_t r = 0; r < M; ++r) {
+        h.entry_row_at[static_cast<size_t>(r)] = at;
+        at += records(r);
+    }
+    h.entry_row_at[static_cast<size_t>(M)] = at;
+}
+
 }  // namespace
 
 extern "C" {
@@ -651,6 +724,7 @@ smat_status_t smat::preprocess(int64_t M, int64_t K, const int64_t* row_ptr, con
             return fail(SMAT_ERR_UNSUPPORTED, e.what());
         }
         plan_quads(*h, workers);
+        plan_entries(*h);
         *out = h.release();
         return SMAT_OK;
     } catch (const std::bad_alloc&) {
@@ -794,6 +868,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
             put(l.t_rows, h->step_rows.data(), h->step_rows.size() * 4);
             put(l.t_base, h->step_base.data(), h->step_base.size() * 4);
         }
+        put(l.e_row_at, h->entry_row_at.data(), h->entry_row_at.size() * 4);
         put(l.pack_ptr, h->pack_ptr.data(), h->pack_ptr.size() * 4);
         put(l.slots_off, h->slots_off.data(), h->slots_off.size() * 4);
         put(l.vals_off, h->vals_off.data(), h->vals_off.size() * 4);
@@ -839,7 +914,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         d_rest.work = reinterpret_cast<const int32_t*>(base + l.work_rest);
         smat::DeviceBcsr d_tiles = d;
         if (two_orders) d_tiles.perm = reinterpret_cast<const int32_t*>(base + l.t_perm);
-        smat::DenseTiles tiles;
+        smat::DenseTiles tiles = planned_tiles(*h);
         tiles.super_rows = reinterpret_cast<const int32_t*>(base + l.t_super);
         tiles.step_ptr = reinterpret_cast<const int32_t*>(base + l.t_ptr);
         tiles.step_cols = reinterpret_cast<const int32_t*>(base + l.t_cols);
@@ -848,17 +923,6 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         tiles.vals = base + l.t_vals;
         tiles.quad_rows = reinterpret_cast<const int32_t*>(base + l.t_quad_rows);
         tiles.quad_index = reinterpret_cast<const uint8_t*>(base + l.t_quad_index);
-        tiles.n_quad_steps = static_cast<int32_t>(h->quad_steps());
-        tiles.max_quad_steps = h->max_quad_steps;
-        tiles.quad_tail = h->quad_tail;
-        tiles.quad_tail_rows = h->quad_tail ? static_cast<int32_t>(b.nbr - 16 * ((b.nbr - 1) / 16)) : 0;      // 1 ... 16
-        tiles.scratch = nullptr;           // a call takes the area of its stream
-        tiles.scratch_bytes = 0;
-        tiles.n = static_cast<int32_t>(h->dense_super.size());
-        tiles.mean_steps = tiles.n ? static_cast<double>(h->step_rows.size()) / tiles.n : 0.0;
-        tiles.cols_per_step = h->elem_bytes == 1 ? 4 : 2;
-        tiles.all_full = h->dense_all_full && tiles.n > 0;
-        tiles.full_steps = tiles.all_full ? h->step_ptr[1] : 0;
         h->d_csr_row_ptr = reinterpret_cast<const int64_t*>(base + l.csr_row_ptr);
         h->d_csr_col_idx = reinterpret_cast<const int32_t*>(base + l.csr_col_idx);
         h->d_csr_vals = reinterpret_cast<const uint16_t*>(base + l.csr_vals);
@@ -874,6 +938,11 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
                                            h->max_quad_steps, s)
                   : smat::launch_dense_fill(d_tiles, tiles, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, base + l.t_vals, h->elem_bytes, s);
         if (e) return hip_fail("fill tile values", e);
+        smat::EntryList entries;
+        if (!h->entry_row_at.empty()) {
+            entries = smat::EntryList{reinterpret_cast<const uint32_t*>(base + l.e_row_at), base + l.e_records, h->csr.M, h->csr.K};
+            if ((e = smat::launch_entry_fill(entries, h->elem_bytes, h->d_csr_row_ptr, h->d_csr_col_idx, h->d_csr_vals, s))) return hip_fail("fill entry list", e);
+        }
         if ((e = static_cast<int>(hipStreamSynchronize(s)))) return hip_fail("bind synchronize", e);
         {
             // set-up is the place to find this device's copy of the static area (smat_spmm_static)
@@ -885,6 +954,7 @@ smat_status_t smat_bind_device(smat_handle_t* h, void* dev_workspace, size_t byt
         h->dev_rest = d_rest;
         h->dev_tiles = d_tiles;
         h->tiles = tiles;
+        h->entries = entries;
         {
             std::lock_guard<std::mutex> lock(h->scratch_mutex);
             h->scratch_base = l.total > l.t_scratch ? base + l.t_scratch : nullptr;
@@ -1037,25 +1107,6 @@ ScratchArea scratch_area_of(const smat_handle* h, void* stream)
 // columns are mostly empty.
 constexpr int64_t kStageColumns = 32;
 
-// Columns that the block rows occupy which tiles would take in their place.
-int64_t columns_of_rows(const smat_handle& h) { return h.bcsr.grouped ? h.b_rows : h.dense_columns; }
-
-// What the rule for tiles goes by (tile_rule.h).
-smat::RuleMatrix rule_matrix(const smat_handle& h)
-{
-    smat::RuleMatrix m;
-    m.dtype = h.dtype;
-    m.es = h.elem_bytes;
-    m.M = h.csr.M;
-    m.K = h.csr.K;
-    m.nbr = h.bcsr.nbr;
-    m.b_rows = h.b_rows;
-    m.columns = columns_of_rows(h);
-    m.tiled_steps = h.tiled_quad_steps();
-    m.rest_packs = h.dev_rest.n_order > 0 ? h.dev_rest.max_row_packs : -1;
-    return m;
-}
-
 // smat_spmm with the area for partial tiles given by the caller of this function.
 // hard_limit = 0: the launch is planned so that its partial tiles fit scratch_bytes.  Otherwise it
 // is planned as if the area were unlimited and refused when its partial tiles exceed hard_limit.
@@ -1106,7 +1157,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     product.in_pieces = in_pieces;
     product.chunk = chunk;
     const int64_t starts = product.starts;
-    const smat::RuleMatrix rule = tiles.n_quad_steps > 0 ? rule_matrix(*h) : smat::RuleMatrix();
+    const smat::RuleMatrix rule = tiles.n_quad_steps > 0 || h->entries.row_at ? rule_matrix(*h) : smat::RuleMatrix();
     // With the static area: the parts that a call is priced, accepted or refused by.  On quads of few steps these are those of the other form, whatever is launched.
     const bool few_steps = tiles.n_quad_steps > 0 && tiles.mean_steps < smat::kDeepSteps;
     auto asked_parts = [&](int64_t n) { return few_steps ? smat::dense_parts(tiles, n) : smat::dense_split(tiles, n); };
@@ -1164,7 +1215,11 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
     // e4m3 goes over the two-of-four form twice
     const double step_flop = 2.0 * 16 * 16 * (h->elem_bytes == 2 ? 32 : 64) * 16;
     const double quad_step_flop = step_flop * (h->dtype == SMAT_E4M3 ? 2.0 : 1.0);
-    if (!use_tiles && h->dense_mode == 0 && smat::few_columns(rule, tiles, product).take()) {
+    if (!use_tiles && h->entries.row_at && smat::entries_pay(rule, tiles, product)) {
+        e = smat::launch_entries(h->entries, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);
+        enqueued("entries", 0);
+        g_kernel = variant;
+    } else if (!use_tiles && h->dense_mode == 0 && smat::few_columns(rule, tiles, product).take()) {
         // (with quad_tail all block rows are among the quads)
         if (h->dev_rest.n_order > 0 && !h->quad_tail) {
             e = smat::launch_spmm(h->dev_rest, h->dtype, dB, ldb, dC, ldc, N, stream, &variant);

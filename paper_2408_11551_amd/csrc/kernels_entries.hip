@@ -1,0 +1,386 @@
+// HIP kernel for gfx950: few columns of a matrix whose rows have dozens of entries, entry by entry (a decode step with pruned weights).
+//
+// With N <= 16 such a product is the stream of A.  On quads (spmm_quad_rows_kernel) that is two slots for every four columns, of which at 5-20 % fill one in
+// two to ten holds an entry, and their positions; here it is the entries themselves with a 16-bit column number each: 8192 x 4096 at 10 % in int8 10 MB instead of 21.
+// The per-row kernel streams less than quads, but its rate of requests for rows of B bounds it.
+//
+// A workgroup of sixteen waves brings all of B into LDS, NC columns of every row; LPR lanes share a row of A, every one takes a record of four entries at a
+// time, reads the four rows of B that it names out of LDS and multiplies in vector instructions, exactly and into fp32 (int8: four products an instruction).
+// What bounds it: up to some 4 MB the launch; then the stream of A (9 TB/s out of the Infinity Cache); with eight columns of a 16-bit type and more the
+// random reads of LDS, whose banks meet, and one instruction per product.  us on quads and here, three matrices in turn: 8192 x 4096 at 10 % in int8, N = 4 6.9 -> 5.4;
+// 7176 x 7988 at 10 % in f16, N = 4 13.8 -> 8.5; 7149 x 7487 in int8, N = 16 9.8 -> 9.4.  On rows and here: 1913 x 5565 at 5 % in f16, N = 12 8.4 -> 5.0.
+// The sums of a row's lanes go through the lanes in halves; each of sixteen columns by itself was 1-2 us slower at N = 16 (7563 x 1177 at 20 % in int8, N = 24 9.6 -> 8.8).  Rows of B
+// that lie next to each other are fetched sixteen bytes at a time: 2958 x 19126 in f16, N = 2 9.9 -> 7 us.
+#include <cstdio>
+#include <type_traits>
+
+#include <hip/hip_runtime.h>
+
+#include "entry_layout.h"
+#include "kernels.h"
+#include "mfma_types.h"
+#include "tile_common.h"
+
+namespace smat {
+
+template <int ES> struct EntryRecord;
+template <> struct EntryRecord<2> { uint32_t w[4]; };
+template <> struct EntryRecord<1> { uint32_t w[3]; };
+static_assert(sizeof(EntryRecord<2>) == entry_record_bytes(2) && sizeof(EntryRecord<1>) == entry_record_bytes(1), "records lie back to back");
+
+// acc[n] += a[e] b[e][n] over a record's four entries e: every product exact, sums in fp32, one after the other (int8: int32).  a: the values as they
+// lie in the record; b[e]: NC columns of a row of B.
+template <int DT, int NC>
+__device__ __forceinline__ void multiply_record(const uint32_t* a, const uint32_t (&b)[kEntriesPerRecord][(NC * Elem<DT>::ES + 3) / 4], typename Elem<DT>::Out (&acc)[NC])
+{
+    if constexpr (DT == kI8) {
+        // the four rows' bytes of a column in one word, four products at a time
+        constexpr int W = (NC + 3) / 4;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t lo0 = __builtin_amdgcn_perm(b[1][w], b[0][w], 0x05010400u), lo1 = __builtin_amdgcn_perm(b[3][w], b[2][w], 0x05010400u);
+            const uint32_t hi0 = __builtin_amdgcn_perm(b[1][w], b[0][w], 0x07030602u), hi1 = __builtin_amdgcn_perm(b[3][w], b[2][w], 0x07030602u);
+#pragma unroll
+            for (int x = 0; x < 4 && 4 * w + x < NC; ++x) {
+                const uint32_t column = __builtin_amdgcn_perm(x < 2 ? lo1 : hi1, x < 2 ? lo0 : hi0, x & 1 ? 0x07060302u : 0x05040100u);
+                acc[4 * w + x] = __builtin_amdgcn_sdot4(static_cast<int>(a[0]), static_cast<int>(column), acc[4 * w + x], false);
+            }
+        }
+    } else {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        // two neighbouring elements of a row as fp32
+        auto pair = [](const uint32_t* w, int first) -> f32x2 {
+            const uint32_t word = w[first * Elem<DT>::ES / 4];
+            if constexpr (DT == kF16) {
+                typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+                const f16x2 h = __builtin_bit_cast(f16x2, word);
+                return f32x2{static_cast<float>(h[0]), static_cast<float>(h[1])};
+            } else if constexpr (DT == kBF16) {
+                return f32x2{__builtin_bit_cast(float, word << 16), __builtin_bit_cast(float, word & 0xFFFF0000u)};
+            } else if constexpr (DT == kE4M3) {
+                return first & 2 ? __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(word), true) : __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(word), false);
+            } else {
+                return first & 2 ? __builtin_amdgcn_cvt_pk_f32_bf8(static_cast<int>(word), true) : __builtin_amdgcn_cvt_pk_f32_bf8(static_cast<int>(word), false);
+            }
+        };
+#pragma unroll
+        for (int e = 0; e < kEntriesPerRecord; ++e) {
+            const float value = pair(a, e & ~1)[e & 1];
+#pragma unroll
+            for (int n = 0; n < NC; n += 2) {
+                const f32x2 columns = pair(b[e], n);
+                acc[n] = __builtin_fmaf(value, columns[0], acc[n]);
+                if (n + 1 < NC) acc[n + 1] = __builtin_fmaf(value, columns[1], acc[n + 1]);
+            }
+        }
+    }
+}
+
+template <int CTRL, typename T>
+__device__ __forceinline__ T entry_moved(T v)
+{
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float entry_sum(float a, float b) { return a + b; }
+__device__ __forceinline__ int32_t entry_sum(int32_t a, int32_t b) { return static_cast<int32_t>(static_cast<uint32_t>(a) + static_cast<uint32_t>(b)); }
+// Sums over the LPR lanes of a row, halving what a lane still sums up with every step: of two lanes one keeps the lower columns and the other the upper ones
+// (sixteen columns: 15 moves and additions instead of 64).  Returns the sum of column (lane % 16) / (16 / NC).
+template <int NC, int LPR, typename T>
+__device__ __forceinline__ T sum_of_lanes(T (&acc)[NC], int lane)
+{
+    auto step = [&](auto half_, auto move, int bit) {
+        constexpr int half = decltype(half_)::value;             // columns kept; 0: there is one left
+        if constexpr (half == 0) {
+            acc[0] = entry_sum(acc[0], move(acc[0]));
+        } else {
+            const bool upper = (lane & bit) != 0;
+#pragma unroll
+            for (int n = 0; n < half; ++n) {
+                const T keep = upper ? acc[n + half] : acc[n], give = upper ? acc[n] : acc[n + half];
+                acc[n] = entry_sum(keep, move(give));
+            }
+        }
+    };
+    step(std::integral_constant<int, NC / 2>{}, [](T v) { return entry_moved<0x140>(v); }, 8);       // 15 - lane of sixteen
+    step(std::integral_constant<int, NC / 4>{}, [](T v) { return entry_moved<0x141>(v); }, 4);       // 7 - lane of eight
+    step(std::integral_constant<int, NC / 8>{}, [](T v) { return entry_moved<0x1B>(v); }, 2);        // 3 - lane of four
+    step(std::integral_constant<int, NC / 16>{}, [](T v) { return entry_moved<0xB1>(v); }, 1);       // the other of two
+    if constexpr (LPR > 16) acc[0] = entry_sum(acc[0], __shfl_xor(acc[0], 16));
+    if constexpr (LPR > 32) acc[0] = entry_sum(acc[0], __shfl_xor(acc[0], 32));
+    return acc[0];
+}
+
+template <int DT, int NC, int LPR>
+__global__ __launch_bounds__(kEntryThreads)
+__attribute__((amdgpu_waves_per_eu(4 * entry_resident(NC * Elem<DT>::ES))))
+void spmm_entry_kernel(const uint32_t* __restrict__ row_at, const void* __restrict__ records, const void* __restrict__ B, uint32_t b_bytes,
+                       uint32_t ldb_bytes, uint32_t K, uint32_t M, int N, typename Elem<DT>::Out* __restrict__ C, int64_t ldc)
+{
+    using Out = typename Elem<DT>::Out;
+    constexpr int ES = Elem<DT>::ES, RB = NC * ES, ROWS = kEntryThreads / LPR, PF = 4;
+    using Record = EntryRecord<ES>;
+    extern __shared__ u32x4 lds_dyn[];
+    uint8_t* const rows_of_b = reinterpret_cast<uint8_t*>(lds_dyn);
+    const Record* const list = static_cast<const Record*>(records);
+    const int tid = static_cast<int>(threadIdx.x), j = tid % LPR;
+    const int col0 = static_cast<int>(blockIdx.y) * NC;
+    const uint32_t stride = gridDim.x * ROWS;
+
+    // the lane's first PF records of the row, asked for ahead of everything else
+    uint32_t row = blockIdx.x * ROWS + static_cast<uint32_t>(tid / LPR);
+    if constexpr (LPR == 64) row = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row)));
+    uint32_t at = 0, end = 0;
+    Record rec[PF];
+    auto load = [&](uint32_t from) {
+#pragma unroll
+        for (int h = 0; h < PF; ++h)
+            if (from + h * LPR < end) rec[h] = list[from + h * LPR];
+    };
+    if (row < M) {
+        at = row_at[row] + static_cast<uint32_t>(j);
+        end = row_at[row + 1];
+    }
+    load(at);
+
+    // B, a row per thread at a time, and a row of zeros (from a base on a dword: rows off the dwords are fetched as the dwords around them and shifted)
+    const uint32_t shift_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(B) & 3u);
+    const uint32_t bytes = b_bytes + shift_base;
+    const __amdgpu_buffer_rsrc_t b_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(static_cast<uint8_t*>(const_cast<void*>(B)) - shift_base, 0, static_cast<int>(bytes), kRsrcFlags);
+    // rows that lie next to each other as they do in LDS: sixteen bytes at a time, but for the last ones
+    uint32_t first_row = 0;
+    if (ldb_bytes == RB && shift_base == 0u) {
+        constexpr uint32_t kWhole = RB > 16 ? RB / 16 : 1;
+        constexpr int U = 4;
+        const uint32_t pieces = b_bytes / 16u / kWhole * kWhole;
+        first_row = pieces * 16u / RB;
+        for (uint32_t x0 = static_cast<uint32_t>(tid); x0 < pieces; x0 += U * kEntryThreads) {
+            u32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = buf_load16(b_rsrc, x0 + u * kEntryThreads < pieces ? 16u * (x0 + u * kEntryThreads) : kOutOfRange, 0u);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (x0 + u * kEntryThreads < pieces) *reinterpret_cast<u32x4*>(rows_of_b + 16u * (x0 + u * kEntryThreads)) = v[u];
+        }
+    }
+    if constexpr (RB >= 4) {
+        constexpr int RW = RB / 4, U = RW >= 4 ? 4 : 8;
+        const bool off_dwords = ((ldb_bytes | shift_base | static_cast<uint32_t>(col0) * ES) & 3u) != 0;
+        auto load_words = [&](uint32_t off, auto& p) {
+            if constexpr (RW == 1) {
+                p[0] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(b_rsrc, off, 0, 0));
+            } else if constexpr (RW == 2) {
+                const i32x2 q = __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, off, 0, 0);
+                p[0] = static_cast<uint32_t>(q[0]);
+                p[1] = static_cast<uint32_t>(q[1]);
+            } else {
+#pragma unroll
+                for (int w = 0; w < RW; w += 4) {
+                    const u32x4 q = buf_load16(b_rsrc, off + 4u * w, 0u);
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) p[w + y] = q[y];
+                }
+            }
+        };
+        for (uint32_t r0 = first_row + static_cast<uint32_t>(tid); r0 <= K; r0 += U * kEntryThreads) {
+            uint32_t v[U][RW];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t r = r0 + u * kEntryThreads;
+#pragma unroll
+                for (int w = 0; w < RW; ++w) v[u][w] = 0u;
+                if (r >= K) continue;
+                const uint32_t off = r * ldb_bytes + static_cast<uint32_t>(col0) * ES + shift_base;
+                if (off_dwords && (off & ~3u) + RB + 4u <= bytes) {
+                    uint32_t p[RW + 1];
+                    load_words(off & ~3u, p);
+                    p[RW] = static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b32(b_rsrc, (off & ~3u) + RB, 0, 0));
+#pragma unroll
+                    for (int w = 0; w < RW; ++w) v[u][w] = __builtin_amdgcn_alignbyte(p[w + 1], p[w], off & 3u);
+                } else if (!off_dwords && off + RB <= bytes) {
+                    load_words(off, v[u]);
+                } else {
+                    // the end of B: element by element
+#pragma unroll
+                    for (int e = 0; e < NC; ++e) {
+                        if (col0 + e >= N) continue;
+                        const uint32_t x = ES == 2 ? static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(b_rsrc, off + 2u * e, 0, 0))
+                                                   : static_cast<uint8_t>(__builtin_amdgcn_raw_buffer_load_b8(b_rsrc, off + e, 0, 0));
+                        v[u][ES * e / 4] |= x << (8 * (ES * e % 4));
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t r = r0 + u * kEntryThreads;
+                if (r > K) continue;
+                uint32_t* dst = reinterpret_cast<uint32_t*>(rows_of_b + static_cast<size_t>(r) * RB);
+                if constexpr (RW == 1) dst[0] = v[u][0];
+                else if constexpr (RW == 2) *reinterpret_cast<u32x2*>(dst) = u32x2{v[u][0], v[u][1]};
+                else {
+#pragma unroll
+                    for (int w = 0; w < RW; w += 4) *reinterpret_cast<u32x4*>(dst + w) = u32x4{v[u][w], v[u][w + 1], v[u][w + 2], v[u][w + 3]};
+                }
+            }
+        }
+    } else {
+        for (uint32_t r = first_row + static_cast<uint32_t>(tid); r <= K; r += kEntryThreads) {
+            const uint32_t off = r * ldb_bytes + static_cast<uint32_t>(col0) * ES + shift_base;
+            uint32_t v = 0u;
+#pragma unroll
+            for (int e = 0; e < NC; ++e) {
+                if (r >= K || col0 + e >= N) continue;
+                const uint32_t x = ES == 2 ? static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(b_rsrc, off + 2u * e, 0, 0))
+                                           : static_cast<uint8_t>(__builtin_amdgcn_raw_buffer_load_b8(b_rsrc, off + e, 0, 0));
+                v |= x << (8 * ES * e);
+            }
+            if constexpr (RB == 2) reinterpret_cast<uint16_t*>(rows_of_b)[r] = static_cast<uint16_t>(v);
+            else rows_of_b[r] = static_cast<uint8_t>(v);
+        }
+    }
+    __syncthreads();
+
+    auto multiply = [&](const Record& record, Out (&acc)[NC]) {
+        constexpr int RW = (RB + 3) / 4;
+        uint32_t b[kEntriesPerRecord][RW];
+#pragma unroll
+        for (int e = 0; e < kEntriesPerRecord; ++e) {
+            const uint32_t column = e & 1 ? record.w[e >> 1] >> 16 : record.w[e >> 1] & 0xFFFFu;
+            const uint8_t* src = rows_of_b + column * static_cast<uint32_t>(RB);
+            if constexpr (RB == 1) b[e][0] = *src;
+            else if constexpr (RB == 2) b[e][0] = *reinterpret_cast<const uint16_t*>(src);
+            else if constexpr (RB == 4) b[e][0] = *reinterpret_cast<const uint32_t*>(src);
+            else if constexpr (RB == 8) {
+                const u32x2 q = *reinterpret_cast<const u32x2*>(src);
+                b[e][0] = q[0];
+                b[e][1] = q[1];
+            } else {
+#pragma unroll
+                for (int w = 0; w < RW; w += 4) {
+                    const u32x4 q = *reinterpret_cast<const u32x4*>(src + 4 * w);
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) b[e][w + y] = q[y];
+                }
+            }
+        }
+        multiply_record<DT, NC>(record.w + 2, b, acc);
+    };
+
+    for (; row < M; row += stride) {
+        Out acc[NC];
+#pragma unroll
+        for (int n = 0; n < NC; ++n) acc[n] = 0;
+        for (; at < end; at += PF * LPR) {
+            Record now[PF];
+#pragma unroll
+            for (int h = 0; h < PF; ++h) now[h] = rec[h];
+            load(at + PF * LPR);
+#pragma unroll
+            for (int h = 0; h < PF; ++h)
+                if (at + h * LPR < end) multiply(now[h], acc);
+        }
+        const uint32_t done = row;
+        if (row + stride < M) {
+            at = row_at[row + stride] + static_cast<uint32_t>(j);
+            end = row_at[row + stride + 1];
+            load(at);
+        }
+        const Out sum = sum_of_lanes<NC, LPR>(acc, j);
+        constexpr int SAME = 16 / NC;                            // lanes with the same column
+        const int column = col0 + j / SAME;
+        if (j < 16 && j % SAME == 0 && column < N) C[static_cast<int64_t>(done) * ldc + column] = sum;
+    }
+}
+
+template <int DT, int NC, int LPR>
+static int launch_entry_shape(const EntryList& t, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N, int64_t workgroups, hipStream_t s)
+{
+    static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_entry_kernel<DT, NC, LPR>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kEntryLds));
+    if (ready != hipSuccess) return static_cast<int>(ready);
+    constexpr int ES = Elem<DT>::ES;
+    const dim3 grid(static_cast<unsigned>(workgroups), static_cast<unsigned>((N + NC - 1) / NC));
+    hipLaunchKernelGGL((spmm_entry_kernel<DT, NC, LPR>), grid, dim3(kEntryThreads), entry_lds(t.K, ES, NC), s, t.row_at, t.records, B,
+                       static_cast<uint32_t>(((t.K - 1) * ldb + N) * ES), static_cast<uint32_t>(ldb * ES), static_cast<uint32_t>(t.K),
+                       static_cast<uint32_t>(t.M), static_cast<int>(N), static_cast<typename Elem<DT>::Out*>(C), ldc);
+    return static_cast<int>(hipGetLastError());
+}
+
+template <int DT, int NC>
+static int launch_entry_columns(const EntryList& t, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N, hipStream_t s, const char** variant)
+{
+    const EntryLaunch launch = entry_launch(t.M, t.K, Elem<DT>::ES, NC, (N + NC - 1) / NC);
+    static thread_local char name[40];
+    const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
+    snprintf(name, sizeof(name), "spmm_%s_entries%dx%d", type, NC, launch.lanes);
+    *variant = name;
+    switch (launch.lanes) {
+    case 64: return launch_entry_shape<DT, NC, 64>(t, B, ldb, C, ldc, N, launch.workgroups, s);
+    case 32: return launch_entry_shape<DT, NC, 32>(t, B, ldb, C, ldc, N, launch.workgroups, s);
+    default: return launch_entry_shape<DT, NC, 16>(t, B, ldb, C, ldc, N, launch.workgroups, s);
+    }
+}
+
+template <int DT>
+static int launch_entry_dtype(const EntryList& t, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N, hipStream_t s, const char** variant)
+{
+    switch (entry_columns(t.K, Elem<DT>::ES, N)) {
+    case 1: return launch_entry_columns<DT, 1>(t, B, ldb, C, ldc, N, s, variant);
+    case 2: return launch_entry_columns<DT, 2>(t, B, ldb, C, ldc, N, s, variant);
+    case 4: return launch_entry_columns<DT, 4>(t, B, ldb, C, ldc, N, s, variant);
+    case 8: return launch_entry_columns<DT, 8>(t, B, ldb, C, ldc, N, s, variant);
+    case 16: return launch_entry_columns<DT, 16>(t, B, ldb, C, ldc, N, s, variant);
+    default: return static_cast<int>(hipErrorInvalidValue);
+    }
+}
+
+int launch_entries(const EntryList& t, int dtype, const void* B, int64_t ldb, void* C, int64_t ldc, int64_t N, void* stream, const char** variant)
+{
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (dtype) {
+    case kF16: return launch_entry_dtype<kF16>(t, B, ldb, C, ldc, N, s, variant);
+    case kBF16: return launch_entry_dtype<kBF16>(t, B, ldb, C, ldc, N, s, variant);
+    case kE4M3: return launch_entry_dtype<kE4M3>(t, B, ldb, C, ldc, N, s, variant);
+    case kE5M2: return launch_entry_dtype<kE5M2>(t, B, ldb, C, ldc, N, s, variant);
+    default: return launch_entry_dtype<kI8>(t, B, ldb, C, ldc, N, s, variant);
+    }
+}
+
+// Bind-time: sixteen threads per row, a record at a time.
+template <int ES>
+__global__ __launch_bounds__(256)
+void entry_fill_kernel(uint32_t M, uint32_t K, const uint32_t* __restrict__ row_at, const int64_t* __restrict__ csr_row_ptr,
+                       const int32_t* __restrict__ csr_col_idx, const uint16_t* __restrict__ csr_vals, EntryRecord<ES>* __restrict__ out)
+{
+    const uint32_t row = blockIdx.x * 16u + threadIdx.x / 16u;
+    if (row >= M) return;
+    const int64_t p0 = csr_row_ptr[row], p1 = csr_row_ptr[row + 1];
+    const uint32_t first = row_at[row], n = row_at[row + 1] - first;
+    for (uint32_t x = threadIdx.x % 16u; x < n; x += 16u) {
+        EntryRecord<ES> record{};
+#pragma unroll
+        for (int e = 0; e < kEntriesPerRecord; ++e) {
+            const int64_t p = p0 + kEntriesPerRecord * static_cast<int64_t>(x) + e;
+            const uint32_t column = p < p1 ? static_cast<uint32_t>(csr_col_idx[p]) : K, value = p < p1 ? csr_vals[p] : 0u;
+            record.w[e >> 1] |= column << (16 * (e & 1));
+            if constexpr (ES == 2) record.w[2 + (e >> 1)] |= value << (16 * (e & 1));
+            else record.w[2] |= (value & 0xFFu) << (8 * e);
+        }
+        out[first + x] = record;
+    }
+}
+
+int launch_entry_fill(const EntryList& t, int elem_bytes, const int64_t* csr_row_ptr, const int32_t* csr_col_idx, const uint16_t* csr_vals, void* stream)
+{
+    if (t.M == 0) return 0;
+    const dim3 grid(static_cast<unsigned>((t.M + 15) / 16));
+    auto fill = [&](auto kernel, auto* records) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream), static_cast<uint32_t>(t.M), static_cast<uint32_t>(t.K), t.row_at,
+                           csr_row_ptr, csr_col_idx, csr_vals, records);
+    };
+    if (elem_bytes == 2) fill(entry_fill_kernel<2>, static_cast<EntryRecord<2>*>(const_cast<void*>(t.records)));
+    else fill(entry_fill_kernel<1>, static_cast<EntryRecord<1>*>(const_cast<void*>(t.records)));
+    return static_cast<int>(hipGetLastError());
+}
+
+}  // namespace smat

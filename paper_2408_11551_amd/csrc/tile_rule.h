@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <limits>
 
+#include "entry_layout.h"
 #include "kernels.h"
 #include "quad_layout.h"
 
@@ -20,6 +21,7 @@ struct RuleMatrix {
     int64_t columns = 0;                 // of them what tiles would take in their place
     int64_t tiled_steps = 0;             // quad steps of the super rows, without those of quad_tail
     int64_t rest_packs = -1;             // packs of the longest block row outside the super rows; -1: there is none
+    int64_t entry_records = 0;           // of the entry list (entry_layout.h); 0: there is none
 };
 // ... and of a product.
 struct RuleProduct {
@@ -53,6 +55,35 @@ inline FewColumns few_columns(const RuleMatrix& m, const DenseTiles& t, const Ru
                             a_mb * passes / (a_mb > 30.0 ? 6.0 : 25.0) + (p.off_dwords() ? 0.7 : 0.0) +
                             (m.rest_packs >= 0 && !t.quad_tail ? 5.0 : 0.0);      // a launch for the other block rows
     return {quads_us, rows_us};
+}
+
+// Does the entry list (kernels_entries.hip) take N columns?  All of them in one pass, that is: with two, 16-bit types lose up to a fifth.  Estimates in us again: a start, B into
+// LDS once per workgroup that a compute unit has, the stream of records, and their multiplications, so many waves of records one after the other.  Fitted on 2498 random products (800 ... 30 000 rows,
+// 600 ... 20 000 columns, 2-30 % fill, N = 1 ... 32, all types): within 9 % (rms) where the list and the others are close.
+// Against the block rows (their estimate, above, over all of them) it takes 468 of 1251 products, which then take 0.7 of the time, 8 are more than 3 % slower, the worst 0.83; against quads of
+// more than 20.5 MB 215 of 301, 0.65 of the time, 2 more than 3 % slower, 0.87.  (The estimate for quads is 15 % low on those.)  Smaller quads stay where they are, though most of
+// them, too, are up to 2 us faster on the list (0.85 of the time): their launches and counted operations are what callers have been told (smat_last_launches).
+inline double entries_us(const RuleMatrix& m, const RuleProduct& p)
+{
+    const int64_t columns = entry_columns(m.K, m.es, p.N);
+    if (m.entry_records == 0 || columns < p.N) return std::numeric_limits<double>::infinity();
+    const EntryLaunch launch = entry_launch(m.M, m.K, m.es, columns, 1);
+    const double in_a_unit = std::ceil(static_cast<double>(launch.workgroups) / 256.0), per_row = static_cast<double>(m.entry_records) / static_cast<double>(m.M);
+    const double rounds = std::ceil(static_cast<double>(m.M * launch.lanes) / kEntryThreads / static_cast<double>(launch.workgroups));
+    const double product = m.dtype == 4 ? 1.80e-3 : m.es == 1 ? 2.77e-3 : 2.61e-3;
+    return 4.1 + 0.636e-5 * in_a_unit * static_cast<double>(entry_lds(m.K, m.es, columns)) + (p.off_dwords() ? 0.523e-4 * in_a_unit * static_cast<double>(m.K) : 0.0) +
+           0.111e-6 * static_cast<double>(m.entry_records * entry_record_bytes(m.es)) +
+           in_a_unit * rounds * std::ceil(per_row / launch.lanes) * 16.0 * product * static_cast<double>(columns);
+}
+inline bool entries_pay(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
+{
+    const double us = entries_us(m, p);
+    const FewColumns few = few_columns(m, t, p);
+    const double quads_mb = static_cast<double>(t.n_quad_steps) * (m.es == 1 ? 20480e-6 : 18432e-6);
+    if (few.take()) return quads_mb > 20.5 && 0.93 * us < few.quads_us;
+    const double b_rows = static_cast<double>(m.b_rows), per_column = m.es == 1 ? 4.2e-6 : b_rows * 36.0 > 26.0e6 ? 6.0e-6 : 4.6e-6;
+    const double rows_us = 3.5 + (p.off_dwords() && p.N * m.es > 16 ? 1.3 : 1.0) * std::max(1.0e-3 * b_rows / static_cast<double>(m.nbr), per_column * b_rows);
+    return 1.05 * us < rows_us;
 }
 
 // What a product of N columns takes on tiles of a shape on quads, in us: a start, the steps of the fullest compute unit's tiles one after the
