@@ -82,6 +82,19 @@ def test_per_row_kernel_on_a_copy_of_b(shape, oracle_c):
         assert S.smat_last_launches()[0] == "+".join(["copy_b+rows"] * (2 if N == 1400 else 1))
 
 
+@pytest.mark.parametrize("shape", [(6000, 2000, 359, 0.02, "i8", 1), (6000, 2000, 101, 0.02, "i8", 0), (8000, 6000, 501, 0.01, "e4m3", 1), (8000, 6000, 501, 0.01, "e5m2", 1),
+                                   (6000, 2500, 201, 0.02, "f16", 1), (8000, 12000, 193, 0.004, "bf16", 1), (8000, 12000, 63, 0.004, "bf16", 0)],
+                         ids=lambda s: "x".join(map(str, s[:5])))
+def test_per_row_kernel_on_a_copy_of_b_off_the_dwords(shape, oracle_c):
+    """Either side of the line from which rows of B off the dwords are copied, by the two kernels that take them otherwise."""
+    M, K, N, density, dtype, copied = shape
+    w = random_csr(M, K, N, density, seed=N, values="smallint", b_dist="smallint")
+    w = w if dtype == "f16" else recast(w, dtype)
+    for ldb, ldc, shift in ((N, N, 0), (N + 2, N + 2, 1)):
+        _exact(w, oracle_c, ldb, ldc, shift)
+        assert S.smat_last_launches()[0] == ("copy_b+rows" if copied else "rows")
+
+
 # columns dealt into quads (kernels_quads.hip): fills that give full quads, quads with gaps (20, 25 %), an incomplete last super row, a
 # ragged last step, steps split over workgroups
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3", "e5m2", "i8"])
