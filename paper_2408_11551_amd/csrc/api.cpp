@@ -1222,6 +1222,8 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         tiles.quad_shape = best.shape;
         tiles.quad_tail_tiled = best.tail;
     }
+    // (with the static area, which has its limit, as before)
+    if (use_tiles && h->dense_mode == 0 && !hard_limit && chunk >= N) tiles.quad_parts = smat::quad_parts(rule, tiles, N);
     const char* variant = "";
     thread_local std::string name;
     int e = 0;

@@ -72,7 +72,8 @@ struct DenseTiles {
     int32_t quad_tail = 0;                 // 1: super row number n is there too (for launch_quad_rows, and for the tiles with quad_tail_tiled), and then all block rows are
     int32_t quad_tail_rows = 0;            // its block rows: all sixteen, too, where it is only too sparse to be one of the n
     // of a call
-    int quad_shape = 0;                    // QuadShape; only the first one's steps may be split over workgroups
+    int quad_shape = 0;                    // QuadShape
+    int quad_parts = 1;                    // of 128 x 32: workgroups that share a tile's steps (256 x 128: dense_even_parts)
     bool quad_tail_tiled = false;          // the tiles cover super row number n too
 };
 

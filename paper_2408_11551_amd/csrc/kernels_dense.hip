@@ -447,35 +447,36 @@ int launch_dense_fill(const DeviceBcsr& d, const DenseTiles& t, const int64_t* c
     return static_cast<int>(hipGetLastError());
 }
 
-// Adds the ks partial tiles of every (super row, 128-column slab) in the order 0 .. ks-1 and
-// writes the rows to C.  Eight workgroups per tile (32 rows each); a thread sums four groups of
-// four columns and has all its loads in flight at once.
+// Adds the ks partial tiles of every tile (TR x TC) in the order 0 .. ks-1 and
+// writes the rows to C.  A thread sums J groups of four columns and has all its loads in flight at once: four with 256 x 128, eight workgroups per
+// tile; one with 128 x 32, four workgroups, as there are at most 128 of those.
 // V is the vector of four elements of C: f32x4, or i32x4 for the integer type.
-template <typename V, typename Out>
+template <typename V, typename Out, int TR, int TC, int J>
 __global__ __launch_bounds__(256)
 void dense_reduce_kernel(DeviceBcsr d, DenseTiles t, int ks, Out* __restrict__ C, int64_t ldc, int N, int vec_store)
 {
-    const int super = t.super_rows[blockIdx.x];
-    const int n0 = blockIdx.y * 128;
+    constexpr int PARTS = 256 / TR;                // tiles per super row and slab
+    const int super = t.super_rows[blockIdx.x / PARTS], first = TR * static_cast<int>(blockIdx.x % PARTS);
+    const int n0 = blockIdx.y * TC;
     const size_t tile = static_cast<size_t>(blockIdx.x) * gridDim.y + blockIdx.y;
-    const Out* part = static_cast<const Out*>(t.scratch) + tile * ks * (256 * 128);
-    V v[4];
+    const Out* part = static_cast<const Out*>(t.scratch) + tile * ks * (TR * TC);
+    V v[J];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = static_cast<int>(blockIdx.z) * 1024 + j * 256 + static_cast<int>(threadIdx.x);
+    for (int j = 0; j < J; ++j) {
+        const int e = static_cast<int>(blockIdx.z) * (256 * J) + j * 256 + static_cast<int>(threadIdx.x);
         v[j] = *reinterpret_cast<const V*>(part + e * 4);
     }
     for (int z = 1; z < ks; ++z)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = static_cast<int>(blockIdx.z) * 1024 + j * 256 + static_cast<int>(threadIdx.x);
-            v[j] += *reinterpret_cast<const V*>(part + static_cast<size_t>(z) * (256 * 128) + e * 4);
+        for (int j = 0; j < J; ++j) {
+            const int e = static_cast<int>(blockIdx.z) * (256 * J) + j * 256 + static_cast<int>(threadIdx.x);
+            v[j] += *reinterpret_cast<const V*>(part + static_cast<size_t>(z) * (TR * TC) + e * 4);
         }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = static_cast<int>(blockIdx.z) * 1024 + j * 256 + static_cast<int>(threadIdx.x);
-        const int row = e >> 5, c = (e & 31) * 4;
-        const int64_t out_row = d.perm[static_cast<int64_t>(super) * 256 + row];
+    for (int j = 0; j < J; ++j) {
+        const int e = static_cast<int>(blockIdx.z) * (256 * J) + j * 256 + static_cast<int>(threadIdx.x);
+        const int row = e / (TC / 4), c = e % (TC / 4) * 4;
+        const int64_t out_row = d.perm[static_cast<int64_t>(super) * 256 + first + row];
         if (out_row < 0 || n0 + c >= N) continue;
         Out* dst = C + out_row * ldc + n0 + c;
         if (vec_store) {                                      // N is a multiple of 4
@@ -486,6 +487,13 @@ void dense_reduce_kernel(DeviceBcsr d, DenseTiles t, int ks, Out* __restrict__ C
                 if (n0 + c + x < N) dst[x] = v[j][x];
         }
     }
+}
+
+template <typename V, typename Out, int TR, int TC, int J>
+static void launch_reduce(const DeviceBcsr& d, const DenseTiles& t, int64_t row_tiles, int ks, void* C, int64_t ldc, int64_t N, int vec_store, hipStream_t s)
+{
+    hipLaunchKernelGGL((dense_reduce_kernel<V, Out, TR, TC, J>), dim3(static_cast<unsigned>(row_tiles), static_cast<unsigned>((N + TC - 1) / TC), TR * TC / (1024 * J)),
+                       dim3(256), 0, s, d, t, ks, static_cast<Out*>(C), ldc, static_cast<int>(N), vec_store);
 }
 
 // An area for partial tiles that belongs to the library, not to a workspace: a file-scope device
@@ -577,7 +585,7 @@ int launch_stage_b(const void* B, int64_t ldb, int64_t K, int64_t cols, int elem
 // How many workgroups share the steps of a 128-column tile: as many as fit the 256 compute
 // units in one round, as long as each keeps at least eight steps and the partial tiles fit the
 // scratch area.
-int dense_split(const DenseTiles& t, int64_t N) { return dense_even_parts(t, N); }
+int dense_split(const DenseTiles& t, int64_t N) { return t.quad_shape == kQuad128x32 ? t.quad_parts : dense_even_parts(t, N); }
 
 template <int DT>
 static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const void* B, int64_t ldb, void* C, int64_t ldc,
@@ -592,16 +600,18 @@ static int launch_dense_dtype(const DeviceBcsr& d, const DenseTiles& t, const vo
     const int ks = dense_split(t, N);
     static thread_local char name[40];
     const char* type = DT == kF16 ? "f16" : DT == kBF16 ? "bf16" : DT == kE4M3 ? "e4m3" : DT == kE5M2 ? "e5m2" : "i8";
-    if (shape != kQuad256x128) snprintf(name, sizeof(name), "spmm_dense_%s_g%d_%dx%d", type, quad_shape_groups(shape), quad_shape_rows(shape), quad_shape_columns(shape));
+    if (shape != kQuad256x128 && ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d_%dx%d", type, quad_shape_groups(shape), ks, quad_shape_rows(shape), quad_shape_columns(shape));
+    else if (shape != kQuad256x128) snprintf(name, sizeof(name), "spmm_dense_%s_g%d_%dx%d", type, quad_shape_groups(shape), quad_shape_rows(shape), quad_shape_columns(shape));
     else if (ks > 1) snprintf(name, sizeof(name), "spmm_dense_%s_g%dk%d", type, deep ? 2 : 1, ks);
     else snprintf(name, sizeof(name), "spmm_dense_%s_g%d", type, deep ? 2 : 1);
     *variant = name;
     if (t.n_quad_steps > 0) launch_quad_tiles(d, t, DT, ks, B, ldb, C, ldc, N, s);
     else if (deep) launch_tile<DT, 2>(d, t, ks, B, ldb, C, ldc, N, s);
     else launch_tile<DT, 1>(d, t, ks, B, ldb, C, ldc, N, s);
-    if (ks > 1)
-        hipLaunchKernelGGL((dense_reduce_kernel<Acc, Out>), dim3(static_cast<unsigned>(t.n), static_cast<unsigned>((N + 127) / 128), 8),
-                           dim3(256), 0, s, d, t, ks, static_cast<Out*>(C), ldc, static_cast<int>(N), vec_store);
+    if (ks > 1) {
+        if (shape == kQuad128x32) launch_reduce<Acc, Out, 128, 32, 1>(d, t, quad_row_tiles(t), ks, C, ldc, N, vec_store, s);
+        else launch_reduce<Acc, Out, 256, 128, 4>(d, t, t.n, ks, C, ldc, N, vec_store, s);
+    }
     return static_cast<int>(hipGetLastError());
 }
 

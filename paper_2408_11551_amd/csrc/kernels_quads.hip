@@ -404,7 +404,7 @@ void spmm_quad_tile_kernel(int n_row_tiles, int n_slab, int per_xcd, int N, cons
 #pragma unroll
             for (int y = 0; y < 4; ++y) out_rows[r][y] = tab.perm[(static_cast<int64_t>(super) * 16 + j0 + r) * 16 + 4 * g + y];
     }
-    finish_tile<DT, KG, RM, NT>(acc, out_rows, lds_words, kg, wave, lane, super, j0, sidx, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
+    finish_tile<DT, KG, RM, NT>(acc, out_rows, lds_words, kg, wave, lane, super, j0, PARTS * sidx + part, slab, n_slab, ks, tab.perm, tab.scratch, C, ldc, N);
 }
 
 template <int DT, int NT, int RM, int KG = 2>
@@ -435,7 +435,7 @@ static void launch_quad_dtype(const DeviceBcsr& d, const DenseTiles& t, int ks, 
     case kQuad256x96: return launch_quad_shape<DT, 6, 4>(d, t, 1, B, ldb, C, ldc, N, s);
     case kQuad256x64: return launch_quad_shape<DT, 4, 4>(d, t, 1, B, ldb, C, ldc, N, s);
     case kQuad128x64: return launch_quad_shape<DT, 4, 2>(d, t, 1, B, ldb, C, ldc, N, s);
-    case kQuad128x32: return launch_quad_shape<DT, 2, 2>(d, t, 1, B, ldb, C, ldc, N, s);
+    case kQuad128x32: return launch_quad_shape<DT, 2, 2>(d, t, ks, B, ldb, C, ldc, N, s);
     default: return launch_quad_shape<DT, 8, 4>(d, t, ks, B, ldb, C, ldc, N, s);
     }
 }

@@ -97,12 +97,16 @@ __device__ __forceinline__ void lds_pair_done(u32x2_t& lo, u32x2_t& hi)
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(YOUNGER));
 }
 
+// Tiles whose steps may be split over workgroups: 256 x 128, and 128 x 32 on quads.
+constexpr bool can_split_steps(int rm, int nt) { return rm == 4 ? nt == 8 : nt == 2; }
+
 // The end of a tile of 16 NT columns: acc[r][x][y] = C'[16 * (16 super + first_row + r) + 4g + y][16 (NT slab + x) + i] of this wave (and, with two
-// groups, the same of the other group's steps).  With ks > 1 workgroups per tile (256 x 128) the partial tile goes to the scratch area.
+// groups, the same of the other group's steps).  With ks > 1 workgroups per tile the partial tile goes to the scratch area; row_tile: the tile's number
+// among those of its slab.
 // lds_words: 4 RM NT KiB with two groups, not used with one.  out_rows: read here with two groups, by the caller with one.
 template <int DT, int KG, int RM = 4, int NT = 8>
 __device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_in)[RM][NT], const int32_t (&out_rows_in)[RM][4], u32x4* lds_words, int kg,
-                                            int wave, int lane, int super, int first_row, int sidx, int slab, int n_slab, int ks,
+                                            int wave, int lane, int super, int first_row, int row_tile, int slab, int n_slab, int ks,
                                             const int32_t* __restrict__ perm, void* scratch, typename Elem<DT>::Out* __restrict__ C,
                                             int64_t ldc, int N)
 {
@@ -140,13 +144,13 @@ __device__ __forceinline__ void finish_tile(const typename Elem<DT>::Acc (&acc_i
         }
     }
     auto store_block_row = [&](int r) {
-        if (RM == 4 && NT == 8 && ks > 1) {
-            // partial tile, row-major 256 x 128 words, at [(tile * ks + z)]
-            const size_t tile_at = static_cast<size_t>(sidx) * n_slab + slab;
-            Out* part = static_cast<Out*>(scratch) + (tile_at * ks + blockIdx.z) * (256 * 128);
+        if (can_split_steps(RM, NT) && ks > 1) {
+            // partial tile, row-major 64 RM x 16 NT words, at [(tile * ks + z)]
+            const size_t tile_at = static_cast<size_t>(row_tile) * n_slab + slab;
+            Out* part = static_cast<Out*>(scratch) + (tile_at * ks + blockIdx.z) * (64 * RM * 16 * NT);
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
-                Out* dst = part + (16 * (first_row + r) + 4 * g + y) * 128 + i;
+                Out* dst = part + (16 * (first_row % (4 * RM) + r) + 4 * g + y) * (16 * NT) + i;
 #pragma unroll
                 for (int x = 0; x < NT; ++x) dst[16 * x] = acc[r][x][y];
             }

@@ -197,8 +197,8 @@ inline TileChoice cheapest_tiles(const RuleMatrix& m, DenseTiles t, const RulePr
 }
 
 // The shape to take.  Narrow or low tiles where those of 256 x 128 are too few for 256 compute units, or a few more than
-// a multiple of them.  (The steps of few tiles used to be split over workgroups instead, whose partial tiles go out and in again:
-// 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.)  The
+// a multiple of them.  (The steps of few tiles of 256 x 128 used to be split over workgroups instead, whose partial tiles go out and in again:
+// 3762 x 3966 at 10 % in fp16, N = 256 22.4 -> 16.9 us, N = 512 24.7 -> 20.2; 7286 x 2652 at 20 % in int8, N = 256 21.9 -> 10.4.  Where those of 128 x 32 are few, too, quad_parts splits them.)  The
 // last super row of quad_tail gets tiles like the others where that pays.
 inline TileChoice best_tiles(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p)
 {
@@ -235,6 +235,29 @@ inline bool coarse_estimates_take_tiles(const RuleMatrix& m, const DenseTiles& t
                c.write * static_cast<double>(m.M) * static_cast<double>(p.N) * 4e-6;
     };
     return 1.08 * tiles.us + 0.5 <= std::max(rows(p.distance), rows(p.starts));
+}
+
+// Into how many parts to split the steps of every tile of 128 x 32, the shape of products with too few tiles for 256 compute units.  A tile of a long super row is a chain of
+// steps, and up to 128 of them leave half the chip or more idle: what that saves, us per step, against a launch that adds the parts and the partial tiles' way out and in.
+// As many as give no compute unit two workgroups (an XCD has an eighth of the tiles, rounded up, and 32 units).  Fitted on half of 3558 such products (1000 ... 6000 rows, 5-20 % fill, N = 33 ...
+// 1500, all types), rms 0.5 - 0.8 us; of the other half it splits 516, which take 0.81 of the time, six of them are more than 5 % slower, the worst 1.18, and all are 0.9 % behind the best
+// number of parts, 7 % before.  us before and now: 1103 x 8120 at 10 % in e5m2, N = 234 24.7 and 17.9; 1247 x 6030 at 20 % in fp16, N = 286 27.8 and 22.0; 4556 x 3816 at 10 %, N = 48 13.5 and 10.8;
+// of less than 45 steps or with more than 128 tiles (two to a unit, or in no fewer rounds) it seldom pays: 2055 x 2489 in bf16, N = 160, 37 steps 9.9 and 10.1; 1573 x 5747, N = 400, 169 tiles 21.7 and 24.1.
+inline int quad_parts(const RuleMatrix& m, const DenseTiles& t, int64_t N)
+{
+    static constexpr double kStep[4] = {0.180, 0.252, 0.264, 0.261};        // fp16 and bf16, e4m3, e5m2, int8
+    if (t.n_quad_steps == 0 || t.quad_shape != kQuad128x32 || t.scratch == nullptr) return 1;
+    const int64_t n_tiles = quad_row_tiles(t) * ((N + 31) / 32), tile_bytes = 128 * 32 * 4;
+    const double steps = static_cast<double>(t.n_quad_steps) / (t.n + (t.quad_tail ? 1 : 0));
+    int parts = 1;
+    double most = 0.4;
+    for (int64_t ks = 2; ks <= 8 && (n_tiles + 7) / 8 * ks <= 32 && static_cast<size_t>(n_tiles * ks * tile_bytes) <= t.scratch_bytes; ++ks) {
+        const double saved = kStep[m.es == 2 ? 0 : m.dtype - 1] * steps * (1.0 - 1.0 / static_cast<double>(ks)) - 2.3 - 0.57e-6 * static_cast<double>(n_tiles * ks * tile_bytes);
+        if (saved <= most) continue;
+        most = saved;
+        parts = static_cast<int>(ks);
+    }
+    return parts;
 }
 
 // Are these tiles faster than rows and the kernel for few columns?
