@@ -260,6 +260,25 @@ inline int quad_parts(const RuleMatrix& m, const DenseTiles& t, int64_t N)
     return parts;
 }
 
+// A product that the estimates above send to rows: is it faster on tiles of 128 x 32 with split steps?  These have an estimate of their own -- a start with the second launch, the steps of a
+// part, the partial tiles, the copy of B -- fitted on 2494 such products (1000 ... 6000 rows, 5-20 % fill, N = 33 ... 1500): within 5-6 % (rms).  Rows are priced up to 8 % too dear there, so
+// it has to be better by 15 %: of 3120 products that ran on rows it takes 428, which then take 0.84 of the time; 18 are more than 5 % slower, the worst 1.16.
+inline bool split_tiles_pay(const RuleMatrix& m, DenseTiles t, const RuleProduct& p)
+{
+    struct Cost { double start, step, write, copy, copy_mb; };
+    static constexpr Cost kCosts[2] = {{6.1, 0.172, 0.653, 2.7, 0.865}, {7.0, 0.223, 0.313, 2.9, 1.41}};        // 16-bit types, 8-bit types
+    if (p.N <= 32 || p.chunk < p.N) return false;
+    t.quad_shape = kQuad128x32;
+    t.quad_tail_tiled = t.quad_tail != 0;
+    const int parts = quad_parts(m, t, p.N);
+    if (parts == 1) return false;
+    const Cost& c = kCosts[m.es == 2 ? 0 : 1];
+    const double steps = static_cast<double>(t.n_quad_steps) / (t.n + (t.quad_tail ? 1 : 0));
+    const double partial_mb = static_cast<double>(quad_row_tiles(t) * ((p.N + 31) / 32) * parts) * (128 * 32 * 4e-6);
+    const double us = c.start + c.step * steps / parts + c.write * partial_mb + (p.in_pieces ? 0.0 : c.copy + c.copy_mb * 1e-6 * static_cast<double>(m.K) * static_cast<double>(p.N * m.es));
+    return 1.15 * us + 0.5 <= rows_us(m, p);
+}
+
 // Are these tiles faster than rows and the kernel for few columns?
 inline bool tiles_pay(const RuleMatrix& m, const DenseTiles& t, const RuleProduct& p, const TileChoice& tiles)
 {
