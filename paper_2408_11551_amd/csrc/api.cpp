@@ -1183,7 +1183,7 @@ smat_status_t spmm_with_scratch(const smat_handle_t* h, const void* dB, int64_t 
         tiles.quad_shape = best.shape;
         tiles.quad_tail_tiled = best.tail;
         use_tiles = smat::tiles_pay(rule, tiles, product, best);
-        if (!use_tiles && smat::split_tiles_pay(rule, tiles, product)) {
+        if (use_tiles ? smat::split_smaller(rule, tiles, product) : smat::split_tiles_pay(rule, tiles, product)) {
             use_tiles = true;
             tiles.quad_shape = smat::kQuad128x32;
             tiles.quad_tail_tiled = tiles.quad_tail != 0;

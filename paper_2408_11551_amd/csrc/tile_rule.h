@@ -260,6 +260,19 @@ inline int quad_parts(const RuleMatrix& m, const DenseTiles& t, int64_t N)
     return parts;
 }
 
+// Tiles of 256 x 128 whose steps are split are slower than those of 128 x 32 with theirs: 212 of 212 products, which take 0.75 of the time (1002 x 7825 at 20 % in fp16, N = 96 19.9 and 13.4 us).  But a
+// sum in fp32 is the less exact the fewer parts it is added in (4016 x 7258 at 20 % in fp16, N = 80: eight parts 1.21e-7, two 2.05e-7 of the result), so the 16-bit types leave them only
+// for as many; int8 is exact, and what the 8-bit floats lose they lose inside an instruction.
+inline bool split_smaller(const RuleMatrix& m, DenseTiles t, const RuleProduct& p)
+{
+    const int parts_now = dense_even_parts(t, p.N);
+    if (t.quad_shape != kQuad256x128 || parts_now == 1 || p.chunk < p.N) return false;
+    t.quad_shape = kQuad128x32;
+    t.quad_tail_tiled = t.quad_tail != 0;
+    const int parts = quad_parts(m, t, p.N);
+    return parts > 1 && (m.es == 1 || parts >= parts_now);
+}
+
 // A product that the estimates above send to rows: is it faster on tiles of 128 x 32 with split steps?  These have an estimate of their own -- a start with the second launch, the steps of a
 // part, the partial tiles, the copy of B -- fitted on 2494 such products (1000 ... 6000 rows, 5-20 % fill, N = 33 ... 1500): within 5-6 % (rms).  Rows are priced up to 8 % too dear there, so
 // it has to be better by 15 %: of 3120 products that ran on rows it takes 428, which then take 0.84 of the time; 18 are more than 5 % slower, the worst 1.16.
@@ -275,7 +288,8 @@ inline bool split_tiles_pay(const RuleMatrix& m, DenseTiles t, const RuleProduct
     const Cost& c = kCosts[m.es == 2 ? 0 : 1];
     const double steps = static_cast<double>(t.n_quad_steps) / (t.n + (t.quad_tail ? 1 : 0));
     const double partial_mb = static_cast<double>(quad_row_tiles(t) * ((p.N + 31) / 32) * parts) * (128 * 32 * 4e-6);
-    const double us = c.start + c.step * steps / parts + c.write * partial_mb + (p.in_pieces ? 0.0 : c.copy + c.copy_mb * 1e-6 * static_cast<double>(m.K) * static_cast<double>(p.N * m.es));
+    const double us = c.start + c.step * steps / parts + c.write * partial_mb + (p.in_pieces ? 0.0 : c.copy + c.copy_mb * 1e-6 * static_cast<double>(m.K) * static_cast<double>(p.N * m.es)) +
+                      (m.rest_packs >= 0 && !t.quad_tail ? 3.0 + 0.09 * static_cast<double>(m.rest_packs) : 0.0);        // (block rows in a launch of their own)
     return 1.15 * us + 0.5 <= rows_us(m, p);
 }
 
